@@ -77,7 +77,7 @@ def draw(rng):
     n, m = (512 * max(2, min(28, _log(rng, 2, 28))) for _ in range(2))
     # tokens so that no drawn pass does more than the largest listed one of its sort
     if rng.random() < 0.5:   # whole sequences
-        tokens = min(256 * _log(rng, 1, 64), 29 * 16384 * 4096 * 14336 // (100 * n * m) // 256 * 256)
+        tokens = min(256 * _log(rng, 1, 64), 27 * 16384 * 4096 * 14336 // (100 * n * m) // 256 * 256)
     else:                    # whatever a batch happens to hold
         tokens = min(_log(rng, 8, 6000), 4090 * 8192 * 3072 // (n * m))
     return dict(kind=rng.choice(("step", "fwd", "bwd")), n=n, m=m, b=b, k=rng.choice((4, 5)), tokens=tokens, dtype="bf16",

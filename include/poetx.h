@@ -45,17 +45,17 @@
  *    reports, 256-byte aligned.
  *  - Alignment: bf16 tensors, block storage and workspaces should be 16-byte aligned
  *    with leading dimensions that are multiples of 8 elements (what any device
- *    allocator gives).  The matrix-core kernels move 16 bytes per lane; a call
- *    whose pointers are not so aligned runs on the plain fp32-FMA kernels.
- *  - Which kernels serve a shape: the matrix-core kernels cover bf16 tensors with
- *    b = 256 or 512 dividing d_in and d_out, dimensions that are multiples of 256
+ *    allocator gives).  The streaming kernels move 16 aligned bytes per lane; a call
+ *    whose pointers are not so aligned runs on the edge-handling kernels.
+ *  - Which kernels serve a shape: the streaming matrix-core kernels cover bf16 tensors
+ *    with b = 256 or 512 dividing d_in and d_out, dimensions that are multiples of 256
  *    and token counts that are multiples of 256, and, for fp32 tensors, the two dense
- *    products when all three dimensions are multiples of 128 (fp32 MFMA); everything
- *    else (the structured stages and the series of fp32 tensors, small blocks, ragged
- *    tails) runs on plain fp32-FMA kernels, correct but one to two orders of magnitude
- *    slower at large sizes.  poetx_linear_path reports the
- *    choice for a descriptor, so a caller can refuse shapes that would fall off
- *    the fast path instead of finding out from the clock.
+ *    products when all three dimensions are multiples of 128 (fp32 MFMA).  The dense
+ *    products, the structured applies and the block gradients of everything else (small
+ *    blocks, ragged tails, any token count, fp32 tensors) run on an edge-handling
+ *    matrix-core product of the tensors' type; the series of fp32 tensors and of small
+ *    blocks and poetx_perm_blockdiag_apply_right run on plain fp32-FMA kernels.
+ *    poetx_linear_path reports which stages of a descriptor the streaming kernels take.
  *  - Output buffers must not overlap input buffers (in-place operation is refused:
  *    the kernels of one call read rows that other workgroups of the same call write).
  *  - Return value: POETX_OK (0) or a poetx_status error.  Arguments are checked
@@ -277,9 +277,9 @@ int poetx_perm_validate(const int32_t* perm, int32_t d, int32_t* scratch, void* 
  */
 size_t poetx_linear_workspace_bytes(const poetx_linear_desc* desc);
 
-/* Which kernel families would serve `desc` (bit set = matrix cores; 16-byte aligned pointers
- * assumed).  Returns a combination of POETX_PATH_* bits, 0 when every stage runs on the plain
- * fp32-FMA kernels, or minus a poetx_status when the descriptor is invalid. */
+/* Which stages of `desc` the streaming matrix-core kernels take (bit set; 16-byte aligned pointers
+ * assumed).  Returns a combination of POETX_PATH_* bits, 0 when every stage runs on the edge-handling
+ * or plain kernels, or minus a poetx_status when the descriptor is invalid. */
 #define POETX_PATH_APPLY 1              /* gather + block-diagonal product + scatter            */
 #define POETX_PATH_DENSE 2              /* B = W A, dA = W^T dB (the only bit fp32 tensors get) */
 #define POETX_PATH_BLOCKGRAD 4          /* block gradients (two-call backward)                 */

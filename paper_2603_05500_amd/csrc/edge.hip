@@ -1,0 +1,203 @@
+// The dense product, the structured apply and the block gradient for every shape the streaming kernels do
+// not take (small blocks, ragged tails, token counts and alignments of any kind, fp32 tensors), on the
+// edge-handling matrix-core product of edge_gemm.h.  The plain fp32-FMA kernels they replace here used
+// 64 x 64 x 16 tiles with one scalar load per element and one workgroup per output tile whatever the
+// contraction: 44 TFLOP/s at 2048 x 5632 x 1999 bf16, and 149 us for the 22 block gradients of 1376 features
+// over 1024 tokens.
+#include "edge_gemm.h"
+
+namespace poetx {
+namespace {
+
+using namespace edge;
+
+// ---- plans -------------------------------------------------------------------------------------
+// Tile: the largest one that still gives three quarters of the CUs a workgroup -- a larger tile halves the
+// operand traffic, an idle CU costs more than that.  Contraction split: up to two workgroups per CU, as long
+// as a split keeps two stages (below that the fill of the ring is all there is).
+Plan pick_plan(i64 batches, i64 M, i64 N, i64 K, size_t es, bool may_split) {
+  Plan p{TILE_32, 1};
+  if (M > 64 && N > 64 && tile_count(batches, M, N, 128) >= kCUs * 3 / 4) p.tile = TILE_128;
+  else if (M > 32 && N > 32 && tile_count(batches, M, N, 64) >= kCUs * 3 / 4) p.tile = TILE_64;
+  if (!may_split) return p;
+  const int side = p.tile == TILE_128 ? 128 : p.tile == TILE_64 ? 64 : 32;
+  const int depth = p.tile == TILE_32 ? 128 : (p.tile == TILE_128 && es == 4) ? 32 : 64;
+  const i64 count = tile_count(batches, M, N, side), stages = (K + depth - 1) / depth;
+  i64 s = 2 * kCUs / count;
+  if (s > stages / 2) s = stages / 2;
+  if (s > 1) {
+    const i64 per = (stages + s - 1) / s;
+    p.splits = (int)((stages + per - 1) / per);   // no empty split
+  }
+  return p;
+}
+
+Plan dense_plan(int dtype, i64 M, i64 N, i64 K) { return pick_plan(1, M, N, K, dtype == POETX_F32 ? 4 : 2, true); }
+Plan grad_plan(int dtype, int d, i64 N, int b) { return pick_plan(ceil_div(d, b), b, b, N, dtype == POETX_F32 ? 4 : 2, true); }
+
+// ---- epilogues ---------------------------------------------------------------------------------
+template <class T>
+struct EpiStore {           // rows of a plain matrix
+  T* out;
+  i64 ld;
+  int M, N;
+  __device__ void operator()(int, int, int row, int col, const float (&v)[8]) const {
+    if (row < M && col < N) store8(out + (i64)row * ld + col, v, N - col);
+  }
+};
+struct EpiPartial {         // fp32 [split][batch][M][N]
+  float* out;
+  int M, N, batches;
+  __device__ void operator()(int batch, int split, int row, int col, const float (&v)[8]) const {
+    if (row < M && col < N) store8(out + (((i64)split * batches + batch) * M + row) * N + col, v, N - col);
+  }
+};
+// Rows scattered through the permutation.  For bf16 blocks (stored as G - I) the identity part is added
+// here in fp32 from the very row that gathered it; `valid` is the number of input columns, columns from
+// there to `cols` are written as zeros.
+template <class T>
+struct EpiScatter {
+  T* out;
+  const T* V;
+  i64 ldo, ldv;
+  const int32_t* perm;
+  int b, d, valid, cols;
+  __device__ void operator()(int batch, int, int row, int col, const float (&v)[8]) const {
+    const int r = batch * b + row;
+    if (row >= b || r >= d || col >= cols) return;
+    const i64 at = perm[r];
+    if constexpr (sizeof(T) == 2) {
+      const u32x4 x = load_masked<uint16_t>(V + at * ldv, col, valid, true);
+      float w[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        w[2 * e] = v[2 * e] + bf16_bits_to_float((uint16_t)(x[e] & 0xFFFF));
+        w[2 * e + 1] = v[2 * e + 1] + bf16_bits_to_float((uint16_t)(x[e] >> 16));
+      }
+      store8(out + at * ldo + col, w, cols - col);
+    } else {
+      store8(out + at * ldo + col, v, cols - col);
+    }
+  }
+};
+
+// out (M x N, row stride ld) = sum of the partials, in order
+template <class T>
+__global__ __launch_bounds__(256) void edge_reduce_kernel(const float* __restrict__ part, i64 total, int splits, T* __restrict__ out, int N, i64 ld) {
+  const i64 e = ((i64)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (e >= total) return;
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  if (e + 4 <= total && (total & 3) == 0) {
+    for (int z = 0; z < splits; ++z) {
+      const float4 p = *reinterpret_cast<const float4*>(part + z * total + e);
+      s[0] += p.x; s[1] += p.y; s[2] += p.z; s[3] += p.w;
+    }
+  } else {
+    for (int z = 0; z < splits; ++z)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (e + i < total) s[i] += part[z * total + e + i];
+  }
+  i64 row = e / N;
+  int col = (int)(e - row * N);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (e + i < total) {
+      if constexpr (sizeof(T) == 2) out[row * ld + col] = (T)mm::pack2_bf16(s[i], 0.f);
+      else out[row * ld + col] = s[i];
+    }
+    if (++col == N) { col = 0; ++row; }
+  }
+}
+
+template <class T>
+void reduce(const float* part, i64 M, i64 N, int splits, T* out, i64 ld, hipStream_t st) {
+  hipLaunchKernelGGL(edge_reduce_kernel<T>, dim3((unsigned)((M * N + 1023) / 1024)), dim3(256), 0, st, part, M * N, splits, out, (int)N, ld);
+}
+
+template <class T>
+void dense_t(int dtype, int trans_w, const T* W, int n, int m, const T* act, i64 ld_act, T* out, i64 ld_out, i64 N, void* ws, hipStream_t st) {
+  const int M = trans_w ? m : n, K = trans_w ? n : m;
+  const Plan p = dense_plan(dtype, M, N, K);
+  Args g{};
+  g.A = Op{W, m, 0, nullptr, n, m, 0, 0};
+  g.B = Op{act, ld_act, 0, nullptr, K, (int)N, 0, 0};
+  if (p.splits > 1) {
+    const EpiPartial epi{(float*)ws, M, (int)N, 1};
+    if (trans_w) launch<T, false, false>(g, epi, 1, M, N, K, p, st);
+    else launch<T, true, false>(g, epi, 1, M, N, K, p, st);
+    reduce<T>((const float*)ws, M, N, p.splits, out, ld_out, st);
+  } else {
+    const EpiStore<T> epi{out, ld_out, M, (int)N};
+    if (trans_w) launch<T, false, false>(g, epi, 1, M, N, K, p, st);
+    else launch<T, true, false>(g, epi, 1, M, N, K, p, st);
+  }
+}
+
+template <class T>
+void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out, const int32_t* perm, const T* blocks, int b, int trans,
+             hipStream_t st) {
+  const int nb = ceil_div(d, b);
+  const Plan p = pick_plan(nb, b, cols_out, b, sizeof(T), false);
+  Args g{};
+  g.rpb = b;
+  g.d = d;
+  g.B = Op{V, ldv, 0, perm, b, (int)cols, 1, 0};
+  const EpiScatter<T> epi{out, V, ldo, ldv, perm, b, d, (int)cols, (int)cols_out};
+  if constexpr (sizeof(T) == 2) {   // pairs (E, E^T): op(E) has contiguous rows either way
+    g.A = Op{blocks + (trans ? (i64)b * b : 0), b, 2ll * b * b, nullptr, b, b, 1, 1};
+    launch<T, true, false>(g, epi, nb, b, cols_out, b, p, st);
+  } else {
+    g.A = Op{blocks, b, (i64)b * b, nullptr, b, b, 1, 1};
+    if (trans) launch<T, false, false>(g, epi, nb, b, cols_out, b, p, st);
+    else launch<T, true, false>(g, epi, nb, b, cols_out, b, p, st);
+  }
+}
+
+template <class T>
+void grad_t(int dtype, const T* U, i64 ldu, const T* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws, hipStream_t st) {
+  const int nb = ceil_div(d, b);
+  const Plan p = grad_plan(dtype, d, N, b);
+  Args g{};
+  g.rpb = b;
+  g.d = d;
+  g.A = Op{U, ldu, 0, perm, b, (int)N, 1, 0};
+  g.B = Op{V, ldv, 0, perm, b, (int)N, 1, 0};
+  const EpiPartial epi{p.splits > 1 ? (float*)ws : dG, b, b, nb};
+  launch<T, true, true>(g, epi, nb, b, b, N, p, st);
+  if (p.splits > 1) reduce<float>((const float*)ws, (i64)nb * b, b, p.splits, dG, b, st);
+}
+
+}  // namespace
+
+size_t edge_dense_workspace_bytes(int dtype, i64 M, i64 N, i64 K) {
+  const Plan p = dense_plan(dtype, M, N, K);
+  return p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
+}
+
+void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void* act, i64 ld_act, void* out, i64 ld_out, i64 N, void* ws,
+                hipStream_t st) {
+  if (dtype == POETX_F32) dense_t<float>(dtype, trans_w, (const float*)W, n, m, (const float*)act, ld_act, (float*)out, ld_out, N, ws, st);
+  else dense_t<uint16_t>(dtype, trans_w, (const uint16_t*)W, n, m, (const uint16_t*)act, ld_act, (uint16_t*)out, ld_out, N, ws, st);
+}
+
+void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int d, i64 cols, i64 cols_out, const int32_t* perm,
+                     const void* blocks, int b, int transpose_G, hipStream_t st) {
+  if (dtype == POETX_F32)
+    apply_t<float>((const float*)V, ldv, (float*)out, ldo, d, cols, cols_out, perm, (const float*)blocks, b, transpose_G, st);
+  else
+    apply_t<uint16_t>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, perm, (const uint16_t*)blocks, b, transpose_G, st);
+}
+
+size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b) {
+  const Plan p = grad_plan(dtype, d, N, b);
+  return p.splits > 1 ? (size_t)p.splits * ceil_div(d, b) * b * b * sizeof(float) : 0;
+}
+
+void edge_blockgrad(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
+                    hipStream_t st) {
+  if (dtype == POETX_F32) grad_t<float>(dtype, (const float*)U, ldu, (const float*)V, ldv, d, N, perm, b, dG, ws, st);
+  else grad_t<uint16_t>(dtype, (const uint16_t*)U, ldu, (const uint16_t*)V, ldv, d, N, perm, b, dG, ws, st);
+}
+
+}  // namespace poetx

@@ -1,0 +1,410 @@
+// Matrix-core product for shapes the streaming kernels do not take: any sizes, any row stride, any
+// alignment of the element type, bf16 (v_mfma_f32_32x32x16_bf16) and fp32 (v_mfma_f32_32x32x2_f32),
+// fp32 accumulation in both.
+//
+//   C[batch](i, j) = sum_k A[batch](i, k) * B[batch](k, j)
+//
+// An operand is a row-major matrix in memory whose rows may be gathered through a permutation.  It is
+// "K major" when the contraction index runs along its rows (contiguous) and "X major" when the output
+// index does.  Tiles are loaded through registers, 16 bytes per lane whatever the alignment (element
+// aligned vectors: one global load either way), masked at the edges with zeros on both operands so that
+// nothing outside the valid ranges takes part, and pass through a two-stage LDS ring with one barrier
+// per stage; the loads of the next stage are in flight under the products of this one.
+//
+// What bounds it: at the sizes it serves the chip is rarely full, so a pass is a chain of latencies (load,
+// LDS, matrix product, store).  Hence the tile follows the problem (see pick_tile): 128 x 128 where that
+// fills the chip, 64 x 64 below, and 32 x 32 with the four waves splitting the contraction (each takes a
+// quarter of every stage; the partial tiles meet in LDS) for the smallest, which quarters the chain.
+// Contractions that still leave CUs idle are split over workgroups as well (fp32 partials, fixed order).
+#pragma once
+#include "mfma_gemm.h"
+
+namespace poetx {
+namespace edge {
+
+using mm::bf16x8;
+using mm::floatx16;
+using mm::short4v;
+using mm::short8v;
+
+// One operand.  Row r of batch bt lies at p + bt * bs + row * ld with row = perm ? perm[bt * rpb + r] : r.
+struct Op {
+  const void* p;
+  i64 ld, bs;
+  const int32_t* perm;
+  int rows, cols;        // valid extents
+  int rows_side;         // != 0: rows (cols) also end at the side of the batch's block
+  int cols_side;
+};
+
+struct Args {
+  Op A, B;
+  int tiles_m, tiles_n, batches;
+  int stages, stages_per_split;   // contraction stages in all and per split
+  int rpb, d;                     // rpb > 0: block side of batch bt is min(rpb, d - bt * rpb)
+};
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ inline u32x4 load16(const uint16_t* p) { return *reinterpret_cast<const u32x4_a2*>(p); }
+__device__ inline u32x4 load16(const float* p) { return *reinterpret_cast<const u32x4_a4*>(p); }
+
+// 16 bytes of a row starting at column c: zeros outside [0, cols)
+template <class T>
+__device__ inline u32x4 load_masked(const T* row, int c, int cols, bool row_ok) {
+  constexpr int V = 16 / sizeof(T);
+  u32x4 v = {0, 0, 0, 0};
+  if (!row_ok || c >= cols) return v;
+  if (c + V <= cols) return load16(row + c);
+  const int n = cols - c;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    if constexpr (sizeof(T) == 4) {
+      if (w < n) v[w] = __builtin_bit_cast(uint32_t, row[c + w]);
+    } else {
+      uint32_t x = 0;
+      if (2 * w < n) x = row[c + 2 * w];
+      if (2 * w + 1 < n) x |= (uint32_t)row[c + 2 * w + 1] << 16;
+      v[w] = x;
+    }
+  }
+  return v;
+}
+
+// ---- eight consecutive output elements ------------------------------------------------------
+__device__ inline void store8(uint16_t* p, const float (&v)[8], int n) {
+  const u32x4 o = {mm::pack2_bf16(v[0], v[1]), mm::pack2_bf16(v[2], v[3]), mm::pack2_bf16(v[4], v[5]), mm::pack2_bf16(v[6], v[7])};
+  if (n >= 8) {
+    *reinterpret_cast<u32x4_a2*>(p) = o;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 7; ++e)
+      if (e < n) p[e] = (uint16_t)(o[e >> 1] >> (16 * (e & 1)));
+  }
+}
+__device__ inline void store8(float* p, const float (&v)[8], int n) {
+  typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+  if (n >= 8) {
+    *reinterpret_cast<f4*>(p) = f4{v[0], v[1], v[2], v[3]};
+    *reinterpret_cast<f4*>(p + 4) = f4{v[4], v[5], v[6], v[7]};
+  } else {
+#pragma unroll
+    for (int e = 0; e < 7; ++e)
+      if (e < n) p[e] = v[e];
+  }
+}
+
+// chunk swizzle of an X-major bf16 tile (see kx_chunk); 32-wide rows need none: the four k rows of a
+// transposing read are 64 bytes apart and already fall on different banks
+template <int X>
+__device__ inline int kx_swz(int c, int k) {
+  if constexpr (X >= 64) return mm::kx_chunk<X>(c, k);
+  else return c;
+}
+
+template <class T, int X, int BK>
+constexpr int tile_bytes() { return sizeof(T) == 2 ? X * BK * 2 : (X + 4) * BK * 4; }
+
+template <class T, int BM, int BN, int BK, int WGM, int WGN>
+struct Shape {
+  static constexpr int WGK = 4 / (WGM * WGN);
+  static constexpr int A_BYTES = tile_bytes<T, BM, BK>(), B_BYTES = tile_bytes<T, BN, BK>();
+  static constexpr int STAGE = A_BYTES + B_BYTES;
+  static constexpr int LDS = 2 * STAGE;
+  static constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
+  static_assert(WGM * WGN * WGK == 4, "four waves");
+  static_assert(WGK == 1 || (WGK - 1) * WGM * WGN * TM * TN * 4096 <= LDS, "partial tiles meet in the ring");
+};
+
+// Epi: __device__ void operator()(int batch, int split, int row, int col, const float (&v)[8]) -- eight
+// consecutive columns of one output row, indices inside the batch; it does its own masking.
+template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
+__global__ __launch_bounds__(256) void edge_kernel(Args g, Epi epi) {
+  using S = Shape<T, BM, BN, BK, WGM, WGN>;
+  constexpr int V = 16 / sizeof(T), WGK = S::WGK, TM = S::TM, TN = S::TN;
+  constexpr bool BF = sizeof(T) == 2;
+  constexpr int NVA = BM * BK / V / 256, NVB = BN * BK / V / 256;
+  static_assert(NVA >= 1 && NVB >= 1, "tile too small");
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave / (WGM * WGN), wm = (wave / WGN) % WGM, wn = wave % WGN;
+  const int tiles = g.tiles_m * g.tiles_n;
+  const int batch = blockIdx.x / tiles, tile = blockIdx.x % tiles, split = blockIdx.y;
+  const int i0 = (tile % g.tiles_m) * BM, j0 = (tile / g.tiles_m) * BN;
+  const int side = g.rpb > 0 ? (g.d - batch * g.rpb < g.rpb ? g.d - batch * g.rpb : g.rpb) : 0x7fffffff;
+
+  // ---- loads: vector s of this thread covers row (s * 256 + tid) / VPR of the tile's memory rows
+  struct Side {
+    const T* base;
+    const int32_t* pm;
+    i64 ld;
+    int rows, cols;
+  };
+  auto side_of = [&](const Op& o) {
+    Side r;
+    r.base = (const T*)o.p + (i64)batch * o.bs;
+    r.pm = o.perm ? o.perm + (i64)batch * g.rpb : nullptr;
+    r.ld = o.ld;
+    r.rows = o.rows_side && side < o.rows ? side : o.rows;
+    r.cols = o.cols_side && side < o.cols ? side : o.cols;
+    return r;
+  };
+  const Side sa = side_of(g.A), sb = side_of(g.B);
+  constexpr int VPRA = (A_K ? BK : BM) / V, VPRB = (B_K ? BK : BN) / V;
+  u32x4 ra[NVA], rb[NVB];
+  // memory row of this thread's vector: fixed for a K-major operand, moving with the stage for an X-major one
+  i64 rowA[NVA], rowB[NVB];
+  auto row_index = [&](const Side& s, int r) -> i64 { return r < s.rows ? (s.pm ? (i64)s.pm[r] : (i64)r) * s.ld : -1; };
+  auto rows_at = [&](int kt) {
+#pragma unroll
+    for (int s = 0; s < NVA; ++s) {
+      const int r = (s * 256 + tid) / VPRA;
+      rowA[s] = row_index(sa, A_K ? i0 + r : kt * BK + r);
+    }
+#pragma unroll
+    for (int s = 0; s < NVB; ++s) {
+      const int r = (s * 256 + tid) / VPRB;
+      rowB[s] = row_index(sb, B_K ? j0 + r : kt * BK + r);
+    }
+  };
+  auto next_rows = [&](int kt) {   // gathered X-major rows change from stage to stage
+    if (!A_K) {
+#pragma unroll
+      for (int s = 0; s < NVA; ++s) rowA[s] = row_index(sa, kt * BK + (s * 256 + tid) / VPRA);
+    }
+    if (!B_K) {
+#pragma unroll
+      for (int s = 0; s < NVB; ++s) rowB[s] = row_index(sb, kt * BK + (s * 256 + tid) / VPRB);
+    }
+  };
+  auto gload = [&](int kt) {
+#pragma unroll
+    for (int s = 0; s < NVA; ++s) {
+      const int c = ((s * 256 + tid) % VPRA) * V + (A_K ? kt * BK : i0);
+      ra[s] = load_masked<T>(sa.base + rowA[s], c, sa.cols, rowA[s] >= 0);
+    }
+#pragma unroll
+    for (int s = 0; s < NVB; ++s) {
+      const int c = ((s * 256 + tid) % VPRB) * V + (B_K ? kt * BK : j0);
+      rb[s] = load_masked<T>(sb.base + rowB[s], c, sb.cols, rowB[s] >= 0);
+    }
+  };
+  // ---- LDS layout.  bf16: 32-deep sub-tiles in the swizzled layouts of mfma_gemm.h.  fp32: [k][x], rows of
+  // X + 4 floats (the transposing stores of a K-major operand then spread over the banks).
+  auto put = [&](char* at, const u32x4& v, int r, int vc, auto X_, bool kmajor) {
+    constexpr int X = decltype(X_)::value;
+    if constexpr (BF) {
+      if (kmajor) *reinterpret_cast<u32x4*>(at + (vc >> 2) * (X * 64) + r * 64 + 16 * mm::xk_chunk(vc & 3, r)) = v;
+      else *reinterpret_cast<u32x4*>(at + (r >> 5) * (X * 64) + (r & 31) * (X * 2) + 16 * kx_swz<X>(vc, r & 31)) = v;
+    } else {
+      float* f = reinterpret_cast<float*>(at);
+      if (kmajor) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[(vc * 4 + e) * (X + 4) + r] = __builtin_bit_cast(float, (uint32_t)v[e]);
+      } else {
+        *reinterpret_cast<u32x4*>(f + r * (X + 4) + vc * 4) = v;
+      }
+    }
+  };
+  auto lstore = [&](int slot) {
+    char* stage = lds + slot * S::STAGE;
+#pragma unroll
+    for (int s = 0; s < NVA; ++s)
+      put(stage, ra[s], (s * 256 + tid) / VPRA, (s * 256 + tid) % VPRA, std::integral_constant<int, BM>{}, A_K);
+#pragma unroll
+    for (int s = 0; s < NVB; ++s)
+      put(stage + S::A_BYTES, rb[s], (s * 256 + tid) / VPRB, (s * 256 + tid) % VPRB, std::integral_constant<int, BN>{}, B_K);
+  };
+
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int c = 0; c < TN; ++c)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
+
+  const int li = lane & 31, h = lane >> 5;
+  auto frag_bf16 = [&](const char* sub, int x0, int ks, auto X_, bool kmajor) -> bf16x8 {
+    constexpr int X = decltype(X_)::value;
+    if (kmajor) {
+      const int r = x0 + li;
+      return *reinterpret_cast<const bf16x8*>(sub + r * 64 + 16 * mm::xk_chunk(2 * ks + h, r));
+    }
+    const int q = lane >> 4, i = lane & 15;
+    const int k = 16 * ks + 8 * (q >> 1) + (i >> 2);
+    const int c = (x0 >> 3) + 2 * (q & 1) + ((i & 3) >> 1);
+    // the swizzle depends on k & 3 only, so the second half (k + 4) uses the same chunk position
+    const char* p = sub + k * (X * 2) + 16 * kx_swz<X>(c, k) + 8 * (i & 1);
+    const short4v lo = mm::lds_read_tr(p), hi = mm::lds_read_tr(p + 4 * (X * 2));
+    const short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  };
+  auto multiply = [&](int slot) {
+    const char* sA = lds + slot * S::STAGE;
+    const char* sB = sA + S::A_BYTES;
+    if constexpr (BF) {
+      constexpr int SUBS = BK / 32 / WGK;      // 32-deep sub-tiles per wave
+      static_assert(SUBS >= 1, "a wave of a split contraction takes whole sub-tiles");
+#pragma unroll
+      for (int u = 0; u < SUBS; ++u) {
+        const int sub = wk * SUBS + u;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          bf16x8 fa[TM], fb[TN];
+#pragma unroll
+          for (int a = 0; a < TM; ++a)
+            fa[a] = frag_bf16(sA + sub * (BM * 64), wm * (BM / WGM) + a * 32, ks, std::integral_constant<int, BM>{}, A_K);
+#pragma unroll
+          for (int c = 0; c < TN; ++c)
+            fb[c] = frag_bf16(sB + sub * (BN * 64), wn * (BN / WGN) + c * 32, ks, std::integral_constant<int, BN>{}, B_K);
+#pragma unroll
+          for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int c = 0; c < TN; ++c)
+              acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[c], fa[a], acc[a][c], 0, 0, 0);
+        }
+      }
+    } else {
+      constexpr int KW = BK / WGK;             // depth of a stage that one wave takes
+      const float* fA = reinterpret_cast<const float*>(sA) + (wk * KW + h) * (BM + 4) + wm * (BM / WGM) + li;
+      const float* fB = reinterpret_cast<const float*>(sB) + (wk * KW + h) * (BN + 4) + wn * (BN / WGN) + li;
+#pragma unroll
+      for (int kk = 0; kk < KW; kk += 2) {
+        float fa[TM], fb[TN];
+#pragma unroll
+        for (int a = 0; a < TM; ++a) fa[a] = fA[kk * (BM + 4) + a * 32];
+#pragma unroll
+        for (int c = 0; c < TN; ++c) fb[c] = fB[kk * (BN + 4) + c * 32];
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int c = 0; c < TN; ++c)
+            acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[c], fa[a], acc[a][c], 0, 0, 0);
+      }
+    }
+  };
+
+  const int k0 = split * g.stages_per_split;
+  const int k1 = k0 + g.stages_per_split < g.stages ? k0 + g.stages_per_split : g.stages;
+  if (k0 < k1) {
+    rows_at(k0);
+    gload(k0);
+    if (k0 + 1 < k1) next_rows(k0 + 1);
+    lstore(0);
+    __syncthreads();
+    for (int kt = k0; kt < k1; ++kt) {
+      const int slot = (kt - k0) & 1;
+      if (kt + 1 < k1) {
+        gload(kt + 1);
+        if (kt + 2 < k1) next_rows(kt + 2);
+      }
+      multiply(slot);
+      if (kt + 1 < k1) lstore(slot ^ 1);   // read last before the previous barrier
+      __syncthreads();
+    }
+  }
+
+  if constexpr (WGK > 1) {
+    // the partial tiles of the waves that share an output piece meet in LDS; wave 0 adds them in order
+    constexpr int TILE_F = TM * TN * 1024;
+    float* part = reinterpret_cast<float*>(lds);
+    const int piece = wm * WGN + wn;
+    if (wk > 0) {
+      float* dst = part + ((wk - 1) * WGM * WGN + piece) * TILE_F + lane * 4;
+#pragma unroll
+      for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int c = 0; c < TN; ++c)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<float4*>(dst + ((a * TN + c) * 4 + q) * 256) =
+                make_float4(acc[a][c][4 * q], acc[a][c][4 * q + 1], acc[a][c][4 * q + 2], acc[a][c][4 * q + 3]);
+    }
+    __syncthreads();
+    if (wk > 0) return;
+#pragma unroll
+    for (int w = 0; w < WGK - 1; ++w) {
+      const float* src = part + (w * WGM * WGN + piece) * TILE_F + lane * 4;
+#pragma unroll
+      for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int c = 0; c < TN; ++c)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float4 p = *reinterpret_cast<const float4*>(src + ((a * TN + c) * 4 + q) * 256);
+            acc[a][c][4 * q] += p.x;
+            acc[a][c][4 * q + 1] += p.y;
+            acc[a][c][4 * q + 2] += p.z;
+            acc[a][c][4 * q + 3] += p.w;
+          }
+    }
+  }
+
+  // a lane holds one output row and four columns per register group; groups are swapped between the lane
+  // halves (v_permlane32_swap) so that it holds eight consecutive columns
+  typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int a = 0; a < TM; ++a) {
+    const int row = i0 + wm * (BM / WGM) + a * 32 + li;
+#pragma unroll
+    for (int c = 0; c < TN; ++c) {
+      const int col = j0 + wn * (BN / WGN) + c * 32 + 8 * h;
+#pragma unroll
+      for (int q = 0; q < 4; q += 2) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = acc[a][c][4 * q + e], y = acc[a][c][4 * q + 4 + e];   // scalars first: a bit cast straight from a vector element reads element 0
+          const uint2v r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+          const unsigned r0 = r[0], r1 = r[1];
+          v[e] = __builtin_bit_cast(float, r0);
+          v[4 + e] = __builtin_bit_cast(float, r1);
+        }
+        epi(batch, split, row, col + 8 * q, v);
+      }
+    }
+  }
+}
+
+// ---- host side -------------------------------------------------------------------------------
+enum Tile { TILE_32 = 0, TILE_64 = 1, TILE_128 = 2 };
+
+struct Plan {
+  Tile tile;
+  int splits;
+};
+
+constexpr int kCUs = 256;
+
+inline i64 tile_count(i64 batches, i64 M, i64 N, int t) { return batches * ((M + t - 1) / t) * ((N + t - 1) / t); }
+inline int stage_depth(Tile t) { return t == TILE_32 ? 128 : 64; }
+
+template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
+void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits, hipStream_t st) {
+  using S = Shape<T, BM, BN, BK, WGM, WGN>;
+  auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi>;
+  // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
+  static const bool configured =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
+  (void)configured;
+  g.tiles_m = ceil_div(M, BM);
+  g.tiles_n = ceil_div(N, BN);
+  g.batches = (int)batches;
+  g.stages = ceil_div(K, BK);
+  g.stages_per_split = ceil_div(g.stages, splits);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(batches * g.tiles_m * g.tiles_n), (unsigned)splits), dim3(256), S::LDS, st, g, epi);
+}
+
+template <class T, bool A_K, bool B_K, class Epi>
+void launch(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, Plan p, hipStream_t st) {
+  if (p.tile == TILE_128) launch_shape<T, 128, 128, (sizeof(T) == 2 ? 64 : 32), 2, 2, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else if (p.tile == TILE_64) launch_shape<T, 64, 64, 64, 2, 2, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else launch_shape<T, 32, 32, 128, 1, 1, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+}
+
+}  // namespace edge
+}  // namespace poetx

@@ -80,12 +80,15 @@ void apply_left_dispatch(int dtype, const void* V, void* out, int d, i64 cols, i
   StageTimer tm(POETX_STAGE_APPLY, st);
   if (use_mfma(dtype) && mfma_apply_left_supported(d, cols, ld, b) && aligned16(V) && aligned16(out) && aligned16(blocks))
     mfma_apply_left(V, out, d, cols, ld, perm, blocks, b, trans, st);
+  else if (!g_force_fma.load())
+    edge_apply_left(dtype, V, ld, out, ld, d, cols, cols, perm, blocks, b, trans, st);
   else
     fma_apply_left(dtype, V, out, d, cols, ld, perm, blocks, b, trans, st);
 }
 
+// part: scratch of dense_part_bytes() for products that split their contraction.
 // w_q8: W is a quantised weight buffer that the product dequantises itself (see weight_in_kernel)
-void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const void* act, void* out, i64 N,
+void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const void* act, void* out, i64 N, void* part,
                     hipStream_t st, bool w_q8 = false) {
   StageTimer tm(POETX_STAGE_DENSE, st);
   if (w_q8) mfma_dense_q8(trans_w, W, n, m, act, out, N, st);
@@ -93,6 +96,7 @@ void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const v
     mfma_dense(trans_w, W, n, m, act, out, N, st);
   else if (dtype == POETX_F32 && !g_force_fma.load() && mfma_dense_f32_supported(n, m, N) && aligned16(W) && aligned16(act) && aligned16(out))
     mfma_dense_f32(trans_w, W, n, m, act, out, N, st);
+  else if (!g_force_fma.load()) edge_dense(dtype, trans_w, W, n, m, act, N, out, N, N, part, st);
   else fma_dense(dtype, trans_w, W, n, m, act, out, N, st);
 }
 
@@ -102,9 +106,29 @@ bool weight_in_kernel(const poetx_linear_desc* d) {
   return (d->flags & POETX_FLAG_W_INT8) && (d->flags & POETX_FLAG_W_INT8_FUSED) && use_mfma(d->dtype) && mfma_dense_q8_supported(d->d_out, d->d_in, d->n_tokens);
 }
 
+// Which kernels run also depends on the pointers (their alignment), which a workspace query does not see: the
+// queries below cover every path.
 size_t blockgrad_ws_bytes(int dtype, int d, i64 N, int b) {
-  if (dtype == POETX_BF16 && mfma_blockgrad_supported(d, N, b)) return align256(mfma_blockgrad_workspace_bytes(d, N, b));
-  return 0;
+  size_t w = edge_blockgrad_workspace_bytes(dtype, d, N, b);
+  if (dtype == POETX_BF16 && mfma_blockgrad_supported(d, N, b)) {
+    const size_t f = mfma_blockgrad_workspace_bytes(d, N, b);
+    if (f > w) w = f;
+  }
+  return align256(w);
+}
+
+// Scratch of the dense products (partials of a split contraction), both directions.
+size_t dense_part_bytes(const poetx_linear_desc* d) {
+  const size_t f = edge_dense_workspace_bytes(d->dtype, d->d_out, d->n_tokens, d->d_in);
+  const size_t b = edge_dense_workspace_bytes(d->dtype, d->d_in, d->n_tokens, d->d_out);
+  return align256(f > b ? f : b);
+}
+
+void blockgrad_dispatch(int dtype, const void* U, const void* V, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
+                        hipStream_t st) {
+  if (use_mfma(dtype) && mfma_blockgrad_supported(d, N, b) && aligned16(U) && aligned16(V)) mfma_blockgrad(U, V, d, N, perm, b, dG, ws, st);
+  else if (!g_force_fma.load()) edge_blockgrad(dtype, U, N, V, N, d, N, perm, b, dG, ws, st);
+  else fma_blockgrad(dtype, U, V, d, N, perm, b, dG, st);
 }
 
 }  // namespace
@@ -267,6 +291,11 @@ int poetx_perm_validate(const int32_t* perm, int32_t d, int32_t* scratch, void* 
   return bad ? POETX_ERR_BAD_PERM : POETX_OK;
 }
 
+static size_t dequantised_weight_bytes(const poetx_linear_desc* desc) {
+  return ((desc->flags & POETX_FLAG_W_INT8) && !weight_in_kernel(desc))
+             ? align256((size_t)desc->d_out * desc->d_in * esize(desc->dtype)) : 0;
+}
+
 // The weight the dense product reads: W itself, or its dequantised copy made at `scratch`.
 static const void* resolve_weight(const poetx_linear_desc* desc, const void* W, void* scratch, hipStream_t st) {
   if (!(desc->flags & POETX_FLAG_W_INT8) || weight_in_kernel(desc)) return W;
@@ -351,10 +380,6 @@ class LayoutStaging {
 
 // poetx_linear_bwd called without saved_B recomputes B itself: B, then the dequantised weight (kept for both
 // of the call's dense products), sit at the very end of the workspace.
-static size_t dequantised_weight_bytes(const poetx_linear_desc* desc) {
-  return ((desc->flags & POETX_FLAG_W_INT8) && !weight_in_kernel(desc))
-             ? align256((size_t)desc->d_out * desc->d_in * esize(desc->dtype)) : 0;
-}
 static size_t recompute_tail_bytes(const poetx_linear_desc* desc) {
   if (!(desc->flags & POETX_FLAG_RECOMPUTE_B)) return 0;
   return align256((size_t)desc->d_out * (size_t)desc->n_tokens * esize(desc->dtype)) + dequantised_weight_bytes(desc);
@@ -367,8 +392,9 @@ static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
   if (desc->flags & POETX_FLAG_RECOMPUTE_B) fwd += align256((size_t)desc->d_out * N * es);  // B lives here too
   const size_t wdeq = ((desc->flags & POETX_FLAG_W_INT8) && !weight_in_kernel(desc))
                           ? align256((size_t)desc->d_out * desc->d_in * es) : 0;   // dequantised copy, only where no kernel converts on the fly
-  fwd += wdeq;                                          // dequantised weight behind A (and B)
-  size_t bwi = align256((size_t)desc->d_out * N * es) + wdeq;  // dB = P dZ
+  const size_t part = dense_part_bytes(desc);
+  fwd += wdeq + part;                                   // dequantised weight behind A (and B), then the dense product's partials
+  size_t bwi = align256((size_t)desc->d_out * N * es) + wdeq + part;  // dB = P dZ
   int dmax = desc->d_in > desc->d_out ? desc->d_in : desc->d_out;
   size_t bg_in = blockgrad_ws_bytes(desc->dtype, desc->d_in, desc->n_tokens, desc->block);
   size_t bg_out = blockgrad_ws_bytes(desc->dtype, desc->d_out, desc->n_tokens, desc->block);
@@ -387,7 +413,7 @@ static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
     size_t tail = align256(mfma_apply_grad_workspace_bytes(desc->d_in, desc->n_tokens));
     const size_t po = align256(mfma_apply_grad_workspace_bytes(desc->d_out, desc->n_tokens));
     if (po > tail) tail = po;
-    if (wdeq > tail) tail = wdeq;
+    if (wdeq + part > tail) tail = wdeq + part;
     const size_t one_pass = align256((size_t)desc->d_in * N * es) + align256((size_t)desc->d_out * N * es) +
                             align256(chain * sizeof(float)) + tail;
     if (one_pass > bwd) bwd = one_pass;
@@ -417,8 +443,9 @@ int poetx_linear_fwd(const poetx_linear_desc* desc, const void* X, const void* W
     after += align256((size_t)n * N * esize(dt));
   }
   W = resolve_weight(desc, W, after, st);
+  void* part = after + dequantised_weight_bytes(desc);
   apply_left_dispatch(dt, X, A, m, N, N, perm_R, blocks_R, b, 1, st);        // mm1: A = R^T X
-  dense_dispatch(dt, 0, W, n, m, A, saved_B, N, st, weight_in_kernel(desc));                        // mm2: B = W A
+  dense_dispatch(dt, 0, W, n, m, A, saved_B, N, part, st, weight_in_kernel(desc));     // mm2: B = W A
   apply_left_dispatch(dt, saved_B, Z, n, N, N, perm_P, blocks_P, b, 1, st);  // mm3: Z = P^T B
   lay.finish();
   return launch_status();
@@ -435,9 +462,10 @@ int poetx_linear_recompute_b(const poetx_linear_desc* desc, const void* X, const
   const i64 N = desc->n_tokens;
   LayoutStaging lay(desc, ws, st);
   X = lay.in(X, m);
-  W = resolve_weight(desc, W, (char*)ws + align256((size_t)m * N * esize(dt)), st);
+  char* after = (char*)ws + align256((size_t)m * N * esize(dt));
+  W = resolve_weight(desc, W, after, st);
   apply_left_dispatch(dt, X, ws, m, N, N, perm_R, blocks_R, b, 1, st);  // A = R^T X
-  dense_dispatch(dt, 0, W, n, m, ws, B_out, N, st, weight_in_kernel(desc));                    // B = W A
+  dense_dispatch(dt, 0, W, n, m, ws, B_out, N, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // B = W A
   return launch_status();
 }
 
@@ -448,9 +476,10 @@ static void bwd_input_impl(const poetx_linear_desc* desc, const void* dZ, const 
   const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype;
   const i64 N = desc->n_tokens;
   void* dB = ws;
-  W = W_resolved ? W_resolved : resolve_weight(desc, W, (char*)ws + align256((size_t)n * N * esize(dt)), st);
+  char* after = (char*)ws + align256((size_t)n * N * esize(dt));
+  W = W_resolved ? W_resolved : resolve_weight(desc, W, after, st);
   apply_left_dispatch(dt, dZ, dB, n, N, N, perm_P, blocks_P, b, 0, st);  // dB = P dZ
-  dense_dispatch(dt, 1, W, n, m, dB, dA, N, st, weight_in_kernel(desc));                        // dA = W^T dB
+  dense_dispatch(dt, 1, W, n, m, dB, dA, N, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // dA = W^T dB
   apply_left_dispatch(dt, dA, dX, m, N, N, perm_R, blocks_R, b, 0, st);  // dX = R dA
 }
 
@@ -499,7 +528,7 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
   // backward is left to poetx_cnp_bwd
   const bool defer = (desc->flags & POETX_FLAG_BLOCK_GRADS) != 0;
   if (desc->cnp_precision == POETX_CNP_BF16 && !g_force_fma.load() && use_mfma(dt) && mfma_cnp_supported(m, b) &&
-      mfma_cnp_supported(n, b) && mfma_blockgrad_supported(m, N, b) && mfma_blockgrad_supported(n, N, b)) {
+      mfma_cnp_supported(n, b)) {
     // Both sides' blocks go through the series backward as one batch (P side first): the chains
     // are latency bound and a side alone leaves most CUs empty.
     const int nbP = n / b, nbR = m / b, nbt = nbP + nbR;
@@ -507,8 +536,8 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
     float* dG = (float*)ws;                                   // [nbt][b][b]
     if (defer) {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      mfma_blockgrad(saved_B, dZ, n, N, perm_P, b, dtheta_P, bg_ws, st);
-      mfma_blockgrad(X, dA, m, N, perm_R, b, dtheta_R, bg_ws, st);
+      blockgrad_dispatch(dt, saved_B, dZ, n, N, perm_P, b, dtheta_P, bg_ws, st);
+      blockgrad_dispatch(dt, X, dA, m, N, perm_R, b, dtheta_R, bg_ws, st);
       return;
     }
     if (!lds_cnp_supported(m, b)) {                            // tiled kernels (b = 512)
@@ -517,8 +546,8 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
       float* chain = Qf + nbt * bb + nbt * bb / 2;            // 3.5 floats per element follow: 6 in all
       {
         StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-        mfma_blockgrad(saved_B, dZ, n, N, perm_P, b, dG, bg_ws, st);
-        mfma_blockgrad(X, dA, m, N, perm_R, b, dG + nbP * bb, bg_ws, st);
+        blockgrad_dispatch(dt, saved_B, dZ, n, N, perm_P, b, dG, bg_ws, st);
+        blockgrad_dispatch(dt, X, dA, m, N, perm_R, b, dG + nbP * bb, bg_ws, st);
       }
       StageTimer tm(POETX_STAGE_CNP_BWD, st);
       skew_materialize_launch(theta_P, b, nbP, Qf, nullptr, Tb, st);
@@ -530,8 +559,8 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
     }
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      mfma_blockgrad(saved_B, dZ, n, N, perm_P, b, dG, bg_ws, st);            // dG_P = B' dZ'^T
-      mfma_blockgrad(X, dA, m, N, perm_R, b, dG + nbP * bb, bg_ws, st);       // dG_R = X' dA'^T
+      blockgrad_dispatch(dt, saved_B, dZ, n, N, perm_P, b, dG, bg_ws, st);            // dG_P = B' dZ'^T
+      blockgrad_dispatch(dt, X, dA, m, N, perm_R, b, dG + nbP * bb, bg_ws, st);       // dG_R = X' dA'^T
     }
     cnp_bwd_both_on_chip(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);
     return;
@@ -549,8 +578,7 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
     float* dGs = defer ? dtheta : dG;
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      if (use_mfma(dt) && mfma_blockgrad_supported(d, N, b)) mfma_blockgrad(U, V, d, N, perm, b, dGs, bg_ws, st);
-      else fma_blockgrad(dt, U, V, d, N, perm, b, dGs, st);
+      blockgrad_dispatch(dt, U, V, d, N, perm, b, dGs, bg_ws, st);
     }
     if (!defer) {
       StageTimer tm(POETX_STAGE_CNP_BWD, st);
@@ -606,12 +634,13 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
     char* B_re = w_keep - align256((size_t)n * N * esize(dt));
     W_resolved = resolve_weight(desc, W, w_keep, st);
     apply_left_dispatch(dt, X, dA, m, N, N, perm_R, blocks_R, b, 1, st);
-    dense_dispatch(dt, 0, W_resolved, n, m, dA, B_re, N, st, weight_in_kernel(desc));
+    dense_dispatch(dt, 0, W_resolved, n, m, dA, B_re, N, rest, st, weight_in_kernel(desc));   // partials where dB will be
     saved_B = B_re;
   }
   const bool one_pass = desc->cnp_precision == POETX_CNP_BF16 && use_mfma(dt) && lds_cnp_supported(m, b) &&
                         lds_cnp_supported(n, b) && mfma_apply_grad_supported(m, N, N, b) &&
-                        mfma_apply_grad_supported(n, N, N, b);
+                        mfma_apply_grad_supported(n, N, N, b) && aligned16(X) && aligned16(dZ) && aligned16(saved_B) &&
+                        aligned16(dX) && aligned16(blocks_R) && aligned16(blocks_P);
   if (!one_pass) {   // the same values through the two halves
     bwd_input_impl(desc, dZ, W, perm_R, perm_P, blocks_R, blocks_P, dX, dA, rest, st, W_resolved);
     bwd_skew_impl(desc, X, dZ, saved_B, dA, perm_R, perm_P, theta_R, theta_P, dtheta_R, dtheta_P, accumulate, rest, st);
@@ -636,7 +665,7 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
     mfma_apply_grad(dZ, saved_B, dB, n, N, N, perm_P, blocks_P, 0, dG_P, part, st);
   }
   W = W_resolved ? W_resolved : resolve_weight(desc, W, part, st);   // the P side's partials are reduced by now (stream order): same space
-  dense_dispatch(dt, 1, W, n, m, dB, dA, N, st, weight_in_kernel(desc));
+  dense_dispatch(dt, 1, W, n, m, dB, dA, N, (char*)part + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));
   {
     StageTimer tm(POETX_STAGE_APPLY_GRAD, st);
     mfma_apply_grad(dA, X, dX, m, N, N, perm_R, blocks_R, 0, dG_R, part, st);

@@ -35,6 +35,18 @@ void fma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void* 
 void fma_cnp_bwd(const float* theta, const float* dG, int d, int b, int k, float* dtheta, int accumulate,
                  float* ws, hipStream_t st);
 
+// ---- edge-handling matrix-core path (edge.hip): bf16 and fp32, any sizes, strides and alignments --------
+// ws: the bytes the queries report (fp32 partials of a split contraction; 0 where there is no split).
+size_t edge_dense_workspace_bytes(int dtype, i64 M, i64 N, i64 K);
+void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void* act, i64 ld_act, void* out, i64 ld_out, i64 N, void* ws,
+                hipStream_t st);
+// V: d x cols, out: d x cols_out (cols_out >= cols; the extra columns are written as zeros)
+void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int d, i64 cols, i64 cols_out, const int32_t* perm,
+                     const void* blocks, int b, int transpose_G, hipStream_t st);
+size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b);
+void edge_blockgrad(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
+                    hipStream_t st);
+
 // dtheta[j][idx(i,c)] (+)= M[j][i][c] - M[j][c][i] (Sec. 3.4: gradient on the packed parameters).
 void skew_project_launch(const float* M, int b, int d, float* dtheta, int accumulate, hipStream_t st);
 

@@ -1,0 +1,60 @@
+"""The edge-handling matrix-core kernels (any size, stride, alignment) against the fp64 oracle at the sizes
+where they can go wrong: one off the 32 / 64 / 128 tile sides, one element, remainders of a 16-byte vector in
+every extent, contractions that are split over workgroups, operands off 16-byte alignment.  Tolerances are
+the dtype's (sums of up to a few thousand terms in fp32, one bf16 rounding per intermediate)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import poetx_oracle as orc
+from workloads import round_bf16, round_f32
+from tests.harness import TOL, rel_err, run_layer, tdtype, to_dev, to_np
+from tests.test_gpu_parity import check_layer, synth_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,n,N,b,k", [
+    (8, 8, 1, 8, 2),            # a single token, a block smaller than any tile
+    (33, 40, 31, 32, 2),        # one past a block, token remainder 7 of 8
+    (96, 65, 33, 32, 3),        # tail blocks of 1 on one side
+    (127, 129, 63, 64, 2),      # one off the 128 tile
+    (160, 96, 65, 64, 2),
+    (1000, 24, 129, 24, 2),     # block side that no tile divides, long contraction split over workgroups
+    (72, 2050, 17, 72, 2),      # the same in the backward direction
+    (640, 1376, 2047, 64, 2),   # 128-wide tiles, every extent ragged
+    (512, 256, 1000, 256, 2),   # large blocks, token count a multiple of 8 only
+])
+def test_layer_at_tile_edges(lib, m, n, N, b, k, dtype):
+    data = synth_layer(9000 + m + n + N + b, m, n, N, b, k, dtype, 0.01)
+    ref = orc.linear_fwd_bwd_from_theta(data["X"], data["dZ"], data["W"], data["pi_R"], data["pi_P"],
+                                        data["theta_R"], data["theta_P"], b, k)
+    check_layer(run_layer(data, dtype), ref, data["pi_P"], dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,b,cols,off", [(64, 32, 96, 1), (256, 256, 256, 1), (320, 64, 40, 3)])
+def test_apply_off_alignment(lib, d, b, cols, off, dtype):
+    """Input, output and blocks that start `off` elements into an allocation: element alignment is enough, and
+    nothing outside the output is written."""
+    rng = np.random.Generator(np.random.PCG64(9100 + d + cols))
+    V = (round_f32 if dtype == "f32" else round_bf16)(rng.standard_normal((d, cols)))
+    E = round_bf16(rng.standard_normal((d // b, b, b)) * 0.05)
+    pi = rng.permutation(d).astype(np.int32)
+    eye = np.eye(b)
+    stored = E + eye if dtype == "f32" else np.stack([E, np.swapaxes(E, 1, 2)], axis=1)
+    dt = tdtype(dtype)
+
+    def shifted(a):
+        flat = torch.zeros(a.size + off, dtype=dt, device="cuda")
+        flat[off:] = to_dev(a, dt).reshape(-1)
+        return flat[off:].view(a.shape)
+    buf = torch.full((d * cols + 2 * off + 8,), -7.0, dtype=dt, device="cuda")
+    out = buf[off:off + d * cols].view(d, cols)
+    blocks, Vd = shifted(stored), shifted(V)
+    for trans in (False, True):
+        lib.poetx_perm_blockdiag_apply_left(Vd, out, torch.from_numpy(pi).cuda(), blocks, b, trans)
+        torch.cuda.synchronize()
+        assert rel_err(to_np(out), orc.apply_left(V, pi, E + eye, trans)) <= TOL[dtype]
+        assert torch.all(buf[:off] == -7.0) and torch.all(buf[off + d * cols:] == -7.0)

@@ -154,18 +154,16 @@ void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out
   }
 }
 
+// block gradients as plan.splits parts at `parts`
 template <class T>
-void grad_t(int dtype, const T* U, i64 ldu, const T* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws, hipStream_t st) {
+void grad_t(const Plan& p, const T* U, i64 ldu, const T* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* parts, hipStream_t st) {
   const int nb = ceil_div(d, b);
-  const Plan p = grad_plan(dtype, d, N, b);
   Args g{};
   g.rpb = b;
   g.d = d;
   g.A = Op{U, ldu, 0, perm, b, (int)N, 1, 0};
   g.B = Op{V, ldv, 0, perm, b, (int)N, 1, 0};
-  const EpiPartial epi{p.splits > 1 ? (float*)ws : dG, b, b, nb};
-  launch<T, true, true>(g, epi, nb, b, b, N, p, st);
-  if (p.splits > 1) reduce<float>((const float*)ws, (i64)nb * b, b, p.splits, dG, b, st);
+  launch<T, true, true>(g, EpiPartial{parts, b, b, nb}, nb, b, b, N, p, st);
 }
 
 }  // namespace
@@ -189,15 +187,27 @@ void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int 
     apply_t<uint16_t>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, perm, (const uint16_t*)blocks, b, transpose_G, st);
 }
 
-size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b) {
+size_t edge_blockgrad_parts_bytes(int dtype, int d, i64 N, int b) {
+  return (size_t)grad_plan(dtype, d, N, b).splits * ceil_div(d, b) * b * b * sizeof(float);
+}
+
+int edge_blockgrad_parts(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* parts,
+                         hipStream_t st) {
   const Plan p = grad_plan(dtype, d, N, b);
-  return p.splits > 1 ? (size_t)p.splits * ceil_div(d, b) * b * b * sizeof(float) : 0;
+  if (dtype == POETX_F32) grad_t<float>(p, (const float*)U, ldu, (const float*)V, ldv, d, N, perm, b, parts, st);
+  else grad_t<uint16_t>(p, (const uint16_t*)U, ldu, (const uint16_t*)V, ldv, d, N, perm, b, parts, st);
+  return p.splits;
+}
+
+size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b) {
+  return grad_plan(dtype, d, N, b).splits > 1 ? edge_blockgrad_parts_bytes(dtype, d, N, b) : 0;
 }
 
 void edge_blockgrad(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
                     hipStream_t st) {
-  if (dtype == POETX_F32) grad_t<float>(dtype, (const float*)U, ldu, (const float*)V, ldv, d, N, perm, b, dG, ws, st);
-  else grad_t<uint16_t>(dtype, (const uint16_t*)U, ldu, (const uint16_t*)V, ldv, d, N, perm, b, dG, ws, st);
+  const bool split = grad_plan(dtype, d, N, b).splits > 1;
+  const int n = edge_blockgrad_parts(dtype, U, ldu, V, ldv, d, N, perm, b, split ? (float*)ws : dG, st);
+  if (split) reduce<float>((const float*)ws, (i64)ceil_div(d, b) * b, b, n, dG, b, st);
 }
 
 }  // namespace poetx

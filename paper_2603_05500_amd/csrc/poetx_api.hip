@@ -38,6 +38,8 @@ int static_scratch(void** out) {
 
 inline bool use_mfma(int dtype) { return dtype == POETX_BF16 && !g_force_fma.load(); }
 // the matrix-core kernels move 16 bytes per lane: every tensor they touch must be 16-byte aligned
+// series of small blocks: fp32 whatever the precision asked for, one launch for a whole chain
+inline bool series_small(int b) { return series_small_supported(b) && !g_force_fma.load(); }
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 inline size_t esize(int dtype) { return dtype == POETX_F32 ? 4 : 2; }
 inline bool dtype_ok(int dtype) { return dtype == POETX_F32 || dtype == POETX_BF16; }
@@ -168,6 +170,8 @@ int poetx_cnp_build(const float* theta, int32_t d, int32_t b, int32_t k, int32_t
   StageTimer tm(POETX_STAGE_CNP_FWD, st);
   if (precision == POETX_CNP_BF16 && !g_force_fma.load() && mfma_cnp_supported(d, b))
     mfma_cnp_build(theta, d, b, k, G_f32, E_bf16, (float*)ws, st);
+  else if (series_small(b))
+    series_small_build(theta, d, b, k, G_f32, E_bf16, st);
   else
     fma_cnp_build(theta, d, b, k, G_f32, E_bf16, (float*)ws, st);
   return launch_status();
@@ -201,7 +205,10 @@ int poetx_cnp_bwd(const float* theta, const float* dG, int32_t d, int32_t b, int
   StageTimer tm(POETX_STAGE_CNP_BWD, st);
   if (precision == POETX_CNP_BF16 && !g_force_fma.load() && mfma_cnp_supported(d, b))
     mfma_cnp_bwd(theta, dG, d, b, k, dtheta, accumulate != 0, (float*)ws, st);
-  else
+  else if (series_small(b)) {
+    const SeriesSide side{theta, dG, 0, 1, d, dtheta};
+    series_small_bwd(&side, 1, b, k, accumulate != 0, st);
+  } else
     fma_cnp_bwd(theta, dG, d, b, k, dtheta, accumulate != 0, (float*)ws, st);
   return launch_status();
 }
@@ -402,6 +409,9 @@ static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
   const size_t both = cnp_bwd_ws_floats_both(desc->d_in, desc->d_out, desc->block, desc->neumann_k);
   if (both > chain) chain = both;
   size_t skew = align256(chain * sizeof(float)) + (bg_in > bg_out ? bg_in : bg_out);
+  const size_t parts = align256(edge_blockgrad_parts_bytes(desc->dtype, desc->d_in, desc->n_tokens, desc->block)) +
+                       align256(edge_blockgrad_parts_bytes(desc->dtype, desc->d_out, desc->n_tokens, desc->block));
+  if (series_small_supported(desc->block) && parts > skew) skew = parts;
   size_t w = fwd > bwi ? fwd : bwi;
   if (skew > w) w = skew;
   // poetx_linear_bwd keeps dA (and, on its one-pass path, dB) in the workspace next to what the two
@@ -563,6 +573,26 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
       blockgrad_dispatch(dt, X, dA, m, N, perm_R, b, dG + nbP * bb, bg_ws, st);       // dG_R = X' dA'^T
     }
     cnp_bwd_both_on_chip(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);
+    return;
+  }
+  if (!defer && series_small(b)) {
+    // Both sides' block gradients, still split over token ranges, then one launch that adds the parts, runs the
+    // series backward and projects.  The P side's parts sit where the other paths keep dG and the chain.
+    SeriesSide sides[2];
+    char* at = (char*)ws;
+    for (int i = 0; i < 2; ++i) {
+      const int d = i == 0 ? n : m;
+      sides[i].theta = i == 0 ? theta_P : theta_R;
+      sides[i].dtheta = i == 0 ? dtheta_P : dtheta_R;
+      sides[i].d = d;
+      sides[i].dG = (const float*)at;
+      sides[i].split_stride = (i64)ceil_div(d, b) * b * b;
+      StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
+      sides[i].nsplit = edge_blockgrad_parts(dt, i == 0 ? saved_B : X, N, i == 0 ? dZ : dA, N, d, N, i == 0 ? perm_P : perm_R, b, (float*)at, st);
+      at += align256(edge_blockgrad_parts_bytes(dt, d, N, b));
+    }
+    StageTimer tm(POETX_STAGE_CNP_BWD, st);
+    series_small_bwd(sides, 2, b, k, accumulate != 0, st);
     return;
   }
   float* dG = (float*)ws;

@@ -46,6 +46,22 @@ void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int 
 size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b);
 void edge_blockgrad(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
                     hipStream_t st);
+// The same, left as its token-range parts (each ceil(d/b) * b * b floats, one after the other at `parts`); returns how many.
+size_t edge_blockgrad_parts_bytes(int dtype, int d, i64 N, int b);
+int edge_blockgrad_parts(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* parts,
+                         hipStream_t st);
+
+// ---- fp32 series of blocks up to 128, one launch (series_small.hip) ----------------------------------------
+bool series_small_supported(int b);
+void series_small_build(const float* theta, int d, int b, int k, float* G_f32, void* E_bf16, hipStream_t st);
+struct SeriesSide {
+  const float* theta;
+  const float* dG;        // nsplit block gradients of ceil(d/b) * b * b floats, split_stride floats apart, that add up to dL/dG
+  i64 split_stride;
+  int nsplit, d;
+  float* dtheta;
+};
+void series_small_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumulate, hipStream_t st);   // one or two sides
 
 // dtheta[j][idx(i,c)] (+)= M[j][i][c] - M[j][c][i] (Sec. 3.4: gradient on the packed parameters).
 void skew_project_launch(const float* M, int b, int d, float* dtheta, int accumulate, hipStream_t st);

@@ -58,3 +58,38 @@ def test_apply_off_alignment(lib, d, b, cols, off, dtype):
         torch.cuda.synchronize()
         assert rel_err(to_np(out), orc.apply_left(V, pi, E + eye, trans)) <= TOL[dtype]
         assert torch.all(buf[:off] == -7.0) and torch.all(buf[off + d * cols:] == -7.0)
+
+
+@pytest.mark.parametrize("b", [2, 15, 16, 31, 33, 64, 65, 128])
+@pytest.mark.parametrize("k", [1, 2, 5])
+def test_small_block_series(lib, b, k):
+    """The one-launch fp32 series (block sides up to 128, padded to 32 / 64 / 128 on chip): build and backward against
+    the oracle in fp32 accuracy (sums of at most 128 k fp32 terms), ragged last block with loud dead slots, accumulate."""
+    d = 2 * b + b // 2 + 1 if b > 2 else 5
+    rng = np.random.Generator(np.random.PCG64(9200 + b + k))
+    nb, L = orc.n_blocks(d, b), b * (b - 1) // 2
+    theta = round_f32(rng.standard_normal((nb, L)) * 0.02)
+    r = orc.tail_side(d, b)
+    iu, ju = np.triu_indices(b, k=1)
+    dead = (iu >= r) | (ju >= r)
+    theta[-1, dead] = 9.0
+    th = to_dev(theta, torch.float32)
+    G = torch.empty((nb, b, b), dtype=torch.float32, device="cuda")
+    E = torch.empty((nb, 2, b, b), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(max(lib.poetx_cnp_workspace_bytes(d, b), lib.poetx_cnp_bwd_workspace_bytes(d, b, k)), dtype=torch.uint8, device="cuda")
+    lib.poetx_cnp_build(th, d, b, k, lib.CNP_FP32, G, E, ws)
+    Q = orc.skew_from_packed(theta, b, d)
+    ref = orc.cnp(Q, k)
+    eye = np.eye(b)
+    assert rel_err(to_np(G) - eye, ref - eye) <= 1e-5
+    assert rel_err(to_np(E)[:, 0], ref - eye) <= 2.0 ** -8
+    assert torch.equal(E[:, 1], E[:, 0].transpose(1, 2))
+    assert np.array_equal(to_np(G)[-1, r:], np.eye(b)[r:]) and np.array_equal(to_np(G)[-1, :, r:], np.eye(b)[:, r:])
+    dG = round_f32(rng.standard_normal((nb, b, b)))
+    want = orc.packed_from_skew_grad(orc.cnp_bwd(Q, dG, k), b, d)
+    for acc, start in ((False, float("nan")), (True, 1.0)):
+        dth = torch.full_like(th, start)
+        lib.poetx_cnp_bwd(th, to_dev(dG, torch.float32), d, b, k, lib.CNP_FP32, dth, acc, ws)
+        got = to_np(dth) - (1.0 if acc else 0.0)
+        assert rel_err(got, want) <= 1e-5
+        assert np.all(got[-1, dead] == 0)

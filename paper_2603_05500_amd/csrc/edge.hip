@@ -33,7 +33,32 @@ Plan pick_plan(i64 batches, i64 M, i64 N, i64 K, size_t es, bool may_split) {
 }
 
 Plan dense_plan(int dtype, i64 M, i64 N, i64 K) { return pick_plan(1, M, N, K, dtype == POETX_F32 ? 4 : 2, true); }
-Plan grad_plan(int dtype, int d, i64 N, int b) { return pick_plan(ceil_div(d, b), b, b, N, dtype == POETX_F32 ? 4 : 2, true); }
+// Block gradients: the contraction is the token range, so a large tile with a split costs only its fp32 parts, while
+// every halving of the tile side doubles the reads of both activations.  A split keeps four stages.
+Plan grad_plan(int dtype, int d, i64 N, int b) {
+  const int nb = ceil_div(d, b);
+  Plan p{TILE_32, 1};
+  int side = 32;
+  i64 depth = 128, least = 2;
+  for (const int t : {128, 64}) {
+    const i64 dep = t == 128 && dtype == POETX_F32 ? 32 : 64, stages = (N + dep - 1) / dep;
+    if (b >= t && tile_count(nb, b, b, t) * (stages / 4 > 1 ? stages / 4 : 1) >= kCUs * 3 / 4) {
+      p.tile = t == 128 ? TILE_128 : TILE_64;
+      side = t;
+      depth = dep;
+      least = 4;
+      break;
+    }
+  }
+  const i64 count = tile_count(nb, b, b, side), stages = (N + depth - 1) / depth;
+  i64 s = 2 * kCUs / count;
+  if (s > stages / least) s = stages / least;
+  if (s > 1) {
+    const i64 per = (stages + s - 1) / s;
+    p.splits = (int)((stages + per - 1) / per);
+  }
+  return p;
+}
 
 // ---- epilogues ---------------------------------------------------------------------------------
 template <class T>

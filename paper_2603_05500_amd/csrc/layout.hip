@@ -11,10 +11,11 @@ namespace {
 
 constexpr int TT = 64;   // tile side in elements
 
-// in: R x C row major (ld_in), out: C x R row major (ld_out).  One 64 x 64 tile per workgroup.
+// in: R x C row major (ld_in), out: C x R_out row major (ld_out), columns R .. R_out - 1 written as zeros.  One 64 x 64
+// tile per workgroup.
 template <class T>
 __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in, T* __restrict__ out, i64 R, i64 C,
-                                                        i64 ld_in, i64 ld_out) {
+                                                        i64 ld_in, i64 ld_out, i64 R_out) {
   constexpr int V = 16 / sizeof(T);          // elements per 16-byte vector
   constexpr int VPR = TT / V;                // vectors per tile row
   constexpr int RPP = 256 / VPR;             // tile rows per pass
@@ -50,24 +51,24 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
   } else {   // ragged edge or unaligned: element by element
     for (int i = tid; i < TT * TT; i += 256) {
       const int r = i / TT, c = i % TT;
-      if (r0 + r < R && c0 + c < C) tile[r][c] = in[(r0 + r) * ld_in + c0 + c];
+      tile[r][c] = r0 + r < R && c0 + c < C ? in[(r0 + r) * ld_in + c0 + c] : T(0);
     }
     __syncthreads();
     for (int i = tid; i < TT * TT; i += 256) {
       const int c = i / TT, r = i % TT;
-      if (r0 + r < R && c0 + c < C) out[(c0 + c) * ld_out + r0 + r] = tile[r][c];
+      if (r0 + r < R_out && c0 + c < C) out[(c0 + c) * ld_out + r0 + r] = tile[r][c];
     }
   }
 }
 
 }  // namespace
 
-void transpose_launch(int dtype, const void* in, void* out, i64 R, i64 C, hipStream_t st) {
-  dim3 grid((unsigned)ceil_div(C, TT), (unsigned)ceil_div(R, TT));
+void transpose_launch(int dtype, const void* in, void* out, i64 R, i64 C, i64 ld_in, i64 ld_out, i64 R_out, hipStream_t st) {
+  dim3 grid((unsigned)ceil_div(C, TT), (unsigned)ceil_div(R_out, TT));
   if (dtype == POETX_F32)
-    hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(256), 0, st, (const float*)in, (float*)out, R, C, C, R);
+    hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(256), 0, st, (const float*)in, (float*)out, R, C, ld_in, ld_out, R_out);
   else
-    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)in, (uint16_t*)out, R, C, C, R);
+    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)in, (uint16_t*)out, R, C, ld_in, ld_out, R_out);
 }
 
 }  // namespace poetx

@@ -5,17 +5,11 @@
 // with E = G - I, so neither the permutation nor the orthogonal matrix is ever
 // materialised and the identity part of G is carried exactly.
 //
-// The stage is HBM bound (b/2 flop per byte), so the kernel is organised around
-// the memory stream: one workgroup owns block j and a tile of BN tokens, gathers
-// the b rows of that tile once into LDS (each row is a contiguous run of tokens,
-// so the gather is coalesced), multiplies from LDS with transposing reads, adds
-// the identity term from the same LDS tile, writes the result back into the tile
-// and streams it out with the same coalesced row pattern (scatter by the same
-// index map).  The block operand op(E_j) is read straight from global memory in
-// matrix-core fragment order: blocks are stored as the pair (E, E^T) so that
-// op(E)(i, .) is always a contiguous row; the pair stays L2 resident because every
-// token tile of block j reuses it.
-#include "mfma_gemm.h"
+// The stage is HBM bound (b/2 flop per byte), so the kernels are organised around the memory stream: the
+// gathered rows of a block are contiguous runs of tokens, pass through LDS once, are multiplied from there with
+// transposing reads and leave with the same row pattern (scatter by the same index map).  Blocks are stored as
+// the pair (E, E^T) so that op(E)(i, .) is always a contiguous row.
+#include "edge_gemm.h"
 
 namespace poetx {
 namespace {
@@ -25,113 +19,8 @@ using mm::floatx16;
 using mm::short4v;
 using mm::short8v;
 
-// Row pad of the gathered [l][token] tile: 32 elements (64 B) spreads the four l rows one
-// transposing read touches over different bank groups.
-constexpr int PAD_T = 32;
-
-// 32 x 16 matrix-core operand fragment from a padded [k][x] LDS tile (row stride `stride`
-// elements): lane gets column x0 + lane%32 and contraction elements k0 + 8*(lane/32) + 0..7.
-__device__ inline bf16x8 frag_from_kx(const uint16_t* tile, int stride, int k0, int x0, int lane) {
-  const int q = lane >> 4, i = lane & 15;
-  const uint16_t* p = tile + (k0 + 8 * (q >> 1) + (i >> 2)) * stride + x0 + 16 * (q & 1) + 4 * (i & 3);
-  short4v lo = mm::lds_read_tr((const char*)p);
-  short4v hi = mm::lds_read_tr((const char*)(p + 4 * stride));
-  short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  return __builtin_bit_cast(bf16x8, v);
-}
-
-// B: block side.  BN: tokens per workgroup.  4 waves, wave w owns output rows
-// [w*B/4, (w+1)*B/4) for all BN tokens.
-template <int B, int BN>
-__global__ __launch_bounds__(256) void apply_left_bf16_kernel(const uint16_t* __restrict__ V, uint16_t* __restrict__ out,
-                                                               i64 ld, const int32_t* __restrict__ perm,
-                                                               const uint16_t* __restrict__ blocks, int trans) {
-  constexpr int SX = BN + PAD_T;
-  constexpr int TM = B / 4 / 32, TN = BN / 32;
-  constexpr int CPR = BN / 8;                 // 16-byte chunks per row
-  constexpr int CHUNKS = B * CPR / 256;       // per thread
-  constexpr int ROWS_PER_PASS = 256 / CPR;
-  extern __shared__ __attribute__((aligned(16))) uint16_t xs[];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int j = blockIdx.y;
-  const i64 t0 = (i64)blockIdx.x * BN;
-  const int32_t* pm = perm + (i64)j * B;
-  const int crow = tid / CPR, cch = tid % CPR;
-
-  // gather: rows pi[j*B + l] of V, BN tokens each
-#pragma unroll 4
-  for (int s = 0; s < CHUNKS; ++s) {
-    const int row = crow + s * ROWS_PER_PASS;
-    const uint4 v = *reinterpret_cast<const uint4*>(V + (i64)pm[row] * ld + t0 + cch * 8);
-    *reinterpret_cast<uint4*>(xs + row * SX + cch * 8) = v;
-  }
-  __syncthreads();
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int a = 0; a < TM; ++a)
-#pragma unroll
-    for (int c = 0; c < TN; ++c)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
-
-  const int li = lane & 31, h = lane >> 5;
-  const int row0 = wave * (B / 4);
-  const uint16_t* Eb = blocks + ((i64)j * 2 + (trans ? 1 : 0)) * B * B + (i64)(row0 + li) * B + 8 * h;
-
-  bf16x8 fa[TM], fa_next[TM];
-#pragma unroll
-  for (int a = 0; a < TM; ++a) fa[a] = *reinterpret_cast<const bf16x8*>(Eb + (i64)a * 32 * B);
-#pragma unroll 4
-  for (int ks = 0; ks < B / 16; ++ks) {
-    if (ks + 1 < B / 16) {
-#pragma unroll
-      for (int a = 0; a < TM; ++a) fa_next[a] = *reinterpret_cast<const bf16x8*>(Eb + (i64)a * 32 * B + (ks + 1) * 16);
-    }
-    bf16x8 fb[TN];
-#pragma unroll
-    for (int c = 0; c < TN; ++c) fb[c] = frag_from_kx(xs, SX, ks * 16, c * 32, lane);
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-      for (int c = 0; c < TN; ++c)
-        acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[c], fa[a], acc[a][c], 0, 0, 0);
-#pragma unroll
-    for (int a = 0; a < TM; ++a) fa[a] = fa_next[a];
-  }
-  __syncthreads();  // every wave is done reading the gathered tile
-
-  // identity term + rounding, in place: lane owns row (row0 + a*32 + li), tokens c*32 + 8q + 4h .. +3
-#pragma unroll
-  for (int a = 0; a < TM; ++a)
-#pragma unroll
-    for (int c = 0; c < TN; ++c)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        uint16_t* p = xs + (row0 + a * 32 + li) * SX + c * 32 + 8 * q + 4 * h;
-        const uint2 x = *reinterpret_cast<const uint2*>(p);
-        uint2 o;
-        o.x = mm::pack2_bf16(acc[a][c][4 * q + 0] + bf16_bits_to_float((uint16_t)(x.x & 0xFFFF)),
-                             acc[a][c][4 * q + 1] + bf16_bits_to_float((uint16_t)(x.x >> 16)));
-        o.y = mm::pack2_bf16(acc[a][c][4 * q + 2] + bf16_bits_to_float((uint16_t)(x.y & 0xFFFF)),
-                             acc[a][c][4 * q + 3] + bf16_bits_to_float((uint16_t)(x.y >> 16)));
-        *reinterpret_cast<uint2*>(p) = o;
-      }
-  __syncthreads();
-
-  // scatter: same row map, coalesced 16-byte stores
-#pragma unroll 4
-  for (int s = 0; s < CHUNKS; ++s) {
-    const int row = crow + s * ROWS_PER_PASS;
-    const uint4 v = *reinterpret_cast<const uint4*>(xs + row * SX + cch * 8);
-    *reinterpret_cast<uint4*>(out + (i64)pm[row] * ld + t0 + cch * 8) = v;
-  }
-}
-
-
 // ---------------------------------------------------------------------------------------
-// Streaming variant: one persistent workgroup per (block, 256-row slice of it, token range).
+// One persistent workgroup per (block, 256-row slice of it, token range).
 //   * 8 waves; wave w owns 32 output rows of the slice for computing and storing.
 //   * those rows of op(E_j) stay in registers as matrix-core fragments for the whole range
 //     (B/16 k steps x 4 VGPRs), so the block operand is read once per workgroup.
@@ -351,26 +240,184 @@ void launch_apply_stream(const uint16_t* V, uint16_t* out, int d, i64 cols, i64 
 }
 constexpr int SBN256 = 128, SBN512 = 64;   // tokens per tile of the streaming kernel
 
-template <int B, int BN>
-void launch_apply(const uint16_t* V, uint16_t* out, int d, i64 cols, i64 ld, const int32_t* perm, const uint16_t* E,
-                  int trans, hipStream_t st) {
-  constexpr size_t LDS = (size_t)B * (BN + PAD_T) * sizeof(uint16_t);
-  auto kern = apply_left_bf16_kernel<B, BN>;
+// ---------------------------------------------------------------------------------------
+// The streaming kernel for token counts and row strides of any kind (V: nv columns, row stride ldv; out: no columns, row
+// stride ldo; columns nv .. no - 1 of out are zeros).  Direct-to-LDS loads need aligned rows, so the tiles come through
+// registers (element-aligned 16-byte loads, masked at the last column) -- the loads of tile t + 1 are in flight while
+// tile t is multiplied and are written to the other LDS stage after it -- and the output pieces are stored element
+// aligned.  Everything else is the kernel above at 64 tokens per tile (128 leave no registers for the staging).
+// 8192 x 4090, b = 256: 43 us = 3.1 TB/s (128 x 128 edge tiles, which read rows twice and the block once per tile: 94 us;
+// the aligned kernel at 4096 tokens: 27 us).
+template <int B>
+__global__ __launch_bounds__(512) void apply_left_ragged_kernel(const uint16_t* __restrict__ V, uint16_t* __restrict__ out, i64 ldv, i64 ldo,
+                                                                 int nv, int no, const int32_t* __restrict__ perm,
+                                                                 const uint16_t* __restrict__ blocks, int trans, int tiles, int tiles_per_wg) {
+  constexpr int BN = 64, MSPLIT = B / 256, TN = BN / 32, KS = B / 16;
+  constexpr int STAGE_BYTES = B * BN * 2;
+  constexpr int CPR = BN / 8, RPI = 64 / CPR, IPW = STAGE_BYTES / 1024 / 8;
+  extern __shared__ __attribute__((aligned(1024))) char ring[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = blockIdx.y, slice = blockIdx.x % MSPLIT, chunk = blockIdx.x / MSPLIT;
+  const int first = chunk * tiles_per_wg;
+  const int T = tiles - first < tiles_per_wg ? tiles - first : tiles_per_wg;
+  if (T <= 0) return;
+  const int tok0 = first * BN;
+  const int32_t* pm = perm + (i64)j * B;
+  const int li = lane & 31, h = lane >> 5;
+
+  i64 goff[IPW];
+  int gcol[IPW];
+#pragma unroll
+  for (int s = 0; s < IPW; ++s) {
+    const int k = (wave * IPW + s) * RPI + lane / CPR;
+    goff[s] = (i64)pm[k] * ldv;
+    gcol[s] = tok0 + mm::kx_unchunk<BN>(lane % CPR, k) * 8;
+  }
+  edge::u32x4 stage_regs[IPW];
+  auto gload = [&](int t) {
+#pragma unroll
+    for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load_masked<uint16_t>(V + goff[s], gcol[s] + t * BN, nv, true);
+  };
+  auto lstore = [&](int t) {
+    char* stage = ring + (t & 1) * STAGE_BYTES + wave * IPW * 1024 + lane * 16;
+#pragma unroll
+    for (int s = 0; s < IPW; ++s) *reinterpret_cast<edge::u32x4*>(stage + s * 1024) = stage_regs[s];
+  };
+  gload(0);
+
+  const int row_own = slice * 256 + wave * 32 + li;
+  const uint16_t* Eb = blocks + ((i64)j * 2 + (trans ? 1 : 0)) * B * B + (i64)row_own * B + 8 * h;
+  bf16x8 fa[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) fa[ks] = *reinterpret_cast<const bf16x8*>(Eb + ks * 16);
+  bf16x8 fi[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) fi[u][e] = (li == u * 16 + 8 * h + e) ? (__bf16)1.0f : (__bf16)0.0f;
+  const int own_kpair = slice * 8 + wave;
+
+  int fragB[TN];
+  {
+    const int q = lane >> 4, i = lane & 15;
+    const int k = 8 * (q >> 1) + (i >> 2);
+#pragma unroll
+    for (int c2 = 0; c2 < TN; ++c2) {
+      const int c = c2 * 4 + 2 * (q & 1) + ((i & 3) >> 1);
+      fragB[c2] = k * (BN * 2) + 16 * mm::kx_chunk<BN>(c, k) + 8 * (i & 1);
+    }
+  }
+  char* stg = ring + 2 * STAGE_BYTES + wave * 4096;   // per-wave output staging, see the kernel above
+  const int stg_w = li * 128 + 16 * (h ^ ((li >> 1) & 7));
+  i64 soff[4];
+  int stg_r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = (lane >> 3) + 8 * i;
+    soff[i] = (i64)pm[slice * 256 + wave * 32 + r] * ldo;
+    stg_r[i] = r * 128 + 16 * ((lane & 7) ^ ((r >> 1) & 7));
+  }
+  const int scol = tok0 + 8 * (lane & 7);
+  edge::u32x4 pend[4];
+  auto flush = [&](int t) {
+    const int col = scol + t * BN;
+    if (col + 8 <= no) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<edge::u32x4_a2*>(out + soff[i] + col) = pend[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 7; ++e)
+          if (col + e < no) out[soff[i] + col + e] = (uint16_t)(pend[i][e >> 1] >> (16 * (e & 1)));
+    }
+  };
+  lstore(0);
+  for (int t = 0; t < T; ++t) {
+    // tile t is in LDS, and every wave is done reading the stage that tile t + 1 will overwrite
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (t + 1 < T) gload(t + 1);
+    if (t > 0) flush(t - 1);
+    const char* stage = ring + (t & 1) * STAGE_BYTES;
+    auto load_tok = [&](bf16x8* fb, int ks) {
+#pragma unroll
+      for (int c = 0; c < TN; ++c) {
+        const char* p = stage + fragB[c] + ks * 16 * (BN * 2);
+        short4v lo = mm::lds_read_tr(p);
+        short4v hi = mm::lds_read_tr(p + 4 * (BN * 2));
+        short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        fb[c] = __builtin_bit_cast(bf16x8, v);
+      }
+    };
+    floatx16 acc[TN];
+#pragma unroll
+    for (int c = 0; c < TN; ++c)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+    bf16x8 fo[2][TN], fb[2][TN];
+    load_tok(fo[0], 2 * own_kpair);
+    load_tok(fo[1], 2 * own_kpair + 1);
+    load_tok(fb[0], 0);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int c = 0; c < TN; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[u][c], fi[u], acc[c], 0, 0, 0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks + 1 < KS) load_tok(fb[(ks + 1) & 1], ks + 1);
+#pragma unroll
+      for (int c = 0; c < TN; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks & 1][c], fa[ks], acc[c], 0, 0, 0);
+    }
+#pragma unroll
+    for (int cl = 0; cl < TN; ++cl) {
+      uint32_t w[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] = mm::pack2_bf16(acc[cl][2 * e], acc[cl][2 * e + 1]);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+        const uint2v r0 = __builtin_amdgcn_permlane32_swap(w[4 * p], w[4 * p + 2], false, false);
+        const uint2v r1 = __builtin_amdgcn_permlane32_swap(w[4 * p + 1], w[4 * p + 3], false, false);
+        *reinterpret_cast<edge::u32x4*>(stg + (stg_w ^ (16 * (cl * 4 + 2 * p)))) = edge::u32x4{r0[0], r1[0], r0[1], r1[1]};
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pend[i] = *reinterpret_cast<const edge::u32x4*>(stg + stg_r[i]);
+    if (t + 1 < T) lstore(t + 1);
+  }
+  flush(T - 1);
+}
+
+// Token ranges per block slice: the fewest tile times on 256 CUs, a workgroup's lead-in (block operand, first tile) counted as
+// three tiles.
+template <int B>
+void launch_apply_ragged(const uint16_t* V, i64 ldv, i64 nv, uint16_t* out, i64 ldo, i64 no, int d, const int32_t* perm, const uint16_t* E,
+                         int trans, hipStream_t st) {
+  constexpr size_t LDS = 2 * (size_t)B * 64 * 2 + 8 * 4096;
+  constexpr int MSPLIT = B / 256;
+  auto kern = apply_left_ragged_kernel<B>;
   // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS) == hipSuccess;
   (void)configured;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(cols / BN), d / B), dim3(256), LDS, st, V, out, ld, perm, E, trans);
+  const int nb = d / B, tiles = ceil_div(no, 64);
+  int per = tiles;
+  i64 best = 0;
+  for (int p = 1; p <= tiles; ++p) {
+    const i64 rounds = ((i64)nb * MSPLIT * ceil_div(tiles, p) + 255) / 256, cost = rounds * (p + 3);
+    if (best == 0 || cost < best) { best = cost; per = p; }
+  }
+  hipLaunchKernelGGL(kern, dim3(ceil_div(tiles, per) * MSPLIT, nb), dim3(512), LDS, st, V, out, ldv, ldo, (int)nv, (int)no, perm, E, trans, tiles, per);
 }
-
-constexpr int BN256 = 128, BN512 = 64;
 
 }  // namespace
 
 bool mfma_apply_left_supported(int d, i64 cols, i64 ld, int b) {
   if (d % b != 0 || ld % 8 != 0) return false;
-  if (b == 256) return cols % BN256 == 0;
-  if (b == 512) return cols % BN512 == 0;
+  if (b == 256) return cols % SBN256 == 0;
+  if (b == 512) return cols % SBN512 == 0;
   return false;
 }
 
@@ -380,10 +427,18 @@ void mfma_apply_left(const void* V, void* out, int d, i64 cols, i64 ld, const in
     launch_apply_stream<256, SBN256>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
   else if (b == 512 && cols % (2 * SBN512) == 0)
     launch_apply_stream<512, SBN512>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
-  else if (b == 256)
-    launch_apply<256, BN256>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
-  else
-    launch_apply<512, BN512>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
+  else   // an odd number of tiles
+    mfma_apply_left_ragged(V, ld, cols, out, ld, cols, d, perm, E, b, transpose_G, st);
+}
+
+// From a few 64-token tiles on the streaming form wins over the edge kernel, which reads the block operand once per tile (256 columns
+// is where a workgroup has a second tile to overlap with; not tuned finer).
+bool mfma_apply_left_ragged_supported(int d, i64 cols_out, int b) { return (b == 256 || b == 512) && d % b == 0 && cols_out >= 256; }
+
+void mfma_apply_left_ragged(const void* V, i64 ldv, i64 cols, void* out, i64 ldo, i64 cols_out, int d, const int32_t* perm, const void* E, int b,
+                            int transpose_G, hipStream_t st) {
+  if (b == 256) launch_apply_ragged<256>((const uint16_t*)V, ldv, cols, (uint16_t*)out, ldo, cols_out, d, perm, (const uint16_t*)E, transpose_G, st);
+  else launch_apply_ragged<512>((const uint16_t*)V, ldv, cols, (uint16_t*)out, ldo, cols_out, d, perm, (const uint16_t*)E, transpose_G, st);
 }
 
 }  // namespace poetx

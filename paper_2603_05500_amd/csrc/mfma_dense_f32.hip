@@ -116,6 +116,11 @@ __global__ __launch_bounds__(256) void dense_f32_kernel(Args g) {
 
 bool mfma_dense_f32_supported(int n, int m, i64 N) { return n % BM == 0 && m % BM == 0 && N % BN == 0; }
 
+// One 128 x 128 tile per workgroup and no split of the contraction: with fewer tiles than three quarters of the CUs
+// the edge kernel's smaller tiles and splits win (forward of 1024 x 1024 x 2048, 128 tiles: 115 against 102 us;
+// 256 x 256 x 512: 32 against 18), above it this kernel does (2048 x 2048 x 4096, 512 tiles: 391 against 471 us).
+bool mfma_dense_f32_fills(int M, i64 N) { return (i64)(M / BM) * (N / BN) >= 192; }
+
 void mfma_dense_f32(int trans_w, const void* W, int n, int m, const void* act, void* out, i64 N, hipStream_t st) {
   Args g{(const float*)W, (const float*)act, (float*)out, n, m, N, trans_w ? n : m};
   const int M = trans_w ? m : n;

@@ -48,6 +48,7 @@ struct DenseArgs {
   uint16_t* C;           // M x N row major
   i64 lda, ldb, ldc;
   int tiles_m, tiles_n, ktiles;   // ktiles counts 32-deep stages
+  int cols;              // RAGGED: columns of C that exist; its rows need element alignment only
 };
 
 // 16 bytes per lane from (uniform base + per-lane byte offset + OFF) straight into LDS at
@@ -79,7 +80,8 @@ static __device__ long long g_diag_cycles[4][4 * 256];
 // the first stage of the first tile (all loads hit in cache) -- the results are then wrong,
 // bit 3 (harmless to the result) records the cycle counts above --
 // every address stays what it was, and the timing shows what the loads or the reads cost.
-template <bool A_KMAJOR, int DIAG = 0>
+// RAGGED: the last tiles of a row reach past the columns of C (B is padded to whole tiles, C is not).
+template <bool A_KMAJOR, bool RAGGED = false, int DIAG = 0>
 __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -333,7 +335,20 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
             for (int i = 0; i < 4; ++i) {
               const int r = (lane >> 3) + 8 * i, ch = lane & 7;
               const u32x4 o = *reinterpret_cast<const u32x4*>(stg + cp * 4096 + r * 128 + 16 * (ch ^ ((r >> 1) & 7)));
-              *reinterpret_cast<u32x4*>(Cw + (i64)(a * 32 + r) * g.ldc + cp * 64 + ch * 8) = o;
+              uint16_t* at = Cw + (i64)(a * 32 + r) * g.ldc + cp * 64 + ch * 8;
+              if constexpr (RAGGED) {
+                typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+                const int left = g.cols - (j0 + wn * (BN / 2) + cp * 64 + ch * 8);
+                if (left >= 8) {
+                  *reinterpret_cast<u32x4_a2*>(at) = o;
+                } else {
+#pragma unroll
+                  for (int e = 0; e < 7; ++e)
+                    if (e < left) at[e] = (uint16_t)(o[e >> 1] >> (16 * (e & 1)));
+                }
+              } else {
+                *reinterpret_cast<u32x4*>(at) = o;
+              }
             }
         }
       }

@@ -77,29 +77,45 @@ size_t cnp_bwd_ws_floats_both(int m, int n, int b, int k) {
   return per_elem * (ceil_div(m, b) + ceil_div(n, b)) * b * b;
 }
 
-void apply_left_dispatch(int dtype, const void* V, void* out, int d, i64 cols, i64 ld, const int32_t* perm,
-                         const void* blocks, int b, int trans, hipStream_t st) {
+// A d x cols activation, row stride ld.  Activations in the workspace have internal_columns() columns, the ones past
+// the call's tokens being zeros (zeros stay zeros through every stage), so that the streaming kernels can run on whole
+// tiles whatever the token count; a caller's tensors have exactly its tokens.
+struct Act {
+  const void* p;
+  i64 ld, cols;
+  void* out() const { return const_cast<void*>(p); }
+};
+inline i64 min64(i64 a, i64 b) { return a < b ? a : b; }
+
+void apply_left_dispatch(int dtype, const Act& V, const Act& out, int d, const int32_t* perm, const void* blocks, int b, int trans,
+                         hipStream_t st) {
   StageTimer tm(POETX_STAGE_APPLY, st);
-  if (use_mfma(dtype) && mfma_apply_left_supported(d, cols, ld, b) && aligned16(V) && aligned16(out) && aligned16(blocks))
-    mfma_apply_left(V, out, d, cols, ld, perm, blocks, b, trans, st);
+  if (use_mfma(dtype) && V.ld == out.ld && V.cols == out.cols && mfma_apply_left_supported(d, V.cols, V.ld, b) && aligned16(V.p) &&
+      aligned16(out.p) && aligned16(blocks))
+    mfma_apply_left(V.p, out.out(), d, V.cols, V.ld, perm, blocks, b, trans, st);
+  else if (use_mfma(dtype) && mfma_apply_left_ragged_supported(d, out.cols, b) && aligned16(blocks))
+    mfma_apply_left_ragged(V.p, V.ld, min64(V.cols, out.cols), out.out(), out.ld, out.cols, d, perm, blocks, b, trans, st);
   else if (!g_force_fma.load())
-    edge_apply_left(dtype, V, ld, out, ld, d, cols, cols, perm, blocks, b, trans, st);
+    edge_apply_left(dtype, V.p, V.ld, out.out(), out.ld, d, min64(V.cols, out.cols), out.cols, perm, blocks, b, trans, st);
   else
-    fma_apply_left(dtype, V, out, d, cols, ld, perm, blocks, b, trans, st);
+    fma_apply_left(dtype, V.p, out.out(), d, V.cols, V.ld, perm, blocks, b, trans, st);
 }
 
 // part: scratch of dense_part_bytes() for products that split their contraction.
 // w_q8: W is a quantised weight buffer that the product dequantises itself (see weight_in_kernel)
-void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const void* act, void* out, i64 N, void* part,
-                    hipStream_t st, bool w_q8 = false) {
+void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const Act& act, const Act& out, void* part, hipStream_t st,
+                    bool w_q8 = false) {
   StageTimer tm(POETX_STAGE_DENSE, st);
-  if (w_q8) mfma_dense_q8(trans_w, W, n, m, act, out, N, st);
-  else if (use_mfma(dtype) && mfma_dense_supported(n, m, N) && aligned16(W) && aligned16(act) && aligned16(out))
-    mfma_dense(trans_w, W, n, m, act, out, N, st);
-  else if (dtype == POETX_F32 && !g_force_fma.load() && mfma_dense_f32_supported(n, m, N) && aligned16(W) && aligned16(act) && aligned16(out))
-    mfma_dense_f32(trans_w, W, n, m, act, out, N, st);
-  else if (!g_force_fma.load()) edge_dense(dtype, trans_w, W, n, m, act, N, out, N, N, part, st);
-  else fma_dense(dtype, trans_w, W, n, m, act, out, N, st);
+  const i64 N = min64(act.cols, out.cols);
+  const bool whole = act.ld == act.cols && out.ld == out.cols && act.cols == out.cols;
+  if (w_q8) mfma_dense_q8(trans_w, W, n, m, act.p, out.out(), N, st);
+  else if (use_mfma(dtype) && act.ld == act.cols && mfma_dense_supported(n, m, act.cols) && aligned16(W) && aligned16(act.p))
+    mfma_dense(trans_w, W, n, m, act.p, act.cols, out.out(), out.ld, N, st);
+  else if (dtype == POETX_F32 && !g_force_fma.load() && whole && mfma_dense_f32_supported(n, m, N) && mfma_dense_f32_fills(trans_w ? m : n, N) &&
+           aligned16(W) && aligned16(act.p) && aligned16(out.p))
+    mfma_dense_f32(trans_w, W, n, m, act.p, out.out(), N, st);
+  else if (!g_force_fma.load()) edge_dense(dtype, trans_w, W, n, m, act.p, act.ld, out.out(), out.ld, N, part, st);
+  else fma_dense(dtype, trans_w, W, n, m, act.p, out.out(), N, st);
 }
 
 // POET-XQ: do the dense kernels read the 8-bit weight directly (conversion inside the operand path; asked for
@@ -108,29 +124,55 @@ bool weight_in_kernel(const poetx_linear_desc* d) {
   return (d->flags & POETX_FLAG_W_INT8) && (d->flags & POETX_FLAG_W_INT8_FUSED) && use_mfma(d->dtype) && mfma_dense_q8_supported(d->d_out, d->d_in, d->n_tokens);
 }
 
+// Columns of the activations in the workspace.  Shapes whose dense products the streaming kernel takes but for the token
+// count are padded to its 256-token tiles (see dense_worth_padding for when that pays); others to whole 16-byte
+// vectors, so that rows stay aligned.
+i64 internal_columns(const poetx_linear_desc* d) {
+  const i64 N = d->n_tokens;
+  if (g_force_fma.load()) return N;                     // the plain kernels know one token count only
+  const i64 Np = (N + 255) / 256 * 256;
+  if (d->dtype == POETX_BF16 && mfma_dense_supported(d->d_out, d->d_in, Np) && mfma_dense_worth_padding(d->d_out, d->d_in, Np)) return Np;
+  return (N + 7) / 8 * 8;
+}
+
 // Which kernels run also depends on the pointers (their alignment), which a workspace query does not see: the
-// queries below cover every path.
-size_t blockgrad_ws_bytes(int dtype, int d, i64 N, int b) {
-  size_t w = edge_blockgrad_workspace_bytes(dtype, d, N, b);
-  if (dtype == POETX_BF16 && mfma_blockgrad_supported(d, N, b)) {
-    const size_t f = mfma_blockgrad_workspace_bytes(d, N, b);
+// queries below cover every path, at every token count a stage may run with.
+size_t blockgrad_ws_bytes(const poetx_linear_desc* d, int dim) {
+  const i64 N = d->n_tokens, Ni = internal_columns(d);
+  size_t w = edge_blockgrad_workspace_bytes(d->dtype, dim, N, d->block);
+  const size_t e = edge_blockgrad_workspace_bytes(d->dtype, dim, Ni, d->block);
+  if (e > w) w = e;
+  if (d->dtype == POETX_BF16 && mfma_blockgrad_supported(dim, Ni, d->block)) {
+    const size_t f = mfma_blockgrad_workspace_bytes(dim, Ni, d->block);
     if (f > w) w = f;
   }
   return align256(w);
 }
+// both sides' block gradients as parts, for the one-launch series backward of small blocks
+size_t blockgrad_parts_bytes(const poetx_linear_desc* d, int dim) {
+  const size_t a = edge_blockgrad_parts_bytes(d->dtype, dim, d->n_tokens, d->block);
+  const size_t b = edge_blockgrad_parts_bytes(d->dtype, dim, internal_columns(d), d->block);
+  return align256(a > b ? a : b);
+}
 
 // Scratch of the dense products (partials of a split contraction), both directions.
 size_t dense_part_bytes(const poetx_linear_desc* d) {
-  const size_t f = edge_dense_workspace_bytes(d->dtype, d->d_out, d->n_tokens, d->d_in);
-  const size_t b = edge_dense_workspace_bytes(d->dtype, d->d_in, d->n_tokens, d->d_out);
-  return align256(f > b ? f : b);
+  size_t w = 0;
+  for (const i64 N : {(i64)d->n_tokens, internal_columns(d)}) {
+    const size_t f = edge_dense_workspace_bytes(d->dtype, d->d_out, N, d->d_in);
+    const size_t b = edge_dense_workspace_bytes(d->dtype, d->d_in, N, d->d_out);
+    w = f > w ? f : w;
+    w = b > w ? b : w;
+  }
+  return align256(w);
 }
 
-void blockgrad_dispatch(int dtype, const void* U, const void* V, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
-                        hipStream_t st) {
-  if (use_mfma(dtype) && mfma_blockgrad_supported(d, N, b) && aligned16(U) && aligned16(V)) mfma_blockgrad(U, V, d, N, perm, b, dG, ws, st);
-  else if (!g_force_fma.load()) edge_blockgrad(dtype, U, N, V, N, d, N, perm, b, dG, ws, st);
-  else fma_blockgrad(dtype, U, V, d, N, perm, b, dG, st);
+void blockgrad_dispatch(int dtype, const Act& U, const Act& V, int d, const int32_t* perm, int b, float* dG, void* ws, hipStream_t st) {
+  const i64 N = min64(U.cols, V.cols);
+  if (use_mfma(dtype) && U.ld == V.ld && N == U.ld && mfma_blockgrad_supported(d, N, b) && aligned16(U.p) && aligned16(V.p))
+    mfma_blockgrad(U.p, V.p, d, N, perm, b, dG, ws, st);
+  else if (!g_force_fma.load()) edge_blockgrad(dtype, U.p, U.ld, V.p, V.ld, d, N, perm, b, dG, ws, st);
+  else fma_blockgrad(dtype, U.p, V.p, d, N, perm, b, dG, st);
 }
 
 }  // namespace
@@ -238,7 +280,7 @@ int poetx_perm_blockdiag_apply_left(const void* V, void* out, int32_t d, int64_t
   if (cols >= (1ll << 31)) return POETX_ERR_UNSUPPORTED;
   size_t bytes = (size_t)d * ld * esize(dtype);
   if (overlap(V, bytes, out, bytes)) return POETX_ERR_INVALID_ARG;
-  apply_left_dispatch(dtype, V, out, d, cols, ld, perm, blocks, b, transpose_G != 0, (hipStream_t)stream);
+  apply_left_dispatch(dtype, Act{V, ld, cols}, Act{out, ld, cols}, d, perm, blocks, b, transpose_G != 0, (hipStream_t)stream);
   return launch_status();
 }
 
@@ -275,15 +317,15 @@ int poetx_merge_weight(const void* W, void* W_out, int32_t n, int32_t m, const i
   // W (n x m) is feature major for the output side (rows = output features): P^T W is a left apply.
   // The input side acts on the columns; a column gather is a row gather of the transpose, so the
   // product with R^T runs as R (P^T W)^T on the transposed matrix and is transposed back.
-  apply_left_dispatch(dtype, W, T1, n, m, m, perm_P, blocks_P, b, 1, st);        // T1 = P^T W         (n x m)
+  apply_left_dispatch(dtype, Act{W, m, m}, Act{T1, m, m}, n, perm_P, blocks_P, b, 1, st);        // T1 = P^T W         (n x m)
   {
     StageTimer tm(POETX_STAGE_LAYOUT, st);
-    transpose_launch(dtype, T1, T2, n, m, st);                                   // T2 = T1^T          (m x n)
+    transpose_launch(dtype, T1, T2, n, m, m, n, n, st);                                   // T2 = T1^T          (m x n)
   }
-  apply_left_dispatch(dtype, T2, T1, m, n, n, perm_R, blocks_R, b, 0, st);       // T1 = R T2          (m x n)
+  apply_left_dispatch(dtype, Act{T2, n, n}, Act{T1, n, n}, m, perm_R, blocks_R, b, 0, st);       // T1 = R T2          (m x n)
   {
     StageTimer tm(POETX_STAGE_LAYOUT, st);
-    transpose_launch(dtype, T1, W_out, m, n, st);                                // W_out = (R T2)^T = P^T W R^T
+    transpose_launch(dtype, T1, W_out, m, n, n, m, m, st);                                // W_out = (R T2)^T = P^T W R^T
   }
   return launch_status();
 }
@@ -311,12 +353,16 @@ static const void* resolve_weight(const poetx_linear_desc* desc, const void* W, 
   return scratch;
 }
 
+// Bytes of a workspace activation of `rows` features.
+static size_t act_bytes(const poetx_linear_desc* d, int rows) {
+  return align256((size_t)rows * (size_t)internal_columns(d) * esize(d->dtype));
+}
+
 // Token-major callers: feature-major copies of the call's activations (at most X, dZ / Z and dX)
 // live behind the regular workspace.
 static size_t layout_staging_bytes(const poetx_linear_desc* d) {
   if (d->layout != POETX_TOKEN_MAJOR) return 0;
-  const size_t es = esize(d->dtype), N = (size_t)d->n_tokens;
-  return 2 * align256((size_t)d->d_in * N * es) + align256((size_t)d->d_out * N * es);
+  return 2 * act_bytes(d, d->d_in) + act_bytes(d, d->d_out);
 }
 static size_t core_workspace_bytes(const poetx_linear_desc* desc);
 
@@ -347,40 +393,42 @@ int poetx_linear_path(const poetx_linear_desc* d) {
   return path;
 }
 
-// Feature-major <-> token-major copies around a call.  in(): the feature-major copy of a
-// token-major input (or the pointer itself); out(): where the call should write a feature-major
-// output; finish(): transposes the registered outputs into the caller's token-major buffers.
+// Feature-major <-> token-major copies around a call.  in(): the feature-major form of an input -- the caller's tensor
+// itself, or its transposed copy in the workspace (padded like every workspace activation); out(): where the call
+// should write a feature-major output; finish(): transposes the registered outputs into the caller's token-major
+// buffers.
 class LayoutStaging {
  public:
   LayoutStaging(const poetx_linear_desc* d, void* ws, hipStream_t st)
-      : on_(d->layout == POETX_TOKEN_MAJOR), dt_(d->dtype), N_(d->n_tokens), st_(st),
+      : d_(d), on_(d->layout == POETX_TOKEN_MAJOR), dt_(d->dtype), N_(d->n_tokens), Ni_(internal_columns(d)), st_(st),
         next_((char*)ws + core_workspace_bytes(d)), n_out_(0) {}
-  const void* in(const void* p, int rows) {
-    if (!on_ || !p) return p;
+  Act in(const void* p, int rows) {
+    if (!on_ || !p) return Act{p, N_, N_};
     void* t = take(rows);
     StageTimer tm(POETX_STAGE_LAYOUT, st_);
-    transpose_launch(dt_, p, t, N_, rows, st_);        // [N][rows] -> [rows][N]
-    return t;
+    transpose_launch(dt_, p, t, N_, rows, rows, Ni_, Ni_, st_);        // [N][rows] -> [rows][Ni], zeros past N
+    return Act{t, Ni_, Ni_};
   }
-  void* out(void* p, int rows) {
-    if (!on_ || !p) return p;
+  Act out(void* p, int rows) {
+    if (!on_ || !p) return Act{p, N_, N_};
     void* t = take(rows);
     outs_[n_out_].user = p; outs_[n_out_].tmp = t; outs_[n_out_].rows = rows; ++n_out_;
-    return t;
+    return Act{t, Ni_, Ni_};
   }
   void finish() {
     for (int i = 0; i < n_out_; ++i) {
       StageTimer tm(POETX_STAGE_LAYOUT, st_);
-      transpose_launch(dt_, outs_[i].tmp, outs_[i].user, outs_[i].rows, N_, st_);   // [rows][N] -> [N][rows]
+      transpose_launch(dt_, outs_[i].tmp, outs_[i].user, outs_[i].rows, N_, Ni_, outs_[i].rows, outs_[i].rows, st_);   // [rows][N] -> [N][rows]
     }
   }
  private:
   void* take(int rows) {
     void* t = next_;
-    next_ += align256((size_t)rows * N_ * esize(dt_));
+    next_ += act_bytes(d_, rows);
     return t;
   }
-  bool on_; int dt_; i64 N_; hipStream_t st_; char* next_;
+  const poetx_linear_desc* d_;
+  bool on_; int dt_; i64 N_, Ni_; hipStream_t st_; char* next_;
   struct { void* user; void* tmp; int rows; } outs_[2];
   int n_out_;
 };
@@ -389,43 +437,42 @@ class LayoutStaging {
 // of the call's dense products), sit at the very end of the workspace.
 static size_t recompute_tail_bytes(const poetx_linear_desc* desc) {
   if (!(desc->flags & POETX_FLAG_RECOMPUTE_B)) return 0;
-  return align256((size_t)desc->d_out * (size_t)desc->n_tokens * esize(desc->dtype)) + dequantised_weight_bytes(desc);
+  return act_bytes(desc, desc->d_out) + dequantised_weight_bytes(desc);
 }
 
 static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
-  size_t es = esize(desc->dtype);
-  size_t N = (size_t)desc->n_tokens;
-  size_t fwd = align256((size_t)desc->d_in * N * es);   // A = R^T X
-  if (desc->flags & POETX_FLAG_RECOMPUTE_B) fwd += align256((size_t)desc->d_out * N * es);  // B lives here too
-  const size_t wdeq = ((desc->flags & POETX_FLAG_W_INT8) && !weight_in_kernel(desc))
-                          ? align256((size_t)desc->d_out * desc->d_in * es) : 0;   // dequantised copy, only where no kernel converts on the fly
+  const i64 Ni = internal_columns(desc);
+  const size_t actm = act_bytes(desc, desc->d_in), actn = act_bytes(desc, desc->d_out);
+  size_t fwd = actm;                                    // A = R^T X
+  if (desc->flags & POETX_FLAG_RECOMPUTE_B) fwd += actn;  // B lives here too
+  const size_t wdeq = dequantised_weight_bytes(desc);   // only where no kernel converts on the fly
   const size_t part = dense_part_bytes(desc);
   fwd += wdeq + part;                                   // dequantised weight behind A (and B), then the dense product's partials
-  size_t bwi = align256((size_t)desc->d_out * N * es) + wdeq + part;  // dB = P dZ
+  size_t bwi = actn + wdeq + part;                      // dB = P dZ
   int dmax = desc->d_in > desc->d_out ? desc->d_in : desc->d_out;
-  size_t bg_in = blockgrad_ws_bytes(desc->dtype, desc->d_in, desc->n_tokens, desc->block);
-  size_t bg_out = blockgrad_ws_bytes(desc->dtype, desc->d_out, desc->n_tokens, desc->block);
+  size_t bg_in = blockgrad_ws_bytes(desc, desc->d_in);
+  size_t bg_out = blockgrad_ws_bytes(desc, desc->d_out);
+  const size_t bg = bg_in > bg_out ? bg_in : bg_out;
   size_t chain = cnp_bwd_ws_floats(dmax, desc->block, desc->neumann_k);
   const size_t both = cnp_bwd_ws_floats_both(desc->d_in, desc->d_out, desc->block, desc->neumann_k);
   if (both > chain) chain = both;
-  size_t skew = align256(chain * sizeof(float)) + (bg_in > bg_out ? bg_in : bg_out);
-  const size_t parts = align256(edge_blockgrad_parts_bytes(desc->dtype, desc->d_in, desc->n_tokens, desc->block)) +
-                       align256(edge_blockgrad_parts_bytes(desc->dtype, desc->d_out, desc->n_tokens, desc->block));
+  size_t skew = align256(chain * sizeof(float)) + bg;
+  const size_t parts = blockgrad_parts_bytes(desc, desc->d_in) + blockgrad_parts_bytes(desc, desc->d_out);
   if (series_small_supported(desc->block) && parts > skew) skew = parts;
   size_t w = fwd > bwi ? fwd : bwi;
   if (skew > w) w = skew;
   // poetx_linear_bwd keeps dA (and, on its one-pass path, dB) in the workspace next to what the two
   // halves need: dA | two-call scratch, or dA | dB | dG + chain | partials or dequantised weight
   const size_t two_calls = bwi > skew ? bwi : skew;
-  size_t bwd = align256((size_t)desc->d_in * N * es) + two_calls;
-  if (desc->dtype == POETX_BF16 && mfma_apply_grad_supported(desc->d_in, desc->n_tokens, desc->n_tokens, desc->block) &&
-      mfma_apply_grad_supported(desc->d_out, desc->n_tokens, desc->n_tokens, desc->block)) {
-    size_t tail = align256(mfma_apply_grad_workspace_bytes(desc->d_in, desc->n_tokens));
-    const size_t po = align256(mfma_apply_grad_workspace_bytes(desc->d_out, desc->n_tokens));
+  size_t bwd = actm + two_calls;
+  if (desc->dtype == POETX_BF16 && mfma_apply_grad_supported(desc->d_in, Ni, Ni, desc->block) &&
+      mfma_apply_grad_supported(desc->d_out, Ni, Ni, desc->block)) {
+    size_t tail = align256(mfma_apply_grad_workspace_bytes(desc->d_in, Ni));
+    const size_t po = align256(mfma_apply_grad_workspace_bytes(desc->d_out, Ni));
     if (po > tail) tail = po;
+    if (bg > tail) tail = bg;                           // a side that runs in two passes
     if (wdeq + part > tail) tail = wdeq + part;
-    const size_t one_pass = align256((size_t)desc->d_in * N * es) + align256((size_t)desc->d_out * N * es) +
-                            align256(chain * sizeof(float)) + tail;
+    const size_t one_pass = actm + actn + align256(chain * sizeof(float)) + tail;
     if (one_pass > bwd) bwd = one_pass;
   }
   bwd += recompute_tail_bytes(desc);
@@ -442,21 +489,20 @@ int poetx_linear_fwd(const poetx_linear_desc* desc, const void* X, const void* W
   if (!ws || ws_bytes < poetx_linear_workspace_bytes(desc)) return POETX_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype;
-  const i64 N = desc->n_tokens;
+  const i64 N = desc->n_tokens, Ni = internal_columns(desc);
   LayoutStaging lay(desc, ws, st);
-  X = lay.in(X, m);
-  Z = lay.out(Z, n);
-  void* A = ws;
-  char* after = (char*)ws + align256((size_t)m * N * esize(dt));
+  const Act x = lay.in(X, m), z = lay.out(Z, n), A{ws, Ni, Ni};
+  char* after = (char*)ws + act_bytes(desc, m);
+  Act B{saved_B, N, N};
   if (!saved_B) {  // memory-saving variant: scratch only
-    saved_B = after;
-    after += align256((size_t)n * N * esize(dt));
+    B = Act{after, Ni, Ni};
+    after += act_bytes(desc, n);
   }
   W = resolve_weight(desc, W, after, st);
   void* part = after + dequantised_weight_bytes(desc);
-  apply_left_dispatch(dt, X, A, m, N, N, perm_R, blocks_R, b, 1, st);        // mm1: A = R^T X
-  dense_dispatch(dt, 0, W, n, m, A, saved_B, N, part, st, weight_in_kernel(desc));     // mm2: B = W A
-  apply_left_dispatch(dt, saved_B, Z, n, N, N, perm_P, blocks_P, b, 1, st);  // mm3: Z = P^T B
+  apply_left_dispatch(dt, x, A, m, perm_R, blocks_R, b, 1, st);              // mm1: A = R^T X
+  dense_dispatch(dt, 0, W, n, m, A, B, part, st, weight_in_kernel(desc));    // mm2: B = W A
+  apply_left_dispatch(dt, B, z, n, perm_P, blocks_P, b, 1, st);              // mm3: Z = P^T B
   lay.finish();
   return launch_status();
 }
@@ -469,28 +515,28 @@ int poetx_linear_recompute_b(const poetx_linear_desc* desc, const void* X, const
   if (!ws || ws_bytes < poetx_linear_workspace_bytes(desc)) return POETX_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype;
-  const i64 N = desc->n_tokens;
+  const i64 N = desc->n_tokens, Ni = internal_columns(desc);
   LayoutStaging lay(desc, ws, st);
-  X = lay.in(X, m);
-  char* after = (char*)ws + align256((size_t)m * N * esize(dt));
+  const Act x = lay.in(X, m), A{ws, Ni, Ni};
+  char* after = (char*)ws + act_bytes(desc, m);
   W = resolve_weight(desc, W, after, st);
-  apply_left_dispatch(dt, X, ws, m, N, N, perm_R, blocks_R, b, 1, st);  // A = R^T X
-  dense_dispatch(dt, 0, W, n, m, ws, B_out, N, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // B = W A
+  apply_left_dispatch(dt, x, A, m, perm_R, blocks_R, b, 1, st);  // A = R^T X
+  dense_dispatch(dt, 0, W, n, m, A, Act{B_out, N, N}, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // B = W A
   return launch_status();
 }
 
 // dB = P dZ, dA = W^T dB, dX = R dA; ws holds dB (and the dequantised weight behind it)
-static void bwd_input_impl(const poetx_linear_desc* desc, const void* dZ, const void* W, const int32_t* perm_R,
-                           const int32_t* perm_P, const void* blocks_R, const void* blocks_P, void* dX, void* dA,
+static void bwd_input_impl(const poetx_linear_desc* desc, const Act& dZ, const void* W, const int32_t* perm_R,
+                           const int32_t* perm_P, const void* blocks_R, const void* blocks_P, const Act& dX, const Act& dA,
                            void* ws, hipStream_t st, const void* W_resolved = nullptr) {
   const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype;
-  const i64 N = desc->n_tokens;
-  void* dB = ws;
-  char* after = (char*)ws + align256((size_t)n * N * esize(dt));
+  const i64 Ni = internal_columns(desc);
+  const Act dB{ws, Ni, Ni};
+  char* after = (char*)ws + act_bytes(desc, n);
   W = W_resolved ? W_resolved : resolve_weight(desc, W, after, st);
-  apply_left_dispatch(dt, dZ, dB, n, N, N, perm_P, blocks_P, b, 0, st);  // dB = P dZ
-  dense_dispatch(dt, 1, W, n, m, dB, dA, N, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // dA = W^T dB
-  apply_left_dispatch(dt, dA, dX, m, N, N, perm_R, blocks_R, b, 0, st);  // dX = R dA
+  apply_left_dispatch(dt, dZ, dB, n, perm_P, blocks_P, b, 0, st);  // dB = P dZ
+  dense_dispatch(dt, 1, W, n, m, dB, dA, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // dA = W^T dB
+  apply_left_dispatch(dt, dA, dX, m, perm_R, blocks_R, b, 0, st);  // dX = R dA
 }
 
 int poetx_linear_bwd_input(const poetx_linear_desc* desc, const void* dZ, const void* W, const int32_t* perm_R,
@@ -501,9 +547,8 @@ int poetx_linear_bwd_input(const poetx_linear_desc* desc, const void* dZ, const 
   if (!dZ || !W || !perm_R || !perm_P || !blocks_R || !blocks_P || !dX || !dA) return POETX_ERR_INVALID_ARG;
   if (!ws || ws_bytes < poetx_linear_workspace_bytes(desc)) return POETX_ERR_WORKSPACE;
   LayoutStaging lay(desc, ws, (hipStream_t)stream);
-  dZ = lay.in(dZ, desc->d_out);
-  dX = lay.out(dX, desc->d_in);
-  bwd_input_impl(desc, dZ, W, perm_R, perm_P, blocks_R, blocks_P, dX, dA, ws, (hipStream_t)stream);
+  const Act dz = lay.in(dZ, desc->d_out), dx = lay.out(dX, desc->d_in);
+  bwd_input_impl(desc, dz, W, perm_R, perm_P, blocks_R, blocks_P, dx, Act{dA, desc->n_tokens, desc->n_tokens}, ws, (hipStream_t)stream);
   lay.finish();
   return launch_status();
 }
@@ -524,12 +569,11 @@ static void cnp_bwd_both_on_chip(const float* theta_R, const float* theta_P, flo
   skew_project_launch(dQ + nbP * bb, b, m, dtheta_R, accumulate != 0, st);
 }
 
-static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const void* dZ, const void* saved_B,
-                          const void* dA, const int32_t* perm_R, const int32_t* perm_P, const float* theta_R,
+static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act& dZ, const Act& saved_B,
+                          const Act& dA, const int32_t* perm_R, const int32_t* perm_P, const float* theta_R,
                           const float* theta_P, float* dtheta_R, float* dtheta_P, int32_t accumulate, void* ws,
                           hipStream_t st) {
   const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype, k = desc->neumann_k;
-  const i64 N = desc->n_tokens;
   const int dmax = m > n ? m : n;
   size_t chain_floats = cnp_bwd_ws_floats(dmax, b, k);
   if (cnp_bwd_ws_floats_both(m, n, b, k) > chain_floats) chain_floats = cnp_bwd_ws_floats_both(m, n, b, k);
@@ -546,8 +590,8 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
     float* dG = (float*)ws;                                   // [nbt][b][b]
     if (defer) {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      blockgrad_dispatch(dt, saved_B, dZ, n, N, perm_P, b, dtheta_P, bg_ws, st);
-      blockgrad_dispatch(dt, X, dA, m, N, perm_R, b, dtheta_R, bg_ws, st);
+      blockgrad_dispatch(dt, saved_B, dZ, n, perm_P, b, dtheta_P, bg_ws, st);
+      blockgrad_dispatch(dt, X, dA, m, perm_R, b, dtheta_R, bg_ws, st);
       return;
     }
     if (!lds_cnp_supported(m, b)) {                            // tiled kernels (b = 512)
@@ -556,8 +600,8 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
       float* chain = Qf + nbt * bb + nbt * bb / 2;            // 3.5 floats per element follow: 6 in all
       {
         StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-        blockgrad_dispatch(dt, saved_B, dZ, n, N, perm_P, b, dG, bg_ws, st);
-        blockgrad_dispatch(dt, X, dA, m, N, perm_R, b, dG + nbP * bb, bg_ws, st);
+        blockgrad_dispatch(dt, saved_B, dZ, n, perm_P, b, dG, bg_ws, st);
+        blockgrad_dispatch(dt, X, dA, m, perm_R, b, dG + nbP * bb, bg_ws, st);
       }
       StageTimer tm(POETX_STAGE_CNP_BWD, st);
       skew_materialize_launch(theta_P, b, nbP, Qf, nullptr, Tb, st);
@@ -569,8 +613,8 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
     }
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      blockgrad_dispatch(dt, saved_B, dZ, n, N, perm_P, b, dG, bg_ws, st);            // dG_P = B' dZ'^T
-      blockgrad_dispatch(dt, X, dA, m, N, perm_R, b, dG + nbP * bb, bg_ws, st);       // dG_R = X' dA'^T
+      blockgrad_dispatch(dt, saved_B, dZ, n, perm_P, b, dG, bg_ws, st);            // dG_P = B' dZ'^T
+      blockgrad_dispatch(dt, X, dA, m, perm_R, b, dG + nbP * bb, bg_ws, st);       // dG_R = X' dA'^T
     }
     cnp_bwd_both_on_chip(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);
     return;
@@ -588,8 +632,10 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
       sides[i].dG = (const float*)at;
       sides[i].split_stride = (i64)ceil_div(d, b) * b * b;
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      sides[i].nsplit = edge_blockgrad_parts(dt, i == 0 ? saved_B : X, N, i == 0 ? dZ : dA, N, d, N, i == 0 ? perm_P : perm_R, b, (float*)at, st);
-      at += align256(edge_blockgrad_parts_bytes(dt, d, N, b));
+      const Act& U = i == 0 ? saved_B : X;
+      const Act& V = i == 0 ? dZ : dA;
+      sides[i].nsplit = edge_blockgrad_parts(dt, U.p, U.ld, V.p, V.ld, d, min64(U.cols, V.cols), i == 0 ? perm_P : perm_R, b, (float*)at, st);
+      at += blockgrad_parts_bytes(desc, d);
     }
     StageTimer tm(POETX_STAGE_CNP_BWD, st);
     series_small_bwd(sides, 2, b, k, accumulate != 0, st);
@@ -598,8 +644,8 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
   float* dG = (float*)ws;
   float* chain = dG + (size_t)ceil_div(dmax, b) * b * b;
   for (int side = 0; side < 2; ++side) {
-    const void* U = side == 0 ? saved_B : X;   // mm3 backward: dG_P = B' dZ'^T; mm1 backward: dG_R = X' dA'^T
-    const void* V = side == 0 ? dZ : dA;
+    const Act& U = side == 0 ? saved_B : X;   // mm3 backward: dG_P = B' dZ'^T; mm1 backward: dG_R = X' dA'^T
+    const Act& V = side == 0 ? dZ : dA;
     const int d = side == 0 ? n : m;
     const int32_t* perm = side == 0 ? perm_P : perm_R;
     const float* theta = side == 0 ? theta_P : theta_R;
@@ -608,7 +654,7 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const void* X, const vo
     float* dGs = defer ? dtheta : dG;
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      blockgrad_dispatch(dt, U, V, d, N, perm, b, dGs, bg_ws, st);
+      blockgrad_dispatch(dt, U, V, d, perm, b, dGs, bg_ws, st);
     }
     if (!defer) {
       StageTimer tm(POETX_STAGE_CNP_BWD, st);
@@ -628,9 +674,9 @@ int poetx_linear_bwd_skew(const poetx_linear_desc* desc, const void* X, const vo
     return POETX_ERR_INVALID_ARG;
   if (!ws || ws_bytes < poetx_linear_workspace_bytes(desc)) return POETX_ERR_WORKSPACE;
   LayoutStaging lay(desc, ws, (hipStream_t)stream);
-  X = lay.in(X, desc->d_in);
-  dZ = lay.in(dZ, desc->d_out);
-  bwd_skew_impl(desc, X, dZ, saved_B, dA, perm_R, perm_P, theta_R, theta_P, dtheta_R, dtheta_P, accumulate, ws,
+  const i64 N = desc->n_tokens;
+  const Act x = lay.in(X, desc->d_in), dz = lay.in(dZ, desc->d_out);
+  bwd_skew_impl(desc, x, dz, Act{saved_B, N, N}, Act{dA, N, N}, perm_R, perm_P, theta_R, theta_P, dtheta_R, dtheta_P, accumulate, ws,
                 (hipStream_t)stream);
   return launch_status();
 }
@@ -648,39 +694,39 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
   if (!ws || ws_bytes < poetx_linear_workspace_bytes(desc)) return POETX_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype, k = desc->neumann_k;
-  const i64 N = desc->n_tokens;
+  const i64 N = desc->n_tokens, Ni = internal_columns(desc);
   LayoutStaging lay(desc, ws, st);
-  X = lay.in(X, m);
-  dZ = lay.in(dZ, n);
-  dX = lay.out(dX, m);
-  void* dA = ws;                                                   // m x N, lives until the R side is done
-  char* rest = (char*)ws + align256((size_t)m * N * esize(dt));
+  const Act x = lay.in(X, m), dz = lay.in(dZ, n), dx = lay.out(dX, m);
+  const Act dA{ws, Ni, Ni};                                        // lives until the R side is done
+  char* rest = (char*)ws + act_bytes(desc, m);
   const void* W_resolved = nullptr;
+  Act B{saved_B, N, N};
   if (!saved_B) {
     // Gradient checkpoint inside the call (Sec. 3.5, memory-saving variant): A = R^T X goes where dA will
     // be, B = W A to the end of the workspace; a quantised weight is dequantised once for both products.
     char* end = (char*)ws + core_workspace_bytes(desc);
     char* w_keep = end - dequantised_weight_bytes(desc);
-    char* B_re = w_keep - align256((size_t)n * N * esize(dt));
+    B = Act{w_keep - act_bytes(desc, n), Ni, Ni};
     W_resolved = resolve_weight(desc, W, w_keep, st);
-    apply_left_dispatch(dt, X, dA, m, N, N, perm_R, blocks_R, b, 1, st);
-    dense_dispatch(dt, 0, W_resolved, n, m, dA, B_re, N, rest, st, weight_in_kernel(desc));   // partials where dB will be
-    saved_B = B_re;
+    apply_left_dispatch(dt, x, dA, m, perm_R, blocks_R, b, 1, st);
+    dense_dispatch(dt, 0, W_resolved, n, m, dA, B, rest, st, weight_in_kernel(desc));   // partials where dB will be
   }
-  const bool one_pass = desc->cnp_precision == POETX_CNP_BF16 && use_mfma(dt) && lds_cnp_supported(m, b) &&
-                        lds_cnp_supported(n, b) && mfma_apply_grad_supported(m, N, N, b) &&
-                        mfma_apply_grad_supported(n, N, N, b) && aligned16(X) && aligned16(dZ) && aligned16(saved_B) &&
-                        aligned16(dX) && aligned16(blocks_R) && aligned16(blocks_P);
-  if (!one_pass) {   // the same values through the two halves
-    bwd_input_impl(desc, dZ, W, perm_R, perm_P, blocks_R, blocks_P, dX, dA, rest, st, W_resolved);
-    bwd_skew_impl(desc, X, dZ, saved_B, dA, perm_R, perm_P, theta_R, theta_P, dtheta_R, dtheta_P, accumulate, rest, st);
+  // Each side's gradient is streamed once where its tensors are whole tiles: dB = P dZ together with
+  // dG_P = B' dZ'^T, then dA = W^T dB, then dX = R dA together with dG_R = X' dA'^T (Sec. 3.5).
+  const bool on_chip = desc->cnp_precision == POETX_CNP_BF16 && use_mfma(dt) && lds_cnp_supported(m, b) && lds_cnp_supported(n, b);
+  auto one_pass = [&](const Act& V, const Act& U, const Act& out, int d, const void* blocks) {
+    return on_chip && V.ld == U.ld && V.ld == out.ld && V.cols == V.ld && U.cols == V.ld && out.cols == V.ld &&
+           mfma_apply_grad_supported(d, V.cols, V.ld, b) && aligned16(V.p) && aligned16(U.p) && aligned16(out.p) && aligned16(blocks);
+  };
+  const Act dB{rest, Ni, Ni};
+  const bool one_P = one_pass(dz, B, dB, n, blocks_P), one_R = one_pass(dA, x, dx, m, blocks_R);
+  if (!one_P && !one_R) {   // the same values through the two halves
+    bwd_input_impl(desc, dz, W, perm_R, perm_P, blocks_R, blocks_P, dx, dA, rest, st, W_resolved);
+    bwd_skew_impl(desc, x, dz, B, dA, perm_R, perm_P, theta_R, theta_P, dtheta_R, dtheta_P, accumulate, rest, st);
     lay.finish();
     return launch_status();
   }
-  // Each side's gradient is streamed once: dB = P dZ together with dG_P = B' dZ'^T, then
-  // dA = W^T dB, then dX = R dA together with dG_R = X' dA'^T (Sec. 3.5), then the series backward.
-  void* dB = rest;
-  char* after_dB = rest + align256((size_t)n * N * esize(dt));
+  char* after_dB = rest + act_bytes(desc, n);
   const int nbP = n / b;
   const size_t bb = (size_t)b * b;
   float* dG = (float*)after_dB;                                    // both sides' block gradients, then chain scratch
@@ -690,16 +736,20 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
   const bool defer = (desc->flags & POETX_FLAG_BLOCK_GRADS) != 0;   // block gradients to the caller, no series backward
   float* dG_P = defer ? dtheta_P : dG;
   float* dG_R = defer ? dtheta_R : dG + nbP * bb;
-  {
-    StageTimer tm(POETX_STAGE_APPLY_GRAD, st);
-    mfma_apply_grad(dZ, saved_B, dB, n, N, N, perm_P, blocks_P, 0, dG_P, part, st);
-  }
+  auto side = [&](bool one, const Act& V, const Act& U, const Act& out, int d, const int32_t* perm, const void* blocks, float* dGs) {
+    if (one) {
+      StageTimer tm(POETX_STAGE_APPLY_GRAD, st);
+      mfma_apply_grad(V.p, U.p, out.out(), d, V.cols, V.ld, perm, blocks, 0, dGs, part, st);
+    } else {
+      apply_left_dispatch(dt, V, out, d, perm, blocks, b, 0, st);
+      StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
+      blockgrad_dispatch(dt, U, V, d, perm, b, dGs, part, st);
+    }
+  };
+  side(one_P, dz, B, dB, n, perm_P, blocks_P, dG_P);
   W = W_resolved ? W_resolved : resolve_weight(desc, W, part, st);   // the P side's partials are reduced by now (stream order): same space
-  dense_dispatch(dt, 1, W, n, m, dB, dA, N, (char*)part + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));
-  {
-    StageTimer tm(POETX_STAGE_APPLY_GRAD, st);
-    mfma_apply_grad(dA, X, dX, m, N, N, perm_R, blocks_R, 0, dG_R, part, st);
-  }
+  dense_dispatch(dt, 1, W, n, m, dB, dA, (char*)part + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));
+  side(one_R, dA, x, dx, m, perm_R, blocks_R, dG_R);
   lay.finish();
   if (defer) return launch_status();
   cnp_bwd_both_on_chip(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);

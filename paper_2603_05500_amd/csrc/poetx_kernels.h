@@ -71,17 +71,21 @@ size_t weight_q8_scale_offset(int n, int m);
 void weight_quantize_q8_launch(int dtype, const void* W, int n, int m, void* Wq, hipStream_t st);
 void weight_dequantize_q8_launch(const void* Wq, int n, int m, int dtype, void* W_out, hipStream_t st);
 
-// out (C x R) = in (R x C)^T, both row major and dense (layout.hip)
-void transpose_launch(int dtype, const void* in, void* out, i64 R, i64 C, hipStream_t st);
+// out (C x R_out, row stride ld_out) = in (R x C, row stride ld_in)^T, columns R .. R_out - 1 of out zero (layout.hip)
+void transpose_launch(int dtype, const void* in, void* out, i64 R, i64 C, i64 ld_in, i64 ld_out, i64 R_out, hipStream_t st);
 
 void perm_validate_launch(const int32_t* perm, int d, int32_t* scratch, hipStream_t st);
 
 // ---- matrix-core path for bf16 (mfma_*.hip) -------------------------------------------
 bool mfma_dense_supported(int n, int m, i64 N);
-void mfma_dense(int trans_w, const void* W, int n, int m, const void* act, void* out, i64 N,
-                hipStream_t st);
+// act: K x N_act dense (whole tiles); the first N columns of the product go to out (row stride ld_out, any alignment
+// where N < N_act)
+void mfma_dense(int trans_w, const void* W, int n, int m, const void* act, i64 N_act, void* out, i64 ld_out, i64 N, hipStream_t st);
+// is a token count padded to Np = whole tiles better served by the streaming product than by the edge one?
+bool mfma_dense_worth_padding(int n, int m, i64 Np);
 // the same products for fp32 tensors (fp32 MFMA, mfma_dense_f32.hip)
 bool mfma_dense_f32_supported(int n, int m, i64 N);
+bool mfma_dense_f32_fills(int M, i64 N);
 void mfma_dense_f32(int trans_w, const void* W, int n, int m, const void* act, void* out, i64 N, hipStream_t st);
 // the same products on a quantised weight buffer (codes + row scales), dequantised inside the kernel (mfma_dense_q8.hip)
 bool mfma_dense_q8_supported(int n, int m, i64 N);
@@ -89,6 +93,11 @@ void mfma_dense_q8(int trans_w, const void* Wq, int n, int m, const void* act, v
 bool mfma_apply_left_supported(int d, i64 cols, i64 ld, int b);
 void mfma_apply_left(const void* V, void* out, int d, i64 cols, i64 ld, const int32_t* perm,
                      const void* E, int b, int transpose_G, hipStream_t st);
+// the same for any token counts and row strides (element-aligned activations, 16-byte aligned blocks): V d x cols, out d x cols_out,
+// columns past cols written as zeros
+bool mfma_apply_left_ragged_supported(int d, i64 cols_out, int b);
+void mfma_apply_left_ragged(const void* V, i64 ldv, i64 cols, void* out, i64 ldo, i64 cols_out, int d, const int32_t* perm, const void* E, int b,
+                            int transpose_G, hipStream_t st);
 bool mfma_blockgrad_supported(int d, i64 N, int b);
 size_t mfma_blockgrad_workspace_bytes(int d, i64 N, int b);
 void mfma_blockgrad(const void* U, const void* V, int d, i64 N, const int32_t* perm, int b, float* dG,

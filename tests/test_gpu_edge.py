@@ -93,3 +93,40 @@ def test_small_block_series(lib, b, k):
         got = to_np(dth) - (1.0 if acc else 0.0)
         assert rel_err(got, want) <= 1e-5
         assert np.all(got[-1, dead] == 0)
+
+
+@pytest.mark.parametrize("m,n,N,b", [(2048, 2304, 1793, 256), (2560, 2048, 2047, 512), (2048, 2048, 1992, 128)])
+def test_ragged_token_counts_on_the_streaming_kernels(lib, m, n, N, b):
+    """Token counts that the layer pads to whole tiles inside the workspace: one past a tile, one short of one, a
+    multiple of 8; both layouts, B kept or recomputed (each has its own mix of padded and unpadded tensors), the
+    workspace poisoned with NaN so that a stage reading what no stage wrote shows."""
+    k = 2
+    data = synth_layer(9300 + m + N + b, m, n, N, b, k, "bf16", 0.005)
+    ref = orc.linear_fwd_bwd_from_theta(data["X"], data["dZ"], data["W"], data["pi_R"], data["pi_P"],
+                                        data["theta_R"], data["theta_P"], b, k)
+    check_layer(run_layer(data, "bf16"), ref, data["pi_P"], "bf16")
+    bf = torch.bfloat16
+    X, dZ, W = (to_dev(data[key], bf) for key in ("X", "dZ", "W"))
+    th = {s: to_dev(data["theta_" + s], torch.float32) for s in "RP"}
+    pi = {s: torch.from_numpy(data["pi_" + s]).cuda() for s in "RP"}
+    blk = {}
+    for s, d in (("R", m), ("P", n)):
+        blk[s] = torch.empty((th[s].shape[0], 2, b, b), dtype=bf, device="cuda")
+        ws = torch.empty(lib.poetx_cnp_workspace_bytes(d, b), dtype=torch.uint8, device="cuda")
+        lib.poetx_cnp_build(th[s], d, b, k, lib.CNP_BF16, None, blk[s], ws)
+    for layout in (lib.FEATURE_MAJOR, lib.TOKEN_MAJOR):
+        tm = layout == lib.TOKEN_MAJOR
+        turn = (lambda t: t.t().contiguous()) if tm else (lambda t: t)
+        for mem in (False, True):
+            desc = lib.make_desc(m, n, b, k, N, lib.BF16, flags=lib.FLAG_RECOMPUTE_B if mem else 0, layout=layout)
+            ws = torch.full((lib.poetx_linear_workspace_bytes(desc) // 4,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
+            Z, dX = torch.empty_like(turn(dZ)), torch.empty_like(turn(X))
+            B = None if mem else torch.empty((n, N), dtype=bf, device="cuda")
+            dth = {s: torch.full_like(th[s], float("nan")) for s in "RP"}
+            lib.poetx_linear_fwd(desc, turn(X), W, pi["R"], pi["P"], blk["R"], blk["P"], Z, B, ws)
+            lib.poetx_linear_bwd(desc, turn(X), turn(dZ), B, W, pi["R"], pi["P"], blk["R"], blk["P"], th["R"], th["P"], dX,
+                                 dth["R"], dth["P"], False, ws)
+            torch.cuda.synchronize()
+            got = {"Z": to_np(turn(Z)), "dX": to_np(turn(dX)), "dtheta_R": to_np(dth["R"]), "dtheta_P": to_np(dth["P"])}
+            for key, v in got.items():
+                assert rel_err(v, ref[key]) <= TOL["bf16"], (key, layout, mem)

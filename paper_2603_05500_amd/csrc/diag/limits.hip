@@ -137,13 +137,13 @@ static float sustained_ms(F launch, int warm, int iters) {
 
 template <bool A_KMAJOR, int DIAG>
 static void time_dense(const char* what, const dense::DenseArgs& g, double flops) {
-  auto kern = dense::dense_stream_kernel<A_KMAJOR, false, DIAG>;
-  CHECK(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, dense::LDS_BYTES));
-  const float ms = sustained_ms([&] { hipLaunchKernelGGL(kern, dim3(256), dim3(256), dense::LDS_BYTES, 0, g); }, 60, 40);
+  auto kern = dense::dense_stream_kernel<A_KMAJOR, dense::OUT_WHOLE, DIAG>;
+  CHECK(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, dense::Tile256::LDS_BYTES));
+  const float ms = sustained_ms([&] { hipLaunchKernelGGL(kern, dim3(256), dim3(256), dense::Tile256::LDS_BYTES, 0, g); }, 60, 40);
   // the same variant with the cycle counters in (DIAG bit 3): main loop and output of each workgroup's second tile
-  auto kclk = dense::dense_stream_kernel<A_KMAJOR, false, DIAG | 8>;
-  CHECK(hipFuncSetAttribute((const void*)kclk, hipFuncAttributeMaxDynamicSharedMemorySize, dense::LDS_BYTES));
-  for (int i = 0; i < 10; ++i) hipLaunchKernelGGL(kclk, dim3(256), dim3(256), dense::LDS_BYTES, 0, g);
+  auto kclk = dense::dense_stream_kernel<A_KMAJOR, dense::OUT_WHOLE, DIAG | 8>;
+  CHECK(hipFuncSetAttribute((const void*)kclk, hipFuncAttributeMaxDynamicSharedMemorySize, dense::Tile256::LDS_BYTES));
+  for (int i = 0; i < 10; ++i) hipLaunchKernelGGL(kclk, dim3(256), dim3(256), dense::Tile256::LDS_BYTES, 0, g);
   CHECK(hipDeviceSynchronize());
   static long long hc[4][1024];
   CHECK(hipMemcpyFromSymbol(hc, HIP_SYMBOL(dense::g_diag_cycles), sizeof(hc)));
@@ -233,8 +233,8 @@ int main() {
     time_dense<false, 4>("backward, every load re-fetches the first stage (cache hits)", g, flops);
     time_dense<false, 6>("backward, cache-hit loads and no fragment reads", g, flops);
     // spot check of the unmodified kernel (forward)
-    auto kern = dense::dense_stream_kernel<true, false, 0>;
-    hipLaunchKernelGGL(kern, dim3(256), dim3(256), dense::LDS_BYTES, 0, g);
+    auto kern = dense::dense_stream_kernel<true, dense::OUT_WHOLE, 0>;
+    hipLaunchKernelGGL(kern, dim3(256), dim3(256), dense::Tile256::LDS_BYTES, 0, g);
     std::vector<uint16_t> hC((size_t)M * N);
     CHECK(hipMemcpy(hC.data(), dC, hC.size() * 2, hipMemcpyDeviceToHost));
     double maxerr = 0, maxref = 0;

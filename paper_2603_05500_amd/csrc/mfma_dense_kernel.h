@@ -7,7 +7,7 @@
 //
 // The kernel is a persistent stream: one workgroup per CU, 4 waves (2 x 2, one per SIMD), each
 // wave owning a 128 x 128 piece of a 256 x 256 output tile in 256 accumulator registers
-// (v_mfma_f32_32x32x16_bf16, fp32).  A workgroup walks its list of output tiles; the 32-deep
+// (v_mfma_f32_32x32x16_bf16, fp32; smaller tiles for products with few of them).  A workgroup walks its list of output tiles; the 32-deep
 // operand stages of ALL its tiles form one stream that flows through a ring of 4 LDS stages
 // (a fifth buys nothing measurable; its 32 KB stage the output instead),
 // filled by direct-to-LDS loads issued that many stages ahead of the multiplication -- across tile
@@ -31,16 +31,31 @@ using mm::floatx16;
 using mm::short4v;
 using mm::short8v;
 
-constexpr int BM = 256, BN = 256, BK = 32, NW = 4, NS = 4;
-constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
-constexpr int OUT_BYTES = 8192;                  // per-wave output staging: two 32-row x 64-column pieces
-constexpr int LDS_BYTES = NS * STAGE_BYTES + NW * OUT_BYTES;   // 128 + 32 = 160 KB: the whole LDS of a CU
-constexpr int IPW = A_BYTES / 1024 / NW;         // direct-to-LDS instructions per wave per operand per stage
-constexpr int LPT = 2 * IPW;                     // loads per stage per wave
-constexpr int TM = 4, TN = 4;                    // 32 x 32 MFMA tiles of a wave
+constexpr int BK = 32, NW = 4;
 constexpr int GROUP = 4;                         // tile rows walked together
-static_assert(NS * LPT < 64, "vmcnt range");
-static_assert(IPW == 4, "dma16g_s covers groups of four loads");
+
+// Output tile and ring of one instance.  256 x 256 with 4 stages is the fast one (32 bytes of operands per cycle and CU);
+// 256 x 128 (48 bytes) and 128 x 128 (64 bytes, what the L2 can deliver at best) exist for products with too few large
+// tiles for the chip; their stages are shorter, so the ring is deeper.
+template <int BM_, int BN_, int NS_>
+struct Tile {
+  static constexpr int BM = BM_, BN = BN_, NS = NS_;
+  static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
+  static constexpr int TM = BM / 64, TN = BN / 64;       // 32 x 32 MFMA tiles of a wave (2 x 2 waves)
+  static constexpr int MF = TM * TN;                     // MFMAs of a k step
+  static constexpr int OUT_BYTES = TN / 2 * 4096;        // per-wave output staging: 32-row x 64-column pieces
+  static constexpr int LDS_BYTES = NS * STAGE_BYTES + NW * OUT_BYTES;
+  static constexpr int IPWA = A_BYTES / 1024 / NW;       // direct-to-LDS instructions per wave per operand per stage
+  static constexpr int IPWB = B_BYTES / 1024 / NW;
+  static constexpr int LPT = IPWA + IPWB;                // loads per stage per wave
+  static_assert(NS * LPT < 64, "vmcnt range");
+  static_assert(IPWA <= 4 && IPWB <= 4 && MF % IPWA == 0 && MF % IPWB == 0, "dma16g_s covers groups of four loads");
+  static_assert(TM + TN <= MF, "a fragment piece per MFMA");
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
+};
+typedef Tile<256, 256, 4> Tile256;        // 128 + 32 = 160 KB: the whole LDS of a CU
+typedef Tile<256, 128, 6> Tile256x128;    // 144 + 16 KB
+typedef Tile<128, 128, 8> Tile128;        // 128 + 16 KB
 
 struct DenseArgs {
   const uint16_t* A;     // A_KMAJOR: M x K row major (lda = K stride); else K x M
@@ -49,6 +64,8 @@ struct DenseArgs {
   i64 lda, ldb, ldc;
   int tiles_m, tiles_n, ktiles;   // ktiles counts 32-deep stages
   int cols;              // RAGGED: columns of C that exist; its rows need element alignment only
+  int splits;            // PARTS: the contraction in so many ranges of ktiles stages each ...
+  float* parts;          // ... whose products go here in fp32, [split][M][N], instead of to C
 };
 
 // 16 bytes per lane from (uniform base + per-lane byte offset + OFF) straight into LDS at
@@ -60,7 +77,7 @@ template <int OFF>
 __device__ inline void dma16g(const void* sbase, uint32_t voff, uint32_t lds_group) {
   asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(sbase), "n"(OFF), "{m0}"(lds_group) : "memory");
 }
-// load s of a wave's group of IPW = 4 (s is a constant wherever this is called)
+// load s of a wave's group of up to four (s is a constant wherever this is called)
 __device__ inline void dma16g_s(int s, const void* sbase, uint32_t voff, uint32_t lds_group) {
   switch (s) {
     case 0: dma16g<0>(sbase, voff, lds_group); break;
@@ -80,9 +97,13 @@ static __device__ long long g_diag_cycles[4][4 * 256];
 // the first stage of the first tile (all loads hit in cache) -- the results are then wrong,
 // bit 3 (harmless to the result) records the cycle counts above --
 // every address stays what it was, and the timing shows what the loads or the reads cost.
-// RAGGED: the last tiles of a row reach past the columns of C (B is padded to whole tiles, C is not).
-template <bool A_KMAJOR, bool RAGGED = false, int DIAG = 0>
+// What a tile's epilogue writes: bf16 rows of C, the same with masked columns and element alignment, or fp32 parts.
+enum Out { OUT_WHOLE = 0, OUT_RAGGED = 1, OUT_PARTS = 2 };
+// OUT_RAGGED: the last tiles of a row reach past the columns of C (B is padded to whole tiles, C is not).
+template <bool A_KMAJOR, Out OUT = OUT_WHOLE, int DIAG = 0, class C = Tile256>
 __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
+  constexpr int BM = C::BM, BN = C::BN, NS = C::NS, A_BYTES = C::A_BYTES, STAGE_BYTES = C::STAGE_BYTES, OUT_BYTES = C::OUT_BYTES;
+  constexpr int IPWA = C::IPWA, IPWB = C::IPWB, LPT = C::LPT, TM = C::TM, TN = C::TN, MF = C::MF;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -93,15 +114,21 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   // ---- this workgroup's tiles.  Workgroups go to the 8 XCDs round robin; in every step of
   // gridDim.x tiles each XCD takes a contiguous run of the tile order (GROUP tile rows walked
   // together), so the tiles an XCD works on at a time share operand panels in its L2.
-  const int T = g.tiles_m * g.tiles_n;
+  const int T0 = g.tiles_m * g.tiles_n;
+  const int T = OUT == OUT_PARTS ? T0 * g.splits : T0;   // one contraction range after the other
   const int G = gridDim.x;
   int wq = blockIdx.x;
   if ((G & 7) == 0) wq = (wq & 7) * (G >> 3) + (wq >> 3);
   const int n_my = wq < T ? (T - 1 - wq) / G + 1 : 0;
   if (n_my == 0) return;
   const int per_group = GROUP * g.tiles_n;
-  auto tile_origin = [&](int ti, int& i0, int& j0) {
-    const int u = ti * G + wq;
+  auto tile_origin = [&](int ti, int& i0, int& j0, int& split) {
+    int u = ti * G + wq;
+    split = 0;
+    if (OUT == OUT_PARTS) {
+      split = u / T0;
+      u -= split * T0;
+    }
     const int first_m = (u / per_group) * GROUP;
     const int gsz = (g.tiles_m - first_m) < GROUP ? (g.tiles_m - first_m) : GROUP;
     i0 = (first_m + (u % per_group) % gsz) * BM;
@@ -111,12 +138,12 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   // per-lane byte offsets of the direct-to-LDS loads (the same for every stage and tile), less the
   // instruction offset s * 1024 of load s (never negative: load s starts 16 s rows, or 2 s rows of at
   // least 256 elements, into the tile).
-  // Instruction (wave, s) fills LDS chunk slots [(wave*IPW + s)*64, +64) of the operand's part of
+  // Instruction (wave, s) of IPW per operand fills LDS chunk slots [(wave*IPW + s)*64, +64) of the operand's part of
   // a stage; the lane's slot decides, through the inverse swizzle, which global chunk it fetches.
-  uint32_t voffA[IPW], voffB[IPW];
+  uint32_t voffA[IPWA], voffB[IPWB];
 #pragma unroll
-  for (int s = 0; s < IPW; ++s) {
-    const int slot = (wave * IPW + s) * 64 + lane;
+  for (int s = 0; s < IPWA; ++s) {
+    const int slot = (wave * IPWA + s) * 64 + lane;
     if (A_KMAJOR) {
       const int r = slot >> 2, c = mm::xk_chunk(slot & 3, r);
       voffA[s] = (uint32_t)((r * g.lda + c * 8) * 2) - s * 1024;
@@ -124,6 +151,10 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
       const int k = slot / (BM / 8), c = mm::kx_unchunk<BM>(slot % (BM / 8), k);
       voffA[s] = (uint32_t)((k * g.lda + c * 8) * 2) - s * 1024;
     }
+  }
+#pragma unroll
+  for (int s = 0; s < IPWB; ++s) {
+    const int slot = (wave * IPWB + s) * 64 + lane;
     const int k = slot / (BN / 8), c = mm::kx_unchunk<BN>(slot % (BN / 8), k);
     voffB[s] = (uint32_t)((k * g.ldb + c * 8) * 2) - s * 1024;
   }
@@ -137,15 +168,15 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   const char* Bb;
   int itile = 0, ikt = 0, islot = 0;
   auto issue_base = [&](int ti) {
-    int i0, j0;
-    tile_origin(ti, i0, j0);
-    Ab = (const char*)(g.A + (A_KMAJOR ? (i64)i0 * g.lda : (i64)i0));
-    Bb = (const char*)(g.B + j0);
+    int i0, j0, split;
+    tile_origin(ti, i0, j0, split);
+    Ab = (const char*)(g.A + (A_KMAJOR ? (i64)i0 * g.lda : (i64)i0)) + split * (KT * stepA);
+    Bb = (const char*)(g.B + j0) + split * (KT * stepB);
   };
   issue_base(0);
   bool loads_on = true;   // DIAG bit 0 switches it off after the prologue
-  auto issue_a = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Ab, voffA[s], lds_base + islot * STAGE_BYTES + wave * IPW * 1024); };
-  auto issue_b = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Bb, voffB[s], lds_base + islot * STAGE_BYTES + A_BYTES + wave * IPW * 1024); };
+  auto issue_a = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Ab, voffA[s], lds_base + islot * STAGE_BYTES + wave * IPWA * 1024); };
+  auto issue_b = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Bb, voffB[s], lds_base + islot * STAGE_BYTES + A_BYTES + wave * IPWB * 1024); };
   // After the last stage of the last tile the stream keeps re-fetching that stage, so the number
   // of loads in flight -- and with it the vmcnt bound of the barrier -- never changes.
   auto issue_advance = [&]() {
@@ -207,23 +238,16 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   struct Frags {
     bf16x8 a[TM], b[TN];
   };
-  // piece p of a k step's fragments, in the order the MFMAs first need them: A0 B0 A1 A2 A3 B1 B2 B3
+  // piece p of a k step's fragments, in the order the MFMAs first need them: A0 B0 A1 .. A(TM-1) B1 .. B(TN-1)
   auto load_piece = [&](Frags& f, const char* stage, int ks, int p) {
-    switch (p) {
-      case 0: f.a[0] = load_frag(stage, fragA[0], A_KMAJOR, BM * 2, ks); break;
-      case 1: f.b[0] = load_frag(stage, fragB[0], false, BN * 2, ks); break;
-      case 2: f.a[1] = load_frag(stage, fragA[1], A_KMAJOR, BM * 2, ks); break;
-      case 3: f.a[2] = load_frag(stage, fragA[2], A_KMAJOR, BM * 2, ks); break;
-      case 4: f.a[3] = load_frag(stage, fragA[3], A_KMAJOR, BM * 2, ks); break;
-      case 5: f.b[1] = load_frag(stage, fragB[1], false, BN * 2, ks); break;
-      case 6: f.b[2] = load_frag(stage, fragB[2], false, BN * 2, ks); break;
-      default: f.b[3] = load_frag(stage, fragB[3], false, BN * 2, ks); break;
-    }
+    if (p == 1) f.b[0] = load_frag(stage, fragB[0], false, BN * 2, ks);
+    else if (p <= TM) f.a[p ? p - 1 : 0] = load_frag(stage, fragA[p ? p - 1 : 0], A_KMAJOR, BM * 2, ks);
+    else f.b[p - TM] = load_frag(stage, fragB[p - TM], false, BN * 2, ks);
   };
   // MFMA i of a k step.  The operands go in swapped, so the accumulator tile is transposed: a lane
   // owns one output row and four consecutive columns per group of four registers.
   auto mfma_one = [&](const Frags& f, int i) {
-    const int c = i >> 2, a = i & 3;
+    const int c = i / TM, a = i % TM;
     acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[c], f.a[a], acc[a][c], 0, 0, 0);
   };
 
@@ -231,28 +255,28 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t) {
 #pragma unroll
-    for (int s = 0; s < IPW; ++s) issue_a(s);
+    for (int s = 0; s < IPWA; ++s) issue_a(s);
 #pragma unroll
-    for (int s = 0; s < IPW; ++s) issue_b(s);
+    for (int s = 0; s < IPWB; ++s) issue_b(s);
     issue_advance();
   }
 #pragma unroll
-  for (int s = 0; s < IPW; ++s) issue_a(s);
-  mm::wait_vmcnt_and_barrier<(NS - 2) * LPT + IPW>();   // stage 0 has landed
+  for (int s = 0; s < IPWA; ++s) issue_a(s);
+  mm::wait_vmcnt_and_barrier<(NS - 2) * LPT + IPWA>();   // stage 0 has landed
   Frags F, Gf;
   int cslot = 0;
 #pragma unroll
-  for (int p = 0; p < 8; ++p) load_piece(F, lds, 0, p);
+  for (int p = 0; p < TM + TN; ++p) load_piece(F, lds, 0, p);
 
   if (DIAG & 2) {   // the loop reads no fragments: both sets come from the first stage
 #pragma unroll
-    for (int p = 0; p < 8; ++p) load_piece(Gf, lds, 1, p);
+    for (int p = 0; p < TM + TN; ++p) load_piece(Gf, lds, 1, p);
   }
   loads_on = false;
   const int h = lane >> 5, li = lane & 31;
 
-  // The body is instantiated once per wave: wave W issues its four loads of a k step after MFMAs
-  // W, W+4, W+8 and W+12, so the four waves never hand the memory pipeline a load in the same place.
+  // The body is instantiated once per wave: wave W issues its loads of a k step after MFMAs W, W + MF / loads, ...
+  // (256 x 256: W, W+4, W+8, W+12), so the four waves never hand the memory pipeline a load in the same place.
   auto run = [&](auto WC) {
     constexpr int W = decltype(WC)::value;
     for (int ti = 0; ti < n_my; ++ti) {
@@ -266,11 +290,11 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
         // k step 0 from F; fetch k step 1 of this stage; B half of the stage in issue (its A half
         // went out during the previous k step, into the slot the last barrier released)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < MF; ++i) {
           mfma_one(F, i);
-          if (i < 8 && !(DIAG & 2)) load_piece(Gf, stage, 1, i);
-          if ((i & 3) == W) issue_b(i >> 2);
-          if (i == 15) issue_advance();
+          if (i < TM + TN && !(DIAG & 2)) load_piece(Gf, stage, 1, i);
+          if (i % (MF / IPWB) == W % (MF / IPWB)) issue_b(i / (MF / IPWB));
+          if (i == MF - 1) issue_advance();
           __builtin_amdgcn_sched_barrier(0);
         }
         // Every wave holds the rest of this stage in registers (lgkmcnt(0)) and the next stage has
@@ -282,10 +306,10 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
         // k step 1 from Gf; fetch k step 0 of the next stage (the next tile's first stage after
         // the last one of this tile); A half of the next stage to issue, into the slot just released
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < MF; ++i) {
           mfma_one(Gf, i);
-          if (i < 8 && !(DIAG & 2)) load_piece(F, nstage, 0, i);
-          if ((i & 3) == W) issue_a(i >> 2);
+          if (i < TM + TN && !(DIAG & 2)) load_piece(F, nstage, 0, i);
+          if (i % (MF / IPWA) == W % (MF / IPWA)) issue_a(i / (MF / IPWA));
           __builtin_amdgcn_sched_barrier(0);
         }
         cslot = nslot;
@@ -302,11 +326,38 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
       // every instruction writes whole 128-byte lines.  So the wave passes its piece through LDS, 32 rows
       // x 64 columns at a time (rows XOR-swizzled in 16-byte chunks, conflict free both ways), and reads
       // it back with 8 lanes per row.
-      {
+      if constexpr (OUT == OUT_PARTS) {
+        // fp32 parts: the swapped groups are 8 consecutive columns = whole 32-byte sectors of a row
+        typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+        int i0, j0, split;
+        tile_origin(ti, i0, j0, split);
+        float* P = g.parts + ((i64)split * (g.tiles_m * BM) + i0 + wm * (BM / 2) + li) * g.ldb + j0 + wn * (BN / 2) + 8 * h;
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int c = 0; c < TN; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; q += 2) {
+              float lo[4], hi[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float x = acc[a][c][4 * q + e], y = acc[a][c][4 * q + 4 + e];   // scalars first: a bit cast straight from a vector element reads element 0
+                const uint2v r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+                const unsigned r0 = r[0], r1 = r[1];
+                lo[e] = __builtin_bit_cast(float, r0);
+                hi[e] = __builtin_bit_cast(float, r1);
+                acc[a][c][4 * q + e] = 0.f;
+                acc[a][c][4 * q + 4 + e] = 0.f;
+              }
+              float* at = P + (i64)(a * 32) * g.ldb + c * 32 + 8 * q;
+              *reinterpret_cast<float4*>(at) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+              *reinterpret_cast<float4*>(at + 4) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+            }
+      } else {
         typedef unsigned uint2v __attribute__((ext_vector_type(2)));
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        int i0, j0;
-        tile_origin(ti, i0, j0);
+        int i0, j0, split;
+        tile_origin(ti, i0, j0, split);
         char* stg = lds + NS * STAGE_BYTES + wave * OUT_BYTES;
         const int wsw = (li >> 1) & 7;
         uint16_t* Cw = g.C + (i64)(i0 + wm * (BM / 2)) * g.ldc + j0 + wn * (BN / 2);
@@ -330,13 +381,13 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
           }
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's own writes; the area is private to it
 #pragma unroll
-          for (int cp = 0; cp < 2; ++cp)
+          for (int cp = 0; cp < TN / 2; ++cp)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int r = (lane >> 3) + 8 * i, ch = lane & 7;
               const u32x4 o = *reinterpret_cast<const u32x4*>(stg + cp * 4096 + r * 128 + 16 * (ch ^ ((r >> 1) & 7)));
               uint16_t* at = Cw + (i64)(a * 32 + r) * g.ldc + cp * 64 + ch * 8;
-              if constexpr (RAGGED) {
+              if constexpr (OUT == OUT_RAGGED) {
                 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
                 const int left = g.cols - (j0 + wn * (BN / 2) + cp * 64 + ch * 8);
                 if (left >= 8) {

@@ -45,6 +45,8 @@ struct DenseQ8Args {
   uint16_t* C;           // M x N row major
   i64 ldq, ldb, ldc;
   int tiles_m, tiles_n, ktiles;
+  int splits;            // PARTS: the contraction in so many ranges of ktiles stages each,
+  float* parts;          // whose products go here in fp32, [split][M][N], instead of to C
 };
 
 // Direct-to-LDS loads as in the bf16 kernel: the instruction offset moves the LDS and the global
@@ -67,22 +69,27 @@ __device__ inline void dma4s(const void* sbase, uint32_t voff, uint32_t lds_addr
 
 // A_KMAJOR: forward (weight rows are output rows, contraction along a row).  Otherwise backward
 // (weight rows are the contraction index).
-template <bool A_KMAJOR>
+template <bool A_KMAJOR, bool PARTS>
 __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  const int T = g.tiles_m * g.tiles_n;
+  const int T0 = g.tiles_m * g.tiles_n, T = PARTS ? T0 * g.splits : T0;
   const int G = gridDim.x;
   int wq = blockIdx.x;
   if ((G & 7) == 0) wq = (wq & 7) * (G >> 3) + (wq >> 3);
   const int n_my = wq < T ? (T - 1 - wq) / G + 1 : 0;
   if (n_my == 0) return;
   const int per_group = GROUP * g.tiles_n;
-  auto tile_origin = [&](int ti, int& i0, int& j0) {
-    const int u = ti * G + wq;
+  auto tile_origin = [&](int ti, int& i0, int& j0, int& split) {
+    int u = ti * G + wq;
+    split = 0;
+    if (PARTS) {
+      split = u / T0;
+      u -= split * T0;
+    }
     const int first_m = (u / per_group) * GROUP;
     const int gsz = (g.tiles_m - first_m) < GROUP ? (g.tiles_m - first_m) : GROUP;
     i0 = (first_m + (u % per_group) % gsz) * BM;
@@ -103,9 +110,9 @@ __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
   const char* Bb;
   int b_tile = 0, b_kt = 0, b_slot = 0;
   auto b_base = [&](int ti) {
-    int i0, j0;
-    tile_origin(ti, i0, j0);
-    Bb = (const char*)(g.B + j0);
+    int i0, j0, split;
+    tile_origin(ti, i0, j0, split);
+    Bb = (const char*)(g.B + j0) + split * (KT * stepB);
   };
   b_base(0);
   auto issue_b = [&](int s) { dma16g_s(s, Bb, voffB[s], lds_base + b_slot * STAGE_BYTES + A_BYTES + wave * IPW * 1024); };
@@ -147,10 +154,10 @@ __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
   const char* Sb;
   int q_tile = 0, q_kt = 0, q_slot = 0;
   auto q_base = [&](int ti) {
-    int i0, j0;
-    tile_origin(ti, i0, j0);
-    Qb = (const char*)g.Q + (A_KMAJOR ? (i64)i0 * g.ldq : (i64)i0);
-    Sb = (const char*)(g.scale + (A_KMAJOR ? i0 : 0));
+    int i0, j0, split;
+    tile_origin(ti, i0, j0, split);
+    Qb = (const char*)g.Q + (A_KMAJOR ? (i64)i0 * g.ldq : (i64)i0) + split * (KT * stepQ);
+    Sb = (const char*)(g.scale + (A_KMAJOR ? i0 : split * KT * BK));
   };
   q_base(0);
   auto issue_q = [&]() {
@@ -330,27 +337,53 @@ __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
         }
         cslot = nslot;
       }
-      int i0, j0;
-      tile_origin(ti, i0, j0);
-      uint16_t* Ct = g.C + (i64)i0 * g.ldc + j0 + coff;
+      int i0, j0, split;
+      tile_origin(ti, i0, j0, split);
+      if constexpr (PARTS) {
+        float* P = g.parts + ((i64)split * (g.tiles_m * BM) + i0 + wm * (BM / 2) + li) * g.ldb + j0 + wn * (BN / 2) + 8 * h;
 #pragma unroll
-      for (int a = 0; a < TM; ++a)
+        for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int c = 0; c < TN; ++c) {
-          uint32_t p[8];
+          for (int c = 0; c < TN; ++c)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) p[e] = mm::pack2_bf16(acc[a][c][2 * e], acc[a][c][2 * e + 1]);
+            for (int q = 0; q < 4; q += 2) {
+              typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+              float lo[4], hi[4];
 #pragma unroll
-          for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
+              for (int e = 0; e < 4; ++e) {
+                const float x = acc[a][c][4 * q + e], y = acc[a][c][4 * q + 4 + e];   // scalars first: a bit cast straight from a vector element reads element 0
+                const uint2v r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+                const unsigned r0 = r[0], r1 = r[1];
+                lo[e] = __builtin_bit_cast(float, r0);
+                hi[e] = __builtin_bit_cast(float, r1);
+                acc[a][c][4 * q + e] = 0.f;
+                acc[a][c][4 * q + 4 + e] = 0.f;
+              }
+              float* at = P + (i64)(a * 32) * g.ldb + c * 32 + 8 * q;
+              *reinterpret_cast<float4*>(at) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+              *reinterpret_cast<float4*>(at + 4) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+            }
+      } else {
+        uint16_t* Ct = g.C + (i64)i0 * g.ldc + j0 + coff;
 #pragma unroll
-          for (int q = 0; q < 4; q += 2) {
-            typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-            const uint2v r0 = __builtin_amdgcn_permlane32_swap(p[2 * q], p[2 * q + 2], false, false);
-            const uint2v r1 = __builtin_amdgcn_permlane32_swap(p[2 * q + 1], p[2 * q + 3], false, false);
-            const u32x4 o = {r0[0], r1[0], r0[1], r1[1]};
-            *reinterpret_cast<u32x4*>(Ct + (i64)a * 32 * g.ldc + c * 32 + 8 * q) = o;
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int c = 0; c < TN; ++c) {
+            uint32_t p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = mm::pack2_bf16(acc[a][c][2 * e], acc[a][c][2 * e + 1]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; q += 2) {
+              typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+              const uint2v r0 = __builtin_amdgcn_permlane32_swap(p[2 * q], p[2 * q + 2], false, false);
+              const uint2v r1 = __builtin_amdgcn_permlane32_swap(p[2 * q + 1], p[2 * q + 3], false, false);
+              const u32x4 o = {r0[0], r1[0], r0[1], r1[1]};
+              *reinterpret_cast<u32x4*>(Ct + (i64)a * 32 * g.ldc + c * 32 + 8 * q) = o;
+            }
           }
-        }
+      }
     }
   };
   switch (wave) {
@@ -372,13 +405,13 @@ int compute_units_q8() {
   return n;
 }
 
-template <bool A_KMAJOR>
+template <bool A_KMAJOR, bool PARTS>
 void launch_dense_q8(const DenseQ8Args& g, hipStream_t st) {
-  auto kern = dense_q8_stream_kernel<A_KMAJOR>;
+  auto kern = dense_q8_stream_kernel<A_KMAJOR, PARTS>;
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) == hipSuccess;
   (void)configured;
-  const int T = g.tiles_m * g.tiles_n, cus = compute_units_q8();
+  const int T = g.tiles_m * g.tiles_n * g.splits, cus = compute_units_q8();
   hipLaunchKernelGGL(kern, dim3(T < cus ? T : cus), dim3(256), LDS_BYTES, st, g);
 }
 
@@ -389,7 +422,9 @@ bool mfma_dense_q8_supported(int n, int m, i64 N) {
   return mfma_dense_supported(n, m, N) && n >= 3 * BK && m >= 3 * BK;
 }
 
-void mfma_dense_q8(int trans_w, const void* Wq, int n, int m, const void* act, void* out, i64 N, hipStream_t st) {
+// The contraction is split exactly where the bf16 product splits it, so that a layer gets the same bits either way.
+void mfma_dense_q8(int trans_w, const void* Wq, int n, int m, const void* act, void* out, i64 N, void* ws, hipStream_t st) {
+  const int M = trans_w ? m : n, K = trans_w ? n : m;
   DenseQ8Args g{};
   g.Q = (const int8_t*)Wq;
   g.scale = (const float*)((const char*)Wq + weight_q8_scale_offset(n, m));
@@ -398,15 +433,18 @@ void mfma_dense_q8(int trans_w, const void* Wq, int n, int m, const void* act, v
   g.ldq = m;
   g.ldb = N;
   g.ldc = N;
+  g.tiles_m = M / BM;
   g.tiles_n = (int)(N / BN);
-  if (!trans_w) {
-    g.tiles_m = n / BM;
-    g.ktiles = m / BK;
-    launch_dense_q8<true>(g, st);
+  g.splits = mfma_dense_splits(M, N, K);
+  g.parts = (float*)ws;
+  g.ktiles = K / BK / g.splits;
+  if (g.splits > 1) {
+    if (trans_w) launch_dense_q8<false, true>(g, st);
+    else launch_dense_q8<true, true>(g, st);
+    mfma_dense_reduce((const float*)ws, g.splits, M, N, out, N, N, st);
   } else {
-    g.tiles_m = m / BM;
-    g.ktiles = n / BK;
-    launch_dense_q8<false>(g, st);
+    if (trans_w) launch_dense_q8<false, false>(g, st);
+    else launch_dense_q8<true, false>(g, st);
   }
 }
 

@@ -108,9 +108,9 @@ void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const A
   StageTimer tm(POETX_STAGE_DENSE, st);
   const i64 N = min64(act.cols, out.cols);
   const bool whole = act.ld == act.cols && out.ld == out.cols && act.cols == out.cols;
-  if (w_q8) mfma_dense_q8(trans_w, W, n, m, act.p, out.out(), N, st);
+  if (w_q8) mfma_dense_q8(trans_w, W, n, m, act.p, out.out(), N, part, st);
   else if (use_mfma(dtype) && act.ld == act.cols && mfma_dense_supported(n, m, act.cols) && aligned16(W) && aligned16(act.p))
-    mfma_dense(trans_w, W, n, m, act.p, act.cols, out.out(), out.ld, N, st);
+    mfma_dense(trans_w, W, n, m, act.p, act.cols, out.out(), out.ld, N, part, st);
   else if (dtype == POETX_F32 && !g_force_fma.load() && whole && mfma_dense_f32_supported(n, m, N) && mfma_dense_f32_fills(trans_w ? m : n, N) &&
            aligned16(W) && aligned16(act.p) && aligned16(out.p))
     mfma_dense_f32(trans_w, W, n, m, act.p, out.out(), N, st);
@@ -131,7 +131,8 @@ i64 internal_columns(const poetx_linear_desc* d) {
   const i64 N = d->n_tokens;
   if (g_force_fma.load()) return N;                     // the plain kernels know one token count only
   const i64 Np = (N + 255) / 256 * 256;
-  if (d->dtype == POETX_BF16 && mfma_dense_supported(d->d_out, d->d_in, Np) && mfma_dense_worth_padding(d->d_out, d->d_in, Np)) return Np;
+  if (N == Np) return N;
+  if (d->dtype == POETX_BF16 && mfma_dense_supported(d->d_out, d->d_in, Np) && mfma_dense_worth_padding(d->d_out, d->d_in, N)) return Np;
   return (N + 7) / 8 * 8;
 }
 
@@ -163,6 +164,11 @@ size_t dense_part_bytes(const poetx_linear_desc* d) {
     const size_t b = edge_dense_workspace_bytes(d->dtype, d->d_in, N, d->d_out);
     w = f > w ? f : w;
     w = b > w ? b : w;
+    if (d->dtype == POETX_BF16 && mfma_dense_supported(d->d_out, d->d_in, N)) {
+      const size_t mf = mfma_dense_workspace_bytes(d->d_out, N, d->d_in), mb = mfma_dense_workspace_bytes(d->d_in, N, d->d_out);
+      w = mf > w ? mf : w;
+      w = mb > w ? mb : w;
+    }
   }
   return align256(w);
 }

@@ -79,17 +79,20 @@ void perm_validate_launch(const int32_t* perm, int d, int32_t* scratch, hipStrea
 // ---- matrix-core path for bf16 (mfma_*.hip) -------------------------------------------
 bool mfma_dense_supported(int n, int m, i64 N);
 // act: K x N_act dense (whole tiles); the first N columns of the product go to out (row stride ld_out, any alignment
-// where N < N_act)
-void mfma_dense(int trans_w, const void* W, int n, int m, const void* act, i64 N_act, void* out, i64 ld_out, i64 N, hipStream_t st);
-// is a token count padded to Np = whole tiles better served by the streaming product than by the edge one?
-bool mfma_dense_worth_padding(int n, int m, i64 Np);
+// where N < N_act).  ws: the bytes the query reports (M, N_act, K of the product; parts of a split contraction).
+size_t mfma_dense_workspace_bytes(i64 M, i64 N, i64 K);
+void mfma_dense(int trans_w, const void* W, int n, int m, const void* act, i64 N_act, void* out, i64 ld_out, i64 N, void* ws, hipStream_t st);
+int mfma_dense_splits(i64 M, i64 N, i64 K);   // contraction ranges of that product
+void mfma_dense_reduce(const float* parts, int splits, i64 M, i64 Np, void* out, i64 ld_out, i64 N, hipStream_t st);
+// is a ragged token count better padded to whole tiles for the streaming product than left to the edge one?
+bool mfma_dense_worth_padding(int n, int m, i64 N);
 // the same products for fp32 tensors (fp32 MFMA, mfma_dense_f32.hip)
 bool mfma_dense_f32_supported(int n, int m, i64 N);
 bool mfma_dense_f32_fills(int M, i64 N);
 void mfma_dense_f32(int trans_w, const void* W, int n, int m, const void* act, void* out, i64 N, hipStream_t st);
 // the same products on a quantised weight buffer (codes + row scales), dequantised inside the kernel (mfma_dense_q8.hip)
 bool mfma_dense_q8_supported(int n, int m, i64 N);
-void mfma_dense_q8(int trans_w, const void* Wq, int n, int m, const void* act, void* out, i64 N, hipStream_t st);
+void mfma_dense_q8(int trans_w, const void* Wq, int n, int m, const void* act, void* out, i64 N, void* ws, hipStream_t st);   // ws as mfma_dense
 bool mfma_apply_left_supported(int d, i64 cols, i64 ld, int b);
 void mfma_apply_left(const void* V, void* out, int d, i64 cols, i64 ld, const int32_t* perm,
                      const void* E, int b, int transpose_G, hipStream_t st);

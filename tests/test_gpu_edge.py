@@ -130,3 +130,37 @@ def test_ragged_token_counts_on_the_streaming_kernels(lib, m, n, N, b):
             got = {"Z": to_np(turn(Z)), "dX": to_np(turn(dX)), "dtheta_R": to_np(dth["R"]), "dtheta_P": to_np(dth["P"])}
             for key, v in got.items():
                 assert rel_err(v, ref[key]) <= TOL["bf16"], (key, layout, mem)
+
+
+@pytest.mark.parametrize("n,m,N", [
+    (256, 256, 256),        # 128 x 128 tiles, contraction too short to split
+    (256, 2048, 256),       # ... split over workgroups
+    (512, 512, 1024),       # 128 x 128 tiles
+    (2048, 512, 2048),      # 256 x 128 tiles one way, 128 x 128 the other
+    (2304, 2048, 2560),     # one way 256 x 128 tiles that do not fill whole groups of four tile rows
+    (2048, 2048, 1801),     # padded to 2048: ragged stores from 128 x 128 tiles
+    (512, 8192, 300),       # padded and split: ragged reduction
+])
+def test_dense_tiles(lib, n, m, N):
+    """Every output tile and contraction split of the streaming bf16 product, both directions, against float64 on the same
+    bf16 operands: a whole pass with blocks equal to the identity is the dense product between two exact
+    permutation round trips.  One bf16 rounding of an fp32 sum: 2^-8 of the largest value is generous."""
+    rng = np.random.Generator(np.random.PCG64(9400 + n + m + N))
+    b = 256
+    X, dZ = round_bf16(rng.standard_normal((m, N))), round_bf16(rng.standard_normal((n, N)))
+    W = round_bf16(rng.standard_normal((n, m)) * 0.02)
+    bf = torch.bfloat16
+    desc = lib.make_desc(m, n, b, 2, N, lib.BF16)
+    ws = torch.full((lib.poetx_linear_workspace_bytes(desc) // 4,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
+    pi = {"R": torch.from_numpy(rng.permutation(m).astype(np.int32)).cuda(), "P": torch.from_numpy(rng.permutation(n).astype(np.int32)).cuda()}
+    blk = {s: torch.zeros((d // b, 2, b, b), dtype=bf, device="cuda") for s, d in (("R", m), ("P", n))}
+    Xd, dZd, Wd = to_dev(X, bf), to_dev(dZ, bf), to_dev(W, bf)
+    guard = torch.full((n * N + 512,), -7.0, dtype=bf, device="cuda")
+    Z, B = torch.empty((n, N), dtype=bf, device="cuda"), guard[256:256 + n * N].view(n, N)
+    dX, dA = torch.empty((m, N), dtype=bf, device="cuda"), torch.empty((m, N), dtype=bf, device="cuda")
+    lib.poetx_linear_fwd(desc, Xd, Wd, pi["R"], pi["P"], blk["R"], blk["P"], Z, B, ws)
+    lib.poetx_linear_bwd_input(desc, dZd, Wd, pi["R"], pi["P"], blk["R"], blk["P"], dX, dA, ws)
+    torch.cuda.synchronize()
+    assert rel_err(to_np(B), W @ X) <= 2.0 ** -8 and torch.equal(Z, B)
+    assert rel_err(to_np(dA), W.T @ dZ) <= 2.0 ** -8 and torch.equal(dX, dA)
+    assert torch.all(guard[:256] == -7.0) and torch.all(guard[256 + n * N:] == -7.0)

@@ -191,15 +191,15 @@ size_t mfma_cnp_bwd_ws_bytes_per_elem() { return 20; }
 
 void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void* E_bf16, float* ws, hipStream_t st) {
   const int nb = d / b;
+  if (lds_cnp_supported(d, b)) {   // whole chain in one launch, block resident in LDS
+    lds_cnp_build(theta, nb, k, G_f32, E_bf16, ws, st);
+    return;
+  }
   const i64 total = (i64)nb * b * b;
   float* Qf = ws;
   uint16_t* Qb = (uint16_t*)(Qf + total);
   uint16_t* H[2] = {Qb + total, Qb + 2 * total};
   skew_materialize_launch(theta, b, nb, Qf, Qb, nullptr, st);
-  if (lds_cnp_supported(d, b)) {   // whole chain in one launch, block resident in LDS
-    lds_cnp_build(Qf, Qb, d, k, G_f32, E_bf16, st);
-    return;
-  }
   const uint16_t* cur = Qb;  // H'_1 = Q
   for (int step = 0; step < k; ++step) {
     const bool last = step == k - 1;
@@ -217,11 +217,9 @@ void mfma_cnp_bwd(const float* theta, const float* dG, int d, int b, int k, floa
                   hipStream_t st) {
   const int nb = d / b;
   const i64 total = (i64)nb * b * b;
-  if (lds_cnp_supported(d, b)) {   // two launches, block resident in LDS; scratch = bf16(Q) + (k + 1) fp32 matrices
-    uint16_t* Qb = (uint16_t*)ws;
-    skew_materialize_launch(theta, b, nb, nullptr, Qb, nullptr, st);
-    const float* dQ = lds_cnp_bwd_chain(Qb, dG, nb, k, ws + total, st);
-    skew_project_launch(dQ, b, d, dtheta, accumulate, st);
+  if (lds_cnp_supported(d, b)) {   // block resident in LDS
+    const SeriesSide side{theta, dG, 0, 1, d, dtheta};
+    lds_cnp_bwd(&side, 1, k, accumulate, ws, st);
     return;
   }
   float* Qf = ws;

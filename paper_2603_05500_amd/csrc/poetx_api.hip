@@ -560,19 +560,14 @@ int poetx_linear_bwd_input(const poetx_linear_desc* desc, const void* dZ, const 
 }
 
 // Series backward of both sides as one batch on the on-chip chains (b = 256): dG holds the block
-// gradients of the P side, then of the R side; Qb and chain are scratch behind it.
+// gradients of the P side, then of the R side; the chain's scratch follows.
 static void cnp_bwd_both_on_chip(const float* theta_R, const float* theta_P, float* dG, int m, int n, int b, int k,
                                  float* dtheta_R, float* dtheta_P, int accumulate, hipStream_t st) {
-  const int nbP = n / b, nbR = m / b, nbt = nbP + nbR;
+  const int nbP = n / b, nbt = nbP + m / b;
   const size_t bb = (size_t)b * b;
-  uint16_t* Qb = (uint16_t*)(dG + nbt * bb);                // [nbt][b][b] bf16 (one float slot per element)
-  float* chain = dG + 2 * nbt * bb;                         // (k + 1) * nbt * b * b floats
+  const SeriesSide sides[2] = {{theta_P, dG, 0, 1, n, dtheta_P}, {theta_R, dG + nbP * bb, 0, 1, m, dtheta_R}};
   StageTimer tm(POETX_STAGE_CNP_BWD, st);
-  skew_materialize_launch(theta_P, b, nbP, nullptr, Qb, nullptr, st);
-  skew_materialize_launch(theta_R, b, nbR, nullptr, Qb + nbP * bb, nullptr, st);
-  const float* dQ = lds_cnp_bwd_chain(Qb, dG, nbt, k, chain, st);
-  skew_project_launch(dQ, b, n, dtheta_P, accumulate != 0, st);
-  skew_project_launch(dQ + nbP * bb, b, m, dtheta_R, accumulate != 0, st);
+  lds_cnp_bwd(sides, 2, k, accumulate != 0, dG + nbt * bb, st);   // at most (k + 1) * nbt * b * b floats
 }
 
 static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act& dZ, const Act& saved_B,

@@ -118,12 +118,15 @@ void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void*
 void mfma_cnp_bwd(const float* theta, const float* dG, int d, int b, int k, float* dtheta, int accumulate,
                   float* ws, hipStream_t st);
 // b = 256: whole chain of a block in one launch, block resident in LDS (mfma_cnp_lds.hip).
-// Qf / Qb: Q in fp32 / bf16, [nb][b][b].  The backward needs (k + 1) * nb*b*b floats of scratch.
 bool lds_cnp_supported(int d, int b);
-void lds_cnp_build(const float* Qf, const uint16_t* Qb, int d, int k, float* G_f32, void* E_bf16, hipStream_t st);
-// dL/dG of nb blocks -> dL/dQ (returned pointer lies inside ws); the blocks may belong to
-// several sides, the chain does not care.
-const float* lds_cnp_bwd_chain(const uint16_t* Qb, const float* dG, int nb, int k, float* ws, hipStream_t st);
+void lds_cnp_build(const float* theta, int nb, int k, float* G_f32, void* E_bf16, float* ws, hipStream_t st);   // ws: 1.5 floats per block element
+// Backward of one or two sides (dG of a side: one matrix per block, nsplit = 1).  ws: lds_cnp_bwd_ws_floats(all blocks, k) floats.
+size_t lds_cnp_bwd_ws_floats(int nb, int k);
+void lds_cnp_bwd(const SeriesSide* sides, int nsides, int k, int accumulate, float* ws, hipStream_t st);
+// b = 256, nb0 + nb1 blocks of two sides: bf16(Q) and, where Q2 is given, 2Q in the chain's order (skew_tiled.hip)
+void skew_materialize_chain_launch(const float* theta0, i64 nb0, const float* theta1, i64 nb1, float* Q2, uint16_t* Qb, hipStream_t st);
+// dL/dQ of nb0 + nb1 blocks -> packed gradients of two sides (skew_tiled.hip)
+void skew_project_sides_launch(const float* M, int b, i64 nb0, float* dtheta0, i64 nb1, float* dtheta1, int accumulate, hipStream_t st);
 // Q of nb blocks from packed parameters: Qf fp32 and/or Qb bf16, [nb][b][b] (either may be null).
 // Tb = bf16(-Q).
 void skew_materialize_launch(const float* theta, int b, i64 nb, float* Qf, uint16_t* Qb, uint16_t* Tb, hipStream_t st);

@@ -23,20 +23,29 @@ __device__ inline void pair_decode(int p, int T, int& I, int& J) {
   J = I + p;
 }
 
+// The upper triangle's tile (I, J) of a block into LDS, zeros on and below the diagonal.  All 16 loads of a thread are in
+// flight together (four at a time, a launch over 32 blocks of 256 took 10.8 us instead of 6.9).
+__device__ __forceinline__ void load_tile(float (&tile)[ST][ST + 1], const float* th, int I, int J, int b) {
+  const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+  float v[ST / 4];
+#pragma unroll
+  for (int s = 0; s < ST / 4; ++s) {
+    const int i = I * ST + r0 + 4 * s, col = J * ST + c;
+    v[s] = i < col ? th[packed_index(i, col, b)] : 0.f;
+  }
+#pragma unroll
+  for (int s = 0; s < ST / 4; ++s) tile[r0 + 4 * s][c] = v[s];
+  __syncthreads();
+}
+
 __global__ __launch_bounds__(256) void skew_materialize_tiled_kernel(const float* __restrict__ theta, int b, float* __restrict__ Qf,
                                                                      uint16_t* __restrict__ Qb, uint16_t* __restrict__ Tb) {
   __shared__ float tile[ST][ST + 1];
   int I, J;
   pair_decode(blockIdx.x, b / ST, I, J);
   const i64 j = blockIdx.y;
-  const float* th = theta + j * ((i64)b * (b - 1) / 2);
+  load_tile(tile, theta + j * ((i64)b * (b - 1) / 2), I, J, b);
   const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
-#pragma unroll 4
-  for (int r = r0; r < ST; r += 4) {
-    const int i = I * ST + r, col = J * ST + c;
-    tile[r][c] = i < col ? th[packed_index(i, col, b)] : 0.f;
-  }
-  __syncthreads();
   auto put = [&](i64 at, float q) {
     if (Qf) Qf[at] = q;
     if (Qb) Qb[at] = float_to_bf16_bits(q);
@@ -51,16 +60,60 @@ __global__ __launch_bounds__(256) void skew_materialize_tiled_kernel(const float
   }
 }
 
-__global__ __launch_bounds__(256) void skew_project_tiled_kernel(const float* __restrict__ M, int b, float* __restrict__ dtheta,
-                                                                 int accumulate) {
+// What the on-chip chains of b = 256 read: bf16(Q) row major, 16 bytes per store, and (forward) 2Q in fp32, 32 x 32 tiles in
+// accumulator order: [block][column tile][row tile][g][lane][e] = 2Q(8g + 4 (lane / 32) + e, lane % 32) of the tile.  Blocks
+// 0 .. nb0 - 1 come from theta, the rest from theta2.
+__global__ __launch_bounds__(256) void skew_materialize_chain_kernel(const float* __restrict__ theta, const float* __restrict__ theta2, int nb0,
+                                                                     float* __restrict__ Q2, uint16_t* __restrict__ Qb) {
+  constexpr int B = 256;
+  __shared__ float tile[ST][ST + 1];
+  int I, J;
+  pair_decode(blockIdx.x, B / ST, I, J);
+  const i64 j = blockIdx.y;
+  load_tile(tile, (j < nb0 ? theta + j * (B * (B - 1) / 2) : theta2 + (j - nb0) * (B * (B - 1) / 2)), I, J, B);
+  const int tid = threadIdx.x;
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll 1
+  for (int m = 0; m < (I == J ? 1 : 2); ++m) {          // the tile, then its mirror image
+    auto q = [&](int r, int c) {
+      if (m) return -tile[c][r];
+      return I != J || c > r ? tile[r][c] : (c < r ? -tile[c][r] : 0.f);
+    };
+    const int R = m ? J : I, C = m ? I : J;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int r = 32 * s + tid / 8, c = 8 * (tid % 8);
+      u32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = float_to_bf16_bits(q(r, c + 2 * e)) | (uint32_t)float_to_bf16_bits(q(r, c + 2 * e + 1)) << 16;
+      *reinterpret_cast<u32x4*>(Qb + (j * B + R * ST + r) * B + C * ST + c) = o;
+    }
+    if (Q2) {
+      const int n = tid & 31, r0 = 8 * (tid >> 6) + 4 * ((tid >> 5) & 1);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int rt = s & 1, ct = s >> 1;
+        f32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = 2.f * q(32 * rt + r0 + e, 32 * ct + n);
+        *reinterpret_cast<f32x4*>(Q2 + ((j * 8 + 2 * C + ct) * 8 + 2 * R + rt) * 1024 + tid * 4) = o;
+      }
+    }
+  }
+}
+
+// blocks 0 .. nb0 - 1 of M go to dtheta, the rest to dtheta2
+__global__ __launch_bounds__(256) void skew_project_tiled_kernel(const float* __restrict__ M, int b, int nb0, float* __restrict__ dtheta,
+                                                                 float* __restrict__ dtheta2, int accumulate) {
   __shared__ float up[ST][ST + 1], lo[ST][ST + 1];
   int I, J;
   pair_decode(blockIdx.x, b / ST, I, J);
   const i64 j = blockIdx.y;
   const float* Mj = M + j * (i64)b * b;
-  float* dt = dtheta + j * ((i64)b * (b - 1) / 2);
+  float* dt = (j < nb0 ? dtheta + j * ((i64)b * (b - 1) / 2) : dtheta2 + (j - nb0) * ((i64)b * (b - 1) / 2));
   const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
-#pragma unroll 4
+#pragma unroll 16
   for (int r = r0; r < ST; r += 4) {
     up[r][c] = Mj[(i64)(I * ST + r) * b + J * ST + c];
     lo[r][c] = Mj[(i64)(J * ST + r) * b + I * ST + c];
@@ -86,9 +139,19 @@ void skew_materialize_tiled_launch(const float* theta, int b, i64 nb, float* Qf,
   hipLaunchKernelGGL(skew_materialize_tiled_kernel, dim3(T * (T + 1) / 2, (unsigned)nb), dim3(256), 0, st, theta, b, Qf, Qb, Tb);
 }
 
+void skew_materialize_chain_launch(const float* theta0, i64 nb0, const float* theta1, i64 nb1, float* Q2, uint16_t* Qb, hipStream_t st) {
+  constexpr int T = 256 / ST;
+  hipLaunchKernelGGL(skew_materialize_chain_kernel, dim3(T * (T + 1) / 2, (unsigned)(nb0 + nb1)), dim3(256), 0, st, theta0, theta1, (int)nb0, Q2, Qb);
+}
+
 void skew_project_tiled_launch(const float* M, int b, i64 nb, float* dtheta, int accumulate, hipStream_t st) {
   const int T = b / ST;
-  hipLaunchKernelGGL(skew_project_tiled_kernel, dim3(T * (T + 1) / 2, (unsigned)nb), dim3(256), 0, st, M, b, dtheta, accumulate);
+  hipLaunchKernelGGL(skew_project_tiled_kernel, dim3(T * (T + 1) / 2, (unsigned)nb), dim3(256), 0, st, M, b, (int)nb, dtheta, (float*)nullptr, accumulate);
+}
+
+void skew_project_sides_launch(const float* M, int b, i64 nb0, float* dtheta0, i64 nb1, float* dtheta1, int accumulate, hipStream_t st) {
+  const int T = b / ST;
+  hipLaunchKernelGGL(skew_project_tiled_kernel, dim3(T * (T + 1) / 2, (unsigned)(nb0 + nb1)), dim3(256), 0, st, M, b, (int)nb0, dtheta0, dtheta1, accumulate);
 }
 
 }  // namespace poetx

@@ -1,14 +1,17 @@
 // Cayley-Neumann series and its backward on the matrix cores (Sec. 3.4, Eq. 8-9),
-// batched over the blocks of one side, for block sides that are multiples of 256.
+// batched over the blocks of one side, for block sides that do not fit on chip (b = 512).
 //
-// Every b x b product runs as bf16 x bf16 -> fp32 on the batched tile kernel.  To
-// keep the small terms, the chain is carried in residual form: with H = 2I + H'
-// Horner's rule H <- H Q + 2I becomes H' <- 2Q + H' Q, where only the small
-// product H' Q goes through bf16 and the 2Q term is added in fp32.
-// After k steps H' is G - I.  The backward recursion (see fma_cnp_bwd) is carried
-// the same way: A = 2I + A', A' <- 2T + A' T and Bm <- 2D + A' D + Bm T with
-// T = -Q, the 2D term added in fp32; the two products of one step are independent
-// and share one launch.
+// Every b x b product runs as bf16 x bf16 -> fp32 on the batched tile kernel; the dominant terms enter in fp32 in its
+// epilogue.  A launch costs 25 us or so however small (512-deep contraction, fill, drain, epilogue), so the
+// recurrences are chosen for few products and fewer launches:
+//   forward    X = Q^2, then Horner's rule in X on the pairs of powers,
+//              G - I = sum_i X^i (c_{2i+1} Q + c_{2i+2} X),  c_p = 2 for p <= k, 1 for p = k + 1:
+//              1 + floor(k/2) products (k by Horner's rule in Q)
+//   backward   P_0 = D = dL/dG,  P_m = D + P_{m-1} T,  Z_0 = D,  Z_m = P_m + T Z_{m-1},  dL/dQ = Z_k + Z_{k-1}
+//              with T = Q^T = -Q (see mfma_cnp_lds.hip); P_m and Z_{m-1} share a launch: 2k products in k + 1 launches
+//              (3k - 1 products by the two-sided Horner rule)
+// Against 64 bits both round less than the Horner forms (b = 512, k = 5: 3.8e-4 -> 3.5e-4 of the gradient, 2.67e-4 -> 2.66e-4
+// of G - I before its own rounding).
 #include "mfma_gemm.h"
 
 namespace poetx {
@@ -48,44 +51,28 @@ __global__ void to_bf16_kernel(const float4* __restrict__ in, uint2* __restrict_
   out[idx] = o;
 }
 
-// value = acc + coef * Qf(row, col).  Writes whichever outputs are set:
-// Hn (bf16 chain value), G (fp32, + I), E (bf16 pair [nb][2][b][b]: value and its transpose).
-struct EpiHorner {
-  const float* Qf;
-  float coef;
+// Forward.  FIRST: acc = X; C (in: Q, out: 2Q + 2X), Xb = bf16(X), value v = 2Q + X.  Otherwise v = acc + C.
+// Writes whichever outputs are set: Hn (bf16 chain value), G (fp32, + I), E (bf16 pair [nb][2][b][b]: value and its transpose).
+template <bool FIRST>
+struct EpiFwd {
+  float* C;
+  uint16_t* Xb;
   int b;
   uint16_t* Hn;
   float* G;
   uint16_t* E;
-  __device__ void operator()(int j, int, int row, int col, float4 a) const {
-    const i64 o = ((i64)j * b + row) * b + col;
-    const float4 q = *reinterpret_cast<const float4*>(Qf + o);
-    float v[4] = {a.x + coef * q.x, a.y + coef * q.y, a.z + coef * q.z, a.w + coef * q.w};
-    uint2 pk;
-    pk.x = mm::pack2_bf16(v[0], v[1]);
-    pk.y = mm::pack2_bf16(v[2], v[3]);
-    if (Hn) *reinterpret_cast<uint2*>(Hn + o) = pk;
-    if (G) {
-      float4 gv = make_float4(v[0], v[1], v[2], v[3]);
-      gv.x += (row == col) ? 1.f : 0.f;
-      gv.y += (row == col + 1) ? 1.f : 0.f;
-      gv.z += (row == col + 2) ? 1.f : 0.f;
-      gv.w += (row == col + 3) ? 1.f : 0.f;
-      *reinterpret_cast<float4*>(G + o) = gv;
-    }
-    if (E) {
-      const i64 base = (i64)j * 2 * b * b;
-      *reinterpret_cast<uint2*>(E + base + (i64)row * b + col) = pk;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) E[base + (i64)b * b + (i64)(col + e) * b + row] = float_to_bf16_bits(v[e]);
-    }
-  }
-  // eight consecutive columns: 32-byte reads of Q, 16-byte stores of the bf16 outputs
   __device__ void wide(int j, int, int row, int col, float4 lo, float4 hi) const {
     const i64 o = ((i64)j * b + row) * b + col;
-    const float4 q0 = *reinterpret_cast<const float4*>(Qf + o), q1 = *reinterpret_cast<const float4*>(Qf + o + 4);
-    const float v[8] = {lo.x + coef * q0.x, lo.y + coef * q0.y, lo.z + coef * q0.z, lo.w + coef * q0.w,
-                        hi.x + coef * q1.x, hi.y + coef * q1.y, hi.z + coef * q1.z, hi.w + coef * q1.w};
+    const float4 c0 = *reinterpret_cast<const float4*>(C + o), c1 = *reinterpret_cast<const float4*>(C + o + 4);
+    const float c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w}, a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = FIRST ? a[e] + 2.f * c[e] : a[e] + c[e];
+    if (FIRST && Xb) {
+      *reinterpret_cast<uint4*>(Xb + o) = make_uint4(mm::pack2_bf16(a[0], a[1]), mm::pack2_bf16(a[2], a[3]), mm::pack2_bf16(a[4], a[5]), mm::pack2_bf16(a[6], a[7]));
+      *reinterpret_cast<float4*>(C + o) = make_float4(v[0] + a[0], v[1] + a[1], v[2] + a[2], v[3] + a[3]);
+      *reinterpret_cast<float4*>(C + o + 4) = make_float4(v[4] + a[4], v[5] + a[5], v[6] + a[6], v[7] + a[7]);
+    }
     const uint4 pk = make_uint4(mm::pack2_bf16(v[0], v[1]), mm::pack2_bf16(v[2], v[3]), mm::pack2_bf16(v[4], v[5]), mm::pack2_bf16(v[6], v[7]));
     if (Hn) *reinterpret_cast<uint4*>(Hn + o) = pk;
     if (G) {
@@ -104,69 +91,53 @@ struct EpiHorner {
   }
 };
 
-// One backward step in one launch.  Batches [0, nb): Bm_next = acc + 2 D  (bf16 chain value and/or
-// the final fp32 result).  Batches [nb, 2nb): A'_next = acc - 2 Q (bf16).
-struct EpiBwdStep {
-  const float* D;
-  const float* Qf;
+// Backward: batches [0, nb) are the first problem of a launch, [nb, 2 nb) the second.  value = acc + add (+ add2), written
+// as bf16 and / or fp32 (the fp32 output may take the place of either addend: same element, same thread).
+struct EpiAdd {
+  struct Side {
+    const float* add;
+    const float* add2;
+    uint16_t* bf;
+    float* f;
+  } s[2];
   int b, nb;
-  uint16_t* Bn;
-  float* Bf;
-  uint16_t* An;
-  __device__ void operator()(int batch, int, int row, int col, float4 a) const {
-    const bool second = batch >= nb;
-    const int j = second ? batch - nb : batch;
-    const i64 o = ((i64)j * b + row) * b + col;
-    const float4 d = *reinterpret_cast<const float4*>((second ? Qf : D) + o);
-    const float coef = second ? -2.f : 2.f;
-    const float4 v = make_float4(a.x + coef * d.x, a.y + coef * d.y, a.z + coef * d.z, a.w + coef * d.w);
-    uint2 pk;
-    pk.x = mm::pack2_bf16(v.x, v.y);
-    pk.y = mm::pack2_bf16(v.z, v.w);
-    if (second) {
-      *reinterpret_cast<uint2*>(An + o) = pk;
-    } else {
-      if (Bn) *reinterpret_cast<uint2*>(Bn + o) = pk;
-      if (Bf) *reinterpret_cast<float4*>(Bf + o) = v;
-    }
-  }
   __device__ void wide(int batch, int, int row, int col, float4 lo, float4 hi) const {
     const bool second = batch >= nb;
-    const int j = second ? batch - nb : batch;
-    const i64 o = ((i64)j * b + row) * b + col;
-    const float* src = (second ? Qf : D) + o;
-    const float4 d0 = *reinterpret_cast<const float4*>(src), d1 = *reinterpret_cast<const float4*>(src + 4);
-    const float coef = second ? -2.f : 2.f;
-    const float4 v0 = make_float4(lo.x + coef * d0.x, lo.y + coef * d0.y, lo.z + coef * d0.z, lo.w + coef * d0.w);
-    const float4 v1 = make_float4(hi.x + coef * d1.x, hi.y + coef * d1.y, hi.z + coef * d1.z, hi.w + coef * d1.w);
-    const uint4 pk = make_uint4(mm::pack2_bf16(v0.x, v0.y), mm::pack2_bf16(v0.z, v0.w), mm::pack2_bf16(v1.x, v1.y), mm::pack2_bf16(v1.z, v1.w));
-    if (second) {
-      *reinterpret_cast<uint4*>(An + o) = pk;
-    } else {
-      if (Bn) *reinterpret_cast<uint4*>(Bn + o) = pk;
-      if (Bf) {
-        *reinterpret_cast<float4*>(Bf + o) = v0;
-        *reinterpret_cast<float4*>(Bf + o + 4) = v1;
-      }
+    const Side& d = s[second ? 1 : 0];
+    const i64 o = ((i64)(second ? batch - nb : batch) * b + row) * b + col;
+    float4 a0 = *reinterpret_cast<const float4*>(d.add + o), a1 = *reinterpret_cast<const float4*>(d.add + o + 4);
+    a0 = make_float4(a0.x + lo.x, a0.y + lo.y, a0.z + lo.z, a0.w + lo.w);
+    a1 = make_float4(a1.x + hi.x, a1.y + hi.y, a1.z + hi.z, a1.w + hi.w);
+    if (d.add2) {
+      const float4 b0 = *reinterpret_cast<const float4*>(d.add2 + o), b1 = *reinterpret_cast<const float4*>(d.add2 + o + 4);
+      a0 = make_float4(a0.x + b0.x, a0.y + b0.y, a0.z + b0.z, a0.w + b0.w);
+      a1 = make_float4(a1.x + b1.x, a1.y + b1.y, a1.z + b1.z, a1.w + b1.w);
+    }
+    if (d.bf) *reinterpret_cast<uint4*>(d.bf + o) = make_uint4(mm::pack2_bf16(a0.x, a0.y), mm::pack2_bf16(a0.z, a0.w), mm::pack2_bf16(a1.x, a1.y), mm::pack2_bf16(a1.z, a1.w));
+    if (d.f) {
+      *reinterpret_cast<float4*>(d.f + o) = a0;
+      *reinterpret_cast<float4*>(d.f + o + 4) = a1;
     }
   }
 };
 
-// 512-wide blocks take 256 x 256 output tiles (8 waves of 128 x 64): four times the work per
-// workgroup for the same 512-deep contraction, whose fill and drain dominate a 128 x 128 tile.
-inline bool big_tiles(int b) { return b % 256 == 0 && b >= 512; }
+// 128 x 128 tiles: 256 x 256 ones have four times the work per workgroup for the same fill and drain, but leave most of the
+// chip idle below 128 blocks (build + backward of 16 blocks, k = 5, by Horner's rule: 354 against 210 us).
 mm::Args batched_args(int b) {
   mm::Args g{};
-  const int t = big_tiles(b) ? 256 : CBM;
-  g.tiles_m = b / t;
-  g.tiles_n = b / t;
+  g.tiles_m = b / CBM;
+  g.tiles_n = b / CBN;
   return g;
 }
 template <class Epi>
-void launch_product(int b, const mm::Args& g, Epi epi, int batches, hipStream_t st) {
-  if (big_tiles(b)) mm::launch<256, 256, 2, 4, true, false, false, CNS, true>(g, epi, batches, 1, st);
-  else mm::launch<CBM, CBN, 2, 2, true, false, false, CNS, true>(g, epi, batches, 1, st);
+void launch_product(const mm::Args& g, Epi epi, int batches, hipStream_t st) {
+  mm::launch<CBM, CBN, 2, 2, true, false, false, CNS, true>(g, epi, batches, 1, st);
 }
+// Blocks worked off together: two workgroups per CU, and what passes from launch to launch (5 MB a block in the backward,
+// rewritten in place by the next group) stays in the 256 MB memory-side cache.  Build + backward at k = 5 in groups of 16 /
+// 32 / 48 against all at once, us: 80 blocks 1029 / 906 / 940 / 999, 160 blocks 2057 / 1791 / 1919 / 2241.
+constexpr int GROUP = 32;
+inline int group_size(int blocks) { return ceil_div(blocks, ceil_div(blocks, GROUP)); }   // equal groups
 void set_src(mm::Source& s, const uint16_t* A, const uint16_t* B, int b) {
   s.A = A; s.B = B; s.lda = b; s.ldb = b; s.sA = (i64)b * b; s.sB = (i64)b * b; s.ktiles = b / CBK;
 }
@@ -184,86 +155,98 @@ void skew_materialize_launch(const float* theta, int b, i64 nb, float* Qf, uint1
 
 bool mfma_cnp_supported(int d, int b) { return (b == 256 || b == 512) && d % b == 0; }
 
-// bytes of scratch per block element (nb*b*b elements): forward Qf(4) + Qb, H0, H1 (2 each);
-// backward Qf(4) + Tb, Db, A0, A1, B0, B1 (2 each) + Bfinal(4).
-size_t mfma_cnp_build_ws_bytes_per_elem() { return 10; }
-size_t mfma_cnp_bwd_ws_bytes_per_elem() { return 20; }
-
+// ws: 3 floats per block element: Q (later 2Q + 2X) in fp32, then bf16(Q), bf16(X) and two chain values.
 void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void* E_bf16, float* ws, hipStream_t st) {
-  const int nb = d / b;
+  const int all = d / b;
   if (lds_cnp_supported(d, b)) {   // whole chain in one launch, block resident in LDS
-    lds_cnp_build(theta, nb, k, G_f32, E_bf16, ws, st);
+    lds_cnp_build(theta, all, k, G_f32, E_bf16, ws, st);
     return;
   }
-  const i64 total = (i64)nb * b * b;
-  float* Qf = ws;
-  uint16_t* Qb = (uint16_t*)(Qf + total);
-  uint16_t* H[2] = {Qb + total, Qb + 2 * total};
-  skew_materialize_launch(theta, b, nb, Qf, Qb, nullptr, st);
-  const uint16_t* cur = Qb;  // H'_1 = Q
-  for (int step = 0; step < k; ++step) {
-    const bool last = step == k - 1;
+  const i64 bb = (i64)b * b;
+  const int group = group_size(all);
+  for (int j0 = 0; j0 < all; j0 += group) {
+    const int nb = all - j0 < group ? all - j0 : group;
+    const i64 total = nb * bb;
+    float* C = ws;
+    uint16_t* Qb = (uint16_t*)(C + total);
+    uint16_t* Xb = Qb + total;
+    uint16_t* H[2] = {Xb + total, Xb + 2 * total};
+    float* G = G_f32 ? G_f32 + j0 * bb : nullptr;
+    uint16_t* E = E_bf16 ? (uint16_t*)E_bf16 + 2 * j0 * bb : nullptr;
+    skew_materialize_launch(theta + j0 * (bb - b) / 2, b, nb, C, Qb, nullptr, st);
+    const int pairs = k / 2;         // Horner steps in X
     mm::Args g = batched_args(b);
     g.nsrc = 1;
-    set_src(g.s[0], cur, Qb, b);
-    uint16_t* nxt = H[step & 1];
-    EpiHorner epi{Qf, 2.f, b, last ? nullptr : nxt, last ? G_f32 : nullptr, last ? (uint16_t*)E_bf16 : nullptr};
-    launch_product(b, g, epi, nb, st);
-    cur = nxt;
+    set_src(g.s[0], Qb, Qb, b);
+    // the top pair of powers is Q alone for even k, 2Q + X for odd k (then the chain starts in this launch's epilogue)
+    const bool odd = k & 1;
+    launch_product(g, EpiFwd<true>{C, pairs ? Xb : nullptr, b, pairs && odd ? H[0] : nullptr, pairs ? nullptr : G, pairs ? nullptr : E}, nb, st);
+    const uint16_t* cur = odd ? H[0] : Qb;
+    for (int i = 1; i <= pairs; ++i) {
+      const bool last = i == pairs;
+      set_src(g.s[0], Xb, cur, b);
+      uint16_t* nxt = H[i & 1];
+      launch_product(g, EpiFwd<false>{C, nullptr, b, last ? nullptr : nxt, last ? G : nullptr, last ? E : nullptr}, nb, st);
+      cur = nxt;
+    }
   }
 }
 
-void mfma_cnp_bwd(const float* theta, const float* dG, int d, int b, int k, float* dtheta, int accumulate, float* ws,
-                  hipStream_t st) {
-  const int nb = d / b;
-  const i64 total = (i64)nb * b * b;
-  if (lds_cnp_supported(d, b)) {   // block resident in LDS
-    const SeriesSide side{theta, dG, 0, 1, d, dtheta};
-    lds_cnp_bwd(&side, 1, k, accumulate, ws, st);
+void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumulate, float* ws, hipStream_t st) {
+  if (lds_cnp_supported(sides[0].d, b)) {   // block resident in LDS
+    lds_cnp_bwd(sides, nsides, k, accumulate, ws, st);
     return;
   }
-  float* Qf = ws;
-  uint16_t* Tb = (uint16_t*)(Qf + total);
-  skew_materialize_launch(theta, b, nb, Qf, nullptr, Tb, st);
-  const float* dQ = mfma_cnp_bwd_chain(Qf, Tb, dG, nb, b, k, Qf + total + total / 2, st);
-  skew_project_launch(dQ, b, d, dtheta, accumulate, st);
-}
-
-// Tiled two-sided Horner backward for nb blocks (of any sides) given Q in fp32 and T = -Q in
-// bf16; ws: 3.5 floats per block element.  Returns dL/dQ (inside ws).
-const float* mfma_cnp_bwd_chain(const float* Qf, const uint16_t* Tb, const float* dG, int nb, int b, int k, float* ws,
-                                hipStream_t st) {
-  const i64 total = (i64)nb * b * b;
-  float* Bfinal = ws;
-  uint16_t* Db = (uint16_t*)(Bfinal + total);
-  uint16_t* A[2] = {Db + total, Db + 2 * total};
-  uint16_t* Bb[2] = {Db + 3 * total, Db + 4 * total};
-  hipLaunchKernelGGL(to_bf16_kernel, dim3(ceil_div(total / 4, 256)), dim3(256), 0, st, (const float4*)dG, (uint2*)Db,
-                     total / 4);
-  const uint16_t* acur = Tb;  // A'_1 = T
-  const uint16_t* bcur = Db;  // Bm_1 = D
-  int ia = 0, ib = 0;
-  for (int p = k - 1; p >= 0; --p) {
-    const bool last = p == 0;
+  // blocks of the sides one after the other; their dG must be contiguous in that order
+  const int nb0 = sides[0].d / b, nb1 = nsides > 1 ? sides[1].d / b : 0, all = nb0 + nb1;
+  const i64 bb = (i64)b * b, L = (bb - b) / 2;
+  uint16_t* T_all = (uint16_t*)ws;                       // -Q of all blocks, the rest for a group at a time
+  ws += all * bb / 2;
+  skew_materialize_launch(sides[0].theta, b, nb0, nullptr, nullptr, T_all, st);
+  if (nb1) skew_materialize_launch(sides[1].theta, b, nb1, nullptr, nullptr, T_all + nb0 * bb, st);
+  const int group = group_size(all);
+  for (int j0 = 0; j0 < all; j0 += group) {
+    const int nb = all - j0 < group ? all - j0 : group;
+    const i64 total = nb * bb;
+    const float* D = sides[0].dG + j0 * bb;
+    const uint16_t* Tb = T_all + j0 * bb;
+    float* Pf[2] = {ws, ws + total};
+    uint16_t* Db = (uint16_t*)(ws + 2 * total);
+    uint16_t* P[2] = {Db + total, Db + 2 * total};
+    uint16_t* Z[2] = {Db + 3 * total, Db + 4 * total};
+    hipLaunchKernelGGL(to_bf16_kernel, dim3(ceil_div(total / 4, 256)), dim3(256), 0, st, (const float4*)D, (uint2*)Db, total / 4);
+    const uint16_t* p = Db;          // P_{m-1}
+    const uint16_t* z = Db;          // Z_{m-2} in launch m
+    for (int m = 1; m <= k; ++m) {   // P_m and, from m = 2, Z_{m-1}
+      mm::Args g = batched_args(b);
+      g.nsrc = 1;
+      set_src(g.s[0], p, Tb, b);
+      EpiAdd epi{};
+      epi.b = b;
+      epi.nb = nb;
+      epi.s[0] = {D, nullptr, m < k ? P[m & 1] : nullptr, Pf[m & 1]};
+      if (m > 1) {
+        g.alt_from = nb;
+        g.alt_nsrc = 1;
+        set_src(g.alt[0], Tb, z, b);
+        epi.s[1] = {Pf[(m - 1) & 1], nullptr, Z[m & 1], m == k ? Pf[(m - 1) & 1] : nullptr};   // Z_{k-1} also in fp32, in P_{k-1}'s place
+        z = Z[m & 1];
+      }
+      launch_product(g, epi, m > 1 ? 2 * nb : nb, st);
+      p = P[m & 1];
+    }
     mm::Args g = batched_args(b);
-    g.nsrc = 2;
-    set_src(g.s[0], acur, Db, b);  // A' D
-    set_src(g.s[1], bcur, Tb, b);  // Bm T
-    if (!last) {                   // second problem of the launch: A' T
-      g.alt_from = nb;
-      g.alt_nsrc = 1;
-      set_src(g.alt[0], acur, Tb, b);
-    }
-    EpiBwdStep epi{dG, Qf, b, nb, last ? nullptr : Bb[ib], last ? Bfinal : nullptr, last ? nullptr : A[ia]};
-    launch_product(b, g, epi, last ? nb : 2 * nb, st);
-    if (!last) {
-      acur = A[ia];
-      ia ^= 1;
-      bcur = Bb[ib];
-      ib ^= 1;
-    }
+    g.nsrc = 1;
+    set_src(g.s[0], Tb, z, b);
+    EpiAdd epi{};
+    epi.b = b;
+    epi.nb = nb;
+    float* dQ = Pf[(k - 1) & 1];
+    epi.s[0] = {Pf[k & 1], k > 1 ? dQ : D, nullptr, dQ};                                       // Z_k + Z_{k-1}
+    launch_product(g, epi, nb, st);
+    const int n0 = nb0 - j0 < 0 ? 0 : nb0 - j0 < nb ? nb0 - j0 : nb, j1 = j0 + n0 - nb0;       // of the group: blocks of the first side, first block of the second
+    skew_project_sides_launch(dQ, b, n0, sides[0].dtheta + j0 * L, nb - n0, nb > n0 ? sides[1].dtheta + j1 * L : nullptr, accumulate, st);
   }
-  return Bfinal;
 }
 
 }  // namespace poetx

@@ -93,8 +93,9 @@ struct Args {
   int rows_per_batch;
   // Set by launch(): > 0 means a one-dimensional grid in which the tiles of one (batch, split) get
   // workgroup ids 8 apart, i.e. run on one XCD at the same time and share their operand panels in its
-  // L2 (consecutive ids go to the 8 XCDs in turn); the value is the number of batches.
-  int xcd_batches;
+  // L2 (consecutive ids go to the 8 XCDs in turn); the value is the number of batches.  xcd_works: (batch, split) pairs --
+  // the grid is rounded up to a multiple of 8 of them, the extra workgroups leave at once.
+  int xcd_batches, xcd_works;
 };
 
 // NS = ring depth (stages); up to NS - 1 tiles are in flight while one is multiplied.
@@ -178,6 +179,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi e
   int batch = blockIdx.y, split = blockIdx.z;
   if (g.xcd_batches > 0) {
     const int slot = blockIdx.x >> 3, work = (slot / total) * 8 + (blockIdx.x & 7);
+    if (work >= g.xcd_works) return;
     wg = slot % total;
     batch = work % g.xcd_batches;
     split = work / g.xcd_batches;
@@ -422,10 +424,11 @@ void launch(const Args& g, Epi epi, int batches, int splits, hipStream_t st) {
   (void)configured;
   // a few tiles per (batch, split) that read the same operand rows: keep them on one XCD
   const int tiles = g.tiles_m * g.tiles_n;
-  if (tiles > 1 && tiles <= 16 && ((i64)batches * splits) % 8 == 0) {
+  if (tiles > 1 && tiles <= 16) {
     Args h = g;
     h.xcd_batches = batches;
-    hipLaunchKernelGGL(kern, dim3(tiles * batches * splits), dim3(64 * WGM * WGN), C::LDS_BYTES, st, h, epi);
+    h.xcd_works = batches * splits;
+    hipLaunchKernelGGL(kern, dim3(tiles * ((h.xcd_works + 7) / 8 * 8)), dim3(64 * WGM * WGN), C::LDS_BYTES, st, h, epi);
     return;
   }
   hipLaunchKernelGGL(kern, dim3(g.tiles_m * g.tiles_n, batches, splits), dim3(64 * WGM * WGN), C::LDS_BYTES, st, g, epi);

@@ -66,14 +66,14 @@ int check_desc(const poetx_linear_desc* d) {
 }
 
 // dG plus chain scratch per block element: five floats cover the tiled kernel families, the
-// on-chip chain keeps bf16(Q), k transposed terms and the result (k + 2 floats)
+// on-chip chain keeps bf16(Q), k matrices between its passes and the result (k + 2 floats)
 size_t cnp_bwd_ws_floats(int d, int b, int k) {
   const size_t per_elem = 1 + (size_t)(k + 2 > 5 ? k + 2 : 5);
   return per_elem * ceil_div(d, b) * b * b;
 }
 // The same when both sides of a layer go through the series backward together.
 size_t cnp_bwd_ws_floats_both(int m, int n, int b, int k) {
-  const size_t per_elem = (size_t)(k + 3 > 6 ? k + 3 : 6);   // tiled kernels: dG, Q, -Q (half), 3.5 of chain
+  const size_t per_elem = (size_t)(k + 3 > 6 ? k + 3 : 6);   // tiled kernels: dG and 5 of chain; on chip: dG, bf16(Q) (half), k + 1 of chain
   return per_elem * (ceil_div(m, b) + ceil_div(n, b)) * b * b;
 }
 
@@ -251,12 +251,12 @@ int poetx_cnp_bwd(const float* theta, const float* dG, int32_t d, int32_t b, int
   if (!ws || ws_bytes < poetx_cnp_bwd_workspace_bytes(d, b, k)) return POETX_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   StageTimer tm(POETX_STAGE_CNP_BWD, st);
+  const SeriesSide side{theta, dG, 0, 1, d, dtheta};
   if (precision == POETX_CNP_BF16 && !g_force_fma.load() && mfma_cnp_supported(d, b))
-    mfma_cnp_bwd(theta, dG, d, b, k, dtheta, accumulate != 0, (float*)ws, st);
-  else if (series_small(b)) {
-    const SeriesSide side{theta, dG, 0, 1, d, dtheta};
+    mfma_cnp_bwd(&side, 1, b, k, accumulate != 0, (float*)ws, st);
+  else if (series_small(b))
     series_small_bwd(&side, 1, b, k, accumulate != 0, st);
-  } else
+  else
     fma_cnp_bwd(theta, dG, d, b, k, dtheta, accumulate != 0, (float*)ws, st);
   return launch_status();
 }
@@ -559,15 +559,15 @@ int poetx_linear_bwd_input(const poetx_linear_desc* desc, const void* dZ, const 
   return launch_status();
 }
 
-// Series backward of both sides as one batch on the on-chip chains (b = 256): dG holds the block
-// gradients of the P side, then of the R side; the chain's scratch follows.
-static void cnp_bwd_both_on_chip(const float* theta_R, const float* theta_P, float* dG, int m, int n, int b, int k,
-                                 float* dtheta_R, float* dtheta_P, int accumulate, hipStream_t st) {
+// Series backward of both sides as one batch (a side alone leaves most CUs empty): dG holds the block gradients of the
+// P side, then of the R side; the chain's scratch follows.
+static void cnp_bwd_both(const float* theta_R, const float* theta_P, float* dG, int m, int n, int b, int k,
+                         float* dtheta_R, float* dtheta_P, int accumulate, hipStream_t st) {
   const int nbP = n / b, nbt = nbP + m / b;
   const size_t bb = (size_t)b * b;
   const SeriesSide sides[2] = {{theta_P, dG, 0, 1, n, dtheta_P}, {theta_R, dG + nbP * bb, 0, 1, m, dtheta_R}};
   StageTimer tm(POETX_STAGE_CNP_BWD, st);
-  lds_cnp_bwd(sides, 2, k, accumulate != 0, dG + nbt * bb, st);   // at most (k + 1) * nbt * b * b floats
+  mfma_cnp_bwd(sides, 2, b, k, accumulate != 0, dG + nbt * bb, st);
 }
 
 static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act& dZ, const Act& saved_B,
@@ -586,7 +586,7 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
       mfma_cnp_supported(n, b)) {
     // Both sides' blocks go through the series backward as one batch (P side first): the chains
     // are latency bound and a side alone leaves most CUs empty.
-    const int nbP = n / b, nbR = m / b, nbt = nbP + nbR;
+    const int nbP = n / b;
     const size_t bb = (size_t)b * b;
     float* dG = (float*)ws;                                   // [nbt][b][b]
     if (defer) {
@@ -595,29 +595,12 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
       blockgrad_dispatch(dt, X, dA, m, perm_R, b, dtheta_R, bg_ws, st);
       return;
     }
-    if (!lds_cnp_supported(m, b)) {                            // tiled kernels (b = 512)
-      float* Qf = dG + nbt * bb;
-      uint16_t* Tb = (uint16_t*)(Qf + nbt * bb);
-      float* chain = Qf + nbt * bb + nbt * bb / 2;            // 3.5 floats per element follow: 6 in all
-      {
-        StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-        blockgrad_dispatch(dt, saved_B, dZ, n, perm_P, b, dG, bg_ws, st);
-        blockgrad_dispatch(dt, X, dA, m, perm_R, b, dG + nbP * bb, bg_ws, st);
-      }
-      StageTimer tm(POETX_STAGE_CNP_BWD, st);
-      skew_materialize_launch(theta_P, b, nbP, Qf, nullptr, Tb, st);
-      skew_materialize_launch(theta_R, b, nbR, Qf + nbP * bb, nullptr, Tb + nbP * bb, st);
-      const float* dQ = mfma_cnp_bwd_chain(Qf, Tb, dG, nbt, b, k, chain, st);
-      skew_project_launch(dQ, b, n, dtheta_P, accumulate != 0, st);
-      skew_project_launch(dQ + nbP * bb, b, m, dtheta_R, accumulate != 0, st);
-      return;
-    }
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
       blockgrad_dispatch(dt, saved_B, dZ, n, perm_P, b, dG, bg_ws, st);            // dG_P = B' dZ'^T
       blockgrad_dispatch(dt, X, dA, m, perm_R, b, dG + nbP * bb, bg_ws, st);       // dG_R = X' dA'^T
     }
-    cnp_bwd_both_on_chip(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);
+    cnp_bwd_both(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);
     return;
   }
   if (!defer && series_small(b)) {
@@ -659,7 +642,8 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
     }
     if (!defer) {
       StageTimer tm(POETX_STAGE_CNP_BWD, st);
-      if (fast_cnp) mfma_cnp_bwd(theta, dG, d, b, k, dtheta, accumulate != 0, chain, st);
+      const SeriesSide one{theta, dG, 0, 1, d, dtheta};
+      if (fast_cnp) mfma_cnp_bwd(&one, 1, b, k, accumulate != 0, chain, st);
       else fma_cnp_bwd(theta, dG, d, b, k, dtheta, accumulate != 0, chain, st);
     }
   }
@@ -753,7 +737,7 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
   side(one_R, dA, x, dx, m, perm_R, blocks_R, dG_R);
   lay.finish();
   if (defer) return launch_status();
-  cnp_bwd_both_on_chip(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);
+  cnp_bwd_both(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);
   return launch_status();
 }
 

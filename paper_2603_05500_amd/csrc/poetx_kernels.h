@@ -115,8 +115,8 @@ void mfma_apply_grad(const void* V, const void* U, void* out, int d, i64 N, i64 
 bool mfma_cnp_supported(int d, int b);
 void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void* E_bf16, float* ws,
                     hipStream_t st);
-void mfma_cnp_bwd(const float* theta, const float* dG, int d, int b, int k, float* dtheta, int accumulate,
-                  float* ws, hipStream_t st);
+// One or two sides whose dG (one matrix per block, nsplit = 1) follow each other in memory; ws: max(k + 2, 5) floats per element.
+void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumulate, float* ws, hipStream_t st);
 // b = 256: whole chain of a block in one launch, block resident in LDS (mfma_cnp_lds.hip).
 bool lds_cnp_supported(int d, int b);
 void lds_cnp_build(const float* theta, int nb, int k, float* G_f32, void* E_bf16, float* ws, hipStream_t st);   // ws: 1.5 floats per block element
@@ -134,9 +134,5 @@ void skew_materialize_launch(const float* theta, int b, i64 nb, float* Qf, uint1
 bool skew_tiled_supported(int b, i64 d);
 void skew_materialize_tiled_launch(const float* theta, int b, i64 nb, float* Qf, uint16_t* Qb, uint16_t* Tb, hipStream_t st);
 void skew_project_tiled_launch(const float* M, int b, i64 nb, float* dtheta, int accumulate, hipStream_t st);
-// Series backward on the tiled kernels (b = 512) for nb blocks: Qf fp32, Tb = bf16(-Q); ws holds
-// 3.5 floats per block element; returns dL/dQ (inside ws).
-const float* mfma_cnp_bwd_chain(const float* Qf, const uint16_t* Tb, const float* dG, int nb, int b, int k, float* ws,
-                                hipStream_t st);
 
 }  // namespace poetx

@@ -164,3 +164,35 @@ def test_dense_tiles(lib, n, m, N):
     assert rel_err(to_np(B), W @ X) <= 2.0 ** -8 and torch.equal(Z, B)
     assert rel_err(to_np(dA), W.T @ dZ) <= 2.0 ** -8 and torch.equal(dX, dA)
     assert torch.all(guard[:256] == -7.0) and torch.all(guard[256 + n * N:] == -7.0)
+
+
+@pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 130, (3,)), (256, 130, (2,)), (256, 3, (1, 2, 7))])
+def test_matrix_core_series(lib, b, nb, ks):
+    """The bf16 series of large blocks, build and backward through poetx_cnp_build / poetx_cnp_bwd: every shape of the
+    recurrences (the tiled one pairs powers: odd and even orders start differently), batches that are worked off in more
+    than one group (256) or on large tiles (512).  The bound is the error of rounding each product's operands
+    to bf16 (2^-9 of the first product, relative to terms of its size) with a factor of four."""
+    L = b * (b - 1) // 2
+    for k in ks:
+        rng = np.random.Generator(np.random.PCG64(9500 + b + nb + k))
+        theta = round_f32(rng.standard_normal((nb, L)) * 0.008)
+        check = sorted({0, nb // 2, nb - 1})
+        th = to_dev(theta, torch.float32)
+        G = torch.empty((nb, b, b), dtype=torch.float32, device="cuda")
+        E = torch.empty((nb, 2, b, b), dtype=torch.bfloat16, device="cuda")
+        d = nb * b
+        ws = torch.full((max(lib.poetx_cnp_workspace_bytes(d, b), lib.poetx_cnp_bwd_workspace_bytes(d, b, k)) // 4,), float("nan"),
+                        dtype=torch.float32, device="cuda").view(torch.uint8)
+        lib.poetx_cnp_build(th, d, b, k, lib.CNP_BF16, G, E, ws)
+        dG = torch.randn((nb, b, b), generator=torch.Generator(device="cuda").manual_seed(k), device="cuda")
+        dth = torch.full_like(th, float("nan"))
+        lib.poetx_cnp_bwd(th, dG, d, b, k, lib.CNP_BF16, dth, False, ws)
+        torch.cuda.synchronize()
+        Q = orc.skew_from_packed(theta[check], b, len(check) * b)
+        ref = orc.cnp(Q, k) - np.eye(b)
+        norm = np.linalg.norm(Q[0], 2)
+        assert np.linalg.norm(to_np(G)[check] - np.eye(b) - ref) <= 4 * 2.0 ** -9 * norm * np.linalg.norm(ref)
+        assert np.linalg.norm(to_np(E[check])[:, 0] - ref) <= (2.0 ** -8 + 4 * 2.0 ** -9 * norm) * np.linalg.norm(ref)
+        assert torch.equal(E[:, 1], E[:, 0].transpose(1, 2))
+        want = orc.packed_from_skew_grad(orc.cnp_bwd(Q, to_np(dG)[check], k), b, len(check) * b)
+        assert np.linalg.norm(to_np(dth)[check] - want) <= 4 * 2.0 ** -9 * norm * np.linalg.norm(want)

@@ -25,7 +25,7 @@ Plan pick_plan(i64 batches, i64 M, i64 N, i64 K, size_t es, bool may_split) {
   else if (M > 32 && N > 32 && tile_count(batches, M, N, 64) >= kCUs * 3 / 4) p.tile = TILE_64;
   if (!may_split) return p;
   const int side = p.tile == TILE_128 ? 128 : p.tile == TILE_64 ? 64 : 32;
-  const int depth = p.tile == TILE_32 ? 128 : (p.tile == TILE_128 && es == 4) ? 32 : 64;
+  const int depth = stage_depth(p.tile, es);
   const i64 count = tile_count(batches, M, N, side), stages = (K + depth - 1) / depth;
   i64 s = min64(2 * kCUs / count, stages / 2);
   if (p.tile == TILE_32) {
@@ -41,25 +41,23 @@ Plan pick_plan(i64 batches, i64 M, i64 N, i64 K, size_t es, bool may_split) {
 
 Plan dense_plan(int dtype, i64 M, i64 N, i64 K) { return pick_plan(1, M, N, K, dtype == POETX_F32 ? 4 : 2, true); }
 // Block gradients: the contraction is the token range, so a large tile with a split costs only its fp32 parts, while
-// every halving of the tile side doubles the reads of both activations.  A split keeps four stages.
+// every halving of the tile side doubles the reads of both activations.  A split keeps 256 tokens, on the smallest tile two
+// stages (one stage each: 1376 x 512, b = 64 step 93 -> 101 us).
 Plan grad_plan(int dtype, int d, i64 N, int b) {
   const int nb = ceil_div(d, b);
+  const size_t es = dtype == POETX_F32 ? 4 : 2;
   Plan p{TILE_32, 1};
+  i64 most = N / (2 * stage_depth(TILE_32, es));
   int side = 32;
-  i64 depth = 128, least = 2;
-  for (const int t : {128, 64}) {
-    const i64 dep = t == 128 && dtype == POETX_F32 ? 32 : 64, stages = (N + dep - 1) / dep;
-    if (b >= t && tile_count(nb, b, b, t) * (stages / 4 > 1 ? stages / 4 : 1) >= kCUs * 3 / 4) {
+  for (const int t : {128, 64})
+    if (b >= t && tile_count(nb, b, b, t) * (N / 256 > 1 ? N / 256 : 1) >= kCUs * 3 / 4) {
       p.tile = t == 128 ? TILE_128 : TILE_64;
       side = t;
-      depth = dep;
-      least = 4;
+      most = N / 256;
       break;
     }
-  }
-  const i64 count = tile_count(nb, b, b, side), stages = (N + depth - 1) / depth;
-  i64 s = 2 * kCUs / count;
-  if (s > stages / least) s = stages / least;
+  const i64 depth = stage_depth(p.tile, es), stages = (N + depth - 1) / depth;
+  const i64 s = min64(2 * kCUs / tile_count(nb, b, b, side), most);
   if (s > 1) {
     const i64 per = (stages + s - 1) / s;
     p.splits = (int)((stages + per - 1) / per);
@@ -188,14 +186,24 @@ void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out
 
 // block gradients as plan.splits parts at `parts`
 template <class T>
-void grad_t(const Plan& p, const T* U, i64 ldu, const T* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* parts, hipStream_t st) {
-  const int nb = ceil_div(d, b);
+Args grad_args(const GradProblem& q, int b) {
   Args g{};
   g.rpb = b;
-  g.d = d;
-  g.A = Op{U, ldu, 0, perm, b, (int)N, 1, 0};
-  g.B = Op{V, ldv, 0, perm, b, (int)N, 1, 0};
-  launch<T, true, true>(g, EpiPartial{parts, b, b, nb}, nb, b, b, N, p, st);
+  g.d = q.d;
+  g.A = Op{q.U, q.ldu, 0, q.perm, b, (int)q.N, 1, 0};
+  g.B = Op{q.V, q.ldv, 0, q.perm, b, (int)q.N, 1, 0};
+  return g;
+}
+template <class T>
+void grad_t(const Plan& p, const GradProblem& q, int b, hipStream_t st) {
+  const int nb = ceil_div(q.d, b);
+  launch<T, true, true>(grad_args<T>(q, b), EpiPartial{q.parts, b, b, nb}, nb, b, b, q.N, p, st);
+}
+template <class T>
+void grad_pair_t(const Plan& p0, const Plan& p1, const GradProblem& q0, const GradProblem& q1, int b, hipStream_t st) {
+  const int n0 = ceil_div(q0.d, b), n1 = ceil_div(q1.d, b);
+  launch_pair<T, true, true>(grad_args<T>(q0, b), grad_args<T>(q1, b), EpiPartial{q0.parts, b, b, n0}, EpiPartial{q1.parts, b, b, n1},
+                             Problem{n0, b, b, q0.N}, Problem{n1, b, b, q1.N}, p0, p1, st);
 }
 
 }  // namespace
@@ -223,12 +231,25 @@ size_t edge_blockgrad_parts_bytes(int dtype, int d, i64 N, int b) {
   return (size_t)grad_plan(dtype, d, N, b).splits * ceil_div(d, b) * b * b * sizeof(float);
 }
 
-int edge_blockgrad_parts(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* parts,
-                         hipStream_t st) {
-  const Plan p = grad_plan(dtype, d, N, b);
-  if (dtype == POETX_F32) grad_t<float>(p, (const float*)U, ldu, (const float*)V, ldv, d, N, perm, b, parts, st);
-  else grad_t<uint16_t>(p, (const uint16_t*)U, ldu, (const uint16_t*)V, ldv, d, N, perm, b, parts, st);
+int edge_blockgrad_parts(int dtype, const GradProblem& q, int b, hipStream_t st) {
+  const Plan p = grad_plan(dtype, q.d, q.N, b);
+  if (dtype == POETX_F32) grad_t<float>(p, q, b, st);
+  else grad_t<uint16_t>(p, q, b, st);
   return p.splits;
+}
+
+void edge_blockgrad_parts_pair(int dtype, const GradProblem& q0, const GradProblem& q1, int b, int* n0, int* n1, hipStream_t st) {
+  const Plan p0 = grad_plan(dtype, q0.d, q0.N, b), p1 = grad_plan(dtype, q1.d, q1.N, b);
+  *n0 = p0.splits;
+  *n1 = p1.splits;
+  if (p0.tile != p1.tile) {
+    edge_blockgrad_parts(dtype, q0, b, st);
+    edge_blockgrad_parts(dtype, q1, b, st);
+  } else if (dtype == POETX_F32) {
+    grad_pair_t<float>(p0, p1, q0, q1, b, st);
+  } else {
+    grad_pair_t<uint16_t>(p0, p1, q0, q1, b, st);
+  }
 }
 
 size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b) {
@@ -238,7 +259,7 @@ size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b) {
 void edge_blockgrad(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
                     hipStream_t st) {
   const bool split = grad_plan(dtype, d, N, b).splits > 1;
-  const int n = edge_blockgrad_parts(dtype, U, ldu, V, ldv, d, N, perm, b, split ? (float*)ws : dG, st);
+  const int n = edge_blockgrad_parts(dtype, GradProblem{U, V, ldu, ldv, N, d, perm, split ? (float*)ws : dG}, b, st);
   if (split) reduce<float>((const float*)ws, (i64)ceil_div(d, b) * b, b, n, dG, b, st);
 }
 

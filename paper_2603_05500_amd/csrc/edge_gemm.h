@@ -121,8 +121,9 @@ struct Shape {
 
 // Epi: __device__ void operator()(int batch, int split, int row, int col, const float (&v)[8]) -- eight
 // consecutive columns of one output row, indices inside the batch; it does its own masking.
+// bx of total: this workgroup among those of the problem.
 template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
-__global__ __launch_bounds__(256) void edge_kernel(Args g, Epi epi) {
+__device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int bx, int total, int split) {
   using S = Shape<T, BM, BN, BK, WGM, WGN>;
   constexpr int V = 16 / sizeof(T), WGK = S::WGK, TM = S::TM, TN = S::TN;
   constexpr bool BF = sizeof(T) == 2;
@@ -135,9 +136,9 @@ __global__ __launch_bounds__(256) void edge_kernel(Args g, Epi epi) {
   const int tiles = g.tiles_m * g.tiles_n;
   // Consecutive workgroups go to the 8 XCDs in turn: give each XCD a contiguous run of tiles (and the tiles of a batch
   // that read the same columns come first), so that shared operand rows meet in one L2.
-  const int total = gridDim.x, xcd = blockIdx.x & 7, per = total >> 3, extra = total & 7;
-  const int id = xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
-  const int batch = id / tiles, tile = id % tiles, split = blockIdx.y;
+  const int xcd = bx & 7, per = total >> 3, extra = total & 7;
+  const int id = xcd * per + (xcd < extra ? xcd : extra) + (bx >> 3);
+  const int batch = id / tiles, tile = id % tiles;
   const int i0 = (tile % g.tiles_m) * BM, j0 = (tile / g.tiles_m) * BN;
   const int side = g.rpb > 0 ? (g.d - batch * g.rpb < g.rpb ? g.d - batch * g.rpb : g.rpb) : 0x7fffffff;
 
@@ -379,6 +380,22 @@ __global__ __launch_bounds__(256) void edge_kernel(Args g, Epi epi) {
   }
 }
 
+template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
+__global__ __launch_bounds__(256) void edge_kernel(Args g, Epi epi) {
+  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K>(g, epi, blockIdx.x, gridDim.x, blockIdx.y);
+}
+
+// Two problems of one shape in one launch: the first n0 workgroups of a row of the grid take g0, the rest g1.
+template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
+__global__ __launch_bounds__(256) void edge_pair_kernel(Args g0, Args g1, Epi e0, Epi e1, int n0) {
+  const bool second = (int)blockIdx.x >= n0;
+  const Args g = second ? g1 : g0;
+  const Epi epi = second ? e1 : e0;
+  const int split = blockIdx.y;
+  if (split * g.stages_per_split >= g.stages) return;
+  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K>(g, epi, second ? (int)blockIdx.x - n0 : (int)blockIdx.x, second ? (int)gridDim.x - n0 : n0, split);
+}
+
 // ---- host side -------------------------------------------------------------------------------
 enum Tile { TILE_32 = 0, TILE_64 = 1, TILE_128 = 2 };
 
@@ -390,7 +407,32 @@ struct Plan {
 constexpr int kCUs = 256;
 
 inline i64 tile_count(i64 batches, i64 M, i64 N, int t) { return batches * ((M + t - 1) / t) * ((N + t - 1) / t); }
-inline int stage_depth(Tile t) { return t == TILE_32 ? 128 : 64; }
+// contraction depth of a stage; fp32 halves it, which keeps as many workgroups per CU as in bf16
+inline int stage_depth(Tile t, size_t es) { return (t == TILE_32 ? 128 : 64) * 2 / (int)es; }
+
+struct Problem {
+  i64 batches, M, N, K;
+};
+inline void tile_args(Args& g, const Problem& q, int BM, int BN, int BK, int splits) {
+  g.tiles_m = ceil_div(q.M, BM);
+  g.tiles_n = ceil_div(q.N, BN);
+  g.batches = (int)q.batches;
+  g.stages = ceil_div(q.K, BK);
+  g.stages_per_split = ceil_div(g.stages, splits);
+}
+
+template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
+void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, int s0, int s1, hipStream_t st) {
+  using S = Shape<T, BM, BN, BK, WGM, WGN>;
+  auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi>;
+  static const bool configured =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
+  (void)configured;
+  tile_args(g0, q0, BM, BN, BK, s0);
+  tile_args(g1, q1, BM, BN, BK, s1);
+  const int n0 = g0.batches * g0.tiles_m * g0.tiles_n, n1 = g1.batches * g1.tiles_m * g1.tiles_n;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(n0 + n1), (unsigned)(s0 > s1 ? s0 : s1)), dim3(256), S::LDS, st, g0, g1, e0, e1, n0);
+}
 
 template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
 void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits, hipStream_t st) {
@@ -400,19 +442,25 @@ void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits,
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
   (void)configured;
-  g.tiles_m = ceil_div(M, BM);
-  g.tiles_n = ceil_div(N, BN);
-  g.batches = (int)batches;
-  g.stages = ceil_div(K, BK);
-  g.stages_per_split = ceil_div(g.stages, splits);
+  tile_args(g, Problem{batches, M, N, K}, BM, BN, BK, splits);
   hipLaunchKernelGGL(kern, dim3((unsigned)(batches * g.tiles_m * g.tiles_n), (unsigned)splits), dim3(256), S::LDS, st, g, epi);
 }
 
 template <class T, bool A_K, bool B_K, class Epi>
 void launch(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, Plan p, hipStream_t st) {
-  if (p.tile == TILE_128) launch_shape<T, 128, 128, (sizeof(T) == 2 ? 64 : 32), 2, 2, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
-  else if (p.tile == TILE_64) launch_shape<T, 64, 64, 64, 2, 2, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
-  else launch_shape<T, 32, 32, 128, 1, 1, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  constexpr int D = 128 / (int)sizeof(T);   // stage_depth
+  if (p.tile == TILE_128) launch_shape<T, 128, 128, D, 2, 2, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else if (p.tile == TILE_64) launch_shape<T, 64, 64, D, 2, 2, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else launch_shape<T, 32, 32, 2 * D, 1, 1, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+}
+
+// two problems planned onto the same tile
+template <class T, bool A_K, bool B_K, class Epi>
+void launch_pair(const Args& g0, const Args& g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, Plan p0, Plan p1, hipStream_t st) {
+  constexpr int D = 128 / (int)sizeof(T);
+  if (p0.tile == TILE_128) launch_pair_shape<T, 128, 128, D, 2, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  else if (p0.tile == TILE_64) launch_pair_shape<T, 64, 64, D, 2, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  else launch_pair_shape<T, 32, 32, 2 * D, 1, 1, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
 }
 
 }  // namespace edge

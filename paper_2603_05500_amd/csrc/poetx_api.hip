@@ -606,20 +606,13 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
   if (!defer && series_small(b)) {
     // Both sides' block gradients, still split over token ranges, then one launch that adds the parts, runs the
     // series backward and projects.  The P side's parts sit where the other paths keep dG and the chain.
-    SeriesSide sides[2];
-    char* at = (char*)ws;
-    for (int i = 0; i < 2; ++i) {
-      const int d = i == 0 ? n : m;
-      sides[i].theta = i == 0 ? theta_P : theta_R;
-      sides[i].dtheta = i == 0 ? dtheta_P : dtheta_R;
-      sides[i].d = d;
-      sides[i].dG = (const float*)at;
-      sides[i].split_stride = (i64)ceil_div(d, b) * b * b;
+    SeriesSide sides[2] = {{theta_P, (const float*)ws, (i64)ceil_div(n, b) * b * b, 1, n, dtheta_P},
+                           {theta_R, (const float*)((char*)ws + blockgrad_parts_bytes(desc, n)), (i64)ceil_div(m, b) * b * b, 1, m, dtheta_R}};
+    {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      const Act& U = i == 0 ? saved_B : X;
-      const Act& V = i == 0 ? dZ : dA;
-      sides[i].nsplit = edge_blockgrad_parts(dt, U.p, U.ld, V.p, V.ld, d, min64(U.cols, V.cols), i == 0 ? perm_P : perm_R, b, (float*)at, st);
-      at += blockgrad_parts_bytes(desc, d);
+      const GradProblem gp{saved_B.p, dZ.p, saved_B.ld, dZ.ld, min64(saved_B.cols, dZ.cols), n, perm_P, (float*)sides[0].dG};
+      const GradProblem gr{X.p, dA.p, X.ld, dA.ld, min64(X.cols, dA.cols), m, perm_R, (float*)sides[1].dG};
+      edge_blockgrad_parts_pair(dt, gp, gr, b, &sides[0].nsplit, &sides[1].nsplit, st);
     }
     StageTimer tm(POETX_STAGE_CNP_BWD, st);
     series_small_bwd(sides, 2, b, k, accumulate != 0, st);

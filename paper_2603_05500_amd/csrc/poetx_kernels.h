@@ -47,9 +47,18 @@ size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b);
 void edge_blockgrad(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
                     hipStream_t st);
 // The same, left as its token-range parts (each ceil(d/b) * b * b floats, one after the other at `parts`); returns how many.
+struct GradProblem {
+  const void* U;
+  const void* V;
+  i64 ldu, ldv, N;
+  int d;
+  const int32_t* perm;
+  float* parts;
+};
 size_t edge_blockgrad_parts_bytes(int dtype, int d, i64 N, int b);
-int edge_blockgrad_parts(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* parts,
-                         hipStream_t st);
+int edge_blockgrad_parts(int dtype, const GradProblem& q, int b, hipStream_t st);
+// both sides of a layer, in one launch where their plans allow
+void edge_blockgrad_parts_pair(int dtype, const GradProblem& q0, const GradProblem& q1, int b, int* n0, int* n1, hipStream_t st);
 
 // ---- fp32 series of blocks up to 128, one launch (series_small.hip) ----------------------------------------
 bool series_small_supported(int b);

@@ -111,6 +111,33 @@ struct EpiScatter {
   }
 };
 
+// The same where V or out is token major (feature r of token c at c * ld + r): a few tokens, element by element.
+template <class T, bool V_TM, bool OUT_TM>
+struct EpiScatterTokens {
+  T* out;
+  const T* V;
+  i64 ldo, ldv;
+  const int32_t* perm;
+  int b, d, valid, cols;
+  __device__ void operator()(int batch, int, int row, int col, const float (&v)[8]) const {
+    const int r = batch * b + row;
+    if (row >= b || r >= d) return;
+    const i64 at = perm[r];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int c = col + e;
+      if (c >= cols) break;
+      float x = v[e];
+      if constexpr (sizeof(T) == 2) {
+        if (c < valid) x += bf16_bits_to_float(V[V_TM ? c * ldv + at : at * ldv + c]);
+        out[OUT_TM ? c * ldo + at : at * ldo + c] = (T)mm::pack2_bf16(x, 0.f);
+      } else {
+        out[OUT_TM ? c * ldo + at : at * ldo + c] = x;
+      }
+    }
+  }
+};
+
 // out (M x N, row stride ld) = sum of the partials, in order
 template <class T>
 __global__ __launch_bounds__(256) void edge_reduce_kernel(const float* __restrict__ part, i64 total, int splits, T* __restrict__ out, int N, i64 ld) {
@@ -184,6 +211,29 @@ void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out
   }
 }
 
+// A few tokens, V or out token major, on the smallest tile (see edge_apply_smallest_tile): what bounds these are the scattered
+// two- and four-byte accesses, each on a cache line of its own, of which a few tokens have few.
+template <class T, bool V_TM, bool OUT_TM>
+void apply_tokens_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out, const int32_t* perm, const T* blocks, int b, int trans,
+                    hipStream_t st) {
+  constexpr int D = stage_depth(TILE_32, sizeof(T));
+  const int nb = ceil_div(d, b);
+  Args g{};
+  g.rpb = b;
+  g.d = d;
+  // a token-major V has its features (rows) one element and its tokens (columns) ldv elements apart
+  g.B = Op{V, V_TM ? 1 : ldv, 0, perm, b, (int)cols, 1, 0, V_TM ? ldv : 1};
+  const EpiScatterTokens<T, V_TM, OUT_TM> epi{out, V, ldo, ldv, perm, b, d, (int)cols, (int)cols_out};
+  if constexpr (sizeof(T) == 2) {
+    g.A = Op{blocks + (trans ? (i64)b * b : 0), b, 2ll * b * b, nullptr, b, b, 1, 1};
+    launch_shape<T, 32, 32, D, 1, 1, true, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
+  } else {
+    g.A = Op{blocks, b, (i64)b * b, nullptr, b, b, 1, 1};
+    if (trans) launch_shape<T, 32, 32, D, 1, 1, false, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
+    else launch_shape<T, 32, 32, D, 1, 1, true, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
+  }
+}
+
 // block gradients as plan.splits parts at `parts`
 template <class T>
 Args grad_args(const GradProblem& q, int b) {
@@ -225,6 +275,19 @@ void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int 
     apply_t<float>((const float*)V, ldv, (float*)out, ldo, d, cols, cols_out, perm, (const float*)blocks, b, transpose_G, st);
   else
     apply_t<uint16_t>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, perm, (const uint16_t*)blocks, b, transpose_G, st);
+}
+
+bool edge_apply_smallest_tile(int d, i64 cols_out, int b) { return pick_plan(ceil_div(d, b), b, cols_out, b, 4, false).tile == TILE_32; }
+
+void edge_apply_tokens(int dtype, const void* V, i64 ldv, bool v_tm, void* out, i64 ldo, bool out_tm, int d, i64 cols, i64 cols_out,
+                       const int32_t* perm, const void* blocks, int b, int transpose_G, hipStream_t st) {
+  if (dtype == POETX_F32) {
+    auto f = v_tm ? apply_tokens_t<float, true, false> : apply_tokens_t<float, false, true>;
+    f((const float*)V, ldv, (float*)out, ldo, d, cols, cols_out, perm, (const float*)blocks, b, transpose_G, st);
+  } else {
+    auto f = v_tm ? apply_tokens_t<uint16_t, true, false> : apply_tokens_t<uint16_t, false, true>;
+    f((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, perm, (const uint16_t*)blocks, b, transpose_G, st);
+  }
 }
 
 size_t edge_blockgrad_parts_bytes(int dtype, int d, i64 N, int b) {

@@ -35,6 +35,7 @@ struct Op {
   int rows, cols;        // valid extents
   int rows_side;         // != 0: rows (cols) also end at the side of the batch's block
   int cols_side;
+  i64 cs;                // strided operands (template flag): distance of neighbouring columns, rows then being ld apart as ever
 };
 
 struct Args {
@@ -68,6 +69,22 @@ __device__ inline u32x4 load_masked(const T* row, int c, int cols, bool row_ok) 
       if (2 * w < n) x = row[c + 2 * w];
       if (2 * w + 1 < n) x |= (uint32_t)row[c + 2 * w + 1] << 16;
       v[w] = x;
+    }
+  }
+  return v;
+}
+
+// the same with columns cs elements apart
+template <class T>
+__device__ inline u32x4 load_strided(const T* row, int c, i64 cs, int cols, bool row_ok) {
+  constexpr int V = 16 / sizeof(T);
+  u32x4 v = {0, 0, 0, 0};
+  if (!row_ok) return v;
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    if (c + e < cols) {
+      if constexpr (sizeof(T) == 4) v[e] = __builtin_bit_cast(uint32_t, row[(c + e) * cs]);
+      else v[e >> 1] |= (uint32_t)row[(c + e) * cs] << (16 * (e & 1));
     }
   }
   return v;
@@ -122,7 +139,7 @@ struct Shape {
 // Epi: __device__ void operator()(int batch, int split, int row, int col, const float (&v)[8]) -- eight
 // consecutive columns of one output row, indices inside the batch; it does its own masking.
 // bx of total: this workgroup among those of the problem.
-template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
 __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int bx, int total, int split) {
   using S = Shape<T, BM, BN, BK, WGM, WGN>;
   constexpr int V = 16 / sizeof(T), WGK = S::WGK, TM = S::TM, TN = S::TN;
@@ -195,7 +212,8 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
 #pragma unroll
     for (int s = 0; s < NVB; ++s) {
       const int c = ((s * 256 + tid) % VPRB) * V + (B_K ? kt * BK : j0);
-      rb[s] = load_masked<T>(sb.base + rowB[s], c, sb.cols, rowB[s] >= 0);
+      if constexpr (B_STRIDED) rb[s] = load_strided<T>(sb.base + rowB[s], c, g.B.cs, sb.cols, rowB[s] >= 0);
+      else rb[s] = load_masked<T>(sb.base + rowB[s], c, sb.cols, rowB[s] >= 0);
     }
   };
   // ---- LDS layout.  bf16: 32-deep sub-tiles in the swizzled layouts of mfma_gemm.h.  fp32: [k][x], rows of
@@ -380,9 +398,9 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   }
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
 __global__ __launch_bounds__(256) void edge_kernel(Args g, Epi epi) {
-  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K>(g, epi, blockIdx.x, gridDim.x, blockIdx.y);
+  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi, B_STRIDED>(g, epi, blockIdx.x, gridDim.x, blockIdx.y);
 }
 
 // Two problems of one shape in one launch: the first n0 workgroups of a row of the grid take g0, the rest g1.
@@ -408,7 +426,7 @@ constexpr int kCUs = 256;
 
 inline i64 tile_count(i64 batches, i64 M, i64 N, int t) { return batches * ((M + t - 1) / t) * ((N + t - 1) / t); }
 // contraction depth of a stage; fp32 halves it, which keeps as many workgroups per CU as in bf16
-inline int stage_depth(Tile t, size_t es) { return (t == TILE_32 ? 128 : 64) * 2 / (int)es; }
+constexpr int stage_depth(Tile t, size_t es) { return (t == TILE_32 ? 128 : 64) * 2 / (int)es; }
 
 struct Problem {
   i64 batches, M, N, K;
@@ -434,10 +452,10 @@ void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, cons
   hipLaunchKernelGGL(kern, dim3((unsigned)(n0 + n1), (unsigned)(s0 > s1 ? s0 : s1)), dim3(256), S::LDS, st, g0, g1, e0, e1, n0);
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, bool B_STRIDED = false, class Epi>
 void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits, hipStream_t st) {
   using S = Shape<T, BM, BN, BK, WGM, WGN>;
-  auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi>;
+  auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi, B_STRIDED>;
   // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;

@@ -136,6 +136,26 @@ i64 internal_columns(const poetx_linear_desc* d) {
   return (N + 7) / 8 * 8;
 }
 
+// Few token-major tokens: the forward's applies read X and write Z as they are, element by element, where the two
+// transposing launches (some 5 us each) would cost more.  Every 32 rows of a block read the whole block's features
+// again, so the element reads are in proportion to (n + m) N b; the workgroups of b = 512 are besides a chain of four
+// dependent stages, and lose from half of that on.  bf16 forwards, us, with transposes / in place: 2048 x 2048, b = 256:
+// 29.7 / 21.0 for one token, 32.3 / 28.7 for 16, 38.2 / 34.5 for 31, 25.7 / 31.2 for 64 (bf16 transposes
+// of whole 64-token tiles are half as dear; 1024 x 1024, b = 128, 128 tokens: 21.8 / 25.2); 512 x 1376, b = 64: 27.5 / 21.6 for 16, 29.1 / 24.9 for 200; 4096 x 14336, b = 512:
+// 57.6 / 50.8 for one, 62.7 / 60.2 for three, 53.7 / 63.5 for 16; 4096 x 4096, b = 512, 8 tokens: 39.5 / 46.6.
+// fp32, 512 x 768, b = 64: 27.7 / 17.1 for 16, 30.6 / 22.0 for 200.
+bool reads_tokens_in_place(const poetx_linear_desc* d) {
+  if (d->layout != POETX_TOKEN_MAJOR || g_force_fma.load()) return false;
+  const i64 N = d->n_tokens;
+  if (d->dtype == POETX_BF16 && N % 64 == 0) return false;
+  const i64 Ni = internal_columns(d);
+  if (use_mfma(d->dtype) && (mfma_apply_left_ragged_supported(d->d_in, Ni, d->block) || mfma_apply_left_ragged_supported(d->d_out, N, d->block)))
+    return false;
+  // the same kernel tile as feature-major calls take: results are the same bit for bit in either layout
+  if (!edge_apply_smallest_tile(d->d_in, Ni, d->block) || !edge_apply_smallest_tile(d->d_out, N, d->block)) return false;
+  return (double)(d->d_in + (i64)d->d_out) * N * d->block <= (d->block <= 256 ? 1 << 25 : 1 << 24);
+}
+
 // Which kernels run also depends on the pointers (their alignment), which a workspace query does not see: the
 // queries below cover every path, at every token count a stage may run with.
 size_t blockgrad_ws_bytes(const poetx_linear_desc* d, int dim) {
@@ -496,8 +516,7 @@ int poetx_linear_fwd(const poetx_linear_desc* desc, const void* X, const void* W
   hipStream_t st = (hipStream_t)stream;
   const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype;
   const i64 N = desc->n_tokens, Ni = internal_columns(desc);
-  LayoutStaging lay(desc, ws, st);
-  const Act x = lay.in(X, m), z = lay.out(Z, n), A{ws, Ni, Ni};
+  const Act A{ws, Ni, Ni};
   char* after = (char*)ws + act_bytes(desc, m);
   Act B{saved_B, N, N};
   if (!saved_B) {  // memory-saving variant: scratch only
@@ -506,6 +525,18 @@ int poetx_linear_fwd(const poetx_linear_desc* desc, const void* X, const void* W
   }
   W = resolve_weight(desc, W, after, st);
   void* part = after + dequantised_weight_bytes(desc);
+  if (reads_tokens_in_place(desc)) {
+    {
+      StageTimer tm(POETX_STAGE_APPLY, st);
+      edge_apply_tokens(dt, X, m, true, A.out(), Ni, false, m, N, Ni, perm_R, blocks_R, b, 1, st);
+    }
+    dense_dispatch(dt, 0, W, n, m, A, B, part, st, weight_in_kernel(desc));
+    StageTimer tm(POETX_STAGE_APPLY, st);
+    edge_apply_tokens(dt, B.p, B.ld, false, Z, n, true, n, N, N, perm_P, blocks_P, b, 1, st);
+    return launch_status();
+  }
+  LayoutStaging lay(desc, ws, st);
+  const Act x = lay.in(X, m), z = lay.out(Z, n);
   apply_left_dispatch(dt, x, A, m, perm_R, blocks_R, b, 1, st);              // mm1: A = R^T X
   dense_dispatch(dt, 0, W, n, m, A, B, part, st, weight_in_kernel(desc));    // mm2: B = W A
   apply_left_dispatch(dt, B, z, n, perm_P, blocks_P, b, 1, st);              // mm3: Z = P^T B

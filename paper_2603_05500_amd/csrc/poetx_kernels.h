@@ -43,6 +43,11 @@ void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void*
 // V: d x cols, out: d x cols_out (cols_out >= cols; the extra columns are written as zeros)
 void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int d, i64 cols, i64 cols_out, const int32_t* perm,
                      const void* blocks, int b, int transpose_G, hipStream_t st);
+// does edge_apply_left take its smallest tile?
+bool edge_apply_smallest_tile(int d, i64 cols_out, int b);
+// the same on that tile for a few tokens with exactly one of V, out token major ([token][ld])
+void edge_apply_tokens(int dtype, const void* V, i64 ldv, bool v_tm, void* out, i64 ldo, bool out_tm, int d, i64 cols, i64 cols_out,
+                       const int32_t* perm, const void* blocks, int b, int transpose_G, hipStream_t st);
 size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b);
 void edge_blockgrad(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
                     hipStream_t st);

@@ -60,6 +60,35 @@ def test_apply_off_alignment(lib, d, b, cols, off, dtype):
         assert torch.all(buf[:off] == -7.0) and torch.all(buf[off + d * cols:] == -7.0)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,n,N,b", [
+    (8, 12, 1, 4),              # one token
+    (65, 40, 31, 32),           # tail blocks, one off a tile
+    (1000, 264, 33, 24),
+    (512, 768, 7, 256),         # a contraction of four stages and more per tile
+    (1024, 512, 200, 64),       # several token tiles, remainder
+])
+def test_forward_reads_tokens_in_place(lib, m, n, N, b, dtype):
+    """A few token-major tokens are read and written without transposing passes: Z and the saved B are the feature-major
+    call's bit for bit, feature-major being checked against the oracle, and nothing outside Z is written."""
+    data = synth_layer(9050 + m + n + N, m, n, N, b, 3, dtype, 0.01)
+    ref = orc.linear_fwd_bwd_from_theta(data["X"], data["dZ"], data["W"], data["pi_R"], data["pi_P"],
+                                        data["theta_R"], data["theta_P"], b, 3)
+    res = run_layer(data, dtype)
+    # on the tensor's scale: a row of one token may be a sum that cancels, whose error is the dtype's rounding of the terms
+    assert rel_err(res["Z"], ref["Z"]) <= TOL[dtype]
+    dev = res["dev"]
+    desc = lib.make_desc(m, n, b, 3, N, lib.F32 if dtype == "f32" else lib.BF16, layout=lib.TOKEN_MAJOR)
+    buf = torch.full((N * n + 16,), -7.0, dtype=tdtype(dtype), device="cuda")
+    Zt = buf[8:8 + N * n].view(N, n)
+    B = torch.full_like(dev["B"], float("nan"))
+    ws = torch.full((lib.poetx_linear_workspace_bytes(desc) // 4 + 1,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
+    lib.poetx_linear_fwd(desc, dev["X"].t().contiguous(), dev["W"], dev["pi_R"], dev["pi_P"], dev["blk_R"], dev["blk_P"], Zt, B, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(Zt, dev["Z"].t()) and torch.equal(B, dev["B"])
+    assert torch.all(buf[:8] == -7.0) and torch.all(buf[8 + N * n:] == -7.0)
+
+
 @pytest.mark.parametrize("b", [2, 15, 16, 31, 33, 64, 65, 128])
 @pytest.mark.parametrize("k", [1, 2, 5])
 def test_small_block_series(lib, b, k):

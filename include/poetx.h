@@ -53,8 +53,9 @@
  *    products when all three dimensions are multiples of 128 (fp32 MFMA).  The dense
  *    products, the structured applies and the block gradients of everything else (small
  *    blocks, ragged tails, any token count, fp32 tensors) run on an edge-handling
- *    matrix-core product of the tensors' type; the series of fp32 tensors and of small
- *    blocks and poetx_perm_blockdiag_apply_right run on plain fp32-FMA kernels.
+ *    matrix-core product of the tensors' type; the series of blocks up to b = 128 run on
+ *    fp32 matrix instructions, one launch per direction; the series of other blocks (fp32,
+ *    b neither 256 nor 512) and poetx_perm_blockdiag_apply_right on plain fp32-FMA kernels.
  *    poetx_linear_path reports which stages of a descriptor the streaming kernels take.
  *  - Output buffers must not overlap input buffers (in-place operation is refused:
  *    the kernels of one call read rows that other workgroups of the same call write).

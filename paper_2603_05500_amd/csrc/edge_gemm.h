@@ -12,7 +12,7 @@
 // per stage; the loads of the next stage are in flight under the products of this one.
 //
 // What bounds it: at the sizes it serves the chip is rarely full, so a pass is a chain of latencies (load,
-// LDS, matrix product, store).  Hence the tile follows the problem (see pick_tile): 128 x 128 where that
+// LDS, matrix product, store).  Hence the tile follows the problem (see pick_plan): 128 x 128 where that
 // fills the chip, 64 x 64 below, and 32 x 32 with the four waves splitting the contraction (each takes a
 // quarter of every stage; the partial tiles meet in LDS) for the smallest, which quarters the chain.
 // Contractions that still leave CUs idle are split over workgroups as well (fp32 partials, fixed order).

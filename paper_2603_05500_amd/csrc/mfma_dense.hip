@@ -16,6 +16,7 @@
 // fragment reads are pinned to fixed places between the MFMAs (each wave spreads its loads
 // over different places), and the load addresses are a uniform base plus a per-lane offset that
 // never changes, so the loop carries no vector address arithmetic.
+// Products of too few such tiles for the chip take 256 x 128 or 128 x 128 ones, or split their contraction (see pick_plan).
 #include "edge_gemm.h"
 #include "mfma_dense_kernel.h"
 

@@ -37,9 +37,9 @@ int static_scratch(void** out) {
 }
 
 inline bool use_mfma(int dtype) { return dtype == POETX_BF16 && !g_force_fma.load(); }
-// the matrix-core kernels move 16 bytes per lane: every tensor they touch must be 16-byte aligned
 // series of small blocks: fp32 whatever the precision asked for, one launch for a whole chain
 inline bool series_small(int b) { return series_small_supported(b) && !g_force_fma.load(); }
+// the streaming kernels move 16 bytes per lane: every tensor they touch must be 16-byte aligned
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 inline size_t esize(int dtype) { return dtype == POETX_F32 ? 4 : 2; }
 inline bool dtype_ok(int dtype) { return dtype == POETX_F32 || dtype == POETX_BF16; }
@@ -403,7 +403,7 @@ int poetx_linear_path(const poetx_linear_desc* d) {
   const int m = d->d_in, n = d->d_out, b = d->block;
   const i64 N = d->n_tokens;
   int path = 0;
-  if (d->dtype == POETX_F32 && !g_force_fma.load() && mfma_dense_f32_supported(n, m, N)) path |= POETX_PATH_DENSE;   // fp32 MFMA; the other stages of fp32 tensors stay on the plain-FMA kernels
+  if (d->dtype == POETX_F32 && !g_force_fma.load() && mfma_dense_f32_supported(n, m, N)) path |= POETX_PATH_DENSE;   // the other stages of fp32 tensors take the edge-handling kernels
   if (!use_mfma(d->dtype)) return path;
   if (mfma_apply_left_supported(m, N, N, b) && mfma_apply_left_supported(n, N, N, b)) path |= POETX_PATH_APPLY;
   if (mfma_dense_supported(n, m, N)) path |= POETX_PATH_DENSE;

@@ -133,11 +133,12 @@ template <class Epi>
 void launch_product(const mm::Args& g, Epi epi, int batches, hipStream_t st) {
   mm::launch<CBM, CBN, 2, 2, true, false, false, CNS, true>(g, epi, batches, 1, st);
 }
-// Blocks worked off together: two workgroups per CU, and what passes from launch to launch (5 MB a block in the backward,
-// rewritten in place by the next group) stays in the 256 MB memory-side cache.  Build + backward at k = 5 in groups of 16 /
-// 32 / 48 against all at once, us: 80 blocks 1029 / 906 / 940 / 999, 160 blocks 2057 / 1791 / 1919 / 2241.
-constexpr int GROUP = 32;
-inline int group_size(int blocks) { return ceil_div(blocks, ceil_div(blocks, GROUP)); }   // equal groups
+// Blocks worked off together, of those left: 32 are two workgroups per CU, and what passes from launch to launch (5 MB a block in
+// the backward, rewritten in place by the next group) stays in the 256 MB memory-side cache; a short remainder joins the last
+// group, as a launch of its own costs the same however few its blocks (up to 40 still fit the cache).  All but the last group are
+// a multiple of 8, which keeps the tiles of a block on one XCD.  Build + backward at k = 5, all at once / equal groups of
+// at most 32 / this, us: 35 blocks 418 / 517 / 418, 47: 549 / 573 / 546, 66: - / 856 / 752, 80: 999 / 961 / 886, 160: 2241 / 1734 / 1737.
+inline int group_size(int left) { return left <= 40 ? left : 32; }
 void set_src(mm::Source& s, const uint16_t* A, const uint16_t* B, int b) {
   s.A = A; s.B = B; s.lda = b; s.ldb = b; s.sA = (i64)b * b; s.sB = (i64)b * b; s.ktiles = b / CBK;
 }
@@ -163,9 +164,8 @@ void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void*
     return;
   }
   const i64 bb = (i64)b * b;
-  const int group = group_size(all);
-  for (int j0 = 0; j0 < all; j0 += group) {
-    const int nb = all - j0 < group ? all - j0 : group;
+  for (int j0 = 0, nb; j0 < all; j0 += nb) {
+    nb = group_size(all - j0);
     const i64 total = nb * bb;
     float* C = ws;
     uint16_t* Qb = (uint16_t*)(C + total);
@@ -204,9 +204,8 @@ void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumul
   ws += all * bb / 2;
   skew_materialize_launch(sides[0].theta, b, nb0, nullptr, nullptr, T_all, st);
   if (nb1) skew_materialize_launch(sides[1].theta, b, nb1, nullptr, nullptr, T_all + nb0 * bb, st);
-  const int group = group_size(all);
-  for (int j0 = 0; j0 < all; j0 += group) {
-    const int nb = all - j0 < group ? all - j0 : group;
+  for (int j0 = 0, nb; j0 < all; j0 += nb) {
+    nb = group_size(all - j0);
     const i64 total = nb * bb;
     const float* D = sides[0].dG + j0 * bb;
     const uint16_t* Tb = T_all + j0 * bb;

@@ -408,13 +408,17 @@ void lds_cnp_build(const float* theta, int nb, int k, float* G_f32, void* E_bf16
   launch_chain<CHAIN_FWD>(a, st);
 }
 
-// Blocks per pair of backward launches: two workgroups per block fill the 256 CUs once, and the W matrices between the two
-// passes (k * 256 KB per block) stay in the 256 MB memory-side cache, being rewritten in place by the next group.
-constexpr int GROUP_BLOCKS = 128;
+// Blocks per pair of backward launches, of those left: 128 are two workgroups per block on 256 CUs, once, and the R_m between the two
+// passes (k * 256 KB per block) stay in the 256 MB memory-side cache, being rewritten in place by the next group; a short
+// remainder joins the last group.  Build + backward at k = 5, all at once / groups of 128, us: 130 blocks 213 / 222, 144: 226 / 224,
+// 200: 280 / 260, 320: 438 / 404.
+constexpr int GROUP_MOST = 144;
+inline int group_size(int left) { return left <= GROUP_MOST ? left : 128; }
+inline int max_group(int blocks) { return blocks < GROUP_MOST ? blocks : GROUP_MOST; }   // bound on any group's size
 
 size_t lds_cnp_bwd_ws_floats(int nb, int k) {
   const size_t bb = (size_t)LB * LB;
-  return ((size_t)k * (nb < GROUP_BLOCKS ? nb : GROUP_BLOCKS) + nb) * bb + nb * bb / 2;
+  return ((size_t)k * max_group(nb) + nb) * bb + nb * bb / 2;
 }
 
 void lds_cnp_bwd(const SeriesSide* sides, int nsides, int k, int accumulate, float* ws, hipStream_t st) {
@@ -428,11 +432,11 @@ void lds_cnp_bwd(const SeriesSide* sides, int nsides, int k, int accumulate, flo
   a.k = k;
   a.dQ = ws;
   a.M = ws + (size_t)nb * LB * LB;
-  uint16_t* Qb = (uint16_t*)(a.M + (size_t)k * (nb < GROUP_BLOCKS ? nb : GROUP_BLOCKS) * LB * LB);
+  uint16_t* Qb = (uint16_t*)(a.M + (size_t)k * max_group(nb) * LB * LB);
   skew_materialize_chain_launch(sides[0].theta, a.nb0, nsides > 1 ? sides[1].theta : nullptr, nb - a.nb0, nullptr, Qb, st);
   a.Qb = Qb;
-  for (a.j0 = 0; a.j0 < nb; a.j0 += GROUP_BLOCKS) {
-    a.nb = nb - a.j0 < GROUP_BLOCKS ? nb - a.j0 : GROUP_BLOCKS;
+  for (a.j0 = 0; a.j0 < nb; a.j0 += a.nb) {
+    a.nb = group_size(nb - a.j0);
     launch_chain<CHAIN_BWD1>(a, st);
     launch_chain<CHAIN_BWD2>(a, st);
   }

@@ -195,7 +195,7 @@ def test_dense_tiles(lib, n, m, N):
     assert torch.all(guard[:256] == -7.0) and torch.all(guard[256 + n * N:] == -7.0)
 
 
-@pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 130, (3,)), (256, 130, (2,)), (256, 3, (1, 2, 7))])
+@pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 40, (3,)), (512, 130, (3,)), (256, 130, (2,)), (256, 150, (2,)), (256, 3, (1, 2, 7))])
 def test_matrix_core_series(lib, b, nb, ks):
     """The bf16 series of large blocks, build and backward through poetx_cnp_build / poetx_cnp_bwd: every shape of the
     recurrences (the tiled one pairs powers: odd and even orders start differently), batches that are worked off in more

@@ -137,7 +137,7 @@ void launch_product(const mm::Args& g, Epi epi, int batches, hipStream_t st) {
 // the backward, rewritten in place by the next group) stays in the 256 MB memory-side cache; a short remainder joins the last
 // group, as a launch of its own costs the same however few its blocks (up to 40 still fit the cache).  All but the last group are
 // a multiple of 8, which keeps the tiles of a block on one XCD.  Build + backward at k = 5, all at once / equal groups of
-// at most 32 / this, us: 35 blocks 418 / 517 / 418, 47: 549 / 573 / 546, 66: - / 856 / 752, 80: 999 / 961 / 886, 160: 2241 / 1734 / 1737.
+// at most 32 / this, us: 35 blocks 418 / 517 / 418, 47: 549 / 573 / 544, 66: - / 856 / 803, 80: 999 / 961 / 886, 160: 2241 / 1734 / 1739.
 inline int group_size(int left) { return left <= 40 ? left : 32; }
 void set_src(mm::Source& s, const uint16_t* A, const uint16_t* B, int b) {
   s.A = A; s.B = B; s.lda = b; s.ldb = b; s.sA = (i64)b * b; s.sB = (i64)b * b; s.ktiles = b / CBK;

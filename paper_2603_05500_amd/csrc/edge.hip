@@ -173,9 +173,10 @@ void reduce(const float* part, i64 M, i64 N, int splits, T* out, i64 ld, hipStre
 }
 
 template <class T>
-void dense_t(int dtype, int trans_w, const T* W, int n, int m, const T* act, i64 ld_act, T* out, i64 ld_out, i64 N, void* ws, hipStream_t st) {
+void dense_t(int dtype, int trans_w, const T* W, int n, int m, const T* act, i64 ld_act, i64 act_cols, T* out, i64 ld_out, i64 N, void* ws,
+             hipStream_t st) {
   const int M = trans_w ? m : n, K = trans_w ? n : m;
-  const Plan p = dense_plan(dtype, M, N, K);
+  const Plan p = dense_plan(dtype, M, act_cols, K);
   Args g{};
   g.A = Op{W, m, 0, nullptr, n, m, 0, 0};
   g.B = Op{act, ld_act, 0, nullptr, K, (int)N, 0, 0};
@@ -192,10 +193,10 @@ void dense_t(int dtype, int trans_w, const T* W, int n, int m, const T* act, i64
 }
 
 template <class T>
-void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out, const int32_t* perm, const T* blocks, int b, int trans,
-             hipStream_t st) {
+void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out, i64 plan_cols, const int32_t* perm, const T* blocks, int b,
+             int trans, hipStream_t st) {
   const int nb = ceil_div(d, b);
-  const Plan p = pick_plan(nb, b, cols_out, b, sizeof(T), false);
+  const Plan p = pick_plan(nb, b, plan_cols, b, sizeof(T), false);
   Args g{};
   g.rpb = b;
   g.d = d;
@@ -258,26 +259,28 @@ void grad_pair_t(const Plan& p0, const Plan& p1, const GradProblem& q0, const Gr
 
 }  // namespace
 
-size_t edge_dense_workspace_bytes(int dtype, i64 M, i64 N, i64 K) {
-  const Plan p = dense_plan(dtype, M, N, K);
-  return p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
+size_t edge_dense_workspace_bytes(int dtype, i64 M, i64 act_cols, i64 K) {
+  const Plan p = dense_plan(dtype, M, act_cols, K);
+  return p.splits > 1 ? (size_t)p.splits * M * act_cols * sizeof(float) : 0;
 }
 
-void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void* act, i64 ld_act, void* out, i64 ld_out, i64 N, void* ws,
-                hipStream_t st) {
-  if (dtype == POETX_F32) dense_t<float>(dtype, trans_w, (const float*)W, n, m, (const float*)act, ld_act, (float*)out, ld_out, N, ws, st);
-  else dense_t<uint16_t>(dtype, trans_w, (const uint16_t*)W, n, m, (const uint16_t*)act, ld_act, (uint16_t*)out, ld_out, N, ws, st);
+void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void* act, i64 ld_act, i64 act_cols, void* out, i64 ld_out, i64 N,
+                void* ws, hipStream_t st) {
+  if (dtype == POETX_F32)
+    dense_t<float>(dtype, trans_w, (const float*)W, n, m, (const float*)act, ld_act, act_cols, (float*)out, ld_out, N, ws, st);
+  else
+    dense_t<uint16_t>(dtype, trans_w, (const uint16_t*)W, n, m, (const uint16_t*)act, ld_act, act_cols, (uint16_t*)out, ld_out, N, ws, st);
 }
 
-void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int d, i64 cols, i64 cols_out, const int32_t* perm,
+void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int d, i64 cols, i64 cols_out, i64 plan_cols, const int32_t* perm,
                      const void* blocks, int b, int transpose_G, hipStream_t st) {
   if (dtype == POETX_F32)
-    apply_t<float>((const float*)V, ldv, (float*)out, ldo, d, cols, cols_out, perm, (const float*)blocks, b, transpose_G, st);
+    apply_t<float>((const float*)V, ldv, (float*)out, ldo, d, cols, cols_out, plan_cols, perm, (const float*)blocks, b, transpose_G, st);
   else
-    apply_t<uint16_t>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, perm, (const uint16_t*)blocks, b, transpose_G, st);
+    apply_t<uint16_t>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, plan_cols, perm, (const uint16_t*)blocks, b, transpose_G, st);
 }
 
-bool edge_apply_smallest_tile(int d, i64 cols_out, int b) { return pick_plan(ceil_div(d, b), b, cols_out, b, 4, false).tile == TILE_32; }
+bool edge_apply_smallest_tile(int d, i64 plan_cols, int b) { return pick_plan(ceil_div(d, b), b, plan_cols, b, 4, false).tile == TILE_32; }
 
 void edge_apply_tokens(int dtype, const void* V, i64 ldv, bool v_tm, void* out, i64 ldo, bool out_tm, int d, i64 cols, i64 cols_out,
                        const int32_t* perm, const void* blocks, int b, int transpose_G, hipStream_t st) {

@@ -87,18 +87,27 @@ struct Act {
 };
 inline i64 min64(i64 a, i64 b) { return a < b ? a : b; }
 
-void apply_left_dispatch(int dtype, const Act& V, const Act& out, int d, const int32_t* perm, const void* blocks, int b, int trans,
-                         hipStream_t st) {
+// Which kernels run an apply is decided before the tensors of a call are looked at (apply_streams below): in one pass some
+// of them have padded columns and some do not, in another layout others, and the results are the same bit for bit.
+// streams: the streaming kernels, whole tiles or not.  plan_cols: columns that the edge kernel's tile is chosen for.
+void apply_left_dispatch(int dtype, const Act& V, const Act& out, int d, const int32_t* perm, const void* blocks, int b, int trans, bool streams,
+                         i64 plan_cols, hipStream_t st) {
   StageTimer tm(POETX_STAGE_APPLY, st);
-  if (use_mfma(dtype) && V.ld == out.ld && V.cols == out.cols && mfma_apply_left_supported(d, V.cols, V.ld, b) && aligned16(V.p) &&
-      aligned16(out.p) && aligned16(blocks))
-    mfma_apply_left(V.p, out.out(), d, V.cols, V.ld, perm, blocks, b, trans, st);
-  else if (use_mfma(dtype) && mfma_apply_left_ragged_supported(d, out.cols, b) && aligned16(blocks))
-    mfma_apply_left_ragged(V.p, V.ld, min64(V.cols, out.cols), out.out(), out.ld, out.cols, d, perm, blocks, b, trans, st);
-  else if (!g_force_fma.load())
-    edge_apply_left(dtype, V.p, V.ld, out.out(), out.ld, d, min64(V.cols, out.cols), out.cols, perm, blocks, b, trans, st);
-  else
+  if (use_mfma(dtype) && streams && aligned16(blocks)) {
+    if (V.ld == out.ld && V.cols == out.cols && mfma_apply_left_supported(d, V.cols, V.ld, b) && aligned16(V.p) && aligned16(out.p))
+      mfma_apply_left(V.p, out.out(), d, V.cols, V.ld, perm, blocks, b, trans, st);
+    else
+      mfma_apply_left_ragged(V.p, V.ld, min64(V.cols, out.cols), out.out(), out.ld, out.cols, d, perm, blocks, b, trans, st);
+  } else if (!g_force_fma.load()) {
+    edge_apply_left(dtype, V.p, V.ld, out.out(), out.ld, d, min64(V.cols, out.cols), out.cols, plan_cols, perm, blocks, b, trans, st);
+  } else {
     fma_apply_left(dtype, V.p, out.out(), d, V.cols, V.ld, perm, blocks, b, trans, st);
+  }
+}
+// an apply on its own: V and out of one shape
+void apply_left_alone(int dtype, const Act& V, const Act& out, int d, const int32_t* perm, const void* blocks, int b, int trans, hipStream_t st) {
+  const bool whole = mfma_apply_left_supported(d, V.cols, V.ld, b) && aligned16(V.p) && aligned16(out.p);
+  apply_left_dispatch(dtype, V, out, d, perm, blocks, b, trans, whole || mfma_apply_left_ragged_supported(d, V.cols, b), V.cols, st);
 }
 
 // part: scratch of dense_part_bytes() for products that split their contraction.
@@ -114,7 +123,7 @@ void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const A
   else if (dtype == POETX_F32 && !g_force_fma.load() && whole && mfma_dense_f32_supported(n, m, N) && mfma_dense_f32_fills(trans_w ? m : n, N) &&
            aligned16(W) && aligned16(act.p) && aligned16(out.p))
     mfma_dense_f32(trans_w, W, n, m, act.p, out.out(), N, st);
-  else if (!g_force_fma.load()) edge_dense(dtype, trans_w, W, n, m, act.p, act.ld, out.out(), out.ld, N, part, st);
+  else if (!g_force_fma.load()) edge_dense(dtype, trans_w, W, n, m, act.p, act.ld, act.cols, out.out(), out.ld, N, part, st);
   else fma_dense(dtype, trans_w, W, n, m, act.p, out.out(), N, st);
 }
 
@@ -136,6 +145,15 @@ i64 internal_columns(const poetx_linear_desc* d) {
   return (N + 7) / 8 * 8;
 }
 
+// Do the applies of a layer's side take the streaming kernels (bf16)?  Whole tiles of the call's own tokens, or enough columns in
+// the workspace.  The same answer for every tensor of every call on this descriptor, whatever its layout.
+bool apply_streams(const poetx_linear_desc* d, int dim) {
+  return mfma_apply_left_supported(dim, d->n_tokens, d->n_tokens, d->block) || mfma_apply_left_ragged_supported(dim, internal_columns(d), d->block);
+}
+void apply_left(const poetx_linear_desc* desc, const Act& V, const Act& out, int d, const int32_t* perm, const void* blocks, int trans, hipStream_t st) {
+  apply_left_dispatch(desc->dtype, V, out, d, perm, blocks, desc->block, trans, apply_streams(desc, d), desc->n_tokens, st);
+}
+
 // Few token-major tokens: the forward's applies read X and write Z as they are, element by element, where the two
 // transposing launches (some 5 us each) would cost more.  Every 32 rows of a block read the whole block's features
 // again, so the element reads are in proportion to (n + m) N b; the workgroups of b = 512 are besides a chain of four
@@ -148,11 +166,9 @@ bool reads_tokens_in_place(const poetx_linear_desc* d) {
   if (d->layout != POETX_TOKEN_MAJOR || g_force_fma.load()) return false;
   const i64 N = d->n_tokens;
   if (d->dtype == POETX_BF16 && N % 64 == 0) return false;
-  const i64 Ni = internal_columns(d);
-  if (use_mfma(d->dtype) && (mfma_apply_left_ragged_supported(d->d_in, Ni, d->block) || mfma_apply_left_ragged_supported(d->d_out, N, d->block)))
-    return false;
+  if (use_mfma(d->dtype) && (apply_streams(d, d->d_in) || apply_streams(d, d->d_out))) return false;
   // the same kernel tile as feature-major calls take: results are the same bit for bit in either layout
-  if (!edge_apply_smallest_tile(d->d_in, Ni, d->block) || !edge_apply_smallest_tile(d->d_out, N, d->block)) return false;
+  if (!edge_apply_smallest_tile(d->d_in, N, d->block) || !edge_apply_smallest_tile(d->d_out, N, d->block)) return false;
   return (double)(d->d_in + (i64)d->d_out) * N * d->block <= (d->block <= 256 ? 1 << 25 : 1 << 24);
 }
 
@@ -176,19 +192,17 @@ size_t blockgrad_parts_bytes(const poetx_linear_desc* d, int dim) {
   return align256(a > b ? a : b);
 }
 
-// Scratch of the dense products (partials of a split contraction), both directions.
+// Scratch of the dense products (partials of a split contraction), both directions.  Their activation operand always lives in
+// the workspace, so every plan is made for internal_columns().
 size_t dense_part_bytes(const poetx_linear_desc* d) {
-  size_t w = 0;
-  for (const i64 N : {(i64)d->n_tokens, internal_columns(d)}) {
-    const size_t f = edge_dense_workspace_bytes(d->dtype, d->d_out, N, d->d_in);
-    const size_t b = edge_dense_workspace_bytes(d->dtype, d->d_in, N, d->d_out);
-    w = f > w ? f : w;
-    w = b > w ? b : w;
-    if (d->dtype == POETX_BF16 && mfma_dense_supported(d->d_out, d->d_in, N)) {
-      const size_t mf = mfma_dense_workspace_bytes(d->d_out, N, d->d_in), mb = mfma_dense_workspace_bytes(d->d_in, N, d->d_out);
-      w = mf > w ? mf : w;
-      w = mb > w ? mb : w;
-    }
+  const i64 N = internal_columns(d);
+  const size_t f = edge_dense_workspace_bytes(d->dtype, d->d_out, N, d->d_in);
+  const size_t b = edge_dense_workspace_bytes(d->dtype, d->d_in, N, d->d_out);
+  size_t w = f > b ? f : b;
+  if (d->dtype == POETX_BF16 && mfma_dense_supported(d->d_out, d->d_in, N)) {
+    const size_t mf = mfma_dense_workspace_bytes(d->d_out, N, d->d_in), mb = mfma_dense_workspace_bytes(d->d_in, N, d->d_out);
+    w = mf > w ? mf : w;
+    w = mb > w ? mb : w;
   }
   return align256(w);
 }
@@ -306,7 +320,7 @@ int poetx_perm_blockdiag_apply_left(const void* V, void* out, int32_t d, int64_t
   if (cols >= (1ll << 31)) return POETX_ERR_UNSUPPORTED;
   size_t bytes = (size_t)d * ld * esize(dtype);
   if (overlap(V, bytes, out, bytes)) return POETX_ERR_INVALID_ARG;
-  apply_left_dispatch(dtype, Act{V, ld, cols}, Act{out, ld, cols}, d, perm, blocks, b, transpose_G != 0, (hipStream_t)stream);
+  apply_left_alone(dtype, Act{V, ld, cols}, Act{out, ld, cols}, d, perm, blocks, b, transpose_G != 0, (hipStream_t)stream);
   return launch_status();
 }
 
@@ -343,12 +357,12 @@ int poetx_merge_weight(const void* W, void* W_out, int32_t n, int32_t m, const i
   // W (n x m) is feature major for the output side (rows = output features): P^T W is a left apply.
   // The input side acts on the columns; a column gather is a row gather of the transpose, so the
   // product with R^T runs as R (P^T W)^T on the transposed matrix and is transposed back.
-  apply_left_dispatch(dtype, Act{W, m, m}, Act{T1, m, m}, n, perm_P, blocks_P, b, 1, st);        // T1 = P^T W         (n x m)
+  apply_left_alone(dtype, Act{W, m, m}, Act{T1, m, m}, n, perm_P, blocks_P, b, 1, st);        // T1 = P^T W         (n x m)
   {
     StageTimer tm(POETX_STAGE_LAYOUT, st);
     transpose_launch(dtype, T1, T2, n, m, m, n, n, st);                                   // T2 = T1^T          (m x n)
   }
-  apply_left_dispatch(dtype, Act{T2, n, n}, Act{T1, n, n}, m, perm_R, blocks_R, b, 0, st);       // T1 = R T2          (m x n)
+  apply_left_alone(dtype, Act{T2, n, n}, Act{T1, n, n}, m, perm_R, blocks_R, b, 0, st);       // T1 = R T2          (m x n)
   {
     StageTimer tm(POETX_STAGE_LAYOUT, st);
     transpose_launch(dtype, T1, W_out, m, n, n, m, m, st);                                // W_out = (R T2)^T = P^T W R^T
@@ -537,9 +551,9 @@ int poetx_linear_fwd(const poetx_linear_desc* desc, const void* X, const void* W
   }
   LayoutStaging lay(desc, ws, st);
   const Act x = lay.in(X, m), z = lay.out(Z, n);
-  apply_left_dispatch(dt, x, A, m, perm_R, blocks_R, b, 1, st);              // mm1: A = R^T X
+  apply_left(desc, x, A, m, perm_R, blocks_R, 1, st);              // mm1: A = R^T X
   dense_dispatch(dt, 0, W, n, m, A, B, part, st, weight_in_kernel(desc));    // mm2: B = W A
-  apply_left_dispatch(dt, B, z, n, perm_P, blocks_P, b, 1, st);              // mm3: Z = P^T B
+  apply_left(desc, B, z, n, perm_P, blocks_P, 1, st);              // mm3: Z = P^T B
   lay.finish();
   return launch_status();
 }
@@ -551,13 +565,13 @@ int poetx_linear_recompute_b(const poetx_linear_desc* desc, const void* X, const
   if (!X || !W || !perm_R || !blocks_R || !B_out) return POETX_ERR_INVALID_ARG;
   if (!ws || ws_bytes < poetx_linear_workspace_bytes(desc)) return POETX_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype;
+  const int m = desc->d_in, n = desc->d_out, dt = desc->dtype;
   const i64 N = desc->n_tokens, Ni = internal_columns(desc);
   LayoutStaging lay(desc, ws, st);
   const Act x = lay.in(X, m), A{ws, Ni, Ni};
   char* after = (char*)ws + act_bytes(desc, m);
   W = resolve_weight(desc, W, after, st);
-  apply_left_dispatch(dt, x, A, m, perm_R, blocks_R, b, 1, st);  // A = R^T X
+  apply_left(desc, x, A, m, perm_R, blocks_R, 1, st);  // A = R^T X
   dense_dispatch(dt, 0, W, n, m, A, Act{B_out, N, N}, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // B = W A
   return launch_status();
 }
@@ -566,14 +580,14 @@ int poetx_linear_recompute_b(const poetx_linear_desc* desc, const void* X, const
 static void bwd_input_impl(const poetx_linear_desc* desc, const Act& dZ, const void* W, const int32_t* perm_R,
                            const int32_t* perm_P, const void* blocks_R, const void* blocks_P, const Act& dX, const Act& dA,
                            void* ws, hipStream_t st, const void* W_resolved = nullptr) {
-  const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype;
+  const int m = desc->d_in, n = desc->d_out, dt = desc->dtype;
   const i64 Ni = internal_columns(desc);
   const Act dB{ws, Ni, Ni};
   char* after = (char*)ws + act_bytes(desc, n);
   W = W_resolved ? W_resolved : resolve_weight(desc, W, after, st);
-  apply_left_dispatch(dt, dZ, dB, n, perm_P, blocks_P, b, 0, st);  // dB = P dZ
+  apply_left(desc, dZ, dB, n, perm_P, blocks_P, 0, st);  // dB = P dZ
   dense_dispatch(dt, 1, W, n, m, dB, dA, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // dA = W^T dB
-  apply_left_dispatch(dt, dA, dX, m, perm_R, blocks_R, b, 0, st);  // dX = R dA
+  apply_left(desc, dA, dX, m, perm_R, blocks_R, 0, st);  // dX = R dA
 }
 
 int poetx_linear_bwd_input(const poetx_linear_desc* desc, const void* dZ, const void* W, const int32_t* perm_R,
@@ -717,7 +731,7 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
     char* w_keep = end - dequantised_weight_bytes(desc);
     B = Act{w_keep - act_bytes(desc, n), Ni, Ni};
     W_resolved = resolve_weight(desc, W, w_keep, st);
-    apply_left_dispatch(dt, x, dA, m, perm_R, blocks_R, b, 1, st);
+    apply_left(desc, x, dA, m, perm_R, blocks_R, 1, st);
     dense_dispatch(dt, 0, W_resolved, n, m, dA, B, rest, st, weight_in_kernel(desc));   // partials where dB will be
   }
   // Each side's gradient is streamed once where its tensors are whole tiles: dB = P dZ together with
@@ -750,7 +764,7 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
       StageTimer tm(POETX_STAGE_APPLY_GRAD, st);
       mfma_apply_grad(V.p, U.p, out.out(), d, V.cols, V.ld, perm, blocks, 0, dGs, part, st);
     } else {
-      apply_left_dispatch(dt, V, out, d, perm, blocks, b, 0, st);
+      apply_left(desc, V, out, d, perm, blocks, 0, st);
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
       blockgrad_dispatch(dt, U, V, d, perm, b, dGs, part, st);
     }

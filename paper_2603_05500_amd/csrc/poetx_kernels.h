@@ -37,14 +37,15 @@ void fma_cnp_bwd(const float* theta, const float* dG, int d, int b, int k, float
 
 // ---- edge-handling matrix-core path (edge.hip): bf16 and fp32, any sizes, strides and alignments --------
 // ws: the bytes the queries report (fp32 partials of a split contraction; 0 where there is no split).
-size_t edge_dense_workspace_bytes(int dtype, i64 M, i64 N, i64 K);
-void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void* act, i64 ld_act, void* out, i64 ld_out, i64 N, void* ws,
-                hipStream_t st);
-// V: d x cols, out: d x cols_out (cols_out >= cols; the extra columns are written as zeros)
-void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int d, i64 cols, i64 cols_out, const int32_t* perm,
+// act has act_cols columns, which the plan is made for and the query is asked with; the first N of the product go to out.
+size_t edge_dense_workspace_bytes(int dtype, i64 M, i64 act_cols, i64 K);
+void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void* act, i64 ld_act, i64 act_cols, void* out, i64 ld_out, i64 N,
+                void* ws, hipStream_t st);
+// V: d x cols, out: d x cols_out (cols_out >= cols; the extra columns are written as zeros); plan_cols: columns to choose the tile for
+void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int d, i64 cols, i64 cols_out, i64 plan_cols, const int32_t* perm,
                      const void* blocks, int b, int transpose_G, hipStream_t st);
 // does edge_apply_left take its smallest tile?
-bool edge_apply_smallest_tile(int d, i64 cols_out, int b);
+bool edge_apply_smallest_tile(int d, i64 plan_cols, int b);
 // the same on that tile for a few tokens with exactly one of V, out token major ([token][ld])
 void edge_apply_tokens(int dtype, const void* V, i64 ldv, bool v_tm, void* out, i64 ldo, bool out_tm, int d, i64 cols, i64 cols_out,
                        const int32_t* perm, const void* blocks, int b, int transpose_G, hipStream_t st);

@@ -8,7 +8,7 @@ import torch
 
 from oracle import poetx_oracle as orc
 from workloads import round_bf16, round_f32
-from tests.harness import TOL, rel_err, run_layer, tdtype, to_dev, to_np
+from tests.harness import TOL, build_blocks, rel_err, run_layer, tdtype, to_dev, to_np
 from tests.test_gpu_parity import check_layer, synth_layer
 
 pytestmark = pytest.mark.gpu
@@ -159,6 +159,71 @@ def test_ragged_token_counts_on_the_streaming_kernels(lib, m, n, N, b):
             got = {"Z": to_np(turn(Z)), "dX": to_np(turn(dX)), "dtheta_R": to_np(dth["R"]), "dtheta_P": to_np(dth["P"])}
             for key, v in got.items():
                 assert rel_err(v, ref[key]) <= TOL["bf16"], (key, layout, mem)
+
+
+def layer_calls(lib, data, dtype, layout, mem):
+    """Every linear call of one layout on device tensors, activations returned feature major: the forward, the recomputed
+    B, the backward in two calls and in one.  mem: B recomputed inside the forward and the one-call backward."""
+    m, n, N, b, k = (data[key] for key in ("m", "n", "N", "b", "k"))
+    dt, tm = tdtype(dtype), layout == lib.TOKEN_MAJOR
+    turn = (lambda t: t.t().contiguous()) if tm else (lambda t: t)
+    X, dZ, W = turn(to_dev(data["X"], dt)), turn(to_dev(data["dZ"], dt)), to_dev(data["W"], dt)
+    pi = {s: torch.from_numpy(data["pi_" + s].astype(np.int32)).cuda() for s in "RP"}
+    th = {s: to_dev(data["theta_" + s], torch.float32) for s in "RP"}
+    blk = {s: build_blocks(data["theta_" + s], d, b, k, dtype)[0] for s, d in (("R", m), ("P", n))}
+    desc = lib.make_desc(m, n, b, k, N, lib.F32 if dtype == "f32" else lib.BF16, flags=lib.FLAG_RECOMPUTE_B if mem else 0, layout=layout)
+    # poisoned: a stage that reads what no stage wrote shows
+    ws = torch.full((lib.poetx_linear_workspace_bytes(desc) // 4,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
+    B, dA = (torch.full((d, N), float("nan"), dtype=dt, device="cuda") for d in (n, m))
+    Z, dX, dX1 = torch.empty_like(dZ), torch.empty_like(X), torch.empty_like(X)
+    two, one = ({s: torch.full_like(th[s], float("nan")) for s in "RP"} for _ in range(2))
+    lib.poetx_linear_fwd(desc, X, W, pi["R"], pi["P"], blk["R"], blk["P"], Z, None if mem else B, ws)
+    if mem:
+        lib.poetx_linear_recompute_b(desc, X, W, pi["R"], blk["R"], B, ws)
+    lib.poetx_linear_bwd_input(desc, dZ, W, pi["R"], pi["P"], blk["R"], blk["P"], dX, dA, ws)
+    lib.poetx_linear_bwd_skew(desc, X, dZ, B, dA, pi["R"], pi["P"], th["R"], th["P"], two["R"], two["P"], False, ws)
+    lib.poetx_linear_bwd(desc, X, dZ, None if mem else B, W, pi["R"], pi["P"], blk["R"], blk["P"], th["R"], th["P"], dX1,
+                         one["R"], one["P"], False, ws)
+    torch.cuda.synchronize()
+    back = (lambda t: t.t().contiguous()) if tm else (lambda t: t)
+    return {"Z": back(Z), "B": B, "dX": back(dX), "dA": dA, "one-call dX": back(dX1), "dtheta_R": two["R"], "dtheta_P": two["P"],
+            "one-call dtheta_R": one["R"], "one-call dtheta_P": one["P"]}
+
+
+RAGGED_LAYERS = [
+    # unpadded layers: rows of the workspace are rounded up to 8 tokens only
+    (1024, 1024, 125, 256, "bf16"),     # 128 columns inside, a whole tile that the caller's tensors do not have
+    (1024, 512, 253, 256, "bf16"),      # 256 inside
+    (1024, 1024, 61, 512, "bf16"),      # 64 inside
+    (512, 768, 255, 64, "bf16"),        # small blocks: the contraction of the block gradients rounds up to a longer one
+    (512, 768, 255, 64, "f32"),
+    (1024, 768, 250, 192, "bf16"),      # neither small nor a streaming block side
+    # layers that are padded to whole 256-token tiles
+    (2048, 2048, 100, 256, "bf16"),     # fewer tokens than a tile
+    (2048, 2304, 192, 256, "bf16"),     # a multiple of the 64-token tiles
+    (2048, 2560, 200, 512, "bf16"),
+    (2048, 2560, 320, 512, "bf16"),
+    (4096, 4096, 72, 128, "bf16"),      # small blocks: their tile must not depend on the padding
+    (2048, 2048, 1088, 256, "bf16"),    # 17 * 64
+    (2048, 2304, 1793, 256, "bf16"),    # one past a tile
+]
+
+
+@pytest.mark.parametrize("m,n,N,b,dtype", RAGGED_LAYERS)
+def test_ragged_tokens_give_the_same_activations_in_every_form(lib, m, n, N, b, dtype):
+    """Activations (Z, B, dX, dA) of a token count that is no whole tile: bit for bit the same from either layout, from B kept
+    or recomputed and from one backward call or two, and right by the oracle."""
+    data = synth_layer(9600 + m + n + N + b, m, n, N, b, 2, dtype, 0.01 if b < 256 else 0.005)
+    ref = orc.linear_fwd_bwd_from_theta(data["X"], data["dZ"], data["W"], data["pi_R"], data["pi_P"],
+                                        data["theta_R"], data["theta_P"], b, 2)
+    first = layer_calls(lib, data, dtype, lib.FEATURE_MAJOR, False)
+    assert rel_err(to_np(first["Z"]), ref["Z"]) <= TOL[dtype] and rel_err(to_np(first["dX"]), ref["dX"]) <= TOL[dtype]
+    assert torch.equal(first["dX"], first["one-call dX"])
+    for layout in (lib.FEATURE_MAJOR, lib.TOKEN_MAJOR):
+        for mem in (False, True):
+            got = layer_calls(lib, data, dtype, layout, mem)
+            off = [key for key in ("Z", "B", "dX", "dA", "one-call dX") if not torch.equal(got[key], first[key])]
+            assert not off, (off, "token major" if layout else "feature major", "B recomputed" if mem else "B kept")
 
 
 @pytest.mark.parametrize("n,m,N", [

@@ -55,16 +55,15 @@ size_t mfma_blockgrad_workspace_bytes(int d, i64 N, int b) {
   return (size_t)pick_splits(d, N, b) * d * b * sizeof(float);
 }
 
-void mfma_blockgrad(const void* U, const void* V, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
-                    hipStream_t st) {
+void mfma_blockgrad(const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws, hipStream_t st) {
   const int nb = d / b;
   const int splits = pick_splits(d, N, b);
   mm::Args g{};
   g.nsrc = 1;
   g.s[0].A = (const uint16_t*)U;
   g.s[0].B = (const uint16_t*)V;
-  g.s[0].lda = N;
-  g.s[0].ldb = N;
+  g.s[0].lda = ldu;
+  g.s[0].ldb = ldv;
   g.s[0].ktiles = (int)(N / GBK) / splits;
   g.tiles_m = b / GBM;
   g.tiles_n = b / GBN;

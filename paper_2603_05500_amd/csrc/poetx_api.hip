@@ -172,24 +172,21 @@ bool reads_tokens_in_place(const poetx_linear_desc* d) {
   return (double)(d->d_in + (i64)d->d_out) * N * d->block <= (d->block <= 256 ? 1 << 25 : 1 << 24);
 }
 
-// Which kernels run also depends on the pointers (their alignment), which a workspace query does not see: the
-// queries below cover every path, at every token count a stage may run with.
+// Block gradients are summed over exactly the call's tokens, never over padding, by kernels that follow from the descriptor: the
+// order of the sum is the same in either layout and with B kept or recomputed, whichever of the tensors have padded columns.
+// Only the pointers' alignment can change the kernel, which a workspace query does not see: it covers both.
 size_t blockgrad_ws_bytes(const poetx_linear_desc* d, int dim) {
-  const i64 N = d->n_tokens, Ni = internal_columns(d);
+  const i64 N = d->n_tokens;
   size_t w = edge_blockgrad_workspace_bytes(d->dtype, dim, N, d->block);
-  const size_t e = edge_blockgrad_workspace_bytes(d->dtype, dim, Ni, d->block);
-  if (e > w) w = e;
-  if (d->dtype == POETX_BF16 && mfma_blockgrad_supported(dim, Ni, d->block)) {
-    const size_t f = mfma_blockgrad_workspace_bytes(dim, Ni, d->block);
+  if (d->dtype == POETX_BF16 && mfma_blockgrad_supported(dim, N, d->block)) {
+    const size_t f = mfma_blockgrad_workspace_bytes(dim, N, d->block);
     if (f > w) w = f;
   }
   return align256(w);
 }
 // both sides' block gradients as parts, for the one-launch series backward of small blocks
 size_t blockgrad_parts_bytes(const poetx_linear_desc* d, int dim) {
-  const size_t a = edge_blockgrad_parts_bytes(d->dtype, dim, d->n_tokens, d->block);
-  const size_t b = edge_blockgrad_parts_bytes(d->dtype, dim, internal_columns(d), d->block);
-  return align256(a > b ? a : b);
+  return align256(edge_blockgrad_parts_bytes(d->dtype, dim, d->n_tokens, d->block));
 }
 
 // Scratch of the dense products (partials of a split contraction), both directions.  Their activation operand always lives in
@@ -207,10 +204,11 @@ size_t dense_part_bytes(const poetx_linear_desc* d) {
   return align256(w);
 }
 
-void blockgrad_dispatch(int dtype, const Act& U, const Act& V, int d, const int32_t* perm, int b, float* dG, void* ws, hipStream_t st) {
-  const i64 N = min64(U.cols, V.cols);
-  if (use_mfma(dtype) && U.ld == V.ld && N == U.ld && mfma_blockgrad_supported(d, N, b) && aligned16(U.p) && aligned16(V.p))
-    mfma_blockgrad(U.p, V.p, d, N, perm, b, dG, ws, st);
+void blockgrad_dispatch(const poetx_linear_desc* desc, const Act& U, const Act& V, int d, const int32_t* perm, float* dG, void* ws, hipStream_t st) {
+  const int dtype = desc->dtype, b = desc->block;
+  const i64 N = desc->n_tokens;
+  if (use_mfma(dtype) && mfma_blockgrad_supported(d, N, b) && aligned16(U.p) && aligned16(V.p))   // N in whole vectors, hence the row strides too
+    mfma_blockgrad(U.p, U.ld, V.p, V.ld, d, N, perm, b, dG, ws, st);
   else if (!g_force_fma.load()) edge_blockgrad(dtype, U.p, U.ld, V.p, V.ld, d, N, perm, b, dG, ws, st);
   else fma_blockgrad(dtype, U.p, V.p, d, N, perm, b, dG, st);
 }
@@ -505,12 +503,12 @@ static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
   // halves need: dA | two-call scratch, or dA | dB | dG + chain | partials or dequantised weight
   const size_t two_calls = bwi > skew ? bwi : skew;
   size_t bwd = actm + two_calls;
-  if (desc->dtype == POETX_BF16 && mfma_apply_grad_supported(desc->d_in, Ni, Ni, desc->block) &&
-      mfma_apply_grad_supported(desc->d_out, Ni, Ni, desc->block)) {
-    size_t tail = align256(mfma_apply_grad_workspace_bytes(desc->d_in, Ni));
-    const size_t po = align256(mfma_apply_grad_workspace_bytes(desc->d_out, Ni));
+  const i64 N = desc->n_tokens;
+  if (desc->dtype == POETX_BF16 && Ni == N && mfma_apply_grad_supported(desc->d_in, N, N, desc->block) &&
+      mfma_apply_grad_supported(desc->d_out, N, N, desc->block)) {
+    size_t tail = align256(mfma_apply_grad_workspace_bytes(desc->d_in, N));
+    const size_t po = align256(mfma_apply_grad_workspace_bytes(desc->d_out, N));
     if (po > tail) tail = po;
-    if (bg > tail) tail = bg;                           // a side that runs in two passes
     if (wdeq + part > tail) tail = wdeq + part;
     const size_t one_pass = actm + actn + align256(chain * sizeof(float)) + tail;
     if (one_pass > bwd) bwd = one_pass;
@@ -636,14 +634,14 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
     float* dG = (float*)ws;                                   // [nbt][b][b]
     if (defer) {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      blockgrad_dispatch(dt, saved_B, dZ, n, perm_P, b, dtheta_P, bg_ws, st);
-      blockgrad_dispatch(dt, X, dA, m, perm_R, b, dtheta_R, bg_ws, st);
+      blockgrad_dispatch(desc, saved_B, dZ, n, perm_P, dtheta_P, bg_ws, st);
+      blockgrad_dispatch(desc, X, dA, m, perm_R, dtheta_R, bg_ws, st);
       return;
     }
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      blockgrad_dispatch(dt, saved_B, dZ, n, perm_P, b, dG, bg_ws, st);            // dG_P = B' dZ'^T
-      blockgrad_dispatch(dt, X, dA, m, perm_R, b, dG + nbP * bb, bg_ws, st);       // dG_R = X' dA'^T
+      blockgrad_dispatch(desc, saved_B, dZ, n, perm_P, dG, bg_ws, st);            // dG_P = B' dZ'^T
+      blockgrad_dispatch(desc, X, dA, m, perm_R, dG + nbP * bb, bg_ws, st);       // dG_R = X' dA'^T
     }
     cnp_bwd_both(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);
     return;
@@ -655,8 +653,8 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
                            {theta_R, (const float*)((char*)ws + blockgrad_parts_bytes(desc, n)), (i64)ceil_div(m, b) * b * b, 1, m, dtheta_R}};
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      const GradProblem gp{saved_B.p, dZ.p, saved_B.ld, dZ.ld, min64(saved_B.cols, dZ.cols), n, perm_P, (float*)sides[0].dG};
-      const GradProblem gr{X.p, dA.p, X.ld, dA.ld, min64(X.cols, dA.cols), m, perm_R, (float*)sides[1].dG};
+      const GradProblem gp{saved_B.p, dZ.p, saved_B.ld, dZ.ld, desc->n_tokens, n, perm_P, (float*)sides[0].dG};
+      const GradProblem gr{X.p, dA.p, X.ld, dA.ld, desc->n_tokens, m, perm_R, (float*)sides[1].dG};
       edge_blockgrad_parts_pair(dt, gp, gr, b, &sides[0].nsplit, &sides[1].nsplit, st);
     }
     StageTimer tm(POETX_STAGE_CNP_BWD, st);
@@ -676,7 +674,7 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
     float* dGs = defer ? dtheta : dG;
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      blockgrad_dispatch(dt, U, V, d, perm, b, dGs, bg_ws, st);
+      blockgrad_dispatch(desc, U, V, d, perm, dGs, bg_ws, st);
     }
     if (!defer) {
       StageTimer tm(POETX_STAGE_CNP_BWD, st);
@@ -734,16 +732,14 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
     apply_left(desc, x, dA, m, perm_R, blocks_R, 1, st);
     dense_dispatch(dt, 0, W_resolved, n, m, dA, B, rest, st, weight_in_kernel(desc));   // partials where dB will be
   }
-  // Each side's gradient is streamed once where its tensors are whole tiles: dB = P dZ together with
-  // dG_P = B' dZ'^T, then dA = W^T dB, then dX = R dA together with dG_R = X' dA'^T (Sec. 3.5).
-  const bool on_chip = desc->cnp_precision == POETX_CNP_BF16 && use_mfma(dt) && lds_cnp_supported(m, b) && lds_cnp_supported(n, b);
-  auto one_pass = [&](const Act& V, const Act& U, const Act& out, int d, const void* blocks) {
-    return on_chip && V.ld == U.ld && V.ld == out.ld && V.cols == V.ld && U.cols == V.ld && out.cols == V.ld &&
-           mfma_apply_grad_supported(d, V.cols, V.ld, b) && aligned16(V.p) && aligned16(U.p) && aligned16(out.p) && aligned16(blocks);
-  };
+  // Each side's gradient is streamed once where the call's tokens are whole tiles: dB = P dZ together with
+  // dG_P = B' dZ'^T, then dA = W^T dB, then dX = R dA together with dG_R = X' dA'^T (Sec. 3.5).  A token count that is padded
+  // in the workspace goes through the two halves: the caller's own tensors have no padded columns to stream.
   const Act dB{rest, Ni, Ni};
-  const bool one_P = one_pass(dz, B, dB, n, blocks_P), one_R = one_pass(dA, x, dx, m, blocks_R);
-  if (!one_P && !one_R) {   // the same values through the two halves
+  const bool one_pass = desc->cnp_precision == POETX_CNP_BF16 && use_mfma(dt) && lds_cnp_supported(m, b) && lds_cnp_supported(n, b) && Ni == N &&
+                        mfma_apply_grad_supported(m, N, N, b) && mfma_apply_grad_supported(n, N, N, b) && aligned16(dz.p) && aligned16(B.p) &&
+                        aligned16(x.p) && aligned16(dx.p) && aligned16(blocks_R) && aligned16(blocks_P);
+  if (!one_pass) {   // the same values through the two halves
     bwd_input_impl(desc, dz, W, perm_R, perm_P, blocks_R, blocks_P, dx, dA, rest, st, W_resolved);
     bwd_skew_impl(desc, x, dz, B, dA, perm_R, perm_P, theta_R, theta_P, dtheta_R, dtheta_P, accumulate, rest, st);
     lay.finish();
@@ -759,20 +755,14 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
   const bool defer = (desc->flags & POETX_FLAG_BLOCK_GRADS) != 0;   // block gradients to the caller, no series backward
   float* dG_P = defer ? dtheta_P : dG;
   float* dG_R = defer ? dtheta_R : dG + nbP * bb;
-  auto side = [&](bool one, const Act& V, const Act& U, const Act& out, int d, const int32_t* perm, const void* blocks, float* dGs) {
-    if (one) {
-      StageTimer tm(POETX_STAGE_APPLY_GRAD, st);
-      mfma_apply_grad(V.p, U.p, out.out(), d, V.cols, V.ld, perm, blocks, 0, dGs, part, st);
-    } else {
-      apply_left(desc, V, out, d, perm, blocks, 0, st);
-      StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      blockgrad_dispatch(dt, U, V, d, perm, b, dGs, part, st);
-    }
+  auto side = [&](const Act& V, const Act& U, const Act& out, int d, const int32_t* perm, const void* blocks, float* dGs) {
+    StageTimer tm(POETX_STAGE_APPLY_GRAD, st);
+    mfma_apply_grad(V.p, U.p, out.out(), d, N, N, perm, blocks, 0, dGs, part, st);
   };
-  side(one_P, dz, B, dB, n, perm_P, blocks_P, dG_P);
+  side(dz, B, dB, n, perm_P, blocks_P, dG_P);
   W = W_resolved ? W_resolved : resolve_weight(desc, W, part, st);   // the P side's partials are reduced by now (stream order): same space
   dense_dispatch(dt, 1, W, n, m, dB, dA, (char*)part + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));
-  side(one_R, dA, x, dx, m, perm_R, blocks_R, dG_R);
+  side(dA, x, dx, m, perm_R, blocks_R, dG_R);
   lay.finish();
   if (defer) return launch_status();
   cnp_bwd_both(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);

@@ -118,8 +118,8 @@ void mfma_apply_left_ragged(const void* V, i64 ldv, i64 cols, void* out, i64 ldo
                             int transpose_G, hipStream_t st);
 bool mfma_blockgrad_supported(int d, i64 N, int b);
 size_t mfma_blockgrad_workspace_bytes(int d, i64 N, int b);
-void mfma_blockgrad(const void* U, const void* V, int d, i64 N, const int32_t* perm, int b, float* dG,
-                    void* ws, hipStream_t st);
+// U and V: d rows of at least N tokens, row strides multiples of 8
+void mfma_blockgrad(const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws, hipStream_t st);
 // One pass over the incoming gradient V (d x N) for one side (mfma_applygrad.hip, b = 256):
 // out = Psi^T Diag(op(G)) Psi V and dG[j] = U'_j V'_j^T (rows gathered by perm).  ws: the bytes the
 // query reports (partial block gradients of the token ranges).

@@ -226,6 +226,24 @@ def test_ragged_tokens_give_the_same_activations_in_every_form(lib, m, n, N, b, 
             assert not off, (off, "token major" if layout else "feature major", "B recomputed" if mem else "B kept")
 
 
+@pytest.mark.parametrize("m,n,N,b,dtype", RAGGED_LAYERS)
+def test_ragged_tokens_give_the_same_parameter_gradients_in_every_form(lib, m, n, N, b, dtype):
+    """The packed gradients of the same layers: bit for bit the same from either layout and from B kept or recomputed, in two
+    calls and in one (which may differ from each other by the order of a sum), and right by the oracle."""
+    data = synth_layer(9600 + m + n + N + b, m, n, N, b, 2, dtype, 0.01 if b < 256 else 0.005)
+    ref = orc.linear_fwd_bwd_from_theta(data["X"], data["dZ"], data["W"], data["pi_R"], data["pi_P"],
+                                        data["theta_R"], data["theta_P"], b, 2)
+    first = layer_calls(lib, data, dtype, lib.FEATURE_MAJOR, False)
+    keys = [pre + "dtheta_" + s for s in "RP" for pre in ("", "one-call ")]
+    for key in keys:
+        assert rel_err(to_np(first[key]), ref[key.split()[-1]]) <= TOL[dtype], key
+    for layout in (lib.FEATURE_MAJOR, lib.TOKEN_MAJOR):
+        for mem in (False, True):
+            got = layer_calls(lib, data, dtype, layout, mem)
+            off = [key for key in keys if not torch.equal(got[key], first[key])]
+            assert not off, (off, "token major" if layout else "feature major", "B recomputed" if mem else "B kept")
+
+
 @pytest.mark.parametrize("n,m,N", [
     (256, 256, 256),        # 128 x 128 tiles, contraction too short to split
     (256, 2048, 256),       # ... split over workgroups

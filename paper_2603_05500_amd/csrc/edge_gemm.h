@@ -399,19 +399,20 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
 }
 
 template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
-__global__ __launch_bounds__(256) void edge_kernel(Args g, Epi epi) {
-  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi, B_STRIDED>(g, epi, blockIdx.x, gridDim.x, blockIdx.y);
+__global__ __launch_bounds__(256) void edge_kernel(Args g, Epi epi, int total, int first) {
+  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi, B_STRIDED>(g, epi, first + (int)blockIdx.x, total, blockIdx.y);
 }
 
 // Two problems of one shape in one launch: the first n0 workgroups of a row of the grid take g0, the rest g1.
 template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
-__global__ __launch_bounds__(256) void edge_pair_kernel(Args g0, Args g1, Epi e0, Epi e1, int n0) {
-  const bool second = (int)blockIdx.x >= n0;
+__global__ __launch_bounds__(256) void edge_pair_kernel(Args g0, Args g1, Epi e0, Epi e1, int n0, int total, int first) {
+  const int bx = first + (int)blockIdx.x;
+  const bool second = bx >= n0;
   const Args g = second ? g1 : g0;
   const Epi epi = second ? e1 : e0;
   const int split = blockIdx.y;
   if (split * g.stages_per_split >= g.stages) return;
-  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K>(g, epi, second ? (int)blockIdx.x - n0 : (int)blockIdx.x, second ? (int)gridDim.x - n0 : n0, split);
+  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K>(g, epi, second ? bx - n0 : bx, second ? total - n0 : n0, split);
 }
 
 // ---- host side -------------------------------------------------------------------------------
@@ -448,8 +449,10 @@ void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, cons
   (void)configured;
   tile_args(g0, q0, BM, BN, BK, s0);
   tile_args(g1, q1, BM, BN, BK, s1);
-  const int n0 = g0.batches * g0.tiles_m * g0.tiles_n, n1 = g1.batches * g1.tiles_m * g1.tiles_n;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(n0 + n1), (unsigned)(s0 > s1 ? s0 : s1)), dim3(256), S::LDS, st, g0, g1, e0, e1, n0);
+  const i64 n0 = q0.batches * g0.tiles_m * g0.tiles_n, n1 = q1.batches * g1.tiles_m * g1.tiles_n;
+  launch_in_rows(n0 + n1, [&](int first, unsigned count) {
+    hipLaunchKernelGGL(kern, dim3(count, (unsigned)(s0 > s1 ? s0 : s1)), dim3(256), S::LDS, st, g0, g1, e0, e1, (int)n0, (int)(n0 + n1), first);
+  });
 }
 
 template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, bool B_STRIDED = false, class Epi>
@@ -461,7 +464,10 @@ void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits,
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
   (void)configured;
   tile_args(g, Problem{batches, M, N, K}, BM, BN, BK, splits);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(batches * g.tiles_m * g.tiles_n), (unsigned)splits), dim3(256), S::LDS, st, g, epi);
+  const i64 total = batches * g.tiles_m * g.tiles_n;
+  launch_in_rows(total, [&](int first, unsigned count) {
+    hipLaunchKernelGGL(kern, dim3(count, (unsigned)splits), dim3(256), S::LDS, st, g, epi, (int)total, first);
+  });
 }
 
 template <class T, bool A_K, bool B_K, class Epi>

@@ -65,6 +65,15 @@ __host__ __device__ inline int block_side(int d, int b, int j) {
   return rem < b ? rem : b;
 }
 
+// A grid dimension holds less than 2^32 threads; very many workgroups (small blocks, very many tokens) take several launches.  Calls
+// launch(first, count) for each; the kernel adds `first` to its number.  More than an int counts is an empty grid, which HIP refuses.
+template <class F>
+inline void launch_in_rows(i64 total, F launch) {
+  constexpr i64 row = 1 << 21;   // of up to 1024 threads
+  if (total > 0x7fffffff) return launch(0, 0u);
+  for (i64 first = 0; first < total; first += row) launch((int)first, (unsigned)(total - first < row ? total - first : row));
+}
+
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Convert the status of the launches enqueued so far into a poetx_status.

@@ -78,13 +78,13 @@ __device__ inline void product(floatx4 (&acc)[NT], const floatx4 (&Y)[NT], const
 
 template <int NT>
 __global__ __launch_bounds__(64 * NT) void series_small_build_kernel(const float* __restrict__ theta, int d, int b, int k, float* __restrict__ G,
-                                                                     uint16_t* __restrict__ E) {
+                                                                     uint16_t* __restrict__ E, int first) {
   constexpr int BP = NT * 16, LD = BP + 4;
   extern __shared__ __attribute__((aligned(16))) float lds[];
   float* Q = lds;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const i64 j = blockIdx.x;
+  const i64 j = first + (int)blockIdx.x;
   const Geometry s{b, block_side(d, b, (int)j)};
   load_q<BP, 64 * NT>(Q, theta + j * ((i64)b * (b - 1) / 2), s, tid);
   __syncthreads();
@@ -134,6 +134,7 @@ struct BwdSide {
 struct BwdArgs {
   BwdSide s[2];          // blocks of the first side, then of the second
   int b, k, accumulate;
+  int first;             // block of the launch's first workgroup
 };
 
 template <int NT>
@@ -145,9 +146,10 @@ __global__ __launch_bounds__(128 * NT) void series_small_bwd_kernel(BwdArgs a) {
   float* const W0 = lds + BP * LD;   // crossing buffers W0 and, where there are two, the one behind it
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool second = (int)blockIdx.x >= a.s[0].nb;
+  const int wg = a.first + (int)blockIdx.x;
+  const bool second = wg >= a.s[0].nb;
   const BwdSide& sd = a.s[second ? 1 : 0];
-  const i64 j = second ? (int)blockIdx.x - a.s[0].nb : (int)blockIdx.x;
+  const i64 j = second ? wg - a.s[0].nb : wg;
   const int b = a.b;
   const Geometry s{b, block_side(sd.d, b, (int)j)};
   const i64 L = (i64)b * (b - 1) / 2;
@@ -242,15 +244,20 @@ void build_t(const float* theta, int d, int b, int k, float* G, uint16_t* E, hip
   static const bool configured = hipFuncSetAttribute((const void*)series_small_build_kernel<NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                      build_lds<NT>()) == hipSuccess;
   (void)configured;
-  hipLaunchKernelGGL(series_small_build_kernel<NT>, dim3(ceil_div(d, b)), dim3(64 * NT), build_lds<NT>(), st, theta, d, b, k, G, E);
+  launch_in_rows(ceil_div(d, b), [&](int first, unsigned count) {
+    hipLaunchKernelGGL(series_small_build_kernel<NT>, dim3(count), dim3(64 * NT), build_lds<NT>(), st, theta, d, b, k, G, E, first);
+  });
 }
 
 template <int NT>
-void bwd_t(const BwdArgs& a, hipStream_t st) {
+void bwd_t(BwdArgs a, hipStream_t st) {
   static const bool configured = hipFuncSetAttribute((const void*)series_small_bwd_kernel<NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                      bwd_lds<NT>()) == hipSuccess;
   (void)configured;
-  hipLaunchKernelGGL(series_small_bwd_kernel<NT>, dim3(a.s[0].nb + a.s[1].nb), dim3(128 * NT), bwd_lds<NT>(), st, a);
+  launch_in_rows((i64)a.s[0].nb + a.s[1].nb, [&](int first, unsigned count) {
+    a.first = first;
+    hipLaunchKernelGGL(series_small_bwd_kernel<NT>, dim3(count), dim3(128 * NT), bwd_lds<NT>(), st, a);
+  });
 }
 
 }  // namespace

@@ -308,3 +308,34 @@ def test_matrix_core_series(lib, b, nb, ks):
         assert torch.equal(E[:, 1], E[:, 0].transpose(1, 2))
         want = orc.packed_from_skew_grad(orc.cnp_bwd(Q, to_np(dG)[check], k), b, len(check) * b)
         assert np.linalg.norm(to_np(dth)[check] - want) <= 4 * 2.0 ** -9 * norm * np.linalg.norm(want)
+
+
+def test_block_counts_beyond_one_grid_dimension(lib):
+    """35 million 2 x 2 blocks: build, backward and apply need more workgroups than a grid dimension holds.  A block is
+    [[0, t], [-t, 0]], so at k = 2 the series is (1 - 2 t^2) I + (2 t - t^3) J."""
+    d, b, k = 70_000_001, 2, 2
+    nb = (d + 1) // 2
+    g = torch.Generator(device="cuda").manual_seed(2)
+    th = torch.randn((nb, 1), generator=g, device="cuda") * 0.1
+    live = th[:, 0].clone()
+    live[-1] = 0.0                                   # a tail block of side one: its parameter is dead
+    ws = torch.empty(max(lib.poetx_cnp_workspace_bytes(d, b), lib.poetx_cnp_bwd_workspace_bytes(d, b, k)), dtype=torch.uint8, device="cuda")
+    G = torch.full((nb, b, b), float("nan"), device="cuda")
+    lib.poetx_cnp_build(th, d, b, k, lib.CNP_FP32, G, None, ws)
+    diag, off = 1 - 2 * live ** 2, 2 * live - live ** 3
+    want = torch.stack((diag, off, -off, diag), 1).view(nb, b, b)
+    assert float((G - want).abs().max()) <= 1e-6
+    dG = torch.randn((nb, b, b), generator=g, device="cuda")
+    dth = torch.full_like(th, float("nan"))
+    lib.poetx_cnp_bwd(th, dG, d, b, k, lib.CNP_FP32, dth, False, ws)
+    grad = -4 * live * (dG[:, 0, 0] + dG[:, 1, 1]) + (2 - 3 * live ** 2) * (dG[:, 0, 1] - dG[:, 1, 0])
+    grad[-1] = 0.0
+    assert float((dth[:, 0] - grad).abs().max()) <= 1e-5
+    pi = torch.randperm(d, generator=g, device="cuda")
+    V = torch.randn((d, 1), generator=g, device="cuda")
+    out = torch.full_like(V, float("nan"))
+    lib.poetx_perm_blockdiag_apply_left(V, out, pi.to(torch.int32), G, b, False)
+    x = torch.zeros(nb * b, device="cuda")
+    x[:d] = V[pi, 0]
+    y = (G * x.view(nb, 1, b)).sum(2).view(-1)[:d]
+    assert float((out[pi, 0] - y).abs().max()) <= 1e-5

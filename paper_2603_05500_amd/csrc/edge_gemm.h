@@ -58,7 +58,7 @@ __device__ inline u32x4 load_masked(const T* row, int c, int cols, bool row_ok) 
   constexpr int V = 16 / sizeof(T);
   u32x4 v = {0, 0, 0, 0};
   if (!row_ok || c >= cols) return v;
-  if (c + V <= cols) return load16(row + c);
+  if (cols - c >= V) return load16(row + c);   // no sum: the last column may be the last int
   const int n = cols - c;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
@@ -79,10 +79,10 @@ template <class T>
 __device__ inline u32x4 load_strided(const T* row, int c, i64 cs, int cols, bool row_ok) {
   constexpr int V = 16 / sizeof(T);
   u32x4 v = {0, 0, 0, 0};
-  if (!row_ok) return v;
+  if (!row_ok || c >= cols) return v;
 #pragma unroll
   for (int e = 0; e < V; ++e) {
-    if (c + e < cols) {
+    if (e < cols - c) {
       if constexpr (sizeof(T) == 4) v[e] = __builtin_bit_cast(uint32_t, row[(c + e) * cs]);
       else v[e >> 1] |= (uint32_t)row[(c + e) * cs] << (16 * (e & 1));
     }

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(512) void apply_left_ragged_kernel(const uint16_t* 
   edge::u32x4 pend[4];
   auto flush = [&](int t) {
     const int col = scol + t * BN;
-    if (col + 8 <= no) {
+    if (no - col >= 8) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) *reinterpret_cast<edge::u32x4_a2*>(out + soff[i] + col) = pend[i];
     } else {

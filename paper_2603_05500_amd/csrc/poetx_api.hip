@@ -140,7 +140,7 @@ i64 internal_columns(const poetx_linear_desc* d) {
   const i64 N = d->n_tokens;
   if (g_force_fma.load()) return N;                     // the plain kernels know one token count only
   const i64 Np = (N + 255) / 256 * 256;
-  if (N == Np) return N;
+  if (N == Np || N > (1ll << 31) - 256) return N;       // column counts are ints
   if (d->dtype == POETX_BF16 && mfma_dense_supported(d->d_out, d->d_in, Np) && mfma_dense_worth_padding(d->d_out, d->d_in, N)) return Np;
   return (N + 7) / 8 * 8;
 }

@@ -310,6 +310,49 @@ def test_matrix_core_series(lib, b, nb, ks):
         assert np.linalg.norm(to_np(dth)[check] - want) <= 4 * 2.0 ** -9 * norm * np.linalg.norm(want)
 
 
+def test_column_counts_up_to_the_last_int(lib):
+    """2^31 - 5 tokens of two features: column indices run up to the last int, and the tiles need more workgroups than one grid
+    dimension holds.  Tokens are zero but for runs at the ends and where an index or a grid could wrap; the apply, the
+    forward and the block gradients against float64 there, and finite (written, from zeros) everywhere else."""
+    m, N, b, bf = 2, 2 ** 31 - 5, 2, torch.bfloat16
+    at = torch.cat([torch.arange(max(c - 40, 0), min(c + 40, N)) for c in (0, 2 ** 24, 2 ** 29, 2 ** 30, N)]).cuda()
+    g = torch.Generator(device="cuda").manual_seed(1)
+
+    def sparse():
+        t = torch.zeros((m, N), dtype=bf, device="cuda")
+        t[:, at] = torch.randn((m, at.numel()), generator=g, device="cuda").to(bf)
+        return t, t[:, at].double()
+    X, x = sparse()
+    E = (torch.randn((1, b, b), generator=g, device="cuda") * 0.1).to(bf)
+    blk, G = torch.stack((E, E.transpose(1, 2)), 1).contiguous(), E[0].double() + torch.eye(b, device="cuda", dtype=torch.float64)
+    W = torch.randn((m, m), generator=g, device="cuda").to(bf)
+    pi = torch.tensor([1, 0], dtype=torch.int32, device="cuda")
+    swap = lambda t: t.flip(0)
+    err = lambda got, want: float((got[:, at].double() - want).norm() / want.norm())
+    Z = torch.full_like(X, float("nan"))
+    lib.poetx_perm_blockdiag_apply_left(X, Z, pi, blk, b, False)
+    torch.cuda.synchronize()
+    assert err(Z, swap(G @ swap(x))) <= 2.0 ** -8 and bool(torch.isfinite(Z).all())
+    desc = lib.make_desc(m, m, b, 1, N, lib.BF16, flags=lib.FLAG_BLOCK_GRADS)
+    ws = torch.empty(lib.poetx_linear_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    B = torch.full_like(X, float("nan"))
+    Z.fill_(float("nan"))
+    lib.poetx_linear_fwd(desc, X, W, pi, pi, blk, blk, Z, B, ws)
+    torch.cuda.synchronize()
+    want = W.double() @ swap(G.T @ swap(x))
+    assert err(B, want) <= 2.0 ** -7 and bool(torch.isfinite(B).all())
+    assert err(Z, swap(G.T @ swap(want))) <= 2.0 ** -6 and bool(torch.isfinite(Z).all())
+    del Z
+    dZ, z = sparse()
+    th = torch.zeros((1, 1), device="cuda")
+    dG = {s: torch.full((1, b, b), float("nan"), device="cuda") for s in "RP"}
+    lib.poetx_linear_bwd_skew(desc, X, dZ, B, dZ, pi, pi, th, th, dG["R"], dG["P"], False, ws)   # dZ in dA's place
+    torch.cuda.synchronize()
+    for s, u in (("R", x), ("P", B[:, at].double())):
+        want = swap(u) @ swap(z).T
+        assert float((dG[s][0].double() - want).norm() / want.norm()) <= 1e-5, s
+
+
 def test_block_counts_beyond_one_grid_dimension(lib):
     """35 million 2 x 2 blocks: build, backward and apply need more workgroups than a grid dimension holds.  A block is
     [[0, t], [-t, 0]], so at k = 2 the series is (1 - 2 t^2) I + (2 t - t^3) J."""

@@ -47,15 +47,18 @@
  *    with leading dimensions that are multiples of 8 elements (what any device
  *    allocator gives).  The streaming kernels move 16 aligned bytes per lane; a call
  *    whose pointers are not so aligned runs on the edge-handling kernels.
- *  - Which kernels serve a shape: the streaming matrix-core kernels cover bf16 tensors
- *    with b = 256 or 512 dividing d_in and d_out, dimensions that are multiples of 256
- *    and token counts that are multiples of 256, and, for fp32 tensors, the two dense
- *    products when all three dimensions are multiples of 128 (fp32 MFMA).  The dense
- *    products, the structured applies and the block gradients of everything else (small
- *    blocks, ragged tails, any token count, fp32 tensors) run on an edge-handling
- *    matrix-core product of the tensors' type; the series of blocks up to b = 128 run on
- *    fp32 matrix instructions, one launch per direction; the series of other blocks (fp32,
- *    b neither 256 nor 512) and poetx_perm_blockdiag_apply_right on plain fp32-FMA kernels.
+ *  - Which kernels serve a shape.  bf16 tensors, streaming matrix-core kernels: the dense
+ *    products where d_in and d_out are multiples of 256 and the token count is one too or
+ *    the layer is large enough for the workspace's activations to be padded to one; the
+ *    structured applies where b = 256 or 512 divides their dimension, for whole tiles of 128
+ *    (b = 512: 64) tokens or from 256 tokens (padding included) on; the block gradients for
+ *    such blocks and multiples of 64 tokens, from 256 on.  fp32 tensors, streaming kernel:
+ *    a dense product whose three dimensions are multiples of 128 with at least 192 output
+ *    tiles of 128 x 128.  The dense products, applies and block gradients of everything else
+ *    run on an edge-handling matrix-core product of the tensors' type.  Series: precision
+ *    POETX_CNP_BF16 with b = 256 or 512 dividing the dimension on bf16 matrix instructions;
+ *    blocks up to b = 128 on fp32 ones whatever the precision, one launch per direction; all
+ *    others, and poetx_perm_blockdiag_apply_right, on plain fp32-FMA kernels.
  *    poetx_linear_path reports which stages of a descriptor the streaming kernels take.
  *  - Output buffers must not overlap input buffers (in-place operation is refused:
  *    the kernels of one call read rows that other workgroups of the same call write).
@@ -281,8 +284,8 @@ size_t poetx_linear_workspace_bytes(const poetx_linear_desc* desc);
 /* Which stages of `desc` the streaming matrix-core kernels take (bit set; 16-byte aligned pointers
  * assumed).  Returns a combination of POETX_PATH_* bits, 0 when every stage runs on the edge-handling
  * or plain kernels, or minus a poetx_status when the descriptor is invalid. */
-#define POETX_PATH_APPLY 1              /* gather + block-diagonal product + scatter            */
-#define POETX_PATH_DENSE 2              /* B = W A, dA = W^T dB (the only bit fp32 tensors get) */
+#define POETX_PATH_APPLY 1              /* gather + block-diagonal product + scatter, both sides */
+#define POETX_PATH_DENSE 2              /* both B = W A and dA = W^T dB (the only bit fp32 tensors get) */
 #define POETX_PATH_BLOCKGRAD 4          /* block gradients (two-call backward)                 */
 #define POETX_PATH_SERIES 8             /* series backward on the matrix cores                 */
 #define POETX_PATH_SERIES_ON_CHIP 16    /* ... as one-launch chains with the block in LDS      */

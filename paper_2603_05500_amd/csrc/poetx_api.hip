@@ -110,6 +110,9 @@ void apply_left_alone(int dtype, const Act& V, const Act& out, int d, const int3
   apply_left_dispatch(dtype, V, out, d, perm, blocks, b, trans, whole || mfma_apply_left_ragged_supported(d, V.cols, b), V.cols, st);
 }
 
+// Does the streaming fp32 product take the direction with M output rows?
+bool dense_f32_streams(int n, int m, int M, i64 N) { return mfma_dense_f32_supported(n, m, N) && mfma_dense_f32_fills(M, N); }
+
 // part: scratch of dense_part_bytes() for products that split their contraction.
 // w_q8: W is a quantised weight buffer that the product dequantises itself (see weight_in_kernel)
 void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const Act& act, const Act& out, void* part, hipStream_t st,
@@ -120,7 +123,7 @@ void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const A
   if (w_q8) mfma_dense_q8(trans_w, W, n, m, act.p, out.out(), N, part, st);
   else if (use_mfma(dtype) && act.ld == act.cols && mfma_dense_supported(n, m, act.cols) && aligned16(W) && aligned16(act.p))
     mfma_dense(trans_w, W, n, m, act.p, act.cols, out.out(), out.ld, N, part, st);
-  else if (dtype == POETX_F32 && !g_force_fma.load() && whole && mfma_dense_f32_supported(n, m, N) && mfma_dense_f32_fills(trans_w ? m : n, N) &&
+  else if (dtype == POETX_F32 && !g_force_fma.load() && whole && dense_f32_streams(n, m, trans_w ? m : n, N) &&
            aligned16(W) && aligned16(act.p) && aligned16(out.p))
     mfma_dense_f32(trans_w, W, n, m, act.p, out.out(), N, st);
   else if (!g_force_fma.load()) edge_dense(dtype, trans_w, W, n, m, act.p, act.ld, act.cols, out.out(), out.ld, N, part, st);
@@ -152,6 +155,13 @@ bool apply_streams(const poetx_linear_desc* d, int dim) {
 }
 void apply_left(const poetx_linear_desc* desc, const Act& V, const Act& out, int d, const int32_t* perm, const void* blocks, int trans, hipStream_t st) {
   apply_left_dispatch(desc->dtype, V, out, d, perm, blocks, desc->block, trans, apply_streams(desc, d), desc->n_tokens, st);
+}
+
+// Does poetx_linear_bwd stream each side's gradient once (aligned tensors)?
+bool bwd_one_pass(const poetx_linear_desc* d) {
+  const i64 N = d->n_tokens;
+  return d->cnp_precision == POETX_CNP_BF16 && use_mfma(d->dtype) && lds_cnp_supported(d->d_in, d->block) && lds_cnp_supported(d->d_out, d->block) &&
+         internal_columns(d) == N && mfma_apply_grad_supported(d->d_in, N, N, d->block) && mfma_apply_grad_supported(d->d_out, N, N, d->block);
 }
 
 // Few token-major tokens: the forward's applies read X and write Z as they are, element by element, where the two
@@ -413,19 +423,18 @@ int poetx_linear_path(const poetx_linear_desc* d) {
   const int rc = check_desc(d);
   if (rc) return -rc;
   const int m = d->d_in, n = d->d_out, b = d->block;
-  const i64 N = d->n_tokens;
+  const i64 N = d->n_tokens, Ni = internal_columns(d);
   int path = 0;
-  if (d->dtype == POETX_F32 && !g_force_fma.load() && mfma_dense_f32_supported(n, m, N)) path |= POETX_PATH_DENSE;   // the other stages of fp32 tensors take the edge-handling kernels
+  // the other stages of fp32 tensors take the edge-handling kernels
+  if (d->dtype == POETX_F32 && !g_force_fma.load() && dense_f32_streams(n, m, n, N) && dense_f32_streams(n, m, m, N)) path |= POETX_PATH_DENSE;
   if (!use_mfma(d->dtype)) return path;
-  if (mfma_apply_left_supported(m, N, N, b) && mfma_apply_left_supported(n, N, N, b)) path |= POETX_PATH_APPLY;
-  if (mfma_dense_supported(n, m, N)) path |= POETX_PATH_DENSE;
+  if (apply_streams(d, m) && apply_streams(d, n)) path |= POETX_PATH_APPLY;
+  if (mfma_dense_supported(n, m, Ni)) path |= POETX_PATH_DENSE;
   if (mfma_blockgrad_supported(m, N, b) && mfma_blockgrad_supported(n, N, b)) path |= POETX_PATH_BLOCKGRAD;
   if (d->cnp_precision == POETX_CNP_BF16 && mfma_cnp_supported(m, b) && mfma_cnp_supported(n, b)) {
     path |= POETX_PATH_SERIES;
     if (lds_cnp_supported(m, b) && lds_cnp_supported(n, b)) path |= POETX_PATH_SERIES_ON_CHIP;
-    if (lds_cnp_supported(m, b) && lds_cnp_supported(n, b) && mfma_apply_grad_supported(m, N, N, b) &&
-        mfma_apply_grad_supported(n, N, N, b))
-      path |= POETX_PATH_BWD_ONE_PASS;
+    if (bwd_one_pass(d)) path |= POETX_PATH_BWD_ONE_PASS;
   }
   if (weight_in_kernel(d)) path |= POETX_PATH_W_INT8_IN_KERNEL;
   return path;
@@ -736,9 +745,8 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
   // dG_P = B' dZ'^T, then dA = W^T dB, then dX = R dA together with dG_R = X' dA'^T (Sec. 3.5).  A token count that is padded
   // in the workspace goes through the two halves: the caller's own tensors have no padded columns to stream.
   const Act dB{rest, Ni, Ni};
-  const bool one_pass = desc->cnp_precision == POETX_CNP_BF16 && use_mfma(dt) && lds_cnp_supported(m, b) && lds_cnp_supported(n, b) && Ni == N &&
-                        mfma_apply_grad_supported(m, N, N, b) && mfma_apply_grad_supported(n, N, N, b) && aligned16(dz.p) && aligned16(B.p) &&
-                        aligned16(x.p) && aligned16(dx.p) && aligned16(blocks_R) && aligned16(blocks_P);
+  const bool one_pass = bwd_one_pass(desc) && aligned16(dz.p) && aligned16(B.p) && aligned16(x.p) && aligned16(dx.p) && aligned16(blocks_R) &&
+                        aligned16(blocks_P);
   if (!one_pass) {   // the same values through the two halves
     bwd_input_impl(desc, dz, W, perm_R, perm_P, blocks_R, blocks_P, dx, dA, rest, st, W_resolved);
     bwd_skew_impl(desc, x, dz, B, dA, perm_R, perm_P, theta_R, theta_P, dtheta_R, dtheta_P, accumulate, rest, st);

@@ -110,13 +110,26 @@ def test_flag_and_quantised_weight_checks(clib):
 
 def test_linear_path_query(clib):
     """poetx_linear_path tells which stages the matrix-core kernels serve: all of them for the benchmark
-    shapes, the dense products alone for fp32 tensors, none for small shapes, and the INT8 bit only with the flag."""
+    shapes, the dense products alone for large fp32 tensors, none for small shapes, and the INT8 bit only with the flag."""
     full = px.PATH_APPLY | px.PATH_DENSE | px.PATH_BLOCKGRAD | px.PATH_SERIES | px.PATH_SERIES_ON_CHIP | px.PATH_BWD_ONE_PASS
     assert px.poetx_linear_path(px.make_desc(4096, 14336, 256, 5, 16384, px.BF16)) == full
     b512 = px.poetx_linear_path(px.make_desc(4096, 1024, 512, 5, 16384, px.BF16))
     assert b512 == px.PATH_APPLY | px.PATH_DENSE | px.PATH_BLOCKGRAD | px.PATH_SERIES
-    # fp32 tensors: only the dense products have a matrix-core kernel (fp32 MFMA), for multiples of 128
-    assert px.poetx_linear_path(px.make_desc(256, 256, 32, 4, 512, px.F32)) == px.PATH_DENSE
+    # fp32 tensors: only the dense products have a streaming kernel, for multiples of 128 and at least 192 output tiles
+    # of 128 x 128 -- in both directions
+    assert px.poetx_linear_path(px.make_desc(256, 256, 32, 4, 512, px.F32)) == 0
+    assert px.poetx_linear_path(px.make_desc(2048, 1536, 64, 4, 2048, px.F32)) == px.PATH_DENSE
+    assert px.poetx_linear_path(px.make_desc(1024, 1536, 64, 4, 2048, px.F32)) == 0          # 192 tiles one way, 128 the other
+    # bf16 token counts that are no whole tiles: padded where the layer is large enough, else the edge kernel
+    series = px.PATH_SERIES | px.PATH_SERIES_ON_CHIP
+    for layout in (px.FEATURE_MAJOR, px.TOKEN_MAJOR):
+        ragged = lambda m, n, N, b=256: px.poetx_linear_path(px.make_desc(m, n, b, 5, N, px.BF16, layout=layout))
+        assert ragged(3072, 8192, 4090) == px.PATH_APPLY | px.PATH_DENSE | series
+        assert ragged(2048, 2048, 100) == px.PATH_APPLY | px.PATH_DENSE | series
+        assert ragged(2048, 2048, 1088) == px.PATH_APPLY | px.PATH_DENSE | px.PATH_BLOCKGRAD | series     # 17 * 64
+        assert ragged(2048, 2048, 16) == series
+        assert ragged(512, 512, 300) == px.PATH_APPLY | series
+        assert ragged(2048, 2048, 1999, 128) == px.PATH_DENSE
     assert px.poetx_linear_path(px.make_desc(64, 64, 16, 3, 256, px.F32)) == 0
     assert px.poetx_linear_path(px.make_desc(512, 1376, 64, 4, 1024, px.BF16)) == 0
     xq = px.make_desc(4096, 4096, 256, 5, 16384, px.BF16, flags=px.FLAG_RECOMPUTE_B | px.FLAG_W_INT8)

@@ -300,15 +300,21 @@ def test_plain_series_orders(lib, k, b, dtype):
     check_layer(res, ref, data["pi_P"], dtype)
 
 
-@pytest.mark.parametrize("m,n,N,b,k", [(256, 384, 256, 64, 4), (640, 128, 384, 128, 3), (128, 128, 128, 32, 5)])
-def test_fp32_layer_dense_on_matrix_cores(lib, m, n, N, b, k):
-    """fp32 tensors whose dense products fit the fp32 matrix-core kernel (multiples of 128): the layer
-    against the oracle at the fp32 tolerance, and the same inputs through the plain-FMA kernels."""
+@pytest.mark.parametrize("m,n,N,b,k,streams", [
+    (256, 384, 256, 64, 4, False), (640, 128, 384, 128, 3, False), (128, 128, 128, 32, 5, False),
+    (2048, 1536, 2048, 64, 4, True),     # 192 and 256 tiles: the streaming fp32 product in both directions
+    (1536, 128, 24576, 128, 3, True),    # 192 tiles in one tile row
+    (1024, 1536, 2048, 64, 4, False),    # in the forward only
+])
+def test_fp32_layer_dense_on_matrix_cores(lib, m, n, N, b, k, streams):
+    """fp32 tensors whose dimensions are multiples of the streaming fp32 product's 128 x 128 tiles: with at least 192 of
+    them on that kernel, with fewer on the edge-handling one; the layer against the oracle at the fp32 tolerance,
+    and the same inputs through the plain-FMA kernels."""
     data = synth_layer(7600 + m + n + N + b, m, n, N, b, k, "f32", 0.01)
     ref = orc.linear_fwd_bwd_from_theta(data["X"], data["dZ"], data["W"], data["pi_R"], data["pi_P"],
                                         data["theta_R"], data["theta_P"], b, k)
     desc = lib.make_desc(m, n, b, k, N, lib.F32)
-    assert lib.poetx_linear_path(desc) & lib.PATH_DENSE
+    assert lib.poetx_linear_path(desc) == (lib.PATH_DENSE if streams else 0)
     check_layer(run_layer(data, "f32"), ref, data["pi_P"], "f32")
     lib.poetx_debug_force_fma(True)
     try:

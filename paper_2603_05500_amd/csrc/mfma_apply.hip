@@ -408,6 +408,7 @@ void launch_apply_ragged(const uint16_t* V, i64 ldv, i64 nv, uint16_t* out, i64 
   for (int p = 1; p <= tiles; ++p) {
     const i64 rounds = ((i64)nb * MSPLIT * ceil_div(tiles, p) + 255) / 256, cost = rounds * (p + 3);
     if (best == 0 || cost < best) { best = cost; per = p; }
+    if (rounds == 1) break;   // longer ranges only cost more: with millions of tokens the search is not to take longer than the launch
   }
   hipLaunchKernelGGL(kern, dim3(ceil_div(tiles, per) * MSPLIT, nb), dim3(512), LDS, st, V, out, ldv, ldo, (int)nv, (int)no, perm, E, trans, tiles, per);
 }
@@ -431,8 +432,11 @@ void mfma_apply_left(const void* V, void* out, int d, i64 cols, i64 ld, const in
     mfma_apply_left_ragged(V, ld, cols, out, ld, cols, d, perm, E, b, transpose_G, st);
 }
 
-// From a few 64-token tiles on the streaming form wins over the edge kernel, which reads the block operand once per tile (256 columns
-// is where a workgroup has a second tile to overlap with; not tuned finer).
+// The edge kernel reads the block operand once per tile and more than one workgroup reads a row, the streaming form starts with a chain
+// of latencies (block operand, first tile).  us per apply of a ragged count, streaming / edge (back to back calls cost 8 us each at
+// least): b = 256, d = 14336: 9.4 / 10.6 at 100 columns, 11.0 / 19.6 at 250, 12.3 / 23.5 at 300; d = 4096: 8.2 / 8.3, 8.8 / 9.3,
+// 8.7 / 10.7.  b = 512, d = 14336: 16.5 / 16.4, 20.0 / 31.7, 20.1 / 38.3; d = 4096: 14.3 / 10.2, 14.5 / 14.1, 15.5 / 16.3; d = 1024:
+// 14.0 / 9.1, 13.7 / 9.2, 14.0 / 10.3.  256 columns: at least as fast but for the few blocks of a small b = 512 side.
 bool mfma_apply_left_ragged_supported(int d, i64 cols_out, int b) { return (b == 256 || b == 512) && d % b == 0 && cols_out >= 256; }
 
 void mfma_apply_left_ragged(const void* V, i64 ldv, i64 cols, void* out, i64 ldo, i64 cols_out, int d, const int32_t* perm, const void* E, int b,

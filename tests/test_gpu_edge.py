@@ -245,16 +245,23 @@ def test_ragged_tokens_give_the_same_parameter_gradients_in_every_form(lib, m, n
 
 
 @pytest.mark.parametrize("n,m,N", [
-    (256, 256, 256),        # 128 x 128 tiles, contraction too short to split
-    (256, 2048, 256),       # ... split over workgroups
-    (512, 512, 1024),       # 128 x 128 tiles
-    (2048, 512, 2048),      # 256 x 128 tiles one way, 128 x 128 the other
-    (2304, 2048, 2560),     # one way 256 x 128 tiles that do not fill whole groups of four tile rows
-    (2048, 2048, 1801),     # padded to 2048: ragged stores from 128 x 128 tiles
-    (512, 8192, 300),       # padded and split: ragged reduction
+    # tile and contraction ranges that the rule gives the forward; the backward
+    (256, 256, 256),        # 128 x 128; the same (contraction too short to split)
+    (256, 2048, 256),       # 128 x 128 in 8 ranges; 128 x 128
+    (512, 512, 1024),       # 128 x 128; the same
+    (2048, 512, 2048),      # 128 x 128; 128 x 128 in 4
+    (2304, 2048, 2560),     # 256 x 128, nine tile rows (no whole groups of four); the same with eight
+    (4096, 512, 2304),      # 256 x 256, 144 tiles; 128 x 128 in 2
+    # ragged counts, padded inside: stores that end at the last token, at rows of odd length
+    (2048, 2048, 1801),     # 128 x 128; the same
+    (512, 8192, 300),       # 128 x 128 in 16 (ragged reduction); 128 x 128
+    (4096, 512, 1100),      # 256 x 128; 128 x 128 in 4
+    (2304, 2048, 2559),     # 256 x 128; the same
+    (4096, 512, 2300),      # 256 x 256; 128 x 128 in 2
+    (512, 2560, 3329),      # 128 x 128 in 2; 256 x 256
 ])
 def test_dense_tiles(lib, n, m, N):
-    """Every output tile and contraction split of the streaming bf16 product, both directions, against float64 on the same
+    """Every output tile of the streaming bf16 product, whole and ragged, and split contractions, both directions, against float64 on the same
     bf16 operands: a whole pass with blocks equal to the identity is the dense product between two exact
     permutation round trips.  One bf16 rounding of an fp32 sum: 2^-8 of the largest value is generous."""
     rng = np.random.Generator(np.random.PCG64(9400 + n + m + N))
@@ -267,22 +274,23 @@ def test_dense_tiles(lib, n, m, N):
     pi = {"R": torch.from_numpy(rng.permutation(m).astype(np.int32)).cuda(), "P": torch.from_numpy(rng.permutation(n).astype(np.int32)).cuda()}
     blk = {s: torch.zeros((d // b, 2, b, b), dtype=bf, device="cuda") for s, d in (("R", m), ("P", n))}
     Xd, dZd, Wd = to_dev(X, bf), to_dev(dZ, bf), to_dev(W, bf)
-    guard = torch.full((n * N + 512,), -7.0, dtype=bf, device="cuda")
+    guard, guard_dA = (torch.full((d * N + 512,), -7.0, dtype=bf, device="cuda") for d in (n, m))
     Z, B = torch.empty((n, N), dtype=bf, device="cuda"), guard[256:256 + n * N].view(n, N)
-    dX, dA = torch.empty((m, N), dtype=bf, device="cuda"), torch.empty((m, N), dtype=bf, device="cuda")
+    dX, dA = torch.empty((m, N), dtype=bf, device="cuda"), guard_dA[256:256 + m * N].view(m, N)
     lib.poetx_linear_fwd(desc, Xd, Wd, pi["R"], pi["P"], blk["R"], blk["P"], Z, B, ws)
     lib.poetx_linear_bwd_input(desc, dZd, Wd, pi["R"], pi["P"], blk["R"], blk["P"], dX, dA, ws)
     torch.cuda.synchronize()
     assert rel_err(to_np(B), W @ X) <= 2.0 ** -8 and torch.equal(Z, B)
     assert rel_err(to_np(dA), W.T @ dZ) <= 2.0 ** -8 and torch.equal(dX, dA)
-    assert torch.all(guard[:256] == -7.0) and torch.all(guard[256 + n * N:] == -7.0)
+    for buf, used in ((guard, n * N), (guard_dA, m * N)):
+        assert torch.all(buf[:256] == -7.0) and torch.all(buf[256 + used:] == -7.0)
 
 
 @pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 40, (3,)), (512, 130, (3,)), (256, 130, (2,)), (256, 150, (2,)), (256, 3, (1, 2, 7))])
 def test_matrix_core_series(lib, b, nb, ks):
     """The bf16 series of large blocks, build and backward through poetx_cnp_build / poetx_cnp_bwd: every shape of the
     recurrences (the tiled one pairs powers: odd and even orders start differently), batches that are worked off in more
-    than one group (256) or on large tiles (512).  The bound is the error of rounding each product's operands
+    than one group.  The bound is the error of rounding each product's operands
     to bf16 (2^-9 of the first product, relative to terms of its size) with a factor of four."""
     L = b * (b - 1) // 2
     for k in ks:
@@ -382,3 +390,35 @@ def test_block_counts_beyond_one_grid_dimension(lib):
     x[:d] = V[pi, 0]
     y = (G * x.view(nb, 1, b)).sum(2).view(-1)[:d]
     assert float((out[pi, 0] - y).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("b,nbR,nbP", [
+    (512, 32, 12),      # groups 32 + 12: the P side ends inside the first group, the R side goes on in the second
+    (512, 8, 36),       # the P side ends inside the second group
+    (512, 12, 32),      # exactly at the boundary
+    (256, 100, 60),     # groups 128 + 32: the boundary inside the first
+    (256, 20, 140),     # inside the second
+])
+def test_series_groups_of_two_sides(lib, b, nbR, nbP):
+    """The series backward of both sides of a layer in one batch of several groups of blocks: packed gradients bit for bit those
+    of poetx_cnp_bwd, side by side, on the block gradients that the same layer reports."""
+    m, n, N, k, bf = nbR * b, nbP * b, 64, 3, torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(b + nbR)
+    normal = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    X, dZ, B, dA = (normal(d, N).to(bf) for d in (m, n, n, m))
+    pi = {s: torch.randperm(d, generator=g, device="cuda").to(torch.int32) for s, d in (("R", m), ("P", n))}
+    th = {s: normal(nb, b * (b - 1) // 2) * 0.005 for s, nb in (("R", nbR), ("P", nbP))}
+
+    def skew(flags, out):
+        desc = lib.make_desc(m, n, b, k, N, lib.BF16, flags=flags)
+        ws = torch.full((lib.poetx_linear_workspace_bytes(desc) // 4,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
+        lib.poetx_linear_bwd_skew(desc, X, dZ, B, dA, pi["R"], pi["P"], th["R"], th["P"], out["R"], out["P"], False, ws)
+        return out
+    got = skew(0, {s: torch.full_like(th[s], float("nan")) for s in "RP"})
+    dG = skew(lib.FLAG_BLOCK_GRADS, {s: torch.full((nb, b, b), float("nan"), device="cuda") for s, nb in (("R", nbR), ("P", nbP))})
+    for s, d in (("R", m), ("P", n)):
+        want = torch.full_like(th[s], float("nan"))
+        ws = torch.empty(lib.poetx_cnp_bwd_workspace_bytes(d, b, k), dtype=torch.uint8, device="cuda")
+        lib.poetx_cnp_bwd(th[s], dG[s], d, b, k, lib.CNP_BF16, want, False, ws)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(want).all()) and torch.equal(got[s], want), s

@@ -65,16 +65,17 @@ int check_desc(const poetx_linear_desc* d) {
   return POETX_OK;
 }
 
-// dG plus chain scratch per block element: five floats cover the tiled kernel families, the
-// on-chip chain keeps bf16(Q), k matrices between its passes and the result (k + 2 floats)
-size_t cnp_bwd_ws_floats(int d, int b, int k) {
-  const size_t per_elem = 1 + (size_t)(k + 2 > 5 ? k + 2 : 5);
-  return per_elem * ceil_div(d, b) * b * b;
+// dG plus the chain's scratch of nb blocks: five floats per element cover the tiled kernel families, k + 2 the on-chip chains
+// (checked against what those lay out)
+size_t cnp_bwd_ws_floats(i64 nb, int b, int k) {
+  const size_t elems = (size_t)nb * b * b;
+  size_t chain = (size_t)(k + 2 > 5 ? k + 2 : 5) * elems;
+  if (lds_cnp_supported(b, b) && lds_cnp_bwd_ws_floats((int)nb, k) > chain) chain = lds_cnp_bwd_ws_floats((int)nb, k);
+  return elems + chain;
 }
-// The same when both sides of a layer go through the series backward together.
-size_t cnp_bwd_ws_floats_both(int m, int n, int b, int k) {
-  const size_t per_elem = (size_t)(k + 3 > 6 ? k + 3 : 6);   // tiled kernels: dG and 5 of chain; on chip: dG, bf16(Q) (half), k + 1 of chain
-  return per_elem * (ceil_div(m, b) + ceil_div(n, b)) * b * b;
+// ... of a call's series: those of one side after the other, or of both sides together
+size_t cnp_bwd_ws_floats(const poetx_linear_desc* d) {
+  return cnp_bwd_ws_floats((i64)ceil_div(d->d_in, d->block) + ceil_div(d->d_out, d->block), d->block, d->neumann_k);
 }
 
 // A d x cols activation, row stride ld.  Activations in the workspace have internal_columns() columns, the ones past
@@ -282,7 +283,7 @@ int poetx_cnp_build_static(const float* theta, int32_t d, int32_t b, int32_t k, 
 
 size_t poetx_cnp_bwd_workspace_bytes(int32_t d, int32_t b, int32_t k) {
   if (d <= 0 || b <= 0 || k < 1) return 0;
-  return align256((cnp_bwd_ws_floats(d, b, k) - (size_t)ceil_div(d, b) * b * b) * sizeof(float));   // without dG itself
+  return align256((cnp_bwd_ws_floats(ceil_div(d, b), b, k) - (size_t)ceil_div(d, b) * b * b) * sizeof(float));   // without dG itself
 }
 
 int poetx_cnp_bwd(const float* theta, const float* dG, int32_t d, int32_t b, int32_t k, int32_t precision,
@@ -496,13 +497,10 @@ static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
   const size_t part = dense_part_bytes(desc);
   fwd += wdeq + part;                                   // dequantised weight behind A (and B), then the dense product's partials
   size_t bwi = actn + wdeq + part;                      // dB = P dZ
-  int dmax = desc->d_in > desc->d_out ? desc->d_in : desc->d_out;
   size_t bg_in = blockgrad_ws_bytes(desc, desc->d_in);
   size_t bg_out = blockgrad_ws_bytes(desc, desc->d_out);
   const size_t bg = bg_in > bg_out ? bg_in : bg_out;
-  size_t chain = cnp_bwd_ws_floats(dmax, desc->block, desc->neumann_k);
-  const size_t both = cnp_bwd_ws_floats_both(desc->d_in, desc->d_out, desc->block, desc->neumann_k);
-  if (both > chain) chain = both;
+  const size_t chain = cnp_bwd_ws_floats(desc);
   size_t skew = align256(chain * sizeof(float)) + bg;
   const size_t parts = blockgrad_parts_bytes(desc, desc->d_in) + blockgrad_parts_bytes(desc, desc->d_out);
   if (series_small_supported(desc->block) && parts > skew) skew = parts;
@@ -628,9 +626,7 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
                           hipStream_t st) {
   const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype, k = desc->neumann_k;
   const int dmax = m > n ? m : n;
-  size_t chain_floats = cnp_bwd_ws_floats(dmax, b, k);
-  if (cnp_bwd_ws_floats_both(m, n, b, k) > chain_floats) chain_floats = cnp_bwd_ws_floats_both(m, n, b, k);
-  void* bg_ws = (char*)ws + align256(chain_floats * sizeof(float));
+  void* bg_ws = (char*)ws + align256(cnp_bwd_ws_floats(desc) * sizeof(float));
   // POETX_FLAG_BLOCK_GRADS: the block gradients go to the caller (in place of dtheta) and the series
   // backward is left to poetx_cnp_bwd
   const bool defer = (desc->flags & POETX_FLAG_BLOCK_GRADS) != 0;
@@ -757,9 +753,7 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
   const int nbP = n / b;
   const size_t bb = (size_t)b * b;
   float* dG = (float*)after_dB;                                    // both sides' block gradients, then chain scratch
-  size_t chain_floats = cnp_bwd_ws_floats(m > n ? m : n, b, k);
-  if (cnp_bwd_ws_floats_both(m, n, b, k) > chain_floats) chain_floats = cnp_bwd_ws_floats_both(m, n, b, k);
-  void* part = after_dB + align256(chain_floats * sizeof(float));
+  void* part = after_dB + align256(cnp_bwd_ws_floats(desc) * sizeof(float));
   const bool defer = (desc->flags & POETX_FLAG_BLOCK_GRADS) != 0;   // block gradients to the caller, no series backward
   float* dG_P = defer ? dtheta_P : dG;
   float* dG_R = defer ? dtheta_R : dG + nbP * bb;

@@ -16,10 +16,7 @@ struct EpiPartial {
   float* out;
   int b;
   i64 split_stride;
-  __device__ void operator()(int batch, int split, int row, int col, float4 v) const {
-    *reinterpret_cast<float4*>(out + split * split_stride + ((i64)batch * b + row) * b + col) = v;
-  }
-  __device__ void wide(int batch, int split, int row, int col, float4 lo, float4 hi) const {   // whole 32-byte sectors
+  __device__ void operator()(int batch, int split, int row, int col, float4 lo, float4 hi) const {   // whole 32-byte sectors
     float* p = out + split * split_stride + ((i64)batch * b + row) * b + col;
     *reinterpret_cast<float4*>(p) = lo;
     *reinterpret_cast<float4*>(p + 4) = hi;
@@ -59,20 +56,18 @@ void mfma_blockgrad(const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N
   const int nb = d / b;
   const int splits = pick_splits(d, N, b);
   mm::Args g{};
-  g.nsrc = 1;
-  g.s[0].A = (const uint16_t*)U;
-  g.s[0].B = (const uint16_t*)V;
-  g.s[0].lda = ldu;
-  g.s[0].ldb = ldv;
-  g.s[0].ktiles = (int)(N / GBK) / splits;
+  g.s.A = (const uint16_t*)U;
+  g.s.B = (const uint16_t*)V;
+  g.s.lda = ldu;
+  g.s.ldb = ldv;
+  g.s.ktiles = (int)(N / GBK) / splits;
   g.tiles_m = b / GBM;
   g.tiles_n = b / GBN;
   g.perm = perm;
   g.rows_per_batch = b;
   const i64 total = (i64)nb * b * b;
   float* part = splits > 1 ? (float*)ws : dG;
-  // a split contracts as few as 8 stages: no redundant tail loads
-  mm::launch<GBM, GBN, 2, 4, true, true, true, 4, true>(g, EpiPartial{part, b, total}, nb, splits, st);
+  mm::launch<GBM, GBN, 2, 4, true, true, true, 4>(g, EpiPartial{part, b, total}, nb, splits, st);
   if (splits > 1)
     hipLaunchKernelGGL(reduce_partials_kernel, dim3(ceil_div(total / 4, 256)), dim3(256), 0, st, (const float4*)part,
                        (float4*)dG, total / 4, splits);

@@ -22,25 +22,6 @@ namespace {
 // stops loading after the last tile instead of re-fetching it.
 constexpr int CBM = 128, CBN = 128, CBK = 64, CNS = 4;
 
-__device__ inline float skew_at(const float* th, int i, int c, int b) {
-  if (i == c) return 0.f;
-  return i < c ? th[packed_index(i, c, b)] : -th[packed_index(c, i, b)];
-}
-
-// Q from the packed parameters: Qf = Q (fp32), Qb = bf16(Q), Tb = bf16(-Q); any may be null.
-__global__ void skew_materialize_kernel(const float* __restrict__ theta, int b, i64 total, float* __restrict__ Qf,
-                                        uint16_t* __restrict__ Qb, uint16_t* __restrict__ Tb) {
-  i64 idx = (i64)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  int c = (int)(idx % b);
-  int i = (int)((idx / b) % b);
-  i64 j = idx / ((i64)b * b);
-  float q = skew_at(theta + j * ((i64)b * (b - 1) / 2), i, c, b);
-  if (Qf) Qf[idx] = q;
-  if (Qb) Qb[idx] = float_to_bf16_bits(q);
-  if (Tb) Tb[idx] = float_to_bf16_bits(-q);
-}
-
 __global__ void to_bf16_kernel(const float4* __restrict__ in, uint2* __restrict__ out, i64 n4) {
   i64 idx = (i64)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n4) return;
@@ -61,7 +42,7 @@ struct EpiFwd {
   uint16_t* Hn;
   float* G;
   uint16_t* E;
-  __device__ void wide(int j, int, int row, int col, float4 lo, float4 hi) const {
+  __device__ void operator()(int j, int, int row, int col, float4 lo, float4 hi) const {
     const i64 o = ((i64)j * b + row) * b + col;
     const float4 c0 = *reinterpret_cast<const float4*>(C + o), c1 = *reinterpret_cast<const float4*>(C + o + 4);
     const float c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w}, a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
@@ -101,7 +82,7 @@ struct EpiAdd {
     float* f;
   } s[2];
   int b, nb;
-  __device__ void wide(int batch, int, int row, int col, float4 lo, float4 hi) const {
+  __device__ void operator()(int batch, int, int row, int col, float4 lo, float4 hi) const {
     const bool second = batch >= nb;
     const Side& d = s[second ? 1 : 0];
     const i64 o = ((i64)(second ? batch - nb : batch) * b + row) * b + col;
@@ -131,7 +112,7 @@ mm::Args batched_args(int b) {
 }
 template <class Epi>
 void launch_product(const mm::Args& g, Epi epi, int batches, hipStream_t st) {
-  mm::launch<CBM, CBN, 2, 2, true, false, false, CNS, true>(g, epi, batches, 1, st);
+  mm::launch<CBM, CBN, 2, 2, true, false, false, CNS>(g, epi, batches, 1, st);
 }
 // Blocks worked off together, of those left: 32 are two workgroups per CU, and what passes from launch to launch (5 MB a block in
 // the backward, rewritten in place by the next group) stays in the 256 MB memory-side cache; a short remainder joins the last
@@ -144,15 +125,6 @@ void set_src(mm::Source& s, const uint16_t* A, const uint16_t* B, int b) {
 }
 
 }  // namespace
-
-void skew_materialize_launch(const float* theta, int b, i64 nb, float* Qf, uint16_t* Qb, uint16_t* Tb, hipStream_t st) {
-  if (skew_tiled_supported(b, (i64)b)) {
-    skew_materialize_tiled_launch(theta, b, nb, Qf, Qb, Tb, st);
-    return;
-  }
-  const i64 total = nb * b * b;
-  hipLaunchKernelGGL(skew_materialize_kernel, dim3(ceil_div(total, 256)), dim3(256), 0, st, theta, b, total, Qf, Qb, Tb);
-}
 
 bool mfma_cnp_supported(int d, int b) { return (b == 256 || b == 512) && d % b == 0; }
 
@@ -173,18 +145,17 @@ void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void*
     uint16_t* H[2] = {Xb + total, Xb + 2 * total};
     float* G = G_f32 ? G_f32 + j0 * bb : nullptr;
     uint16_t* E = E_bf16 ? (uint16_t*)E_bf16 + 2 * j0 * bb : nullptr;
-    skew_materialize_launch(theta + j0 * (bb - b) / 2, b, nb, C, Qb, nullptr, st);
+    skew_materialize_tiled_launch(theta + j0 * (bb - b) / 2, b, nb, C, Qb, nullptr, st);
     const int pairs = k / 2;         // Horner steps in X
     mm::Args g = batched_args(b);
-    g.nsrc = 1;
-    set_src(g.s[0], Qb, Qb, b);
+      set_src(g.s, Qb, Qb, b);
     // the top pair of powers is Q alone for even k, 2Q + X for odd k (then the chain starts in this launch's epilogue)
     const bool odd = k & 1;
     launch_product(g, EpiFwd<true>{C, pairs ? Xb : nullptr, b, pairs && odd ? H[0] : nullptr, pairs ? nullptr : G, pairs ? nullptr : E}, nb, st);
     const uint16_t* cur = odd ? H[0] : Qb;
     for (int i = 1; i <= pairs; ++i) {
       const bool last = i == pairs;
-      set_src(g.s[0], Xb, cur, b);
+      set_src(g.s, Xb, cur, b);
       uint16_t* nxt = H[i & 1];
       launch_product(g, EpiFwd<false>{C, nullptr, b, last ? nullptr : nxt, last ? G : nullptr, last ? E : nullptr}, nb, st);
       cur = nxt;
@@ -202,8 +173,8 @@ void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumul
   const i64 bb = (i64)b * b, L = (bb - b) / 2;
   uint16_t* T_all = (uint16_t*)ws;                       // -Q of all blocks, the rest for a group at a time
   ws += all * bb / 2;
-  skew_materialize_launch(sides[0].theta, b, nb0, nullptr, nullptr, T_all, st);
-  if (nb1) skew_materialize_launch(sides[1].theta, b, nb1, nullptr, nullptr, T_all + nb0 * bb, st);
+  skew_materialize_tiled_launch(sides[0].theta, b, nb0, nullptr, nullptr, T_all, st);
+  if (nb1) skew_materialize_tiled_launch(sides[1].theta, b, nb1, nullptr, nullptr, T_all + nb0 * bb, st);
   for (int j0 = 0, nb; j0 < all; j0 += nb) {
     nb = group_size(all - j0);
     const i64 total = nb * bb;
@@ -218,16 +189,14 @@ void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumul
     const uint16_t* z = Db;          // Z_{m-2} in launch m
     for (int m = 1; m <= k; ++m) {   // P_m and, from m = 2, Z_{m-1}
       mm::Args g = batched_args(b);
-      g.nsrc = 1;
-      set_src(g.s[0], p, Tb, b);
+          set_src(g.s, p, Tb, b);
       EpiAdd epi{};
       epi.b = b;
       epi.nb = nb;
       epi.s[0] = {D, nullptr, m < k ? P[m & 1] : nullptr, Pf[m & 1]};
       if (m > 1) {
         g.alt_from = nb;
-        g.alt_nsrc = 1;
-        set_src(g.alt[0], Tb, z, b);
+        set_src(g.alt, Tb, z, b);
         epi.s[1] = {Pf[(m - 1) & 1], nullptr, Z[m & 1], m == k ? Pf[(m - 1) & 1] : nullptr};   // Z_{k-1} also in fp32, in P_{k-1}'s place
         z = Z[m & 1];
       }
@@ -235,8 +204,7 @@ void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumul
       p = P[m & 1];
     }
     mm::Args g = batched_args(b);
-    g.nsrc = 1;
-    set_src(g.s[0], Tb, z, b);
+      set_src(g.s, Tb, z, b);
     EpiAdd epi{};
     epi.b = b;
     epi.nb = nb;

@@ -76,17 +76,15 @@ struct Source {
   const uint16_t* B;
   i64 lda, ldb;        // row strides (elements)
   i64 sA, sB;          // batch strides (elements)
-  int ktiles;          // 64-deep k tiles taken from this source (per split)
+  int ktiles;          // 64-deep k tiles (per split)
 };
 
 struct Args {
-  Source s[2];
-  int nsrc;
+  Source s;
   // Optional second problem in the same launch: batches >= alt_from run it (with batch index
   // batch - alt_from for the operand strides; the epilogue still sees the raw batch index).
   // Same tile shape, strides and layout flags as the first; alt_from = 0 disables it.
-  Source alt[2];
-  int alt_nsrc;
+  Source alt;
   int alt_from;
   int tiles_m, tiles_n;      // output tiles per batch
   const int32_t* perm;       // GATHER: row r of batch j of both operands is memory row perm[j*rows_per_batch + r]
@@ -147,24 +145,14 @@ __device__ inline void wait_tiles_and_barrier(int tiles) {
   }
 }
 
-// An epilogue may also offer  void wide(int batch, int split, int row, int col, float4 lo, float4 hi)  for
-// eight consecutive columns col..col+7; the kernel then calls that instead (wider loads and stores).
-template <class E, class = void>
-struct has_wide : std::false_type {};
-template <class E>
-struct has_wide<E, std::void_t<decltype(&E::wide)>> : std::true_type {};
-
-// Epi: __device__ void operator()(int batch, int split, int row, int col, float4 v) -- four
-// consecutive columns col..col+3 of output row `row` (indices local to the batch).
+// Epi: __device__ void operator()(int batch, int split, int row, int col, float4 lo, float4 hi) -- eight
+// consecutive columns col..col+7 of output row `row` (indices local to the batch).
 // grid = (tiles_m * tiles_n, batches, splits).  With splits > 1 split z contracts k tiles
-// [z * ktiles, (z+1) * ktiles) of source 0.  Source::ktiles counts 64-deep tiles.
+// [z * ktiles, (z+1) * ktiles).  Source::ktiles counts 64-deep tiles.
 //
-// EXACT_TAIL = false keeps the loop free of branches: loads past the last tile re-fetch it, so
-// one fixed vmcnt bound serves every iteration (NS - 1 redundant tile loads per workgroup:
-// nothing next to a long contraction).  With EXACT_TAIL the kernel stops issuing after the last
-// tile and shrinks the bound instead -- for short contractions, where redundant loads and the
-// latency of the first tiles are a visible share of the work.
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, bool GATHER, int NS, bool EXACT_TAIL, class Epi>
+// The contractions are short (eight stages and up): the kernel stops issuing loads after the last tile and shrinks the bound of
+// the wait, as redundant loads that would keep it fixed are a visible share of the work.
+template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, bool GATHER, int NS, class Epi>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi epi) {
   using C = Cfg<BM, BN, WGM, WGN, NS>;
   constexpr int NSTAGE = NS;
@@ -208,11 +196,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi e
       if (A_KMAJOR) {
         const int r = slot >> 2, c = xk_chunk(slot & 3, r);
         const i64 row = GATHER ? (i64)pm[i0 + r] : (i64)(i0 + r);
-        offA[s] = row * g.s[0].lda + c * 8;
+        offA[s] = row * g.s.lda + c * 8;
       } else {
         constexpr int CPR = BM / 8;
         const int k = slot / CPR, c = kx_unchunk<BM>(slot % CPR, k);
-        offA[s] = (i64)k * g.s[0].lda + i0 + c * 8;
+        offA[s] = (i64)k * g.s.lda + i0 + c * 8;
       }
     }
 #pragma unroll
@@ -221,30 +209,26 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi e
       if (B_KMAJOR) {
         const int r = slot >> 2, c = xk_chunk(slot & 3, r);
         const i64 row = GATHER ? (i64)pm[j0 + r] : (i64)(j0 + r);
-        offB[s] = row * g.s[0].ldb + c * 8;
+        offB[s] = row * g.s.ldb + c * 8;
       } else {
         constexpr int CPR = BN / 8;
         const int k = slot / CPR, c = kx_unchunk<BN>(slot % CPR, k);
-        offB[s] = (i64)k * g.s[0].ldb + j0 + c * 8;
+        offB[s] = (i64)k * g.s.ldb + j0 + c * 8;
       }
     }
   }
 
   const bool use_alt = g.alt_from > 0 && batch >= g.alt_from;
-  const Source* S = use_alt ? g.alt : g.s;
-  const int nsrc = use_alt ? g.alt_nsrc : g.nsrc;
+  const Source& src = use_alt ? g.alt : g.s;
   const int bidx = use_alt ? batch - g.alt_from : batch;
-  const int kt0 = S[0].ktiles * 2;  // in BK = 32 tiles
-  const int KT = kt0 + (nsrc > 1 ? S[1].ktiles * 2 : 0);
-  const int kbase = split * kt0;
+  const int KT = src.ktiles * 2;  // in BK = 32 tiles
+  const int kbase = split * KT;
 
   // LDS byte address of the ring (wave uniform) for the direct-to-LDS loads
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
   auto issue_at = [&](int t, int ring_slot) {
-    const bool second = t >= kt0;
-    const Source& src = S[second ? 1 : 0];
-    const i64 kt = second ? (t - kt0) : (kbase + t);
+    const i64 kt = kbase + t;
     const uint16_t* Ab = src.A + (GATHER ? 0 : bidx * src.sA) + (A_KMAJOR ? kt * BK : kt * BK * src.lda);
     const uint16_t* Bb = src.B + (GATHER ? 0 : bidx * src.sB) + (B_KMAJOR ? kt * BK : kt * BK * src.ldb);
     const uint32_t stage = lds_base + ring_slot * C::STAGE_BYTES;
@@ -339,21 +323,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi e
   // same wait checks -- can be prefetched under the second half of the MFMAs.
   constexpr int LPT = C::IPW_A + C::IPW_B;  // direct-to-LDS loads per tile per wave
   static_assert(NSTAGE * LPT < 64, "vmcnt range");
-  // !EXACT_TAIL: loads past the last tile re-fetch the last tile into a free stage, which keeps
-  // the number of outstanding loads constant (no branches, one fixed vmcnt bound).
-  auto issue_clamped = [&](int t) {
-    if (EXACT_TAIL) {
-      if (t < KT) issue_at(t, t % NSTAGE);
-    } else {
-      issue_at(t < KT ? t : KT - 1, t % NSTAGE);
-    }
+  auto issue = [&](int t) {
+    if (t < KT) issue_at(t, t % NSTAGE);
   };
   // with `issued` tiles issued so far, the number of tiles younger than tile `need`
   auto younger_than = [&](int issued, int need) { return (issued < KT ? issued : KT) - 1 - need; };
 #pragma unroll
-  for (int t = 0; t < NSTAGE; ++t) issue_clamped(t);
-  if (EXACT_TAIL) wait_tiles_and_barrier<LPT, NSTAGE - 1>(younger_than(NSTAGE, 0));
-  else wait_vmcnt_and_barrier<(NSTAGE - 1) * LPT>();
+  for (int t = 0; t < NSTAGE; ++t) issue(t);
+  wait_tiles_and_barrier<LPT, NSTAGE - 1>(younger_than(NSTAGE, 0));
   Frags F, G;
   load_frags(F, 0, 0);
   for (int kt = 0; kt < KT; ++kt) {
@@ -361,9 +338,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi e
     mfma_all(F);
     interleave_hint();
     // tile kt+1 has landed and tile kt is in registers, for every wave
-    if (EXACT_TAIL) wait_tiles_and_barrier<LPT, NSTAGE - 2>(younger_than(kt + NSTAGE, kt + 1));
-    else wait_all_reads_and_barrier<(NSTAGE - 2) * LPT>();
-    issue_clamped(kt + NSTAGE);                     // into the stage of tile kt
+    wait_tiles_and_barrier<LPT, NSTAGE - 2>(younger_than(kt + NSTAGE, kt + 1));
+    issue(kt + NSTAGE);                             // into the stage of tile kt
     load_frags(F, kt + 1, 0);                       // stale but harmless after the last tile
     mfma_all(G);
     interleave_hint();
@@ -371,53 +347,37 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi e
   wait_vmcnt_and_barrier<0>();
 
   const int h = lane >> 5, li = lane & 31;
-  if constexpr (has_wide<Epi>::value) {
-    // An epilogue that takes 8 consecutive columns: register groups q and q + 1 are swapped between the
-    // lane halves (v_permlane32_swap: the upper half of its first operand against the lower half of its
-    // second), after which the lower lanes hold columns 8q .. 8q + 7 and the upper lanes 8(q+1) .. + 7.
-    typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+  // Eight consecutive columns per lane: register groups q and q + 1 are swapped between the
+  // lane halves (v_permlane32_swap: the upper half of its first operand against the lower half of its
+  // second), after which the lower lanes hold columns 8q .. 8q + 7 and the upper lanes 8(q+1) .. + 7.
+  typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 #pragma unroll
-    for (int a = 0; a < TM; ++a) {
-      const int row = i0 + wm * (BM / WGM) + a * 32 + li;
+  for (int a = 0; a < TM; ++a) {
+    const int row = i0 + wm * (BM / WGM) + a * 32 + li;
 #pragma unroll
-      for (int c = 0; c < TN; ++c) {
-        const int col = j0 + wn * (BN / WGN) + c * 32 + 8 * h;
+    for (int c = 0; c < TN; ++c) {
+      const int col = j0 + wn * (BN / WGN) + c * 32 + 8 * h;
 #pragma unroll
-        for (int q = 0; q < 4; q += 2) {
-          float lo[4], hi[4];
+      for (int q = 0; q < 4; q += 2) {
+        float lo[4], hi[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float x = acc[a][c][4 * q + e], y = acc[a][c][4 * q + 4 + e];   // scalars first: a bit cast straight from a vector element reads element 0
-            const uint2v r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
-            const unsigned r0 = r[0], r1 = r[1];
-            lo[e] = __builtin_bit_cast(float, r0);
-            hi[e] = __builtin_bit_cast(float, r1);
-          }
-          epi.wide(batch, split, row, col + 8 * q, make_float4(lo[0], lo[1], lo[2], lo[3]), make_float4(hi[0], hi[1], hi[2], hi[3]));
+        for (int e = 0; e < 4; ++e) {
+          const float x = acc[a][c][4 * q + e], y = acc[a][c][4 * q + 4 + e];   // scalars first: a bit cast straight from a vector element reads element 0
+          const uint2v r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+          const unsigned r0 = r[0], r1 = r[1];
+          lo[e] = __builtin_bit_cast(float, r0);
+          hi[e] = __builtin_bit_cast(float, r1);
         }
-      }
-    }
-  } else {
-#pragma unroll
-    for (int a = 0; a < TM; ++a) {
-      const int row = i0 + wm * (BM / WGM) + a * 32 + li;
-#pragma unroll
-      for (int c = 0; c < TN; ++c) {
-        const int col = j0 + wn * (BN / WGN) + c * 32 + 4 * h;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          epi(batch, split, row, col + 8 * q,
-              make_float4(acc[a][c][4 * q], acc[a][c][4 * q + 1], acc[a][c][4 * q + 2], acc[a][c][4 * q + 3]));
+        epi(batch, split, row, col + 8 * q, make_float4(lo[0], lo[1], lo[2], lo[3]), make_float4(hi[0], hi[1], hi[2], hi[3]));
       }
     }
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, bool GATHER, int NS = 4, bool EXACT_TAIL = (NS > 4),
-          class Epi>
+template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, bool GATHER, int NS, class Epi>
 void launch(const Args& g, Epi epi, int batches, int splits, hipStream_t st) {
   using C = Cfg<BM, BN, WGM, WGN, NS>;
-  auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, A_KMAJOR, B_KMAJOR, GATHER, NS, EXACT_TAIL, Epi>;
+  auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, A_KMAJOR, B_KMAJOR, GATHER, NS, Epi>;
   // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES) == hipSuccess;
@@ -433,18 +393,6 @@ void launch(const Args& g, Epi epi, int batches, int splits, hipStream_t st) {
   }
   hipLaunchKernelGGL(kern, dim3(g.tiles_m * g.tiles_n, batches, splits), dim3(64 * WGM * WGN), C::LDS_BYTES, st, g, epi);
 }
-
-// Plain bf16 store of the output tile.
-struct EpiStoreBf16 {
-  uint16_t* C;
-  i64 ldc, sC;
-  __device__ void operator()(int batch, int, int row, int col, float4 v) const {
-    uint2 o;
-    o.x = pack2_bf16(v.x, v.y);
-    o.y = pack2_bf16(v.z, v.w);
-    *reinterpret_cast<uint2*>(C + batch * sC + (i64)row * ldc + col) = o;
-  }
-};
 
 }  // namespace mm
 }  // namespace poetx

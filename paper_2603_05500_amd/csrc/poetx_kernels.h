@@ -142,10 +142,8 @@ void lds_cnp_bwd(const SeriesSide* sides, int nsides, int k, int accumulate, flo
 void skew_materialize_chain_launch(const float* theta0, i64 nb0, const float* theta1, i64 nb1, float* Q2, uint16_t* Qb, hipStream_t st);
 // dL/dQ of nb0 + nb1 blocks -> packed gradients of two sides (skew_tiled.hip)
 void skew_project_sides_launch(const float* M, int b, i64 nb0, float* dtheta0, i64 nb1, float* dtheta1, int accumulate, hipStream_t st);
-// Q of nb blocks from packed parameters: Qf fp32 and/or Qb bf16, [nb][b][b] (either may be null).
-// Tb = bf16(-Q).
-void skew_materialize_launch(const float* theta, int b, i64 nb, float* Qf, uint16_t* Qb, uint16_t* Tb, hipStream_t st);
-// skew_tiled.hip: the same two operations through 64 x 64 tiles (coalesced on both sides of the transpose)
+// Through 64 x 64 tiles, coalesced on both sides of the transpose (skew_tiled.hip): Q of nb blocks from packed parameters, Qf fp32, Qb bf16,
+// Tb = bf16(-Q), [nb][b][b] (any may be null); and the projection.
 bool skew_tiled_supported(int b, i64 d);
 void skew_materialize_tiled_launch(const float* theta, int b, i64 nb, float* Qf, uint16_t* Qb, uint16_t* Tb, hipStream_t st);
 void skew_project_tiled_launch(const float* M, int b, i64 nb, float* dtheta, int accumulate, hipStream_t st);

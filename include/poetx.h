@@ -93,8 +93,9 @@ typedef enum { POETX_F32 = 0, POETX_BF16 = 1 } poetx_dtype;
  * FEATURE_MAJOR ([d][N], the library's native layout: the feature permutation of Eq. 5 is then a
  * gather of whole rows, fused into the block kernels at no cost).  TOKEN_MAJOR ([N][d], what a
  * framework usually holds): every such tensor is re-laid by one transposing pass through LDS on
- * its way in or out (feature-major copies live in the workspace, which grows accordingly); all
- * values are bit for bit those of the feature-major call.  saved_B, dA and the block gradients keep
+ * its way in or out (feature-major copies live in the workspace, which grows accordingly; the
+ * forward of a few tokens reads X and writes Z in place instead); all values are bit for bit those
+ * of the feature-major call on 16-byte aligned tensors, whatever the token count.  saved_B, dA and the block gradients keep
  * their layouts in both modes. */
 typedef enum { POETX_FEATURE_MAJOR = 0, POETX_TOKEN_MAJOR = 1 } poetx_layout;
 
@@ -142,7 +143,7 @@ typedef struct {
 #define POETX_FLAG_W_INT8 2
 
 /* With POETX_FLAG_W_INT8: the dense products read the codes themselves, for bf16 layers whose
- * dimensions are multiples of 256 (other shapes and fp32 layers ignore the flag).  Code tiles and row
+ * dimensions and token counts are multiples of 256 (other shapes and fp32 layers ignore the flag).  Code tiles and row
  * scales stream into LDS and are converted to bf16(scale * q) there, two stages ahead of the
  * multiplication, so no high-precision weight is ever written to memory and the workspace is that of
  * the plain memory-saving variant -- for callers to whom one weight's worth of workspace matters more
@@ -277,7 +278,14 @@ int poetx_perm_validate(const int32_t* perm, int32_t d, int32_t* scratch, void* 
  *             dG_P^j = B'_j dZ'_j^T, dG_R^j = X'_j dA'_j^T  (primes: rows
  *             gathered by the side's permutation), then the chain rule through
  *             the series and the projection onto the packed parameters.
- * poetx_linear_workspace_bytes: scratch needed by the largest of the linear calls.
+ * poetx_linear_workspace_bytes: scratch needed by the largest of the linear calls.  Besides the
+ * activations between the stages it holds fp32 parts of products that split their contraction,
+ * and token counts that are no multiple of 256 make its activations wider: to a multiple of 8, or of
+ * 256 where the dense products of a layer with multiples of 256 gain by it (more than 64 tokens and
+ * d_in * d_out * padded tokens >= 2^30).  In MB: 2048 x 5632 with 1999 tokens 115 (85 without parts
+ * and padding), 8192 x 3072 with 4090 token-major tokens 268 (235), 4096 x 14336 with 70 tokens 158
+ * (153), fp32 1024 x 768 with 1001 tokens 15.5 (7.2).  Large whole token counts have neither:
+ * 14336 x 4096 with 16384 tokens 789.
  */
 size_t poetx_linear_workspace_bytes(const poetx_linear_desc* desc);
 
@@ -331,8 +339,9 @@ int poetx_linear_bwd_skew(const poetx_linear_desc* desc, const void* X, const vo
 
 /* The whole backward pass in one call (Sec. 3.5, all three bullets, then Sec. 3.4 backward): the
  * results of poetx_linear_bwd_input followed by poetx_linear_bwd_skew, with dA kept in the workspace.
- * Where the shapes allow (bf16, b = 256, d_in, d_out multiples of 256, n_tokens a multiple of 256) each
- * side's gradient is streamed from memory once: dB = P dZ is produced together with
+ * Where the shapes allow (bf16, b = 256, d_in, d_out multiples of 256, n_tokens a multiple of 256, or of
+ * 64 from 256 on in layers whose token count is not padded) each side's gradient is streamed from
+ * memory once: dB = P dZ is produced together with
  * dG_P^j = B'_j dZ'_j^T, and dX = R dA together with dG_R^j = X'_j dA'_j^T, instead of one pass
  * for the product and another for the block gradient.  Otherwise it runs the two halves as they are.
  * The block gradients are summed over token ranges in a fixed order, so results are reproducible

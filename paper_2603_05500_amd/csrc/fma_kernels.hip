@@ -1,8 +1,8 @@
 // Plain fp32-FMA kernels for every step of the POET-X linear hot path.
 //
-// This path serves the series of fp32 tensors (where the 1e-4 tolerance rules out bf16
-// matrix-core products) and of small blocks, poetx_perm_blockdiag_apply_right, and -- under
-// poetx_debug_force_fma -- every other step, as an independent second implementation to
+// This path serves the series of blocks wider than 128 that the bf16 matrix-core series does not take
+// (fp32 precision, where the 1e-4 tolerance rules out bf16 products; other block sides; ragged tails),
+// poetx_perm_blockdiag_apply_right, and -- under poetx_debug_force_fma -- every other step, as an independent second implementation to
 // compare the matrix-core kernels with.  Every step is one instance of a small LDS-tiled batched product
 //     C[batch](i, j) = sum_k A[batch](i, k) * B[batch](k, j)
 // whose operands are described by accessor structs, so gather-by-permutation,

@@ -328,7 +328,7 @@ def test_fp32_layer_dense_on_matrix_cores(lib, m, n, N, b, k, streams):
 @pytest.mark.parametrize("N", [64, 128, 192, 320, 384, 576])
 def test_kernel_family_boundaries(lib, N):
     """Token counts around the tile sizes of the matrix-core kernels (128-token apply tiles, 256-token
-    dense tiles, 64-token reduction tiles): each stage falls back to the plain kernels on its own
+    dense tiles, 64-token reduction tiles): each stage goes to the edge-handling kernels on its own
     when its tiling does not fit, so every mix of the two families must still match the oracle."""
     m, n, b, k = 512, 256, 256, 2
     data = synth_layer(7400 + N, m, n, N, b, k, "bf16", 0.005)

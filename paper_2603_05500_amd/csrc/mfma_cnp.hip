@@ -2,15 +2,21 @@
 // batched over the blocks of one side, for block sides that do not fit on chip (b = 512).
 //
 // Every b x b product runs as bf16 x bf16 -> fp32 on the batched tile kernel; the dominant terms enter in fp32 in its
-// epilogue.  A launch costs 25 us or so however small (512-deep contraction, fill, drain, epilogue), so the
-// recurrences are chosen for few products and fewer launches:
-//   forward    X = Q^2, then Horner's rule in X on the pairs of powers,
+// epilogue.  A launch costs 20 us or so however small (512-deep contraction, fill, drain, epilogue), so the
+// recurrences are chosen for few launches, and for little fp32 traffic between them: from 32 blocks on a launch fills the chip
+// and its epilogue's memory accesses are a third of its time.
+//   forward    k >= 3: X = Q^2, then Horner's rule in X on the pairs of powers,
 //              G - I = sum_i X^i (c_{2i+1} Q + c_{2i+2} X),  c_p = 2 for p <= k, 1 for p = k + 1:
-//              1 + floor(k/2) products (k by Horner's rule in Q)
+//              1 + floor(k/2) products; k <= 2: Horner's rule in Q, as many products without X
 //   backward   P_0 = D = dL/dG,  P_m = D + P_{m-1} T,  Z_0 = D,  Z_m = P_m + T Z_{m-1},  dL/dQ = Z_k + Z_{k-1}
-//              with T = Q^T = -Q (see mfma_cnp_lds.hip); P_m and Z_{m-1} share a launch: 2k products in k + 1 launches
-//              (3k - 1 products by the two-sided Horner rule)
-// Against 64 bits both round less than the Horner forms (b = 512, k = 5: 3.8e-4 -> 3.5e-4 of the gradient, 2.67e-4 -> 2.66e-4
+//              with T = Q^T = -Q (see mfma_cnp_lds.hip).  Launch m makes P_m and Z_m = D + P_{m-1} T + T Z_{m-1}, the
+//              latter as one contraction over two operand pairs, so that P_m is only ever written as the bf16 operand of the next
+//              launch: 3k - 1 products in k launches.  Adding an fp32 P_m in Z_m's epilogue instead saves k products and
+//              loses by its traffic (and a launch) except for a few blocks of the first orders.  us per backward,
+//              that / this / the two-sided Horner rule on 256 x 256 tiles: k = 3: 16 blocks 102 / 91 / 139,
+//              40: 226 / 204 / 203, 48: 272 / 241 / 242, 160: 900 / 808 / 854; k = 5: 16: 147 / 133 / 214, 32: 254 / 242 / 245,
+//              48: 400 / 364 / 374, 64: 515 / 465 / 512, 160: 1315 / 1200 / 1346.
+// Against 64 bits the recurrences round less than the Horner forms (b = 512, k = 5: 3.8e-4 -> 3.5e-4 of the gradient, 2.67e-4 -> 2.66e-4
 // of G - I before its own rounding).
 #include "mfma_gemm.h"
 
@@ -103,23 +109,23 @@ struct EpiAdd {
 };
 
 // 128 x 128 tiles: 256 x 256 ones have four times the work per workgroup for the same fill and drain, but leave most of the
-// chip idle below 128 blocks (build + backward of 16 blocks, k = 5, by Horner's rule: 354 against 210 us).
+// chip idle below 128 blocks (build + backward of 16 blocks, k = 5: 327 against 191 us; 64 blocks: 650 against 634).
 mm::Args batched_args(int b) {
   mm::Args g{};
   g.tiles_m = b / CBM;
   g.tiles_n = b / CBN;
   return g;
 }
-template <class Epi>
+template <bool PAIR, class Epi>
 void launch_product(const mm::Args& g, Epi epi, int batches, hipStream_t st) {
-  mm::launch<CBM, CBN, 2, 2, true, false, false, CNS>(g, epi, batches, 1, st);
+  mm::launch<CBM, CBN, 2, 2, true, false, false, CNS, PAIR>(g, epi, batches, 1, st);
 }
-// Blocks worked off together, of those left: 32 are two workgroups per CU, and what passes from launch to launch (5 MB a block in
-// the backward, rewritten in place by the next group) stays in the 256 MB memory-side cache; a short remainder joins the last
-// group, as a launch of its own costs the same however few its blocks (up to 40 still fit the cache).  All but the last group are
-// a multiple of 8, which keeps the tiles of a block on one XCD.  Build + backward at k = 5, all at once / equal groups of
-// at most 32 / this, us: 35 blocks 418 / 517 / 418, 47: 549 / 573 / 544, 66: - / 856 / 803, 80: 999 / 961 / 886, 160: 2241 / 1734 / 1739.
-inline int group_size(int left) { return left <= 40 ? left : 32; }
+// Blocks worked off together, of those left: what passes from launch to launch (4 MB a block in the backward, rewritten in place by
+// the next group) stays largely in the 256 MB memory-side cache; a short remainder joins the last group, as a launch of its own
+// costs the same however few its blocks.  All but the last group are a multiple of 8, which keeps the tiles of a block on one
+// XCD.  Build + backward at k = 5, us, groups of 32 (last up to 40) / 64 (last up to 80) / all at once:
+// 48 blocks 515 / 493 / -, 64: 663 / 634 / -, 80: 858 / 848 / -, 96: 1009 / 995 / 1082, 160: 1709 / 1631 / 1980.
+inline int group_size(int left) { return left <= 80 ? left : 64; }
 void set_src(mm::Source& s, const uint16_t* A, const uint16_t* B, int b) {
   s.A = A; s.B = B; s.lda = b; s.ldb = b; s.sA = (i64)b * b; s.sB = (i64)b * b; s.ktiles = b / CBK;
 }
@@ -146,18 +152,27 @@ void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void*
     float* G = G_f32 ? G_f32 + j0 * bb : nullptr;
     uint16_t* E = E_bf16 ? (uint16_t*)E_bf16 + 2 * j0 * bb : nullptr;
     skew_materialize_tiled_launch(theta + j0 * (bb - b) / 2, b, nb, C, Qb, nullptr, st);
-    const int pairs = k / 2;         // Horner steps in X
     mm::Args g = batched_args(b);
+    if (k <= 2) {                    // H = Q Q + 2Q (k = 1: that is it), H Q + 2Q
       set_src(g.s, Qb, Qb, b);
+      if (k == 2) {
+        launch_product<false>(g, EpiFwd<true>{C, nullptr, b, H[0], nullptr, nullptr}, nb, st);
+        set_src(g.s, H[0], Qb, b);
+      }
+      launch_product<false>(g, EpiFwd<true>{C, nullptr, b, nullptr, G, E}, nb, st);
+      continue;
+    }
     // the top pair of powers is Q alone for even k, 2Q + X for odd k (then the chain starts in this launch's epilogue)
+    const int pairs = k / 2;         // Horner steps in X
     const bool odd = k & 1;
-    launch_product(g, EpiFwd<true>{C, pairs ? Xb : nullptr, b, pairs && odd ? H[0] : nullptr, pairs ? nullptr : G, pairs ? nullptr : E}, nb, st);
+    set_src(g.s, Qb, Qb, b);
+    launch_product<false>(g, EpiFwd<true>{C, Xb, b, odd ? H[0] : nullptr, nullptr, nullptr}, nb, st);
     const uint16_t* cur = odd ? H[0] : Qb;
     for (int i = 1; i <= pairs; ++i) {
       const bool last = i == pairs;
       set_src(g.s, Xb, cur, b);
       uint16_t* nxt = H[i & 1];
-      launch_product(g, EpiFwd<false>{C, nullptr, b, last ? nullptr : nxt, last ? G : nullptr, last ? E : nullptr}, nb, st);
+      launch_product<false>(g, EpiFwd<false>{C, nullptr, b, last ? nullptr : nxt, last ? G : nullptr, last ? E : nullptr}, nb, st);
       cur = nxt;
     }
   }
@@ -180,39 +195,32 @@ void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumul
     const i64 total = nb * bb;
     const float* D = sides[0].dG + j0 * bb;
     const uint16_t* Tb = T_all + j0 * bb;
-    float* Pf[2] = {ws, ws + total};
-    uint16_t* Db = (uint16_t*)(ws + 2 * total);
+    float* Zf = ws;                  // Z_{k-1}, then dL/dQ
+    uint16_t* Db = (uint16_t*)(ws + total);
     uint16_t* P[2] = {Db + total, Db + 2 * total};
     uint16_t* Z[2] = {Db + 3 * total, Db + 4 * total};
     hipLaunchKernelGGL(to_bf16_kernel, dim3(ceil_div(total / 4, 256)), dim3(256), 0, st, (const float4*)D, (uint2*)Db, total / 4);
-    const uint16_t* p = Db;          // P_{m-1}
-    const uint16_t* z = Db;          // Z_{m-2} in launch m
-    for (int m = 1; m <= k; ++m) {   // P_m and, from m = 2, Z_{m-1}
+    const uint16_t *p = Db, *z = Db;
+    for (int m = 1; m <= k; ++m) {
+      const bool last = m == k;
       mm::Args g = batched_args(b);
-          set_src(g.s, p, Tb, b);
+      set_src(g.s, p, Tb, b);        // Z_m
+      set_src(g.s2, Tb, z, b);
       EpiAdd epi{};
       epi.b = b;
       epi.nb = nb;
-      epi.s[0] = {D, nullptr, m < k ? P[m & 1] : nullptr, Pf[m & 1]};
-      if (m > 1) {
+      epi.s[0] = {D, !last ? nullptr : k > 1 ? Zf : D, last ? nullptr : Z[m & 1], m >= k - 1 ? Zf : nullptr};
+      if (!last) {                   // P_m
         g.alt_from = nb;
-        set_src(g.alt, Tb, z, b);
-        epi.s[1] = {Pf[(m - 1) & 1], nullptr, Z[m & 1], m == k ? Pf[(m - 1) & 1] : nullptr};   // Z_{k-1} also in fp32, in P_{k-1}'s place
-        z = Z[m & 1];
+        set_src(g.alt, p, Tb, b);
+        epi.s[1] = {D, nullptr, P[m & 1], nullptr};
       }
-      launch_product(g, epi, m > 1 ? 2 * nb : nb, st);
+      launch_product<true>(g, epi, last ? nb : 2 * nb, st);
       p = P[m & 1];
+      z = Z[m & 1];
     }
-    mm::Args g = batched_args(b);
-      set_src(g.s, Tb, z, b);
-    EpiAdd epi{};
-    epi.b = b;
-    epi.nb = nb;
-    float* dQ = Pf[(k - 1) & 1];
-    epi.s[0] = {Pf[k & 1], k > 1 ? dQ : D, nullptr, dQ};                                       // Z_k + Z_{k-1}
-    launch_product(g, epi, nb, st);
     const int n0 = nb0 - j0 < 0 ? 0 : nb0 - j0 < nb ? nb0 - j0 : nb, j1 = j0 + n0 - nb0;       // of the group: blocks of the first side, first block of the second
-    skew_project_sides_launch(dQ, b, n0, sides[0].dtheta + j0 * L, nb - n0, nb > n0 ? sides[1].dtheta + j1 * L : nullptr, accumulate, st);
+    skew_project_sides_launch(Zf, b, n0, sides[0].dtheta + j0 * L, nb - n0, nb > n0 ? sides[1].dtheta + j1 * L : nullptr, accumulate, st);
   }
 }
 

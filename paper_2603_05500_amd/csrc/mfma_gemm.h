@@ -81,6 +81,7 @@ struct Source {
 
 struct Args {
   Source s;
+  Source s2;           // PAIR: a second operand pair, contracted after the first into the same sum (strides of the first); not of `alt`
   // Optional second problem in the same launch: batches >= alt_from run it (with batch index
   // batch - alt_from for the operand strides; the epilogue still sees the raw batch index).
   // Same tile shape, strides and layout flags as the first; alt_from = 0 disables it.
@@ -148,11 +149,11 @@ __device__ inline void wait_tiles_and_barrier(int tiles) {
 // Epi: __device__ void operator()(int batch, int split, int row, int col, float4 lo, float4 hi) -- eight
 // consecutive columns col..col+7 of output row `row` (indices local to the batch).
 // grid = (tiles_m * tiles_n, batches, splits).  With splits > 1 split z contracts k tiles
-// [z * ktiles, (z+1) * ktiles).  Source::ktiles counts 64-deep tiles.
+// [z * ktiles, (z+1) * ktiles) of the first operand pair.  Source::ktiles counts 64-deep tiles.
 //
 // The contractions are short (eight stages and up): the kernel stops issuing loads after the last tile and shrinks the bound of
 // the wait, as redundant loads that would keep it fixed are a visible share of the work.
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, bool GATHER, int NS, class Epi>
+template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, bool GATHER, int NS, bool PAIR, class Epi>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi epi) {
   using C = Cfg<BM, BN, WGM, WGN, NS>;
   constexpr int NSTAGE = NS;
@@ -219,16 +220,19 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi e
   }
 
   const bool use_alt = g.alt_from > 0 && batch >= g.alt_from;
-  const Source& src = use_alt ? g.alt : g.s;
+  const Source& S = use_alt ? g.alt : g.s;
   const int bidx = use_alt ? batch - g.alt_from : batch;
-  const int KT = src.ktiles * 2;  // in BK = 32 tiles
-  const int kbase = split * KT;
+  const int kt0 = S.ktiles * 2;  // in BK = 32 tiles
+  const int KT = PAIR && !use_alt ? kt0 + g.s2.ktiles * 2 : kt0;
+  const int kbase = split * kt0;
 
   // LDS byte address of the ring (wave uniform) for the direct-to-LDS loads
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
   auto issue_at = [&](int t, int ring_slot) {
-    const i64 kt = kbase + t;
+    const bool second = PAIR && t >= kt0;
+    const Source& src = second ? g.s2 : S;
+    const i64 kt = second ? (t - kt0) : (kbase + t);
     const uint16_t* Ab = src.A + (GATHER ? 0 : bidx * src.sA) + (A_KMAJOR ? kt * BK : kt * BK * src.lda);
     const uint16_t* Bb = src.B + (GATHER ? 0 : bidx * src.sB) + (B_KMAJOR ? kt * BK : kt * BK * src.ldb);
     const uint32_t stage = lds_base + ring_slot * C::STAGE_BYTES;
@@ -374,10 +378,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(Args g, Epi e
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, bool GATHER, int NS, class Epi>
+template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, bool GATHER, int NS, bool PAIR, class Epi>
 void launch(const Args& g, Epi epi, int batches, int splits, hipStream_t st) {
   using C = Cfg<BM, BN, WGM, WGN, NS>;
-  auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, A_KMAJOR, B_KMAJOR, GATHER, NS, Epi>;
+  auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, A_KMAJOR, B_KMAJOR, GATHER, NS, PAIR, Epi>;
   // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES) == hipSuccess;

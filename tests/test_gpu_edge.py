@@ -393,9 +393,9 @@ def test_block_counts_beyond_one_grid_dimension(lib):
 
 
 @pytest.mark.parametrize("b,nbR,nbP", [
-    (512, 32, 12),      # groups 32 + 12: the P side ends inside the first group, the R side goes on in the second
-    (512, 8, 36),       # the P side ends inside the second group
-    (512, 12, 32),      # exactly at the boundary
+    (512, 60, 30),      # groups 64 + 26: the P side ends inside the first group, the R side goes on in the second
+    (512, 16, 70),      # the P side ends inside the second group
+    (512, 20, 64),      # exactly at the boundary
     (256, 100, 60),     # groups 128 + 32: the boundary inside the first
     (256, 20, 140),     # inside the second
 ])

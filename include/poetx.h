@@ -55,7 +55,8 @@
  *    such blocks and multiples of 64 tokens, from 256 on.  fp32 tensors, streaming kernel:
  *    a dense product whose three dimensions are multiples of 128 with at least 192 output
  *    tiles of 128 x 128.  The dense products, applies and block gradients of everything else
- *    run on an edge-handling matrix-core product of the tensors' type.  Series: precision
+ *    run on an edge-handling matrix-core product of the tensors' type (applies of blocks up to
+ *    b = 16 over many tokens on the plain fp32-FMA kernel).  Series: precision
  *    POETX_CNP_BF16 with b = 256 or 512 dividing the dimension on bf16 matrix instructions;
  *    blocks up to b = 128 on fp32 ones whatever the precision, one launch per direction; all
  *    others, and poetx_perm_blockdiag_apply_right, on plain fp32-FMA kernels.

@@ -2,7 +2,7 @@
 //
 // This path serves the series of blocks wider than 128 that the bf16 matrix-core series does not take
 // (fp32 precision, where the 1e-4 tolerance rules out bf16 products; other block sides; ragged tails),
-// poetx_perm_blockdiag_apply_right, and -- under poetx_debug_force_fma -- every other step, as an independent second implementation to
+// applies of very small blocks over many tokens, poetx_perm_blockdiag_apply_right, and -- under poetx_debug_force_fma -- every other step, as an independent second implementation to
 // compare the matrix-core kernels with.  Every step is one instance of a small LDS-tiled batched product
 //     C[batch](i, j) = sum_k A[batch](i, k) * B[batch](k, j)
 // whose operands are described by accessor structs, so gather-by-permutation,
@@ -138,12 +138,12 @@ struct BlockOpB {
   }
 };
 template <class T>
-struct GatherRowsB {  // B(l, c) = V[perm[j*b + l]][c]
-  const T* V; i64 ld; const int32_t* perm; int b; int d;
+struct GatherRowsB {  // B(l, c) = V[perm[j*b + l]][c], zero past V's columns
+  const T* V; i64 ld; const int32_t* perm; int b; int d; int cols;
   static constexpr bool k_fast = false;
   __device__ float operator()(int j, int l, int c) const {
     int row = j * b + l;
-    if (row >= d) return 0.f;
+    if (row >= d || c >= cols) return 0.f;
     return to_float(V[(i64)perm[row] * ld + c]);
   }
 };
@@ -283,13 +283,13 @@ __global__ void perm_mark_kernel(const int32_t* perm, int d, int32_t* scratch) {
 }
 
 template <class T, bool RES>
-void apply_left_t(const T* V, T* out, int d, i64 cols, i64 ld, const int32_t* perm, const T* blocks, int b,
-                  int trans, hipStream_t st) {
+void apply_left_t(const T* V, i64 ldv, i64 cols, T* out, i64 ldo, i64 cols_out, int d, const int32_t* perm, const T* blocks, int b, int trans,
+                  hipStream_t st) {
   int nb = ceil_div(d, b);
-  GatherRowsB<T> fb{V, ld, perm, b, d};
-  ScatterRowsC<T> fc{out, ld, perm, b, d};
-  if (trans) launch_gemm(nb, b, cols, b, BlockOpA<T, true, RES>{blocks, b, d}, fb, fc, st);
-  else launch_gemm(nb, b, cols, b, BlockOpA<T, false, RES>{blocks, b, d}, fb, fc, st);
+  GatherRowsB<T> fb{V, ldv, perm, b, d, (int)cols};
+  ScatterRowsC<T> fc{out, ldo, perm, b, d};
+  if (trans) launch_gemm(nb, b, cols_out, b, BlockOpA<T, true, RES>{blocks, b, d}, fb, fc, st);
+  else launch_gemm(nb, b, cols_out, b, BlockOpA<T, false, RES>{blocks, b, d}, fb, fc, st);
 }
 template <class T, bool RES>
 void apply_right_t(const T* V, T* out, i64 rows, int d, i64 ld, const int32_t* perm, const T* blocks, int b,
@@ -316,12 +316,21 @@ void fma_dense(int dtype, int trans_w, const void* W, int n, int m, const void* 
   else dense_t<bf16_t>(trans_w, (const bf16_t*)W, n, m, (const bf16_t*)act, (bf16_t*)out, N, st);
 }
 
-void fma_apply_left(int dtype, const void* V, void* out, int d, i64 cols, i64 ld, const int32_t* perm,
-                    const void* blocks, int b, int transpose_G, hipStream_t st) {
+// Every product pads its blocks to 64 rows and 16 of contraction, the edge kernel to 32 rows and a whole stage (64 or 128): for blocks
+// up to 16 the padding is what bounds either, and it is less here (8192 features, 4096 tokens, plain / edge, us: b = 16 fp32 143 / 203,
+// bf16 118 / 161; b = 8: 192 / 392, 181 / 315; b = 2: 498 / 1527, 510 / 1297; b = 24: 150 / 151, 132 / 129) -- where there are
+// enough tiles of 32 tokens to fill the chip several times; with 2048 of them (512 x 1000, b = 8) both take no longer than their launch.
+bool fma_apply_left_preferred(int d, i64 cols, int b) {
+  const i64 nb = ceil_div(d, b);
+  return b <= 16 && nb * ((cols + 31) / 32) >= 4096 && nb < 65536 && cols < (1 << 29);   // the grid's limits
+}
+
+void fma_apply_left(int dtype, const void* V, i64 ldv, i64 cols, void* out, i64 ldo, i64 cols_out, int d, const int32_t* perm, const void* blocks,
+                    int b, int transpose_G, hipStream_t st) {
   if (dtype == POETX_F32)
-    apply_left_t<float, false>((const float*)V, (float*)out, d, cols, ld, perm, (const float*)blocks, b, transpose_G, st);
+    apply_left_t<float, false>((const float*)V, ldv, cols, (float*)out, ldo, cols_out, d, perm, (const float*)blocks, b, transpose_G, st);
   else
-    apply_left_t<bf16_t, true>((const bf16_t*)V, (bf16_t*)out, d, cols, ld, perm, (const bf16_t*)blocks, b, transpose_G, st);
+    apply_left_t<bf16_t, true>((const bf16_t*)V, ldv, cols, (bf16_t*)out, ldo, cols_out, d, perm, (const bf16_t*)blocks, b, transpose_G, st);
 }
 
 void fma_apply_right(int dtype, const void* V, void* out, i64 rows, int d, i64 ld, const int32_t* perm,

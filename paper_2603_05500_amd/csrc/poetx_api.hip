@@ -90,7 +90,7 @@ inline i64 min64(i64 a, i64 b) { return a < b ? a : b; }
 
 // Which kernels run an apply is decided before the tensors of a call are looked at (apply_streams below): in one pass some
 // of them have padded columns and some do not, in another layout others, and the results are the same bit for bit.
-// streams: the streaming kernels, whole tiles or not.  plan_cols: columns that the edge kernel's tile is chosen for.
+// streams: the streaming kernels, whole tiles or not.  plan_cols: columns that the choice between the others, and their tile, is made for.
 void apply_left_dispatch(int dtype, const Act& V, const Act& out, int d, const int32_t* perm, const void* blocks, int b, int trans, bool streams,
                          i64 plan_cols, hipStream_t st) {
   StageTimer tm(POETX_STAGE_APPLY, st);
@@ -99,10 +99,10 @@ void apply_left_dispatch(int dtype, const Act& V, const Act& out, int d, const i
       mfma_apply_left(V.p, out.out(), d, V.cols, V.ld, perm, blocks, b, trans, st);
     else
       mfma_apply_left_ragged(V.p, V.ld, min64(V.cols, out.cols), out.out(), out.ld, out.cols, d, perm, blocks, b, trans, st);
-  } else if (!g_force_fma.load()) {
+  } else if (!g_force_fma.load() && !fma_apply_left_preferred(d, plan_cols, b)) {
     edge_apply_left(dtype, V.p, V.ld, out.out(), out.ld, d, min64(V.cols, out.cols), out.cols, plan_cols, perm, blocks, b, trans, st);
   } else {
-    fma_apply_left(dtype, V.p, out.out(), d, V.cols, V.ld, perm, blocks, b, trans, st);
+    fma_apply_left(dtype, V.p, V.ld, min64(V.cols, out.cols), out.out(), out.ld, out.cols, d, perm, blocks, b, trans, st);
   }
 }
 // an apply on its own: V and out of one shape
@@ -178,7 +178,8 @@ bool reads_tokens_in_place(const poetx_linear_desc* d) {
   const i64 N = d->n_tokens;
   if (d->dtype == POETX_BF16 && N % 64 == 0) return false;
   if (use_mfma(d->dtype) && (apply_streams(d, d->d_in) || apply_streams(d, d->d_out))) return false;
-  // the same kernel tile as feature-major calls take: results are the same bit for bit in either layout
+  // the same kernel and tile as feature-major calls take: results are the same bit for bit in either layout
+  if (fma_apply_left_preferred(d->d_in, N, d->block) || fma_apply_left_preferred(d->d_out, N, d->block)) return false;
   if (!edge_apply_smallest_tile(d->d_in, N, d->block) || !edge_apply_smallest_tile(d->d_out, N, d->block)) return false;
   return (double)(d->d_in + (i64)d->d_out) * N * d->block <= (d->block <= 256 ? 1 << 25 : 1 << 24);
 }

@@ -21,8 +21,11 @@ class StageTimer {
 // trans_w == 1: out (m x N) = W^T act (n x N).
 void fma_dense(int dtype, int trans_w, const void* W, int n, int m, const void* act, void* out,
                i64 N, hipStream_t st);
-void fma_apply_left(int dtype, const void* V, void* out, int d, i64 cols, i64 ld, const int32_t* perm,
-                    const void* blocks, int b, int transpose_G, hipStream_t st);
+// V: d x cols, out: d x cols_out (the columns past cols are written as zeros)
+void fma_apply_left(int dtype, const void* V, i64 ldv, i64 cols, void* out, i64 ldo, i64 cols_out, int d, const int32_t* perm, const void* blocks,
+                    int b, int transpose_G, hipStream_t st);
+// is that faster than the edge kernel?
+bool fma_apply_left_preferred(int d, i64 cols, int b);
 void fma_apply_right(int dtype, const void* V, void* out, i64 rows, int d, i64 ld, const int32_t* perm,
                      const void* blocks, int b, int transpose_G, hipStream_t st);
 // dG[j] = U'_j V'_j^T with rows of U and V (d x N each) gathered by perm; dG is [nb][b][b] float.

@@ -34,7 +34,8 @@ def test_layer_at_tile_edges(lib, m, n, N, b, k, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("d,b,cols,off", [(64, 32, 96, 1), (256, 256, 256, 1), (320, 64, 40, 3)])
+@pytest.mark.parametrize("d,b,cols,off", [(64, 32, 96, 1), (256, 256, 256, 1), (320, 64, 40, 3),
+                                          (1032, 8, 1021, 1), (2048, 16, 1021, 3)])   # blocks up to 16, 4128 and 4096 tiles: plain kernel
 def test_apply_off_alignment(lib, d, b, cols, off, dtype):
     """Input, output and blocks that start `off` elements into an allocation: element alignment is enough, and
     nothing outside the output is written."""
@@ -198,6 +199,9 @@ RAGGED_LAYERS = [
     (512, 768, 255, 64, "bf16"),        # small blocks: the contraction of the block gradients rounds up to a longer one
     (512, 768, 255, 64, "f32"),
     (1024, 768, 250, 192, "bf16"),      # neither small nor a streaming block side
+    (520, 512, 2045, 8, "bf16"),        # applies of very small blocks on the plain kernel ...
+    (520, 512, 2045, 8, "f32"),
+    (1056, 768, 2001, 16, "bf16"),      # ... on one side only
     # layers that are padded to whole 256-token tiles
     (2048, 2048, 100, 256, "bf16"),     # fewer tokens than a tile
     (2048, 2304, 192, 256, "bf16"),     # a multiple of the 64-token tiles

@@ -116,16 +116,18 @@ bool dense_f32_streams(int n, int m, int M, i64 N) { return mfma_dense_f32_suppo
 
 // part: scratch of dense_part_bytes() for products that split their contraction.
 // w_q8: W is a quantised weight buffer that the product dequantises itself (see weight_in_kernel)
-void dense_dispatch(int dtype, int trans_w, const void* W, int n, int m, const Act& act, const Act& out, void* part, hipStream_t st,
-                    bool w_q8 = false) {
+// As with the applies the kernel follows from the descriptor: the plan from the activation operand, which is always a workspace
+// one, the fp32 kernel from the call's own tokens (whole tiles of those leave no tensor padded).
+void dense_dispatch(const poetx_linear_desc* desc, int trans_w, const void* W, const Act& act, const Act& out, void* part, hipStream_t st,
+                    bool w_q8) {
   StageTimer tm(POETX_STAGE_DENSE, st);
+  const int dtype = desc->dtype, n = desc->d_out, m = desc->d_in;
   const i64 N = min64(act.cols, out.cols);
-  const bool whole = act.ld == act.cols && out.ld == out.cols && act.cols == out.cols;
   if (w_q8) mfma_dense_q8(trans_w, W, n, m, act.p, out.out(), N, part, st);
   else if (use_mfma(dtype) && act.ld == act.cols && mfma_dense_supported(n, m, act.cols) && aligned16(W) && aligned16(act.p))
     mfma_dense(trans_w, W, n, m, act.p, act.cols, out.out(), out.ld, N, part, st);
-  else if (dtype == POETX_F32 && !g_force_fma.load() && whole && dense_f32_streams(n, m, trans_w ? m : n, N) &&
-           aligned16(W) && aligned16(act.p) && aligned16(out.p))
+  else if (dtype == POETX_F32 && !g_force_fma.load() && dense_f32_streams(n, m, trans_w ? m : n, desc->n_tokens) && aligned16(W) && aligned16(act.p) &&
+           aligned16(out.p))
     mfma_dense_f32(trans_w, W, n, m, act.p, out.out(), N, st);
   else if (!g_force_fma.load()) edge_dense(dtype, trans_w, W, n, m, act.p, act.ld, act.cols, out.out(), out.ld, N, part, st);
   else fma_dense(dtype, trans_w, W, n, m, act.p, out.out(), N, st);
@@ -550,7 +552,7 @@ int poetx_linear_fwd(const poetx_linear_desc* desc, const void* X, const void* W
       StageTimer tm(POETX_STAGE_APPLY, st);
       edge_apply_tokens(dt, X, m, true, A.out(), Ni, false, m, N, Ni, perm_R, blocks_R, b, 1, st);
     }
-    dense_dispatch(dt, 0, W, n, m, A, B, part, st, weight_in_kernel(desc));
+    dense_dispatch(desc, 0, W, A, B, part, st, weight_in_kernel(desc));
     StageTimer tm(POETX_STAGE_APPLY, st);
     edge_apply_tokens(dt, B.p, B.ld, false, Z, n, true, n, N, N, perm_P, blocks_P, b, 1, st);
     return launch_status();
@@ -558,7 +560,7 @@ int poetx_linear_fwd(const poetx_linear_desc* desc, const void* X, const void* W
   LayoutStaging lay(desc, ws, st);
   const Act x = lay.in(X, m), z = lay.out(Z, n);
   apply_left(desc, x, A, m, perm_R, blocks_R, 1, st);              // mm1: A = R^T X
-  dense_dispatch(dt, 0, W, n, m, A, B, part, st, weight_in_kernel(desc));    // mm2: B = W A
+  dense_dispatch(desc, 0, W, A, B, part, st, weight_in_kernel(desc));    // mm2: B = W A
   apply_left(desc, B, z, n, perm_P, blocks_P, 1, st);              // mm3: Z = P^T B
   lay.finish();
   return launch_status();
@@ -571,14 +573,14 @@ int poetx_linear_recompute_b(const poetx_linear_desc* desc, const void* X, const
   if (!X || !W || !perm_R || !blocks_R || !B_out) return POETX_ERR_INVALID_ARG;
   if (!ws || ws_bytes < poetx_linear_workspace_bytes(desc)) return POETX_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  const int m = desc->d_in, n = desc->d_out, dt = desc->dtype;
+  const int m = desc->d_in;
   const i64 N = desc->n_tokens, Ni = internal_columns(desc);
   LayoutStaging lay(desc, ws, st);
   const Act x = lay.in(X, m), A{ws, Ni, Ni};
   char* after = (char*)ws + act_bytes(desc, m);
   W = resolve_weight(desc, W, after, st);
   apply_left(desc, x, A, m, perm_R, blocks_R, 1, st);  // A = R^T X
-  dense_dispatch(dt, 0, W, n, m, A, Act{B_out, N, N}, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // B = W A
+  dense_dispatch(desc, 0, W, A, Act{B_out, N, N}, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // B = W A
   return launch_status();
 }
 
@@ -586,13 +588,13 @@ int poetx_linear_recompute_b(const poetx_linear_desc* desc, const void* X, const
 static void bwd_input_impl(const poetx_linear_desc* desc, const Act& dZ, const void* W, const int32_t* perm_R,
                            const int32_t* perm_P, const void* blocks_R, const void* blocks_P, const Act& dX, const Act& dA,
                            void* ws, hipStream_t st, const void* W_resolved = nullptr) {
-  const int m = desc->d_in, n = desc->d_out, dt = desc->dtype;
+  const int m = desc->d_in, n = desc->d_out;
   const i64 Ni = internal_columns(desc);
   const Act dB{ws, Ni, Ni};
   char* after = (char*)ws + act_bytes(desc, n);
   W = W_resolved ? W_resolved : resolve_weight(desc, W, after, st);
   apply_left(desc, dZ, dB, n, perm_P, blocks_P, 0, st);  // dB = P dZ
-  dense_dispatch(dt, 1, W, n, m, dB, dA, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // dA = W^T dB
+  dense_dispatch(desc, 1, W, dB, dA, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // dA = W^T dB
   apply_left(desc, dA, dX, m, perm_R, blocks_R, 0, st);  // dX = R dA
 }
 
@@ -720,7 +722,7 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
   if (!saved_B && !(desc->flags & POETX_FLAG_RECOMPUTE_B)) return POETX_ERR_INVALID_ARG;
   if (!ws || ws_bytes < poetx_linear_workspace_bytes(desc)) return POETX_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype, k = desc->neumann_k;
+  const int m = desc->d_in, n = desc->d_out, b = desc->block, k = desc->neumann_k;
   const i64 N = desc->n_tokens, Ni = internal_columns(desc);
   LayoutStaging lay(desc, ws, st);
   const Act x = lay.in(X, m), dz = lay.in(dZ, n), dx = lay.out(dX, m);
@@ -736,7 +738,7 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
     B = Act{w_keep - act_bytes(desc, n), Ni, Ni};
     W_resolved = resolve_weight(desc, W, w_keep, st);
     apply_left(desc, x, dA, m, perm_R, blocks_R, 1, st);
-    dense_dispatch(dt, 0, W_resolved, n, m, dA, B, rest, st, weight_in_kernel(desc));   // partials where dB will be
+    dense_dispatch(desc, 0, W_resolved, dA, B, rest, st, weight_in_kernel(desc));   // partials where dB will be
   }
   // Each side's gradient is streamed once where the call's tokens are whole tiles: dB = P dZ together with
   // dG_P = B' dZ'^T, then dA = W^T dB, then dX = R dA together with dG_R = X' dA'^T (Sec. 3.5).  A token count that is padded
@@ -764,7 +766,7 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
   };
   side(dz, B, dB, n, perm_P, blocks_P, dG_P);
   W = W_resolved ? W_resolved : resolve_weight(desc, W, part, st);   // the P side's partials are reduced by now (stream order): same space
-  dense_dispatch(dt, 1, W, n, m, dB, dA, (char*)part + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));
+  dense_dispatch(desc, 1, W, dB, dA, (char*)part + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));
   side(dA, x, dx, m, perm_R, blocks_R, dG_R);
   lay.finish();
   if (defer) return launch_status();

@@ -199,6 +199,7 @@ RAGGED_LAYERS = [
     (512, 768, 255, 64, "bf16"),        # small blocks: the contraction of the block gradients rounds up to a longer one
     (512, 768, 255, 64, "f32"),
     (1024, 768, 250, 192, "bf16"),      # neither small nor a streaming block side
+    (2048, 1920, 1660, 64, "f32"),      # 1664 columns inside: whole tiles of the streaming fp32 product, which 1660 tokens are not
     (520, 512, 2045, 8, "bf16"),        # applies of very small blocks on the plain kernel ...
     (520, 512, 2045, 8, "f32"),
     (1056, 768, 2001, 16, "bf16"),      # ... on one side only

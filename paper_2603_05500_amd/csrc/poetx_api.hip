@@ -218,12 +218,15 @@ size_t dense_part_bytes(const poetx_linear_desc* d) {
   return align256(w);
 }
 
+GradProblem grad_problem(const poetx_linear_desc* desc, const Act& U, const Act& V, int d, const int32_t* perm, float* parts = nullptr) {
+  return GradProblem{U.p, V.p, U.ld, U.cols, V.ld, V.cols, desc->n_tokens, d, perm, parts};
+}
 void blockgrad_dispatch(const poetx_linear_desc* desc, const Act& U, const Act& V, int d, const int32_t* perm, float* dG, void* ws, hipStream_t st) {
   const int dtype = desc->dtype, b = desc->block;
   const i64 N = desc->n_tokens;
   if (use_mfma(dtype) && mfma_blockgrad_supported(d, N, b) && aligned16(U.p) && aligned16(V.p))   // N in whole vectors, hence the row strides too
     mfma_blockgrad(U.p, U.ld, V.p, V.ld, d, N, perm, b, dG, ws, st);
-  else if (!g_force_fma.load()) edge_blockgrad(dtype, U.p, U.ld, V.p, V.ld, d, N, perm, b, dG, ws, st);
+  else if (!g_force_fma.load()) edge_blockgrad(dtype, grad_problem(desc, U, V, d, perm), b, dG, ws, st);
   else fma_blockgrad(dtype, U.p, V.p, d, N, perm, b, dG, st);
 }
 
@@ -661,8 +664,7 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
                            {theta_R, (const float*)((char*)ws + blockgrad_parts_bytes(desc, n)), (i64)ceil_div(m, b) * b * b, 1, m, dtheta_R}};
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      const GradProblem gp{saved_B.p, dZ.p, saved_B.ld, dZ.ld, desc->n_tokens, n, perm_P, (float*)sides[0].dG};
-      const GradProblem gr{X.p, dA.p, X.ld, dA.ld, desc->n_tokens, m, perm_R, (float*)sides[1].dG};
+      const GradProblem gp = grad_problem(desc, saved_B, dZ, n, perm_P, (float*)sides[0].dG), gr = grad_problem(desc, X, dA, m, perm_R, (float*)sides[1].dG);
       edge_blockgrad_parts_pair(dt, gp, gr, b, &sides[0].nsplit, &sides[1].nsplit, st);
     }
     StageTimer tm(POETX_STAGE_CNP_BWD, st);

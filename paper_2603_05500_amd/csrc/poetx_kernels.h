@@ -52,18 +52,19 @@ bool edge_apply_smallest_tile(int d, i64 plan_cols, int b);
 // the same on that tile for a few tokens with exactly one of V, out token major ([token][ld])
 void edge_apply_tokens(int dtype, const void* V, i64 ldv, bool v_tm, void* out, i64 ldo, bool out_tm, int d, i64 cols, i64 cols_out,
                        const int32_t* perm, const void* blocks, int b, int transpose_G, hipStream_t st);
-size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b);
-void edge_blockgrad(int dtype, const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws,
-                    hipStream_t st);
-// The same, left as its token-range parts (each ceil(d/b) * b * b floats, one after the other at `parts`); returns how many.
+// Block gradients over N tokens.  cols_u, cols_v: columns that the operands have, those past N being zeros (of a feature whose weights are
+// not finite also NaN: its tokens are not finite either).  parts: the sums of token ranges, each ceil(d/b) * b * b floats, one after the other.
 struct GradProblem {
   const void* U;
   const void* V;
-  i64 ldu, ldv, N;
+  i64 ldu, cols_u, ldv, cols_v, N;
   int d;
   const int32_t* perm;
   float* parts;
 };
+size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b);
+void edge_blockgrad(int dtype, GradProblem q, int b, float* dG, void* ws, hipStream_t st);   // summed up (parts is not used)
+// The same, left as its parts; returns how many.
 size_t edge_blockgrad_parts_bytes(int dtype, int d, i64 N, int b);
 int edge_blockgrad_parts(int dtype, const GradProblem& q, int b, hipStream_t st);
 // both sides of a layer, in one launch where their plans allow

@@ -60,11 +60,10 @@ __global__ __launch_bounds__(256) void skew_materialize_tiled_kernel(const float
   }
 }
 
-// What the on-chip chains of b = 256 read: bf16(Q) row major, 16 bytes per store, and (forward) 2Q in fp32, 32 x 32 tiles in
-// accumulator order: [block][column tile][row tile][g][lane][e] = 2Q(8g + 4 (lane / 32) + e, lane % 32) of the tile.  Blocks
-// 0 .. nb0 - 1 come from theta, the rest from theta2.
+// What the on-chip chains of b = 256 read: bf16(Q) as matrix-core fragments, [block][row tile][k step][lane][8], lane 32h + r holding
+// of row r of the tile the contraction elements 16s + 4h + {0, 1, 2, 3, 8, 9, 10, 11}.  Blocks 0 .. nb0 - 1 come from theta, the rest from theta2.
 __global__ __launch_bounds__(256) void skew_materialize_chain_kernel(const float* __restrict__ theta, const float* __restrict__ theta2, int nb0,
-                                                                     float* __restrict__ Q2, uint16_t* __restrict__ Qb) {
+                                                                     uint16_t* __restrict__ Qf) {
   constexpr int B = 256;
   __shared__ float tile[ST][ST + 1];
   int I, J;
@@ -73,7 +72,6 @@ __global__ __launch_bounds__(256) void skew_materialize_chain_kernel(const float
   load_tile(tile, (j < nb0 ? theta + j * (B * (B - 1) / 2) : theta2 + (j - nb0) * (B * (B - 1) / 2)), I, J, B);
   const int tid = threadIdx.x;
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll 1
   for (int m = 0; m < (I == J ? 1 : 2); ++m) {          // the tile, then its mirror image
     auto q = [&](int r, int c) {
@@ -82,23 +80,56 @@ __global__ __launch_bounds__(256) void skew_materialize_chain_kernel(const float
     };
     const int R = m ? J : I, C = m ? I : J;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int r = 32 * s + tid / 8, c = 8 * (tid % 8);
+    for (int p = 0; p < 2; ++p) {                       // row tile 2R + p, k steps 4C + s
+      const int s = tid >> 6, r = 32 * p + (tid & 31), c = 16 * s + 4 * ((tid >> 5) & 1);
       u32x4 o;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = float_to_bf16_bits(q(r, c + 2 * e)) | (uint32_t)float_to_bf16_bits(q(r, c + 2 * e + 1)) << 16;
-      *reinterpret_cast<u32x4*>(Qb + (j * B + R * ST + r) * B + C * ST + c) = o;
-    }
-    if (Q2) {
-      const int n = tid & 31, r0 = 8 * (tid >> 6) + 4 * ((tid >> 5) & 1);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int rt = s & 1, ct = s >> 1;
-        f32x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = 2.f * q(32 * rt + r0 + e, 32 * ct + n);
-        *reinterpret_cast<f32x4*>(Q2 + ((j * 8 + 2 * C + ct) * 8 + 2 * R + rt) * 1024 + tid * 4) = o;
+      for (int e = 0; e < 4; ++e) {
+        const int cc = c + 8 * (e >> 1) + 2 * (e & 1);
+        o[e] = float_to_bf16_bits(q(r, cc)) | (uint32_t)float_to_bf16_bits(q(r, cc + 1)) << 16;
       }
+      *reinterpret_cast<u32x4*>(Qf + (((j * 8 + 2 * R + p) * 16 + 4 * C + s) * 64 + (tid & 63)) * 8) = o;
+    }
+  }
+}
+
+// M of the on-chip chains (b = 256, 32 x 32 tiles [block][row tile][column tile][1024]: element (r, c) of a tile at
+// 256 (c / 8) + 128 ((c / 4) & 1) + 4 r + (c & 3)) -> packed gradients; blocks 0 .. nb0 - 1 go to dtheta, the rest to dtheta2
+__global__ __launch_bounds__(256) void skew_project_chain_kernel(const float* __restrict__ M, int nb0, float* __restrict__ dtheta,
+                                                                 float* __restrict__ dtheta2, int accumulate) {
+  constexpr int B = 256;
+  __shared__ float up[ST][ST + 1], lo[ST][ST + 1];
+  int I, J;
+  pair_decode(blockIdx.x, B / ST, I, J);
+  const i64 j = blockIdx.y;
+  const int tid = threadIdx.x;
+  {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const int r = tid & 31, c = 8 * (tid >> 6) + 4 * ((tid >> 5) & 1);
+    f32x4 u[4], l[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      u[q] = *reinterpret_cast<const f32x4*>(M + ((j * 8 + 2 * I + (q >> 1)) * 8 + 2 * J + (q & 1)) * 1024 + tid * 4);
+      l[q] = *reinterpret_cast<const f32x4*>(M + ((j * 8 + 2 * J + (q >> 1)) * 8 + 2 * I + (q & 1)) * 1024 + tid * 4);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        up[32 * (q >> 1) + r][32 * (q & 1) + c + e] = u[q][e];
+        lo[32 * (q >> 1) + r][32 * (q & 1) + c + e] = l[q][e];
+      }
+  }
+  __syncthreads();
+  float* dt = (j < nb0 ? dtheta + j * (B * (B - 1) / 2) : dtheta2 + (j - nb0) * (B * (B - 1) / 2));
+  const int c = tid & 63, r0 = tid >> 6;
+#pragma unroll 4
+  for (int r = r0; r < ST; r += 4) {
+    const int i = I * ST + r, col = J * ST + c;
+    if (i < col) {
+      const float v = up[r][c] - lo[c][r];   // M[i][col] - M[col][i]
+      float* dst = dt + packed_index(i, col, B);
+      *dst = accumulate ? *dst + v : v;
     }
   }
 }
@@ -139,9 +170,14 @@ void skew_materialize_tiled_launch(const float* theta, int b, i64 nb, float* Qf,
   hipLaunchKernelGGL(skew_materialize_tiled_kernel, dim3(T * (T + 1) / 2, (unsigned)nb), dim3(256), 0, st, theta, b, Qf, Qb, Tb);
 }
 
-void skew_materialize_chain_launch(const float* theta0, i64 nb0, const float* theta1, i64 nb1, float* Q2, uint16_t* Qb, hipStream_t st) {
+void skew_materialize_chain_launch(const float* theta0, i64 nb0, const float* theta1, i64 nb1, uint16_t* Qf, hipStream_t st) {
   constexpr int T = 256 / ST;
-  hipLaunchKernelGGL(skew_materialize_chain_kernel, dim3(T * (T + 1) / 2, (unsigned)(nb0 + nb1)), dim3(256), 0, st, theta0, theta1, (int)nb0, Q2, Qb);
+  hipLaunchKernelGGL(skew_materialize_chain_kernel, dim3(T * (T + 1) / 2, (unsigned)(nb0 + nb1)), dim3(256), 0, st, theta0, theta1, (int)nb0, Qf);
+}
+
+void skew_project_chain_launch(const float* M, i64 nb0, float* dtheta0, i64 nb1, float* dtheta1, int accumulate, hipStream_t st) {
+  constexpr int T = 256 / ST;
+  hipLaunchKernelGGL(skew_project_chain_kernel, dim3(T * (T + 1) / 2, (unsigned)(nb0 + nb1)), dim3(256), 0, st, M, (int)nb0, dtheta0, dtheta1, accumulate);
 }
 
 void skew_project_tiled_launch(const float* M, int b, i64 nb, float* dtheta, int accumulate, hipStream_t st) {

@@ -291,7 +291,7 @@ def test_dense_tiles(lib, n, m, N):
         assert torch.all(buf[:256] == -7.0) and torch.all(buf[256 + used:] == -7.0)
 
 
-@pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 40, (3,)), (512, 130, (3,)), (256, 130, (2,)), (256, 150, (2,)), (256, 3, (1, 2, 7))])
+@pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 40, (3,)), (512, 130, (3,)), (256, 130, (2,)), (256, 150, (2,)), (256, 3, (1, 2, 7)), (256, 9, (1, 5)), (256, 200, (4,))])
 def test_matrix_core_series(lib, b, nb, ks):
     """The bf16 series of large blocks, build and backward through poetx_cnp_build / poetx_cnp_bwd: every shape of the
     recurrences (the tiled one pairs powers: odd and even orders start differently), batches that are worked off in more
@@ -401,7 +401,7 @@ def test_block_counts_beyond_one_grid_dimension(lib):
     (512, 60, 30),      # groups 64 + 26: the P side ends inside the first group, the R side goes on in the second
     (512, 16, 70),      # the P side ends inside the second group
     (512, 20, 64),      # exactly at the boundary
-    (256, 100, 60),     # groups 128 + 32: the boundary inside the first
+    (256, 100, 60),     # groups 80 + 80: the boundary inside the first
     (256, 20, 140),     # inside the second
 ])
 def test_series_groups_of_two_sides(lib, b, nbR, nbP):

@@ -186,6 +186,20 @@ bool reads_tokens_in_place(const poetx_linear_desc* d) {
   return (double)(d->d_in + (i64)d->d_out) * N * d->block <= (d->block <= 256 ? 1 << 25 : 1 << 24);
 }
 
+// A handful of tokens: the forward's own short kernels, in every call that computes A and B (few_tokens_supported says where it pays).
+bool few_tokens(const poetx_linear_desc* d) { return use_mfma(d->dtype) && few_tokens_supported(d->d_out, d->d_in, d->block, d->n_tokens); }
+// B = W R^T X on them; A: scratch of n_tokens * d_in elements
+void few_b(const poetx_linear_desc* d, const void* X, const void* W, const int32_t* perm_R, const void* blocks_R, const Act& A, const Act& B, hipStream_t st) {
+  const bool tm = d->layout == POETX_TOKEN_MAJOR;
+  const int N = (int)d->n_tokens;
+  {
+    StageTimer tim(POETX_STAGE_APPLY, st);
+    few_apply(X, tm ? d->d_in : N, tm, A.out(), d->d_in, true, d->d_in, N, perm_R, blocks_R, d->block, 1, st);
+  }
+  StageTimer tim(POETX_STAGE_DENSE, st);
+  few_dense(W, d->d_out, d->d_in, A.p, B.out(), B.ld, N, (int)B.cols, st);
+}
+
 // Block gradients are summed over exactly the call's tokens, never over padding, by kernels that follow from the descriptor: the
 // order of the sum is the same in either layout and with B kept or recomputed, whichever of the tensors have padded columns.
 // Only the pointers' alignment can change the kernel, which a workspace query does not see: it covers both.
@@ -550,6 +564,13 @@ int poetx_linear_fwd(const poetx_linear_desc* desc, const void* X, const void* W
   }
   W = resolve_weight(desc, W, after, st);
   void* part = after + dequantised_weight_bytes(desc);
+  if (few_tokens(desc)) {
+    few_b(desc, X, W, perm_R, blocks_R, A, B, st);
+    StageTimer tm(POETX_STAGE_APPLY, st);
+    const bool tok = desc->layout == POETX_TOKEN_MAJOR;
+    few_apply(B.p, B.ld, false, Z, tok ? n : N, tok, n, (int)N, perm_P, blocks_P, b, 1, st);
+    return launch_status();
+  }
   if (reads_tokens_in_place(desc)) {
     {
       StageTimer tm(POETX_STAGE_APPLY, st);
@@ -578,10 +599,15 @@ int poetx_linear_recompute_b(const poetx_linear_desc* desc, const void* X, const
   hipStream_t st = (hipStream_t)stream;
   const int m = desc->d_in;
   const i64 N = desc->n_tokens, Ni = internal_columns(desc);
-  LayoutStaging lay(desc, ws, st);
-  const Act x = lay.in(X, m), A{ws, Ni, Ni};
+  const Act A{ws, Ni, Ni};
   char* after = (char*)ws + act_bytes(desc, m);
   W = resolve_weight(desc, W, after, st);
+  if (few_tokens(desc)) {
+    few_b(desc, X, W, perm_R, blocks_R, A, Act{B_out, N, N}, st);
+    return launch_status();
+  }
+  LayoutStaging lay(desc, ws, st);
+  const Act x = lay.in(X, m);
   apply_left(desc, x, A, m, perm_R, blocks_R, 1, st);  // A = R^T X
   dense_dispatch(desc, 0, W, A, Act{B_out, N, N}, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // B = W A
   return launch_status();
@@ -739,8 +765,12 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
     char* w_keep = end - dequantised_weight_bytes(desc);
     B = Act{w_keep - act_bytes(desc, n), Ni, Ni};
     W_resolved = resolve_weight(desc, W, w_keep, st);
-    apply_left(desc, x, dA, m, perm_R, blocks_R, 1, st);
-    dense_dispatch(desc, 0, W_resolved, dA, B, rest, st, weight_in_kernel(desc));   // partials where dB will be
+    if (few_tokens(desc)) {
+      few_b(desc, X, W_resolved, perm_R, blocks_R, dA, B, st);
+    } else {
+      apply_left(desc, x, dA, m, perm_R, blocks_R, 1, st);
+      dense_dispatch(desc, 0, W_resolved, dA, B, rest, st, weight_in_kernel(desc));   // partials where dB will be
+    }
   }
   // Each side's gradient is streamed once where the call's tokens are whole tiles: dB = P dZ together with
   // dG_P = B' dZ'^T, then dA = W^T dB, then dX = R dA together with dG_R = X' dA'^T (Sec. 3.5).  A token count that is padded

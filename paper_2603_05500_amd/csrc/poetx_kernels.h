@@ -70,6 +70,14 @@ int edge_blockgrad_parts(int dtype, const GradProblem& q, int b, hipStream_t st)
 // both sides of a layer, in one launch where their plans allow
 void edge_blockgrad_parts_pair(int dtype, const GradProblem& q0, const GradProblem& q1, int b, int* n0, int* n1, hipStream_t st);
 
+// ---- the forward of up to 32 bf16 tokens (few_tokens.hip); tensors of any alignment ----------
+bool few_tokens_supported(int n, int m, int b, i64 N);
+// V, out: feature major (row stride ld) or token major ([token][ld]); not V token major with out feature major
+void few_apply(const void* V, i64 ldv, bool v_tm, void* out, i64 ldo, bool out_tm, int d, int N, const int32_t* perm, const void* E, int b, int trans,
+               hipStream_t st);
+// out (M x cols feature major, columns from N on zero) = W (M x K) times act ([token][K])
+void few_dense(const void* W, int M, int K, const void* act, void* out, i64 ldo, int N, int cols, hipStream_t st);
+
 // ---- fp32 series of blocks up to 128, one launch (series_small.hip) ----------------------------------------
 bool series_small_supported(int b);
 void series_small_build(const float* theta, int d, int b, int k, float* G_f32, void* E_bf16, hipStream_t st);

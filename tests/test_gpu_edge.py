@@ -203,6 +203,15 @@ RAGGED_LAYERS = [
     (520, 512, 2045, 8, "bf16"),        # applies of very small blocks on the plain kernel ...
     (520, 512, 2045, 8, "f32"),
     (1056, 768, 2001, 16, "bf16"),      # ... on one side only
+    # a handful of tokens
+    (512, 768, 1, 256, "bf16"),
+    (1024, 512, 7, 512, "bf16"),        # a contraction of fewer than eight steps per wave, and with a remainder
+    (1472, 960, 16, 64, "bf16"),
+    (256, 384, 17, 128, "bf16"),        # two token tiles
+    (768, 512, 32, 256, "bf16"),        # the last that takes the short kernels ...
+    (768, 512, 33, 256, "bf16"),
+    (2048, 8192, 13, 256, "bf16"),      # four row tiles per workgroup
+    (4096, 4608, 17, 512, "bf16"),      # ... of a larger weight
     # layers that are padded to whole 256-token tiles
     (2048, 2048, 100, 256, "bf16"),     # fewer tokens than a tile
     (2048, 2304, 192, 256, "bf16"),     # a multiple of the 64-token tiles

@@ -70,7 +70,7 @@ int check_desc(const poetx_linear_desc* d) {
 size_t cnp_bwd_ws_floats(i64 nb, int b, int k) {
   const size_t elems = (size_t)nb * b * b;
   size_t chain = (size_t)(k + 2 > 5 ? k + 2 : 5) * elems;
-  if (lds_cnp_supported(b, b) && lds_cnp_bwd_ws_floats((int)nb, k) > chain) chain = lds_cnp_bwd_ws_floats((int)nb, k);
+  if (lds_cnp_supported(b, b) && lds_cnp_bwd_ws_floats((int)nb) > chain) chain = lds_cnp_bwd_ws_floats((int)nb);
   return elems + chain;
 }
 // ... of a call's series: those of one side after the other, or of both sides together

@@ -147,11 +147,13 @@ void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumul
 // b = 256: whole chain of a block in one launch, block resident on chip (mfma_cnp_lds.hip).
 bool lds_cnp_supported(int d, int b);
 void lds_cnp_build(const float* theta, int nb, int k, float* G_f32, void* E_bf16, float* ws, hipStream_t st);   // ws: half a float per block element
-// Backward of one or two sides (dG of a side: one matrix per block, nsplit = 1).  ws: lds_cnp_bwd_ws_floats(all blocks, k) floats.
-size_t lds_cnp_bwd_ws_floats(int nb, int k);
+// Backward of one or two sides (dG of a side: one matrix per block, nsplit = 1).  ws: lds_cnp_bwd_ws_floats(all blocks) floats.
+size_t lds_cnp_bwd_ws_floats(int nb);
 void lds_cnp_bwd(const SeriesSide* sides, int nsides, int k, int accumulate, float* ws, hipStream_t st);
-// b = 256, nb0 + nb1 blocks of two sides: bf16(Q) as the chains' fragments, and their dL/dQ (tiles in the chains' order) -> packed gradients (skew_tiled.hip)
-void skew_materialize_chain_launch(const float* theta0, i64 nb0, const float* theta1, i64 nb1, uint16_t* Qf, hipStream_t st);
+// b = 256, nb0 + nb1 blocks of two sides: bf16(Q), or where dL/dG is given bf16(-Q) and bf16(dL/dG), as the chains' fragments; and their dL/dQ (tiles
+// in the chains' order) -> packed gradients (skew_tiled.hip)
+void skew_materialize_chain_launch(const float* theta0, i64 nb0, const float* theta1, i64 nb1, uint16_t* Qf, const float* D0, const float* D1, uint16_t* Df,
+                                   hipStream_t st);
 void skew_project_chain_launch(const float* M, i64 nb0, float* dtheta0, i64 nb1, float* dtheta1, int accumulate, hipStream_t st);
 // dL/dQ of nb0 + nb1 blocks -> packed gradients of two sides (skew_tiled.hip)
 void skew_project_sides_launch(const float* M, int b, i64 nb0, float* dtheta0, i64 nb1, float* dtheta1, int accumulate, hipStream_t st);

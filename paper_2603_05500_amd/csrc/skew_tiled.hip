@@ -60,23 +60,48 @@ __global__ __launch_bounds__(256) void skew_materialize_tiled_kernel(const float
   }
 }
 
-// What the on-chip chains of b = 256 read: bf16(Q) as matrix-core fragments, [block][row tile][k step][lane][8], lane 32h + r holding
-// of row r of the tile the contraction elements 16s + 4h + {0, 1, 2, 3, 8, 9, 10, 11}.  Blocks 0 .. nb0 - 1 come from theta, the rest from theta2.
+// What the on-chip chains of b = 256 read, as matrix-core fragments [block][row tile][k step][lane][8], lane 32h + r holding of row r
+// of the tile the contraction elements 16s + 4h + {0, 1, 2, 3, 8, 9, 10, 11}: bf16(Q), or for the backward bf16(-Q) and bf16(D) (D given).
+// Blocks 0 .. nb0 - 1 come from theta and D, the rest from theta2 and D2.
 __global__ __launch_bounds__(256) void skew_materialize_chain_kernel(const float* __restrict__ theta, const float* __restrict__ theta2, int nb0,
-                                                                     uint16_t* __restrict__ Qf) {
-  constexpr int B = 256;
+                                                                     uint16_t* __restrict__ Qf, const float* __restrict__ D,
+                                                                     const float* __restrict__ D2, uint16_t* __restrict__ Df) {
+  constexpr int B = 256, PAIRS = (B / ST) * (B / ST + 1) / 2;
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
   __shared__ float tile[ST][ST + 1];
+  const i64 j = blockIdx.y;
+  const int tid = threadIdx.x;
+  if (blockIdx.x >= PAIRS) {                            // a row tile of D
+    const int w = blockIdx.x - PAIRS;
+    const float* d = (j < nb0 ? D + j * B * B : D2 + (j - nb0) * B * B) + (32 * w + (tid & 31)) * B + 16 * (tid >> 6) + 4 * ((tid >> 5) & 1);
+    f32x4_a4 lo[4], hi[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      lo[i] = *reinterpret_cast<const f32x4_a4*>(d + 64 * i);
+      hi[i] = *reinterpret_cast<const f32x4_a4*>(d + 64 * i + 8);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      u32x4 o;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        o[e] = float_to_bf16_bits(lo[i][2 * e]) | (uint32_t)float_to_bf16_bits(lo[i][2 * e + 1]) << 16;
+        o[2 + e] = float_to_bf16_bits(hi[i][2 * e]) | (uint32_t)float_to_bf16_bits(hi[i][2 * e + 1]) << 16;
+      }
+      *reinterpret_cast<u32x4*>(Df + (((j * 8 + w) * 16 + 4 * i + (tid >> 6)) * 64 + (tid & 63)) * 8) = o;
+    }
+    return;
+  }
   int I, J;
   pair_decode(blockIdx.x, B / ST, I, J);
-  const i64 j = blockIdx.y;
   load_tile(tile, (j < nb0 ? theta + j * (B * (B - 1) / 2) : theta2 + (j - nb0) * (B * (B - 1) / 2)), I, J, B);
-  const int tid = threadIdx.x;
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const float sign = D ? -1.f : 1.f;
 #pragma unroll 1
   for (int m = 0; m < (I == J ? 1 : 2); ++m) {          // the tile, then its mirror image
     auto q = [&](int r, int c) {
-      if (m) return -tile[c][r];
-      return I != J || c > r ? tile[r][c] : (c < r ? -tile[c][r] : 0.f);
+      if (m) return -sign * tile[c][r];
+      return I != J || c > r ? sign * tile[r][c] : (c < r ? -sign * tile[c][r] : 0.f);
     };
     const int R = m ? J : I, C = m ? I : J;
 #pragma unroll
@@ -94,7 +119,7 @@ __global__ __launch_bounds__(256) void skew_materialize_chain_kernel(const float
 }
 
 // M of the on-chip chains (b = 256, 32 x 32 tiles [block][row tile][column tile][1024]: element (r, c) of a tile at
-// 256 (c / 8) + 128 ((c / 4) & 1) + 4 r + (c & 3)) -> packed gradients; blocks 0 .. nb0 - 1 go to dtheta, the rest to dtheta2
+// 256 (r / 8) + 128 ((r / 4) & 1) + 4 c + (r & 3)) -> packed gradients; blocks 0 .. nb0 - 1 go to dtheta, the rest to dtheta2
 __global__ __launch_bounds__(256) void skew_project_chain_kernel(const float* __restrict__ M, int nb0, float* __restrict__ dtheta,
                                                                  float* __restrict__ dtheta2, int accumulate) {
   constexpr int B = 256;
@@ -105,7 +130,7 @@ __global__ __launch_bounds__(256) void skew_project_chain_kernel(const float* __
   const int tid = threadIdx.x;
   {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const int r = tid & 31, c = 8 * (tid >> 6) + 4 * ((tid >> 5) & 1);
+    const int c = tid & 31, r = 8 * (tid >> 6) + 4 * ((tid >> 5) & 1);
     f32x4 u[4], l[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -116,8 +141,8 @@ __global__ __launch_bounds__(256) void skew_project_chain_kernel(const float* __
     for (int q = 0; q < 4; ++q)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        up[32 * (q >> 1) + r][32 * (q & 1) + c + e] = u[q][e];
-        lo[32 * (q >> 1) + r][32 * (q & 1) + c + e] = l[q][e];
+        up[32 * (q >> 1) + r + e][32 * (q & 1) + c] = u[q][e];
+        lo[32 * (q >> 1) + r + e][32 * (q & 1) + c] = l[q][e];
       }
   }
   __syncthreads();
@@ -170,9 +195,10 @@ void skew_materialize_tiled_launch(const float* theta, int b, i64 nb, float* Qf,
   hipLaunchKernelGGL(skew_materialize_tiled_kernel, dim3(T * (T + 1) / 2, (unsigned)nb), dim3(256), 0, st, theta, b, Qf, Qb, Tb);
 }
 
-void skew_materialize_chain_launch(const float* theta0, i64 nb0, const float* theta1, i64 nb1, uint16_t* Qf, hipStream_t st) {
+void skew_materialize_chain_launch(const float* theta0, i64 nb0, const float* theta1, i64 nb1, uint16_t* Qf, const float* D0, const float* D1, uint16_t* Df,
+                                   hipStream_t st) {
   constexpr int T = 256 / ST;
-  hipLaunchKernelGGL(skew_materialize_chain_kernel, dim3(T * (T + 1) / 2, (unsigned)(nb0 + nb1)), dim3(256), 0, st, theta0, theta1, (int)nb0, Qf);
+  hipLaunchKernelGGL(skew_materialize_chain_kernel, dim3(T * (T + 1) / 2 + (D0 ? 8 : 0), (unsigned)(nb0 + nb1)), dim3(256), 0, st, theta0, theta1, (int)nb0, Qf, D0, D1, Df);
 }
 
 void skew_project_chain_launch(const float* M, i64 nb0, float* dtheta0, i64 nb1, float* dtheta1, int accumulate, hipStream_t st) {

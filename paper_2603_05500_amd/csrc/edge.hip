@@ -14,32 +14,39 @@ using namespace edge;
 inline i64 min64(i64 a, i64 b) { return a < b ? a : b; }
 
 // ---- plans -------------------------------------------------------------------------------------
-// Tile: the largest one that still gives three quarters of the CUs a workgroup -- a larger tile halves the
-// operand traffic, an idle CU costs more than that.  Contraction split: up to two workgroups per CU, as long
-// as a split keeps two stages (below that the fill of the ring is all there is).  The smallest tile, which serves
-// products bound by the reads of one operand (few tokens), goes to four per CU where a split keeps four stages: what is
-// in flight sets its rate (forward of 16 tokens, 4096 x 14336: 44 -> 39 us; 14336 x 4096: 44 -> 38).
-Plan pick_plan(i64 batches, i64 M, i64 N, i64 K, size_t es, bool may_split) {
-  Plan p{TILE_32, 1};
-  if (M > 64 && N > 64 && tile_count(batches, M, N, 128) >= kCUs * 3 / 4) p.tile = TILE_128;
-  else if (M > 32 && N > 32 && tile_count(batches, M, N, 64) >= kCUs * 3 / 4) p.tile = TILE_64;
-  if (!may_split) return p;
-  const int side = p.tile == TILE_128 ? 128 : p.tile == TILE_64 ? 64 : 32;
-  const int depth = stage_depth(p.tile, es);
-  const i64 count = tile_count(batches, M, N, side), stages = (K + depth - 1) / depth;
-  i64 s = min64(2 * kCUs / count, stages / 2);
-  if (p.tile == TILE_32) {
-    const i64 more = min64(4 * kCUs / count, stages / 4);
-    if (more > s) s = more;
-  }
-  if (s > 1) {
-    const i64 per = (stages + s - 1) / s;
-    p.splits = (int)((stages + per - 1) / per);   // no empty split
-  }
-  return p;
+// Tile of an apply (a contraction as short as a block): the largest one that still gives three quarters of the CUs a workgroup -- a larger tile
+// halves the operand traffic, an idle CU costs more than that.
+Tile apply_tile(i64 batches, i64 M, i64 N) {
+  if (M > 64 && N > 64 && tile_count(batches, M, N, 128) >= kCUs * 3 / 4) return TILE_128;
+  if (M > 32 && N > 32 && tile_count(batches, M, N, 64) >= kCUs * 3 / 4) return TILE_64;
+  return TILE_32;
 }
 
-Plan dense_plan(int dtype, i64 M, i64 N, i64 K) { return pick_plan(1, M, N, K, dtype == POETX_F32 ? 4 : 2, true); }
+// Dense products: tile and contraction split priced together.  A workgroup takes `lone` us for a stage when it has a CU to itself and
+// `shared` when more of them fill it; a split adds its fp32 parts, written and read at 4 TB/s, and a launch of 2.5 us.  Measured, us,
+// tile / splits (64D: 64 x 64 with sixteen waves): fp32 1024 x 768 x 1001 32/1 29.0, 64/1 29.9, 64/2 27.6, 64/4 27.8, 64D/1 25.4,
+// 128/4 32.8 (the rule before took 64/2 of four waves: 30.7); its transpose product 27.3, 37.7, 32.5, 26.6, 29.8, 36.6; 256 x 256 x 512 32/1 6.0,
+// 32/2 7.7 (the choice before); bf16 512 x 1376 x 1024 32/1 10.7, 32/2 13.9 (before), 64D/1 10.6 (but 18.0 against 14.1 for 1024 x 1024 x 2000); 1024 x 1536 x 3001 32/1 55.6, 64/1 27.0, 128/2 37 - 43 (before).
+Plan dense_plan(int dtype, i64 M, i64 N, i64 K) {
+  struct Cost { Tile tile; int side; double lone, shared; };
+  static const Cost f32[] = {{TILE_32, 32, 0.75, 0.52}, {TILE_64, 64, 1.1, 0.6}, {TILE_64D, 64, 1.75, 1.4}, {TILE_128, 128, 2.8, 2.2}};
+  static const Cost bf16[] = {{TILE_32, 32, 0.42, 0.31}, {TILE_64, 64, 0.42, 0.33}, {TILE_128, 128, 1.1, 1.1}};
+  const size_t es = dtype == POETX_F32 ? 4 : 2;
+  Plan best{TILE_32, 1};
+  double least = 0;
+  for (int t = 0; t < (dtype == POETX_F32 ? 4 : 3); ++t) {
+    const Cost& c = dtype == POETX_F32 ? f32[t] : bf16[t];
+    const i64 count = tile_count(1, M, N, c.side), depth = stage_depth(c.tile, es), stages = (K + depth - 1) / depth;
+    for (i64 s = 1; s <= 16 && (s == 1 || (stages / s >= 2 && count * s <= 4 * kCUs)); s += s < 4 ? 1 : s / 2) {
+      const i64 per = (stages + s - 1) / s, splits = (stages + per - 1) / per;   // no empty split
+      const double fill = (double)((count * splits + kCUs - 1) / kCUs) * c.shared;
+      double us = per * (c.lone > fill ? c.lone : fill);
+      if (splits > 1) us += 2.5 + 8e-6 / 4 * splits * (double)M * (double)N;
+      if (least == 0 || us < least) { least = us; best = Plan{c.tile, (int)splits}; }
+    }
+  }
+  return best;
+}
 // Block gradients: the contraction is the token range, so a large tile with a split costs only its fp32 parts, while
 // every halving of the tile side doubles the reads of both activations.  A split keeps 256 tokens, on the smallest tile two
 // stages (one stage each: 1376 x 512, b = 64 step 93 -> 101 us).
@@ -182,13 +189,13 @@ void dense_t(int dtype, int trans_w, const T* W, int n, int m, const T* act, i64
   g.B = Op{act, ld_act, 0, nullptr, K, (int)N, 0, 0};
   if (p.splits > 1) {
     const EpiPartial epi{(float*)ws, M, (int)N, 1};
-    if (trans_w) launch<T, false, false>(g, epi, 1, M, N, K, p, st);
-    else launch<T, true, false>(g, epi, 1, M, N, K, p, st);
+    if (trans_w) launch<T, false, false, true>(g, epi, 1, M, N, K, p, st);
+    else launch<T, true, false, true>(g, epi, 1, M, N, K, p, st);
     reduce<T>((const float*)ws, M, N, p.splits, out, ld_out, st);
   } else {
     const EpiStore<T> epi{out, ld_out, M, (int)N};
-    if (trans_w) launch<T, false, false>(g, epi, 1, M, N, K, p, st);
-    else launch<T, true, false>(g, epi, 1, M, N, K, p, st);
+    if (trans_w) launch<T, false, false, true>(g, epi, 1, M, N, K, p, st);
+    else launch<T, true, false, true>(g, epi, 1, M, N, K, p, st);
   }
 }
 
@@ -196,7 +203,7 @@ template <class T>
 void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out, i64 plan_cols, const int32_t* perm, const T* blocks, int b,
              int trans, hipStream_t st) {
   const int nb = ceil_div(d, b);
-  const Plan p = pick_plan(nb, b, plan_cols, b, sizeof(T), false);
+  const Plan p{apply_tile(nb, b, plan_cols), 1};
   Args g{};
   g.rpb = b;
   g.d = d;
@@ -227,11 +234,11 @@ void apply_tokens_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 c
   const EpiScatterTokens<T, V_TM, OUT_TM> epi{out, V, ldo, ldv, perm, b, d, (int)cols, (int)cols_out};
   if constexpr (sizeof(T) == 2) {
     g.A = Op{blocks + (trans ? (i64)b * b : 0), b, 2ll * b * b, nullptr, b, b, 1, 1};
-    launch_shape<T, 32, 32, D, 1, 1, true, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
+    launch_shape<T, 32, 32, D, 1, 1, 4, true, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
   } else {
     g.A = Op{blocks, b, (i64)b * b, nullptr, b, b, 1, 1};
-    if (trans) launch_shape<T, 32, 32, D, 1, 1, false, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
-    else launch_shape<T, 32, 32, D, 1, 1, true, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
+    if (trans) launch_shape<T, 32, 32, D, 1, 1, 4, false, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
+    else launch_shape<T, 32, 32, D, 1, 1, 4, true, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
   }
 }
 
@@ -283,7 +290,7 @@ void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int 
     apply_t<uint16_t>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, plan_cols, perm, (const uint16_t*)blocks, b, transpose_G, st);
 }
 
-bool edge_apply_smallest_tile(int d, i64 plan_cols, int b) { return pick_plan(ceil_div(d, b), b, plan_cols, b, 4, false).tile == TILE_32; }
+bool edge_apply_smallest_tile(int d, i64 plan_cols, int b) { return apply_tile(ceil_div(d, b), b, plan_cols) == TILE_32; }
 
 void edge_apply_tokens(int dtype, const void* V, i64 ldv, bool v_tm, void* out, i64 ldo, bool out_tm, int d, i64 cols, i64 cols_out,
                        const int32_t* perm, const void* blocks, int b, int transpose_G, hipStream_t st) {

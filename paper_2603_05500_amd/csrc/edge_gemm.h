@@ -9,13 +9,12 @@
 // index does.  Tiles are loaded through registers, 16 bytes per lane whatever the alignment (element
 // aligned vectors: one global load either way), masked at the edges with zeros on both operands so that
 // nothing outside the valid ranges takes part, and pass through a two-stage LDS ring with one barrier
-// per stage; the loads of the next stage are in flight under the products of this one.
+// per stage; the loads of the next two stages are in flight under the products of this one.
 //
 // What bounds it: at the sizes it serves the chip is rarely full, so a pass is a chain of latencies (load,
-// LDS, matrix product, store).  Hence the tile follows the problem (see pick_plan): 128 x 128 where that
-// fills the chip, 64 x 64 below, and 32 x 32 with the four waves splitting the contraction (each takes a
-// quarter of every stage; the partial tiles meet in LDS) for the smallest, which quarters the chain.
-// Contractions that still leave CUs idle are split over workgroups as well (fp32 partials, fixed order).
+// LDS, matrix product, store).  Hence tile and contraction split follow the problem (dense_plan, apply_tile, grad_plan): 128 x 128, 64 x 64,
+// and 32 x 32 with all waves splitting the contraction (each takes its part of every stage; the partial tiles meet in LDS) for the
+// smallest, which quarters the chain.
 #pragma once
 #include "mfma_gemm.h"
 
@@ -52,26 +51,50 @@ typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 __device__ inline u32x4 load16(const uint16_t* p) { return *reinterpret_cast<const u32x4_a2*>(p); }
 __device__ inline u32x4 load16(const float* p) { return *reinterpret_cast<const u32x4_a4*>(p); }
 
-// 16 bytes of a row starting at column c: zeros outside [0, cols)
+// v without its first n elements, zeros behind them (all zeros from n = 16 bytes on)
 template <class T>
-__device__ inline u32x4 load_masked(const T* row, int c, int cols, bool row_ok) {
+__device__ __forceinline__ u32x4 drop_first(const u32x4& v, int n) {
+  typedef unsigned long long u64;
+  constexpr int B = 8 * sizeof(T);
+  const u64 lo = (u64)v[1] << 32 | v[0], hi = (u64)v[3] << 32 | v[2];
+  const int bits = n * B, in = bits & 63;
+  const u64 carry = in ? hi << (64 - in) : 0, l = bits < 64 ? lo >> in | carry : hi >> in, h = bits < 64 ? hi >> in : 0;
+  const bool none = bits >= 128;
+  u32x4 r;
+  r[0] = none ? 0 : (uint32_t)l;
+  r[1] = none ? 0 : (uint32_t)(l >> 32);
+  r[2] = none ? 0 : (uint32_t)h;
+  r[3] = none ? 0 : (uint32_t)(h >> 32);
+  return r;
+}
+
+// 16 bytes of a row starting at column c >= 0 in two halves: the load (a vector that would pass the row's end ends there instead; no branch
+// per lane, a row that is not there is some other one) and, once it is waited for, the mask: zeros from column cols on, or altogether if !row_ok.
+template <class T>
+__device__ __forceinline__ u32x4 load_raw(const T* row, int c, int cols) {
   constexpr int V = 16 / sizeof(T);
-  u32x4 v = {0, 0, 0, 0};
-  if (!row_ok || c >= cols) return v;
-  if (cols - c >= V) return load16(row + c);   // no sum: the last column may be the last int
-  const int n = cols - c;
+  if (cols < V) {              // uniform: too short for a vector
+    u32x4 v = {0, 0, 0, 0};
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    if constexpr (sizeof(T) == 4) {
-      if (w < n) v[w] = __builtin_bit_cast(uint32_t, row[c + w]);
-    } else {
-      uint32_t x = 0;
-      if (2 * w < n) x = row[c + 2 * w];
-      if (2 * w + 1 < n) x |= (uint32_t)row[c + 2 * w + 1] << 16;
-      v[w] = x;
+    for (int e = 0; e < V - 1; ++e) {
+      if (e < cols - c) {
+        if constexpr (sizeof(T) == 4) v[e] = __builtin_bit_cast(uint32_t, row[c + e]);
+        else v[e >> 1] |= (uint32_t)row[c + e] << (16 * (e & 1));
+      }
     }
+    return v;
   }
-  return v;
+  return load16(row + (c < cols - V ? c : cols - V));
+}
+template <class T>
+__device__ __forceinline__ u32x4 mask_raw(const u32x4& v, int c, int cols, bool row_ok) {
+  constexpr int V = 16 / sizeof(T);
+  const int past = cols < V || c <= cols - V ? 0 : c - (cols - V);
+  return drop_first<T>(v, row_ok && past < V ? past : V);
+}
+template <class T>
+__device__ __forceinline__ u32x4 load_masked(const T* row, int c, int cols, bool row_ok) {
+  return mask_raw<T>(load_raw<T>(row, c, cols), c, cols, row_ok);
 }
 
 // the same with columns cs elements apart
@@ -113,6 +136,10 @@ __device__ inline void store8(float* p, const float (&v)[8], int n) {
   }
 }
 
+// this wave's LDS accesses have been carried out, and every other wave's; loads from memory stay in flight, which __syncthreads()
+// would wait for
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // chunk swizzle of an X-major bf16 tile (see kx_chunk); 32-wide rows need none: the four k rows of a
 // transposing read are 64 bytes apart and already fall on different banks
 template <int X>
@@ -124,27 +151,28 @@ __device__ inline int kx_swz(int c, int k) {
 template <class T, int X, int BK>
 constexpr int tile_bytes() { return sizeof(T) == 2 ? X * BK * 2 : (X + 4) * BK * 4; }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN>
+// WAVES waves: those beyond WGM x WGN split the contraction of a stage
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES>
 struct Shape {
-  static constexpr int WGK = 4 / (WGM * WGN);
+  static constexpr int THREADS = 64 * WAVES, WGK = WAVES / (WGM * WGN);
   static constexpr int A_BYTES = tile_bytes<T, BM, BK>(), B_BYTES = tile_bytes<T, BN, BK>();
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int LDS = 2 * STAGE;
   static constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
-  static_assert(WGM * WGN * WGK == 4, "four waves");
-  static_assert(4 * 32 * (TN * 32 + 4) * 4 <= LDS, "output staging fits the ring");
+  static_assert(WGM * WGN * 32 * (TN * 32 + 4) * 4 <= LDS, "output staging fits the ring");
   static_assert(WGK == 1 || (WGK - 1) * WGM * WGN * TM * TN * 4096 <= LDS, "partial tiles meet in the ring");
 };
 
 // Epi: __device__ void operator()(int batch, int split, int row, int col, const float (&v)[8]) -- eight
 // consecutive columns of one output row, indices inside the batch; it does its own masking.
 // bx of total: this workgroup among those of the problem.
-template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
 __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int bx, int total, int split) {
-  using S = Shape<T, BM, BN, BK, WGM, WGN>;
+  using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
   constexpr int V = 16 / sizeof(T), WGK = S::WGK, TM = S::TM, TN = S::TN;
   constexpr bool BF = sizeof(T) == 2;
-  constexpr int NVA = BM * BK / V / 256, NVB = BN * BK / V / 256;
+  constexpr int PF = 2;            // stages whose loads are in flight
+  constexpr int NTH = S::THREADS, NVA = BM * BK / V / NTH, NVB = BN * BK / V / NTH;
   static_assert(NVA >= 1 && NVB >= 1, "tile too small");
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -159,7 +187,7 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   const int i0 = (tile % g.tiles_m) * BM, j0 = (tile / g.tiles_m) * BN;
   const int side = g.rpb > 0 ? (g.d - batch * g.rpb < g.rpb ? g.d - batch * g.rpb : g.rpb) : 0x7fffffff;
 
-  // ---- loads: vector s of this thread covers row (s * 256 + tid) / VPR of the tile's memory rows
+  // ---- loads: vector s of this thread covers row (s * NTH + tid) / VPR of the tile's memory rows
   struct Side {
     const T* base;
     const int32_t* pm;
@@ -177,43 +205,39 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   };
   const Side sa = side_of(g.A), sb = side_of(g.B);
   constexpr int VPRA = (A_K ? BK : BM) / V, VPRB = (B_K ? BK : BN) / V;
-  u32x4 ra[NVA], rb[NVB];
-  // memory row of this thread's vector: fixed for a K-major operand, moving with the stage for an X-major one
+  u32x4 ra[PF][NVA], rb[PF][NVB];
+  // Memory row of this thread's vector (its offset; where there is none, that of the first): fixed for a K-major operand, moving with
+  // the stage for an X-major one.
   i64 rowA[NVA], rowB[NVB];
-  auto row_index = [&](const Side& s, int r) -> i64 { return r < s.rows ? (s.pm ? (i64)s.pm[r] : (i64)r) * s.ld : -1; };
-  auto rows_at = [&](int kt) {
+  auto row_at = [&](const Side& s, int r) {
+    const int rr = r < s.rows ? r : 0;
+    return (s.pm ? (i64)s.pm[rr] : (i64)rr) * s.ld;
+  };
+  auto rowno_a = [&](int s, int kt) { return (A_K ? i0 : kt * BK) + (s * NTH + tid) / VPRA; };
+  auto rowno_b = [&](int s, int kt) { return (B_K ? j0 : kt * BK) + (s * NTH + tid) / VPRB; };
+  auto col_a = [&](int s, int kt) { return (A_K ? kt * BK : i0) + ((s * NTH + tid) % VPRA) * V; };
+  auto col_b = [&](int s, int kt) { return (B_K ? kt * BK : j0) + ((s * NTH + tid) % VPRB) * V; };
+  auto rows_at = [&](int kt, bool first) {
+    if (!A_K || first) {
 #pragma unroll
-    for (int s = 0; s < NVA; ++s) {
-      const int r = (s * 256 + tid) / VPRA;
-      rowA[s] = row_index(sa, A_K ? i0 + r : kt * BK + r);
+      for (int s = 0; s < NVA; ++s) rowA[s] = row_at(sa, rowno_a(s, kt));
     }
+    if (!B_K || first) {
 #pragma unroll
-    for (int s = 0; s < NVB; ++s) {
-      const int r = (s * 256 + tid) / VPRB;
-      rowB[s] = row_index(sb, B_K ? j0 + r : kt * BK + r);
+      for (int s = 0; s < NVB; ++s) rowB[s] = row_at(sb, rowno_b(s, kt));
     }
   };
-  auto next_rows = [&](int kt) {   // gathered X-major rows change from stage to stage
-    if (!A_K) {
+  // Stages up to here are whole and need no mask.  The others are masked on their way into LDS, not where they are loaded: that would wait for
+  // the load, and the workgroups at the edges are the last to finish.
+  const int whole_a = i0 + BM <= (A_K ? sa.rows : sa.cols) ? (A_K ? sa.cols : sa.rows) / BK : 0;
+  const int whole_b = j0 + BN <= (B_K ? sb.rows : sb.cols) ? (B_K ? sb.cols : sb.rows) / BK : 0;
+  auto gload = [&](int kt, int q) {
 #pragma unroll
-      for (int s = 0; s < NVA; ++s) rowA[s] = row_index(sa, kt * BK + (s * 256 + tid) / VPRA);
-    }
-    if (!B_K) {
-#pragma unroll
-      for (int s = 0; s < NVB; ++s) rowB[s] = row_index(sb, kt * BK + (s * 256 + tid) / VPRB);
-    }
-  };
-  auto gload = [&](int kt) {
-#pragma unroll
-    for (int s = 0; s < NVA; ++s) {
-      const int c = ((s * 256 + tid) % VPRA) * V + (A_K ? kt * BK : i0);
-      ra[s] = load_masked<T>(sa.base + rowA[s], c, sa.cols, rowA[s] >= 0);
-    }
+    for (int s = 0; s < NVA; ++s) ra[q][s] = load_raw<T>(sa.base + rowA[s], col_a(s, kt), sa.cols);
 #pragma unroll
     for (int s = 0; s < NVB; ++s) {
-      const int c = ((s * 256 + tid) % VPRB) * V + (B_K ? kt * BK : j0);
-      if constexpr (B_STRIDED) rb[s] = load_strided<T>(sb.base + rowB[s], c, g.B.cs, sb.cols, rowB[s] >= 0);
-      else rb[s] = load_masked<T>(sb.base + rowB[s], c, sb.cols, rowB[s] >= 0);
+      if constexpr (B_STRIDED) rb[q][s] = load_strided<T>(sb.base + rowB[s], col_b(s, kt), g.B.cs, sb.cols, rowno_b(s, kt) < sb.rows);
+      else rb[q][s] = load_raw<T>(sb.base + rowB[s], col_b(s, kt), sb.cols);
     }
   };
   // ---- LDS layout.  bf16: 32-deep sub-tiles in the swizzled layouts of mfma_gemm.h.  fp32: [k][x], rows of
@@ -233,14 +257,22 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
       }
     }
   };
-  auto lstore = [&](int slot) {
+  auto lstore = [&](int slot, int q, int kt) {
+    if (kt >= whole_a) {
+#pragma unroll
+      for (int s = 0; s < NVA; ++s) ra[q][s] = mask_raw<T>(ra[q][s], col_a(s, kt), sa.cols, rowno_a(s, kt) < sa.rows);
+    }
+    if (!B_STRIDED && kt >= whole_b) {
+#pragma unroll
+      for (int s = 0; s < NVB; ++s) rb[q][s] = mask_raw<T>(rb[q][s], col_b(s, kt), sb.cols, rowno_b(s, kt) < sb.rows);
+    }
     char* stage = lds + slot * S::STAGE;
 #pragma unroll
     for (int s = 0; s < NVA; ++s)
-      put(stage, ra[s], (s * 256 + tid) / VPRA, (s * 256 + tid) % VPRA, std::integral_constant<int, BM>{}, A_K);
+      put(stage, ra[q][s], (s * NTH + tid) / VPRA, (s * NTH + tid) % VPRA, std::integral_constant<int, BM>{}, A_K);
 #pragma unroll
     for (int s = 0; s < NVB; ++s)
-      put(stage + S::A_BYTES, rb[s], (s * 256 + tid) / VPRB, (s * 256 + tid) % VPRB, std::integral_constant<int, BN>{}, B_K);
+      put(stage + S::A_BYTES, rb[q][s], (s * NTH + tid) / VPRB, (s * NTH + tid) % VPRB, std::integral_constant<int, BN>{}, B_K);
   };
 
   floatx16 acc[TM][TN];
@@ -315,21 +347,29 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   const int k0 = split * g.stages_per_split;
   const int k1 = k0 + g.stages_per_split < g.stages ? k0 + g.stages_per_split : g.stages;
   if (k0 < k1) {
-    rows_at(k0);
-    gload(k0);
-    if (k0 + 1 < k1) next_rows(k0 + 1);
-    lstore(0);
-    __syncthreads();
-    for (int kt = k0; kt < k1; ++kt) {
-      const int slot = (kt - k0) & 1;
-      if (kt + 1 < k1) {
-        gload(kt + 1);
-        if (kt + 2 < k1) next_rows(kt + 2);
+    // stage kt + PF is requested while kt is multiplied: its registers were written to LDS a stage ago
+    rows_at(k0, true);
+#pragma unroll
+    for (int q = 0; q < PF; ++q)
+      if (k0 + q < k1) {
+        gload(k0 + q, q);
+        if (k0 + q + 1 < k1) rows_at(k0 + q + 1, false);
       }
-      multiply(slot);
-      if (kt + 1 < k1) lstore(slot ^ 1);   // read last before the previous barrier
-      __syncthreads();
-    }
+    lstore(0, 0, k0);
+    lds_barrier();
+    for (int kt = k0; kt < k1; kt += PF)
+#pragma unroll
+      for (int q = 0; q < PF; ++q) {
+        if (kt + q >= k1) break;
+        const int slot = (kt + q - k0) & 1;
+        if (kt + q + PF < k1) {
+          gload(kt + q + PF, q);
+          if (kt + q + PF + 1 < k1) rows_at(kt + q + PF + 1, false);
+        }
+        multiply(slot);
+        if (kt + q + 1 < k1) lstore(slot ^ 1, (q + 1) % PF, kt + q + 1);   // read last before the previous barrier
+        lds_barrier();
+      }
   }
 
   if constexpr (WGK > 1) {
@@ -348,24 +388,29 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
             *reinterpret_cast<float4*>(dst + ((a * TN + c) * 4 + q) * 256) =
                 make_float4(acc[a][c][4 * q], acc[a][c][4 * q + 1], acc[a][c][4 * q + 2], acc[a][c][4 * q + 3]);
     }
-    __syncthreads();
-    if (wk > 0) return;
+    lds_barrier();
+    if (wk == 0) {
 #pragma unroll
-    for (int w = 0; w < WGK - 1; ++w) {
-      const float* src = part + (w * WGM * WGN + piece) * TILE_F + lane * 4;
+      for (int w = 0; w < WGK - 1; ++w) {
+        const float* src = part + (w * WGM * WGN + piece) * TILE_F + lane * 4;
 #pragma unroll
-      for (int a = 0; a < TM; ++a)
+        for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int c = 0; c < TN; ++c)
+          for (int c = 0; c < TN; ++c)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float4 p = *reinterpret_cast<const float4*>(src + ((a * TN + c) * 4 + q) * 256);
-            acc[a][c][4 * q] += p.x;
-            acc[a][c][4 * q + 1] += p.y;
-            acc[a][c][4 * q + 2] += p.z;
-            acc[a][c][4 * q + 3] += p.w;
-          }
+            for (int q = 0; q < 4; ++q) {
+              const float4 p = *reinterpret_cast<const float4*>(src + ((a * TN + c) * 4 + q) * 256);
+              acc[a][c][4 * q] += p.x;
+              acc[a][c][4 * q + 1] += p.y;
+              acc[a][c][4 * q + 2] += p.z;
+              acc[a][c][4 * q + 3] += p.w;
+            }
+      }
     }
+    // the areas below overlap the partial tiles of other pieces: every wave has read its own
+    if (WGM * WGN > 1) lds_barrier();
+    else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (wk > 0) return;
   }
 
   // A lane holds one output row and four columns per register group: written like that, an instruction would touch
@@ -374,10 +419,6 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   // epilogue's loads and stores (8192 x 4090 apply at b = 256: 105 -> 94 us).
   constexpr int CW = TN * 32, LDC = CW + 4, LPR = CW / 8, RPP = 64 / LPR;
   float* stg = reinterpret_cast<float*>(lds) + wave * (32 * LDC);
-  if constexpr (WGK > 1) {
-    // waves 1 .. of a split contraction are gone; the partial tiles they left were read by this wave itself
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  }
 #pragma unroll
   for (int a = 0; a < TM; ++a) {
 #pragma unroll
@@ -398,25 +439,25 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   }
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
-__global__ __launch_bounds__(256) void edge_kernel(Args g, Epi epi, int total, int first) {
-  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi, B_STRIDED>(g, epi, first + (int)blockIdx.x, total, blockIdx.y);
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
+__global__ __launch_bounds__((Shape<T, BM, BN, BK, WGM, WGN, WAVES>::THREADS)) void edge_kernel(Args g, Epi epi, int total, int first) {
+  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, B_STRIDED>(g, epi, first + (int)blockIdx.x, total, blockIdx.y);
 }
 
 // Two problems of one shape in one launch: the first n0 workgroups of a row of the grid take g0, the rest g1.
-template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
-__global__ __launch_bounds__(256) void edge_pair_kernel(Args g0, Args g1, Epi e0, Epi e1, int n0, int total, int first) {
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi>
+__global__ __launch_bounds__((Shape<T, BM, BN, BK, WGM, WGN, WAVES>::THREADS)) void edge_pair_kernel(Args g0, Args g1, Epi e0, Epi e1, int n0, int total, int first) {
   const int bx = first + (int)blockIdx.x;
   const bool second = bx >= n0;
   const Args g = second ? g1 : g0;
   const Epi epi = second ? e1 : e0;
   const int split = blockIdx.y;
   if (split * g.stages_per_split >= g.stages) return;
-  edge_product<T, BM, BN, BK, WGM, WGN, A_K, B_K>(g, epi, second ? bx - n0 : bx, second ? total - n0 : n0, split);
+  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K>(g, epi, second ? bx - n0 : bx, second ? total - n0 : n0, split);
 }
 
 // ---- host side -------------------------------------------------------------------------------
-enum Tile { TILE_32 = 0, TILE_64 = 1, TILE_128 = 2 };
+enum Tile { TILE_32 = 0, TILE_64 = 1, TILE_128 = 2, TILE_64D = 3 };   // 64D: 64 x 64, deeper stages, sixteen waves (fp32 dense products)
 
 struct Plan {
   Tile tile;
@@ -427,7 +468,7 @@ constexpr int kCUs = 256;
 
 inline i64 tile_count(i64 batches, i64 M, i64 N, int t) { return batches * ((M + t - 1) / t) * ((N + t - 1) / t); }
 // contraction depth of a stage; fp32 halves it, which keeps as many workgroups per CU as in bf16
-constexpr int stage_depth(Tile t, size_t es) { return (t == TILE_32 ? 128 : 64) * 2 / (int)es; }
+constexpr int stage_depth(Tile t, size_t es) { return (t == TILE_32 || t == TILE_64D ? 128 : 64) * 2 / (int)es; }
 
 struct Problem {
   i64 batches, M, N, K;
@@ -440,10 +481,10 @@ inline void tile_args(Args& g, const Problem& q, int BM, int BN, int BK, int spl
   g.stages_per_split = ceil_div(g.stages, splits);
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi>
 void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, int s0, int s1, hipStream_t st) {
-  using S = Shape<T, BM, BN, BK, WGM, WGN>;
-  auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi>;
+  using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
+  auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi>;
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
   (void)configured;
@@ -451,14 +492,14 @@ void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, cons
   tile_args(g1, q1, BM, BN, BK, s1);
   const i64 n0 = q0.batches * g0.tiles_m * g0.tiles_n, n1 = q1.batches * g1.tiles_m * g1.tiles_n;
   launch_in_rows(n0 + n1, [&](int first, unsigned count) {
-    hipLaunchKernelGGL(kern, dim3(count, (unsigned)(s0 > s1 ? s0 : s1)), dim3(256), S::LDS, st, g0, g1, e0, e1, (int)n0, (int)(n0 + n1), first);
+    hipLaunchKernelGGL(kern, dim3(count, (unsigned)(s0 > s1 ? s0 : s1)), dim3(S::THREADS), S::LDS, st, g0, g1, e0, e1, (int)n0, (int)(n0 + n1), first);
   });
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, bool A_K, bool B_K, bool B_STRIDED = false, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, bool B_STRIDED = false, class Epi>
 void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits, hipStream_t st) {
-  using S = Shape<T, BM, BN, BK, WGM, WGN>;
-  auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, A_K, B_K, Epi, B_STRIDED>;
+  using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
+  auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, B_STRIDED>;
   // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
@@ -466,25 +507,31 @@ void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits,
   tile_args(g, Problem{batches, M, N, K}, BM, BN, BK, splits);
   const i64 total = batches * g.tiles_m * g.tiles_n;
   launch_in_rows(total, [&](int first, unsigned count) {
-    hipLaunchKernelGGL(kern, dim3(count, (unsigned)splits), dim3(256), S::LDS, st, g, epi, (int)total, first);
+    hipLaunchKernelGGL(kern, dim3(count, (unsigned)splits), dim3(S::THREADS), S::LDS, st, g, epi, (int)total, first);
   });
 }
 
-template <class T, bool A_K, bool B_K, class Epi>
+// LONG: a long contraction (dense products).  Its larger tiles have twice the waves, halves of which split every stage: what bounds the plain
+// ones are the latencies of one or two waves per SIMD (fp32 1024 x 1024 x 2048, 64 x 64: 53.0 -> 49.2 us; bf16 1024 x 1536 x 3001, 128 x 128: 44 -> 33).
+// Contractions of a block or of a token range gain nothing.
+template <class T, bool A_K, bool B_K, bool LONG = false, class Epi>
 void launch(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, Plan p, hipStream_t st) {
-  constexpr int D = 128 / (int)sizeof(T);   // stage_depth
-  if (p.tile == TILE_128) launch_shape<T, 128, 128, D, 2, 2, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
-  else if (p.tile == TILE_64) launch_shape<T, 64, 64, D, 2, 2, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
-  else launch_shape<T, 32, 32, 2 * D, 1, 1, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  constexpr int D = 128 / (int)sizeof(T), W = LONG ? 8 : 4;   // stage_depth
+  if constexpr (LONG && sizeof(T) == 4) {
+    if (p.tile == TILE_64D) return launch_shape<T, 64, 64, 2 * D, 2, 2, 16, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  }
+  if (p.tile == TILE_128) launch_shape<T, 128, 128, D, 2, 2, W, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else if (p.tile == TILE_64) launch_shape<T, 64, 64, D, 2, 2, W, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else launch_shape<T, 32, 32, 2 * D, 1, 1, sizeof(T) == 4 ? W : 4, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
 }
 
 // two problems planned onto the same tile
 template <class T, bool A_K, bool B_K, class Epi>
 void launch_pair(const Args& g0, const Args& g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, Plan p0, Plan p1, hipStream_t st) {
   constexpr int D = 128 / (int)sizeof(T);
-  if (p0.tile == TILE_128) launch_pair_shape<T, 128, 128, D, 2, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
-  else if (p0.tile == TILE_64) launch_pair_shape<T, 64, 64, D, 2, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
-  else launch_pair_shape<T, 32, 32, 2 * D, 1, 1, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  if (p0.tile == TILE_128) launch_pair_shape<T, 128, 128, D, 2, 2, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  else if (p0.tile == TILE_64) launch_pair_shape<T, 64, 64, D, 2, 2, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  else launch_pair_shape<T, 32, 32, 2 * D, 1, 1, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
 }
 
 }  // namespace edge

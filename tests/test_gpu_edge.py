@@ -25,6 +25,10 @@ pytestmark = pytest.mark.gpu
     (72, 2050, 17, 72, 2),      # the same in the backward direction
     (640, 1376, 2047, 64, 2),   # 128-wide tiles, every extent ragged
     (512, 256, 1000, 256, 2),   # large blocks, token count a multiple of 8 only
+    # 64-wide tiles whose waves split the stages, sixteen of them in fp32; backward split over workgroups.  (A tail block of side 2 would have
+    # one parameter: its gradient, one sum of rounded products, has no bound relative to itself where they cancel.)
+    (768, 1096, 1001, 64, 2),
+    (2000, 2040, 2001, 40, 1),  # 128-wide ones with eight
 ])
 def test_layer_at_tile_edges(lib, m, n, N, b, k, dtype):
     data = synth_layer(9000 + m + n + N + b, m, n, N, b, k, dtype, 0.01)

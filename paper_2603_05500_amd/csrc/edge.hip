@@ -23,25 +23,37 @@ Tile apply_tile(i64 batches, i64 M, i64 N) {
 }
 
 // Dense products: tile and contraction split priced together.  A workgroup takes `lone` us for a stage when it has a CU to itself and
-// `shared` when more of them fill it; a split adds its fp32 parts, written and read at 4 TB/s, and a launch of 2.5 us.  Measured, us,
-// tile / splits (64D: 64 x 64 with sixteen waves): fp32 1024 x 768 x 1001 32/1 29.0, 64/1 29.9, 64/2 27.6, 64/4 27.8, 64D/1 25.4,
-// 128/4 32.8 (the rule before took 64/2 of four waves: 30.7); its transpose product 27.3, 37.7, 32.5, 26.6, 29.8, 36.6; 256 x 256 x 512 32/1 6.0,
-// 32/2 7.7 (the choice before); bf16 512 x 1376 x 1024 32/1 10.7, 32/2 13.9 (before), 64D/1 10.6 (but 18.0 against 14.1 for 1024 x 1024 x 2000); 1024 x 1536 x 3001 32/1 55.6, 64/1 27.0, 128/2 37 - 43 (before).
+// `shared` for each of the workgroups on its CU, of which the fullest CU counts, in bf16's shorter stages the mean; `fill` stages more to
+// fill the ring and to store.  A split adds a launch of `reduce` us with its gap and its fp32 parts, written and read at 4 TB/s.  The constants are
+// fitted to 570 products of 128 - 1536 rows, 16 - 4096 tokens and contractions of 128 - 1536, each timed with every tile and split: the
+// choice is 1 % slower than the best one on average and at most 12 % slower than that of the rule before, which took the tile first (four waves
+// each) and then the split, and is 10 % (bf16 22 %) slower than the best.  us, tile / splits (64D: 64 x 64 with sixteen waves): fp32 1024 x 768 x 1001
+// 32/1 29.0, 64/1 29.9, 64/2 27.6, 64/4 27.8, 64D/1 25.4, 128/4 32.8 (before: 64/2 at 30.7); 256 x 256 x 512 32/1 6.0, 32/2 7.7 (before); bf16
+// 512 x 1376 x 1024 32/1 10.7, 32/2 13.9 (before), 64/1 12.5; 1024 x 1536 x 3001 32/1 55.6, 64/1 27.0, 128/2 37 - 43 (before).
+struct TileCost {
+  Tile tile;
+  int side;
+  double lone, shared;
+  bool mean;
+};
 Plan dense_plan(int dtype, i64 M, i64 N, i64 K) {
-  struct Cost { Tile tile; int side; double lone, shared; };
-  static const Cost f32[] = {{TILE_32, 32, 0.75, 0.52}, {TILE_64, 64, 1.1, 0.6}, {TILE_64D, 64, 1.75, 1.4}, {TILE_128, 128, 2.8, 2.2}};
-  static const Cost bf16[] = {{TILE_32, 32, 0.42, 0.31}, {TILE_64, 64, 0.42, 0.33}, {TILE_128, 128, 1.1, 1.1}};
-  const size_t es = dtype == POETX_F32 ? 4 : 2;
+  static const TileCost f32[] = {{TILE_32, 32, 0.72, 0.52, false}, {TILE_64, 64, 1.47, 0.61, false}, {TILE_64D, 64, 1.58, 1.39, false}, {TILE_128, 128, 2.93, 2.19, false}};
+  static const TileCost bf16[] = {{TILE_32, 32, 0.46, 0.33, true}, {TILE_64, 64, 0.52, 0.32, true}, {TILE_128, 128, 0.97, 0.94, false}};
+  const bool f = dtype == POETX_F32;
+  const double fill = f ? 3.5 : 0.6, reduce = f ? 2.3 : 2.1;
+  const size_t es = f ? 4 : 2;
   Plan best{TILE_32, 1};
   double least = 0;
-  for (int t = 0; t < (dtype == POETX_F32 ? 4 : 3); ++t) {
-    const Cost& c = dtype == POETX_F32 ? f32[t] : bf16[t];
+  for (int t = 0; t < (f ? 4 : 3); ++t) {
+    const TileCost& c = f ? f32[t] : bf16[t];
     const i64 count = tile_count(1, M, N, c.side), depth = stage_depth(c.tile, es), stages = (K + depth - 1) / depth;
-    for (i64 s = 1; s <= 16 && (s == 1 || (stages / s >= 2 && count * s <= 4 * kCUs)); s += s < 4 ? 1 : s / 2) {
+    for (const int s : {1, 2, 3, 4, 6, 8, 12, 16}) {
+      if (s > 1 && (stages / s < 2 || count * s > 8 * kCUs)) break;
       const i64 per = (stages + s - 1) / s, splits = (stages + per - 1) / per;   // no empty split
-      const double fill = (double)((count * splits + kCUs - 1) / kCUs) * c.shared;
-      double us = per * (c.lone > fill ? c.lone : fill);
-      if (splits > 1) us += 2.5 + 8e-6 / 4 * splits * (double)M * (double)N;
+      const double on_cu = c.mean ? (double)(count * splits) / kCUs : (double)((count * splits + kCUs - 1) / kCUs);
+      const double stage = on_cu * c.shared;
+      double us = ((double)per + fill) * (c.lone > stage ? c.lone : stage);
+      if (splits > 1) us += reduce + 8e-6 / 4 * (double)splits * (double)M * (double)N;
       if (least == 0 || us < least) { least = us; best = Plan{c.tile, (int)splits}; }
     }
   }
@@ -189,13 +201,13 @@ void dense_t(int dtype, int trans_w, const T* W, int n, int m, const T* act, i64
   g.B = Op{act, ld_act, 0, nullptr, K, (int)N, 0, 0};
   if (p.splits > 1) {
     const EpiPartial epi{(float*)ws, M, (int)N, 1};
-    if (trans_w) launch<T, false, false, true>(g, epi, 1, M, N, K, p, st);
-    else launch<T, true, false, true>(g, epi, 1, M, N, K, p, st);
+    if (trans_w) launch<T, false, false, DENSE>(g, epi, 1, M, N, K, p, st);
+    else launch<T, true, false, DENSE>(g, epi, 1, M, N, K, p, st);
     reduce<T>((const float*)ws, M, N, p.splits, out, ld_out, st);
   } else {
     const EpiStore<T> epi{out, ld_out, M, (int)N};
-    if (trans_w) launch<T, false, false, true>(g, epi, 1, M, N, K, p, st);
-    else launch<T, true, false, true>(g, epi, 1, M, N, K, p, st);
+    if (trans_w) launch<T, false, false, DENSE>(g, epi, 1, M, N, K, p, st);
+    else launch<T, true, false, DENSE>(g, epi, 1, M, N, K, p, st);
   }
 }
 
@@ -211,11 +223,11 @@ void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out
   const EpiScatter<T> epi{out, V, ldo, ldv, perm, b, d, (int)cols, (int)cols_out};
   if constexpr (sizeof(T) == 2) {   // pairs (E, E^T): op(E) has contiguous rows either way
     g.A = Op{blocks + (trans ? (i64)b * b : 0), b, 2ll * b * b, nullptr, b, b, 1, 1};
-    launch<T, true, false>(g, epi, nb, b, cols_out, b, p, st);
+    launch<T, true, false, APPLY>(g, epi, nb, b, cols_out, b, p, st);
   } else {
     g.A = Op{blocks, b, (i64)b * b, nullptr, b, b, 1, 1};
-    if (trans) launch<T, false, false>(g, epi, nb, b, cols_out, b, p, st);
-    else launch<T, true, false>(g, epi, nb, b, cols_out, b, p, st);
+    if (trans) launch<T, false, false, APPLY>(g, epi, nb, b, cols_out, b, p, st);
+    else launch<T, true, false, APPLY>(g, epi, nb, b, cols_out, b, p, st);
   }
 }
 
@@ -224,7 +236,6 @@ void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out
 template <class T, bool V_TM, bool OUT_TM>
 void apply_tokens_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out, const int32_t* perm, const T* blocks, int b, int trans,
                     hipStream_t st) {
-  constexpr int D = stage_depth(TILE_32, sizeof(T));
   const int nb = ceil_div(d, b);
   Args g{};
   g.rpb = b;
@@ -234,11 +245,11 @@ void apply_tokens_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 c
   const EpiScatterTokens<T, V_TM, OUT_TM> epi{out, V, ldo, ldv, perm, b, d, (int)cols, (int)cols_out};
   if constexpr (sizeof(T) == 2) {
     g.A = Op{blocks + (trans ? (i64)b * b : 0), b, 2ll * b * b, nullptr, b, b, 1, 1};
-    launch_shape<T, 32, 32, D, 1, 1, 4, true, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
+    launch_apply_32<T, true, false, V_TM>(g, epi, nb, b, cols_out, b, st);
   } else {
     g.A = Op{blocks, b, (i64)b * b, nullptr, b, b, 1, 1};
-    if (trans) launch_shape<T, 32, 32, D, 1, 1, 4, false, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
-    else launch_shape<T, 32, 32, D, 1, 1, 4, true, false, V_TM>(g, epi, nb, b, cols_out, b, 1, st);
+    if (trans) launch_apply_32<T, false, false, V_TM>(g, epi, nb, b, cols_out, b, st);
+    else launch_apply_32<T, true, false, V_TM>(g, epi, nb, b, cols_out, b, st);
   }
 }
 
@@ -258,7 +269,7 @@ Args grad_args(const GradProblem& q, int b) {
 template <class T>
 void grad_t(const Plan& p, const GradProblem& q, int b, hipStream_t st) {
   const int nb = ceil_div(q.d, b);
-  launch<T, true, true>(grad_args<T>(q, b), EpiPartial{q.parts, b, b, nb}, nb, b, b, q.N, p, st);
+  launch<T, true, true, GRAD>(grad_args<T>(q, b), EpiPartial{q.parts, b, b, nb}, nb, b, b, q.N, p, st);
 }
 template <class T>
 void grad_pair_t(const Plan& p0, const Plan& p1, const GradProblem& q0, const GradProblem& q1, int b, hipStream_t st) {

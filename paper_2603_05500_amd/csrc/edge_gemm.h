@@ -97,6 +97,21 @@ __device__ __forceinline__ u32x4 load_masked(const T* row, int c, int cols, bool
   return mask_raw<T>(load_raw<T>(row, c, cols), c, cols, row_ok);
 }
 
+// the same with a branch per lane, in as few registers
+__device__ __forceinline__ u32x4 load_branched(const uint16_t* row, int c, int cols) {
+  u32x4 v = {0, 0, 0, 0};
+  if (c >= cols) return v;
+  if (cols - c >= 8) return load16(row + c);   // no sum: the last column may be the last int
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    uint32_t x = 0;
+    if (2 * w < cols - c) x = row[c + 2 * w];
+    if (2 * w + 1 < cols - c) x |= (uint32_t)row[c + 2 * w + 1] << 16;
+    v[w] = x;
+  }
+  return v;
+}
+
 // the same with columns cs elements apart
 template <class T>
 __device__ inline u32x4 load_strided(const T* row, int c, i64 cs, int cols, bool row_ok) {
@@ -165,13 +180,12 @@ struct Shape {
 
 // Epi: __device__ void operator()(int batch, int split, int row, int col, const float (&v)[8]) -- eight
 // consecutive columns of one output row, indices inside the batch; it does its own masking.
-// bx of total: this workgroup among those of the problem.
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
+// bx of total: this workgroup among those of the problem.  PF: stages whose loads are in flight.
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
 __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int bx, int total, int split) {
   using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
   constexpr int V = 16 / sizeof(T), WGK = S::WGK, TM = S::TM, TN = S::TN;
   constexpr bool BF = sizeof(T) == 2;
-  constexpr int PF = 2;            // stages whose loads are in flight
   constexpr int NTH = S::THREADS, NVA = BM * BK / V / NTH, NVB = BN * BK / V / NTH;
   static_assert(NVA >= 1 && NVB >= 1, "tile too small");
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -439,13 +453,13 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   }
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
 __global__ __launch_bounds__((Shape<T, BM, BN, BK, WGM, WGN, WAVES>::THREADS)) void edge_kernel(Args g, Epi epi, int total, int first) {
-  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, B_STRIDED>(g, epi, first + (int)blockIdx.x, total, blockIdx.y);
+  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, PF, A_K, B_K, Epi, B_STRIDED>(g, epi, first + (int)blockIdx.x, total, blockIdx.y);
 }
 
 // Two problems of one shape in one launch: the first n0 workgroups of a row of the grid take g0, the rest g1.
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, class Epi>
 __global__ __launch_bounds__((Shape<T, BM, BN, BK, WGM, WGN, WAVES>::THREADS)) void edge_pair_kernel(Args g0, Args g1, Epi e0, Epi e1, int n0, int total, int first) {
   const int bx = first + (int)blockIdx.x;
   const bool second = bx >= n0;
@@ -453,7 +467,7 @@ __global__ __launch_bounds__((Shape<T, BM, BN, BK, WGM, WGN, WAVES>::THREADS)) v
   const Epi epi = second ? e1 : e0;
   const int split = blockIdx.y;
   if (split * g.stages_per_split >= g.stages) return;
-  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K>(g, epi, second ? bx - n0 : bx, second ? total - n0 : n0, split);
+  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, PF, A_K, B_K>(g, epi, second ? bx - n0 : bx, second ? total - n0 : n0, split);
 }
 
 // ---- host side -------------------------------------------------------------------------------
@@ -481,10 +495,10 @@ inline void tile_args(Args& g, const Problem& q, int BM, int BN, int BK, int spl
   g.stages_per_split = ceil_div(g.stages, splits);
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, class Epi>
 void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, int s0, int s1, hipStream_t st) {
   using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
-  auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi>;
+  auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, PF, A_K, B_K, Epi>;
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
   (void)configured;
@@ -496,10 +510,10 @@ void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, cons
   });
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, bool B_STRIDED = false, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, bool B_STRIDED = false, class Epi>
 void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits, hipStream_t st) {
   using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
-  auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, B_STRIDED>;
+  auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, WAVES, PF, A_K, B_K, Epi, B_STRIDED>;
   // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
   static const bool configured =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
@@ -511,27 +525,39 @@ void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits,
   });
 }
 
-// LONG: a long contraction (dense products).  Its larger tiles have twice the waves, halves of which split every stage: what bounds the plain
-// ones are the latencies of one or two waves per SIMD (fp32 1024 x 1024 x 2048, 64 x 64: 53.0 -> 49.2 us; bf16 1024 x 1536 x 3001, 128 x 128: 44 -> 33).
-// Contractions of a block or of a token range gain nothing.
-template <class T, bool A_K, bool B_K, bool LONG = false, class Epi>
+// Applies on the smallest tile: the contraction is a block, and a stage no deeper than it (masked halves of a stage cost a launch
+// some 0.4 us).
+template <class T, bool A_K, bool B_K, bool B_STRIDED = false, class Epi>
+void launch_apply_32(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, hipStream_t st) {
+  constexpr int D = 128 / (int)sizeof(T);
+  if (K > D) launch_shape<T, 32, 32, 2 * D, 1, 1, 4, 1, A_K, B_K, B_STRIDED>(g, epi, batches, M, N, K, 1, st);
+  else if constexpr (sizeof(T) == 4) launch_shape<T, 32, 32, D, 1, 1, 4, 1, A_K, B_K, B_STRIDED>(g, epi, batches, M, N, K, 1, st);
+  else launch_shape<T, 32, 32, D, 1, 1, 2, 1, A_K, B_K, B_STRIDED>(g, epi, batches, M, N, K, 1, st);
+}
+
+// What a product is for.  Dense products (long contractions) have twice the waves on their larger tiles, halves of which split every stage: what
+// bounds the plain ones are the latencies of one or two waves per SIMD (fp32 1024 x 1024 x 2048, 64 x 64: 53.0 -> 49.2 us; bf16 1024 x 1536 x 3001,
+// 128 x 128: 44 -> 33; block gradients on 128 x 128 lose: 69 -> 95).  Applies (a stage or two) look one stage ahead only: two cost them 0.4 us.
+enum Use { APPLY = 0, DENSE = 1, GRAD = 2 };
+template <class T, bool A_K, bool B_K, Use USE, class Epi>
 void launch(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, Plan p, hipStream_t st) {
-  constexpr int D = 128 / (int)sizeof(T), W = LONG ? 8 : 4;   // stage_depth
-  if constexpr (LONG && sizeof(T) == 4) {
-    if (p.tile == TILE_64D) return launch_shape<T, 64, 64, 2 * D, 2, 2, 16, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  constexpr int D = 128 / (int)sizeof(T), W = USE == DENSE ? 8 : 4, PF = USE == APPLY ? 1 : 2;   // D: stage_depth
+  if constexpr (USE == DENSE && sizeof(T) == 4) {
+    if (p.tile == TILE_64D) return launch_shape<T, 64, 64, 2 * D, 2, 2, 16, PF, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
   }
-  if (p.tile == TILE_128) launch_shape<T, 128, 128, D, 2, 2, W, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
-  else if (p.tile == TILE_64) launch_shape<T, 64, 64, D, 2, 2, W, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
-  else launch_shape<T, 32, 32, 2 * D, 1, 1, sizeof(T) == 4 ? W : 4, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  if (p.tile == TILE_128) launch_shape<T, 128, 128, D, 2, 2, W, PF, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else if (p.tile == TILE_64) launch_shape<T, 64, 64, D, 2, 2, W, PF, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else if constexpr (USE == APPLY) launch_apply_32<T, A_K, B_K>(g, epi, batches, M, N, K, st);
+  else launch_shape<T, 32, 32, 2 * D, 1, 1, sizeof(T) == 4 ? W : 4, PF, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
 }
 
 // two problems planned onto the same tile
 template <class T, bool A_K, bool B_K, class Epi>
 void launch_pair(const Args& g0, const Args& g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, Plan p0, Plan p1, hipStream_t st) {
   constexpr int D = 128 / (int)sizeof(T);
-  if (p0.tile == TILE_128) launch_pair_shape<T, 128, 128, D, 2, 2, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
-  else if (p0.tile == TILE_64) launch_pair_shape<T, 64, 64, D, 2, 2, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
-  else launch_pair_shape<T, 32, 32, 2 * D, 1, 1, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  if (p0.tile == TILE_128) launch_pair_shape<T, 128, 128, D, 2, 2, 4, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  else if (p0.tile == TILE_64) launch_pair_shape<T, 64, 64, D, 2, 2, 4, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  else launch_pair_shape<T, 32, 32, 2 * D, 1, 1, 4, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
 }
 
 }  // namespace edge

@@ -267,19 +267,30 @@ __global__ __launch_bounds__(512) void apply_left_ragged_kernel(const uint16_t* 
   const int li = lane & 31, h = lane >> 5;
 
   i64 goff[IPW];
-  int gcol[IPW];
 #pragma unroll
-  for (int s = 0; s < IPW; ++s) {
-    const int k = (wave * IPW + s) * RPI + lane / CPR;
-    goff[s] = (i64)pm[k] * ldv;
-    gcol[s] = tok0 + mm::kx_unchunk<BN>(lane % CPR, k) * 8;
-  }
+  for (int s = 0; s < IPW; ++s) goff[s] = (i64)pm[(wave * IPW + s) * RPI + lane / CPR] * ldv;
+  const int gcol = tok0 + mm::kx_unchunk<BN>(lane % CPR, lane / CPR) * 8;   // the swizzle repeats after RPI rows
   edge::u32x4 stage_regs[IPW];
+  // Whole tiles without masks, the last one masked on its way into LDS: where it is loaded that would wait for the loads (2048 x 5632, 1999
+  // tokens, b = 256: 21.3 and 15.7 -> 20.5 and 12.8 us).  b = 512 has no registers for that: masked by branches around the loads (4001 tokens of 8192 x 3072,
+  // forward 303 us so, 316 the other way).
   auto gload = [&](int t) {
+    if constexpr (B == 512) {
 #pragma unroll
-    for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load_masked<uint16_t>(V + goff[s], gcol[s] + t * BN, nv, true);
+      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load_branched(V + goff[s], gcol + t * BN, nv);
+    } else if (tok0 + (t + 1) * BN <= nv) {
+#pragma unroll
+      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load16(V + goff[s] + gcol + t * BN);
+    } else {
+#pragma unroll
+      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load_raw<uint16_t>(V + goff[s], gcol + t * BN, nv);
+    }
   };
   auto lstore = [&](int t) {
+    if (B != 512 && tok0 + (t + 1) * BN > nv) {
+#pragma unroll
+      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::mask_raw<uint16_t>(stage_regs[s], gcol + t * BN, nv, true);
+    }
     char* stage = ring + (t & 1) * STAGE_BYTES + wave * IPW * 1024 + lane * 16;
 #pragma unroll
     for (int s = 0; s < IPW; ++s) *reinterpret_cast<edge::u32x4*>(stage + s * 1024) = stage_regs[s];

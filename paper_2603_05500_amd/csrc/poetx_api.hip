@@ -65,8 +65,8 @@ int check_desc(const poetx_linear_desc* d) {
   return POETX_OK;
 }
 
-// dG plus the chain's scratch of nb blocks: five floats per element cover the tiled kernel families, k + 2 the on-chip chains
-// (checked against what those lay out)
+// dG plus the chain's scratch of nb blocks: max(k + 2, 5) floats per element, more than any of the kernel families
+// lays out now (the tiled ones five, the on-chip chain two); the figure stays, as callers size workspaces by it
 size_t cnp_bwd_ws_floats(i64 nb, int b, int k) {
   const size_t elems = (size_t)nb * b * b;
   size_t chain = (size_t)(k + 2 > 5 ? k + 2 : 5) * elems;
@@ -167,10 +167,11 @@ bool bwd_one_pass(const poetx_linear_desc* d) {
          internal_columns(d) == N && mfma_apply_grad_supported(d->d_in, N, N, d->block) && mfma_apply_grad_supported(d->d_out, N, N, d->block);
 }
 
-// Few token-major tokens: the forward's applies read X and write Z as they are, element by element, where the two
+// Few token-major tokens outside few_tokens(): the forward's applies read X and write Z as they are, element by element, where the two
 // transposing launches (some 5 us each) would cost more.  Every 32 rows of a block read the whole block's features
 // again, so the element reads are in proportion to (n + m) N b; the workgroups of b = 512 are besides a chain of four
-// dependent stages, and lose from half of that on.  bf16 forwards, us, with transposes / in place: 2048 x 2048, b = 256:
+// dependent stages, and lose from half of that on.  bf16 forwards, us, with transposes / in place (the smallest token counts of
+// these shapes now belong to few_tokens(), which is faster than either): 2048 x 2048, b = 256:
 // 29.7 / 21.0 for one token, 32.3 / 28.7 for 16, 38.2 / 34.5 for 31, 25.7 / 31.2 for 64 (bf16 transposes
 // of whole 64-token tiles are half as dear; 1024 x 1024, b = 128, 128 tokens: 21.8 / 25.2); 512 x 1376, b = 64: 27.5 / 21.6 for 16, 29.1 / 24.9 for 200; 4096 x 14336, b = 512:
 // 57.6 / 50.8 for one, 62.7 / 60.2 for three, 53.7 / 63.5 for 16; 4096 x 4096, b = 512, 8 tokens: 39.5 / 46.6.

@@ -142,7 +142,8 @@ void mfma_apply_grad(const void* V, const void* U, void* out, int d, i64 N, i64 
 bool mfma_cnp_supported(int d, int b);
 void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void* E_bf16, float* ws,
                     hipStream_t st);
-// One or two sides whose dG (one matrix per block, nsplit = 1) follow each other in memory; ws: max(k + 2, 5) floats per element.
+// One or two sides whose dG (one matrix per block, nsplit = 1) follow each other in memory; ws: 5 floats per element
+// (tiled), 2 (on chip).
 void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumulate, float* ws, hipStream_t st);
 // b = 256: whole chain of a block in one launch, block resident on chip (mfma_cnp_lds.hip).
 bool lds_cnp_supported(int d, int b);

@@ -414,8 +414,8 @@ def test_block_counts_beyond_one_grid_dimension(lib):
     (512, 60, 30),      # groups 64 + 26: the P side ends inside the first group, the R side goes on in the second
     (512, 16, 70),      # the P side ends inside the second group
     (512, 20, 64),      # exactly at the boundary
-    (256, 100, 60),     # groups 80 + 80: the boundary inside the first
-    (256, 20, 140),     # inside the second
+    (256, 100, 60),     # the sides' boundary early in the one launch over all blocks
+    (256, 20, 140),     # late in it
 ])
 def test_series_groups_of_two_sides(lib, b, nbR, nbP):
     """The series backward of both sides of a layer in one batch of several groups of blocks: packed gradients bit for bit those

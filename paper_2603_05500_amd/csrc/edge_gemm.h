@@ -243,8 +243,8 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   };
   // Stages up to here are whole and need no mask.  The others are masked on their way into LDS, not where they are loaded: that would wait for
   // the load, and the workgroups at the edges are the last to finish.
-  const int whole_a = i0 + BM <= (A_K ? sa.rows : sa.cols) ? (A_K ? sa.cols : sa.rows) / BK : 0;
-  const int whole_b = j0 + BN <= (B_K ? sb.rows : sb.cols) ? (B_K ? sb.cols : sb.rows) / BK : 0;
+  const int whole_a = tile_inside(i0, BM, A_K ? sa.rows : sa.cols) ? (A_K ? sa.cols : sa.rows) / BK : 0;
+  const int whole_b = tile_inside(j0, BN, B_K ? sb.rows : sb.cols) ? (B_K ? sb.cols : sb.rows) / BK : 0;
   auto gload = [&](int kt, int q) {
 #pragma unroll
     for (int s = 0; s < NVA; ++s) ra[q][s] = load_raw<T>(sa.base + rowA[s], col_a(s, kt), sa.cols);

@@ -278,7 +278,7 @@ __global__ __launch_bounds__(512) void apply_left_ragged_kernel(const uint16_t* 
     if constexpr (B == 512) {
 #pragma unroll
       for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load_branched(V + goff[s], gcol + t * BN, nv);
-    } else if (tok0 + (t + 1) * BN <= nv) {
+    } else if (tile_inside(tok0 + t * BN, BN, nv)) {
 #pragma unroll
       for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load16(V + goff[s] + gcol + t * BN);
     } else {
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(512) void apply_left_ragged_kernel(const uint16_t* 
     }
   };
   auto lstore = [&](int t) {
-    if (B != 512 && tok0 + (t + 1) * BN > nv) {
+    if (B != 512 && !tile_inside(tok0 + t * BN, BN, nv)) {
 #pragma unroll
       for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::mask_raw<uint16_t>(stage_regs[s], gcol + t * BN, nv, true);
     }

@@ -74,6 +74,11 @@ inline void launch_in_rows(i64 total, F launch) {
   for (i64 first = 0; first < total; first += row) launch((int)first, (unsigned)(total - first < row ? total - first : row));
 }
 
+// Do the `width` rows or columns from `start` on lie inside an extent?  No sum: counts go up to the last int, where the end of the last tile is beyond it.
+__host__ __device__ constexpr bool tile_inside(int start, int width, int extent) { return start <= extent - width; }
+static_assert(!tile_inside(0x7fffff80, 128, 0x7ffffffb) && tile_inside(0x7fffff00, 128, 0x7ffffffb) && tile_inside(0, 128, 128) && !tile_inside(0, 128, 127),
+              "the last tile of 2^31 - 5 columns is no whole one");
+
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Convert the status of the launches enqueued so far into a poetx_status.

@@ -104,7 +104,7 @@ struct EpiPartial {         // fp32 [split][batch][M][N]
 // Rows scattered through the permutation.  For bf16 blocks (stored as G - I) the identity part is added
 // here in fp32 from the very row that gathered it; `valid` is the number of input columns, columns from
 // there to `cols` are written as zeros.
-template <class T>
+template <class T, Load LOAD>
 struct EpiScatter {
   T* out;
   const T* V;
@@ -116,7 +116,9 @@ struct EpiScatter {
     if (row >= b || r >= d || col >= cols) return;
     const i64 at = perm[r];
     if constexpr (sizeof(T) == 2) {
-      const u32x4 x = load_masked<uint16_t>(V + at * ldv, col, valid, true);
+      u32x4 x;
+      if constexpr (LOAD == MASKED) x = mask_raw(load_raw(V + at * ldv, col, valid), col, valid, true);
+      else x = load_branched(V + at * ldv, col, valid, true);
       float w[8];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -198,7 +200,7 @@ void dense_t(int dtype, int trans_w, const T* W, int n, int m, const T* act, i64
   const Plan p = dense_plan(dtype, M, act_cols, K);
   Args g{};
   g.A = Op{W, m, 0, nullptr, n, m, 0, 0};
-  g.B = Op{act, ld_act, 0, nullptr, K, (int)N, 0, 0};
+  g.B = Op{act, ld_act, 0, nullptr, K, (int)act_cols, 0, 0};   // whole vectors: columns from N on are not stored
   if (p.splits > 1) {
     const EpiPartial epi{(float*)ws, M, (int)N, 1};
     if (trans_w) launch<T, false, false, DENSE>(g, epi, 1, M, N, K, p, st);
@@ -211,23 +213,23 @@ void dense_t(int dtype, int trans_w, const T* W, int n, int m, const T* act, i64
   }
 }
 
-template <class T>
+template <class T, Load LOAD>
 void apply_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 cols_out, i64 plan_cols, const int32_t* perm, const T* blocks, int b,
              int trans, hipStream_t st) {
   const int nb = ceil_div(d, b);
-  const Plan p{apply_tile(nb, b, plan_cols), 1};
+  const Tile t = apply_tile(nb, b, plan_cols);
   Args g{};
   g.rpb = b;
   g.d = d;
   g.B = Op{V, ldv, 0, perm, b, (int)cols, 1, 0};
-  const EpiScatter<T> epi{out, V, ldo, ldv, perm, b, d, (int)cols, (int)cols_out};
+  const EpiScatter<T, LOAD> epi{out, V, ldo, ldv, perm, b, d, (int)cols, (int)cols_out};
   if constexpr (sizeof(T) == 2) {   // pairs (E, E^T): op(E) has contiguous rows either way
     g.A = Op{blocks + (trans ? (i64)b * b : 0), b, 2ll * b * b, nullptr, b, b, 1, 1};
-    launch<T, true, false, APPLY>(g, epi, nb, b, cols_out, b, p, st);
+    launch_apply<T, true, false, LOAD>(g, epi, nb, b, cols_out, b, t, st);
   } else {
     g.A = Op{blocks, b, (i64)b * b, nullptr, b, b, 1, 1};
-    if (trans) launch<T, false, false, APPLY>(g, epi, nb, b, cols_out, b, p, st);
-    else launch<T, true, false, APPLY>(g, epi, nb, b, cols_out, b, p, st);
+    if (trans) launch_apply<T, false, false, LOAD>(g, epi, nb, b, cols_out, b, t, st);
+    else launch_apply<T, true, false, LOAD>(g, epi, nb, b, cols_out, b, t, st);
   }
 }
 
@@ -245,11 +247,11 @@ void apply_tokens_t(const T* V, i64 ldv, T* out, i64 ldo, int d, i64 cols, i64 c
   const EpiScatterTokens<T, V_TM, OUT_TM> epi{out, V, ldo, ldv, perm, b, d, (int)cols, (int)cols_out};
   if constexpr (sizeof(T) == 2) {
     g.A = Op{blocks + (trans ? (i64)b * b : 0), b, 2ll * b * b, nullptr, b, b, 1, 1};
-    launch_apply_32<T, true, false, V_TM>(g, epi, nb, b, cols_out, b, st);
+    launch_apply_32<T, true, false, V_TM ? STRIDED : BRANCHED>(g, epi, nb, b, cols_out, b, st);
   } else {
     g.A = Op{blocks, b, (i64)b * b, nullptr, b, b, 1, 1};
-    if (trans) launch_apply_32<T, false, false, V_TM>(g, epi, nb, b, cols_out, b, st);
-    else launch_apply_32<T, true, false, V_TM>(g, epi, nb, b, cols_out, b, st);
+    if (trans) launch_apply_32<T, false, false, V_TM ? STRIDED : BRANCHED>(g, epi, nb, b, cols_out, b, st);
+    else launch_apply_32<T, true, false, V_TM ? STRIDED : BRANCHED>(g, epi, nb, b, cols_out, b, st);
   }
 }
 
@@ -296,9 +298,11 @@ void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void*
 void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int d, i64 cols, i64 cols_out, i64 plan_cols, const int32_t* perm,
                      const void* blocks, int b, int transpose_G, hipStream_t st) {
   if (dtype == POETX_F32)
-    apply_t<float>((const float*)V, ldv, (float*)out, ldo, d, cols, cols_out, plan_cols, perm, (const float*)blocks, b, transpose_G, st);
+    apply_t<float, BRANCHED>((const float*)V, ldv, (float*)out, ldo, d, cols, cols_out, plan_cols, perm, (const float*)blocks, b, transpose_G, st);
+  else if (cols >= 8 && cols % 8 != 0)
+    apply_t<uint16_t, MASKED>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, plan_cols, perm, (const uint16_t*)blocks, b, transpose_G, st);
   else
-    apply_t<uint16_t>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, plan_cols, perm, (const uint16_t*)blocks, b, transpose_G, st);
+    apply_t<uint16_t, BRANCHED>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, plan_cols, perm, (const uint16_t*)blocks, b, transpose_G, st);
 }
 
 bool edge_apply_smallest_tile(int d, i64 plan_cols, int b) { return apply_tile(ceil_div(d, b), b, plan_cols) == TILE_32; }

@@ -9,7 +9,7 @@
 // index does.  Tiles are loaded through registers, 16 bytes per lane whatever the alignment (element
 // aligned vectors: one global load either way), masked at the edges with zeros on both operands so that
 // nothing outside the valid ranges takes part, and pass through a two-stage LDS ring with one barrier
-// per stage; the loads of the next two stages are in flight under the products of this one.
+// per stage; the loads of the next stage are in flight under the products of this one.
 //
 // What bounds it: at the sizes it serves the chip is rarely full, so a pass is a chain of latencies (load,
 // LDS, matrix product, store).  Hence tile and contraction split follow the problem (dense_plan, apply_tile, grad_plan): 128 x 128, 64 x 64,
@@ -51,13 +51,34 @@ typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 __device__ inline u32x4 load16(const uint16_t* p) { return *reinterpret_cast<const u32x4_a2*>(p); }
 __device__ inline u32x4 load16(const float* p) { return *reinterpret_cast<const u32x4_a4*>(p); }
 
-// v without its first n elements, zeros behind them (all zeros from n = 16 bytes on)
+// 16 bytes of a row starting at column c >= 0: zeros from column cols on, or altogether if !row_ok.  A branch per lane: lanes that have
+// nothing to read read nothing, and whole vectors cost nothing more; a tail is read element by element and waited for.
 template <class T>
+__device__ __forceinline__ u32x4 load_branched(const T* row, int c, int cols, bool row_ok) {
+  constexpr int V = 16 / sizeof(T);
+  u32x4 v = {0, 0, 0, 0};
+  if (!row_ok || c >= cols) return v;
+  if (cols - c >= V) return load16(row + c);   // no sum: the last column may be the last int
+  const int n = cols - c;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    if constexpr (sizeof(T) == 4) {
+      if (w < n) v[w] = __builtin_bit_cast(uint32_t, row[c + w]);
+    } else {
+      uint32_t x = 0;
+      if (2 * w < n) x = row[c + 2 * w];
+      if (2 * w + 1 < n) x |= (uint32_t)row[c + 2 * w + 1] << 16;
+      v[w] = x;
+    }
+  }
+  return v;
+}
+
+// v without its first n elements, zeros behind them (all zeros from n = 8 on)
 __device__ __forceinline__ u32x4 drop_first(const u32x4& v, int n) {
   typedef unsigned long long u64;
-  constexpr int B = 8 * sizeof(T);
   const u64 lo = (u64)v[1] << 32 | v[0], hi = (u64)v[3] << 32 | v[2];
-  const int bits = n * B, in = bits & 63;
+  const int bits = n * 16, in = bits & 63;
   const u64 carry = in ? hi << (64 - in) : 0, l = bits < 64 ? lo >> in | carry : hi >> in, h = bits < 64 ? hi >> in : 0;
   const bool none = bits >= 128;
   u32x4 r;
@@ -68,48 +89,12 @@ __device__ __forceinline__ u32x4 drop_first(const u32x4& v, int n) {
   return r;
 }
 
-// 16 bytes of a row starting at column c >= 0 in two halves: the load (a vector that would pass the row's end ends there instead; no branch
-// per lane, a row that is not there is some other one) and, once it is waited for, the mask: zeros from column cols on, or altogether if !row_ok.
-template <class T>
-__device__ __forceinline__ u32x4 load_raw(const T* row, int c, int cols) {
-  constexpr int V = 16 / sizeof(T);
-  if (cols < V) {              // uniform: too short for a vector
-    u32x4 v = {0, 0, 0, 0};
-#pragma unroll
-    for (int e = 0; e < V - 1; ++e) {
-      if (e < cols - c) {
-        if constexpr (sizeof(T) == 4) v[e] = __builtin_bit_cast(uint32_t, row[c + e]);
-        else v[e >> 1] |= (uint32_t)row[c + e] << (16 * (e & 1));
-      }
-    }
-    return v;
-  }
-  return load16(row + (c < cols - V ? c : cols - V));
-}
-template <class T>
+// The same load of a bf16 row of at least 8 columns without a branch, in two halves: the load (a vector that would pass the row's end ends there
+// instead; a row that is not there is some other one) and, once it is waited for, the mask.
+__device__ __forceinline__ u32x4 load_raw(const uint16_t* row, int c, int cols) { return load16(row + (c < cols - 8 ? c : cols - 8)); }
 __device__ __forceinline__ u32x4 mask_raw(const u32x4& v, int c, int cols, bool row_ok) {
-  constexpr int V = 16 / sizeof(T);
-  const int past = cols < V || c <= cols - V ? 0 : c - (cols - V);
-  return drop_first<T>(v, row_ok && past < V ? past : V);
-}
-template <class T>
-__device__ __forceinline__ u32x4 load_masked(const T* row, int c, int cols, bool row_ok) {
-  return mask_raw<T>(load_raw<T>(row, c, cols), c, cols, row_ok);
-}
-
-// the same with a branch per lane, in as few registers
-__device__ __forceinline__ u32x4 load_branched(const uint16_t* row, int c, int cols) {
-  u32x4 v = {0, 0, 0, 0};
-  if (c >= cols) return v;
-  if (cols - c >= 8) return load16(row + c);   // no sum: the last column may be the last int
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    uint32_t x = 0;
-    if (2 * w < cols - c) x = row[c + 2 * w];
-    if (2 * w + 1 < cols - c) x |= (uint32_t)row[c + 2 * w + 1] << 16;
-    v[w] = x;
-  }
-  return v;
+  const int past = c <= cols - 8 ? 0 : c - (cols - 8);
+  return drop_first(v, row_ok && past < 8 ? past : 8);
 }
 
 // the same with columns cs elements apart
@@ -178,10 +163,21 @@ struct Shape {
   static_assert(WGK == 1 || (WGK - 1) * WGM * WGN * TM * TN * 4096 <= LDS, "partial tiles meet in the ring");
 };
 
+// How the operands' vectors are loaded; STRIDED and MASKED are about B alone.
+// WHOLE: every tile and stage lies inside both operands, nothing is checked.
+// MASKED (bf16 rows of at least 8 columns whose count is no multiple of 8; B X major): every stage of the last tile ends in tails, and what is
+// branched waits for them -- load_raw, and the mask on the way into LDS.  us, branched / masked: applies of 411 features, b = 256, 28 tokens 6.3 / 5.3;
+// 1258, b = 128, 1501 7.3 / 6.1; 524, b = 64, 302 4.9 / 3.9; but 4122, b = 128, 1032 tokens 11.4 / 11.8.
+// Elsewhere branches are the better form of an edge, and one stage ahead is enough: the arithmetic of masks and the registers of a second stage cost
+// more than they hide (us, masks and two stages / branches and one: fp32 gradients of 2380 features, b = 48, 3925 tokens 57.3 / 45.1; products of sizes in
+// 32s with few tokens 19 % (bf16) and 6 % (fp32) less time).  A choice between WHOLE and BRANCHED inside one kernel costs the short launches that are
+// not whole up to 5 % (the code), so it is made outside; WHOLE takes gradients of 1024 features, b = 64, 512 tokens from 4.26 to 4.06, bf16 1024 x 1024 x 512 from 9.1 to 8.5.
+enum Load { BRANCHED, STRIDED, MASKED, WHOLE };
+
 // Epi: __device__ void operator()(int batch, int split, int row, int col, const float (&v)[8]) -- eight
 // consecutive columns of one output row, indices inside the batch; it does its own masking.
-// bx of total: this workgroup among those of the problem.  PF: stages whose loads are in flight.
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
+// bx of total: this workgroup among those of the problem.
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi, Load LOAD>
 __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int bx, int total, int split) {
   using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
   constexpr int V = 16 / sizeof(T), WGK = S::WGK, TM = S::TM, TN = S::TN;
@@ -219,12 +215,13 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   };
   const Side sa = side_of(g.A), sb = side_of(g.B);
   constexpr int VPRA = (A_K ? BK : BM) / V, VPRB = (B_K ? BK : BN) / V;
-  u32x4 ra[PF][NVA], rb[PF][NVB];
+  static_assert(LOAD != MASKED || (BF && !B_K), "masked loads are of bf16 rows along the output index");
+  u32x4 ra[NVA], rb[NVB];
   // Memory row of this thread's vector (its offset; where there is none, that of the first): fixed for a K-major operand, moving with
   // the stage for an X-major one.
   i64 rowA[NVA], rowB[NVB];
   auto row_at = [&](const Side& s, int r) {
-    const int rr = r < s.rows ? r : 0;
+    const int rr = LOAD == WHOLE || r < s.rows ? r : 0;
     return (s.pm ? (i64)s.pm[rr] : (i64)rr) * s.ld;
   };
   auto rowno_a = [&](int s, int kt) { return (A_K ? i0 : kt * BK) + (s * NTH + tid) / VPRA; };
@@ -241,17 +238,19 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
       for (int s = 0; s < NVB; ++s) rowB[s] = row_at(sb, rowno_b(s, kt));
     }
   };
-  // Stages up to here are whole and need no mask.  The others are masked on their way into LDS, not where they are loaded: that would wait for
-  // the load, and the workgroups at the edges are the last to finish.
-  const int whole_a = tile_inside(i0, BM, A_K ? sa.rows : sa.cols) ? (A_K ? sa.cols : sa.rows) / BK : 0;
-  const int whole_b = tile_inside(j0, BN, B_K ? sb.rows : sb.cols) ? (B_K ? sb.cols : sb.rows) / BK : 0;
-  auto gload = [&](int kt, int q) {
+  const int whole_b = tile_inside(j0, BN, sb.cols) ? sb.rows / BK : 0;   // MASKED: stages up to here are whole and need no mask
+  auto gload = [&](int kt) {
 #pragma unroll
-    for (int s = 0; s < NVA; ++s) ra[q][s] = load_raw<T>(sa.base + rowA[s], col_a(s, kt), sa.cols);
+    for (int s = 0; s < NVA; ++s) {
+      if constexpr (LOAD == WHOLE) ra[s] = load16(sa.base + rowA[s] + col_a(s, kt));
+      else ra[s] = load_branched(sa.base + rowA[s], col_a(s, kt), sa.cols, rowno_a(s, kt) < sa.rows);
+    }
 #pragma unroll
     for (int s = 0; s < NVB; ++s) {
-      if constexpr (B_STRIDED) rb[q][s] = load_strided<T>(sb.base + rowB[s], col_b(s, kt), g.B.cs, sb.cols, rowno_b(s, kt) < sb.rows);
-      else rb[q][s] = load_raw<T>(sb.base + rowB[s], col_b(s, kt), sb.cols);
+      if constexpr (LOAD == WHOLE) rb[s] = load16(sb.base + rowB[s] + col_b(s, kt));
+      else if constexpr (LOAD == STRIDED) rb[s] = load_strided<T>(sb.base + rowB[s], col_b(s, kt), g.B.cs, sb.cols, rowno_b(s, kt) < sb.rows);
+      else if constexpr (LOAD == MASKED) rb[s] = load_raw(sb.base + rowB[s], col_b(s, kt), sb.cols);
+      else rb[s] = load_branched(sb.base + rowB[s], col_b(s, kt), sb.cols, rowno_b(s, kt) < sb.rows);
     }
   };
   // ---- LDS layout.  bf16: 32-deep sub-tiles in the swizzled layouts of mfma_gemm.h.  fp32: [k][x], rows of
@@ -271,22 +270,20 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
       }
     }
   };
-  auto lstore = [&](int slot, int q, int kt) {
-    if (kt >= whole_a) {
+  auto lstore = [&](int slot, int kt) {
+    if constexpr (LOAD == MASKED) {
+      if (kt >= whole_b) {
 #pragma unroll
-      for (int s = 0; s < NVA; ++s) ra[q][s] = mask_raw<T>(ra[q][s], col_a(s, kt), sa.cols, rowno_a(s, kt) < sa.rows);
-    }
-    if (!B_STRIDED && kt >= whole_b) {
-#pragma unroll
-      for (int s = 0; s < NVB; ++s) rb[q][s] = mask_raw<T>(rb[q][s], col_b(s, kt), sb.cols, rowno_b(s, kt) < sb.rows);
+        for (int s = 0; s < NVB; ++s) rb[s] = mask_raw(rb[s], col_b(s, kt), sb.cols, rowno_b(s, kt) < sb.rows);
+      }
     }
     char* stage = lds + slot * S::STAGE;
 #pragma unroll
     for (int s = 0; s < NVA; ++s)
-      put(stage, ra[q][s], (s * NTH + tid) / VPRA, (s * NTH + tid) % VPRA, std::integral_constant<int, BM>{}, A_K);
+      put(stage, ra[s], (s * NTH + tid) / VPRA, (s * NTH + tid) % VPRA, std::integral_constant<int, BM>{}, A_K);
 #pragma unroll
     for (int s = 0; s < NVB; ++s)
-      put(stage + S::A_BYTES, rb[q][s], (s * NTH + tid) / VPRB, (s * NTH + tid) % VPRB, std::integral_constant<int, BN>{}, B_K);
+      put(stage + S::A_BYTES, rb[s], (s * NTH + tid) / VPRB, (s * NTH + tid) % VPRB, std::integral_constant<int, BN>{}, B_K);
   };
 
   floatx16 acc[TM][TN];
@@ -361,29 +358,22 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   const int k0 = split * g.stages_per_split;
   const int k1 = k0 + g.stages_per_split < g.stages ? k0 + g.stages_per_split : g.stages;
   if (k0 < k1) {
-    // stage kt + PF is requested while kt is multiplied: its registers were written to LDS a stage ago
+    // stage kt + 1 is requested while kt is multiplied: its registers were written to LDS a stage ago
     rows_at(k0, true);
-#pragma unroll
-    for (int q = 0; q < PF; ++q)
-      if (k0 + q < k1) {
-        gload(k0 + q, q);
-        if (k0 + q + 1 < k1) rows_at(k0 + q + 1, false);
-      }
-    lstore(0, 0, k0);
+    gload(k0);
+    if (k0 + 1 < k1) rows_at(k0 + 1, false);
+    lstore(0, k0);
     lds_barrier();
-    for (int kt = k0; kt < k1; kt += PF)
-#pragma unroll
-      for (int q = 0; q < PF; ++q) {
-        if (kt + q >= k1) break;
-        const int slot = (kt + q - k0) & 1;
-        if (kt + q + PF < k1) {
-          gload(kt + q + PF, q);
-          if (kt + q + PF + 1 < k1) rows_at(kt + q + PF + 1, false);
-        }
-        multiply(slot);
-        if (kt + q + 1 < k1) lstore(slot ^ 1, (q + 1) % PF, kt + q + 1);   // read last before the previous barrier
-        lds_barrier();
+    for (int kt = k0; kt < k1; ++kt) {
+      const int slot = (kt - k0) & 1;
+      if (kt + 1 < k1) {
+        gload(kt + 1);
+        if (kt + 2 < k1) rows_at(kt + 2, false);
       }
+      multiply(slot);
+      if (kt + 1 < k1) lstore(slot ^ 1, kt + 1);   // read last before the previous barrier
+      lds_barrier();
+    }
   }
 
   if constexpr (WGK > 1) {
@@ -453,13 +443,13 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
   }
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, class Epi, bool B_STRIDED = false>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi, Load LOAD>
 __global__ __launch_bounds__((Shape<T, BM, BN, BK, WGM, WGN, WAVES>::THREADS)) void edge_kernel(Args g, Epi epi, int total, int first) {
-  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, PF, A_K, B_K, Epi, B_STRIDED>(g, epi, first + (int)blockIdx.x, total, blockIdx.y);
+  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, LOAD>(g, epi, first + (int)blockIdx.x, total, blockIdx.y);
 }
 
 // Two problems of one shape in one launch: the first n0 workgroups of a row of the grid take g0, the rest g1.
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi, Load LOAD>
 __global__ __launch_bounds__((Shape<T, BM, BN, BK, WGM, WGN, WAVES>::THREADS)) void edge_pair_kernel(Args g0, Args g1, Epi e0, Epi e1, int n0, int total, int first) {
   const int bx = first + (int)blockIdx.x;
   const bool second = bx >= n0;
@@ -467,7 +457,7 @@ __global__ __launch_bounds__((Shape<T, BM, BN, BK, WGM, WGN, WAVES>::THREADS)) v
   const Epi epi = second ? e1 : e0;
   const int split = blockIdx.y;
   if (split * g.stages_per_split >= g.stages) return;
-  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, PF, A_K, B_K>(g, epi, second ? bx - n0 : bx, second ? total - n0 : n0, split);
+  edge_product<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, LOAD>(g, epi, second ? bx - n0 : bx, second ? total - n0 : n0, split);
 }
 
 // ---- host side -------------------------------------------------------------------------------
@@ -487,6 +477,7 @@ constexpr int stage_depth(Tile t, size_t es) { return (t == TILE_32 || t == TILE
 struct Problem {
   i64 batches, M, N, K;
 };
+inline bool lds_limit(const void* kern, int bytes) { return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; }
 inline void tile_args(Args& g, const Problem& q, int BM, int BN, int BK, int splits) {
   g.tiles_m = ceil_div(q.M, BM);
   g.tiles_n = ceil_div(q.N, BN);
@@ -495,69 +486,103 @@ inline void tile_args(Args& g, const Problem& q, int BM, int BN, int BK, int spl
   g.stages_per_split = ceil_div(g.stages, splits);
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, class Epi>
+// WHOLE: do all tiles and stages lie inside the operands?
+template <int BM, int BN, int BK, bool A_K, bool B_K>
+bool whole_tiles(const Args& g) {
+  const i64 M = (i64)g.tiles_m * BM, N = (i64)g.tiles_n * BN, K = (i64)g.stages * BK;
+  return (g.rpb == 0 || g.d % g.rpb == 0) && M <= (A_K ? g.A.rows : g.A.cols) && K <= (A_K ? g.A.cols : g.A.rows) &&
+         N <= (B_K ? g.B.rows : g.B.cols) && K <= (B_K ? g.B.cols : g.B.rows);
+}
+
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi>
 void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, int s0, int s1, hipStream_t st) {
   using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
-  auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, PF, A_K, B_K, Epi>;
-  static const bool configured =
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
-  (void)configured;
   tile_args(g0, q0, BM, BN, BK, s0);
   tile_args(g1, q1, BM, BN, BK, s1);
   const i64 n0 = q0.batches * g0.tiles_m * g0.tiles_n, n1 = q1.batches * g1.tiles_m * g1.tiles_n;
-  launch_in_rows(n0 + n1, [&](int first, unsigned count) {
-    hipLaunchKernelGGL(kern, dim3(count, (unsigned)(s0 > s1 ? s0 : s1)), dim3(S::THREADS), S::LDS, st, g0, g1, e0, e1, (int)n0, (int)(n0 + n1), first);
-  });
+  auto go = [&](auto kern) {
+    launch_in_rows(n0 + n1, [&](int first, unsigned count) {
+      hipLaunchKernelGGL(kern, dim3(count, (unsigned)(s0 > s1 ? s0 : s1)), dim3(S::THREADS), S::LDS, st, g0, g1, e0, e1, (int)n0, (int)(n0 + n1), first);
+    });
+  };
+  // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
+  if (whole_tiles<BM, BN, BK, A_K, B_K>(g0) && whole_tiles<BM, BN, BK, A_K, B_K>(g1)) {
+    auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, WHOLE>;
+    static const bool configured = lds_limit((const void*)kern, S::LDS);
+    (void)configured;
+    go(kern);
+  } else {
+    auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, BRANCHED>;
+    static const bool configured = lds_limit((const void*)kern, S::LDS);
+    (void)configured;
+    go(kern);
+  }
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, int PF, bool A_K, bool B_K, bool B_STRIDED = false, class Epi>
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, Load LOAD = BRANCHED, class Epi>
 void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits, hipStream_t st) {
   using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
-  auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, WAVES, PF, A_K, B_K, Epi, B_STRIDED>;
-  // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
-  static const bool configured =
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS) == hipSuccess;
-  (void)configured;
   tile_args(g, Problem{batches, M, N, K}, BM, BN, BK, splits);
   const i64 total = batches * g.tiles_m * g.tiles_n;
-  launch_in_rows(total, [&](int first, unsigned count) {
-    hipLaunchKernelGGL(kern, dim3(count, (unsigned)splits), dim3(S::THREADS), S::LDS, st, g, epi, (int)total, first);
-  });
+  auto go = [&](auto kern) {
+    launch_in_rows(total, [&](int first, unsigned count) {
+      hipLaunchKernelGGL(kern, dim3(count, (unsigned)splits), dim3(S::THREADS), S::LDS, st, g, epi, (int)total, first);
+    });
+  };
+  if constexpr (LOAD == BRANCHED) {
+    if (whole_tiles<BM, BN, BK, A_K, B_K>(g)) {
+      auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, WHOLE>;
+      static const bool configured = lds_limit((const void*)kern, S::LDS);
+      (void)configured;
+      return go(kern);
+    }
+  }
+  auto kern = edge_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, LOAD>;
+  static const bool configured = lds_limit((const void*)kern, S::LDS);
+  (void)configured;
+  go(kern);
 }
 
 // Applies on the smallest tile: the contraction is a block, and a stage no deeper than it (masked halves of a stage cost a launch
-// some 0.4 us).
-template <class T, bool A_K, bool B_K, bool B_STRIDED = false, class Epi>
+// some 0.4 us).  Strided bf16 loads are eight accesses each: four waves share those of 64 features, whose shallow stage has two (1280 features,
+// b = 64, 86 tokens 8.4 / 7.6 us; b = 32 the other way).
+template <class T, bool A_K, bool B_K, Load LOAD, class Epi>
 void launch_apply_32(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, hipStream_t st) {
   constexpr int D = 128 / (int)sizeof(T);
-  if (K > D) launch_shape<T, 32, 32, 2 * D, 1, 1, 4, 1, A_K, B_K, B_STRIDED>(g, epi, batches, M, N, K, 1, st);
-  else if constexpr (sizeof(T) == 4) launch_shape<T, 32, 32, D, 1, 1, 4, 1, A_K, B_K, B_STRIDED>(g, epi, batches, M, N, K, 1, st);
-  else launch_shape<T, 32, 32, D, 1, 1, 2, 1, A_K, B_K, B_STRIDED>(g, epi, batches, M, N, K, 1, st);
+  if (K > D || (sizeof(T) == 2 && LOAD == STRIDED && 2 * K > D)) launch_shape<T, 32, 32, 2 * D, 1, 1, 4, A_K, B_K, LOAD>(g, epi, batches, M, N, K, 1, st);
+  else if constexpr (sizeof(T) == 4) launch_shape<T, 32, 32, D, 1, 1, 4, A_K, B_K, LOAD>(g, epi, batches, M, N, K, 1, st);
+  else launch_shape<T, 32, 32, D, 1, 1, 2, A_K, B_K, LOAD>(g, epi, batches, M, N, K, 1, st);
+}
+template <class T, bool A_K, bool B_K, Load LOAD, class Epi>
+void launch_apply(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, Tile t, hipStream_t st) {
+  constexpr int D = 128 / (int)sizeof(T);
+  if (t == TILE_128) launch_shape<T, 128, 128, D, 2, 2, 4, A_K, B_K, LOAD>(g, epi, batches, M, N, K, 1, st);
+  else if (t == TILE_64) launch_shape<T, 64, 64, D, 2, 2, 4, A_K, B_K, LOAD>(g, epi, batches, M, N, K, 1, st);
+  else launch_apply_32<T, A_K, B_K, LOAD>(g, epi, batches, M, N, K, st);
 }
 
-// What a product is for.  Dense products (long contractions) have twice the waves on their larger tiles, halves of which split every stage: what
+// Dense products (long contractions) have twice the waves on their larger tiles, halves of which split every stage: what
 // bounds the plain ones are the latencies of one or two waves per SIMD (fp32 1024 x 1024 x 2048, 64 x 64: 53.0 -> 49.2 us; bf16 1024 x 1536 x 3001,
-// 128 x 128: 44 -> 33; block gradients on 128 x 128 lose: 69 -> 95).  Applies (a stage or two) look one stage ahead only: two cost them 0.4 us.
-enum Use { APPLY = 0, DENSE = 1, GRAD = 2 };
+// 128 x 128: 44 -> 33; block gradients on 128 x 128 lose: 69 -> 95).
+enum Use { DENSE, GRAD };
 template <class T, bool A_K, bool B_K, Use USE, class Epi>
 void launch(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, Plan p, hipStream_t st) {
-  constexpr int D = 128 / (int)sizeof(T), W = USE == DENSE ? 8 : 4, PF = USE == APPLY ? 1 : 2;   // D: stage_depth
+  constexpr int D = 128 / (int)sizeof(T), W = USE == DENSE ? 8 : 4;   // D: stage_depth
   if constexpr (USE == DENSE && sizeof(T) == 4) {
-    if (p.tile == TILE_64D) return launch_shape<T, 64, 64, 2 * D, 2, 2, 16, PF, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+    if (p.tile == TILE_64D) return launch_shape<T, 64, 64, 2 * D, 2, 2, 16, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
   }
-  if (p.tile == TILE_128) launch_shape<T, 128, 128, D, 2, 2, W, PF, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
-  else if (p.tile == TILE_64) launch_shape<T, 64, 64, D, 2, 2, W, PF, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
-  else if constexpr (USE == APPLY) launch_apply_32<T, A_K, B_K>(g, epi, batches, M, N, K, st);
-  else launch_shape<T, 32, 32, 2 * D, 1, 1, sizeof(T) == 4 ? W : 4, PF, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  if (p.tile == TILE_128) launch_shape<T, 128, 128, D, 2, 2, W, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else if (p.tile == TILE_64) launch_shape<T, 64, 64, D, 2, 2, W, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  else launch_shape<T, 32, 32, 2 * D, 1, 1, sizeof(T) == 4 ? W : 4, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
 }
 
 // two problems planned onto the same tile
 template <class T, bool A_K, bool B_K, class Epi>
 void launch_pair(const Args& g0, const Args& g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, Plan p0, Plan p1, hipStream_t st) {
   constexpr int D = 128 / (int)sizeof(T);
-  if (p0.tile == TILE_128) launch_pair_shape<T, 128, 128, D, 2, 2, 4, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
-  else if (p0.tile == TILE_64) launch_pair_shape<T, 64, 64, D, 2, 2, 4, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
-  else launch_pair_shape<T, 32, 32, 2 * D, 1, 1, 4, 2, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  if (p0.tile == TILE_128) launch_pair_shape<T, 128, 128, D, 2, 2, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  else if (p0.tile == TILE_64) launch_pair_shape<T, 64, 64, D, 2, 2, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+  else launch_pair_shape<T, 32, 32, 2 * D, 1, 1, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
 }
 
 }  // namespace edge

@@ -55,7 +55,8 @@ __global__ __launch_bounds__(256) void apply_few_kernel(const uint16_t* __restri
     } else {
       u32x4 v[NT * 2];
 #pragma unroll
-      for (int c = 0; c < NT * 2; ++c) v[c] = edge::load_masked<uint16_t>(V + pf[i] * ldv, 8 * c, N, true);
+      for (int c = 0; c < NT * 2; ++c) v[c] = N < 8 ? edge::load_branched(V + pf[i] * ldv, 8 * c, N, true)
+                          : edge::mask_raw(edge::load_raw(V + pf[i] * ldv, 8 * c, N), 8 * c, N, true);
 #pragma unroll
       for (int t = 0; t < NT * 16; ++t) xs[t * LD + f] = (uint16_t)(v[t >> 3][(t >> 1) & 3] >> (16 * (t & 1)));
     }

@@ -277,19 +277,19 @@ __global__ __launch_bounds__(512) void apply_left_ragged_kernel(const uint16_t* 
   auto gload = [&](int t) {
     if constexpr (B == 512) {
 #pragma unroll
-      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load_branched(V + goff[s], gcol + t * BN, nv);
+      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load_branched(V + goff[s], gcol + t * BN, nv, true);
     } else if (tile_inside(tok0 + t * BN, BN, nv)) {
 #pragma unroll
       for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load16(V + goff[s] + gcol + t * BN);
     } else {
 #pragma unroll
-      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load_raw<uint16_t>(V + goff[s], gcol + t * BN, nv);
+      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::load_raw(V + goff[s], gcol + t * BN, nv);
     }
   };
   auto lstore = [&](int t) {
     if (B != 512 && !tile_inside(tok0 + t * BN, BN, nv)) {
 #pragma unroll
-      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::mask_raw<uint16_t>(stage_regs[s], gcol + t * BN, nv, true);
+      for (int s = 0; s < IPW; ++s) stage_regs[s] = edge::mask_raw(stage_regs[s], gcol + t * BN, nv, true);
     }
     char* stage = ring + (t & 1) * STAGE_BYTES + wave * IPW * 1024 + lane * 16;
 #pragma unroll

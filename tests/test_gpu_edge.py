@@ -29,6 +29,13 @@ pytestmark = pytest.mark.gpu
     # one parameter: its gradient, one sum of rounded products, has no bound relative to itself where they cancel.)
     (768, 1096, 1001, 64, 2),
     (2000, 2040, 2001, 40, 1),  # 128-wide ones with eight
+    # bf16 rows shorter than a vector, whole vectors, and tails (each loaded in its own way); blocks that no tile divides
+    (192, 288, 7, 96, 2),
+    (192, 288, 8, 96, 2),
+    (192, 288, 9, 96, 2),
+    (256, 128, 1041, 64, 2),    # tails behind whole tiles
+    (256, 384, 512, 128, 2),    # every tile and stage whole, and all but the last: the block gradients of 520 tokens
+    (256, 384, 520, 128, 2),
 ])
 def test_layer_at_tile_edges(lib, m, n, N, b, k, dtype):
     data = synth_layer(9000 + m + n + N + b, m, n, N, b, k, dtype, 0.01)

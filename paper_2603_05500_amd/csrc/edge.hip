@@ -22,37 +22,48 @@ Tile apply_tile(i64 batches, i64 M, i64 N) {
   return TILE_32;
 }
 
-// Dense products: tile and contraction split priced together.  A workgroup takes `lone` us for a stage when it has a CU to itself and
-// `shared` for each of the workgroups on its CU, of which the fullest CU counts, in bf16's shorter stages the mean; `fill` stages more to
-// fill the ring and to store.  A split adds a launch of `reduce` us with its gap and its fp32 parts, written and read at 4 TB/s.  The constants are
-// fitted to 570 products of 128 - 1536 rows, 16 - 4096 tokens and contractions of 128 - 1536, each timed with every tile and split: the
-// choice is 1 % slower than the best one on average and at most 12 % slower than that of the rule before, which took the tile first (four waves
-// each) and then the split, and is 10 % (bf16 22 %) slower than the best.  us, tile / splits (64D: 64 x 64 with sixteen waves): fp32 1024 x 768 x 1001
-// 32/1 29.0, 64/1 29.9, 64/2 27.6, 64/4 27.8, 64D/1 25.4, 128/4 32.8 (before: 64/2 at 30.7); 256 x 256 x 512 32/1 6.0, 32/2 7.7 (before); bf16
-// 512 x 1376 x 1024 32/1 10.7, 32/2 13.9 (before), 64/1 12.5; 1024 x 1536 x 3001 32/1 55.6, 64/1 27.0, 128/2 37 - 43 (before).
+// Dense products: tile and contraction split priced together.  A workgroup takes `lone` us for a stage when it has a CU to itself (`cold` more
+// where the weight is larger than the L2s would keep) and `shared` for each of the workgroups on its CU, of which the fullest CU counts; `fill` stages
+// more to fill the ring and to store.  A split adds a launch of `reduce` us with its gap and its fp32 parts, written and read at 4 TB/s.
+// The constants are fitted to 1520 products of 128 - 14336 rows, 1 - 5000 columns and contractions of 256 - 14336, both directions, weights over 6 MB read from
+// memory, each timed with every tile and split: the choice is 1 % slower than the best one on average and takes 10 % (fp32) and 25 % (bf16) less time than a rule
+// that takes the largest tile to fill three quarters of the CUs, with four waves each, and then the split.  us, tile / splits (64D: 64 x 64 with sixteen waves):
+// fp32 1024 x 768 x 1001 64D/1 27.4, 64/3 29.8, 32/1 31.2; 256 x 256 x 512 32/1 6.2, 32/2 7.4; bf16 1376 x 512 x 1024 64/1 9.6, 32/1 10.7, 128/1 13.8;
+// 1024 x 1536 x 3001 64/1 24.7, 128/2 34.6; 4096 x 14336 x 64 64/12 34.0, 64/4 and 32 at any split over 40; 4192 x 8000 x 1567 128/1 200, 128/4 228, 64/1 275.
+// Up to 32 columns of a large weight are bound by its reads, for which this price is too coarse (up to 12 % slower than four workgroups per CU): as many splits as
+// give each CU four workgroups of at least four stages (5632 x 8192 x 24 32/5 25.8, 32/4 29.7; fp32 6208 x 3072 x 2 32/5 27.6, 32/3 33.2).
 struct TileCost {
   Tile tile;
   int side;
   double lone, shared;
-  bool mean;
 };
 Plan dense_plan(int dtype, i64 M, i64 N, i64 K) {
-  static const TileCost f32[] = {{TILE_32, 32, 0.72, 0.52, false}, {TILE_64, 64, 1.47, 0.61, false}, {TILE_64D, 64, 1.58, 1.39, false}, {TILE_128, 128, 2.93, 2.19, false}};
-  static const TileCost bf16[] = {{TILE_32, 32, 0.46, 0.33, true}, {TILE_64, 64, 0.52, 0.32, true}, {TILE_128, 128, 0.97, 0.94, false}};
+  static const TileCost f32[] = {{TILE_32, 32, 0.70, 0.51}, {TILE_64, 64, 1.51, 0.66}, {TILE_64D, 64, 1.57, 1.46}, {TILE_128, 128, 2.69, 2.32}};
+  static const TileCost bf16[] = {{TILE_32, 32, 0.58, 0.31}, {TILE_64, 64, 0.58, 0.35}, {TILE_128, 128, 1.14, 0.62}};
   const bool f = dtype == POETX_F32;
-  const double fill = f ? 3.5 : 0.6, reduce = f ? 2.3 : 2.1;
   const size_t es = f ? 4 : 2;
+  const double fill = f ? 0.94 : 1.1, reduce = f ? 1.95 : 2.3;
+  const bool large = (double)M * (double)K * (double)es > 6.3e6;
+  const double cold = large ? (f ? 0.63 : 0.39) : 0;
+  if (large && N <= 32) {     // bound by the reads of the weight
+    const i64 count = tile_count(1, M, N, 32), depth = stage_depth(TILE_32, es), stages = (K + depth - 1) / depth;
+    const i64 two = min64(2 * kCUs / count, stages / 2), four = min64(4 * kCUs / count, stages / 4), s = two > four ? two : four;
+    if (s <= 1) return Plan{TILE_32, 1};
+    const i64 per = (stages + s - 1) / s;
+    return Plan{TILE_32, (int)((stages + per - 1) / per)};
+  }
   Plan best{TILE_32, 1};
   double least = 0;
   for (int t = 0; t < (f ? 4 : 3); ++t) {
     const TileCost& c = f ? f32[t] : bf16[t];
+    if (c.side > 32 && (2 * M <= c.side || 2 * N <= c.side)) continue;   // half of it idle
     const i64 count = tile_count(1, M, N, c.side), depth = stage_depth(c.tile, es), stages = (K + depth - 1) / depth;
-    for (const int s : {1, 2, 3, 4, 6, 8, 12, 16}) {
-      if (s > 1 && (stages / s < 2 || count * s > 8 * kCUs)) break;
+    const i64 most = (c.tile == TILE_128 ? 2 : 4) * kCUs;      // workgroups of a split: bounds the parts to 34 MB
+    for (int s = 1; s <= 16; ++s) {
+      if (s > 1 && (stages / s < 2 || count * s > most)) break;
       const i64 per = (stages + s - 1) / s, splits = (stages + per - 1) / per;   // no empty split
-      const double on_cu = c.mean ? (double)(count * splits) / kCUs : (double)((count * splits + kCUs - 1) / kCUs);
-      const double stage = on_cu * c.shared;
-      double us = ((double)per + fill) * (c.lone > stage ? c.lone : stage);
+      const double stage = (double)((count * splits + kCUs - 1) / kCUs) * c.shared;
+      double us = ((double)per + fill) * (c.lone + cold > stage ? c.lone + cold : stage);
       if (splits > 1) us += reduce + 8e-6 / 4 * (double)splits * (double)M * (double)N;
       if (least == 0 || us < least) { least = us; best = Plan{c.tile, (int)splits}; }
     }

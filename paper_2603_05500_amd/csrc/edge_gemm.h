@@ -563,7 +563,8 @@ void launch_apply(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, Tile
 
 // Dense products (long contractions) have twice the waves on their larger tiles, halves of which split every stage: what
 // bounds the plain ones are the latencies of one or two waves per SIMD (fp32 1024 x 1024 x 2048, 64 x 64: 53.0 -> 49.2 us; bf16 1024 x 1536 x 3001,
-// 128 x 128: 44 -> 33; block gradients on 128 x 128 lose: 69 -> 95).
+// 128 x 128: 44 -> 33; block gradients on 128 x 128 lose: 69 -> 95).  Not so 128 x 128 of bf16 with A K major (B = W A): 8192-deep products of 4192 x 1567
+// 291 / 199 us with eight waves / four, 7488 x 1984 x 3821 275 / 207; with A X major 7936 x 7872 x 734 169 / 190, 6560 x 3712 x 881 88 / 101.
 enum Use { DENSE, GRAD };
 template <class T, bool A_K, bool B_K, Use USE, class Epi>
 void launch(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, Plan p, hipStream_t st) {
@@ -571,7 +572,7 @@ void launch(const Args& g, Epi epi, i64 batches, i64 M, i64 N, i64 K, Plan p, hi
   if constexpr (USE == DENSE && sizeof(T) == 4) {
     if (p.tile == TILE_64D) return launch_shape<T, 64, 64, 2 * D, 2, 2, 16, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
   }
-  if (p.tile == TILE_128) launch_shape<T, 128, 128, D, 2, 2, W, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
+  if (p.tile == TILE_128) launch_shape<T, 128, 128, D, 2, 2, sizeof(T) == 2 && A_K ? 4 : W, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
   else if (p.tile == TILE_64) launch_shape<T, 64, 64, D, 2, 2, W, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
   else launch_shape<T, 32, 32, 2 * D, 1, 1, sizeof(T) == 4 ? W : 4, A_K, B_K>(g, epi, batches, M, N, K, p.splits, st);
 }

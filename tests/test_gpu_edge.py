@@ -25,10 +25,10 @@ pytestmark = pytest.mark.gpu
     (72, 2050, 17, 72, 2),      # the same in the backward direction
     (640, 1376, 2047, 64, 2),   # 128-wide tiles, every extent ragged
     (512, 256, 1000, 256, 2),   # large blocks, token count a multiple of 8 only
-    # 64-wide tiles whose waves split the stages, sixteen of them in fp32; backward split over workgroups.  (A tail block of side 2 would have
+    # 64-wide tiles whose waves split the stages, in fp32 split over workgroups as well.  (A tail block of side 2 would have
     # one parameter: its gradient, one sum of rounded products, has no bound relative to itself where they cancel.)
     (768, 1096, 1001, 64, 2),
-    (2000, 2040, 2001, 40, 1),  # 128-wide ones with eight
+    (2000, 2040, 2001, 40, 1),  # 128-wide ones with four waves (bf16 forward) and eight (backward)
     # bf16 rows shorter than a vector, whole vectors, and tails (each loaded in its own way); blocks that no tile divides
     (192, 288, 7, 96, 2),
     (192, 288, 8, 96, 2),
@@ -36,6 +36,13 @@ pytestmark = pytest.mark.gpu
     (256, 128, 1041, 64, 2),    # tails behind whole tiles
     (256, 384, 512, 128, 2),    # every tile and stage whole, and all but the last: the block gradients of 520 tokens
     (256, 384, 520, 128, 2),
+    # other tiles and splits that the rule gives
+    (200, 776, 1001, 40, 1),    # fp32 forward: 64 x 64 with sixteen waves ...
+    (992, 632, 200, 40, 1),     # ... in 6 ranges
+    (776, 1064, 200, 24, 1),    # fp32 backward: 64 x 64 in 9
+    (848, 200, 200, 40, 1),     # bf16 forward: 64 x 64 in 7
+    (200, 848, 200, 40, 1),     # ... backward
+    (2080, 2048, 24, 32, 1),    # a few tokens of a large weight: splits by workgroups per CU
 ])
 def test_layer_at_tile_edges(lib, m, n, N, b, k, dtype):
     data = synth_layer(9000 + m + n + N + b, m, n, N, b, k, dtype, 0.01)

@@ -55,8 +55,8 @@ __global__ __launch_bounds__(256) void apply_few_kernel(const uint16_t* __restri
     } else {
       u32x4 v[NT * 2];
 #pragma unroll
-      for (int c = 0; c < NT * 2; ++c) v[c] = N < 8 ? edge::load_branched(V + pf[i] * ldv, 8 * c, N, true)
-                          : edge::mask_raw(edge::load_raw(V + pf[i] * ldv, 8 * c, N), 8 * c, N, true);
+      for (int c = 0; c < NT * 2; ++c)
+        v[c] = N < 8 ? edge::load_branched(V + pf[i] * ldv, 8 * c, N, true) : edge::mask_raw(edge::load_raw(V + pf[i] * ldv, 8 * c, N), 8 * c, N, true);
 #pragma unroll
       for (int t = 0; t < NT * 16; ++t) xs[t * LD + f] = (uint16_t)(v[t >> 3][(t >> 1) & 3] >> (16 * (t & 1)));
     }
@@ -147,12 +147,15 @@ void launch_apply(const uint16_t* V, i64 ldv, uint16_t* out, i64 ldo, int d, int
 
 }  // namespace
 
-// Whole forwards, us, the edge kernels / these: 2048 x 2048, b = 256, one token-major token 21.1 / 16.0, 16: 28.5 / 15.3, 32: 29.6 / 18.9, 16 feature major
-// 20.4 / 14.8; 4096 x 14336 1: 40.3 / 27.6, 16: 50.6 / 38.8, 17: 53.9 / 42.8, 32: 52.4 / 57.0; 14336 x 4096, b = 512, 17 feature major 46.7 / 48.0, 32:
-// 43.4 / 59.1 (the second sixteen tokens double what every workgroup reads of A); 512 x 768, b = 64, 32: 22.1 / 15.1.
+// Every workgroup reads all of A, its waves an eighth of the contraction each, one group of loads after the other: what loses is tokens times the
+// contraction, where the edge kernels split; the second sixteen tokens double it.  Whole forwards, us, the edge kernels / these, feature major, token major (large weights
+// from memory): 2048 x 2048, b = 256, one token 20.3 / 11.1, 20.4 / 11.0, 16: 20.5 / 13.3, 28.7 / 14.6, 32: 19.0 / 16.8, 29.0 / 19.2; b = 128, 16: 18.9 / 11.8,
+// 25.5 / 13.0; b = 64: 18.2 / 11.4, 24.2 / 12.5; 4096 x 4096, b = 512, 16: 29.1 / 22.7, 41.6 / 26.1, 32: 27.0 / 30.3, 40.7 / 38.2; 14336 x 4096, 16: 44.3 / 40.8,
+// 56.9 / 41.8; 4096 x 14336, 4: 46.7 / 34.4, 49.6 / 34.6, 8: 42.8 / 37.6, 52.3 / 38.4.  Refused: 512 x 14336, 16: 22.6 / 33.7, 32: 26.2 / 48 (feature major); 2048 x 8192, 32:
+// 27.9 / 36.6; 10240 x 8192, 16: 50.5 / 58.7; 4096 x 14336, 16: 42.9 / 44.2.
 bool few_tokens_supported(int n, int m, int b, i64 N) {
   return (b == 64 || b == 128 || b == 256 || b == 512) && n % b == 0 && m % b == 0 && n < (1 << 22) && m < (1 << 22) &&
-         (N <= 16 || (N <= 32 && (i64)n * m <= 1 << 24));
+         (N <= 16 || (N <= 32 && (i64)n * m <= 1 << 24)) && m * N <= (n < 1024 || n > 8192 ? 1 << 16 : 1 << 17);
 }
 
 void few_apply(const void* V, i64 ldv, bool v_tm, void* out, i64 ldo, bool out_tm, int d, int N, const int32_t* perm, const void* E, int b, int trans,
@@ -166,9 +169,9 @@ void few_dense(const void* W, int M, int K, const void* act, void* out, i64 ldo,
   auto go = [&](auto kern, int rt, int nw) {
     hipLaunchKernelGGL(kern, dim3((unsigned)(M / (16 * rt))), dim3(64 * nw), 0, st, (const uint16_t*)W, K, (const uint16_t*)act, (uint16_t*)out, ldo, N, cols);
   };
-  // Every workgroup reads all of act (from L2): four row tiles each where that leaves enough workgroups.  14336 x 4096, one tile / four, us: 1 token
-  // 24.1 / 29.7, 16: 36.7 / 31.1; 4096 x 14336: 24.4 / 68.3, 32.8 / 77.1; 2048 x 2048: 4.5 / 9.5, 5.5 / 10.7.
-  const bool tall = M >= 8192 && N > 8;
+  // Every workgroup reads all of act (from L2): four row tiles each where that leaves enough workgroups.  Forwards of M x 4096, one tile / four, us: 14336, 8 tokens
+  // 41.0 / 37.8, 16: 45.3 / 39.2; 10240, 8: 32.1 / 35.2, 16: 37.6 / 37.1; 8192 x 8192, 16: 47.7 / 56.5.
+  const bool tall = M >= 12288 && N > 6;
   if (N <= 16) tall ? go(dense_few_kernel<4, 1, 8>, 4, 8) : go(dense_few_kernel<1, 1, 8>, 1, 8);
   else go(dense_few_kernel<1, 2, 8>, 1, 8);
 }

@@ -170,12 +170,10 @@ bool bwd_one_pass(const poetx_linear_desc* d) {
 // Few token-major tokens outside few_tokens(): the forward's applies read X and write Z as they are, element by element, where the two
 // transposing launches (some 5 us each) would cost more.  Every 32 rows of a block read the whole block's features
 // again, so the element reads are in proportion to (n + m) N b; the workgroups of b = 512 are besides a chain of four
-// dependent stages, and lose from half of that on.  bf16 forwards, us, with transposes / in place (the smallest token counts of
-// these shapes now belong to few_tokens(), which is faster than either): 2048 x 2048, b = 256:
-// 29.7 / 21.0 for one token, 32.3 / 28.7 for 16, 38.2 / 34.5 for 31, 25.7 / 31.2 for 64 (bf16 transposes
-// of whole 64-token tiles are half as dear; 1024 x 1024, b = 128, 128 tokens: 21.8 / 25.2); 512 x 1376, b = 64: 27.5 / 21.6 for 16, 29.1 / 24.9 for 200; 4096 x 14336, b = 512:
-// 57.6 / 50.8 for one, 62.7 / 60.2 for three, 53.7 / 63.5 for 16; 4096 x 4096, b = 512, 8 tokens: 39.5 / 46.6.
-// fp32, 512 x 768, b = 64: 27.7 / 17.1 for 16, 30.6 / 22.0 for 200.
+// dependent stages, and lose from half of that on.  Forwards, us, with transposes / in place: bf16 512 x 1376, b = 64: 24.5 / 16.4 for one token, 26.1 / 20.8 for 16,
+// 28.5 / 24.2 for 200; 480 x 960, b = 96: 24.0 / 16.1, 26.3 / 21.9, 27.0 / 23.7; 1024 x 1024, b = 128, 33 tokens 27.3 / 23.0, 100: 28.4 / 24.0 (128 tokens, before: 21.8 / 25.2,
+// as bf16 transposes of whole 64-token tiles are half as dear); fp32 512 x 768, b = 64: 26.3 / 16.0, 25.9 / 16.0, 29.8 / 21.1; 2048 x 2048, b = 256: 37.9 / 27.5, 38.7 / 29.8;
+// 4096 x 4096, b = 512: 61.9 / 54.4, three tokens 62.9 / 59.0, 16: 62.8 / 64.0.
 bool reads_tokens_in_place(const poetx_linear_desc* d) {
   if (d->layout != POETX_TOKEN_MAJOR || g_force_fma.load()) return false;
   const i64 N = d->n_tokens;

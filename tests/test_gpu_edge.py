@@ -223,13 +223,19 @@ RAGGED_LAYERS = [
     (1056, 768, 2001, 16, "bf16"),      # ... on one side only
     # a handful of tokens
     (512, 768, 1, 256, "bf16"),
-    (1024, 512, 7, 512, "bf16"),        # a contraction of fewer than eight steps per wave, and with a remainder
+    (1024, 512, 7, 512, "bf16"),        # a contraction of four steps per wave, forward, none of the groups of eight
+    (2304, 512, 5, 256, "bf16"),        # nine steps per wave: a group and one more
     (1472, 960, 16, 64, "bf16"),
     (256, 384, 17, 128, "bf16"),        # two token tiles
     (768, 512, 32, 256, "bf16"),        # the last that takes the short kernels ...
     (768, 512, 33, 256, "bf16"),
-    (2048, 8192, 13, 256, "bf16"),      # four row tiles per workgroup
-    (4096, 4608, 17, 512, "bf16"),      # ... of a larger weight
+    (2048, 8192, 13, 256, "bf16"),
+    (512, 12288, 13, 512, "bf16"),      # four row tiles per workgroup
+    (4096, 4608, 17, 512, "bf16"),      # the short kernels refuse this weight from 17 tokens on ...
+    (8192, 512, 8, 256, "bf16"),        # ... and for few rows by tokens times contraction: the last that they take
+    (8192, 512, 9, 256, "bf16"),
+    (4096, 1024, 32, 512, "bf16"),      # ... for more rows
+    (4352, 1024, 31, 256, "bf16"),
     # layers that are padded to whole 256-token tiles
     (2048, 2048, 100, 256, "bf16"),     # fewer tokens than a tile
     (2048, 2304, 192, 256, "bf16"),     # a multiple of the 64-token tiles

@@ -17,7 +17,7 @@
 //
 // What bounds it: latency.  A step of a 64-block is 2048 cycles of matrix instructions backward (512 forward) on a quarter of the chip's
 // SIMDs where a layer has 20 to 30 blocks, the rest loads and barriers.  Launches, us, a workgroup per block -> 16 columns of one: 30 blocks of 64,
-// k = 4, build 8.8 -> 6.2, backward 20.5 -> 10.8 (28 blocks: 23.8 -> 11.7); 16 of 32 backward 9.4 -> 6.5; whole calls, 30 blocks of 128: 39 -> 12 and 68 -> 25.
+// k = 4, build 8.8 -> 6.2, backward 20.5 -> 10.8 (28 blocks: 23.8 -> 11.7); whole calls, 30 blocks of 128: 39 -> 12 and 68 -> 25.
 // Error of the packed gradient against 64 bits 7.3e-8 -> 4.4e-8.
 #include "poetx_kernels.h"
 
@@ -135,6 +135,41 @@ struct BwdArgs {
   int first;             // number of the launch's first workgroup
 };
 
+// The parts of a block's dL/dG into LDS, added in order, zero outside the live side; the loads of ZU parts are in flight together (whole blocks, backward calls, us,
+// one part at a time / four: 256 x 256, b = 32, 4096 tokens 41 / 37; 512 x 512, b = 64, 8192 tokens, stripes 59 / 51).  More than two cost blocks of 32 a wave per SIMD.
+template <int BP, int NTH, int ZU>
+__device__ __forceinline__ void load_d(float* D, const BwdSide& sd, i64 j, Geometry s, int tid) {
+  constexpr int LD = BP + 4, NE = BP * BP / NTH;
+  const float* dG = sd.dG + j * (i64)s.b * s.b;
+  float v[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) v[e] = 0.f;
+  int z = 0;
+  auto add = [&](auto N_) {
+    constexpr int N = decltype(N_)::value;
+    float q[N][NE];
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const int idx = tid + e * NTH, i = idx / BP, c = idx % BP;
+        q[u][e] = dG[(z + u) * sd.stride + (i < s.side && c < s.side ? i * s.b + c : 0)];
+      }
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int e = 0; e < NE; ++e) v[e] += q[u][e];
+    z += N;
+  };
+  while (z + ZU <= sd.nsplit) add(std::integral_constant<int, ZU>{});
+  while (z < sd.nsplit) add(std::integral_constant<int, 1>{});
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int idx = tid + e * NTH, i = idx / BP, c = idx % BP;
+    D[i * LD + c] = i < s.side && c < s.side ? v[e] : 0.f;
+  }
+}
+
 template <int NT>
 __global__ __launch_bounds__(64 * NT) void series_small_bwd_kernel(BwdArgs a) {
   constexpr int BP = NT * 16, LD = BP + 4, NTH = 64 * NT, ST = NT * 64;
@@ -149,37 +184,7 @@ __global__ __launch_bounds__(64 * NT) void series_small_bwd_kernel(BwdArgs a) {
   const Geometry s{b, block_side(sd.d, b, (int)j)};
   const i64 L = (i64)b * (b - 1) / 2;
   load_q<BP, NTH>(Q, sd.theta + j * L, s, tid);
-  const float* dG = sd.dG + j * (i64)b * b;
-  {   // the parts of D, added in order, zero outside the live side; the loads of several parts are in flight together
-    constexpr int NE = BP * BP / NTH, ZU = NT <= 4 ? 4 : 1;
-    float v[NE];
-#pragma unroll
-    for (int e = 0; e < NE; ++e) v[e] = 0.f;
-    int z = 0;
-    auto add = [&](auto N_) {
-      constexpr int N = decltype(N_)::value;
-      float q[N][NE];
-#pragma unroll
-      for (int u = 0; u < N; ++u)
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-          const int idx = tid + e * NTH, i = idx / BP, c = idx % BP;
-          q[u][e] = dG[(z + u) * sd.stride + (i < s.side && c < s.side ? i * b + c : 0)];
-        }
-#pragma unroll
-      for (int u = 0; u < N; ++u)
-#pragma unroll
-        for (int e = 0; e < NE; ++e) v[e] += q[u][e];
-      z += N;
-    };
-    while (z + ZU <= sd.nsplit) add(std::integral_constant<int, ZU>{});
-    while (z < sd.nsplit) add(std::integral_constant<int, 1>{});
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const int idx = tid + e * NTH, i = idx / BP, c = idx % BP;
-      D[i * LD + c] = i < s.side && c < s.side ? v[e] : 0.f;
-    }
-  }
+  load_d<BP, NTH, NT <= 4 ? 4 : 1>(D, sd, j, s, tid);
   __syncthreads();
   const int row = 16 * p.w + p.x, col = p.ct * 16 + p.x, r0 = 16 * p.w + 4 * p.g;
   const float sk = a.k & 1 ? -1.f : 1.f;          // (-1)^k
@@ -242,7 +247,7 @@ __global__ __launch_bounds__(64 * NT) void series_small_bwd_kernel(BwdArgs a) {
   }
 }
 
-// ---- whole blocks.  Many blocks fill the chip by themselves; then half the products count for more: a workgroup owns a block, a wave 16
+// ---- whole blocks.  Many blocks fill the chip by themselves, and those of 32 are short chains anyway; then half the products count for more: a workgroup owns a block, a wave 16
 // columns of it and all rows.  Backward
 //   V_0 = D^T, V_m = Q V_{m-1},  W_m = 2 (V_0 + .. + V_m) - V_m,   Y_0 = D,  Y_m = W_m^T - Q Y_{m-1},  dL/dQ = Y_k,  dtheta_ic = Y_ic - Y_ci:
 // half of the waves carry V and half carry Y; W_m crosses over through LDS, transposed by the read, one barrier per order (two buffers; one
@@ -340,26 +345,7 @@ __global__ __launch_bounds__(128 * NT) void series_small_bwd_whole_kernel(BwdArg
   const i64 L = (i64)b * (b - 1) / 2;
   load_q<BP, NTH>(Q, sd.theta + j * L, s, tid);
   float* D = W0;
-  const float* dG = sd.dG + j * (i64)b * b;
-  {   // the parts of D, added in order; the loads of a thread's elements are in flight together
-    constexpr int NE = BP * BP / NTH;
-    float v[NE];
-#pragma unroll
-    for (int e = 0; e < NE; ++e) v[e] = 0.f;
-    for (int z = 0; z < sd.nsplit; ++z) {
-      const float* part = dG + z * sd.stride;
-#pragma unroll
-      for (int e = 0; e < NE; ++e) {
-        const int idx = tid + e * NTH, i = idx / BP, c = idx % BP;
-        if (i < b && c < b) v[e] += part[i * b + c];
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const int idx = tid + e * NTH;
-      D[(idx / BP) * LD + idx % BP] = v[e];
-    }
-  }
+  load_d<BP, NTH, NT == 2 ? 2 : NT == 4 ? 4 : 1>(D, sd, j, s, tid);
   __syncthreads();
   const int x = lane & 15, g = lane >> 4;
   const bool isV = wave < NT;
@@ -434,16 +420,18 @@ constexpr int bwd_whole_lds() { return (NT <= 4 ? 3 : 2) * 16 * NT * (16 * NT + 
 template <class K>
 bool lds_set(K kern, int bytes) { return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; }
 
-// Stripes or whole blocks.  us, whole / stripes, k = 4: backward, blocks of 64: 30 of them 13.3 / 9.7, 64: 13.5 / 10.2, 128: 13.3 / 14.2, 320: 21.9 / 32.9; of
-// 128: 30: 68.0 / 27.7, 64: 68.1 / 53.5, 128: 68.8 / 101.5; build, of 128: 30: 39.2 / 14.8, 64: 39.3 / 27.7, 128: 39.5 / 52.8 (a workgroup of the
-// stripes fills a CU's LDS there), of 64: 30: 9.4 / 8.0, at k = 5
-// 160: 11.0 / 10.1, 193: 10.7 / 11.4; at k = 1 64 blocks of 128 17.3 / 21.5, 320 of 64 8.1 / 8.8.
-inline bool in_stripes(i64 nb, int b, int k) { return nb * ceil_div(b, 16) <= (b <= 64 ? 384 : k < 3 ? 256 : 512); }
+// Stripes or whole blocks, by the workgroups that stripes would be.  us, whole / stripes: backward, k = 4, blocks of 64: 30 of them 12.8 / 9.5, 64: 12.8 / 9.7, 96: 12.8 / 13.4,
+// 160: 13.0 / 20.5, 320: 22 / 32; of 48: 60: 12.5 / 9.4, 100: 12.5 / 13.1; of 128: 30: 66 / 25, 64: 67 / 50, 80: 67 / 70, 128: 67 / 93 (a workgroup of the stripes fills a
+// CU's LDS there), at k = 1 64: 23.4 / 23.3; of 32 and less whole is the faster form of any number (16 of 32: 4.8 / 6.1; with 13 token ranges to add up 256 x 256 x 512
+// backward 21.8 / 23.3).  Build, of 128: 30: 39.2 / 14.8, 64: 39.3 / 27.7, 128: 39.5 / 52.8, of 64: 30: 9.4 / 8.0, at k = 5 160: 11.0 / 10.1, 193: 10.7 / 11.4; at k = 1
+// 64 of 128 17.3 / 21.5, 320 of 64 8.1 / 8.8.  Both forms of the build have the same bits; those of the backward add up in another order.
+inline bool build_in_stripes(i64 nb, int b, int k) { return nb * ceil_div(b, 16) <= (b <= 64 ? (k < 3 ? 384 : 640) : k < 3 ? 256 : 512); }
+inline bool bwd_in_stripes(i64 nb, int b) { return b > 32 && nb * ceil_div(b, 16) <= (b <= 64 ? 256 : 512); }
 
 template <int NT>
 void build_t(const float* theta, int d, int b, int k, float* G, uint16_t* E, hipStream_t st) {
   const i64 nb = ceil_div(d, b);
-  if (b > 64 || k < 3 ? !in_stripes(nb, b, k) : nb * ceil_div(b, 16) > 640) {
+  if (!build_in_stripes(nb, b, k)) {
     static const bool configured = lds_set(series_small_build_whole_kernel<NT>, build_whole_lds<NT>());
     (void)configured;
     launch_in_rows(nb, [&](int first, unsigned count) {
@@ -462,21 +450,23 @@ void build_t(const float* theta, int d, int b, int k, float* G, uint16_t* E, hip
 template <int NT>
 void bwd_t(BwdArgs a, hipStream_t st) {
   const i64 nb = (i64)a.s[0].nb + a.s[1].nb;
-  if (!in_stripes(nb, a.b, a.k)) {
-    static const bool configured = lds_set(series_small_bwd_whole_kernel<NT>, bwd_whole_lds<NT>());
-    (void)configured;
-    launch_in_rows(nb, [&](int first, unsigned count) {
-      a.first = first;
-      hipLaunchKernelGGL(series_small_bwd_whole_kernel<NT>, dim3(count), dim3(128 * NT), bwd_whole_lds<NT>(), st, a);
-    });
-    return;
+  if constexpr (NT > 2) {
+    if (bwd_in_stripes(nb, a.b)) {
+      static const bool configured = lds_set(series_small_bwd_kernel<NT>, bwd_lds<NT>());
+      (void)configured;
+      a.stripes = ceil_div(a.b, 16);
+      launch_in_rows(nb * a.stripes, [&](int first, unsigned count) {
+        a.first = first;
+        hipLaunchKernelGGL(series_small_bwd_kernel<NT>, dim3(count), dim3(64 * NT), bwd_lds<NT>(), st, a);
+      });
+      return;
+    }
   }
-  static const bool configured = lds_set(series_small_bwd_kernel<NT>, bwd_lds<NT>());
+  static const bool configured = lds_set(series_small_bwd_whole_kernel<NT>, bwd_whole_lds<NT>());
   (void)configured;
-  a.stripes = ceil_div(a.b, 16);
-  launch_in_rows(nb * a.stripes, [&](int first, unsigned count) {
+  launch_in_rows(nb, [&](int first, unsigned count) {
     a.first = first;
-    hipLaunchKernelGGL(series_small_bwd_kernel<NT>, dim3(count), dim3(64 * NT), bwd_lds<NT>(), st, a);
+    hipLaunchKernelGGL(series_small_bwd_whole_kernel<NT>, dim3(count), dim3(128 * NT), bwd_whole_lds<NT>(), st, a);
   });
 }
 

@@ -34,6 +34,7 @@ pytestmark = pytest.mark.gpu
     (192, 288, 8, 96, 2),
     (192, 288, 9, 96, 2),
     (256, 128, 1041, 64, 2),    # tails behind whole tiles
+    (2592, 1950, 33, 64, 3),    # 72 blocks: the sides' series backward in stripes each, in whole blocks together
     (256, 384, 512, 128, 2),    # every tile and stage whole, and all but the last: the block gradients of 520 tokens
     (256, 384, 520, 128, 2),
     # other tiles and splits that the rule gives
@@ -141,6 +142,54 @@ def test_small_block_series(lib, b, k):
         got = to_np(dth) - (1.0 if acc else 0.0)
         assert rel_err(got, want) <= 1e-5
         assert np.all(got[-1, dead] == 0)
+
+
+@pytest.mark.parametrize("b,nb,k", [
+    # the last count in column stripes and the first of whole blocks: backward ...
+    (64, 64, 4), (64, 65, 4), (48, 85, 2), (48, 86, 2), (128, 64, 3), (128, 65, 3), (100, 73, 1), (100, 74, 1),
+    # ... build (below three powers, and from three on)
+    (64, 96, 2), (64, 97, 2), (64, 160, 3), (64, 161, 3), (128, 32, 2), (128, 33, 2), (32, 192, 1), (32, 193, 1), (32, 320, 5), (32, 321, 5),
+])
+def test_small_block_series_of_many_blocks(lib, b, nb, k):
+    """Both forms of the one-launch fp32 series on either side of the block counts where it changes from one to the other: first, middle
+    and ragged last block against the oracle in fp32 accuracy (sums of at most 128 k fp32 terms), dead slots, accumulate.  Blocks have
+    the bits that they have alone; packed gradients too, up to a side of 32, where the backward has one form."""
+    r, L = b // 2 + 1, b * (b - 1) // 2
+    d = (nb - 1) * b + r
+    rng = np.random.Generator(np.random.PCG64(9700 + b + nb + k))
+    theta = round_f32(rng.standard_normal((nb, L)) * 0.02)
+    iu, ju = np.triu_indices(b, k=1)
+    dead = (iu >= r) | (ju >= r)
+    theta[-1, dead] = 9.0
+    dG = round_f32(rng.standard_normal((nb, b, b)))
+
+    def run(lo, acc, start):
+        n, dd = nb - lo, d - lo * b
+        th = to_dev(theta[lo:], torch.float32)
+        G = torch.full((n, b, b), float("nan"), dtype=torch.float32, device="cuda")
+        E = torch.full((n, 2, b, b), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ws = torch.empty(max(lib.poetx_cnp_workspace_bytes(dd, b), lib.poetx_cnp_bwd_workspace_bytes(dd, b, k)), dtype=torch.uint8, device="cuda")
+        lib.poetx_cnp_build(th, dd, b, k, lib.CNP_FP32, G, E, ws)
+        dth = torch.full_like(th, start)
+        lib.poetx_cnp_bwd(th, to_dev(dG[lo:], torch.float32), dd, b, k, lib.CNP_FP32, dth, acc, ws)
+        torch.cuda.synchronize()
+        return G, E, dth
+    G, E, dth = run(0, False, float("nan"))
+    added = to_np(run(0, True, 1.0)[2]) - 1.0
+    eye = np.eye(b)
+    for at, side in (([0, nb // 2], b), ([nb - 1], r)):
+        span = (len(at) - 1) * b + side
+        Q = orc.skew_from_packed(theta[at], b, span)
+        ref = orc.cnp(Q, k) - eye
+        assert rel_err(to_np(G[at]) - eye, ref) <= 1e-5
+        assert rel_err(to_np(E[at])[:, 0], ref) <= 2.0 ** -8
+        want = orc.packed_from_skew_grad(orc.cnp_bwd(Q, dG[at], k), b, span)
+        assert rel_err(to_np(dth[at]), want) <= 1e-5 and rel_err(added[at], want) <= 1e-5
+    assert torch.equal(E[:, 1], E[:, 0].transpose(1, 2))
+    assert bool(torch.isfinite(dth).all()) and np.all(to_np(dth)[-1, dead] == 0) and np.all(added[-1, dead] == 0)
+    G2, E2, dth2 = run(nb - 2, False, float("nan"))
+    assert torch.equal(G2, G[-2:]) and torch.equal(E2, E[-2:])
+    assert b > 32 or torch.equal(dth2, dth[-2:])
 
 
 @pytest.mark.parametrize("m,n,N,b", [(2048, 2304, 1793, 256), (2560, 2048, 2047, 512), (2048, 2048, 1992, 128)])

@@ -135,8 +135,9 @@ struct BwdArgs {
   int first;             // number of the launch's first workgroup
 };
 
-// The parts of a block's dL/dG into LDS, added in order, zero outside the live side; the loads of ZU parts are in flight together (whole blocks, backward calls, us,
-// one part at a time / four: 256 x 256, b = 32, 4096 tokens 41 / 37; 512 x 512, b = 64, 8192 tokens, stripes 59 / 51).  More than two cost blocks of 32 a wave per SIMD.
+// The parts of a block's dL/dG into LDS, added in order, zero outside the live side; the loads of ZU parts are in flight together (backward calls, us,
+// one part at a time / ZU: whole blocks 256 x 256, b = 32, 4096 tokens 41 / 37; stripes 512 x 512, b = 64, 8192 tokens 59 / 51).  More than two would cost whole blocks the
+// registers of a fifth wave per SIMD (768 of 64, k = 4: 32.4 / 40.7 with four).
 template <int BP, int NTH, int ZU>
 __device__ __forceinline__ void load_d(float* D, const BwdSide& sd, i64 j, Geometry s, int tid) {
   constexpr int LD = BP + 4, NE = BP * BP / NTH;
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(128 * NT) void series_small_bwd_whole_kernel(BwdArg
   const i64 L = (i64)b * (b - 1) / 2;
   load_q<BP, NTH>(Q, sd.theta + j * L, s, tid);
   float* D = W0;
-  load_d<BP, NTH, NT == 2 ? 2 : NT == 4 ? 4 : 1>(D, sd, j, s, tid);
+  load_d<BP, NTH, NT <= 4 ? 2 : 1>(D, sd, j, s, tid);
   __syncthreads();
   const int x = lane & 15, g = lane >> 4;
   const bool isV = wave < NT;

@@ -151,11 +151,11 @@ void launch_apply(const uint16_t* V, i64 ldv, uint16_t* out, i64 ldo, int d, int
 // contraction, where the edge kernels split; the second sixteen tokens double it.  Whole forwards, us, the edge kernels / these, feature major, token major (large weights
 // from memory): 2048 x 2048, b = 256, one token 20.3 / 11.1, 20.4 / 11.0, 16: 20.5 / 13.3, 28.7 / 14.6, 32: 19.0 / 16.8, 29.0 / 19.2; b = 128, 16: 18.9 / 11.8,
 // 25.5 / 13.0; b = 64: 18.2 / 11.4, 24.2 / 12.5; 4096 x 4096, b = 512, 16: 29.1 / 22.7, 41.6 / 26.1, 32: 27.0 / 30.3, 40.7 / 38.2; 14336 x 4096, 16: 44.3 / 40.8,
-// 56.9 / 41.8; 4096 x 14336, 4: 46.7 / 34.4, 49.6 / 34.6, 8: 42.8 / 37.6, 52.3 / 38.4.  Refused: 512 x 14336, 16: 22.6 / 33.7, 32: 26.2 / 48 (feature major); 2048 x 8192, 32:
-// 27.9 / 36.6; 10240 x 8192, 16: 50.5 / 58.7; 4096 x 14336, 16: 42.9 / 44.2.
+// 56.9 / 41.8; 4096 x 14336, 4: 46.7 / 34.4, 49.6 / 34.6, 8: 42.8 / 37.6, 52.3 / 38.4; 512 x 3328, 25 token-major tokens
+// 28.0 / 19.8.  Refused: 512 x 14336, 16: 22.6 / 33.7, 32: 26.2 / 48 (feature major); 2048 x 8192, 32: 27.9 / 36.6; 10240 x 8192, 16: 50.5 / 58.7; 4096 x 14336, 16: 42.9 / 44.2.
 bool few_tokens_supported(int n, int m, int b, i64 N) {
   return (b == 64 || b == 128 || b == 256 || b == 512) && n % b == 0 && m % b == 0 && n < (1 << 22) && m < (1 << 22) &&
-         (N <= 16 || (N <= 32 && (i64)n * m <= 1 << 24)) && m * N <= (n < 1024 || n > 8192 ? 1 << 16 : 1 << 17);
+         (N <= 16 || (N <= 32 && (i64)n * m <= 1 << 24)) && m * N <= (n < 1024 ? 3 << 15 : n > 8192 ? 1 << 16 : 1 << 17);
 }
 
 void few_apply(const void* V, i64 ldv, bool v_tm, void* out, i64 ldo, bool out_tm, int d, int N, const int32_t* perm, const void* E, int b, int trans,

@@ -281,8 +281,8 @@ RAGGED_LAYERS = [
     (2048, 8192, 13, 256, "bf16"),
     (512, 12288, 13, 512, "bf16"),      # four row tiles per workgroup
     (4096, 4608, 17, 512, "bf16"),      # the short kernels refuse this weight from 17 tokens on ...
-    (8192, 512, 8, 256, "bf16"),        # ... and for few rows by tokens times contraction: the last that they take
-    (8192, 512, 9, 256, "bf16"),
+    (8192, 512, 12, 256, "bf16"),       # ... and for few rows by tokens times contraction: the last that they take
+    (8192, 512, 13, 256, "bf16"),
     (4096, 1024, 32, 512, "bf16"),      # ... for more rows
     (4352, 1024, 31, 256, "bf16"),
     # layers that are padded to whole 256-token tiles

@@ -291,8 +291,6 @@ void lds_cnp_build(const float* theta, int nb, int k, float* G_f32, void* E_bf16
   hipLaunchKernelGGL(cnp_build_kernel, chain_grid(nb), dim3(512), 0, st, BuildArgs{Qf, theta, k, nb, G_f32, (uint16_t*)E_bf16});
 }
 
-size_t lds_cnp_bwd_ws_floats(int nb) { return 2 * (size_t)nb * LB * LB; }
-
 void lds_cnp_bwd(const SeriesSide* sides, int nsides, int k, int accumulate, float* ws, hipStream_t st) {
   const bool two = nsides > 1;
   const int nb0 = sides[0].d / LB, nb1 = two ? sides[1].d / LB : 0, nb = nb0 + nb1;

@@ -65,13 +65,11 @@ int check_desc(const poetx_linear_desc* d) {
   return POETX_OK;
 }
 
-// dG plus the chain's scratch of nb blocks: max(k + 2, 5) floats per element, more than any of the kernel families
-// lays out now (the tiled ones five, the on-chip chain two); the figure stays, as callers size workspaces by it
+// dG plus the chain's scratch of nb blocks.  The b = 512 chain lays out five floats per element, the plain one four, the on-chip one of b = 256 two;
+// what k + 2 > 5 reserves beyond that is slack, left as it has always been reported.
 size_t cnp_bwd_ws_floats(i64 nb, int b, int k) {
   const size_t elems = (size_t)nb * b * b;
-  size_t chain = (size_t)(k + 2 > 5 ? k + 2 : 5) * elems;
-  if (lds_cnp_supported(b, b) && lds_cnp_bwd_ws_floats((int)nb) > chain) chain = lds_cnp_bwd_ws_floats((int)nb);
-  return elems + chain;
+  return elems + (size_t)(k + 2 > 5 ? k + 2 : 5) * elems;
 }
 // ... of a call's series: those of one side after the other, or of both sides together
 size_t cnp_bwd_ws_floats(const poetx_linear_desc* d) {

@@ -148,8 +148,7 @@ void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumul
 // b = 256: whole chain of a block in one launch, block resident on chip (mfma_cnp_lds.hip).
 bool lds_cnp_supported(int d, int b);
 void lds_cnp_build(const float* theta, int nb, int k, float* G_f32, void* E_bf16, float* ws, hipStream_t st);   // ws: half a float per block element
-// Backward of one or two sides (dG of a side: one matrix per block, nsplit = 1).  ws: lds_cnp_bwd_ws_floats(all blocks) floats.
-size_t lds_cnp_bwd_ws_floats(int nb);
+// Backward of one or two sides (dG of a side: one matrix per block, nsplit = 1).  ws: 2 floats per block element.
 void lds_cnp_bwd(const SeriesSide* sides, int nsides, int k, int accumulate, float* ws, hipStream_t st);
 // b = 256, nb0 + nb1 blocks of two sides: bf16(Q), or where dL/dG is given bf16(-Q) and bf16(dL/dG), as the chains' fragments; and their dL/dQ (tiles
 // in the chains' order) -> packed gradients (skew_tiled.hip)

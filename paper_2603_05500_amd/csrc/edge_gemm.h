@@ -23,6 +23,7 @@ namespace edge {
 
 using mm::bf16x8;
 using mm::floatx16;
+using mm::lds_barrier;
 using mm::short4v;
 using mm::short8v;
 
@@ -135,10 +136,6 @@ __device__ inline void store8(float* p, const float (&v)[8], int n) {
       if (e < n) p[e] = v[e];
   }
 }
-
-// this wave's LDS accesses have been carried out, and every other wave's; loads from memory stay in flight, which __syncthreads()
-// would wait for
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // chunk swizzle of an X-major bf16 tile (see kx_chunk); 32-wide rows need none: the four k rows of a
 // transposing read are 64 bytes apart and already fall on different banks

@@ -137,7 +137,7 @@ bool mfma_cnp_supported(int d, int b) { return (b == 256 || b == 512) && d % b =
 // ws: 3 floats per block element: Q (later 2Q + 2X) in fp32, then bf16(Q), bf16(X) and two chain values.
 void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void* E_bf16, float* ws, hipStream_t st) {
   const int all = d / b;
-  if (lds_cnp_supported(d, b)) {   // whole chain in one launch, block resident in LDS
+  if (lds_cnp_supported(d, b)) {   // whole chain in one launch, rows of the block in registers
     lds_cnp_build(theta, all, k, G_f32, E_bf16, ws, st);
     return;
   }
@@ -179,7 +179,7 @@ void mfma_cnp_build(const float* theta, int d, int b, int k, float* G_f32, void*
 }
 
 void mfma_cnp_bwd(const SeriesSide* sides, int nsides, int b, int k, int accumulate, float* ws, hipStream_t st) {
-  if (lds_cnp_supported(sides[0].d, b)) {   // block resident in LDS
+  if (lds_cnp_supported(sides[0].d, b)) {   // one launch, left factors in registers
     lds_cnp_bwd(sides, nsides, k, accumulate, ws, st);
     return;
   }

@@ -33,6 +33,7 @@ namespace {
 
 using mm::bf16x8;
 using mm::floatx16;
+using mm::lds_barrier;
 
 constexpr int LB = 256;                  // block side
 constexpr int NT = LB / 32;              // row tiles = waves = column stripes
@@ -55,10 +56,6 @@ __device__ __forceinline__ bf16x8 pack8(const floatx16& a, int u) {
   for (int e = 0; e < 4; ++e) r[e] = mm::pack2_bf16(a[8 * u + 2 * e], a[8 * u + 2 * e + 1]);
   return __builtin_bit_cast(bf16x8, r);
 }
-
-// this wave's LDS accesses have been carried out, and every other wave's: not __syncthreads(), which would wait for global stores
-// as well
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Where a wave of a chain stands.  The eight stripes of a block have ids 8 apart: one XCD, whose L2 brings the block's fragments in once.
 struct Place {
@@ -149,45 +146,45 @@ __global__ __launch_bounds__(512, 4) void cnp_build_kernel(BuildArgs a) {
       lds_barrier();
     }
   }
-      if (a.G) {
-        float* gc = a.G + blk + (i64)(32 * w + 4 * h) * LB + 32 * ct + n;
-  #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int r = 8 * (v >> 2) + (v & 3);
-          gc[r * LB] = acc[v] + (w == ct && r + 4 * h == n ? 1.f : 0.f);
-        }
+  if (a.G) {
+    float* gc = a.G + blk + (i64)(32 * w + 4 * h) * LB + 32 * ct + n;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int r = 8 * (v >> 2) + (v & 3);
+      gc[r * LB] = acc[v] + (w == ct && r + 4 * h == n ? 1.f : 0.f);
+    }
+  }
+  if (a.E) {
+    // The pair leaves through 2 KB of the buffer that the last product did not read, row by row: 64 bytes of 16 rows per store.
+    // Rows of 32 elements in 16-byte chunks, XORed by the row (writes of one column, reads of 16 rows).
+    uint16_t* st = reinterpret_cast<uint16_t*>(lds + (a.k & 1) * Y_LDS) + w * 1024;
+    uint16_t* e0 = a.E + 2 * blk;
+    const int r = lane >> 2, ch = lane & 3;
+    auto out = [&](uint16_t* at) {           // at: the tile's first element
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int row = r + 16 * i;
+        *reinterpret_cast<u32x4*>(at + row * LB + 8 * ch) = *reinterpret_cast<const u32x4*>(st + row * 32 + 8 * (ch ^ ((row >> 2) & 3)));
       }
-      if (a.E) {
-        // The pair leaves through 2 KB of the buffer that the last product did not read, row by row: 64 bytes of 16 rows per store.
-        // Rows of 32 elements in 16-byte chunks, XORed by the row (writes of one column, reads of 16 rows).
-        uint16_t* st = reinterpret_cast<uint16_t*>(lds + (a.k & 1) * Y_LDS) + w * 1024;
-        uint16_t* e0 = a.E + 2 * blk;
-        const int r = lane >> 2, ch = lane & 3;
-        auto out = [&](uint16_t* at) {           // at: the tile's first element
-  #pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            const int row = r + 16 * i;
-            *reinterpret_cast<u32x4*>(at + row * LB + 8 * ch) = *reinterpret_cast<const u32x4*>(st + row * 32 + 8 * (ch ^ ((row >> 2) & 3)));
-          }
-        };
-  #pragma unroll
-        for (int v = 0; v < 16; v += 2) {
-          const uint32_t pk = mm::pack2_bf16(acc[v], acc[v + 1]);
-          const int row = 8 * (v >> 2) + 4 * h + (v & 3);
-          const int at = 8 * ((n >> 3) ^ ((row >> 2) & 3)) + (n & 7);       // the same for row + 1
-          st[row * 32 + at] = (uint16_t)pk;
-          st[(row + 1) * 32 + at] = (uint16_t)(pk >> 16);
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own writes
-        out(e0 + 32 * w * LB + 32 * ct);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read back before the area is rewritten
-  #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<uint2*>(st + n * 32 + 8 * (g ^ ((n >> 2) & 3)) + 4 * h) =
-              make_uint2(mm::pack2_bf16(acc[4 * g], acc[4 * g + 1]), mm::pack2_bf16(acc[4 * g + 2], acc[4 * g + 3]));
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        out(e0 + (i64)LB * LB + 32 * ct * LB + 32 * w);
-      }
+    };
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      const uint32_t pk = mm::pack2_bf16(acc[v], acc[v + 1]);
+      const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+      const int at = 8 * ((n >> 3) ^ ((row >> 2) & 3)) + (n & 7);       // the same for row + 1
+      st[row * 32 + at] = (uint16_t)pk;
+      st[(row + 1) * 32 + at] = (uint16_t)(pk >> 16);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own writes
+    out(e0 + 32 * w * LB + 32 * ct);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read back before the area is rewritten
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<uint2*>(st + n * 32 + 8 * (g ^ ((n >> 2) & 3)) + 4 * h) =
+          make_uint2(mm::pack2_bf16(acc[4 * g], acc[4 * g + 1]), mm::pack2_bf16(acc[4 * g + 2], acc[4 * g + 3]));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    out(e0 + (i64)LB * LB + 32 * ct * LB + 32 * w);
+  }
 }
 
 // ---- backward

@@ -121,6 +121,9 @@ __device__ inline void dma16(const void* gptr, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory");
 }
 
+// This wave's LDS accesses have been carried out, and every other wave's; memory traffic stays in flight, which __syncthreads() would wait for.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 template <int N>
 __device__ inline void wait_vmcnt_and_barrier() {
   static_assert(N >= 0 && N < 64, "vmcnt range");

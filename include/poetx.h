@@ -56,7 +56,10 @@
  *    a dense product whose three dimensions are multiples of 128 with at least 192 output
  *    tiles of 128 x 128.  The dense products, applies and block gradients of everything else
  *    run on an edge-handling matrix-core product of the tensors' type (applies of blocks up to
- *    b = 16 over many tokens on the plain fp32-FMA kernel).  Series: precision
+ *    b = 16 over many tokens on the plain fp32-FMA kernel).  A handful of bf16 tokens, where
+ *    b = 64, 128, 256 or 512 divides both dimensions: the forward, and B where it is recomputed,
+ *    on short kernels of their own (up to 16 tokens, 32 for weights up to 2^24 elements, and
+ *    d_in * tokens up to 2^17; 3 * 2^15 for d_out below 1024, 2^16 above 8192).  Series: precision
  *    POETX_CNP_BF16 with b = 256 or 512 dividing the dimension on bf16 matrix instructions;
  *    blocks up to b = 128 on fp32 ones whatever the precision, one launch per direction; all
  *    others, and poetx_perm_blockdiag_apply_right, on plain fp32-FMA kernels.
@@ -221,7 +224,12 @@ int poetx_cnp_build_static(const float* theta, int32_t d, int32_t b, int32_t k, 
  * over blocks: dG [nb][b][b] float = dL/dG -> dtheta [nb][b(b-1)/2] float, overwritten when
  * accumulate == 0 and added to otherwise; theta, d, b, k, precision as in poetx_cnp_build (the
  * blocks may be those of several sides or projections laid end to end when b divides each of
- * their dimensions).  ws: poetx_cnp_bwd_workspace_bytes(d, b, k) bytes. */
+ * their dimensions).  ws: poetx_cnp_bwd_workspace_bytes(d, b, k) bytes.
+ * A block and its gradient have the same bits whatever other blocks share the call, with one
+ * exception: for 32 < b <= 128 few and many blocks take different evaluations of the backward, so
+ * that gradients of calls on either side of the line (256 stripes of 16 columns for b <= 64, 512
+ * above: 64 blocks of 64 or of 128) agree to fp32 accuracy (about 1e-7 of their size), not bit for bit.
+ * The same holds inside poetx_linear_bwd, whose call is on the blocks of both sides. */
 size_t poetx_cnp_bwd_workspace_bytes(int32_t d, int32_t b, int32_t k);
 int poetx_cnp_bwd(const float* theta, const float* dG, int32_t d, int32_t b, int32_t k, int32_t precision,
                   float* dtheta, int32_t accumulate, void* ws, size_t ws_bytes, void* stream);
@@ -283,21 +291,21 @@ int poetx_perm_validate(const int32_t* perm, int32_t d, int32_t* scratch, void* 
  * activations between the stages it holds fp32 parts of products that split their contraction,
  * and token counts that are no multiple of 256 make its activations wider: to a multiple of 8, or of
  * 256 where the dense products of a layer with multiples of 256 gain by it (more than 64 tokens and
- * d_in * d_out * padded tokens >= 2^30).  In MB: 2048 x 5632 with 1999 tokens 115 (85 without parts
+ * d_in * d_out * padded tokens >= 2^30).  In MB, k = 5: 2048 x 5632 with 1999 tokens 115 (85 without parts
  * and padding), 8192 x 3072 with 4090 token-major tokens 268 (235), 4096 x 14336 with 70 tokens 158
- * (153), fp32 1024 x 768 with 1001 tokens 15.5 (7.2).  Large whole token counts have neither:
+ * (153), fp32 1024 x 768, b = 64, with 1001 tokens 19.6 (7.2).  Large whole token counts have neither:
  * 14336 x 4096 with 16384 tokens 789.
  */
 size_t poetx_linear_workspace_bytes(const poetx_linear_desc* desc);
 
 /* Which stages of `desc` the streaming matrix-core kernels take (bit set; 16-byte aligned pointers
- * assumed).  Returns a combination of POETX_PATH_* bits, 0 when every stage runs on the edge-handling
- * or plain kernels, or minus a poetx_status when the descriptor is invalid. */
+ * assumed).  Returns a combination of POETX_PATH_* bits, 0 when every stage runs on the edge-handling,
+ * few-token or plain kernels, or minus a poetx_status when the descriptor is invalid. */
 #define POETX_PATH_APPLY 1              /* gather + block-diagonal product + scatter, both sides */
 #define POETX_PATH_DENSE 2              /* both B = W A and dA = W^T dB (the only bit fp32 tensors get) */
 #define POETX_PATH_BLOCKGRAD 4          /* block gradients (two-call backward)                 */
 #define POETX_PATH_SERIES 8             /* series backward on the matrix cores                 */
-#define POETX_PATH_SERIES_ON_CHIP 16    /* ... as one-launch chains with the block in LDS      */
+#define POETX_PATH_SERIES_ON_CHIP 16    /* ... as one-launch chains (b = 256)                   */
 #define POETX_PATH_BWD_ONE_PASS 32      /* poetx_linear_bwd streams each side's gradient once  */
 #define POETX_PATH_W_INT8_IN_KERNEL 64  /* POETX_FLAG_W_INT8_FUSED honoured: codes converted inside the dense kernels */
 int poetx_linear_path(const poetx_linear_desc* desc);

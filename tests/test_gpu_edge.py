@@ -376,8 +376,8 @@ def test_dense_tiles(lib, n, m, N):
 @pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 40, (3,)), (512, 130, (3,)), (256, 130, (2,)), (256, 150, (2,)), (256, 3, (1, 2, 7)), (256, 9, (1, 5)), (256, 200, (4,))])
 def test_matrix_core_series(lib, b, nb, ks):
     """The bf16 series of large blocks, build and backward through poetx_cnp_build / poetx_cnp_bwd: every shape of the
-    recurrences (the tiled one pairs powers: odd and even orders start differently), batches that are worked off in more
-    than one group.  The bound is the error of rounding each product's operands
+    recurrences (the tiled one pairs powers: odd and even orders start differently), batches that the tiled one of b = 512 works off
+    in more than one group and that fill the chip once, in part and more than once in the one launch of b = 256.  The bound is the error of rounding each product's operands
     to bf16 (2^-9 of the first product, relative to terms of its size) with a factor of four."""
     L = b * (b - 1) // 2
     for k in ks:
@@ -487,8 +487,8 @@ def test_block_counts_beyond_one_grid_dimension(lib):
     (256, 20, 140),     # late in it
 ])
 def test_series_groups_of_two_sides(lib, b, nbR, nbP):
-    """The series backward of both sides of a layer in one batch of several groups of blocks: packed gradients bit for bit those
-    of poetx_cnp_bwd, side by side, on the block gradients that the same layer reports."""
+    """The series backward of both sides of a layer in one batch (several groups of blocks of 512, one launch for those of 256): packed
+    gradients bit for bit those of poetx_cnp_bwd, side by side, on the block gradients that the same layer reports."""
     m, n, N, k, bf = nbR * b, nbP * b, 64, 3, torch.bfloat16
     g = torch.Generator(device="cuda").manual_seed(b + nbR)
     normal = lambda *shape: torch.randn(shape, generator=g, device="cuda")

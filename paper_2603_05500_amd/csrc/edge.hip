@@ -25,11 +25,12 @@ Tile apply_tile(i64 batches, i64 M, i64 N) {
 // Dense products: tile and contraction split priced together.  A workgroup takes `lone` us for a stage when it has a CU to itself (`cold` more
 // where the weight is larger than the L2s would keep) and `shared` for each of the workgroups on its CU, of which the fullest CU counts; `fill` stages
 // more to fill the ring and to store.  A split adds a launch of `reduce` us with its gap and its fp32 parts, written and read at 4 TB/s.
-// The constants are fitted to 1520 products of 128 - 14336 rows, 1 - 5000 columns and contractions of 256 - 14336, both directions, weights over 6 MB read from
+// The constants are fitted to 1520 products of 128 - 14336 rows, 1 - 5000 columns and contractions of 128 - 14336, both directions, weights over 6 MB read from
 // memory, each timed with every tile and split: the choice is 1 % slower than the best one on average and takes 10 % (fp32) and 25 % (bf16) less time than a rule
-// that takes the largest tile to fill three quarters of the CUs, with four waves each, and then the split.  us, tile / splits (64D: 64 x 64 with sixteen waves):
+// that takes the largest tile to fill three quarters of the CUs, with four waves each, and then the split.  us of launches one after the other on the same operands (inside a
+// step they come from further away: the first is 30.2 there), tile / splits (64D: 64 x 64 with sixteen waves):
 // fp32 1024 x 768 x 1001 64D/1 27.4, 64/3 29.8, 32/1 31.2; 256 x 256 x 512 32/1 6.2, 32/2 7.4; bf16 1376 x 512 x 1024 64/1 9.6, 32/1 10.7, 128/1 13.8;
-// 1024 x 1536 x 3001 64/1 24.7, 128/2 34.6; 4096 x 14336 x 64 64/12 34.0, 64/4 and 32 at any split over 40; 4192 x 8000 x 1567 128/1 200, 128/4 228, 64/1 275.
+// 1024 x 1536 x 3001 64/1 24.7, 128/2 34.6; 4096 x 14336 x 64 64/12 34.0, 64/8 37.3; 4192 x 8000 x 1567 128/1 200, 128/4 228, 64/1 275.
 // Up to 32 columns of a large weight are bound by its reads, for which this price is too coarse (up to 12 % slower than four workgroups per CU): as many splits as
 // give each CU four workgroups of at least four stages (5632 x 8192 x 24 32/5 25.8, 32/4 29.7; fp32 6208 x 3072 x 2 32/5 27.6, 32/3 33.2).
 struct TileCost {

@@ -163,12 +163,13 @@ struct Shape {
 // How the operands' vectors are loaded; STRIDED and MASKED are about B alone.
 // WHOLE: every tile and stage lies inside both operands, nothing is checked.
 // MASKED (bf16 rows of at least 8 columns whose count is no multiple of 8; B X major): every stage of the last tile ends in tails, and what is
-// branched waits for them -- load_raw, and the mask on the way into LDS.  us, branched / masked: applies of 411 features, b = 256, 28 tokens 6.3 / 5.3;
-// 1258, b = 128, 1501 7.3 / 6.1; 524, b = 64, 302 4.9 / 3.9; but 4122, b = 128, 1032 tokens 11.4 / 11.8.
+// branched waits for them -- load_raw, and the mask on the way into LDS.  us, branched / masked: applies of 411 features, b = 256, 28 tokens 6.3 / 5.1;
+// 1258, b = 128, 1501 7.2 / 5.9; 524, b = 64, 302 4.9 / 3.9; but 4122, b = 128, 1032 tokens 11.0 / 11.5.
 // Elsewhere branches are the better form of an edge, and one stage ahead is enough: the arithmetic of masks and the registers of a second stage cost
-// more than they hide (us, masks and two stages / branches and one: fp32 gradients of 2380 features, b = 48, 3925 tokens 57.3 / 45.1; products of sizes in
-// 32s with few tokens 19 % (bf16) and 6 % (fp32) less time).  A choice between WHOLE and BRANCHED inside one kernel costs the short launches that are
-// not whole up to 5 % (the code), so it is made outside; WHOLE takes gradients of 1024 features, b = 64, 512 tokens from 4.26 to 4.06, bf16 1024 x 1024 x 512 from 9.1 to 8.5.
+// more than they hide (us, masks and two stages / branches and one: fp32 gradients of 2380 features, b = 48, 3925 tokens 57.3 / 46.1; bf16 products of sizes in
+// 32s with 1 - 7 tokens 25 % less time, fp32 ones 7 %).  A choice between WHOLE and BRANCHED inside one kernel costs the short launches that are
+// not whole up to 5 % (the code), so it is made outside; us, BRANCHED / WHOLE: gradients of 1024 features, b = 64, 512 tokens 4.28 / 3.77; bf16 1024 x 1024 x 512 8.4 / 7.5 and,
+// backward, 9.2 / 7.8; fp32 256 x 256 x 512 6.4 / 6.0.
 enum Load { BRANCHED, STRIDED, MASKED, WHOLE };
 
 // Epi: __device__ void operator()(int batch, int split, int row, int col, const float (&v)[8]) -- eight

@@ -311,7 +311,7 @@ void edge_apply_left(int dtype, const void* V, i64 ldv, void* out, i64 ldo, int 
                      const void* blocks, int b, int transpose_G, hipStream_t st) {
   if (dtype == POETX_F32)
     apply_t<float, BRANCHED>((const float*)V, ldv, (float*)out, ldo, d, cols, cols_out, plan_cols, perm, (const float*)blocks, b, transpose_G, st);
-  else if (cols >= 8 && cols % 8 != 0)
+  else if (cols >= 8 && cols % 8 != 0)   // tails, in rows that hold a vector (see Load)
     apply_t<uint16_t, MASKED>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, plan_cols, perm, (const uint16_t*)blocks, b, transpose_G, st);
   else
     apply_t<uint16_t, BRANCHED>((const uint16_t*)V, ldv, (uint16_t*)out, ldo, d, cols, cols_out, plan_cols, perm, (const uint16_t*)blocks, b, transpose_G, st);

@@ -1,9 +1,9 @@
 // poetx_limits: what the MI355X in front of you sustains, next to what the dense product of the
 // library gets out of it.  Measurement tool, not part of the library.
-//   1. matrix-core rate of a loop of nothing but v_mfma_f32_32x32x16_bf16 (one wave per SIMD with a
-//      128 x 128 accumulator tile, and two waves per SIMD), with operands of zeros and with normally
+//   1. matrix-core rate of a loop of nothing but v_mfma_f32_32x32x16_bf16 and of one of v_mfma_f32_16x16x32_bf16
+//      (one wave per SIMD with a 128 x 128 accumulator tile, and two waves per SIMD), with operands of zeros and with normally
 //      distributed operands: the sustained clock, and with it the ceiling of any bf16 product,
-//      depends on how many bits the operands toggle;
+//      depends on how many bits the operands toggle and on how often the accumulators are read and written;
 //   2. plain device-to-device copy rate (the ceiling of the HBM-bound stages);
 //   3. the library's dense product (same kernel, same launch) on one llama-8B shape, as it is and
 //      with its direct-to-LDS loads and / or its LDS fragment reads switched off inside the loop
@@ -39,7 +39,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
     }                                                                               \
   } while (0)
 
-// 4 x 4 MFMA tiles per wave (the dense kernel's wave tile), operands fixed in registers
+// 4 x 4 MFMA tiles per wave (the dense kernel's wave tile), operands in registers, turned over from one pass to the next
 __global__ __launch_bounds__(256) void mfma_loop_kernel(const bf16x8* __restrict__ src, float* out, int iters) {
   bf16x8 a[4], b[4];
   const int tid = blockIdx.x * 256 + threadIdx.x;
@@ -65,7 +65,8 @@ __global__ __launch_bounds__(256) void mfma_loop_kernel(const bf16x8* __restrict
 }
 
 // the same wave tile (128 x 128) out of 8 x 8 tiles of v_mfma_f32_16x16x32_bf16: twice the operand
-// register reads per flop, half the accumulator traffic
+// register reads per flop, half the accumulator traffic.  The operands stay where they are: moves between its shorter
+// MFMAs would cost a third of the rate.
 __global__ __launch_bounds__(256) void mfma16_loop_kernel(const bf16x8* __restrict__ src, float* out, int iters) {
   typedef float floatx4 __attribute__((ext_vector_type(4)));
   bf16x8 a[8], b[8];
@@ -81,9 +82,6 @@ __global__ __launch_bounds__(256) void mfma16_loop_kernel(const bf16x8* __restri
     for (int i = 0; i < 8; ++i)
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    bf16x8 t = a[0];
-    for (int i = 0; i < 7; ++i) a[i] = a[i + 1];
-    a[7] = t;
   }
   float s = 0;
   for (int i = 0; i < 8; ++i)
@@ -162,7 +160,7 @@ static void time_dense(const char* what, const dense::DenseArgs& g, double flops
     xmin = fmin(xmin, d);
     xmax = fmax(xmax, d);
   }
-  printf("  %-58s %.3f ms  %7.1f TFLOP/s   %6.0f cycles per 32-deep stage (32 MFMAs = 1024), %5.0f per tile output, %.2f GHz, "
+  printf("  %-58s %.3f ms  %7.1f TFLOP/s   %6.0f cycles per 32-deep stage (64 MFMAs = 1024), %5.0f per tile output, %.2f GHz, "
          "workgroups live %.0f-%.0f us by XCD\n", what, ms, flops / ms / 1e9, loop / 1024 / g.ktiles, outc / 1024, loop / ticks / 10.0, xmin, xmax);
 }
 
@@ -177,7 +175,7 @@ int main() {
     float* out;
     CHECK(hipMalloc(&d, n * 2));
     CHECK(hipMalloc(&out, 512 * 256 * 4));
-    printf("1. v_mfma_f32_32x32x16_bf16 alone (16 independent accumulator tiles per wave)\n");
+    printf("1. v_mfma_f32_32x32x16_bf16 alone (16 independent accumulator tiles per wave), and 16x16x32 (64 of them)\n");
     for (int mode = 0; mode < 2; ++mode) {
       for (size_t i = 0; i < n; ++i) h[i] = f2b(mode == 0 ? 0.f : nd(rng) * (i < 4 * 65536 * 8 ? 0.02f : 1.f));
       CHECK(hipMemcpy(d, h.data(), n * 2, hipMemcpyHostToDevice));

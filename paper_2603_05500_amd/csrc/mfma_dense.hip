@@ -1,21 +1,4 @@
-// Dense bf16 products of the POET-X linear layer on the matrix cores:
-//   forward  (Eq. 10, mm2):       B  (n x N) = W   (n x m) * A  (m x N)
-//   backward (Sec. 3.5, mm2 bwd): dA (m x N) = W^T (m x n) * dB (n x N)   -- no weight gradient
-// W is row major n x m; activations are feature major (token index contiguous), so the
-// activation operand (and W in the backward product) is contracted over its strided index and
-// is read from LDS with the transposing load.
-//
-// The kernel is a persistent stream: one workgroup per CU, 4 waves (2 x 2, one per SIMD), each
-// wave owning a 128 x 128 piece of a 256 x 256 output tile in 256 accumulator registers
-// (v_mfma_f32_32x32x16_bf16, fp32).  A workgroup walks its list of output tiles; the 32-deep
-// operand stages of ALL its tiles form one stream that flows through a ring of 4 LDS stages,
-// filled by direct-to-LDS loads issued that many stages ahead of the multiplication -- across tile
-// boundaries, so a new tile starts multiplying the moment the previous one is rounded and stored.
-// Per stage there is one barrier, placed after the first of the two k steps, where every wave
-// holds the rest of the stage in registers: the stage's slot is refilled at once.  Loads and
-// fragment reads are pinned to fixed places between the MFMAs (each wave spreads its loads
-// over different places), and the load addresses are a uniform base plus a per-lane offset that
-// never changes, so the loop carries no vector address arithmetic.
+// Dense bf16 products of the POET-X linear layer on the matrix cores (mfma_dense_kernel.h): which tile and split a product takes, and its launches.
 // Products of too few such tiles for the chip take 256 x 128 or 128 x 128 ones, or split their contraction (see pick_plan).
 #include "edge_gemm.h"
 #include "mfma_dense_kernel.h"
@@ -65,25 +48,25 @@ void launch_tile(DenseArgs g, i64 M, i64 N, hipStream_t st) {
 
 // ---- which tile, how many contraction ranges ----------------------------------------------------
 // Estimated time: rounds of the chip, times a tile's time, times the depth.  Measured per 4096 of depth with the whole chip
-// busy: 108 us for a 256 x 256 tile, 0.65 of that for 256 x 128 and 0.40 for 128 x 128 (half and a quarter of the work: smaller
+// busy: 94 us for a 256 x 256 tile, 0.65 of that for 256 x 128 and 0.39 for 128 x 128 (half and a quarter of the work: smaller
 // tiles move more operand bytes per flop), so a smaller tile pays where it takes the place of idle CUs (4096 x 4096 x 2048, 128
-// large tiles: 90 -> 73 us on 256 x 128; 2048 x 2048 x 2048, 64: 44 -> 26 us on 128 x 128).  Splitting the contraction of the
+// large tiles: 90 -> 73 us on 256 x 128; 2048 x 2048 x 2048, 64: 44 -> 26 us on 128 x 128; both with the 32 x 32 x 16 kernel).  Splitting the contraction of the
 // smallest tile adds fp32 parts written and read at about 4 TB/s and a launch (5 us).
 enum { T256 = 0, T256x128 = 1, T128 = 2 };
 struct DensePlan {
   int tile, splits;
 };
 DensePlan pick_plan(i64 M, i64 N, i64 K) {
-  const double cost[3] = {1.0, 0.65, 0.40};
+  const double cost[3] = {1.0, 0.65, 0.39};
   const int bm[3] = {256, 256, 128}, bn[3] = {256, 128, 128};
   DensePlan best{T256, 1};
   double best_us = 0.0;
   for (int t = 0; t < 3; ++t)
     for (int s = 1; s <= (t == T128 ? 16 : 1); s *= 2) {
-      if ((K / BK) % s != 0 || K / s < 256) break;
+      if ((K / BK) % (2 * s) != 0 || K / s < 256) break;   // an even number of stages each
       const double units = (double)(M / bm[t]) * (double)(N / bn[t]) * s;
       const double rounds = (double)(long long)((units + 255) / 256);
-      double us = rounds * cost[t] * 108.0 / 4096.0 * (double)(K / s);
+      double us = rounds * cost[t] * 94.0 / 4096.0 * (double)(K / s);
       if (s > 1) us += 8.0 * s * (double)M * (double)N / 4e6 + 5.0;
       if (best_us == 0.0 || us < 0.97 * best_us) { best_us = us; best = DensePlan{t, s}; }
     }

@@ -7,16 +7,22 @@
 //
 // The kernel is a persistent stream: one workgroup per CU, 4 waves (2 x 2, one per SIMD), each
 // wave owning a 128 x 128 piece of a 256 x 256 output tile in 256 accumulator registers
-// (v_mfma_f32_32x32x16_bf16, fp32; smaller tiles for products with few of them).  A workgroup walks its list of output tiles; the 32-deep
+// (v_mfma_f32_16x16x32_bf16, fp32; smaller tiles for products with few of them).  A workgroup walks its list of output tiles; the 32-deep
 // operand stages of ALL its tiles form one stream that flows through a ring of 4 LDS stages
 // (a fifth buys nothing measurable; its 32 KB stage the output instead),
 // filled by direct-to-LDS loads issued that many stages ahead of the multiplication -- across tile
 // boundaries, so a new tile starts multiplying the moment the previous one is rounded and stored.
-// Per stage there is one barrier, placed after the first of the two k steps, where every wave
-// holds the rest of the stage in registers: the stage's slot is refilled at once.  Loads and
+// A wave multiplies a stage from registers while it reads the next one's fragments into a second set (128 registers for
+// both), so the one barrier of a stage stands at its start, where every wave holds the stage: its slot is refilled at once.  Loads and
 // fragment reads are pinned to fixed places between the MFMAs (each wave spreads its loads
 // over different places), and the load addresses are a uniform base plus a per-lane offset that
-// never changes, so the loop carries no vector address arithmetic.
+// never changes, so the loop carries no vector address arithmetic and no branch.
+//
+// What bounds it is power: the clock falls until the chip keeps its limit, so what counts is energy per flop.  A loop of MFMAs alone on normally
+// distributed operands sustains 2.04 PFLOP/s with 16 x 16 x 32 and 1.77 with 32 x 32 x 16 (an accumulator is read and written
+// once per 32 of depth, not per 16; on zeros both reach 2.45).  The same stream on 32 x 32 x 16, before / now, us, sustained: forward 4096 x 4096 x 16384 413 / 374,
+// 14336 x 4096 x 16384 1420 / 1290; backward 400 / 369, 1405 / 1270; tiles of 256 x 128, 4096 x 4096 x 2048: 67 / 64.7 and 62.8 / 59; of 128 x 128, 2048 x 5632 x 2048:
+// 51.8 / 50.9 and 50.8 / 49.
 #pragma once
 #include <type_traits>
 
@@ -27,7 +33,7 @@ namespace dense {
 
 
 using mm::bf16x8;
-using mm::floatx16;
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 using mm::short4v;
 using mm::short8v;
 
@@ -41,16 +47,20 @@ template <int BM_, int BN_, int NS_>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, NS = NS_;
   static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
-  static constexpr int TM = BM / 64, TN = BN / 64;       // 32 x 32 MFMA tiles of a wave (2 x 2 waves)
-  static constexpr int MF = TM * TN;                     // MFMAs of a k step
-  static constexpr int OUT_BYTES = TN / 2 * 4096;        // per-wave output staging: 32-row x 64-column pieces
+  static constexpr int TM = BM / 32, TN = BN / 32;       // 16 x 16 MFMA tiles of a wave (2 x 2 waves)
+  static constexpr int MF = TM * TN;                     // MFMAs of a stage
+  // MFMAs per fragment read: the four waves' reads take up to half of the time of a stage's MFMAs in LDS (256 x 256; three quarters on 256 x 128, all of it
+  // on 128 x 128); bunched, they would hold up the MFMAs behind them (256 x 256, backward, one / two / three: 391 / 382 / 379 us)
+  static constexpr int RS = MF / (TM + TN) < 3 ? MF / (TM + TN) : 3;
+  static constexpr int OUT_BYTES = TN / 4 * 4096;        // per-wave output staging: 32-row x 64-column pieces
   static constexpr int LDS_BYTES = NS * STAGE_BYTES + NW * OUT_BYTES;
   static constexpr int IPWA = A_BYTES / 1024 / NW;       // direct-to-LDS instructions per wave per operand per stage
   static constexpr int IPWB = B_BYTES / 1024 / NW;
   static constexpr int LPT = IPWA + IPWB;                // loads per stage per wave
   static_assert(NS * LPT < 64, "vmcnt range");
-  static_assert(IPWA <= 4 && IPWB <= 4 && MF % IPWA == 0 && MF % IPWB == 0, "dma16g_s covers groups of four loads");
-  static_assert(TM + TN <= MF, "a fragment piece per MFMA");
+  static constexpr int DS = MF / LPT;                    // MFMAs per load
+  static_assert(IPWA <= 4 && IPWB <= 4 && DS >= 1, "dma16g_s covers groups of four loads");
+  static_assert(RS >= 1 && (TM + TN) * RS <= MF, "the next stage's fragments fit under this one's MFMAs");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
 };
 typedef Tile<256, 256, 4> Tile256;        // 128 + 32 = 160 KB: the whole LDS of a CU
@@ -62,11 +72,51 @@ struct DenseArgs {
   const uint16_t* B;     // K x N row major
   uint16_t* C;           // M x N row major
   i64 lda, ldb, ldc;
-  int tiles_m, tiles_n, ktiles;   // ktiles counts 32-deep stages
+  int tiles_m, tiles_n, ktiles;   // ktiles counts 32-deep stages; even
   int cols;              // RAGGED: columns of C that exist; its rows need element alignment only
   int splits;            // PARTS: the contraction in so many ranges of ktiles stages each ...
   float* parts;          // ... whose products go here in fp32, [split][M][N], instead of to C
 };
+
+// ---- swizzled tile layouts for 16 x 16 x 32 fragments (16-byte chunks) ----------------------------
+// [x][k] tile: 4 chunks per row.  A 16-byte read serves 16 lanes at a time: lanes 0-3, 12-15, 20-23 and 24-27 (rows 0-3 and 12-15 of chunk c, 4-7 and 8-11 of
+// chunk c + 1), then 4-11, 16-19 and 28-31, and the upper half the same way.  The four row groups of each get four positions.
+__device__ inline int xk16_chunk(int c, int row) {
+  const int x = (row >> 2) & 3;
+  return c ^ (((x ^ (x >> 1)) & 1) << 1 | x >> 1);
+}
+// [k][x] tile.  A transposing read touches 4 consecutive k rows x 2 chunks per 16 lanes, rows 8 further down in the next 16: the k row
+// spreads the former over 8 positions, its bit 3 puts the latter into the other 128 bytes.
+__device__ inline int kx16_chunk(int c, int k) { return c ^ (2 * (k & 3)) ^ (((k >> 3) & 1) << 3); }
+
+// c += a b on 16 x 16 x 32, in place.  Inline asm: the compiler gives the builtin's result other registers than its addend and then moves accumulators around
+// (up to 300 spills here).  Its operands are loaded by code the compiler sees, which also inserts their waits; before the accumulators
+// are read by anything but another of these, settle() lets the last of them finish.
+__device__ __forceinline__ void mfma16(floatx4& c, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+template <int TM, int TN>
+__device__ __forceinline__ void settle(floatx4 (&c)[TM][TN]) {
+  // the last TM products went to the last column of tiles; the others are at least TM products old
+  static_assert(TM == 4 || TM == 8, "accumulator rows of a wave");
+  constexpr int L = TN - 1;
+  if constexpr (TM == 8)
+    asm volatile("s_nop 15\n\ts_nop 3" : "+a"(c[0][L]), "+a"(c[1][L]), "+a"(c[2][L]), "+a"(c[3][L]), "+a"(c[4][L]), "+a"(c[5][L]), "+a"(c[6][L]), "+a"(c[7][L]));
+  else
+    asm volatile("s_nop 15\n\ts_nop 3" : "+a"(c[0][L]), "+a"(c[1][L]), "+a"(c[2][L]), "+a"(c[3][L]));
+}
+
+// Two neighbouring tiles' accumulators of a row (columns 4 (lane >> 4) .. + 3 of each) as eight consecutive bf16 columns per lane: 8 (lane >> 5) .. + 7 of
+// the first tile in the even groups of 16 lanes, of the second in the odd ones.
+__device__ __forceinline__ void pack_pair(const floatx4& x, const floatx4& y, uint32_t (&o)[4]) {
+  typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+  const uint2v r0 = __builtin_amdgcn_permlane16_swap(mm::pack2_bf16(x[0], x[1]), mm::pack2_bf16(y[0], y[1]), false, false);
+  const uint2v r1 = __builtin_amdgcn_permlane16_swap(mm::pack2_bf16(x[2], x[3]), mm::pack2_bf16(y[2], y[3]), false, false);
+  o[0] = r0[0];
+  o[1] = r1[0];
+  o[2] = r0[1];
+  o[3] = r1[1];
+}
 
 // 16 bytes per lane from (uniform base + per-lane byte offset + OFF) straight into LDS at
 // lds_group + OFF + 16 * lane: the instruction offset moves the LDS address and the global address
@@ -103,7 +153,7 @@ enum Out { OUT_WHOLE = 0, OUT_RAGGED = 1, OUT_PARTS = 2 };
 template <bool A_KMAJOR, Out OUT = OUT_WHOLE, int DIAG = 0, class C = Tile256>
 __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   constexpr int BM = C::BM, BN = C::BN, NS = C::NS, A_BYTES = C::A_BYTES, STAGE_BYTES = C::STAGE_BYTES, OUT_BYTES = C::OUT_BYTES;
-  constexpr int IPWA = C::IPWA, IPWB = C::IPWB, LPT = C::LPT, TM = C::TM, TN = C::TN, MF = C::MF;
+  constexpr int IPWA = C::IPWA, IPWB = C::IPWB, LPT = C::LPT, TM = C::TM, TN = C::TN, MF = C::MF, RS = C::RS, DS = C::DS;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -145,17 +195,17 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   for (int s = 0; s < IPWA; ++s) {
     const int slot = (wave * IPWA + s) * 64 + lane;
     if (A_KMAJOR) {
-      const int r = slot >> 2, c = mm::xk_chunk(slot & 3, r);
+      const int r = slot >> 2, c = xk16_chunk(slot & 3, r);
       voffA[s] = (uint32_t)((r * g.lda + c * 8) * 2) - s * 1024;
     } else {
-      const int k = slot / (BM / 8), c = mm::kx_unchunk<BM>(slot % (BM / 8), k);
+      const int k = slot / (BM / 8), c = kx16_chunk(slot % (BM / 8), k);
       voffA[s] = (uint32_t)((k * g.lda + c * 8) * 2) - s * 1024;
     }
   }
 #pragma unroll
   for (int s = 0; s < IPWB; ++s) {
     const int slot = (wave * IPWB + s) * 64 + lane;
-    const int k = slot / (BN / 8), c = mm::kx_unchunk<BN>(slot % (BN / 8), k);
+    const int k = slot / (BN / 8), c = kx16_chunk(slot % (BN / 8), k);
     voffB[s] = (uint32_t)((k * g.ldb + c * 8) * 2) - s * 1024;
   }
   const i64 stepA = A_KMAJOR ? (i64)BK * 2 : (i64)BK * g.lda * 2;
@@ -163,225 +213,180 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   const int KT = g.ktiles;
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
-  // ---- issue side of the stream: runs NS stages ahead of the multiplication, across tiles
-  const char* Ab;
-  const char* Bb;
-  int itile = 0, ikt = 0, islot = 0;
-  auto issue_base = [&](int ti) {
+  // ---- issue side of the stream: runs NS stages ahead of the multiplication, across tiles.  An, Bn: where the tile after the one in issue
+  // starts, so that moving on is a choice between two values.  Past the last stage of the last tile the stream fetches that tile
+  // from its start again: the number of loads in flight -- and with it the vmcnt bound of the barrier -- never changes.
+  const char *Ab, *Bb, *An, *Bn;
+  int ikt = 0, islot = 0;
+  auto tile_base = [&](int ti, const char*& a, const char*& b) {
     int i0, j0, split;
-    tile_origin(ti, i0, j0, split);
-    Ab = (const char*)(g.A + (A_KMAJOR ? (i64)i0 * g.lda : (i64)i0)) + split * (KT * stepA);
-    Bb = (const char*)(g.B + j0) + split * (KT * stepB);
+    tile_origin(ti < n_my ? ti : n_my - 1, i0, j0, split);
+    a = (const char*)(g.A + (A_KMAJOR ? (i64)i0 * g.lda : (i64)i0)) + split * (KT * stepA);
+    b = (const char*)(g.B + j0) + split * (KT * stepB);
   };
-  issue_base(0);
+  tile_base(0, Ab, Bb);
+  tile_base(1, An, Bn);
   bool loads_on = true;   // DIAG bit 0 switches it off after the prologue
   auto issue_a = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Ab, voffA[s], lds_base + islot * STAGE_BYTES + wave * IPWA * 1024); };
   auto issue_b = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Bb, voffB[s], lds_base + islot * STAGE_BYTES + A_BYTES + wave * IPWB * 1024); };
-  // After the last stage of the last tile the stream keeps re-fetching that stage, so the number
-  // of loads in flight -- and with it the vmcnt bound of the barrier -- never changes.
   auto issue_advance = [&]() {
     islot = islot + 1 == NS ? 0 : islot + 1;
     if (DIAG & 4) return;   // every stage re-fetches the first one: the loads stay, their misses go
-    if (ikt + 1 < KT) {
-      ++ikt;
-      Ab += stepA;
-      Bb += stepB;
-    } else if (itile + 1 < n_my) {
-      ++itile;
-      ikt = 0;
-      issue_base(itile);
-    }
+    const bool last = ikt + 1 == KT;
+    ikt = last ? 0 : ikt + 1;
+    Ab = last ? An : Ab + stepA;
+    Bb = last ? Bn : Bb + stepB;
   };
 
-  // ---- LDS byte offsets of this lane's fragments inside a stage (k step 0)
+  // ---- LDS byte offsets of this lane's fragments inside a stage: row (column) lane & 15 of a 16-wide piece, k = 8 (lane >> 4) .. + 7
   int fragA[TM], fragB[TN];
   {
     const int q = lane >> 4, i = lane & 15;
+    const int k = 8 * q + (i >> 2);
 #pragma unroll
     for (int a = 0; a < TM; ++a) {
-      const int x0 = wm * (BM / 2) + a * 32;
+      const int x0 = wm * (BM / 2) + a * 16;
       if (A_KMAJOR) {
-        const int r = x0 + (lane & 31);
-        fragA[a] = r * 64 + 16 * mm::xk_chunk(lane >> 5, r);
+        const int r = x0 + i;
+        fragA[a] = r * 64 + 16 * xk16_chunk(q, r);
       } else {
-        const int k = 8 * (q >> 1) + (i >> 2);
-        const int c = (x0 >> 3) + 2 * (q & 1) + ((i & 3) >> 1);
-        fragA[a] = k * (BM * 2) + 16 * mm::kx_chunk<BM>(c, k) + 8 * (i & 1);
+        fragA[a] = k * (BM * 2) + 16 * kx16_chunk((x0 >> 3) + ((i & 3) >> 1), k) + 8 * (i & 1);
       }
     }
 #pragma unroll
     for (int c2 = 0; c2 < TN; ++c2) {
-      const int x0 = wn * (BN / 2) + c2 * 32;
-      const int k = 8 * (q >> 1) + (i >> 2);
-      const int c = (x0 >> 3) + 2 * (q & 1) + ((i & 3) >> 1);
-      fragB[c2] = A_BYTES + k * (BN * 2) + 16 * mm::kx_chunk<BN>(c, k) + 8 * (i & 1);
+      const int x0 = wn * (BN / 2) + c2 * 16;
+      fragB[c2] = A_BYTES + k * (BN * 2) + 16 * kx16_chunk((x0 >> 3) + ((i & 3) >> 1), k) + 8 * (i & 1);
     }
   }
 
-  floatx16 acc[TM][TN];
+  floatx4 acc[TM][TN];
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
-    for (int c = 0; c < TN; ++c)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
+    for (int c = 0; c < TN; ++c) acc[a][c] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  auto load_frag = [&](const char* stage, int off, bool kmajor, int row_bytes, int ks) -> bf16x8 {
-    // K major: k step 1 is logical chunk + 2, which flips bit 1 of the swizzled position
-    if (kmajor) return *reinterpret_cast<const bf16x8*>(stage + (ks ? (off ^ 32) : off));
-    const char* p = stage + off + ks * 16 * row_bytes;
-    short4v lo = mm::lds_read_tr(p);
-    short4v hi = mm::lds_read_tr(p + 4 * row_bytes);
-    short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  auto load_frag = [&](const char* p, bool kmajor, int row_bytes) -> bf16x8 {
+    if (kmajor) return *reinterpret_cast<const bf16x8*>(p);
+    const short4v lo = mm::lds_read_tr(p), hi = mm::lds_read_tr(p + 4 * row_bytes);   // the swizzle is the same 4 rows further down
+    const short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
   struct Frags {
     bf16x8 a[TM], b[TN];
   };
-  // piece p of a k step's fragments, in the order the MFMAs first need them: A0 B0 A1 .. A(TM-1) B1 .. B(TN-1)
-  auto load_piece = [&](Frags& f, const char* stage, int ks, int p) {
-    if (p == 1) f.b[0] = load_frag(stage, fragB[0], false, BN * 2, ks);
-    else if (p <= TM) f.a[p ? p - 1 : 0] = load_frag(stage, fragA[p ? p - 1 : 0], A_KMAJOR, BM * 2, ks);
-    else f.b[p - TM] = load_frag(stage, fragB[p - TM], false, BN * 2, ks);
-  };
-  // MFMA i of a k step.  The operands go in swapped, so the accumulator tile is transposed: a lane
-  // owns one output row and four consecutive columns per group of four registers.
-  auto mfma_one = [&](const Frags& f, int i) {
-    const int c = i / TM, a = i % TM;
-    acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[c], f.a[a], acc[a][c], 0, 0, 0);
+  // piece p of a stage's fragments, in the order the MFMAs first need them: A0 B0 A1 .. A(TM-1) B1 .. B(TN-1)
+  auto load_piece = [&](Frags& f, const char* stage, int p) {
+    if (p == 1) f.b[0] = load_frag(stage + fragB[0], false, BN * 2);
+    else if (p <= TM) f.a[p ? p - 1 : 0] = load_frag(stage + fragA[p ? p - 1 : 0], A_KMAJOR, BM * 2);
+    else f.b[p - TM] = load_frag(stage + fragB[p - TM], false, BN * 2);
   };
 
-  // ---- prologue: stages 0 .. NS-2 and the A half of stage NS-1
+  // ---- prologue: stages 0 .. NS-1
 #pragma unroll
-  for (int t = 0; t < NS - 1; ++t) {
+  for (int t = 0; t < NS; ++t) {
 #pragma unroll
     for (int s = 0; s < IPWA; ++s) issue_a(s);
 #pragma unroll
     for (int s = 0; s < IPWB; ++s) issue_b(s);
     issue_advance();
   }
-#pragma unroll
-  for (int s = 0; s < IPWA; ++s) issue_a(s);
-  mm::wait_vmcnt_and_barrier<(NS - 2) * LPT + IPWA>();   // stage 0 has landed
+  mm::wait_vmcnt_and_barrier<(NS - 1) * LPT>();   // stage 0 has landed
   Frags F, Gf;
   int cslot = 0;
 #pragma unroll
-  for (int p = 0; p < TM + TN; ++p) load_piece(F, lds, 0, p);
+  for (int p = 0; p < TM + TN; ++p) load_piece(F, lds, p);
 
   if (DIAG & 2) {   // the loop reads no fragments: both sets come from the first stage
 #pragma unroll
-    for (int p = 0; p < TM + TN; ++p) load_piece(Gf, lds, 1, p);
+    for (int p = 0; p < TM + TN; ++p) load_piece(Gf, lds, p);
   }
   loads_on = false;
-  const int h = lane >> 5, li = lane & 31;
+  const int q4 = lane >> 4, li = lane & 15;
 
-  // The body is instantiated once per wave: wave W issues its loads of a k step after MFMAs W, W + MF / loads, ...
-  // (256 x 256: W, W+4, W+8, W+12), so the four waves never hand the memory pipeline a load in the same place.
+  // The body is instantiated once per wave: wave W issues its loads W quarters of the way from one to the next, so the four waves
+  // do not hand the memory pipeline a load in the same place.
   auto run = [&](auto WC) {
     constexpr int W = decltype(WC)::value;
+    // stage kt from X; the fragments of the next stage (the next tile's first one after the last one of this tile) into Y; stage kt + NS to issue
+    auto multiply = [&](const Frags& X, Frags& Y) {
+      // Every wave holds this stage in registers (lgkmcnt(0)) and the next one has landed: stages up to kt + NS - 1 are issued, so at
+      // most NS - 2 of them may be in flight.  Stores of a finished tile share the counter and only make this wait stricter.
+      mm::wait_all_reads_and_barrier<(NS - 2) * LPT>();
+      const int nslot = cslot + 1 == NS ? 0 : cslot + 1;
+      const char* nstage = lds + nslot * STAGE_BYTES;
+#pragma unroll
+      for (int i = 0; i < MF; ++i) {
+        // the operands go in swapped, so the accumulator tile is transposed: a lane owns one output row and four consecutive columns
+        mfma16(acc[i % TM][i / TM], X.b[i / TM], X.a[i % TM]);
+        if (i % RS == 0 && i / RS < TM + TN && !(DIAG & 2)) load_piece(Y, nstage, i / RS);
+        if (i % DS == W * DS / 4 && i / DS < LPT) {
+          if (i / DS < IPWA) issue_a(i / DS);
+          else issue_b(i / DS - IPWA);
+        }
+        if (i == MF - 1) issue_advance();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      cslot = nslot;
+    };
     for (int ti = 0; ti < n_my; ++ti) {
+      // the tile after the one in issue, which is NS stages ahead: that of stage NS of this tile
+      if (ti > 0 || KT == NS) tile_base(ti + (KT > NS ? 1 : 2), An, Bn);   // KT >= 8 >= NS
       long long tc0 = 0, tc1 = 0, tr0 = 0, tr1 = 0;
       if ((DIAG & 8) && ti == 1) {
         tc0 = __builtin_readcyclecounter();
         tr0 = __builtin_amdgcn_s_memrealtime();
       }
-      for (int kt = 0; kt < KT; ++kt) {
-        const char* stage = lds + cslot * STAGE_BYTES;
-        // k step 0 from F; fetch k step 1 of this stage; B half of the stage in issue (its A half
-        // went out during the previous k step, into the slot the last barrier released)
-#pragma unroll
-        for (int i = 0; i < MF; ++i) {
-          mfma_one(F, i);
-          if (i < TM + TN && !(DIAG & 2)) load_piece(Gf, stage, 1, i);
-          if (i % (MF / IPWB) == W % (MF / IPWB)) issue_b(i / (MF / IPWB));
-          if (i == MF - 1) issue_advance();
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        // Every wave holds the rest of this stage in registers (lgkmcnt(0)) and the next stage has
-        // landed: stages up to kt + NS - 1 are issued, so at most NS - 2 of them may be in flight.
-        // Stores of a finished tile share the counter and only make this wait stricter.
-        mm::wait_all_reads_and_barrier<(NS - 2) * LPT>();
-        const int nslot = cslot + 1 == NS ? 0 : cslot + 1;
-        const char* nstage = lds + nslot * STAGE_BYTES;
-        // k step 1 from Gf; fetch k step 0 of the next stage (the next tile's first stage after
-        // the last one of this tile); A half of the next stage to issue, into the slot just released
-#pragma unroll
-        for (int i = 0; i < MF; ++i) {
-          mfma_one(Gf, i);
-          if (i < TM + TN && !(DIAG & 2)) load_piece(F, nstage, 0, i);
-          if (i % (MF / IPWA) == W % (MF / IPWA)) issue_a(i / (MF / IPWA));
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        cslot = nslot;
+      for (int kt = 0; kt < KT; kt += 2) {
+        multiply(F, Gf);
+        multiply(Gf, F);
       }
       if ((DIAG & 8) && ti == 1) {
         tc1 = __builtin_readcyclecounter();
         tr1 = __builtin_amdgcn_s_memrealtime();
       }
       // ---- tile done: round to bf16 and store, clear the accumulators.  The accumulator layout gives a
-      // lane 4 consecutive columns of its row per register group; swapping groups between the lane halves
-      // (v_permlane32_swap: the upper half of its first operand against the lower half of its second)
-      // makes that 8 columns = 16 bytes.  Stored like this an instruction would write 32 contiguous bytes
-      // per row, and all workgroups finish their tiles together: the burst drains twice as fast when
+      // lane 4 consecutive columns of its row per 16-column tile; swapping two neighbouring tiles' between lane groups
+      // (v_permlane16_swap: the odd groups of 16 lanes of its first operand against the even ones of its second)
+      // makes that 8 columns = 16 bytes.  All workgroups finish their tiles together: the burst drains twice as fast when
       // every instruction writes whole 128-byte lines.  So the wave passes its piece through LDS, 32 rows
       // x 64 columns at a time (rows XOR-swizzled in 16-byte chunks, conflict free both ways), and reads
       // it back with 8 lanes per row.
+      settle(acc);
+      int i0, j0, split;
+      tile_origin(ti, i0, j0, split);
       if constexpr (OUT == OUT_PARTS) {
-        // fp32 parts: the swapped groups are 8 consecutive columns = whole 32-byte sectors of a row
-        typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-        int i0, j0, split;
-        tile_origin(ti, i0, j0, split);
-        float* P = g.parts + ((i64)split * (g.tiles_m * BM) + i0 + wm * (BM / 2) + li) * g.ldb + j0 + wn * (BN / 2) + 8 * h;
+        // fp32 parts: 16 columns of a row per instruction and row, 64 bytes
+        float* P = g.parts + ((i64)split * (g.tiles_m * BM) + i0 + wm * (BM / 2) + li) * g.ldb + j0 + wn * (BN / 2) + 4 * q4;
 #pragma unroll
         for (int a = 0; a < TM; ++a)
 #pragma unroll
-          for (int c = 0; c < TN; ++c)
-#pragma unroll
-            for (int q = 0; q < 4; q += 2) {
-              float lo[4], hi[4];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const float x = acc[a][c][4 * q + e], y = acc[a][c][4 * q + 4 + e];   // scalars first: a bit cast straight from a vector element reads element 0
-                const uint2v r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
-                const unsigned r0 = r[0], r1 = r[1];
-                lo[e] = __builtin_bit_cast(float, r0);
-                hi[e] = __builtin_bit_cast(float, r1);
-                acc[a][c][4 * q + e] = 0.f;
-                acc[a][c][4 * q + 4 + e] = 0.f;
-              }
-              float* at = P + (i64)(a * 32) * g.ldb + c * 32 + 8 * q;
-              *reinterpret_cast<float4*>(at) = make_float4(lo[0], lo[1], lo[2], lo[3]);
-              *reinterpret_cast<float4*>(at + 4) = make_float4(hi[0], hi[1], hi[2], hi[3]);
-            }
+          for (int c = 0; c < TN; ++c) {
+            *reinterpret_cast<floatx4*>(P + (i64)(a * 16) * g.ldb + c * 16) = acc[a][c];
+            acc[a][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
       } else {
-        typedef unsigned uint2v __attribute__((ext_vector_type(2)));
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        int i0, j0, split;
-        tile_origin(ti, i0, j0, split);
         char* stg = lds + NS * STAGE_BYTES + wave * OUT_BYTES;
-        const int wsw = (li >> 1) & 7;
         uint16_t* Cw = g.C + (i64)(i0 + wm * (BM / 2)) * g.ldc + j0 + wn * (BN / 2);
 #pragma unroll
-        for (int a = 0; a < TM; ++a) {
+        for (int a = 0; a < TM / 2; ++a) {
 #pragma unroll
-          for (int c = 0; c < TN; ++c) {
-            uint32_t p[8];   // p[2q], p[2q+1]: columns 8q + 4h + 0..3 of the 32-column tile
+          for (int a2 = 0; a2 < 2; ++a2) {
+            const int row = a2 * 16 + li;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) p[e] = mm::pack2_bf16(acc[a][c][2 * e], acc[a][c][2 * e + 1]);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
-#pragma unroll
-            for (int q = 0; q < 4; q += 2) {
-              const uint2v r0 = __builtin_amdgcn_permlane32_swap(p[2 * q], p[2 * q + 2], false, false);
-              const uint2v r1 = __builtin_amdgcn_permlane32_swap(p[2 * q + 1], p[2 * q + 3], false, false);
-              const u32x4 o = {r0[0], r1[0], r0[1], r1[1]};   // columns 8 (q + h) .. + 7 of tile c
-              const int ch = (c & 1) * 4 + q + h;             // 16-byte chunk of the 64-column piece
-              *reinterpret_cast<u32x4*>(stg + (c >> 1) * 4096 + li * 128 + 16 * (ch ^ wsw)) = o;
+            for (int c = 0; c < TN; c += 2) {
+              uint32_t o[4];
+              pack_pair(acc[2 * a + a2][c], acc[2 * a + a2][c + 1], o);   // columns 8 (q4 >> 1) .. + 7 of tile c + (q4 & 1)
+              acc[2 * a + a2][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+              acc[2 * a + a2][c + 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+              const int ch = ((c & 3) + (q4 & 1)) * 2 + (q4 >> 1);         // 16-byte chunk of the 64-column piece
+              *reinterpret_cast<u32x4*>(stg + (c >> 2) * 4096 + row * 128 + 16 * (ch ^ ((row >> 1) & 7))) = u32x4{o[0], o[1], o[2], o[3]};
             }
           }
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's own writes; the area is private to it
 #pragma unroll
-          for (int cp = 0; cp < TN / 2; ++cp)
+          for (int cp = 0; cp < TN / 4; ++cp)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int r = (lane >> 3) + 8 * i, ch = lane & 7;

@@ -5,21 +5,21 @@
 // Same persistent stream as the bf16 product (mfma_dense.hip: one wave per SIMD, 128 x 128 wave
 // tiles, 32-deep stages through an LDS ring, one barrier per stage); only the weight operand takes
 // another road into its ring slot.  Its 8-bit codes (8 KB per stage) and the scales the stage needs
-// arrive by direct-to-LDS loads in a small side ring; two stages ahead of the multiplication each
+// arrive by direct-to-LDS loads in a small side ring; two stages ahead of the multiplication (three and four ahead of it they are in flight) each
 // wave converts exactly the bytes it loaded itself -- so its own vmcnt wait is all the
 // synchronisation the side ring needs -- into bf16(scale * q) and writes them into the weight half
 // of the stage's slot, in the layout the bf16 kernel uses.  The conversion (one cvt + one fma per
 // element, rounded once to fp32 and once to bf16, i.e. bit for bit the stand-alone dequantiser)
 // runs in the shadow of the MFMAs.
-#include <type_traits>
-
-#include "mfma_gemm.h"
+#include "mfma_dense_kernel.h"
 
 namespace poetx {
 namespace {
 
+using dense::dma16g;
+using dense::dma16g_s;
+using dense::floatx4;
 using mm::bf16x8;
-using mm::floatx16;
 using mm::short4v;
 using mm::short8v;
 
@@ -31,11 +31,11 @@ constexpr int Q_BASE = NS * STAGE_BYTES;         // side ring behind the main ri
 constexpr int LDS_BYTES = Q_BASE + NQ * Q_SLOT;  // 155648
 constexpr int IPW = B_BYTES / 1024 / NW;         // 4 direct-to-LDS instructions per wave per stage for the activations
 constexpr int QLOADS = 3;                        // per wave per stage: 2 x 16 bytes of codes per lane + 1 x 4 bytes of scale
-constexpr int TM = 4, TN = 4, GROUP = 4;
-// At the barrier of stage kt the wave's own codes of stage kt+2 and everybody's activations of
-// stage kt+1 must have landed.  Issue order: ... B(kt+1), Q(kt+2), B(kt+2), Q(kt+3), B(kt+3), barrier:
-// the loads younger than Q(kt+2) are two activation stages and one code stage.
-constexpr int VM_BOUND = 2 * IPW + QLOADS;
+constexpr int TM = BM / 32, TN = BN / 32, MF = TM * TN, GROUP = 4;
+// At the barrier before stage kt the wave's own codes of stage kt+2 and everybody's activations of
+// stage kt+1 must have landed.  Issue order: ... B(kt+1), Q(kt+2), B(kt+2), Q(kt+3), B(kt+3), Q(kt+4), barrier:
+// the loads younger than Q(kt+2) are two activation stages and two code stages.
+constexpr int VM_BOUND = 2 * IPW + 2 * QLOADS;
 static_assert(NS * IPW + NQ * QLOADS < 64, "vmcnt range");
 
 struct DenseQ8Args {
@@ -49,20 +49,6 @@ struct DenseQ8Args {
   float* parts;          // whose products go here in fp32, [split][M][N], instead of to C
 };
 
-// Direct-to-LDS loads as in the bf16 kernel: the instruction offset moves the LDS and the global
-// address alike, so a group of loads shares one M0 and the per-lane offsets carry the bias.
-template <int OFF>
-__device__ inline void dma16g(const void* sbase, uint32_t voff, uint32_t lds_group) {
-  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(sbase), "n"(OFF), "{m0}"(lds_group) : "memory");
-}
-__device__ inline void dma16g_s(int s, const void* sbase, uint32_t voff, uint32_t lds_group) {
-  switch (s) {
-    case 0: dma16g<0>(sbase, voff, lds_group); break;
-    case 1: dma16g<1024>(sbase, voff, lds_group); break;
-    case 2: dma16g<2048>(sbase, voff, lds_group); break;
-    default: dma16g<3072>(sbase, voff, lds_group); break;
-  }
-}
 __device__ inline void dma4s(const void* sbase, uint32_t voff, uint32_t lds_addr) {
   asm volatile("global_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(lds_addr) : "memory");
 }
@@ -103,7 +89,7 @@ __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
 #pragma unroll
   for (int s = 0; s < IPW; ++s) {
     const int slot = (wave * IPW + s) * 64 + lane;
-    const int k = slot / (BN / 8), c = mm::kx_unchunk<BN>(slot % (BN / 8), k);
+    const int k = slot / (BN / 8), c = dense::kx16_chunk(slot % (BN / 8), k);
     voffB[s] = (uint32_t)((k * g.ldb + c * 8) * 2) - s * 1024;   // less the instruction offset of load s
   }
   const i64 stepB = (i64)BK * g.ldb * 2;
@@ -137,14 +123,14 @@ __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
     if (A_KMAJOR) {
       const int r = ch >> 1, c = ch & 1;
       voffQ[j] = (uint32_t)(r * g.ldq + 16 * c) - j * 1024;
-      cvt_dst[j][0] = r * 64 + 16 * mm::xk_chunk(2 * c, r);
-      cvt_dst[j][1] = r * 64 + 16 * mm::xk_chunk(2 * c + 1, r);
+      cvt_dst[j][0] = r * 64 + 16 * dense::xk16_chunk(2 * c, r);
+      cvt_dst[j][1] = r * 64 + 16 * dense::xk16_chunk(2 * c + 1, r);
       cvt_scale[j] = Q_CODES + 4 * r;
     } else {
       const int k = ch >> 4, c = ch & 15;
       voffQ[j] = (uint32_t)(k * g.ldq + 16 * c) - j * 1024;
-      cvt_dst[j][0] = k * (BM * 2) + 16 * mm::kx_chunk<BM>(2 * c, k);
-      cvt_dst[j][1] = k * (BM * 2) + 16 * mm::kx_chunk<BM>(2 * c + 1, k);
+      cvt_dst[j][0] = k * (BM * 2) + 16 * dense::kx16_chunk(2 * c, k);
+      cvt_dst[j][1] = k * (BM * 2) + 16 * dense::kx16_chunk(2 * c + 1, k);
       cvt_scale[j] = Q_CODES + 4 * (64 * wave + (k - 8 * wave));
     }
   }
@@ -217,171 +203,131 @@ __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
   int fragA[TM], fragB[TN];
   {
     const int q = lane >> 4, i = lane & 15;
+    const int k = 8 * q + (i >> 2);
 #pragma unroll
     for (int a = 0; a < TM; ++a) {
-      const int x0 = wm * (BM / 2) + a * 32;
+      const int x0 = wm * (BM / 2) + a * 16;
       if (A_KMAJOR) {
-        const int r = x0 + (lane & 31);
-        fragA[a] = r * 64 + 16 * mm::xk_chunk(lane >> 5, r);
+        const int r = x0 + i;
+        fragA[a] = r * 64 + 16 * dense::xk16_chunk(q, r);
       } else {
-        const int k = 8 * (q >> 1) + (i >> 2);
-        const int c = (x0 >> 3) + 2 * (q & 1) + ((i & 3) >> 1);
-        fragA[a] = k * (BM * 2) + 16 * mm::kx_chunk<BM>(c, k) + 8 * (i & 1);
+        fragA[a] = k * (BM * 2) + 16 * dense::kx16_chunk((x0 >> 3) + ((i & 3) >> 1), k) + 8 * (i & 1);
       }
     }
 #pragma unroll
     for (int c2 = 0; c2 < TN; ++c2) {
-      const int x0 = wn * (BN / 2) + c2 * 32;
-      const int k = 8 * (q >> 1) + (i >> 2);
-      const int c = (x0 >> 3) + 2 * (q & 1) + ((i & 3) >> 1);
-      fragB[c2] = A_BYTES + k * (BN * 2) + 16 * mm::kx_chunk<BN>(c, k) + 8 * (i & 1);
+      const int x0 = wn * (BN / 2) + c2 * 16;
+      fragB[c2] = A_BYTES + k * (BN * 2) + 16 * dense::kx16_chunk((x0 >> 3) + ((i & 3) >> 1), k) + 8 * (i & 1);
     }
   }
-  floatx16 acc[TM][TN];
+  floatx4 acc[TM][TN];
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
-    for (int c = 0; c < TN; ++c)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
-  auto load_frag = [&](const char* stage, int off, bool kmajor, int row_bytes, int ks) -> bf16x8 {
-    if (kmajor) return *reinterpret_cast<const bf16x8*>(stage + (ks ? (off ^ 32) : off));
-    const char* p = stage + off + ks * 16 * row_bytes;
-    short4v lo = mm::lds_read_tr(p);
-    short4v hi = mm::lds_read_tr(p + 4 * row_bytes);
-    short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    for (int c = 0; c < TN; ++c) acc[a][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto load_frag = [&](const char* p, bool kmajor, int row_bytes) -> bf16x8 {
+    if (kmajor) return *reinterpret_cast<const bf16x8*>(p);
+    const short4v lo = mm::lds_read_tr(p), hi = mm::lds_read_tr(p + 4 * row_bytes);
+    const short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
   struct Frags {
     bf16x8 a[TM], b[TN];
   };
-  auto load_piece = [&](Frags& f, const char* stage, int ks, int p) {
-    switch (p) {
-      case 0: f.a[0] = load_frag(stage, fragA[0], A_KMAJOR, BM * 2, ks); break;
-      case 1: f.b[0] = load_frag(stage, fragB[0], false, BN * 2, ks); break;
-      case 2: f.a[1] = load_frag(stage, fragA[1], A_KMAJOR, BM * 2, ks); break;
-      case 3: f.a[2] = load_frag(stage, fragA[2], A_KMAJOR, BM * 2, ks); break;
-      case 4: f.a[3] = load_frag(stage, fragA[3], A_KMAJOR, BM * 2, ks); break;
-      case 5: f.b[1] = load_frag(stage, fragB[1], false, BN * 2, ks); break;
-      case 6: f.b[2] = load_frag(stage, fragB[2], false, BN * 2, ks); break;
-      default: f.b[3] = load_frag(stage, fragB[3], false, BN * 2, ks); break;
-    }
-  };
-  auto mfma_one = [&](const Frags& f, int i) {
-    const int c = i >> 2, a = i & 3;
-    acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[c], f.a[a], acc[a][c], 0, 0, 0);
+  auto load_piece = [&](Frags& f, const char* stage, int p) {   // in the order the MFMAs first need them
+    if (p == 1) f.b[0] = load_frag(stage + fragB[0], false, BN * 2);
+    else if (p <= TM) f.a[p ? p - 1 : 0] = load_frag(stage + fragA[p ? p - 1 : 0], A_KMAJOR, BM * 2);
+    else f.b[p - TM] = load_frag(stage + fragB[p - TM], false, BN * 2);
   };
 
-  // ---- prologue: codes of stages 0..2, activations of stages 0..2; stage 0 and half of stage 1
-  // converted (the loop's first k step finishes stage 1, as every k step finishes the stage the
-  // previous one began); then the codes of stage 3 into the slot stage 0 has left
+  // ---- prologue: codes of stages 0..2 and activations of stages 0, 1; stages 0 and 1 converted; then, in the order of the loop,
+  // the activations of stages 2 and 3 and, into the slots that stages 0 and 1 have left, the codes of stages 3 and 4
   Codes cd;
   issue_q();
   issue_q();
   issue_q();
-#pragma unroll
-  for (int t = 0; t < NS - 1; ++t) {
+  auto issue_stage_b = [&]() {
 #pragma unroll
     for (int s = 0; s < IPW; ++s) issue_b(s);
     b_advance();
-  }
+  };
+  issue_stage_b();
+  issue_stage_b();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  cvt_read(cd);            // stage 0, whole
-  cvt_write(cd, 0);
-  cvt_write(cd, 1);
-  cvt_done();
-  cvt_read(cd);            // stage 1: first chunk here, second chunk in the first k step of the loop
-  cvt_write(cd, 0);
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // conversion reads done before the slot is refilled
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    cvt_read(cd);
+    cvt_write(cd, 0);
+    cvt_write(cd, 1);
+    cvt_done();
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // conversion reads done before their slots are refilled
+  issue_stage_b();
   issue_q();
-  mm::wait_all_reads_and_barrier<QLOADS>();           // everybody's stage 0 is in place
+  issue_stage_b();
+  issue_q();
+  mm::wait_all_reads_and_barrier<VM_BOUND>();           // everybody's stage 0 is in place
   Frags F, Gf;
   int cslot = 0;
 #pragma unroll
-  for (int p = 0; p < 8; ++p) load_piece(F, lds, 0, p);
+  for (int p = 0; p < TM + TN; ++p) load_piece(F, lds, p);
 
-  const int h = lane >> 5, li = lane & 31;
-  const i64 coff = (i64)(wm * (BM / 2) + li) * g.ldc + wn * (BN / 2) + 8 * h;
+  const int q4 = lane >> 4, li = lane & 15;
 
   auto run = [&](auto WC) {
     constexpr int W = decltype(WC)::value;
-    for (int ti = 0; ti < n_my; ++ti) {
-      for (int kt = 0; kt < KT; ++kt) {
-        const char* stage = lds + cslot * STAGE_BYTES;
-        // k step 0 from F; fetch k step 1; activations of stage kt + NS - 1 into the slot the last
-        // barrier released; second half of the conversion that the previous k step began
+    // stage kt from X; the fragments of the next one into Y; the activations of stage kt + NS into the slot of this one; the codes of stage kt + 2
+    // converted into theirs, and those of stage kt + 5 into the side-ring slot they leave
+    auto multiply = [&](const Frags& X, Frags& Y) {
+      // every wave holds this stage in registers; the activations of the next stage and this wave's codes of the stage after it have
+      // landed; the next stage's weights are converted
+      mm::wait_all_reads_and_barrier<VM_BOUND>();
+      const int nslot = cslot + 1 == NS ? 0 : cslot + 1;
+      const char* nstage = lds + nslot * STAGE_BYTES;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          mfma_one(F, i);
-          if (i < 8) load_piece(Gf, stage, 1, i);
-          if ((i & 3) == W) issue_b(i >> 2);
-          if (i >= 8) cvt_step(cd, 1, i - 8);          // second chunk of the codes read after the last barrier
-          if (i == 15) { cvt_done(); b_advance(); }
-          __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < MF; ++i) {
+        dense::mfma16(acc[i % TM][i / TM], X.b[i / TM], X.a[i % TM]);
+        if (i == 0) cvt_read(cd);
+        if (i % 3 == 1 && i / 3 < TM + TN) load_piece(Y, nstage, i / 3);
+        if (i % 16 == 4 * W + 2) issue_b(i / 16);
+        if (i >= 14 && i % 3 == 2 && (i - 14) / 3 < 16) cvt_step(cd, (i - 14) / 3 / 8, (i - 14) / 3 % 8);
+        if (i == MF - 1) {
+          cvt_done();
+          b_advance();
+          issue_q();
         }
-        // every wave holds the rest of this stage in registers; the activations of the next stage and
-        // this wave's codes of the stage after it have landed; the next stage's weights are converted
-        mm::wait_all_reads_and_barrier<VM_BOUND>();
-        const int nslot = cslot + 1 == NS ? 0 : cslot + 1;
-        const char* nstage = lds + nslot * STAGE_BYTES;
-        // k step 1 from Gf; fetch k step 0 of the next stage; read this wave's codes of stage kt + 2,
-        // convert their first half, refill the side-ring slot that stage kt + 1 has left
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          mfma_one(Gf, i);
-          if (i < 8) load_piece(F, nstage, 0, i);
-          if (i == 0) cvt_read(cd);
-          if (i >= 8) cvt_step(cd, 0, i - 8);          // first chunk, into the slot of stage kt + 2
-          if (i == 15) issue_q();
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        cslot = nslot;
+        __builtin_amdgcn_sched_barrier(0);
       }
+      cslot = nslot;
+    };
+    for (int ti = 0; ti < n_my; ++ti) {
+      for (int kt = 0; kt < KT; kt += 2) {
+        multiply(F, Gf);
+        multiply(Gf, F);
+      }
+      dense::settle(acc);
       int i0, j0, split;
       tile_origin(ti, i0, j0, split);
       if constexpr (PARTS) {
-        float* P = g.parts + ((i64)split * (g.tiles_m * BM) + i0 + wm * (BM / 2) + li) * g.ldb + j0 + wn * (BN / 2) + 8 * h;
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-          for (int c = 0; c < TN; ++c)
-#pragma unroll
-            for (int q = 0; q < 4; q += 2) {
-              typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-              float lo[4], hi[4];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const float x = acc[a][c][4 * q + e], y = acc[a][c][4 * q + 4 + e];   // scalars first: a bit cast straight from a vector element reads element 0
-                const uint2v r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
-                const unsigned r0 = r[0], r1 = r[1];
-                lo[e] = __builtin_bit_cast(float, r0);
-                hi[e] = __builtin_bit_cast(float, r1);
-                acc[a][c][4 * q + e] = 0.f;
-                acc[a][c][4 * q + 4 + e] = 0.f;
-              }
-              float* at = P + (i64)(a * 32) * g.ldb + c * 32 + 8 * q;
-              *reinterpret_cast<float4*>(at) = make_float4(lo[0], lo[1], lo[2], lo[3]);
-              *reinterpret_cast<float4*>(at + 4) = make_float4(hi[0], hi[1], hi[2], hi[3]);
-            }
-      } else {
-        uint16_t* Ct = g.C + (i64)i0 * g.ldc + j0 + coff;
+        float* P = g.parts + ((i64)split * (g.tiles_m * BM) + i0 + wm * (BM / 2) + li) * g.ldb + j0 + wn * (BN / 2) + 4 * q4;
 #pragma unroll
         for (int a = 0; a < TM; ++a)
 #pragma unroll
           for (int c = 0; c < TN; ++c) {
-            uint32_t p[8];
+            *reinterpret_cast<floatx4*>(P + (i64)(a * 16) * g.ldb + c * 16) = acc[a][c];
+            acc[a][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
+      } else {
+        uint16_t* Ct = g.C + (i64)(i0 + wm * (BM / 2) + li) * g.ldc + j0 + wn * (BN / 2) + 16 * (q4 & 1) + 8 * (q4 >> 1);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) p[e] = mm::pack2_bf16(acc[a][c][2 * e], acc[a][c][2 * e + 1]);
+        for (int a = 0; a < TM; ++a)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
-#pragma unroll
-            for (int q = 0; q < 4; q += 2) {
-              typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-              const uint2v r0 = __builtin_amdgcn_permlane32_swap(p[2 * q], p[2 * q + 2], false, false);
-              const uint2v r1 = __builtin_amdgcn_permlane32_swap(p[2 * q + 1], p[2 * q + 3], false, false);
-              const u32x4 o = {r0[0], r1[0], r0[1], r1[1]};
-              *reinterpret_cast<u32x4*>(Ct + (i64)a * 32 * g.ldc + c * 32 + 8 * q) = o;
-            }
+          for (int c = 0; c < TN; c += 2) {
+            uint32_t o[4];
+            dense::pack_pair(acc[a][c], acc[a][c + 1], o);
+            acc[a][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+            acc[a][c + 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<u32x4*>(Ct + (i64)a * 16 * g.ldc + c * 16) = u32x4{o[0], o[1], o[2], o[3]};
           }
       }
     }

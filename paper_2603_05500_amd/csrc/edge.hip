@@ -4,7 +4,7 @@
 // 64 x 64 x 16 tiles with one scalar load per element and one workgroup per output tile whatever the
 // contraction: 44 TFLOP/s at 2048 x 5632 x 1999 bf16, and 149 us for the 22 block gradients of 1376 features
 // over 1024 tokens.
-#include "edge_gemm.h"
+#include "edge_slices.h"
 
 namespace poetx {
 namespace {
@@ -22,7 +22,71 @@ Tile apply_tile(i64 batches, i64 M, i64 N) {
   return TILE_32;
 }
 
-// Dense products: tile and contraction split priced together.  A workgroup takes `lone` us for a stage when it has a CU to itself (`cold` more
+// Dense products on the sliced kernel (edge_slices.h): tile and contraction split priced together.  A workgroup's wave takes `lone` us for a slice when the
+// workgroup has a CU to itself (`cold` more where the weight is larger than the L2s would keep) and `shared` for each of the workgroups of
+// the fullest CU, each of which adds `tail`, on top of `base` for the launch, the first loads and the last stores.  A split adds a launch of `reduce` us with its gap and the
+// fp32 parts, written and read; it leaves every wave two slices, and no more than four workgroups per CU (parts of 16 MB at most).
+// The constants are fitted to 1750 products of 128 - 14336 rows, 1 - 4096 columns and contractions of 128 - 14336, both directions, each timed with every tile and up to sixteen
+// splits: the choice is 1.3 % slower than the best one on average, and takes a third less time than the edge kernel under its own plan (fp32 33 %, bf16 36 %).
+// us, edge kernel / here: fp32 1024 x 768 x 1001 29.0 / 18.0 and, backward, 29.7 (with its reduce) / 21; 256 x 256 x 512 6.0 / 4.3; bf16 1376 x 512 x 1024 9.1 / 6.4 and 11.2 / 5.6;
+// 768 x 1024 x 500 9.0 / 5.1; 1536 x 1536 x 3000 40.3 / 37.7.
+struct SliceCost {
+  int bm, bn, waves;
+  double base, lone, shared, tail, cold, reduce, parts;
+};
+enum SliceTile { SLICES_32 = 0, SLICES_32x64 = 1, SLICES_64 = 2, SLICES_64x32 = 3, EDGE_TILES = -1 };
+constexpr SliceCost kSlicesF32[] = {{32, 32, 8, 2.5, 0.16, 0.50, 0.83, 0.26, 2.7, 1.0e-6}, {32, 64, 4, 3.4, 0.41, 0.535, 0.45, 0.22, 2.7, 1.0e-6}, {64, 64, 4, 4.0, 0.975, 0.975, 0.25, 0.07, 2.7, 2.0e-6}};
+constexpr SliceCost kSlicesBf16[] = {{32, 32, 8, 1.73, 0.01, 0.52, 0.51, 0.35, 3.2, 0.8e-6}, {32, 64, 4, 2.05, 0.03, 0.345, 0.45, 0.11, 3.2, 0.8e-6}, {64, 64, 4, 1.8, 0.43, 0.445, 1.17, 0.09, 3.2, 1.0e-6}};
+// Up to 32 columns of a large bf16 weight are bound by the reads of it.  Where its rows are the contraction (dA = W^T dB) 32 of them are half a cache line, so 64 go to
+// a workgroup: 7168 x 12800, one token 37.4 us, on 32 x 32 64.4; 9728 x 4096, 5: 21.0 / 26.2.  Fitted to 230 products like the above, 3 % slower than the best on average.
+constexpr SliceCost kSlicesFew[] = {{32, 32, 8, 1.50, 0.67, 0.68, 0.53, 0, 3.3, 1.8e-6}, {64, 32, 4, 1.20, 0.04, 0.59, 0.57, 0, 4.75, 1.3e-6}};
+struct SlicePlan {
+  SliceTile tile;
+  int splits;
+};
+constexpr double kLargeWeight = 6.3e6;         // bytes
+// sizes the kernel takes (operands on 16-byte boundaries besides, which the caller looks at): whole slices, rows in whole 16-byte vectors
+bool slices_take(int dtype, i64 M, i64 ld_w, i64 act_cols, i64 K) {
+  const i64 es = dtype == POETX_F32 ? 4 : 2;
+  return K * es % 64 == 0 && ld_w * es % 16 == 0 && act_cols % 8 == 0 && ld_w < (1 << 22) && act_cols < (1 << 22) && tile_count(1, M, act_cols, 32) < (1 << 21);
+}
+double edge_price(int dtype, i64 M, i64 N, i64 K, Plan* plan);
+SlicePlan slice_plan(int dtype, int trans_w, i64 M, i64 N, i64 K) {
+  const bool f = dtype == POETX_F32;
+  const i64 es = f ? 4 : 2, slices = K * es / 64;
+  const bool large = (double)M * (double)K * (double)es > kLargeWeight;
+  SlicePlan best{SLICES_32, 1};
+  double least = 0;
+  auto price = [&](const SliceCost& c, SliceTile tile) {
+    const i64 count = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    for (int s = 1; s <= 16; ++s) {
+      const i64 each = (slices + s - 1) / s, splits = (slices + each - 1) / each;      // no empty split
+      if (s > 1 && (each <= c.waves || count * s > 4 * kCUs)) break;
+      const double per_cu = (double)((count * splits + kCUs - 1) / kCUs), stage = per_cu * c.shared, lone = c.lone + (large ? c.cold : 0);
+      double us = c.base + (double)((each + c.waves - 1) / c.waves) * (lone > stage ? lone : stage) + c.tail * per_cu;
+      if (splits > 1) us += c.reduce + c.parts * (double)splits * (double)M * (double)N;
+      if (least == 0 || us < least) { least = us; best = SlicePlan{tile, (int)splits}; }
+    }
+  };
+  if (!f && large && N <= 32) {
+    price(kSlicesFew[trans_w ? 1 : 0], trans_w ? SLICES_64x32 : SLICES_32);
+    return best;
+  }
+  for (int i = 0; i < 3; ++i) {
+    const SliceCost& c = f ? kSlicesF32[i] : kSlicesBf16[i];
+    if (i == 0 || (2 * M > c.bm && 2 * N > c.bn)) price(c, (SliceTile)i);    // not where half of the tile would be idle
+  }
+  // Large bf16 weights: the 128 x 128 tiles of the edge kernel read each operand half as often.  They stay unless this price is a quarter below theirs: of 1750 products
+  // three are then more than 2 % slower than under the edge plan alone, eleven more than 5 % where the lower price decides.
+  if (!f && large) {
+    Plan p;
+    const double us = edge_price(dtype, M, N, K, &p);
+    if (p.tile == TILE_128 && us < 1.25 * least) best.tile = EDGE_TILES;
+  }
+  return best;
+}
+
+// Dense products of the edge kernel: tile and contraction split priced together.  A workgroup takes `lone` us for a stage when it has a CU to itself (`cold` more
 // where the weight is larger than the L2s would keep) and `shared` for each of the workgroups on its CU, of which the fullest CU counts; `fill` stages
 // more to fill the ring and to store.  A split adds a launch of `reduce` us with its gap and its fp32 parts, written and read at 4 TB/s.
 // The constants are fitted to 1520 products of 128 - 14336 rows, 1 - 5000 columns and contractions of 128 - 14336, both directions, weights over 6 MB read from
@@ -38,21 +102,14 @@ struct TileCost {
   int side;
   double lone, shared;
 };
-Plan dense_plan(int dtype, i64 M, i64 N, i64 K) {
+double edge_price(int dtype, i64 M, i64 N, i64 K, Plan* plan) {
   static const TileCost f32[] = {{TILE_32, 32, 0.70, 0.51}, {TILE_64, 64, 1.51, 0.66}, {TILE_64D, 64, 1.57, 1.46}, {TILE_128, 128, 2.69, 2.32}};
   static const TileCost bf16[] = {{TILE_32, 32, 0.58, 0.31}, {TILE_64, 64, 0.58, 0.35}, {TILE_128, 128, 1.14, 0.62}};
   const bool f = dtype == POETX_F32;
   const size_t es = f ? 4 : 2;
   const double fill = f ? 0.94 : 1.1, reduce = f ? 1.95 : 2.3;
-  const bool large = (double)M * (double)K * (double)es > 6.3e6;
+  const bool large = (double)M * (double)K * (double)es > kLargeWeight;
   const double cold = large ? (f ? 0.63 : 0.39) : 0;
-  if (large && N <= 32) {     // bound by the reads of the weight
-    const i64 count = tile_count(1, M, N, 32), depth = stage_depth(TILE_32, es), stages = (K + depth - 1) / depth;
-    const i64 two = min64(2 * kCUs / count, stages / 2), four = min64(4 * kCUs / count, stages / 4), s = two > four ? two : four;
-    if (s <= 1) return Plan{TILE_32, 1};
-    const i64 per = (stages + s - 1) / s;
-    return Plan{TILE_32, (int)((stages + per - 1) / per)};
-  }
   Plan best{TILE_32, 1};
   double least = 0;
   for (int t = 0; t < (f ? 4 : 3); ++t) {
@@ -69,7 +126,21 @@ Plan dense_plan(int dtype, i64 M, i64 N, i64 K) {
       if (least == 0 || us < least) { least = us; best = Plan{c.tile, (int)splits}; }
     }
   }
-  return best;
+  *plan = best;
+  return least;
+}
+Plan dense_plan(int dtype, i64 M, i64 N, i64 K) {
+  const size_t es = dtype == POETX_F32 ? 4 : 2;
+  if (N <= 32 && (double)M * (double)K * (double)es > kLargeWeight) {     // bound by the reads of the weight
+    const i64 count = tile_count(1, M, N, 32), depth = stage_depth(TILE_32, es), stages = (K + depth - 1) / depth;
+    const i64 two = min64(2 * kCUs / count, stages / 2), four = min64(4 * kCUs / count, stages / 4), s = two > four ? two : four;
+    if (s <= 1) return Plan{TILE_32, 1};
+    const i64 per = (stages + s - 1) / s;
+    return Plan{TILE_32, (int)((stages + per - 1) / per)};
+  }
+  Plan p;
+  edge_price(dtype, M, N, K, &p);
+  return p;
 }
 // Block gradients: the contraction is the token range, so a large tile with a split costs only its fp32 parts, while
 // every halving of the tile side doubles the reads of both activations.  A split keeps 256 tokens, on the smallest tile two
@@ -205,10 +276,39 @@ void reduce(const float* part, i64 M, i64 N, int splits, T* out, i64 ld, hipStre
   hipLaunchKernelGGL(edge_reduce_kernel<T>, dim3((unsigned)((M * N + 1023) / 1024)), dim3(256), 0, st, part, M * N, splits, out, (int)N, ld);
 }
 
+template <class T, bool A_K, class Epi>
+void launch_slice_tile(SliceTile tile, const SliceArgs& g, const Epi& epi, i64 N, int splits, hipStream_t st) {
+  if constexpr (sizeof(T) == 2 && !A_K) {
+    if (tile == SLICES_64x32) return launch_slices<T, 64, 32, 4, 2, A_K>(g, epi, N, splits, st);
+  }
+  if (tile == SLICES_32) launch_slices<T, 32, 32, 8, 2, A_K>(g, epi, N, splits, st);
+  else if (tile == SLICES_32x64) launch_slices<T, 32, 64, 4, 2, A_K>(g, epi, N, splits, st);
+  else launch_slices<T, 64, 64, 4, 2, A_K>(g, epi, N, splits, st);
+}
+template <class T>
+void dense_slices(const SlicePlan& p, int trans_w, const T* W, int n, int m, const T* act, i64 act_cols, T* out, i64 ld_out, i64 N, float* parts, hipStream_t st) {
+  const int M = trans_w ? m : n, K = trans_w ? n : m;
+  const SliceArgs g{W, act, m, act_cols, M, (int)act_cols, 0, K * (int)sizeof(T) / 64, 0};
+  if (p.splits > 1) {
+    const EpiPartial epi{parts, M, (int)N, 1};
+    if (trans_w) launch_slice_tile<T, false>(p.tile, g, epi, N, p.splits, st);
+    else launch_slice_tile<T, true>(p.tile, g, epi, N, p.splits, st);
+    reduce<T>(parts, M, N, p.splits, out, ld_out, st);
+  } else {
+    const EpiStore<T> epi{out, ld_out, M, (int)N};
+    if (trans_w) launch_slice_tile<T, false>(p.tile, g, epi, N, 1, st);
+    else launch_slice_tile<T, true>(p.tile, g, epi, N, 1, st);
+  }
+}
+
 template <class T>
 void dense_t(int dtype, int trans_w, const T* W, int n, int m, const T* act, i64 ld_act, i64 act_cols, T* out, i64 ld_out, i64 N, void* ws,
              hipStream_t st) {
   const int M = trans_w ? m : n, K = trans_w ? n : m;
+  if (slices_take(dtype, M, m, act_cols, K) && ld_act == act_cols && (((uintptr_t)W | (uintptr_t)act) & 15) == 0) {
+    const SlicePlan sp = slice_plan(dtype, trans_w, M, act_cols, K);
+    if (sp.tile != EDGE_TILES) return dense_slices(sp, trans_w, W, n, m, act, act_cols, out, ld_out, N, (float*)ws, st);
+  }
   const Plan p = dense_plan(dtype, M, act_cols, K);
   Args g{};
   g.A = Op{W, m, 0, nullptr, n, m, 0, 0};
@@ -294,9 +394,17 @@ void grad_pair_t(const Plan& p0, const Plan& p1, const GradProblem& q0, const Gr
 
 }  // namespace
 
+// Which of the two kernels it is depends on the pointers' alignment as well, which a query does not see: the parts of either, and of either direction.
 size_t edge_dense_workspace_bytes(int dtype, i64 M, i64 act_cols, i64 K) {
   const Plan p = dense_plan(dtype, M, act_cols, K);
-  return p.splits > 1 ? (size_t)p.splits * M * act_cols * sizeof(float) : 0;
+  int splits = p.splits;
+  if (slices_take(dtype, M, 16, act_cols, K)) {
+    for (int trans = 0; trans < 2; ++trans) {
+      const SlicePlan s = slice_plan(dtype, trans, M, act_cols, K);
+      if (s.tile != EDGE_TILES && s.splits > splits) splits = s.splits;
+    }
+  }
+  return splits > 1 ? (size_t)splits * M * act_cols * sizeof(float) : 0;
 }
 
 void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void* act, i64 ld_act, i64 act_cols, void* out, i64 ld_out, i64 N,

@@ -145,6 +145,25 @@ __device__ inline int kx_swz(int c, int k) {
   else return c;
 }
 
+// Fragment of 32 rows (columns) from x0, k step ks of a 32-deep bf16 sub-tile: K major, or X major through the transposing read
+template <int X, bool K_MAJOR>
+__device__ __forceinline__ bf16x8 frag_bf16(const char* sub, int x0, int ks) {
+  const int lane = threadIdx.x & 63;
+  if constexpr (K_MAJOR) {
+    const int r = x0 + (lane & 31);
+    return *reinterpret_cast<const bf16x8*>(sub + r * 64 + 16 * mm::xk_chunk(2 * ks + (lane >> 5), r));
+  } else {
+    const int q = lane >> 4, i = lane & 15;
+    const int k = 16 * ks + 8 * (q >> 1) + (i >> 2);
+    const int c = (x0 >> 3) + 2 * (q & 1) + ((i & 3) >> 1);
+    // the swizzle depends on k & 3 only, so the second half (k + 4) uses the same chunk position
+    const char* p = sub + k * (X * 2) + 16 * kx_swz<X>(c, k) + 8 * (i & 1);
+    const short4v lo = mm::lds_read_tr(p), hi = mm::lds_read_tr(p + 4 * (X * 2));
+    const short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  }
+}
+
 template <class T, int X, int BK>
 constexpr int tile_bytes() { return sizeof(T) == 2 ? X * BK * 2 : (X + 4) * BK * 4; }
 
@@ -293,21 +312,6 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
       for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
 
   const int li = lane & 31, h = lane >> 5;
-  auto frag_bf16 = [&](const char* sub, int x0, int ks, auto X_, bool kmajor) -> bf16x8 {
-    constexpr int X = decltype(X_)::value;
-    if (kmajor) {
-      const int r = x0 + li;
-      return *reinterpret_cast<const bf16x8*>(sub + r * 64 + 16 * mm::xk_chunk(2 * ks + h, r));
-    }
-    const int q = lane >> 4, i = lane & 15;
-    const int k = 16 * ks + 8 * (q >> 1) + (i >> 2);
-    const int c = (x0 >> 3) + 2 * (q & 1) + ((i & 3) >> 1);
-    // the swizzle depends on k & 3 only, so the second half (k + 4) uses the same chunk position
-    const char* p = sub + k * (X * 2) + 16 * kx_swz<X>(c, k) + 8 * (i & 1);
-    const short4v lo = mm::lds_read_tr(p), hi = mm::lds_read_tr(p + 4 * (X * 2));
-    const short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
-  };
   auto multiply = [&](int slot) {
     const char* sA = lds + slot * S::STAGE;
     const char* sB = sA + S::A_BYTES;
@@ -322,10 +326,10 @@ __device__ __forceinline__ void edge_product(const Args& g, const Epi& epi, int 
           bf16x8 fa[TM], fb[TN];
 #pragma unroll
           for (int a = 0; a < TM; ++a)
-            fa[a] = frag_bf16(sA + sub * (BM * 64), wm * (BM / WGM) + a * 32, ks, std::integral_constant<int, BM>{}, A_K);
+            fa[a] = frag_bf16<BM, A_K>(sA + sub * (BM * 64), wm * (BM / WGM) + a * 32, ks);
 #pragma unroll
           for (int c = 0; c < TN; ++c)
-            fb[c] = frag_bf16(sB + sub * (BN * 64), wn * (BN / WGN) + c * 32, ks, std::integral_constant<int, BN>{}, B_K);
+            fb[c] = frag_bf16<BN, B_K>(sB + sub * (BN * 64), wn * (BN / WGN) + c * 32, ks);
 #pragma unroll
           for (int a = 0; a < TM; ++a)
 #pragma unroll

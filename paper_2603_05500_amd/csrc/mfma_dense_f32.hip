@@ -116,10 +116,12 @@ __global__ __launch_bounds__(256) void dense_f32_kernel(Args g) {
 
 bool mfma_dense_f32_supported(int n, int m, i64 N) { return n % BM == 0 && m % BM == 0 && N % BN == 0; }
 
-// One 128 x 128 tile per workgroup and no split of the contraction: with fewer tiles than three quarters of the CUs
-// the edge kernel's smaller tiles and splits win (forward of 1024 x 1024 x 2048, 128 tiles: 115 against 102 us;
-// 256 x 256 x 512: 32 against 18), above it this kernel does (2048 x 2048 x 4096, 512 tiles: 391 against 471 us).
+// Three quarters of the CUs have a 128 x 128 tile: what poetx_linear_path calls a large fp32 product.
 bool mfma_dense_f32_fills(int M, i64 N) { return (i64)(M / BM) * (N / BN) >= 192; }
+// One tile per workgroup and no split of the contraction, but half of the operand traffic of the sliced kernel's 64 x 64 tiles: it takes four tiles per CU until that tells.
+// us, here / sliced, forward and backward: 2048 x 2048 x 1536 (192 tiles) 157 / 106, 162 / 107; 2048 x 2048 x 4096 (512) 277 / 270, 270 / 259; 14336 x 4096 x 1024 (896, 256) 1022 / 917,
+// 1095 / 899; 4096 x 4096 x 4096 (1024) 1018 / 1027, 1038 / 1018; 2048 x 2048 x 16384 (2048) 1019 / 1047, 1037 / 1041; 1536 x 128 x 24576 (2304, 192) 93 / 115, 122 / 82.
+bool mfma_dense_f32_preferred(int n, int m, int M, i64 N) { return mfma_dense_f32_supported(n, m, N) && (i64)(M / BM) * (N / BN) >= 1024; }
 
 void mfma_dense_f32(int trans_w, const void* W, int n, int m, const void* act, void* out, i64 N, hipStream_t st) {
   Args g{(const float*)W, (const float*)act, (float*)out, n, m, N, trans_w ? n : m};

@@ -109,7 +109,8 @@ void apply_left_alone(int dtype, const Act& V, const Act& out, int d, const int3
   apply_left_dispatch(dtype, V, out, d, perm, blocks, b, trans, whole || mfma_apply_left_ragged_supported(d, V.cols, b), V.cols, st);
 }
 
-// Does the streaming fp32 product take the direction with M output rows?
+// Is the direction with M output rows a large fp32 product, in whole tiles that fill the chip (poetx_linear_path)?  Either fp32 kernel that moves aligned vectors may
+// take it; see mfma_dense_f32_preferred.
 bool dense_f32_streams(int n, int m, int M, i64 N) { return mfma_dense_f32_supported(n, m, N) && mfma_dense_f32_fills(M, N); }
 
 // part: scratch of dense_part_bytes() for products that split their contraction.
@@ -124,7 +125,7 @@ void dense_dispatch(const poetx_linear_desc* desc, int trans_w, const void* W, c
   if (w_q8) mfma_dense_q8(trans_w, W, n, m, act.p, out.out(), N, part, st);
   else if (use_mfma(dtype) && act.ld == act.cols && mfma_dense_supported(n, m, act.cols) && aligned16(W) && aligned16(act.p))
     mfma_dense(trans_w, W, n, m, act.p, act.cols, out.out(), out.ld, N, part, st);
-  else if (dtype == POETX_F32 && !g_force_fma.load() && dense_f32_streams(n, m, trans_w ? m : n, desc->n_tokens) && aligned16(W) && aligned16(act.p) &&
+  else if (dtype == POETX_F32 && !g_force_fma.load() && mfma_dense_f32_preferred(n, m, trans_w ? m : n, desc->n_tokens) && aligned16(W) && aligned16(act.p) &&
            aligned16(out.p))
     mfma_dense_f32(trans_w, W, n, m, act.p, out.out(), N, st);
   else if (!g_force_fma.load()) edge_dense(dtype, trans_w, W, n, m, act.p, act.ld, act.cols, out.out(), out.ld, N, part, st);

@@ -373,6 +373,60 @@ def test_dense_tiles(lib, n, m, N):
         assert torch.all(buf[:256] == -7.0) and torch.all(buf[256 + used:] == -7.0)
 
 
+@pytest.mark.parametrize("dtype,n,m,N", [
+    # tile and contraction ranges of the sliced product, forward; backward
+    ("f32", 64, 48, 5),          # 32 x 32, fewer slices than waves; the same
+    ("f32", 256, 256, 512),      # 32 x 32; the same
+    ("f32", 1024, 768, 1001),    # 32 x 64, half a tile of columns over; the same
+    ("f32", 1040, 1008, 1991),   # 64 x 64, rows and columns over; the same
+    ("f32", 144, 3264, 33),      # 32 x 32 in ranges; 32 x 32
+    ("f32", 1792, 16, 40),       # one slice: seven waves without any; 32 x 32 in ranges
+    ("f32", 4112, 4096, 2040),   # 64 x 64, large weight
+    ("bf16", 64, 96, 3),         # 32 x 32, three slices for eight waves; two
+    ("bf16", 512, 1376, 1024),   # 32 x 64; 64 x 64
+    ("bf16", 1376, 512, 1023),   # 64 x 64, rows and columns over; 32 x 64
+    ("bf16", 96, 3200, 17),      # 32 x 32; the same
+    ("bf16", 3104, 2080, 29),    # few columns of a large weight: 32 x 32 in ranges; 64 x 32 in ranges
+    ("bf16", 2080, 3104, 300),   # large weight: edge tiles or slices by price
+    ("bf16", 1568, 1504, 2999),  # 64 x 64
+])
+def test_sliced_dense_products(lib, dtype, n, m, N):
+    """The sliced product at the edges of its tiles, with fewer slices than waves and with split contractions, both directions, against float64 on the same operands, nothing written outside; and
+    against the general kernel, which the same call takes when the weight lies one element off a 16-byte boundary.  A whole pass with blocks equal to the
+    identity is the dense product between two exact permutation round trips.  fp32: K additions rounded by 2^-24 of a running sum no larger than the
+    largest result, which add up like a random walk: sqrt(4112) 2^-24 = 3.8e-6; bf16: one rounding more, 2^-9."""
+    rng = np.random.Generator(np.random.PCG64(9900 + n + m + N))
+    b, dt, tol = 16, tdtype(dtype), (4e-6 if dtype == "f32" else 2.0 ** -8)
+    rnd = round_f32 if dtype == "f32" else round_bf16
+    X, dZ = rnd(rng.standard_normal((m, N))), rnd(rng.standard_normal((n, N)))
+    W = rnd(rng.standard_normal((n, m)) * 0.02)
+    desc = lib.make_desc(m, n, b, 2, N, lib.F32 if dtype == "f32" else lib.BF16)
+    pi = {"R": torch.from_numpy(rng.permutation(m).astype(np.int32)).cuda(), "P": torch.from_numpy(rng.permutation(n).astype(np.int32)).cuda()}
+    if dtype == "f32":
+        blk = {s: torch.eye(b, device="cuda").repeat(d // b, 1, 1).contiguous() for s, d in (("R", m), ("P", n))}
+    else:
+        blk = {s: torch.zeros((d // b, 2, b, b), dtype=dt, device="cuda") for s, d in (("R", m), ("P", n))}
+    Xd, dZd = to_dev(X, dt), to_dev(dZ, dt)
+    got = []
+    for off in (0, 1):
+        Wd = torch.empty(n * m + 1, dtype=dt, device="cuda")[off:off + n * m].view(n, m)
+        Wd.copy_(to_dev(W, dt))
+        ws = torch.full((lib.poetx_linear_workspace_bytes(desc) // 4,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
+        guard, guard_dA = (torch.full((d * N + 512,), -7.0, dtype=dt, device="cuda") for d in (n, m))
+        Z, B = torch.empty((n, N), dtype=dt, device="cuda"), guard[256:256 + n * N].view(n, N)
+        dX, dA = torch.empty((m, N), dtype=dt, device="cuda"), guard_dA[256:256 + m * N].view(m, N)
+        lib.poetx_linear_fwd(desc, Xd, Wd, pi["R"], pi["P"], blk["R"], blk["P"], Z, B, ws)
+        lib.poetx_linear_bwd_input(desc, dZd, Wd, pi["R"], pi["P"], blk["R"], blk["P"], dX, dA, ws)
+        torch.cuda.synchronize()
+        assert rel_err(to_np(B), W @ X) <= tol and torch.equal(Z, B)
+        assert rel_err(to_np(dA), W.T @ dZ) <= tol and torch.equal(dX, dA)
+        for buf, used in ((guard, n * N), (guard_dA, m * N)):
+            assert torch.all(buf[:256] == -7.0) and torch.all(buf[256 + used:] == -7.0)
+        got.append((to_np(B), to_np(dA)))
+    for here, general in zip(*got):
+        assert rel_err(here, general) <= tol
+
+
 @pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 40, (3,)), (512, 130, (3,)), (256, 130, (2,)), (256, 150, (2,)), (256, 3, (1, 2, 7)), (256, 9, (1, 5)), (256, 200, (4,))])
 def test_matrix_core_series(lib, b, nb, ks):
     """The bf16 series of large blocks, build and backward through poetx_cnp_build / poetx_cnp_bwd: every shape of the

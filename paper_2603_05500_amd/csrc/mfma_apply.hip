@@ -19,6 +19,8 @@ using mm::floatx16;
 using mm::short4v;
 using mm::short8v;
 
+constexpr int SBN256 = 128, SBN = 64;   // tokens of a tile: of long streams at b = 256, and elsewhere
+
 // ---------------------------------------------------------------------------------------
 // One persistent workgroup per (block, 256-row slice of it, token range).
 //   * 8 waves; wave w owns 32 output rows of the slice for computing and storing.
@@ -31,14 +33,17 @@ using mm::short8v;
 //     wave's own rows (1.0 * x accumulates exactly in fp32), so nothing is re-read.
 //   * results leave from registers: a lane owns one row and 4 consecutive tokens (8-byte
 //     packed stores), scattered through the same index map that gathered them.
-// b = 256: one slice, 128-token tiles.  b = 512: two slices per block (the block operand of
-// a whole block does not fit the register file), 64-token tiles; the two workgroups of a
+// b = 256: one slice.  b = 512: two slices per block (the block operand of
+// a whole block does not fit the register file); the two workgroups of a
 // block read the same token tiles, the second read being served by L2 / Infinity Cache.
+// Tiles of 64 tokens (one 128-byte line of a row) fill the chip from half the tokens that 128 take and start sooner; long streams are read and written from
+// memory in 256-byte pieces of a row (b = 256, us in a layer, 64 / 128 tokens a tile: 4096 features, 4096 tokens 18.4 / 19.6, 16384 70.9 / 63.6 = 4.2 TB/s;
+// 14336 features, 16384 tokens 223 / 207).
 template <int B, int BN>
 __global__ __launch_bounds__(512) void apply_left_stream_kernel(const uint16_t* __restrict__ V,
                                                                  uint16_t* __restrict__ out, i64 ld,
                                                                  const int32_t* __restrict__ perm,
-                                                                 const uint16_t* __restrict__ blocks, int trans,
+                                                                 const uint16_t* __restrict__ blocks, int trans, int tiles,
                                                                  int tiles_per_wg, int paired_chunks) {
   constexpr int MSPLIT = B / 256, TN = BN / 32, KS = B / 16;
   constexpr int STAGE_BYTES = B * BN * 2;
@@ -58,7 +63,10 @@ __global__ __launch_bounds__(512) void apply_left_stream_kernel(const uint16_t* 
     j = pair / paired_chunks;
     chunk = pair % paired_chunks;
   }
-  const i64 tok0 = (i64)chunk * tiles_per_wg * BN;
+  const int first = chunk * tiles_per_wg;
+  const int T = tiles - first < tiles_per_wg ? tiles - first : tiles_per_wg;
+  if (T <= 0) return;
+  const i64 tok0 = (i64)first * BN;
   const int32_t* pm = perm + (i64)j * B;
   const int li = lane & 31, h = lane >> 5;
   const uint32_t ring_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
@@ -136,13 +144,13 @@ __global__ __launch_bounds__(512) void apply_left_stream_kernel(const uint16_t* 
       for (int i = 0; i < 4; ++i)
         *reinterpret_cast<u32x4*>(out + soff[i] + (i64)t * BN + hf * 64) = pend[hf * 4 + i];
   };
-  for (int t = 0; t < tiles_per_wg; ++t) {
+  for (int t = 0; t < T; ++t) {
     // tile t has landed and every wave is done reading the stage that tile t+1 overwrites: the
     // wait covers this wave's own LDS reads too (lgkmcnt), so the ring does not depend on where the
     // compiler places the MFMAs that consume them
     mm::wait_all_reads_and_barrier<0>();
     if (t > 0) flush(t - 1);
-    if (t + 1 < tiles_per_wg) issue(t + 1);
+    if (t + 1 < T) issue(t + 1);
     const char* stage = ring + (t & 1) * STAGE_BYTES;
     auto load_tok = [&](bf16x8* fb, int ks) {
 #pragma unroll
@@ -204,10 +212,24 @@ __global__ __launch_bounds__(512) void apply_left_stream_kernel(const uint16_t* 
       if (hf + 1 < NH) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read back before the area is rewritten
     }
   }
-  flush(tiles_per_wg - 1);
+  flush(T - 1);
 }
 
-// token ranges per block slice: fill the 256 CUs in whole rounds, at least 2 tiles per workgroup
+// Tiles per workgroup of `units` block slices with `tiles` token tiles each: the fewest tile times on 256 CUs, a workgroup's lead-in (indices, block operand, first
+// tile) counted as three tiles.  (Measured, b = 256: 6 us and 1.7 a tile, 3.6 where all CUs share the memory; b = 512: 9.6 and 2.9, 4.3.)  Each count is tried up to
+// 64, then steps of a 64th, so that with millions of tokens the search does not take longer than the launch.
+int tiles_per_workgroup(i64 units, int tiles) {
+  int per = tiles;
+  i64 best = 0;
+  for (int p = 1; p <= tiles; p += 1 + p / 64) {
+    const i64 rounds = (units * ceil_div(tiles, p) + 255) / 256, cost = rounds * (p + 3);
+    if (best == 0 || cost < best) { best = cost; per = p; }
+    if (rounds == 1) break;   // longer ranges only cost more
+  }
+  return per;
+}
+
+// Chunks of long streams (128-token tiles): whole rounds of 256 workgroups of at least two tiles.
 int stream_chunks(int slices, int tiles) {
   int best = 1;
   double best_eff = 0.0;
@@ -232,13 +254,12 @@ void launch_apply_stream(const uint16_t* V, uint16_t* out, int d, i64 cols, i64 
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS) == hipSuccess;
   (void)configured;
   const int nb = d / B, tiles = (int)(cols / BN);
-  const int chunks = stream_chunks(nb * MSPLIT, tiles);
-  if (MSPLIT == 2 && (nb * chunks) % 8 == 0)
-    hipLaunchKernelGGL(kern, dim3(chunks * MSPLIT * nb), dim3(512), LDS, st, V, out, ld, perm, E, trans, tiles / chunks, chunks);
+  const int per = BN == 128 ? tiles / stream_chunks(nb * MSPLIT, tiles) : tiles_per_workgroup((i64)nb * MSPLIT, tiles), chunks = ceil_div(tiles, per);
+  if (MSPLIT == 2 && ((i64)nb * chunks) % 8 == 0)
+    hipLaunchKernelGGL(kern, dim3(chunks * MSPLIT * nb), dim3(512), LDS, st, V, out, ld, perm, E, trans, tiles, per, chunks);
   else
-    hipLaunchKernelGGL(kern, dim3(chunks * MSPLIT, nb), dim3(512), LDS, st, V, out, ld, perm, E, trans, tiles / chunks, 0);
+    hipLaunchKernelGGL(kern, dim3(chunks * MSPLIT, nb), dim3(512), LDS, st, V, out, ld, perm, E, trans, tiles, per, 0);
 }
-constexpr int SBN256 = 128, SBN512 = 64;   // tokens per tile of the streaming kernel
 
 // ---------------------------------------------------------------------------------------
 // The streaming kernel for token counts and row strides of any kind (V: nv columns, row stride ldv; out: no columns, row
@@ -401,8 +422,6 @@ __global__ __launch_bounds__(512) void apply_left_ragged_kernel(const uint16_t* 
   flush(T - 1);
 }
 
-// Token ranges per block slice: the fewest tile times on 256 CUs, a workgroup's lead-in (block operand, first tile) counted as
-// three tiles.
 template <int B>
 void launch_apply_ragged(const uint16_t* V, i64 ldv, i64 nv, uint16_t* out, i64 ldo, i64 no, int d, const int32_t* perm, const uint16_t* E,
                          int trans, hipStream_t st) {
@@ -414,13 +433,7 @@ void launch_apply_ragged(const uint16_t* V, i64 ldv, i64 nv, uint16_t* out, i64 
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS) == hipSuccess;
   (void)configured;
   const int nb = d / B, tiles = ceil_div(no, 64);
-  int per = tiles;
-  i64 best = 0;
-  for (int p = 1; p <= tiles; ++p) {
-    const i64 rounds = ((i64)nb * MSPLIT * ceil_div(tiles, p) + 255) / 256, cost = rounds * (p + 3);
-    if (best == 0 || cost < best) { best = cost; per = p; }
-    if (rounds == 1) break;   // longer ranges only cost more: with millions of tokens the search is not to take longer than the launch
-  }
+  const int per = tiles_per_workgroup((i64)nb * MSPLIT, tiles);
   hipLaunchKernelGGL(kern, dim3(ceil_div(tiles, per) * MSPLIT, nb), dim3(512), LDS, st, V, out, ldv, ldo, (int)nv, (int)no, perm, E, trans, tiles, per);
 }
 
@@ -429,18 +442,20 @@ void launch_apply_ragged(const uint16_t* V, i64 ldv, i64 nv, uint16_t* out, i64 
 bool mfma_apply_left_supported(int d, i64 cols, i64 ld, int b) {
   if (d % b != 0 || ld % 8 != 0) return false;
   if (b == 256) return cols % SBN256 == 0;
-  if (b == 512) return cols % SBN512 == 0;
+  if (b == 512) return cols % SBN == 0;
   return false;
 }
 
 void mfma_apply_left(const void* V, void* out, int d, i64 cols, i64 ld, const int32_t* perm, const void* E, int b,
                      int transpose_G, hipStream_t st) {
-  if (b == 256 && cols % (2 * SBN256) == 0)
-    launch_apply_stream<256, SBN256>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
-  else if (b == 512 && cols % (2 * SBN512) == 0)
-    launch_apply_stream<512, SBN512>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
-  else   // an odd number of tiles
-    mfma_apply_left_ragged(V, ld, cols, out, ld, cols, d, perm, E, b, transpose_G, st);
+  if (b == 512) return launch_apply_stream<512, SBN>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
+  // By 64-token tiles per workgroup.  One or two: the ragged kernel's loads through registers are there a little earlier (us: 4096 features, 1024 tokens 10.4 / 9.5, 2048
+  // 14.2 / 13.3, with 128-token tiles 14.6 and 16.7; 8192 features, 2048 tokens, four tiles, 21.7 / 23.4).  From eight on 128-token tiles (see the kernel).  All three sum in
+  // the same order: the bits do not depend on the choice.
+  const int per = tiles_per_workgroup(d / 256, (int)(cols / SBN));
+  if (per <= 2) mfma_apply_left_ragged(V, ld, cols, out, ld, cols, d, perm, E, b, transpose_G, st);
+  else if (per < 8 || cols % (2 * SBN256) != 0) launch_apply_stream<256, SBN>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
+  else launch_apply_stream<256, SBN256>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
 }
 
 // The edge kernel reads the block operand once per tile and more than one workgroup reads a row, the streaming form starts with a chain

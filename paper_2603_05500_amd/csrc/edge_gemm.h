@@ -462,6 +462,24 @@ __global__ __launch_bounds__((Shape<T, BM, BN, BK, WGM, WGN, WAVES>::THREADS)) v
   edge_product<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, LOAD>(g, epi, second ? bx - n0 : bx, second ? total - n0 : n0, split);
 }
 
+// An apply and two problems of one shape (the block gradients of both sides) in one launch: what a small layer's backward has left once dA is there.  Each is a chain of
+// latencies that leaves most of the chip idle, and they do not depend on each other.  Workgroups: n0 of g0 for each of its splits, n1 of g1, then those of the apply.
+template <class T, int ABM, int ABK, int AWG, int AWAVES, Load ALOAD, class AEpi, int BK, Load LOAD, class Epi>
+__global__ __launch_bounds__(256) void edge_apply_pair_kernel(Args ga, AEpi ea, Args g0, Args g1, Epi e0, Epi e1, int n0, int n1, int pairs0, int pairs, int na) {
+  int bx = blockIdx.x;
+  if (bx < pairs) {
+    const bool second = bx >= pairs0;
+    const Args g = second ? g1 : g0;
+    const Epi epi = second ? e1 : e0;
+    if (second) bx -= pairs0;
+    const int n = second ? n1 : n0, split = bx / n;
+    edge_product<T, 32, 32, BK, 1, 1, 4, true, true, Epi, LOAD>(g, epi, bx - split * n, n, split);
+  } else {
+    if (threadIdx.x >= 64 * AWAVES) return;
+    edge_product<T, ABM, ABM, ABK, AWG, AWG, AWAVES, true, false, AEpi, ALOAD>(ga, ea, bx - pairs, na, 0);
+  }
+}
+
 // ---- host side -------------------------------------------------------------------------------
 enum Tile { TILE_32 = 0, TILE_64 = 1, TILE_128 = 2, TILE_64D = 3 };   // 64D: 64 x 64, deeper stages, sixteen waves (fp32 dense products)
 
@@ -586,6 +604,37 @@ void launch_pair(const Args& g0, const Args& g1, Epi e0, Epi e1, const Problem& 
   if (p0.tile == TILE_128) launch_pair_shape<T, 128, 128, D, 2, 2, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
   else if (p0.tile == TILE_64) launch_pair_shape<T, 64, 64, D, 2, 2, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
   else launch_pair_shape<T, 32, 32, 2 * D, 1, 1, 4, A_K, B_K>(g0, g1, e0, e1, q0, q1, p0.splits, p1.splits, st);
+}
+
+// the apply qa (ABM x ABM tiles) beside two gradients on 32 x 32 tiles
+template <class T, int ABM, int ABK, int AWG, int AWAVES, bool MASKS, class AEpi, class Epi>
+void launch_apply_pair(Args ga, AEpi ea, const Problem& qa, Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, int s0, int s1, hipStream_t st) {
+  constexpr int BK = 256 / (int)sizeof(T);
+  using S = Shape<T, 32, 32, BK, 1, 1, 4>;
+  using SA = Shape<T, ABM, ABM, ABK, AWG, AWG, AWAVES>;
+  constexpr int LDS = S::LDS > SA::LDS ? S::LDS : SA::LDS;
+  tile_args(ga, qa, ABM, ABM, ABK, 1);
+  tile_args(g0, q0, 32, 32, BK, s0);
+  tile_args(g1, q1, 32, 32, BK, s1);
+  const int na = (int)qa.batches * ga.tiles_m * ga.tiles_n, n0 = (int)q0.batches * g0.tiles_m * g0.tiles_n, n1 = (int)q1.batches * g1.tiles_m * g1.tiles_n;
+  // no split without stages
+  s0 = ceil_div(g0.stages, g0.stages_per_split);
+  s1 = ceil_div(g1.stages, g1.stages_per_split);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)(n0 * s0 + n1 * s1 + na)), dim3(256), LDS, st, ga, ea, g0, g1, e0, e1, n0, n1, n0 * s0, n0 * s0 + n1 * s1, na);
+  };
+  if constexpr (!MASKS) {
+    if (whole_tiles<ABM, ABM, ABK, true, false>(ga) && whole_tiles<32, 32, BK, true, true>(g0) && whole_tiles<32, 32, BK, true, true>(g1)) {
+      auto kern = edge_apply_pair_kernel<T, ABM, ABK, AWG, AWAVES, WHOLE, AEpi, BK, WHOLE, Epi>;
+      static const bool configured = lds_limit((const void*)kern, LDS);
+      (void)configured;
+      return go(kern);
+    }
+  }
+  auto kern = edge_apply_pair_kernel<T, ABM, ABK, AWG, AWAVES, MASKS ? MASKED : BRANCHED, AEpi, BK, BRANCHED, Epi>;
+  static const bool configured = lds_limit((const void*)kern, LDS);
+  (void)configured;
+  go(kern);
 }
 
 }  // namespace edge

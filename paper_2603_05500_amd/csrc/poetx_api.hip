@@ -611,10 +611,21 @@ int poetx_linear_recompute_b(const poetx_linear_desc* desc, const void* X, const
   return launch_status();
 }
 
-// dB = P dZ, dA = W^T dB, dX = R dA; ws holds dB (and the dequantised weight behind it)
+// dX = R dA beside the block gradients of a one-call backward (small blocks): what bwd_input_impl leaves out and bwd_skew_impl then does
+struct JoinedApply {
+  const void* blocks_R;
+  Act dX;
+};
+static bool joins_apply(const poetx_linear_desc* d) {
+  const int m = d->d_in, n = d->d_out, b = d->block;
+  return !(d->flags & POETX_FLAG_BLOCK_GRADS) && series_small(b) && !apply_streams(d, m) && !fma_apply_left_preferred(m, d->n_tokens, b) &&
+         edge_apply_joins_blockgrads(d->dtype, m, d->n_tokens, n, m, d->n_tokens, b);
+}
+
+// dB = P dZ, dA = W^T dB, dX = R dA (unless it is joined); ws holds dB (and the dequantised weight behind it)
 static void bwd_input_impl(const poetx_linear_desc* desc, const Act& dZ, const void* W, const int32_t* perm_R,
                            const int32_t* perm_P, const void* blocks_R, const void* blocks_P, const Act& dX, const Act& dA,
-                           void* ws, hipStream_t st, const void* W_resolved = nullptr) {
+                           void* ws, hipStream_t st, const void* W_resolved = nullptr, bool joined = false) {
   const int m = desc->d_in, n = desc->d_out;
   const i64 Ni = internal_columns(desc);
   const Act dB{ws, Ni, Ni};
@@ -622,7 +633,7 @@ static void bwd_input_impl(const poetx_linear_desc* desc, const Act& dZ, const v
   W = W_resolved ? W_resolved : resolve_weight(desc, W, after, st);
   apply_left(desc, dZ, dB, n, perm_P, blocks_P, 0, st);  // dB = P dZ
   dense_dispatch(desc, 1, W, dB, dA, after + dequantised_weight_bytes(desc), st, weight_in_kernel(desc));   // dA = W^T dB
-  apply_left(desc, dA, dX, m, perm_R, blocks_R, 0, st);  // dX = R dA
+  if (!joined) apply_left(desc, dA, dX, m, perm_R, blocks_R, 0, st);  // dX = R dA
 }
 
 int poetx_linear_bwd_input(const poetx_linear_desc* desc, const void* dZ, const void* W, const int32_t* perm_R,
@@ -653,7 +664,7 @@ static void cnp_bwd_both(const float* theta_R, const float* theta_P, float* dG, 
 static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act& dZ, const Act& saved_B,
                           const Act& dA, const int32_t* perm_R, const int32_t* perm_P, const float* theta_R,
                           const float* theta_P, float* dtheta_R, float* dtheta_P, int32_t accumulate, void* ws,
-                          hipStream_t st) {
+                          hipStream_t st, const JoinedApply* joined = nullptr) {
   const int m = desc->d_in, n = desc->d_out, b = desc->block, dt = desc->dtype, k = desc->neumann_k;
   const int dmax = m > n ? m : n;
   void* bg_ws = (char*)ws + align256(cnp_bwd_ws_floats(desc) * sizeof(float));
@@ -689,7 +700,11 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
       const GradProblem gp = grad_problem(desc, saved_B, dZ, n, perm_P, (float*)sides[0].dG), gr = grad_problem(desc, X, dA, m, perm_R, (float*)sides[1].dG);
-      edge_blockgrad_parts_pair(dt, gp, gr, b, &sides[0].nsplit, &sides[1].nsplit, st);
+      if (joined)
+        edge_apply_blockgrad_parts(dt, dA.p, dA.ld, joined->dX.out(), joined->dX.ld, min64(dA.cols, joined->dX.cols), joined->dX.cols, desc->n_tokens, joined->blocks_R, gp, gr, b,
+                                   &sides[0].nsplit, &sides[1].nsplit, st);
+      else
+        edge_blockgrad_parts_pair(dt, gp, gr, b, &sides[0].nsplit, &sides[1].nsplit, st);
     }
     StageTimer tm(POETX_STAGE_CNP_BWD, st);
     series_small_bwd(sides, 2, b, k, accumulate != 0, st);
@@ -777,8 +792,10 @@ int poetx_linear_bwd(const poetx_linear_desc* desc, const void* X, const void* d
   const bool one_pass = bwd_one_pass(desc) && aligned16(dz.p) && aligned16(B.p) && aligned16(x.p) && aligned16(dx.p) && aligned16(blocks_R) &&
                         aligned16(blocks_P);
   if (!one_pass) {   // the same values through the two halves
-    bwd_input_impl(desc, dz, W, perm_R, perm_P, blocks_R, blocks_P, dx, dA, rest, st, W_resolved);
-    bwd_skew_impl(desc, x, dz, B, dA, perm_R, perm_P, theta_R, theta_P, dtheta_R, dtheta_P, accumulate, rest, st);
+    const JoinedApply join{blocks_R, dx};
+    const bool joined = joins_apply(desc);
+    bwd_input_impl(desc, dz, W, perm_R, perm_P, blocks_R, blocks_P, dx, dA, rest, st, W_resolved, joined);
+    bwd_skew_impl(desc, x, dz, B, dA, perm_R, perm_P, theta_R, theta_P, dtheta_R, dtheta_P, accumulate, rest, st, joined ? &join : nullptr);
     lay.finish();
     return launch_status();
   }

@@ -69,6 +69,10 @@ size_t edge_blockgrad_parts_bytes(int dtype, int d, i64 N, int b);
 int edge_blockgrad_parts(int dtype, const GradProblem& q, int b, hipStream_t st);
 // both sides of a layer, in one launch where their plans allow
 void edge_blockgrad_parts_pair(int dtype, const GradProblem& q0, const GradProblem& q1, int b, int* n0, int* n1, hipStream_t st);
+// ... and, in the same launch, out = op(blocks) V on q1's side: where the first says so
+bool edge_apply_joins_blockgrads(int dtype, int d_apply, i64 plan_cols, int d0, int d1, i64 N, int b);
+void edge_apply_blockgrad_parts(int dtype, const void* V, i64 ldv, void* out, i64 ldo, i64 cols, i64 cols_out, i64 plan_cols, const void* blocks, const GradProblem& q0,
+                                const GradProblem& q1, int b, int* n0, int* n1, hipStream_t st);
 
 // ---- the forward of up to 32 bf16 tokens (few_tokens.hip); tensors of any alignment ----------
 bool few_tokens_supported(int n, int m, int b, i64 N);

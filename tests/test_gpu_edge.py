@@ -427,6 +427,43 @@ def test_sliced_dense_products(lib, dtype, n, m, N):
         assert rel_err(here, general) <= tol
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,n,N,b", [
+    (256, 256, 512, 32),      # whole tiles throughout, apply on 32 x 32
+    (512, 1376, 1024, 64),    # a ragged last block on one side only
+    (768, 1024, 1001, 64),    # apply on 64 x 64, tails
+    (384, 256, 30, 128),      # stages of half a block, fewer tokens than a tile
+    (130, 75, 5, 65),         # last blocks of one row and of ten, rows shorter than a vector
+    (2048, 64, 4096, 64),     # 64 x 64 gradients: two launches
+])
+def test_apply_and_block_gradients_in_one_launch(lib, m, n, N, b, dtype):
+    """The one-call backward of small blocks launches dX = R dA and both block gradients together where their tiles allow it: the same tiles, so the same bits as the two halves."""
+    rng = np.random.Generator(np.random.PCG64(9950 + m + n + N + b))
+    dt, k = tdtype(dtype), 3
+    code = lib.F32 if dtype == "f32" else lib.BF16
+    t = lambda *shape: torch.from_numpy(rng.standard_normal(shape)).to("cuda", dt)
+    X, dZ, B, W = t(m, N), t(n, N), t(n, N), t(n, m) * 0.02
+    nR, nP = -(-m // b), -(-n // b)
+    pi = [torch.from_numpy(rng.permutation(d).astype(np.int32)).cuda() for d in (m, n)]
+    blk = [t(nb, b, b) * 0.1 if dtype == "f32" else t(nb, 2, b, b) * 0.1 for nb in (nR, nP)]
+    th = [torch.from_numpy(rng.standard_normal((nb, b * (b - 1) // 2)) * 0.01).to("cuda", torch.float32) for nb in (nR, nP)]
+    desc = lib.make_desc(m, n, b, k, N, code)
+    got = []
+    for one in (True, False):
+        ws = torch.full((lib.poetx_linear_workspace_bytes(desc) // 4,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
+        dX, dA = torch.full_like(X, float("nan")), torch.empty_like(X)
+        dth = [torch.full_like(x, float("nan")) for x in th]
+        if one:
+            lib.poetx_linear_bwd(desc, X, dZ, B, W, *pi, *blk, *th, dX, *dth, False, ws)
+        else:
+            lib.poetx_linear_bwd_input(desc, dZ, W, *pi, *blk, dX, dA, ws)
+            lib.poetx_linear_bwd_skew(desc, X, dZ, B, dA, *pi, *th, *dth, False, ws)
+        torch.cuda.synchronize()
+        got.append((dX, *dth))
+    for one, two in zip(*got):
+        assert torch.all(torch.isfinite(one)) and torch.equal(one, two)
+
+
 @pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 40, (3,)), (512, 130, (3,)), (256, 130, (2,)), (256, 150, (2,)), (256, 3, (1, 2, 7)), (256, 9, (1, 5)), (256, 200, (4,))])
 def test_matrix_core_series(lib, b, nb, ks):
     """The bf16 series of large blocks, build and backward through poetx_cnp_build / poetx_cnp_bwd: every shape of the

@@ -302,8 +302,8 @@ size_t poetx_linear_workspace_bytes(const poetx_linear_desc* desc);
  * assumed).  Returns a combination of POETX_PATH_* bits, 0 when every stage runs on the edge-handling,
  * few-token or plain kernels, or minus a poetx_status when the descriptor is invalid. */
 #define POETX_PATH_APPLY 1              /* gather + block-diagonal product + scatter, both sides */
-#define POETX_PATH_DENSE 2              /* both B = W A and dA = W^T dB (the only bit fp32 tensors get) */
-#define POETX_PATH_BLOCKGRAD 4          /* block gradients (two-call backward)                 */
+#define POETX_PATH_DENSE 2              /* both B = W A and dA = W^T dB (the only bit fp32 tensors get: whole 128-wide tiles that fill the chip) */
+#define POETX_PATH_BLOCKGRAD 4          /* block gradients (two-call backward): token counts whole; short streams take the edge-handling kernel */
 #define POETX_PATH_SERIES 8             /* series backward on the matrix cores                 */
 #define POETX_PATH_SERIES_ON_CHIP 16    /* ... as one-launch chains (b = 256)                   */
 #define POETX_PATH_BWD_ONE_PASS 32      /* poetx_linear_bwd streams each side's gradient once  */

@@ -271,6 +271,27 @@ __global__ __launch_bounds__(256) void edge_reduce_kernel(const float* __restric
   }
 }
 
+// The same for two sums of whole vectors, n0 the number of workgroups of the first
+struct ReduceSide {
+  const float* part;
+  float* out;
+  i64 total;
+  int splits;
+};
+__global__ __launch_bounds__(256) void edge_reduce_pair_kernel(ReduceSide s0, ReduceSide s1, int n0) {
+  const bool second = (int)blockIdx.x >= n0;
+  const ReduceSide s = second ? s1 : s0;
+  const i64 e = ((i64)(blockIdx.x - (second ? n0 : 0)) * 256 + threadIdx.x) * 4;
+  if (e >= s.total) return;
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int z = 0; z < s.splits; ++z) {
+    const float4 p = *reinterpret_cast<const float4*>(s.part + z * s.total + e);
+    v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+  }
+  typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));   // out may be the caller's
+  *reinterpret_cast<f4*>(s.out + e) = f4{v.x, v.y, v.z, v.w};
+}
+
 template <class T>
 void reduce(const float* part, i64 M, i64 N, int splits, T* out, i64 ld, hipStream_t st) {
   hipLaunchKernelGGL(edge_reduce_kernel<T>, dim3((unsigned)((M * N + 1023) / 1024)), dim3(256), 0, st, part, M * N, splits, out, (int)N, ld);
@@ -510,6 +531,21 @@ void edge_apply_blockgrad_parts(int dtype, const void* V, i64 ldv, void* out, i6
 
 size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b) {
   return grad_plan(dtype, d, N, b).splits > 1 ? edge_blockgrad_parts_bytes(dtype, d, N, b) : 0;
+}
+
+// Both sides: one launch (where their tiles are the same) and one that adds the parts of both.  Parts of a side lie behind each other in ws, whole vectors (b * b a multiple of four).
+size_t edge_blockgrad_pair_workspace_bytes(int dtype, int d0, int d1, i64 N, int b) {
+  return align256(edge_blockgrad_workspace_bytes(dtype, d0, N, b)) + align256(edge_blockgrad_workspace_bytes(dtype, d1, N, b));
+}
+void edge_blockgrad_pair(int dtype, GradProblem q0, GradProblem q1, int b, float* dG0, float* dG1, void* ws, hipStream_t st) {
+  const bool split0 = grad_plan(dtype, q0.d, q0.N, b).splits > 1, split1 = grad_plan(dtype, q1.d, q1.N, b).splits > 1;
+  q0.parts = split0 ? (float*)ws : dG0;
+  q1.parts = split1 ? (float*)((char*)ws + align256(edge_blockgrad_workspace_bytes(dtype, q0.d, q0.N, b))) : dG1;
+  int n0 = 1, n1 = 1;
+  edge_blockgrad_parts_pair(dtype, q0, q1, b, &n0, &n1, st);
+  const ReduceSide s0{q0.parts, dG0, split0 ? (i64)ceil_div(q0.d, b) * b * b : 0, n0}, s1{q1.parts, dG1, split1 ? (i64)ceil_div(q1.d, b) * b * b : 0, n1};
+  const int w0 = ceil_div(s0.total, 1024), w1 = ceil_div(s1.total, 1024);
+  if (w0 + w1 > 0) hipLaunchKernelGGL(edge_reduce_pair_kernel, dim3((unsigned)(w0 + w1)), dim3(256), 0, st, s0, s1, w0);
 }
 
 void edge_blockgrad(int dtype, GradProblem q, int b, float* dG, void* ws, hipStream_t st) {

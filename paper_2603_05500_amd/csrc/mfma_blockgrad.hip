@@ -48,6 +48,12 @@ bool mfma_blockgrad_supported(int d, i64 N, int b) {
   return (b == 256 || b == 512) && d % b == 0 && N % GBK == 0 && N >= 4 * GBK && N < (1ll << 31);
 }
 
+// The 256 x 256 tiles read every row once (b = 256) or twice and leave most CUs without one until there are many tokens; the edge kernel's 128 x 128 tiles with a split per
+// 256 tokens read twice as much.  us for two sides, here / edge kernel: b = 256: 1024 features, 256 tokens 29.8 / 7.9, 4096 56.9 / 39.6; 4096 features, 2048 tokens 54 / 47,
+// 8192 (2^25 elements) 107 / 88, 16384 166 / 182; 14336, 4096 155 / 153; b = 512: 1024, 256 31.0 / 8.9; 4096, 4096 84 / 76; 2048, 16384 126 / 128; 8192, 4096 (both 2^25) 130 / 139,
+// 16384 372 / 424.
+bool mfma_blockgrad_preferred(int d, i64 N, int b) { return mfma_blockgrad_supported(d, N, b) && (i64)d * N + (b == 512) > 1 << 25; }
+
 size_t mfma_blockgrad_workspace_bytes(int d, i64 N, int b) {
   return (size_t)pick_splits(d, N, b) * d * b * sizeof(float);
 }

@@ -159,10 +159,12 @@ void apply_left(const poetx_linear_desc* desc, const Act& V, const Act& out, int
   apply_left_dispatch(desc->dtype, V, out, d, perm, blocks, desc->block, trans, apply_streams(desc, d), desc->n_tokens, st);
 }
 
-// Does poetx_linear_bwd stream each side's gradient once (aligned tensors)?
+// Does poetx_linear_bwd stream each side's gradient once (aligned tensors)?  Not a short stream: the two halves' smaller tiles and both gradients in a launch are sooner done.  us without
+// the series, one pass / two halves: 1024 x 1024, 256 tokens 37 / 30, 2048 55 / 44, 4096 (2^23 elements) 62 / 57, 8192 81 / 90; 2048 x 2048, 1024 58 / 49; 4096 x 4096, 512 68 / 58,
+// 2048 111 / 125; 4096 x 1024, 768 64 / 54; 8192 x 4096, 512 84 / 84, 768 103 / 108.
 bool bwd_one_pass(const poetx_linear_desc* d) {
   const i64 N = d->n_tokens;
-  return d->cnp_precision == POETX_CNP_BF16 && use_mfma(d->dtype) && lds_cnp_supported(d->d_in, d->block) && lds_cnp_supported(d->d_out, d->block) &&
+  return (d->d_in + (i64)d->d_out) * N > 1 << 23 && d->cnp_precision == POETX_CNP_BF16 && use_mfma(d->dtype) && lds_cnp_supported(d->d_in, d->block) && lds_cnp_supported(d->d_out, d->block) &&
          internal_columns(d) == N && mfma_apply_grad_supported(d->d_in, N, N, d->block) && mfma_apply_grad_supported(d->d_out, N, N, d->block);
 }
 
@@ -201,13 +203,14 @@ void few_b(const poetx_linear_desc* d, const void* X, const void* W, const int32
 // Block gradients are summed over exactly the call's tokens, never over padding, by kernels that follow from the descriptor: the
 // order of the sum is the same in either layout and with B kept or recomputed, whichever of the tensors have padded columns.
 // Only the pointers' alignment can change the kernel, which a workspace query does not see: it covers both.
-size_t blockgrad_ws_bytes(const poetx_linear_desc* d, int dim) {
+size_t blockgrad_ws_bytes(const poetx_linear_desc* d) {
   const i64 N = d->n_tokens;
-  size_t w = edge_blockgrad_workspace_bytes(d->dtype, dim, N, d->block);
-  if (d->dtype == POETX_BF16 && mfma_blockgrad_supported(dim, N, d->block)) {
-    const size_t f = mfma_blockgrad_workspace_bytes(dim, N, d->block);
-    if (f > w) w = f;
-  }
+  size_t w = edge_blockgrad_pair_workspace_bytes(d->dtype, d->d_out, d->d_in, N, d->block);
+  for (const int dim : {d->d_in, d->d_out})
+    if (d->dtype == POETX_BF16 && mfma_blockgrad_preferred(dim, N, d->block)) {
+      const size_t f = mfma_blockgrad_workspace_bytes(dim, N, d->block);
+      if (f > w) w = f;
+    }
   return align256(w);
 }
 // both sides' block gradients as parts, for the one-launch series backward of small blocks
@@ -233,10 +236,13 @@ size_t dense_part_bytes(const poetx_linear_desc* d) {
 GradProblem grad_problem(const poetx_linear_desc* desc, const Act& U, const Act& V, int d, const int32_t* perm, float* parts = nullptr) {
   return GradProblem{U.p, V.p, U.ld, U.cols, V.ld, V.cols, desc->n_tokens, d, perm, parts};
 }
+bool blockgrad_streams(const poetx_linear_desc* desc, const Act& U, const Act& V, int d) {   // N in whole vectors, hence the row strides too
+  return use_mfma(desc->dtype) && mfma_blockgrad_preferred(d, desc->n_tokens, desc->block) && aligned16(U.p) && aligned16(V.p);
+}
 void blockgrad_dispatch(const poetx_linear_desc* desc, const Act& U, const Act& V, int d, const int32_t* perm, float* dG, void* ws, hipStream_t st) {
   const int dtype = desc->dtype, b = desc->block;
   const i64 N = desc->n_tokens;
-  if (use_mfma(dtype) && mfma_blockgrad_supported(d, N, b) && aligned16(U.p) && aligned16(V.p))   // N in whole vectors, hence the row strides too
+  if (blockgrad_streams(desc, U, V, d))
     mfma_blockgrad(U.p, U.ld, V.p, V.ld, d, N, perm, b, dG, ws, st);
   else if (!g_force_fma.load()) edge_blockgrad(dtype, grad_problem(desc, U, V, d, perm), b, dG, ws, st);
   else fma_blockgrad(dtype, U.p, V.p, d, N, perm, b, dG, st);
@@ -515,9 +521,7 @@ static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
   const size_t part = dense_part_bytes(desc);
   fwd += wdeq + part;                                   // dequantised weight behind A (and B), then the dense product's partials
   size_t bwi = actn + wdeq + part;                      // dB = P dZ
-  size_t bg_in = blockgrad_ws_bytes(desc, desc->d_in);
-  size_t bg_out = blockgrad_ws_bytes(desc, desc->d_out);
-  const size_t bg = bg_in > bg_out ? bg_in : bg_out;
+  const size_t bg = blockgrad_ws_bytes(desc);
   const size_t chain = cnp_bwd_ws_floats(desc);
   size_t skew = align256(chain * sizeof(float)) + bg;
   const size_t parts = blockgrad_parts_bytes(desc, desc->d_in) + blockgrad_parts_bytes(desc, desc->d_out);
@@ -678,17 +682,17 @@ static void bwd_skew_impl(const poetx_linear_desc* desc, const Act& X, const Act
     const int nbP = n / b;
     const size_t bb = (size_t)b * b;
     float* dG = (float*)ws;                                   // [nbt][b][b]
-    if (defer) {
-      StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      blockgrad_dispatch(desc, saved_B, dZ, n, perm_P, dtheta_P, bg_ws, st);
-      blockgrad_dispatch(desc, X, dA, m, perm_R, dtheta_R, bg_ws, st);
-      return;
-    }
     {
       StageTimer tm(POETX_STAGE_BLOCKGRAD, st);
-      blockgrad_dispatch(desc, saved_B, dZ, n, perm_P, dG, bg_ws, st);            // dG_P = B' dZ'^T
-      blockgrad_dispatch(desc, X, dA, m, perm_R, dG + nbP * bb, bg_ws, st);       // dG_R = X' dA'^T
+      float *dG_P = defer ? dtheta_P : dG, *dG_R = defer ? dtheta_R : dG + nbP * bb;   // B' dZ'^T, X' dA'^T
+      if (blockgrad_streams(desc, saved_B, dZ, n) || blockgrad_streams(desc, X, dA, m)) {
+        blockgrad_dispatch(desc, saved_B, dZ, n, perm_P, dG_P, bg_ws, st);
+        blockgrad_dispatch(desc, X, dA, m, perm_R, dG_R, bg_ws, st);
+      } else {
+        edge_blockgrad_pair(dt, grad_problem(desc, saved_B, dZ, n, perm_P), grad_problem(desc, X, dA, m, perm_R), b, dG_P, dG_R, bg_ws, st);
+      }
     }
+    if (defer) return;
     cnp_bwd_both(theta_R, theta_P, dG, m, n, b, k, dtheta_R, dtheta_P, accumulate, st);
     return;
   }

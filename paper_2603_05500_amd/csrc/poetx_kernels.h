@@ -64,6 +64,9 @@ struct GradProblem {
 };
 size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b);
 void edge_blockgrad(int dtype, GradProblem q, int b, float* dG, void* ws, hipStream_t st);   // summed up (parts is not used)
+// both sides of a layer (b * b a multiple of four)
+size_t edge_blockgrad_pair_workspace_bytes(int dtype, int d0, int d1, i64 N, int b);
+void edge_blockgrad_pair(int dtype, GradProblem q0, GradProblem q1, int b, float* dG0, float* dG1, void* ws, hipStream_t st);
 // The same, left as its parts; returns how many.
 size_t edge_blockgrad_parts_bytes(int dtype, int d, i64 N, int b);
 int edge_blockgrad_parts(int dtype, const GradProblem& q, int b, hipStream_t st);
@@ -134,6 +137,7 @@ bool mfma_apply_left_ragged_supported(int d, i64 cols_out, int b);
 void mfma_apply_left_ragged(const void* V, i64 ldv, i64 cols, void* out, i64 ldo, i64 cols_out, int d, const int32_t* perm, const void* E, int b,
                             int transpose_G, hipStream_t st);
 bool mfma_blockgrad_supported(int d, i64 N, int b);
+bool mfma_blockgrad_preferred(int d, i64 N, int b);   // ... and large enough for it
 size_t mfma_blockgrad_workspace_bytes(int d, i64 N, int b);
 // U and V: d rows of at least N tokens, row strides multiples of 8
 void mfma_blockgrad(const void* U, i64 ldu, const void* V, i64 ldv, int d, i64 N, const int32_t* perm, int b, float* dG, void* ws, hipStream_t st);

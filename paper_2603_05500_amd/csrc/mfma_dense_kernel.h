@@ -20,7 +20,7 @@
 //
 // What bounds it is power: the clock falls until the chip keeps its limit, so what counts is energy per flop.  A loop of MFMAs alone on normally
 // distributed operands sustains 2.04 PFLOP/s with 16 x 16 x 32 and 1.77 with 32 x 32 x 16 (an accumulator is read and written
-// once per 32 of depth, not per 16; on zeros both reach 2.45).  The same stream on 32 x 32 x 16, before / now, us, sustained: forward 4096 x 4096 x 16384 413 / 374,
+// once per 32 of depth, not per 16; on zeros both reach 2.45).  The same stream on 32 x 32 x 16, before / now, us, sustained (smaller tiles without WIDE, see below): forward 4096 x 4096 x 16384 413 / 374,
 // 14336 x 4096 x 16384 1420 / 1290; backward 400 / 369, 1405 / 1270; tiles of 256 x 128, 4096 x 4096 x 2048: 67 / 64.7 and 62.8 / 59; of 128 x 128, 2048 x 5632 x 2048:
 // 51.8 / 50.9 and 50.8 / 49.
 #pragma once
@@ -154,6 +154,13 @@ template <bool A_KMAJOR, Out OUT = OUT_WHOLE, int DIAG = 0, class C = Tile256>
 __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   constexpr int BM = C::BM, BN = C::BN, NS = C::NS, A_BYTES = C::A_BYTES, STAGE_BYTES = C::STAGE_BYTES, OUT_BYTES = C::OUT_BYTES;
   constexpr int IPWA = C::IPWA, IPWB = C::IPWB, LPT = C::LPT, TM = C::TM, TN = C::TN, MF = C::MF, RS = C::RS, DS = C::DS;
+  // WIDE: rows of a K-major A come 64 deep, whole 128-byte lines.  Two stages share a unit of A, which arrives in two halves of its rows, one per stage and one
+  // stage later than B's tile of the same number (a unit is needed as a whole, and its slot is free, when its first stage is): the last half is in flight for NS - 3 stages, so
+  // the ring has to be deep.  With 64-byte pieces every line is asked for twice; us, forward, weights from memory, 64 / 128 bytes:
+  // 256 x 128 tiles, 4096 x 4096 x 2048 78.7 / 62; 128 x 128, 2048 x 5632 x 2048 69.5 / 55.
+  constexpr bool WIDE = A_KMAJOR && NS >= 6;
+  constexpr int A_STRIDE = WIDE ? A_BYTES : STAGE_BYTES, B_STRIDE = WIDE ? C::B_BYTES : STAGE_BYTES, B_BASE = WIDE ? NS * A_BYTES : A_BYTES;
+  static_assert(!WIDE || NS % 2 == 0, "whole units");
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -194,7 +201,10 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
 #pragma unroll
   for (int s = 0; s < IPWA; ++s) {
     const int slot = (wave * IPWA + s) * 64 + lane;
-    if (A_KMAJOR) {
+    if (WIDE) {
+      const int r = slot >> 3, c = (slot & 7) ^ ((r >> 1) & 7);
+      voffA[s] = (uint32_t)((r * g.lda + c * 8) * 2) - s * 1024;
+    } else if (A_KMAJOR) {
       const int r = slot >> 2, c = xk16_chunk(slot & 3, r);
       voffA[s] = (uint32_t)((r * g.lda + c * 8) * 2) - s * 1024;
     } else {
@@ -217,7 +227,8 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   // starts, so that moving on is a choice between two values.  Past the last stage of the last tile the stream fetches that tile
   // from its start again: the number of loads in flight -- and with it the vmcnt bound of the barrier -- never changes.
   const char *Ab, *Bb, *An, *Bn;
-  int ikt = 0, islot = 0;
+  int ikt = 0, islot = 0, iah = 0, iaslot = 0;      // iah, iaslot: WIDE, half of a unit in issue and where it goes
+  const i64 half_rows = (i64)(BM / 2) * g.lda * 2;
   auto tile_base = [&](int ti, const char*& a, const char*& b) {
     int i0, j0, split;
     tile_origin(ti < n_my ? ti : n_my - 1, i0, j0, split);
@@ -227,15 +238,22 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   tile_base(0, Ab, Bb);
   tile_base(1, An, Bn);
   bool loads_on = true;   // DIAG bit 0 switches it off after the prologue
-  auto issue_a = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Ab, voffA[s], lds_base + islot * STAGE_BYTES + wave * IPWA * 1024); };
-  auto issue_b = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Bb, voffB[s], lds_base + islot * STAGE_BYTES + A_BYTES + wave * IPWB * 1024); };
+  auto issue_a = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Ab, voffA[s], lds_base + (WIDE ? iaslot : islot) * A_STRIDE + wave * IPWA * 1024); };
+  auto issue_b = [&](int s) { if (!(DIAG & 1) || loads_on) dma16g_s(s, Bb, voffB[s], lds_base + islot * B_STRIDE + B_BASE + wave * IPWB * 1024); };
   auto issue_advance = [&]() {
     islot = islot + 1 == NS ? 0 : islot + 1;
     if (DIAG & 4) return;   // every stage re-fetches the first one: the loads stay, their misses go
     const bool last = ikt + 1 == KT;
     ikt = last ? 0 : ikt + 1;
-    Ab = last ? An : Ab + stepA;
+    if (!WIDE) Ab = last ? An : Ab + stepA;
     Bb = last ? Bn : Bb + stepB;
+  };
+  auto a_half_advance = [&](bool second) {      // WIDE: from half `second` of a unit to the next
+    iaslot = iaslot + 1 == NS ? 0 : iaslot + 1;
+    const bool last = iah + 1 == KT;
+    iah = last ? 0 : iah + 1;
+    if (!second) Ab += half_rows;
+    else Ab = last ? An : Ab + (2 * stepA - half_rows);
   };
 
   // ---- LDS byte offsets of this lane's fragments inside a stage: row (column) lane & 15 of a 16-wide piece, k = 8 (lane >> 4) .. + 7
@@ -246,7 +264,10 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
 #pragma unroll
     for (int a = 0; a < TM; ++a) {
       const int x0 = wm * (BM / 2) + a * 16;
-      if (A_KMAJOR) {
+      if (WIDE) {
+        const int r = x0 + i;
+        fragA[a] = r * 128 + 16 * (q ^ ((r >> 1) & 7));      // of a unit's first stage; the second's chunks are 4 further, bit 2 of the position
+      } else if (A_KMAJOR) {
         const int r = x0 + i;
         fragA[a] = r * 64 + 16 * xk16_chunk(q, r);
       } else {
@@ -256,7 +277,7 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
 #pragma unroll
     for (int c2 = 0; c2 < TN; ++c2) {
       const int x0 = wn * (BN / 2) + c2 * 16;
-      fragB[c2] = A_BYTES + k * (BN * 2) + 16 * kx16_chunk((x0 >> 3) + ((i & 3) >> 1), k) + 8 * (i & 1);
+      fragB[c2] = B_BASE + k * (BN * 2) + 16 * kx16_chunk((x0 >> 3) + ((i & 3) >> 1), k) + 8 * (i & 1);
     }
   }
 
@@ -276,30 +297,35 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
     bf16x8 a[TM], b[TN];
   };
   // piece p of a stage's fragments, in the order the MFMAs first need them: A0 B0 A1 .. A(TM-1) B1 .. B(TN-1)
-  auto load_piece = [&](Frags& f, const char* stage, int p) {
-    if (p == 1) f.b[0] = load_frag(stage + fragB[0], false, BN * 2);
-    else if (p <= TM) f.a[p ? p - 1 : 0] = load_frag(stage + fragA[p ? p - 1 : 0], A_KMAJOR, BM * 2);
-    else f.b[p - TM] = load_frag(stage + fragB[p - TM], false, BN * 2);
+  auto load_piece = [&](Frags& f, int slot, bool odd, int p) {      // odd: the second stage of a unit
+    const char* sa = lds + (WIDE && odd ? slot - 1 : slot) * A_STRIDE;
+    const char* sb = lds + slot * B_STRIDE;
+    if (p == 1) f.b[0] = load_frag(sb + fragB[0], false, BN * 2);
+    else if (p <= TM) f.a[p ? p - 1 : 0] = load_frag(sa + (WIDE && odd ? fragA[p ? p - 1 : 0] ^ 64 : fragA[p ? p - 1 : 0]), A_KMAJOR, BM * 2);
+    else f.b[p - TM] = load_frag(sb + fragB[p - TM], false, BN * 2);
   };
 
-  // ---- prologue: stages 0 .. NS-1
+  // ---- prologue: stages 0 .. NS-1 (WIDE: the halves of A up to NS-2), in the order of the loop
 #pragma unroll
   for (int t = 0; t < NS; ++t) {
+    if (!WIDE || t > 0) {
 #pragma unroll
-    for (int s = 0; s < IPWA; ++s) issue_a(s);
+      for (int s = 0; s < IPWA; ++s) issue_a(s);
+      if (WIDE) a_half_advance(t % 2 == 0);      // half t - 1
+    }
 #pragma unroll
     for (int s = 0; s < IPWB; ++s) issue_b(s);
     issue_advance();
   }
-  mm::wait_vmcnt_and_barrier<(NS - 1) * LPT>();   // stage 0 has landed
+  mm::wait_vmcnt_and_barrier<WIDE ? (NS - 3) * LPT + IPWB : (NS - 1) * LPT>();   // stage 0 (its unit) has landed
   Frags F, Gf;
   int cslot = 0;
 #pragma unroll
-  for (int p = 0; p < TM + TN; ++p) load_piece(F, lds, p);
+  for (int p = 0; p < TM + TN; ++p) load_piece(F, 0, false, p);
 
   if (DIAG & 2) {   // the loop reads no fragments: both sets come from the first stage
 #pragma unroll
-    for (int p = 0; p < TM + TN; ++p) load_piece(Gf, lds, p);
+    for (int p = 0; p < TM + TN; ++p) load_piece(Gf, 0, false, p);
   }
   loads_on = false;
   const int q4 = lane >> 4, li = lane & 15;
@@ -309,37 +335,45 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   auto run = [&](auto WC) {
     constexpr int W = decltype(WC)::value;
     // stage kt from X; the fragments of the next stage (the next tile's first one after the last one of this tile) into Y; stage kt + NS to issue
-    auto multiply = [&](const Frags& X, Frags& Y) {
+    auto multiply = [&](const Frags& X, Frags& Y, auto ODD) {
+      constexpr bool odd = decltype(ODD)::value;       // this stage is the second of a unit
       // Every wave holds this stage in registers (lgkmcnt(0)) and the next one has landed: stages up to kt + NS - 1 are issued, so at
       // most NS - 2 of them may be in flight.  Stores of a finished tile share the counter and only make this wait stricter.
-      mm::wait_all_reads_and_barrier<(NS - 2) * LPT>();
+      // WIDE, a new unit next: its second half was the first thing issued NS - 3 stages ago.
+      mm::wait_all_reads_and_barrier<WIDE && odd ? (NS - 4) * LPT + IPWB : (NS - 2) * LPT>();
       const int nslot = cslot + 1 == NS ? 0 : cslot + 1;
-      const char* nstage = lds + nslot * STAGE_BYTES;
 #pragma unroll
       for (int i = 0; i < MF; ++i) {
         // the operands go in swapped, so the accumulator tile is transposed: a lane owns one output row and four consecutive columns
         mfma16(acc[i % TM][i / TM], X.b[i / TM], X.a[i % TM]);
-        if (i % RS == 0 && i / RS < TM + TN && !(DIAG & 2)) load_piece(Y, nstage, i / RS);
+        if (i % RS == 0 && i / RS < TM + TN && !(DIAG & 2)) load_piece(Y, nslot, !odd, i / RS);
         if (i % DS == W * DS / 4 && i / DS < LPT) {
           if (i / DS < IPWA) issue_a(i / DS);
           else issue_b(i / DS - IPWA);
         }
-        if (i == MF - 1) issue_advance();
+        if (i == MF - 1) {
+          issue_advance();
+          if (WIDE) a_half_advance(!odd);      // half kt + NS - 1
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
       cslot = nslot;
     };
     for (int ti = 0; ti < n_my; ++ti) {
       // the tile after the one in issue, which is NS stages ahead: that of stage NS of this tile
-      if (ti > 0 || KT == NS) tile_base(ti + (KT > NS ? 1 : 2), An, Bn);   // KT >= 8 >= NS
+      if (ti > 0 || KT == NS) {      // KT >= 8 >= NS
+        const char* unused;
+        tile_base(ti + (KT > NS ? 1 : 2), An, Bn);
+        if (WIDE && KT == NS) tile_base(ti + 1, An, unused);      // A is a stage behind, in this tile still
+      }
       long long tc0 = 0, tc1 = 0, tr0 = 0, tr1 = 0;
       if ((DIAG & 8) && ti == 1) {
         tc0 = __builtin_readcyclecounter();
         tr0 = __builtin_amdgcn_s_memrealtime();
       }
       for (int kt = 0; kt < KT; kt += 2) {
-        multiply(F, Gf);
-        multiply(Gf, F);
+        multiply(F, Gf, std::false_type{});
+        multiply(Gf, F, std::true_type{});
       }
       if ((DIAG & 8) && ti == 1) {
         tc1 = __builtin_readcyclecounter();

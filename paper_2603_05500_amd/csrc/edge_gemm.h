@@ -514,31 +514,6 @@ bool whole_tiles(const Args& g) {
          N <= (B_K ? g.B.rows : g.B.cols) && K <= (B_K ? g.B.cols : g.B.rows);
 }
 
-template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi>
-void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, int s0, int s1, hipStream_t st) {
-  using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
-  tile_args(g0, q0, BM, BN, BK, s0);
-  tile_args(g1, q1, BM, BN, BK, s1);
-  const i64 n0 = q0.batches * g0.tiles_m * g0.tiles_n, n1 = q1.batches * g1.tiles_m * g1.tiles_n;
-  auto go = [&](auto kern) {
-    launch_in_rows(n0 + n1, [&](int first, unsigned count) {
-      hipLaunchKernelGGL(kern, dim3(count, (unsigned)(s0 > s1 ? s0 : s1)), dim3(S::THREADS), S::LDS, st, g0, g1, e0, e1, (int)n0, (int)(n0 + n1), first);
-    });
-  };
-  // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
-  if (whole_tiles<BM, BN, BK, A_K, B_K>(g0) && whole_tiles<BM, BN, BK, A_K, B_K>(g1)) {
-    auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, WHOLE>;
-    static const bool configured = lds_limit((const void*)kern, S::LDS);
-    (void)configured;
-    go(kern);
-  } else {
-    auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, BRANCHED>;
-    static const bool configured = lds_limit((const void*)kern, S::LDS);
-    (void)configured;
-    go(kern);
-  }
-}
-
 template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, Load LOAD = BRANCHED, class Epi>
 void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits, hipStream_t st) {
   using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
@@ -561,6 +536,38 @@ void launch_shape(Args g, Epi epi, i64 batches, i64 M, i64 N, i64 K, int splits,
   static const bool configured = lds_limit((const void*)kern, S::LDS);
   (void)configured;
   go(kern);
+}
+
+template <class T, int BM, int BN, int BK, int WGM, int WGN, int WAVES, bool A_K, bool B_K, class Epi>
+void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, const Problem& q1, int s0, int s1, hipStream_t st) {
+  using S = Shape<T, BM, BN, BK, WGM, WGN, WAVES>;
+  tile_args(g0, q0, BM, BN, BK, s0);
+  tile_args(g1, q1, BM, BN, BK, s1);
+  const i64 n0 = q0.batches * g0.tiles_m * g0.tiles_n, n1 = q1.batches * g1.tiles_m * g1.tiles_n;
+  const bool whole0 = whole_tiles<BM, BN, BK, A_K, B_K>(g0), whole1 = whole_tiles<BM, BN, BK, A_K, B_K>(g1);
+  // Only one of them whole and the chip full of either: each on its own kernel (gradients of 8192 and 3072 features, 4090 tokens, the latter's padded: 74 us together, 46 + 20 so)
+  if (whole0 != whole1 && n0 * s0 + n1 * s1 > 2 * kCUs) {
+    launch_shape<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K>(g0, e0, q0.batches, q0.M, q0.N, q0.K, s0, st);
+    launch_shape<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K>(g1, e1, q1.batches, q1.M, q1.N, q1.K, s1, st);
+    return;
+  }
+  auto go = [&](auto kern) {
+    launch_in_rows(n0 + n1, [&](int first, unsigned count) {
+      hipLaunchKernelGGL(kern, dim3(count, (unsigned)(s0 > s1 ? s0 : s1)), dim3(S::THREADS), S::LDS, st, g0, g1, e0, e1, (int)n0, (int)(n0 + n1), first);
+    });
+  };
+  // once per kernel instance; a function-local static is initialised exactly once, whichever thread gets there first
+  if (whole0 && whole1) {
+    auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, WHOLE>;
+    static const bool configured = lds_limit((const void*)kern, S::LDS);
+    (void)configured;
+    go(kern);
+  } else {
+    auto kern = edge_pair_kernel<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K, Epi, BRANCHED>;
+    static const bool configured = lds_limit((const void*)kern, S::LDS);
+    (void)configured;
+    go(kern);
+  }
 }
 
 // Applies on the smallest tile: the contraction is a block, and a stage no deeper than it (masked halves of a stage cost a launch

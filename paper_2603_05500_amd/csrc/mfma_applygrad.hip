@@ -20,6 +20,10 @@
 // rows x 32 bytes) and the row-wise reads (16 consecutive rows x 16 bytes) free of bank conflicts.
 // Each workgroup writes its partial block gradient once, at the end; a small kernel adds the
 // partials of a block in a fixed order (deterministic, no atomics).
+//
+// Where equal token ranges leave compute units idle (their number is nb times a power of two), long streams walk instead: the blocks' tiles lie
+// end to end and every pair of workgroups takes an equal share, over a block's border if need be, so all units end together
+// (grad_walks below says where).
 #include "mfma_gemm.h"
 
 namespace poetx {
@@ -54,10 +58,19 @@ struct GradArgs {
   const int32_t* perm;
   const uint16_t* blocks;   // bf16 pairs [nb][2][256][256]
   int trans;                // which member of the pair multiplies V
-  float* partial;           // [chunks][nb][256][256]
+  float* partial;           // [chunks][nb][256][256]; walking: a [256][256] per piece, piece (pair p, block j) at p + j
   int nb, tiles_per_wg, n_pairs;
+  int tiles, extra;         // walking: tiles of a block; the first `extra` pairs take tiles_per_wg + 1
 };
 
+// walking: first tile of pair p, and the pair of a tile (of all blocks: d N / 2^14, far below 2^31)
+__host__ __device__ inline int pair_start(int p, int share, int extra) { return p * share + (p < extra ? p : extra); }
+__host__ __device__ inline int pair_of(int tile, int share, int extra) {
+  const int wide = extra * (share + 1);
+  return tile < wide ? tile / (share + 1) : extra + (tile - wide) / share;
+}
+
+template <bool WALK>
 __global__ __launch_bounds__(512) void apply_grad_stream_kernel(GradArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char ring[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -65,14 +78,20 @@ __global__ __launch_bounds__(512) void apply_grad_stream_kernel(GradArgs g) {
   // workgroups go to the XCDs round robin: ids 8 apart are neighbours on one XCD
   const int id = blockIdx.x;
   const int half = (id >> 3) & 1;
-  const int pair = (id >> 4) * 8 + (id & 7);
+  // walking, an XCD takes consecutive pairs: those of a block share its operand there
+  const int pair = WALK ? (id & 7) * ((g.n_pairs + 7) / 8) + (id >> 4) : (id >> 4) * 8 + (id & 7);
   if (pair >= g.n_pairs) return;
-  const int j = pair % g.nb, chunk = pair / g.nb;
-  const i64 tok0 = (i64)chunk * g.tiles_per_wg * GBN;
-  const int32_t* pm = g.perm + (i64)j * GB;
   const int li = lane & 31, h = lane >> 5;
   const uint32_t ring_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
-  const int T = g.tiles_per_wg;
+  int at = WALK ? pair_start(pair, g.tiles_per_wg, g.extra) : 0;
+  const int end = WALK ? pair_start(pair + 1, g.tiles_per_wg, g.extra) : 0;
+  do {   // the tiles of one block at a time
+  const int j = WALK ? at / g.tiles : pair % g.nb;
+  const int tile0 = WALK ? at - j * g.tiles : pair / g.nb * g.tiles_per_wg;
+  const int T = !WALK ? g.tiles_per_wg : end - at < g.tiles - tile0 ? end - at : g.tiles - tile0;
+  const i64 piece = WALK ? pair + j : pair;   // = chunk * nb + j
+  const i64 tok0 = (i64)tile0 * GBN;
+  const int32_t* pm = g.perm + (i64)j * GB;
 
   // ---- direct-to-LDS loads: V instruction s of wave w fills chunk slots [(4w+s)*64, +64) of the V
   // part (8 rows of 8 chunks), U instruction s fills [(2w+s)*64, +64) of the U part
@@ -256,7 +275,7 @@ __global__ __launch_bounds__(512) void apply_grad_stream_kernel(GradArgs g) {
     // leaves the lower lanes with columns 8q .. 8q + 7 and the upper lanes with 8(q+1) .. 8(q+1) + 7:
     // every lane stores whole 32-byte sectors.
     typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-    float* P = g.partial + (((i64)chunk * g.nb + j) * GB + half * 128 + gw * 32 + li) * GB + 8 * h;
+    float* P = g.partial + (piece * GB + half * 128 + gw * 32 + li) * GB + 8 * h;
 #pragma unroll
     for (int ct = 0; ct < 8; ++ct)
 #pragma unroll
@@ -274,6 +293,11 @@ __global__ __launch_bounds__(512) void apply_grad_stream_kernel(GradArgs g) {
         *reinterpret_cast<float4*>(P + ct * 32 + 8 * q + 4) = make_float4(hi[0], hi[1], hi[2], hi[3]);
       }
   }
+  if constexpr (WALK) {
+    at += T;
+    if (at < end) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // every wave is done with the ring
+  }
+  } while (WALK && at < end);
 }
 
 __global__ void reduce_grad_partials_kernel(const float4* __restrict__ part, float4* __restrict__ out, i64 n4, int chunks) {
@@ -285,6 +309,19 @@ __global__ void reduce_grad_partials_kernel(const float4* __restrict__ part, flo
     s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
   }
   out[idx] = s;
+}
+
+// walking: a workgroup adds the pieces of 256 float4 of one block, in token order
+__global__ void reduce_grad_pieces_kernel(const float4* __restrict__ part, float4* __restrict__ out, int tiles, int share, int extra) {
+  constexpr int N4 = GB * GB / 4;
+  const int j = blockIdx.x / (N4 / 256), idx = blockIdx.x % (N4 / 256) * 256 + threadIdx.x;
+  const int first = pair_of(j * tiles, share, extra), last = pair_of((j + 1) * tiles - 1, share, extra);
+  float4 s = part[(i64)(first + j) * N4 + idx];
+  for (int p = first + 1; p <= last; ++p) {
+    const float4 v = part[(i64)(p + j) * N4 + idx];
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  }
+  out[(i64)j * N4 + idx] = s;
 }
 
 // token ranges per block: workgroups = 2 nb chunks; fill the CUs in whole rounds, keep at least
@@ -307,6 +344,17 @@ int grad_chunks(int nb, int tiles) {
   return best;
 }
 
+// Walking pairs: one per two CUs, or none.  A border costs a drained and refilled ring and a piece more to write and add up, so the walk pays for
+// shares of 20 tiles on where equal ranges keep less than 15/16 of the CUs busy.  Whole backward of d x 256, us, equal ranges / walking: 14336 features with 16384 tokens
+// (112 tiles a share) 585 / 545, 11008 with 8192 (43) 264 / 243, 5632 with 8192 (22) 147 / 141, 3072 with 16384 (24) 159 / 154; 14336 with 2048 (14) 94 / 106,
+// 3072 with 4096 (6) 65 / 71.
+constexpr int WALK_PAIRS = 128;
+bool grad_walks(int nb, int tiles) {
+  const i64 total = (i64)nb * tiles;
+  const int pairs = nb * grad_chunks(nb, tiles), rounds = (pairs + WALK_PAIRS - 1) / WALK_PAIRS;
+  return total >= 20 * WALK_PAIRS && total < (1ll << 31) && 16 * pairs < 15 * WALK_PAIRS * rounds;
+}
+
 }  // namespace
 
 bool mfma_apply_grad_supported(int d, i64 N, i64 ld, int b) {
@@ -314,13 +362,15 @@ bool mfma_apply_grad_supported(int d, i64 N, i64 ld, int b) {
 }
 
 size_t mfma_apply_grad_workspace_bytes(int d, i64 N) {
-  return (size_t)grad_chunks(d / GB, (int)(N / GBN)) * d * GB * sizeof(float);
+  const int nb = d / GB, tiles = (int)(N / GBN);
+  return (size_t)(grad_walks(nb, tiles) ? WALK_PAIRS + nb - 1 : grad_chunks(nb, tiles) * nb) * GB * GB * sizeof(float);
 }
 
 void mfma_apply_grad(const void* V, const void* U, void* out, int d, i64 N, i64 ld, const int32_t* perm, const void* E,
                      int transpose_G, float* dG, void* ws, hipStream_t st) {
   static const bool configured =
-      hipFuncSetAttribute((const void*)apply_grad_stream_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, G_LDS) == hipSuccess;
+      hipFuncSetAttribute((const void*)apply_grad_stream_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, G_LDS) == hipSuccess &&
+      hipFuncSetAttribute((const void*)apply_grad_stream_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, G_LDS) == hipSuccess;
   (void)configured;
   GradArgs g{};
   g.V = (const uint16_t*)V;
@@ -332,11 +382,22 @@ void mfma_apply_grad(const void* V, const void* U, void* out, int d, i64 N, i64 
   g.trans = transpose_G;
   g.nb = d / GB;
   const int tiles = (int)(N / GBN), chunks = grad_chunks(g.nb, tiles);
+  if (grad_walks(g.nb, tiles)) {
+    g.tiles = tiles;
+    g.n_pairs = WALK_PAIRS;
+    g.tiles_per_wg = g.nb * tiles / WALK_PAIRS;
+    g.extra = g.nb * tiles % WALK_PAIRS;
+    g.partial = (float*)ws;
+    hipLaunchKernelGGL(apply_grad_stream_kernel<true>, dim3(2 * WALK_PAIRS), dim3(512), G_LDS, st, g);
+    hipLaunchKernelGGL(reduce_grad_pieces_kernel, dim3(g.nb * (GB * GB / 1024)), dim3(256), 0, st, (const float4*)ws, (float4*)dG, tiles, g.tiles_per_wg,
+                       g.extra);
+    return;
+  }
   g.tiles_per_wg = tiles / chunks;
   g.n_pairs = g.nb * chunks;
   g.partial = chunks > 1 ? (float*)ws : dG;
   const int grid = ceil_div(g.n_pairs, 8) * 16;
-  hipLaunchKernelGGL(apply_grad_stream_kernel, dim3(grid), dim3(512), G_LDS, st, g);
+  hipLaunchKernelGGL(apply_grad_stream_kernel<false>, dim3(grid), dim3(512), G_LDS, st, g);
   if (chunks > 1) {
     const i64 n4 = (i64)d * GB / 4;
     hipLaunchKernelGGL(reduce_grad_partials_kernel, dim3(ceil_div(n4, 256)), dim3(256), 0, st, (const float4*)ws, (float4*)dG, n4, chunks);

@@ -464,6 +464,38 @@ def test_apply_and_block_gradients_in_one_launch(lib, m, n, N, b, dtype):
         assert torch.all(torch.isfinite(one)) and torch.equal(one, two)
 
 
+@pytest.mark.parametrize("m,n,N", [
+    (5376, 256, 7936),    # 21 blocks of 124 tiles over 128 pairs: shares of 20 and 21, borders anywhere in a share
+    (256, 33280, 1280),   # 130 blocks of 20 tiles: blocks that one pair covers whole, and a border at nearly every share
+    (2816, 2816, 16384),  # both sides, 11 blocks of 256 tiles: 22 a share
+])
+def test_block_stage_over_block_borders(lib, m, n, N):
+    """One-pass backward whose workgroups take equal shares of all blocks' tiles: the two halves' bits for dX, and every block gradient as its own sum in fp64."""
+    g = torch.Generator(device="cuda").manual_seed(9980 + m + n + N)
+    r = lambda *shape: torch.randn(*shape, device="cuda", dtype=torch.float32, generator=g).to(torch.bfloat16)
+    b = 256
+    X, dZ, B, W = r(m, N), r(n, N), r(n, N), r(n, m) * 0.02
+    pi = [torch.randperm(d, device="cuda", generator=g).to(torch.int32) for d in (m, n)]
+    blk = [r(d // b, 2, b, b) * 0.01 for d in (m, n)]
+    th = [torch.zeros(d // b, b * (b - 1) // 2, device="cuda") for d in (m, n)]
+    desc = lib.make_desc(m, n, b, 3, N, lib.BF16, flags=lib.FLAG_BLOCK_GRADS)
+    assert lib.poetx_linear_path(desc) & lib.PATH_BWD_ONE_PASS
+    ws = torch.full((lib.poetx_linear_workspace_bytes(desc) // 4,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
+    dX, dX2, dA = torch.full_like(X, float("nan")), torch.full_like(X, float("nan")), torch.empty_like(X)
+    dG = [torch.full((d // b, b, b), float("nan"), device="cuda") for d in (m, n)]
+    lib.poetx_linear_bwd(desc, X, dZ, B, W, *pi, *blk, *th, dX, *dG, False, ws)
+    lib.poetx_linear_bwd_input(desc, dZ, W, *pi, *blk, dX2, dA, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(dX, dX2)
+    for U, V, p, got in ((X, dA, pi[0], dG[0]), (B, dZ, pi[1], dG[1])):
+        p = p.long()
+        for j in range(got.shape[0]):
+            rows = p[j * b:(j + 1) * b]
+            ref = U[rows].double() @ V[rows].double().t()
+            # a sum of N products in fp32, each addition off by 2^-24 of what it adds to; they add up like a walk, at most by their number's root times 4
+            assert (got[j].double() - ref).abs().max() <= 4 * N ** 0.5 * 2.0 ** -24 * ref.abs().max()
+
+
 @pytest.mark.parametrize("b,nb,ks", [(512, 2, (1, 2, 3, 4, 5, 6)), (512, 40, (3,)), (512, 130, (3,)), (256, 130, (2,)), (256, 150, (2,)), (256, 3, (1, 2, 7)), (256, 9, (1, 5)), (256, 200, (4,))])
 def test_matrix_core_series(lib, b, nb, ks):
     """The bf16 series of large blocks, build and backward through poetx_cnp_build / poetx_cnp_bwd: every shape of the

@@ -329,10 +329,11 @@ __global__ void reduce_grad_pieces_kernel(const float4* __restrict__ part, float
 // Token chunks per half block.  More chunks fill the 256 CUs in whole rounds, but every chunk writes an
 // fp32 partial of its half block that the reduction reads again: the choice minimises the bytes moved,
 // with the three activation passes weighted by the share of the CUs that the workgroups keep busy.
-int grad_chunks(int nb, int tiles) {
+double grad_bytes(int nb, int tiles) { return 3.0 * nb * GB * (double)tiles * GBN * 2.0; }   // the three activation passes
+int grad_chunks(int nb, int tiles, double* cost_out = nullptr) {
   int best = 1;
   double best_cost = 0.0;
-  const double act = 3.0 * nb * GB * (double)tiles * GBN * 2.0;
+  const double act = grad_bytes(nb, tiles);
   for (int c = 1; c <= tiles; c *= 2) {
     if (tiles % c != 0 || tiles / c < 4) break;
     const double wgs = 2.0 * nb * c;
@@ -341,18 +342,23 @@ int grad_chunks(int nb, int tiles) {
     const double cost = act / eff + (c > 1 ? 2.0 * c * nb * GB * GB * 4.0 : 0.0);
     if (c == 1 || cost < best_cost) { best_cost = cost; best = c; }
   }
+  if (cost_out) *cost_out = best_cost;
   return best;
 }
 
-// Walking pairs: one per two CUs, or none.  A border costs a drained and refilled ring and a piece more to write and add up, so the walk pays for
-// shares of 20 tiles on where equal ranges keep less than 15/16 of the CUs busy.  Whole backward of d x 256, us, equal ranges / walking: 14336 features with 16384 tokens
-// (112 tiles a share) 585 / 545, 11008 with 8192 (43) 264 / 243, 5632 with 8192 (22) 147 / 141, 3072 with 16384 (24) 159 / 154; 14336 with 2048 (14) 94 / 106,
-// 3072 with 4096 (6) 65 / 71.
+// Walking pairs: one per two CUs, or none.  Priced in the same bytes: all CUs are busy, but every piece of a share costs about three tiles of a drained and refilled ring
+// and a partial, written and read.  Three per cent have to be left, for blocks that equal ranges write in one piece.  Whole backward of d x 256, us, equal ranges / walking
+// (tiles of a share): taken 14336 features with 16384 tokens (112) 585 / 546, 18944 with 8192 (74) 442 / 389, 11008 with 8192 (43) 265 / 243, 9216 with 8192 (36) 245 / 216,
+// 2816 with 16384 (22) 157 / 149, 6144 with 8192 (24) 152 / 148; left 13824 with 4096 (27) 162 / 167, 7168 with 8192 (28) 167 / 169, 24576 with 4096 (48) 257 / 260,
+// 14336 with 2048 (14) 94 / 106, 3072 with 4096 (6) 65 / 71.
 constexpr int WALK_PAIRS = 128;
 bool grad_walks(int nb, int tiles) {
   const i64 total = (i64)nb * tiles;
-  const int pairs = nb * grad_chunks(nb, tiles), rounds = (pairs + WALK_PAIRS - 1) / WALK_PAIRS;
-  return total >= 20 * WALK_PAIRS && total < (1ll << 31) && 16 * pairs < 15 * WALK_PAIRS * rounds;
+  if (total < WALK_PAIRS || total >= (1ll << 31)) return false;
+  double equal;
+  grad_chunks(nb, tiles, &equal);
+  const double pieces = WALK_PAIRS + nb - 1, walk = grad_bytes(nb, tiles) * (1.0 + 3.0 * pieces / (double)total) + 2.0 * pieces * GB * GB * 4.0;
+  return walk < 0.97 * equal;
 }
 
 }  // namespace

@@ -291,10 +291,10 @@ int poetx_perm_validate(const int32_t* perm, int32_t d, int32_t* scratch, void* 
  * activations between the stages it holds fp32 parts of products that split their contraction,
  * and token counts that are no multiple of 256 make its activations wider: to a multiple of 8, or of
  * 256 where the dense products of a layer with multiples of 256 gain by it (more than 64 tokens and
- * d_in * d_out * padded tokens >= 2^30).  In MB, k = 5: 2048 x 5632 with 1999 tokens 115 (85 without parts
- * and padding), 8192 x 3072 with 4090 token-major tokens 268 (235), 4096 x 14336 with 70 tokens 158
- * (153), fp32 1024 x 768, b = 64, with 1001 tokens 19.6 (7.2).  Large whole token counts have neither:
- * 14336 x 4096 with 16384 tokens 789.
+ * d_in * d_out * padded tokens >= 2^30).  In MB, k = 5: 2048 x 5632 with 1999 tokens 129 (85 without parts
+ * and padding), 8192 x 3072 with 4090 token-major tokens 300 (235), 4096 x 14336 with 70 tokens 158
+ * (153), fp32 1024 x 768, b = 64, with 1001 tokens 19.6 (7.2).  Large whole token counts have little of either:
+ * 14336 x 4096 with 16384 tokens 803.
  */
 size_t poetx_linear_workspace_bytes(const poetx_linear_desc* desc);
 

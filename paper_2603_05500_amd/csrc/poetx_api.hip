@@ -161,10 +161,11 @@ void apply_left(const poetx_linear_desc* desc, const Act& V, const Act& out, int
 
 // Does poetx_linear_bwd stream each side's gradient once (aligned tensors)?  Not a short stream: the two halves' smaller tiles and both gradients in a launch are sooner done.  us without
 // the series, one pass / two halves: 1024 x 1024, 256 tokens 37 / 30, 2048 55 / 44, 4096 (2^23 elements) 62 / 57, 8192 81 / 90; 2048 x 2048, 1024 58 / 49; 4096 x 4096, 512 68 / 58,
-// 2048 111 / 125; 4096 x 1024, 768 64 / 54; 8192 x 4096, 512 84 / 84, 768 103 / 108.
+// 2048 111 / 125; 4096 x 1024, 768 64 / 54; 8192 x 4096, 512 84 / 84, 768 103 / 108. Unequal sides, whose gradients share a launch less evenly,
+// a quarter earlier: 4096 x 2048, 1024 (3 * 2^21 elements) 69 / 68, 1280 74 / 76; 2048 x 1024, 2048 59 / 59, 2560 62 / 64; 5632 x 2048, 768 73 / 72, 1024 76 / 78.
 bool bwd_one_pass(const poetx_linear_desc* d) {
   const i64 N = d->n_tokens;
-  return (d->d_in + (i64)d->d_out) * N > 1 << 23 && d->cnp_precision == POETX_CNP_BF16 && use_mfma(d->dtype) && lds_cnp_supported(d->d_in, d->block) && lds_cnp_supported(d->d_out, d->block) &&
+  return (d->d_in + (i64)d->d_out) * N > (d->d_in == d->d_out ? 4 : 3) << 21 && d->cnp_precision == POETX_CNP_BF16 && use_mfma(d->dtype) && lds_cnp_supported(d->d_in, d->block) && lds_cnp_supported(d->d_out, d->block) &&
          internal_columns(d) == N && mfma_apply_grad_supported(d->d_in, N, N, d->block) && mfma_apply_grad_supported(d->d_out, N, N, d->block);
 }
 

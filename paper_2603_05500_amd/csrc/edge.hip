@@ -508,13 +508,16 @@ void apply_pair_t(Tile t, const T* V, i64 ldv, T* out, i64 ldo, i64 cols, i64 co
 }
 }  // namespace
 
-// Both on tiles that one launch holds, and not so many workgroups that either fills the chip for long.  us, two launches without the gap between them / one: fp32 256 x 256, b = 32, 512 tokens
+// Both on tiles that one launch holds: few of the apply, so that they do not fill the chip for long, and with the gradients' (whose blocks may be very many) no more than one grid
+// dimension takes.  us, two launches without the gap between them / one: fp32 256 x 256, b = 32, 512 tokens
 // 3.9 + 5.4 / 5.6; 1024 x 768, b = 64, 1001 tokens 5.9 + 10.7 / 12.1; bf16 1376 x 512, b = 64, 1024 tokens 4.3 + 5.9 / 6.5.  Whole backward calls of 220 random small layers: 13 % less on
 // average, 1 % more at worst (apply tiles up to four per CU, 16 - 4096 tokens).
 bool edge_apply_joins_blockgrads(int dtype, int d_apply, i64 plan_cols, int d0, int d1, i64 N, int b) {
   const Tile t = apply_tile(ceil_div(d_apply, b), b, plan_cols);
-  if (t == TILE_128 || grad_plan(dtype, d0, N, b).tile != TILE_32 || grad_plan(dtype, d1, N, b).tile != TILE_32) return false;
-  return tile_count(ceil_div(d_apply, b), b, plan_cols, t == TILE_64 ? 64 : 32) <= 4 * kCUs;
+  const Plan p0 = grad_plan(dtype, d0, N, b), p1 = grad_plan(dtype, d1, N, b);
+  if (t == TILE_128 || p0.tile != TILE_32 || p1.tile != TILE_32) return false;
+  const i64 apply = tile_count(ceil_div(d_apply, b), b, plan_cols, t == TILE_64 ? 64 : 32);
+  return apply <= 4 * kCUs && apply + tile_count(ceil_div(d0, b), b, b, 32) * p0.splits + tile_count(ceil_div(d1, b), b, b, 32) * p1.splits <= kGridRow;
 }
 
 // dX = R dA (out = op(blocks) V on the rows of q1's side) and both sides' block gradients

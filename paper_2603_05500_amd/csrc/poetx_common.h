@@ -67,11 +67,11 @@ __host__ __device__ inline int block_side(int d, int b, int j) {
 
 // A grid dimension holds less than 2^32 threads; very many workgroups (small blocks, very many tokens) take several launches.  Calls
 // launch(first, count) for each; the kernel adds `first` to its number.  More than an int counts is an empty grid, which HIP refuses.
+constexpr i64 kGridRow = 1 << 21;   // workgroups of up to 1024 threads
 template <class F>
 inline void launch_in_rows(i64 total, F launch) {
-  constexpr i64 row = 1 << 21;   // of up to 1024 threads
   if (total > 0x7fffffff) return launch(0, 0u);
-  for (i64 first = 0; first < total; first += row) launch((int)first, (unsigned)(total - first < row ? total - first : row));
+  for (i64 first = 0; first < total; first += kGridRow) launch((int)first, (unsigned)(total - first < kGridRow ? total - first : kGridRow));
 }
 
 // Do the `width` rows or columns from `start` on lie inside an extent?  No sum: counts go up to the last int, where the end of the last tile is beyond it.

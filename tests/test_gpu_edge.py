@@ -602,6 +602,43 @@ def test_block_counts_beyond_one_grid_dimension(lib):
     assert float((out[pi, 0] - y).abs().max()) <= 1e-5
 
 
+def test_one_call_backward_of_blocks_beyond_one_grid_dimension(lib):
+    """The whole backward of one token where one side has a single 2 x 2 block and the other 35 million: more gradient workgroups than a grid dimension
+    holds, beside an apply of one.  Series gradient of a 2 x 2 block at k = 2 as in the test above."""
+    m, n, b, k = 2, 70_000_000, 2, 2
+    g = torch.Generator(device="cuda").manual_seed(4)
+    r = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    th = {"R": r(1, 1) * 0.1, "P": r(n // b, 1) * 0.1}
+    pi = {"R": torch.tensor([1, 0], device="cuda"), "P": torch.randperm(n, generator=g, device="cuda")}
+
+    def block(t):
+        t = t[:, 0]
+        diag, off = 1 - 2 * t ** 2, 2 * t - t ** 3
+        return torch.stack((diag, off, -off, diag), 1).view(-1, b, b).contiguous()
+    blk = {s: block(th[s]) for s in "RP"}
+    X, dZ, B, W = r(m, 1), r(n, 1), r(n, 1), r(n, m) * 0.02
+    desc = lib.make_desc(m, n, b, k, 1, lib.F32)
+    ws = torch.empty(lib.poetx_linear_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    dX, dth = torch.full_like(X, float("nan")), {s: torch.full_like(th[s], float("nan")) for s in "RP"}
+    p32 = {s: pi[s].to(torch.int32) for s in "RP"}
+    lib.poetx_linear_bwd(desc, X, dZ, B, W, p32["R"], p32["P"], blk["R"], blk["P"], th["R"], th["P"], dX, dth["R"], dth["P"], False, ws)
+    torch.cuda.synchronize()
+
+    def apply(v, s):
+        out = torch.empty_like(v)
+        out[pi[s], 0] = (blk[s].double() * v[pi[s], 0].view(-1, 1, b)).sum(2).view(-1)
+        return out
+
+    def series_grad(u, v, s):
+        d, t = u[pi[s], 0].view(-1, b, 1) * v[pi[s], 0].view(-1, 1, b), th[s][:, 0].double()
+        return -4 * t * (d[:, 0, 0] + d[:, 1, 1]) + (2 - 3 * t ** 2) * (d[:, 0, 1] - d[:, 1, 0])
+    dA = W.double().T @ apply(dZ.double(), "P")
+    err = lambda got, want: float((got.double() - want).norm() / want.norm())
+    assert err(dX, apply(dA, "R")) <= 1e-5
+    assert err(dth["P"][:, 0], series_grad(B.double(), dZ.double(), "P")) <= 1e-6
+    assert err(dth["R"][:, 0], series_grad(X.double(), dA, "R")) <= 1e-5
+
+
 @pytest.mark.parametrize("b,nbR,nbP", [
     (512, 60, 30),      # groups 64 + 26: the P side ends inside the first group, the R side goes on in the second
     (512, 16, 70),      # the P side ends inside the second group

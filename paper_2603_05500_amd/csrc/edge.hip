@@ -309,7 +309,7 @@ void launch_slice_tile(SliceTile tile, const SliceArgs& g, const Epi& epi, i64 N
 template <class T>
 void dense_slices(const SlicePlan& p, int trans_w, const T* W, int n, int m, const T* act, i64 act_cols, T* out, i64 ld_out, i64 N, float* parts, hipStream_t st) {
   const int M = trans_w ? m : n, K = trans_w ? n : m;
-  const SliceArgs g{W, act, m, act_cols, M, (int)act_cols, 0, K * (int)sizeof(T) / 64, 0};
+  const SliceArgs g{W, act, m, act_cols, M, (int)act_cols, 0, slice_count(K, (int)sizeof(T)), 0};
   if (p.splits > 1) {
     const EpiPartial epi{parts, M, (int)N, 1};
     if (trans_w) launch_slice_tile<T, false>(p.tile, g, epi, N, p.splits, st);

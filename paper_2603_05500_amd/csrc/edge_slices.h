@@ -26,6 +26,10 @@ __device__ __forceinline__ void wait_slices(int slices) {
   }
 }
 
+// slices of a whole contraction (a multiple of a slice's depth).  No product of K and the element size: K goes up to the last int.
+constexpr int slice_count(int K, int element) { return K / (64 / element); }
+static_assert(slice_count(1 << 29, 4) == 1 << 25 && slice_count(1 << 30, 2) == 1 << 25 && slice_count(0x7fffffe0, 2) == 0x3ffffff, "the bytes of such a row are more than an int holds");
+
 template <class T, int BM, int BN, int WAVES, int NS>
 struct SliceShape {
   static constexpr int DEPTH = 64 / (int)sizeof(T);            // of a slice

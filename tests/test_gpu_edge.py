@@ -602,6 +602,26 @@ def test_block_counts_beyond_one_grid_dimension(lib):
     assert float((out[pi, 0] - y).abs().max()) <= 1e-5
 
 
+def test_contraction_of_two_to_the_29(lib):
+    """A backward product over 2^29 output features, fp32: its operand's row of 2^31 bytes is past what an int counts.  Blocks of one, equal to one, and the identity
+    order, so that dA = W^T dZ; features are zero but for runs at the ends and where a count or an offset could wrap."""
+    m, n, b = 4, 2 ** 29, 1
+    g = torch.Generator(device="cuda").manual_seed(3)
+    at = torch.cat([torch.arange(max(c - 20, 0), min(c + 20, n)) for c in (0, 2 ** 25, 2 ** 27, 2 ** 28, n)]).cuda()
+    W, dZ = torch.zeros((n, m), device="cuda"), torch.zeros((n, 1), device="cuda")
+    W[at] = torch.randn((at.numel(), m), generator=g, device="cuda")
+    dZ[at] = torch.randn((at.numel(), 1), generator=g, device="cuda")
+    pi = torch.arange(n, dtype=torch.int32, device="cuda")
+    one = torch.ones((n, 1, 1), device="cuda")
+    desc = lib.make_desc(m, n, b, 1, 1, lib.F32)
+    ws = torch.empty(lib.poetx_linear_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    dX, dA = (torch.full((m, 1), float("nan"), device="cuda") for _ in range(2))
+    lib.poetx_linear_bwd_input(desc, dZ, W, pi[:m], pi, one[:m], one, dX, dA, ws)
+    torch.cuda.synchronize()
+    want = W[at].double().T @ dZ[at].double()
+    assert float((dA.double() - want).norm() / want.norm()) <= 1e-6 and torch.equal(dX, dA)
+
+
 def test_one_call_backward_of_blocks_beyond_one_grid_dimension(lib):
     """The whole backward of one token where one side has a single 2 x 2 block and the other 35 million: more gradient workgroups than a grid dimension
     holds, beside an apply of one.  Series gradient of a 2 x 2 block at k = 2 as in the test above."""

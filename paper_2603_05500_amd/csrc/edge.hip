@@ -31,15 +31,15 @@ Tile apply_tile(i64 batches, i64 M, i64 N) {
 // us, edge kernel / here: fp32 1024 x 768 x 1001 29.0 / 18.0 and, backward, 29.7 (with its reduce) / 21; 256 x 256 x 512 6.0 / 4.3; bf16 1376 x 512 x 1024 9.1 / 6.4 and 11.2 / 5.6;
 // 768 x 1024 x 500 9.0 / 5.1; 1536 x 1536 x 3000 40.3 / 37.7.
 struct SliceCost {
-  int bm, bn, waves;
+  int bm, bn, waves_log2;
   double base, lone, shared, tail, cold, reduce, parts;
 };
 enum SliceTile { SLICES_32 = 0, SLICES_32x64 = 1, SLICES_64 = 2, SLICES_64x32 = 3, EDGE_TILES = -1 };
-constexpr SliceCost kSlicesF32[] = {{32, 32, 8, 2.5, 0.16, 0.50, 0.83, 0.26, 2.7, 1.0e-6}, {32, 64, 4, 3.4, 0.41, 0.535, 0.45, 0.22, 2.7, 1.0e-6}, {64, 64, 4, 4.0, 0.975, 0.975, 0.25, 0.07, 2.7, 2.0e-6}};
-constexpr SliceCost kSlicesBf16[] = {{32, 32, 8, 1.73, 0.01, 0.52, 0.51, 0.35, 3.2, 0.8e-6}, {32, 64, 4, 2.05, 0.03, 0.345, 0.45, 0.11, 3.2, 0.8e-6}, {64, 64, 4, 1.8, 0.43, 0.445, 1.17, 0.09, 3.2, 1.0e-6}};
+constexpr SliceCost kSlicesF32[] = {{32, 32, 3, 2.5, 0.16, 0.50, 0.83, 0.26, 2.7, 1.0e-6}, {32, 64, 2, 3.4, 0.41, 0.535, 0.45, 0.22, 2.7, 1.0e-6}, {64, 64, 2, 4.0, 0.975, 0.975, 0.25, 0.07, 2.7, 2.0e-6}};
+constexpr SliceCost kSlicesBf16[] = {{32, 32, 3, 1.73, 0.01, 0.52, 0.51, 0.35, 3.2, 0.8e-6}, {32, 64, 2, 2.05, 0.03, 0.345, 0.45, 0.11, 3.2, 0.8e-6}, {64, 64, 2, 1.8, 0.43, 0.445, 1.17, 0.09, 3.2, 1.0e-6}};
 // Up to 32 columns of a large bf16 weight are bound by the reads of it.  Where its rows are the contraction (dA = W^T dB) 32 of them are half a cache line, so 64 go to
 // a workgroup: 7168 x 12800, one token 37.4 us, on 32 x 32 64.4; 9728 x 4096, 5: 21.0 / 26.2.  Fitted to 230 products like the above, 3 % slower than the best on average.
-constexpr SliceCost kSlicesFew[] = {{32, 32, 8, 1.50, 0.67, 0.68, 0.53, 0, 3.3, 1.8e-6}, {64, 32, 4, 1.20, 0.04, 0.59, 0.57, 0, 4.75, 1.3e-6}};
+constexpr SliceCost kSlicesFew[] = {{32, 32, 3, 1.50, 0.67, 0.68, 0.53, 0, 3.3, 1.8e-6}, {64, 32, 2, 1.20, 0.04, 0.59, 0.57, 0, 4.75, 1.3e-6}};
 struct SlicePlan {
   SliceTile tile;
   int splits;
@@ -50,20 +50,32 @@ bool slices_take(int dtype, i64 M, i64 ld_w, i64 act_cols, i64 K) {
   const i64 es = dtype == POETX_F32 ? 4 : 2;
   return K * es % 64 == 0 && ld_w * es % 16 == 0 && act_cols % 8 == 0 && ld_w < (1 << 22) && act_cols < (1 << 22) && tile_count(1, M, act_cols, 32) < (1 << 21);
 }
-double edge_price(int dtype, i64 M, i64 N, i64 K, Plan* plan);
-SlicePlan slice_plan(int dtype, int trans_w, i64 M, i64 N, i64 K) {
+struct EdgePrice {
+  double us;
+  Plan plan;
+};
+EdgePrice edge_price(int dtype, i64 M, i64 N, i64 K);
+// ceil(x / s) for s up to 16 and x < 2^31 without a division: every linear call prices its products.  The half keeps the product's rounding off whole numbers.
+constexpr double kInverse[] = {0,       1.0 / 1, 1.0 / 2,  1.0 / 3,  1.0 / 4,  1.0 / 5,  1.0 / 6,  1.0 / 7, 1.0 / 8,
+                               1.0 / 9, 1.0 / 10, 1.0 / 11, 1.0 / 12, 1.0 / 13, 1.0 / 14, 1.0 / 15, 1.0 / 16};
+inline unsigned share(unsigned x, unsigned s) { return (unsigned)(((double)(x + s) - 0.5) * kInverse[s]); }
+// edge: the edge kernel's price of the same product, from a caller that has it
+SlicePlan slice_plan(int dtype, int trans_w, i64 M, i64 N, i64 K, const EdgePrice* edge = nullptr) {
   const bool f = dtype == POETX_F32;
-  const i64 es = f ? 4 : 2, slices = K * es / 64;
+  const int es = f ? 4 : 2;
+  const unsigned slices = (unsigned)slice_count((int)K, es);
   const bool large = (double)M * (double)K * (double)es > kLargeWeight;
   SlicePlan best{SLICES_32, 1};
   double least = 0;
   auto price = [&](const SliceCost& c, SliceTile tile) {
-    const i64 count = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-    for (int s = 1; s <= 16; ++s) {
-      const i64 each = (slices + s - 1) / s, splits = (slices + each - 1) / each;      // no empty split
-      if (s > 1 && (each <= c.waves || count * s > 4 * kCUs)) break;
-      const double per_cu = (double)((count * splits + kCUs - 1) / kCUs), stage = per_cu * c.shared, lone = c.lone + (large ? c.cold : 0);
-      double us = c.base + (double)((each + c.waves - 1) / c.waves) * (lone > stage ? lone : stage) + c.tail * per_cu;
+    const unsigned count = (unsigned)(((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn));     // below 2^21, see slices_take
+    const double lone = c.lone + (large ? c.cold : 0);
+    for (unsigned s = 1; s <= 16; ++s) {
+      const unsigned each = share(slices, s);
+      if (s > 1 && (each <= 1u << c.waves_log2 || count * s > 4 * kCUs)) break;
+      const unsigned splits = (slices + each - 1) / each;      // no empty split
+      const double per_cu = (double)((count * splits + kCUs - 1) / kCUs), stage = per_cu * c.shared;
+      double us = c.base + (double)((each + (1u << c.waves_log2) - 1) >> c.waves_log2) * (lone > stage ? lone : stage) + c.tail * per_cu;
       if (splits > 1) us += c.reduce + c.parts * (double)splits * (double)M * (double)N;
       if (least == 0 || us < least) { least = us; best = SlicePlan{tile, (int)splits}; }
     }
@@ -79,9 +91,8 @@ SlicePlan slice_plan(int dtype, int trans_w, i64 M, i64 N, i64 K) {
   // Large bf16 weights: the 128 x 128 tiles of the edge kernel read each operand half as often.  They stay unless this price is a quarter below theirs: of 1750 products
   // three are then more than 2 % slower than under the edge plan alone, eleven more than 5 % where the lower price decides.
   if (!f && large) {
-    Plan p;
-    const double us = edge_price(dtype, M, N, K, &p);
-    if (p.tile == TILE_128 && us < 1.25 * least) best.tile = EDGE_TILES;
+    const EdgePrice e = edge ? *edge : edge_price(dtype, M, N, K);
+    if (e.plan.tile == TILE_128 && e.us < 1.25 * least) best.tile = EDGE_TILES;
   }
   return best;
 }
@@ -102,7 +113,7 @@ struct TileCost {
   int side;
   double lone, shared;
 };
-double edge_price(int dtype, i64 M, i64 N, i64 K, Plan* plan) {
+EdgePrice edge_price(int dtype, i64 M, i64 N, i64 K) {
   static const TileCost f32[] = {{TILE_32, 32, 0.70, 0.51}, {TILE_64, 64, 1.51, 0.66}, {TILE_64D, 64, 1.57, 1.46}, {TILE_128, 128, 2.69, 2.32}};
   static const TileCost bf16[] = {{TILE_32, 32, 0.58, 0.31}, {TILE_64, 64, 0.58, 0.35}, {TILE_128, 128, 1.14, 0.62}};
   const bool f = dtype == POETX_F32;
@@ -110,37 +121,36 @@ double edge_price(int dtype, i64 M, i64 N, i64 K, Plan* plan) {
   const double fill = f ? 0.94 : 1.1, reduce = f ? 1.95 : 2.3;
   const bool large = (double)M * (double)K * (double)es > kLargeWeight;
   const double cold = large ? (f ? 0.63 : 0.39) : 0;
-  Plan best{TILE_32, 1};
-  double least = 0;
+  EdgePrice best{0, {TILE_32, 1}};
   for (int t = 0; t < (f ? 4 : 3); ++t) {
     const TileCost& c = f ? f32[t] : bf16[t];
     if (c.side > 32 && (2 * M <= c.side || 2 * N <= c.side)) continue;   // half of it idle
-    const i64 count = tile_count(1, M, N, c.side), depth = stage_depth(c.tile, es), stages = (K + depth - 1) / depth;
+    const i64 count = tile_count(1, M, N, c.side);
+    const unsigned depth = (unsigned)stage_depth(c.tile, es), stages = ((unsigned)K + depth - 1) / depth;
     const i64 most = (c.tile == TILE_128 ? 2 : 4) * kCUs;      // workgroups of a split: bounds the parts to 34 MB
-    for (int s = 1; s <= 16; ++s) {
-      if (s > 1 && (stages / s < 2 || count * s > most)) break;
-      const i64 per = (stages + s - 1) / s, splits = (stages + per - 1) / per;   // no empty split
+    for (unsigned s = 1; s <= 16; ++s) {
+      if (s > 1 && (stages < 2 * s || count * s > most)) break;
+      const unsigned per = share(stages, s), splits = (stages + per - 1) / per;   // no empty split
       const double stage = (double)((count * splits + kCUs - 1) / kCUs) * c.shared;
       double us = ((double)per + fill) * (c.lone + cold > stage ? c.lone + cold : stage);
       if (splits > 1) us += reduce + 8e-6 / 4 * (double)splits * (double)M * (double)N;
-      if (least == 0 || us < least) { least = us; best = Plan{c.tile, (int)splits}; }
+      if (best.us == 0 || us < best.us) best = EdgePrice{us, {c.tile, (int)splits}};
     }
   }
-  *plan = best;
-  return least;
+  return best;
 }
+// Few columns of a large weight
+bool weight_bound(int dtype, i64 M, i64 N, i64 K) { return N <= 32 && (double)M * (double)K * (dtype == POETX_F32 ? 4.0 : 2.0) > kLargeWeight; }
 Plan dense_plan(int dtype, i64 M, i64 N, i64 K) {
-  const size_t es = dtype == POETX_F32 ? 4 : 2;
-  if (N <= 32 && (double)M * (double)K * (double)es > kLargeWeight) {     // bound by the reads of the weight
-    const i64 count = tile_count(1, M, N, 32), depth = stage_depth(TILE_32, es), stages = (K + depth - 1) / depth;
-    const i64 two = min64(2 * kCUs / count, stages / 2), four = min64(4 * kCUs / count, stages / 4), s = two > four ? two : four;
-    if (s <= 1) return Plan{TILE_32, 1};
-    const i64 per = (stages + s - 1) / s;
-    return Plan{TILE_32, (int)((stages + per - 1) / per)};
-  }
-  Plan p;
-  edge_price(dtype, M, N, K, &p);
-  return p;
+  if (!weight_bound(dtype, M, N, K)) return edge_price(dtype, M, N, K).plan;
+  const i64 count = tile_count(1, M, N, 32);
+  if (count > 4 * kCUs) return Plan{TILE_32, 1};
+  const unsigned depth = (unsigned)stage_depth(TILE_32, dtype == POETX_F32 ? 4 : 2), stages = ((unsigned)K + depth - 1) / depth;
+  const unsigned four_each = 4 * kCUs / (unsigned)count, two_each = four_each / 2;     // workgroups of a tile for four and two on every CU
+  const unsigned two = two_each < stages / 2 ? two_each : stages / 2, four = four_each < stages / 4 ? four_each : stages / 4, s = two > four ? two : four;
+  if (s <= 1) return Plan{TILE_32, 1};
+  const unsigned per = (stages + s - 1) / s;
+  return Plan{TILE_32, (int)((stages + per - 1) / per)};
 }
 // Block gradients: the contraction is the token range, so a large tile with a split costs only its fp32 parts, while
 // every halving of the tile side doubles the reads of both activations.  A split keeps 256 tokens, on the smallest tile two
@@ -415,15 +425,16 @@ void grad_pair_t(const Plan& p0, const Plan& p1, const GradProblem& q0, const Gr
 
 }  // namespace
 
-// Which of the two kernels it is depends on the pointers' alignment as well, which a query does not see: the parts of either, and of either direction.
-size_t edge_dense_workspace_bytes(int dtype, i64 M, i64 act_cols, i64 K) {
-  const Plan p = dense_plan(dtype, M, act_cols, K);
-  int splits = p.splits;
-  if (slices_take(dtype, M, 16, act_cols, K)) {
-    for (int trans = 0; trans < 2; ++trans) {
-      const SlicePlan s = slice_plan(dtype, trans, M, act_cols, K);
-      if (s.tile != EDGE_TILES && s.splits > splits) splits = s.splits;
-    }
+// Which of the two kernels it is depends on the pointers' alignment as well, which a query does not see: the parts of either.  Every linear call asks,
+// so each product is priced once.
+size_t edge_dense_workspace_bytes(int dtype, int trans_w, int n, int m, i64 act_cols, bool aligned) {
+  const i64 M = trans_w ? m : n, K = trans_w ? n : m;
+  const bool bound = weight_bound(dtype, M, act_cols, K);
+  const EdgePrice e = bound ? EdgePrice{0, dense_plan(dtype, M, act_cols, K)} : edge_price(dtype, M, act_cols, K);
+  int splits = e.plan.splits;
+  if (aligned && slices_take(dtype, M, m, act_cols, K)) {
+    const SlicePlan s = slice_plan(dtype, trans_w, M, act_cols, K, bound ? nullptr : &e);
+    if (s.tile != EDGE_TILES && s.splits > splits) splits = s.splits;
   }
   return splits > 1 ? (size_t)splits * M * act_cols * sizeof(float) : 0;
 }
@@ -533,7 +544,8 @@ void edge_apply_blockgrad_parts(int dtype, const void* V, i64 ldv, void* out, i6
 }
 
 size_t edge_blockgrad_workspace_bytes(int dtype, int d, i64 N, int b) {
-  return grad_plan(dtype, d, N, b).splits > 1 ? edge_blockgrad_parts_bytes(dtype, d, N, b) : 0;
+  const int splits = grad_plan(dtype, d, N, b).splits;
+  return splits > 1 ? (size_t)splits * ceil_div(d, b) * b * b * sizeof(float) : 0;
 }
 
 // Both sides: one launch (where their tiles are the same) and one that adds the parts of both.  Parts of a side lie behind each other in ws, whole vectors (b * b a multiple of four).

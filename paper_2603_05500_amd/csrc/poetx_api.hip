@@ -223,11 +223,13 @@ size_t blockgrad_parts_bytes(const poetx_linear_desc* d, int dim) {
 // the workspace, so every plan is made for internal_columns().
 size_t dense_part_bytes(const poetx_linear_desc* d) {
   const i64 N = internal_columns(d);
-  const size_t f = edge_dense_workspace_bytes(d->dtype, d->d_out, N, d->d_in);
-  const size_t b = edge_dense_workspace_bytes(d->dtype, d->d_in, N, d->d_out);
+  const int n = d->d_out, m = d->d_in;
+  const bool streams = d->dtype == POETX_BF16 && mfma_dense_supported(n, m, N);   // what is aligned; the rest is the edge kernel's
+  const size_t f = few_tokens(d) ? 0 : edge_dense_workspace_bytes(d->dtype, 0, n, m, N, !streams);   // whose forward has kernels of its own
+  const size_t b = edge_dense_workspace_bytes(d->dtype, 1, n, m, N, !streams);
   size_t w = f > b ? f : b;
-  if (d->dtype == POETX_BF16 && mfma_dense_supported(d->d_out, d->d_in, N)) {
-    const size_t mf = mfma_dense_workspace_bytes(d->d_out, N, d->d_in), mb = mfma_dense_workspace_bytes(d->d_in, N, d->d_out);
+  if (streams) {
+    const size_t mf = mfma_dense_workspace_bytes(n, N, m), mb = mfma_dense_workspace_bytes(m, N, n);
     w = mf > w ? mf : w;
     w = mb > w ? mb : w;
   }
@@ -474,7 +476,7 @@ class LayoutStaging {
  public:
   LayoutStaging(const poetx_linear_desc* d, void* ws, hipStream_t st)
       : d_(d), on_(d->layout == POETX_TOKEN_MAJOR), dt_(d->dtype), N_(d->n_tokens), Ni_(internal_columns(d)), st_(st),
-        next_((char*)ws + core_workspace_bytes(d)), n_out_(0) {}
+        next_(on_ ? (char*)ws + core_workspace_bytes(d) : nullptr), n_out_(0) {}
   Act in(const void* p, int rows) {
     if (!on_ || !p) return Act{p, N_, N_};
     void* t = take(rows);
@@ -525,8 +527,10 @@ static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
   const size_t bg = blockgrad_ws_bytes(desc);
   const size_t chain = cnp_bwd_ws_floats(desc);
   size_t skew = align256(chain * sizeof(float)) + bg;
-  const size_t parts = blockgrad_parts_bytes(desc, desc->d_in) + blockgrad_parts_bytes(desc, desc->d_out);
-  if (series_small_supported(desc->block) && parts > skew) skew = parts;
+  if (series_small_supported(desc->block)) {
+    const size_t parts = blockgrad_parts_bytes(desc, desc->d_in) + blockgrad_parts_bytes(desc, desc->d_out);
+    if (parts > skew) skew = parts;
+  }
   size_t w = fwd > bwi ? fwd : bwi;
   if (skew > w) w = skew;
   // poetx_linear_bwd keeps dA (and, on its one-pass path, dB) in the workspace next to what the two

@@ -41,7 +41,8 @@ void fma_cnp_bwd(const float* theta, const float* dG, int d, int b, int k, float
 // ---- edge-handling matrix-core path (edge.hip): bf16 and fp32, any sizes, strides and alignments --------
 // ws: the bytes the queries report (fp32 partials of a split contraction; 0 where there is no split).
 // act has act_cols columns, which the plan is made for and the query is asked with; the first N of the product go to out.
-size_t edge_dense_workspace_bytes(int dtype, i64 M, i64 act_cols, i64 K);
+// aligned: may both operands lie on 16-byte boundaries (not where such a product runs on another kernel)?
+size_t edge_dense_workspace_bytes(int dtype, int trans_w, int n, int m, i64 act_cols, bool aligned);
 void edge_dense(int dtype, int trans_w, const void* W, int n, int m, const void* act, i64 ld_act, i64 act_cols, void* out, i64 ld_out, i64 N,
                 void* ws, hipStream_t st);
 // V: d x cols, out: d x cols_out (cols_out >= cols; the extra columns are written as zeros); plan_cols: columns to choose the tile for

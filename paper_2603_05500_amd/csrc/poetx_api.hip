@@ -521,9 +521,8 @@ static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
   size_t fwd = actm;                                    // A = R^T X
   if (desc->flags & POETX_FLAG_RECOMPUTE_B) fwd += actn;  // B lives here too
   const size_t wdeq = dequantised_weight_bytes(desc);   // only where no kernel converts on the fly
-  const size_t part = dense_part_bytes(desc);
-  fwd += wdeq + part;                                   // dequantised weight behind A (and B), then the dense product's partials
-  size_t bwi = actn + wdeq + part;                      // dB = P dZ
+  fwd += wdeq;                                          // dequantised weight behind A (and B), then the dense product's partials
+  size_t bwi = actn + wdeq;                             // dB = P dZ; partials likewise
   const size_t bg = blockgrad_ws_bytes(desc);
   const size_t chain = cnp_bwd_ws_floats(desc);
   size_t skew = align256(chain * sizeof(float)) + bg;
@@ -531,6 +530,12 @@ static size_t core_workspace_bytes(const poetx_linear_desc* desc) {
     const size_t parts = blockgrad_parts_bytes(desc, desc->d_in) + blockgrad_parts_bytes(desc, desc->d_out);
     if (parts > skew) skew = parts;
   }
+  // A few tokens' partials (of the backward product alone: up to sixteen ranges, or 1024 tiles of 32 x 32) mostly disappear in what the series needs, and the price of its plan,
+  // which this query of every call then leaves out, is most of its time.
+  const size_t few = 64 * (size_t)desc->d_in * (size_t)Ni, most = few > (4u << 20) ? few : 4u << 20;
+  const size_t part = few_tokens(desc) && bwi + most <= skew ? 0 : dense_part_bytes(desc);
+  fwd += part;
+  bwi += part;
   size_t w = fwd > bwi ? fwd : bwi;
   if (skew > w) w = skew;
   // poetx_linear_bwd keeps dA (and, on its one-pass path, dB) in the workspace next to what the two

@@ -51,11 +51,11 @@
  *    products where d_in and d_out are multiples of 256 and the token count is one too or
  *    the layer is large enough for the workspace's activations to be padded to one; the
  *    structured applies where b = 256 or 512 divides their dimension, for whole tiles of 128
- *    (b = 512: 64) tokens or from 256 tokens (padding included) on; the block gradients for
- *    such blocks and multiples of 64 tokens, from 256 on.  fp32 tensors, streaming kernel:
- *    a dense product whose three dimensions are multiples of 128 with at least 192 output
- *    tiles of 128 x 128.  The dense products, applies and block gradients of everything else
- *    run on an edge-handling matrix-core product of the tensors' type (applies of blocks up to
+ *    (b = 512: 64) tokens or from 256 tokens (padding included) on; the block gradients of a
+ *    side for such blocks, multiples of 64 tokens and more than 2^25 elements (b = 512: from 2^25 on).
+ *    fp32 tensors, streaming kernel: a dense product whose three dimensions are multiples of 128 with
+ *    at least 1024 output tiles of 128 x 128.  The dense products, applies and block gradients of everything else
+ *    run on edge-handling matrix-core products of the tensors' type (applies of blocks up to
  *    b = 16 over many tokens on the plain fp32-FMA kernel).  A handful of bf16 tokens, where
  *    b = 64, 128, 256 or 512 divides both dimensions: the forward, and B where it is recomputed,
  *    on short kernels of their own (up to 16 tokens, 32 for weights up to 2^24 elements, and
@@ -302,8 +302,8 @@ size_t poetx_linear_workspace_bytes(const poetx_linear_desc* desc);
  * assumed).  Returns a combination of POETX_PATH_* bits, 0 when every stage runs on the edge-handling,
  * few-token or plain kernels, or minus a poetx_status when the descriptor is invalid. */
 #define POETX_PATH_APPLY 1              /* gather + block-diagonal product + scatter, both sides */
-#define POETX_PATH_DENSE 2              /* both B = W A and dA = W^T dB (the only bit fp32 tensors get: whole 128-wide tiles that fill the chip) */
-#define POETX_PATH_BLOCKGRAD 4          /* block gradients (two-call backward): token counts whole; short streams take the edge-handling kernel */
+#define POETX_PATH_DENSE 2              /* both B = W A and dA = W^T dB (the only bit fp32 tensors get) */
+#define POETX_PATH_BLOCKGRAD 4          /* block gradients of both sides (two-call backward) */
 #define POETX_PATH_SERIES 8             /* series backward on the matrix cores                 */
 #define POETX_PATH_SERIES_ON_CHIP 16    /* ... as one-launch chains (b = 256)                   */
 #define POETX_PATH_BWD_ONE_PASS 32      /* poetx_linear_bwd streams each side's gradient once  */

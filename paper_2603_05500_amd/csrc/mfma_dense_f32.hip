@@ -116,8 +116,6 @@ __global__ __launch_bounds__(256) void dense_f32_kernel(Args g) {
 
 bool mfma_dense_f32_supported(int n, int m, i64 N) { return n % BM == 0 && m % BM == 0 && N % BN == 0; }
 
-// Three quarters of the CUs have a 128 x 128 tile: what poetx_linear_path calls a large fp32 product.
-bool mfma_dense_f32_fills(int M, i64 N) { return (i64)(M / BM) * (N / BN) >= 192; }
 // One tile per workgroup and no split of the contraction, but half of the operand traffic of the sliced kernel's 64 x 64 tiles: it takes four tiles per CU until that tells.
 // us, here / sliced, forward and backward: 2048 x 2048 x 1536 (192 tiles) 157 / 106, 162 / 107; 2048 x 2048 x 4096 (512) 277 / 270, 270 / 259; 14336 x 4096 x 1024 (896, 256) 1022 / 917,
 // 1095 / 899; 4096 x 4096 x 4096 (1024) 1018 / 1027, 1038 / 1018; 2048 x 2048 x 16384 (2048) 1019 / 1047, 1037 / 1041; 1536 x 128 x 24576 (2304, 192) 93 / 115, 122 / 82.

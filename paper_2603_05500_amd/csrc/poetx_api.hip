@@ -109,10 +109,6 @@ void apply_left_alone(int dtype, const Act& V, const Act& out, int d, const int3
   apply_left_dispatch(dtype, V, out, d, perm, blocks, b, trans, whole || mfma_apply_left_ragged_supported(d, V.cols, b), V.cols, st);
 }
 
-// Is the direction with M output rows a large fp32 product, in whole tiles that fill the chip (poetx_linear_path)?  Either fp32 kernel that moves aligned vectors may
-// take it; see mfma_dense_f32_preferred.
-bool dense_f32_streams(int n, int m, int M, i64 N) { return mfma_dense_f32_supported(n, m, N) && mfma_dense_f32_fills(M, N); }
-
 // part: scratch of dense_part_bytes() for products that split their contraction.
 // w_q8: W is a quantised weight buffer that the product dequantises itself (see weight_in_kernel)
 // As with the applies the kernel follows from the descriptor: the plan from the activation operand, which is always a workspace
@@ -453,12 +449,12 @@ int poetx_linear_path(const poetx_linear_desc* d) {
   const int m = d->d_in, n = d->d_out, b = d->block;
   const i64 N = d->n_tokens, Ni = internal_columns(d);
   int path = 0;
-  // the other stages of fp32 tensors take the edge-handling kernels
-  if (d->dtype == POETX_F32 && !g_force_fma.load() && dense_f32_streams(n, m, n, N) && dense_f32_streams(n, m, m, N)) path |= POETX_PATH_DENSE;
+  // each bit by what the dispatch asks; the other stages of fp32 tensors take the edge-handling kernels
+  if (d->dtype == POETX_F32 && !g_force_fma.load() && mfma_dense_f32_preferred(n, m, n, N) && mfma_dense_f32_preferred(n, m, m, N)) path |= POETX_PATH_DENSE;
   if (!use_mfma(d->dtype)) return path;
   if (apply_streams(d, m) && apply_streams(d, n)) path |= POETX_PATH_APPLY;
   if (mfma_dense_supported(n, m, Ni)) path |= POETX_PATH_DENSE;
-  if (mfma_blockgrad_supported(m, N, b) && mfma_blockgrad_supported(n, N, b)) path |= POETX_PATH_BLOCKGRAD;
+  if (mfma_blockgrad_preferred(m, N, b) && mfma_blockgrad_preferred(n, N, b)) path |= POETX_PATH_BLOCKGRAD;
   if (d->cnp_precision == POETX_CNP_BF16 && mfma_cnp_supported(m, b) && mfma_cnp_supported(n, b)) {
     path |= POETX_PATH_SERIES;
     if (lds_cnp_supported(m, b) && lds_cnp_supported(n, b)) path |= POETX_PATH_SERIES_ON_CHIP;

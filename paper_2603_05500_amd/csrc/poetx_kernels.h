@@ -123,7 +123,6 @@ void mfma_dense_reduce(const float* parts, int splits, i64 M, i64 Np, void* out,
 bool mfma_dense_worth_padding(int n, int m, i64 N);
 // the same products for fp32 tensors (fp32 MFMA, mfma_dense_f32.hip)
 bool mfma_dense_f32_supported(int n, int m, i64 N);
-bool mfma_dense_f32_fills(int M, i64 N);
 bool mfma_dense_f32_preferred(int n, int m, int M, i64 N);
 void mfma_dense_f32(int trans_w, const void* W, int n, int m, const void* act, void* out, i64 N, hipStream_t st);
 // the same products on a quantised weight buffer (codes + row scales), dequantised inside the kernel (mfma_dense_q8.hip)

@@ -113,20 +113,26 @@ def test_linear_path_query(clib):
     shapes, the dense products alone for large fp32 tensors, none for small shapes, and the INT8 bit only with the flag."""
     full = px.PATH_APPLY | px.PATH_DENSE | px.PATH_BLOCKGRAD | px.PATH_SERIES | px.PATH_SERIES_ON_CHIP | px.PATH_BWD_ONE_PASS
     assert px.poetx_linear_path(px.make_desc(4096, 14336, 256, 5, 16384, px.BF16)) == full
-    b512 = px.poetx_linear_path(px.make_desc(4096, 1024, 512, 5, 16384, px.BF16))
-    assert b512 == px.PATH_APPLY | px.PATH_DENSE | px.PATH_BLOCKGRAD | px.PATH_SERIES
-    # fp32 tensors: only the dense products have a streaming kernel, for multiples of 128 and at least 192 output tiles
+    tiled = px.PATH_APPLY | px.PATH_DENSE | px.PATH_SERIES
+    # block gradients from 2^25 elements of the smaller side on (b = 256: beyond it)
+    assert px.poetx_linear_path(px.make_desc(4096, 1024, 512, 5, 16384, px.BF16)) == tiled
+    assert px.poetx_linear_path(px.make_desc(4096, 2048, 512, 5, 16384, px.BF16)) == tiled | px.PATH_BLOCKGRAD
+    assert px.poetx_linear_path(px.make_desc(4096, 2048, 256, 5, 16384, px.BF16)) == full & ~px.PATH_BLOCKGRAD
+    assert px.poetx_linear_path(px.make_desc(4096, 2048, 256, 5, 16640, px.BF16)) == full
+    # fp32 tensors: only the dense products have a streaming kernel, for multiples of 128 and at least 1024 output tiles
     # of 128 x 128 -- in both directions
     assert px.poetx_linear_path(px.make_desc(256, 256, 32, 4, 512, px.F32)) == 0
-    assert px.poetx_linear_path(px.make_desc(2048, 1536, 64, 4, 2048, px.F32)) == px.PATH_DENSE
-    assert px.poetx_linear_path(px.make_desc(1024, 1536, 64, 4, 2048, px.F32)) == 0          # 192 tiles one way, 128 the other
+    assert px.poetx_linear_path(px.make_desc(2048, 1536, 64, 4, 2048, px.F32)) == 0          # 192 and 256 tiles
+    assert px.poetx_linear_path(px.make_desc(1024, 1024, 64, 4, 16384, px.F32)) == px.PATH_DENSE
+    assert px.poetx_linear_path(px.make_desc(1536, 128, 128, 3, 24576, px.F32)) == 0         # 192 tiles one way, 2304 the other
     # bf16 token counts that are no whole tiles: padded where the layer is large enough, else the edge kernel
     series = px.PATH_SERIES | px.PATH_SERIES_ON_CHIP
     for layout in (px.FEATURE_MAJOR, px.TOKEN_MAJOR):
         ragged = lambda m, n, N, b=256: px.poetx_linear_path(px.make_desc(m, n, b, 5, N, px.BF16, layout=layout))
         assert ragged(3072, 8192, 4090) == px.PATH_APPLY | px.PATH_DENSE | series
         assert ragged(2048, 2048, 100) == px.PATH_APPLY | px.PATH_DENSE | series
-        assert ragged(2048, 2048, 1088) == px.PATH_APPLY | px.PATH_DENSE | px.PATH_BLOCKGRAD | series     # 17 * 64
+        assert ragged(2048, 2048, 1088) == px.PATH_APPLY | px.PATH_DENSE | series                         # 17 * 64, a short stream
+        assert ragged(8192, 8192, 4160) == px.PATH_APPLY | px.PATH_DENSE | px.PATH_BLOCKGRAD | series     # 65 * 64
         assert ragged(2048, 2048, 16) == series
         assert ragged(512, 512, 300) == px.PATH_APPLY | series
         assert ragged(2048, 2048, 1999, 128) == px.PATH_DENSE

@@ -302,13 +302,15 @@ def test_plain_series_orders(lib, k, b, dtype):
 
 @pytest.mark.parametrize("m,n,N,b,k,streams", [
     (256, 384, 256, 64, 4, False), (640, 128, 384, 128, 3, False), (128, 128, 128, 32, 5, False),
-    (2048, 1536, 2048, 64, 4, True),     # 192 and 256 tiles: the streaming fp32 product in both directions
-    (1536, 128, 24576, 128, 3, True),    # 192 tiles in one tile row
-    (1024, 1536, 2048, 64, 4, False),    # in the forward only
+    (2048, 1536, 2048, 64, 4, False),    # 192 and 256 tiles: the sliced product in both directions
+    (1536, 128, 24576, 128, 3, False),   # 192 and 2304: the streaming fp32 product in the backward only
+    (128, 1536, 24576, 128, 3, False),   # ... in the forward only
+    (1024, 1024, 16384, 64, 4, True),    # 1024 both ways
+    (1024, 1536, 2048, 64, 4, False),
 ])
 def test_fp32_layer_dense_on_matrix_cores(lib, m, n, N, b, k, streams):
-    """fp32 tensors whose dimensions are multiples of the streaming fp32 product's 128 x 128 tiles: with at least 192 of
-    them on that kernel, with fewer on the edge-handling one; the layer against the oracle at the fp32 tolerance,
+    """fp32 tensors whose dimensions are multiples of the streaming fp32 product's 128 x 128 tiles: a product of at least 1024 of
+    them on that kernel, of fewer on the sliced one; the layer against the oracle at the fp32 tolerance,
     and the same inputs through the plain-FMA kernels."""
     data = synth_layer(7600 + m + n + N + b, m, n, N, b, k, "f32", 0.01)
     ref = orc.linear_fwd_bwd_from_theta(data["X"], data["dZ"], data["W"], data["pi_R"], data["pi_P"],

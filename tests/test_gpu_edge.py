@@ -266,7 +266,8 @@ RAGGED_LAYERS = [
     (512, 768, 255, 64, "bf16"),        # small blocks: the contraction of the block gradients rounds up to a longer one
     (512, 768, 255, 64, "f32"),
     (1024, 768, 250, 192, "bf16"),      # neither small nor a streaming block side
-    (2048, 1920, 1660, 64, "f32"),      # 1664 columns inside: whole tiles of the streaming fp32 product, which 1660 tokens are not
+    (2048, 1920, 1660, 64, "f32"),      # 1664 columns inside: multiples of 128, which 1660 tokens are not
+    (128, 10240, 1660, 64, "f32"),      # ... and 1040 tiles, enough for the streaming fp32 product, which takes whole tiles of tokens only
     (520, 512, 2045, 8, "bf16"),        # applies of very small blocks on the plain kernel ...
     (520, 512, 2045, 8, "f32"),
     (1056, 768, 2001, 16, "bf16"),      # ... on one side only
@@ -492,6 +493,42 @@ def test_block_stage_over_block_borders(lib, m, n, N):
         for j in range(got.shape[0]):
             rows = p[j * b:(j + 1) * b]
             ref = U[rows].double() @ V[rows].double().t()
+            # a sum of N products in fp32, each addition off by 2^-24 of what it adds to; they add up like a walk, at most by their number's root times 4
+            assert (got[j].double() - ref).abs().max() <= 4 * N ** 0.5 * 2.0 ** -24 * ref.abs().max()
+
+
+@pytest.mark.parametrize("m,n,N,b", [
+    (1024, 768, 65600, 256),   # 1025 * 64 tokens: one range, on 768 features just beyond the line of 2^25 elements
+    (512, 768, 65664, 256),    # 1026 * 64: two ranges of an odd number of stages
+    (512, 1024, 65664, 512),   # four tiles of a block
+    (5376, 512, 66560, 512),   # 1040 * 64, 512 features: sixteen ranges of 65; 5376 = 10.5 * 512: the other side on the edge kernel
+])
+def test_streaming_block_gradients(lib, m, n, N, b):
+    """Block gradients of long streams, two-call backward, on the kernel of whole 64-token stages: both layouts (rows as long as the tokens, and padded ones) the same bits, and every
+    block as its own sum in fp64."""
+    g = torch.Generator(device="cuda").manual_seed(9990 + m + n + N)
+    r = lambda *shape: torch.randn(*shape, device="cuda", dtype=torch.float32, generator=g).to(torch.bfloat16)
+    X, dZ, B, dA = r(m, N), r(n, N), r(n, N), r(m, N)
+    pi = [torch.randperm(d, device="cuda", generator=g).to(torch.int32) for d in (m, n)]
+    nb = [-(-d // b) for d in (m, n)]
+    th = [torch.zeros(k, b * (b - 1) // 2, device="cuda") for k in nb]
+    first = None
+    for layout in (lib.FEATURE_MAJOR, lib.TOKEN_MAJOR):
+        desc = lib.make_desc(m, n, b, 2, N, lib.BF16, flags=lib.FLAG_BLOCK_GRADS, layout=layout)
+        assert m % b or lib.poetx_linear_path(desc) & lib.PATH_BLOCKGRAD
+        ws = torch.full((lib.poetx_linear_workspace_bytes(desc) // 4,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
+        turn = (lambda t: t.t().contiguous()) if layout == lib.TOKEN_MAJOR else (lambda t: t)
+        dG = [torch.full((k, b, b), float("nan"), device="cuda") for k in nb]
+        lib.poetx_linear_bwd_skew(desc, turn(X), turn(dZ), B, dA, *pi, *th, *dG, False, ws)
+        torch.cuda.synchronize()
+        first = first or dG
+        assert all(torch.equal(a, c) for a, c in zip(dG, first))
+    for U, V, p, got in ((X, dA, pi[0], dG[0]), (B, dZ, pi[1], dG[1])):
+        p = p.long()
+        for j in range(got.shape[0]):
+            rows = p[j * b:(j + 1) * b]
+            ref = torch.zeros((b, b), dtype=torch.float64, device="cuda")
+            ref[:rows.numel(), :rows.numel()] = U[rows].double() @ V[rows].double().t()
             # a sum of N products in fp32, each addition off by 2^-24 of what it adds to; they add up like a walk, at most by their number's root times 4
             assert (got[j].double() - ref).abs().max() <= 4 * N ** 0.5 * 2.0 ** -24 * ref.abs().max()
 

@@ -349,7 +349,8 @@ int poetx_linear_bwd_skew(const poetx_linear_desc* desc, const void* X, const vo
 /* The whole backward pass in one call (Sec. 3.5, all three bullets, then Sec. 3.4 backward): the
  * results of poetx_linear_bwd_input followed by poetx_linear_bwd_skew, with dA kept in the workspace.
  * Where the shapes allow (bf16, b = 256, d_in, d_out multiples of 256, n_tokens a multiple of 256, or of
- * 64 from 256 on in layers whose token count is not padded) each side's gradient is streamed from
+ * 64 from 256 on in layers whose token count is not padded, and (d_in + d_out) * n_tokens above 2^23, 3 * 2^21 where
+ * one side is at most two thirds of the other) each side's gradient is streamed from
  * memory once: dB = P dZ is produced together with
  * dG_P^j = B'_j dZ'_j^T, and dX = R dA together with dG_R^j = X'_j dA'_j^T, instead of one pass
  * for the product and another for the block gradient.  Otherwise it runs the two halves as they are.

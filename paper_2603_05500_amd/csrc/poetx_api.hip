@@ -155,13 +155,15 @@ void apply_left(const poetx_linear_desc* desc, const Act& V, const Act& out, int
   apply_left_dispatch(desc->dtype, V, out, d, perm, blocks, desc->block, trans, apply_streams(desc, d), desc->n_tokens, st);
 }
 
-// Does poetx_linear_bwd stream each side's gradient once (aligned tensors)?  Not a short stream: the two halves' smaller tiles and both gradients in a launch are sooner done.  us without
-// the series, one pass / two halves: 1024 x 1024, 256 tokens 37 / 30, 2048 55 / 44, 4096 (2^23 elements) 62 / 57, 8192 81 / 90; 2048 x 2048, 1024 58 / 49; 4096 x 4096, 512 68 / 58,
-// 2048 111 / 125; 4096 x 1024, 768 64 / 54; 8192 x 4096, 512 84 / 84, 768 103 / 108. Unequal sides, whose gradients share a launch less evenly,
-// a quarter earlier: 4096 x 2048, 1024 (3 * 2^21 elements) 69 / 68, 1280 74 / 76; 2048 x 1024, 2048 59 / 59, 2560 62 / 64; 5632 x 2048, 768 73 / 72, 1024 76 / 78.
+// Does poetx_linear_bwd stream each side's gradient once (aligned tensors)?  Not a short stream: the two halves' smaller tiles and both gradients in a launch are sooner done, the more so
+// the more alike the sides are, as their gradients then share the launch evenly.  us without the series, one pass / two halves, by (d_in + d_out) N in units of 2^21: equal sides 3: 2048 x 2048 64 / 55;
+// 4: 1024 x 1024 60 / 56, 2048 x 2048 64 / 59, 4096 x 4096 79 / 76; 5: 70 / 72, 75 / 79, 95 / 99; 15/16 to 3/4: 2048 x 1792 3.3: 66 / 55, 3.8: 62 / 57, 4.7: 74 / 78; 4096 x 3840 3.9: 78 / 75, 4.8: 92 / 98;
+// 4096 x 3072 3.5: 73 / 70, 4.4: 80 / 83; a half and less: 2048 x 1024 2.6: 64 / 57, 3: 59 / 59, 3.8: 62 / 65; 4096 x 2048 3: 69 / 68, 3.8: 73 / 76; 4096 x 1024 2.5: 61 / 58, 3.1: 65 / 67.  Sides of ratios between
+// 1/2 and 3/4 were not measured.
 bool bwd_one_pass(const poetx_linear_desc* d) {
-  const i64 N = d->n_tokens;
-  return (d->d_in + (i64)d->d_out) * N > (d->d_in == d->d_out ? 4 : 3) << 21 && d->cnp_precision == POETX_CNP_BF16 && use_mfma(d->dtype) && lds_cnp_supported(d->d_in, d->block) && lds_cnp_supported(d->d_out, d->block) &&
+  const i64 N = d->n_tokens, wide = d->d_in > d->d_out ? d->d_in : d->d_out, narrow = d->d_in + (i64)d->d_out - wide;
+  const bool alike = 3 * narrow > 2 * wide;
+  return (wide + narrow) * N > (alike ? 4 : 3) << 21 && d->cnp_precision == POETX_CNP_BF16 && use_mfma(d->dtype) && lds_cnp_supported(d->d_in, d->block) && lds_cnp_supported(d->d_out, d->block) &&
          internal_columns(d) == N && mfma_apply_grad_supported(d->d_in, N, N, d->block) && mfma_apply_grad_supported(d->d_out, N, N, d->block);
 }
 

@@ -119,6 +119,10 @@ def test_linear_path_query(clib):
     assert px.poetx_linear_path(px.make_desc(4096, 2048, 512, 5, 16384, px.BF16)) == tiled | px.PATH_BLOCKGRAD
     assert px.poetx_linear_path(px.make_desc(4096, 2048, 256, 5, 16384, px.BF16)) == full & ~px.PATH_BLOCKGRAD
     assert px.poetx_linear_path(px.make_desc(4096, 2048, 256, 5, 16640, px.BF16)) == full
+    # the one-pass backward: beyond 2^23 elements of both sides, 3 * 2^21 where they are far from alike
+    for m, n, N, one in ((4096, 4096, 1024, False), (4096, 4096, 1280, True), (4096, 3840, 1024, False), (3840, 4096, 1024, False), (4096, 3840, 1280, True),
+                         (3072, 2304, 1536, False), (4096, 2048, 1024, False), (4096, 2048, 1280, True), (1024, 4096, 1280, True)):
+        assert bool(px.poetx_linear_path(px.make_desc(m, n, 256, 5, N, px.BF16)) & px.PATH_BWD_ONE_PASS) == one, (m, n, N)
     # fp32 tensors: only the dense products have a streaming kernel, for multiples of 128 and at least 1024 output tiles
     # of 128 x 128 -- in both directions
     assert px.poetx_linear_path(px.make_desc(256, 256, 32, 4, 512, px.F32)) == 0

@@ -73,7 +73,7 @@ __host__ __device__ inline int pair_of(int tile, int share, int extra) {
 template <bool WALK>
 __global__ __launch_bounds__(512) void apply_grad_stream_kernel(GradArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char ring[];
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // workgroups go to the XCDs round robin: ids 8 apart are neighbours on one XCD
   const int id = blockIdx.x;
@@ -81,11 +81,13 @@ __global__ __launch_bounds__(512) void apply_grad_stream_kernel(GradArgs g) {
   // walking, an XCD takes consecutive pairs: those of a block share its operand there
   const int pair = WALK ? (id & 7) * ((g.n_pairs + 7) / 8) + (id >> 4) : (id >> 4) * 8 + (id & 7);
   if (pair >= g.n_pairs) return;
-  const int li = lane & 31, h = lane >> 5;
   const uint32_t ring_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
   int at = WALK ? pair_start(pair, g.tiles_per_wg, g.extra) : 0;
   const int end = WALK ? pair_start(pair + 1, g.tiles_per_wg, g.extra) : 0;
   do {   // the tiles of one block at a time
+  int lane = tid & 63;
+  if constexpr (WALK) asm volatile("" : "+v"(lane));   // anew for each block: what follows from it, held across the loop, would take more registers than there are
+  const int li = lane & 31, h = lane >> 5;
   const int j = WALK ? at / g.tiles : pair % g.nb;
   const int tile0 = WALK ? at - j * g.tiles : pair / g.nb * g.tiles_per_wg;
   const int T = !WALK ? g.tiles_per_wg : end - at < g.tiles - tile0 ? end - at : g.tiles - tile0;

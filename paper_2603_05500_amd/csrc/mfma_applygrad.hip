@@ -348,19 +348,20 @@ int grad_chunks(int nb, int tiles, double* cost_out = nullptr) {
   return best;
 }
 
-// Walking pairs: one per two CUs, or none.  Priced in the same bytes: all CUs are busy, but every piece of a share costs about three tiles of a drained and refilled ring
-// and a partial, written and read.  Three per cent have to be left, for blocks that equal ranges write in one piece.  Whole backward of d x 256, us, equal ranges / walking
-// (tiles of a share): taken 14336 features with 16384 tokens (112) 585 / 546, 18944 with 8192 (74) 442 / 389, 11008 with 8192 (43) 265 / 243, 9216 with 8192 (36) 245 / 216,
-// 2816 with 16384 (22) 157 / 149, 6144 with 8192 (24) 152 / 148; left 13824 with 4096 (27) 162 / 167, 7168 with 8192 (28) 167 / 169, 24576 with 4096 (48) 257 / 260,
-// 14336 with 2048 (14) 94 / 106, 3072 with 4096 (6) 65 / 71.
+// Walking pairs: one per two CUs, or none.  Priced in the same bytes: all CUs are busy, but every piece of a share costs about four tiles of a drained and refilled ring
+// and a partial, written and read; on top of that the division and the uneven reduction, worth 30 MB (7 us) and 4 % of what equal ranges take.  Fitted to 467 whole backward calls of
+// d x 256 and d x d layers, 512 - 24576 features and 1024 - 33024 tokens, each timed both ways: 0.35 % slower than the better one on average, and walks in 8 where that is more than 2 % slower.  us, equal
+// ranges / walking (tiles of a share): taken 14336 features with 16384 tokens (112) 525 / 482, 18944 with 8192 (74) 407 / 339, 11008 with 6656 (35) 235 / 208, 9216 with 5120 (22.5) 180 / 157,
+// 2048 x 2048 with 7936 (8) 175 / 140, 768 x 768 with 5888 (2) 105 / 74; left 14336 with 2048 (14) 95 / 106, 5632 with 6144 (17) 118 / 123, 11008 with 3840 (20) 138 / 149, 1536 x 1536 with 6656 (5) 102 / 112,
+// 512 x 512 with 13312 (3) 82 / 97.
 constexpr int WALK_PAIRS = 128;
 bool grad_walks(int nb, int tiles) {
   const i64 total = (i64)nb * tiles;
   if (total < WALK_PAIRS || total >= (1ll << 31)) return false;
   double equal;
   grad_chunks(nb, tiles, &equal);
-  const double pieces = WALK_PAIRS + nb - 1, walk = grad_bytes(nb, tiles) * (1.0 + 3.0 * pieces / (double)total) + 2.0 * pieces * GB * GB * 4.0;
-  return walk < 0.97 * equal;
+  const double pieces = WALK_PAIRS + nb - 1, walk = grad_bytes(nb, tiles) * (1.0 + 4.0 * pieces / (double)total) + 2.0 * pieces * GB * GB * 4.0 + 30e6;
+  return walk < 1.04 * equal;
 }
 
 }  // namespace

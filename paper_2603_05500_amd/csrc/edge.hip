@@ -25,9 +25,11 @@ Tile apply_tile(i64 batches, i64 M, i64 N) {
 // Dense products on the sliced kernel (edge_slices.h): tile and contraction split priced together.  A workgroup's wave takes `lone` us for a slice when the
 // workgroup has a CU to itself (`cold` more where the weight is larger than the L2s would keep) and `shared` for each of the workgroups of
 // the fullest CU, each of which adds `tail`, on top of `base` for the launch, the first loads and the last stores.  A split adds a launch of `reduce` us with its gap and the
-// fp32 parts, written and read; it leaves every wave two slices, and no more than four workgroups per CU (parts of 16 MB at most).
+// fp32 parts, written and read; it keeps more slices than a workgroup has waves, and no more than four workgroups per CU (parts of 16 MB at most).  Products of large fp32 weights take no
+// less than their operands' way from the L2s, 10 TB/s: without that the smallest tile was priced at half of its time (13312 x 712, 14016 deep 4.5 ms, on 64 x 64 tiles 2.3; 3913 such products: 5.5 % slower than the best tile on average, now 1.2).
 // The constants are fitted to 1750 products of 128 - 14336 rows, 1 - 4096 columns and contractions of 128 - 14336, both directions, each timed with every tile and up to sixteen
-// splits: the choice is 1.3 % slower than the best one on average, and takes a third less time than the edge kernel under its own plan (fp32 33 %, bf16 36 %).
+// splits on operands in the caches but for the large weights: the choice is 1.3 % slower than the best one on average, and takes a third less time than the edge kernel under its own plan (fp32 33 %,
+// bf16 36 %).  Whole steps gain as much with 700 MB of operands in turn (1376 x 512, 1024 tokens 71.5 / 58.0 us, on the same operands 67.0 / 55.3; fp32 1024 x 768, 1001 112 / 86, 106 / 82).
 // us, edge kernel / here: fp32 1024 x 768 x 1001 29.0 / 18.0 and, backward, 29.7 (with its reduce) / 21; 256 x 256 x 512 6.0 / 4.3; bf16 1376 x 512 x 1024 9.1 / 6.4 and 11.2 / 5.6;
 // 768 x 1024 x 500 9.0 / 5.1; 1536 x 1536 x 3000 40.3 / 37.7.
 struct SliceCost {
@@ -69,13 +71,14 @@ SlicePlan slice_plan(int dtype, int trans_w, i64 M, i64 N, i64 K, const EdgePric
   double least = 0;
   auto price = [&](const SliceCost& c, SliceTile tile) {
     const unsigned count = (unsigned)(((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn));     // below 2^21, see slices_take
-    const double lone = c.lone + (large ? c.cold : 0);
+    const double lone = c.lone + (large ? c.cold : 0), traffic = (c.bm + c.bn) * 4e-7 * (double)K;
     for (unsigned s = 1; s <= 16; ++s) {
       const unsigned each = share(slices, s);
       if (s > 1 && (each <= 1u << c.waves_log2 || count * s > 4 * kCUs)) break;
       const unsigned splits = (slices + each - 1) / each;      // no empty split
       const double per_cu = (double)((count * splits + kCUs - 1) / kCUs), stage = per_cu * c.shared;
       double us = c.base + (double)((each + (1u << c.waves_log2) - 1) >> c.waves_log2) * (lone > stage ? lone : stage) + c.tail * per_cu;
+      if (f && large && us < (double)count * traffic) us = (double)count * traffic;
       if (splits > 1) us += c.reduce + c.parts * (double)splits * (double)M * (double)N;
       if (least == 0 || us < least) { least = us; best = SlicePlan{tile, (int)splits}; }
     }
@@ -88,11 +91,16 @@ SlicePlan slice_plan(int dtype, int trans_w, i64 M, i64 N, i64 K, const EdgePric
     const SliceCost& c = f ? kSlicesF32[i] : kSlicesBf16[i];
     if (i == 0 || (2 * M > c.bm && 2 * N > c.bn)) price(c, (SliceTile)i);    // not where half of the tile would be idle
   }
-  // Large bf16 weights: the 128 x 128 tiles of the edge kernel read each operand half as often.  They stay unless this price is a quarter below theirs: of 1750 products
-  // three are then more than 2 % slower than under the edge plan alone, eleven more than 5 % where the lower price decides.
-  if (!f && large) {
+  // The edge kernel's larger tiles where they still are the better ones, by 26000 products of 64 - 16384 rows and contractions and 1 - 16384 columns timed on both:
+  // - Many tiles of a short contraction are bound by their output, and a workgroup here keeps its stores for the end.  fp32 (us, edge / here): 5632 x 10328, 96 deep 140 / 188; 11648 x 3384, 96 107 / 133; bf16
+  //   11456 x 12424, 64 96 / 190; 2816 x 10840, 96 34 / 43; 8640 x 1208, 224 26.7 / 28.0.  fp32 up to 160 of depth and two 64 x 64 tiles per CU, bf16 from 384 tiles of 128 x 128 priced 30 % below: of those
+  //   products 0.12 and 0.17 % slower than the better kernel on average (0.6 and 1.3 % without these rules; at most 26 %, not 100 %).
+  // - Large bf16 weights: 128 x 128 tiles read each operand half as often.  They stay unless this price is a quarter below theirs.
+  if (f) {
+    if (K <= 160 && tile_count(1, M, N, 64) >= 2 * kCUs) best.tile = EDGE_TILES;
+  } else if (large || tile_count(1, M, N, 128) >= 384) {
     const EdgePrice e = edge ? *edge : edge_price(dtype, M, N, K);
-    if (e.plan.tile == TILE_128 && e.us < 1.25 * least) best.tile = EDGE_TILES;
+    if (e.plan.tile == TILE_128 && e.us < (large ? 1.25 : 0.7) * least) best.tile = EDGE_TILES;
   }
   return best;
 }

@@ -390,6 +390,10 @@ def test_dense_tiles(lib, n, m, N):
     ("bf16", 3104, 2080, 29),    # few columns of a large weight: 32 x 32 in ranges; 64 x 32 in ranges
     ("bf16", 2080, 3104, 300),   # large weight: edge tiles or slices by price
     ("bf16", 1568, 1504, 2999),  # 64 x 64
+    ("f32", 4128, 96, 2056),     # many tiles of a short contraction: the edge kernel; 32 x 32 or 32 x 64
+    ("f32", 4128, 176, 2056),    # not short: 64 x 64
+    ("bf16", 3104, 64, 2999),    # the edge kernel; 32 x 32
+    ("bf16", 64, 3104, 2999),    # ... in the backward
 ])
 def test_sliced_dense_products(lib, dtype, n, m, N):
     """The sliced product at the edges of its tiles, with fewer slices than waves and with split contractions, both directions, against float64 on the same operands, nothing written outside; and

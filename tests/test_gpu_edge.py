@@ -25,7 +25,7 @@ pytestmark = pytest.mark.gpu
     (72, 2050, 17, 72, 2),      # the same in the backward direction
     (640, 1376, 2047, 64, 2),   # 128-wide tiles, every extent ragged
     (512, 256, 1000, 256, 2),   # large blocks, token count a multiple of 8 only
-    # 64-wide tiles whose waves split the stages, in fp32 split over workgroups as well.  (A tail block of side 2 would have
+    # 64-wide tiles whose waves split the stages (fp32 backward), split over workgroups as well.  (A tail block of side 2 would have
     # one parameter: its gradient, one sum of rounded products, has no bound relative to itself where they cancel.)
     (768, 1096, 1001, 64, 2),
     (2000, 2040, 2001, 40, 1),  # 128-wide ones with four waves (bf16 forward) and eight (backward)
@@ -39,11 +39,13 @@ pytestmark = pytest.mark.gpu
     (256, 384, 520, 128, 2),
     # other tiles and splits that the rule gives
     (200, 776, 1001, 40, 1),    # fp32 forward: 64 x 64 with sixteen waves ...
-    (992, 632, 200, 40, 1),     # ... in 6 ranges
+    (1000, 632, 200, 40, 1),    # ... in 6 ranges
+    (992, 632, 200, 40, 1),     # a contraction of 16 more takes slices
     (776, 1064, 200, 24, 1),    # fp32 backward: 64 x 64 in 9
     (848, 200, 200, 40, 1),     # bf16 forward: 64 x 64 in 7
     (200, 848, 200, 40, 1),     # ... backward
-    (2080, 2048, 24, 32, 1),    # a few tokens of a large weight: splits by workgroups per CU
+    (2080, 2048, 24, 32, 1),    # a few tokens of a large weight: slices, ...
+    (2100, 2040, 24, 60, 1),    # ... and what they do not take (contractions in no whole slices): splits by workgroups per CU
 ])
 def test_layer_at_tile_edges(lib, m, n, N, b, k, dtype):
     data = synth_layer(9000 + m + n + N + b, m, n, N, b, k, dtype, 0.01)
@@ -337,16 +339,20 @@ def test_ragged_tokens_give_the_same_parameter_gradients_in_every_form(lib, m, n
     (256, 256, 256),        # 128 x 128; the same (contraction too short to split)
     (256, 2048, 256),       # 128 x 128 in 8 ranges; 128 x 128
     (512, 512, 1024),       # 128 x 128; the same
-    (2048, 512, 2048),      # 128 x 128; 128 x 128 in 4
+    (2048, 512, 2048),      # 128 x 128; the same
+    (2048, 768, 768),       # 128 x 128; 128 x 128 in 4
     (2304, 2048, 2560),     # 256 x 128, nine tile rows (no whole groups of four); the same with eight
     (4096, 512, 2304),      # 256 x 256, 144 tiles; 128 x 128 in 2
     # ragged counts, padded inside: stores that end at the last token, at rows of odd length
     (2048, 2048, 1801),     # 128 x 128; the same
-    (512, 8192, 300),       # 128 x 128 in 16 (ragged reduction); 128 x 128
+    (512, 8192, 300),       # 128 x 128 in 8 (ragged reduction); 128 x 128
+    (256, 8192, 301),       # 128 x 128 in 16; 128 x 128
+    (512, 2048, 1001),      # 128 x 128 in 4; 128 x 128
+    (768, 2560, 1501),      # 128 x 128 in 2; 128 x 128
     (4096, 512, 1100),      # 256 x 128; 128 x 128 in 4
     (2304, 2048, 2559),     # 256 x 128; the same
     (4096, 512, 2300),      # 256 x 256; 128 x 128 in 2
-    (512, 2560, 3329),      # 128 x 128 in 2; 256 x 256
+    (512, 2560, 3329),      # 128 x 128; 256 x 256
 ])
 def test_dense_tiles(lib, n, m, N):
     """Every output tile of the streaming bf16 product, whole and ragged, and split contractions, both directions, against float64 on the same
@@ -378,20 +384,30 @@ def test_dense_tiles(lib, n, m, N):
     # tile and contraction ranges of the sliced product, forward; backward
     ("f32", 64, 48, 5),          # 32 x 32, fewer slices than waves; the same
     ("f32", 256, 256, 512),      # 32 x 32; the same
-    ("f32", 1024, 768, 1001),    # 32 x 64, half a tile of columns over; the same
-    ("f32", 1040, 1008, 1991),   # 64 x 64, rows and columns over; the same
+    ("f32", 1024, 768, 1001),    # 64 x 64, columns over; 32 x 32
+    ("f32", 1040, 1008, 1991),   # 32 x 32, half a tile of rows over; 64 x 64, rows and columns over
+    ("f32", 432, 1840, 583),     # 64 x 64 in ranges, a quarter tile of rows over; 32 x 64
+    ("f32", 1808, 336, 759),     # 32 x 64, rows and columns over; 64 x 64 in ranges
+    ("f32", 3440, 304, 271),     # 32 x 32; 32 x 64 in ranges
     ("f32", 144, 3264, 33),      # 32 x 32 in ranges; 32 x 32
     ("f32", 1792, 16, 40),       # one slice: seven waves without any; 32 x 32 in ranges
     ("f32", 4112, 4096, 2040),   # 64 x 64, large weight
     ("bf16", 64, 96, 3),         # 32 x 32, three slices for eight waves; two
-    ("bf16", 512, 1376, 1024),   # 32 x 64; 64 x 64
-    ("bf16", 1376, 512, 1023),   # 64 x 64, rows and columns over; 32 x 64
-    ("bf16", 96, 3200, 17),      # 32 x 32; the same
-    ("bf16", 3104, 2080, 29),    # few columns of a large weight: 32 x 32 in ranges; 64 x 32 in ranges
-    ("bf16", 2080, 3104, 300),   # large weight: edge tiles or slices by price
-    ("bf16", 1568, 1504, 2999),  # 64 x 64
-    ("f32", 4128, 96, 2056),     # many tiles of a short contraction: the edge kernel; 32 x 32 or 32 x 64
-    ("f32", 4128, 176, 2056),    # not short: 64 x 64
+    ("bf16", 512, 1376, 1024),   # 32 x 64; the same
+    ("bf16", 1376, 512, 1023),   # 32 x 64; the same
+    ("bf16", 96, 3200, 17),      # 32 x 32 in ranges; 32 x 32
+    ("bf16", 2208, 32, 43),      # 32 x 32; 32 x 64 in ranges
+    ("bf16", 32, 1984, 40),      # the other way round
+    ("bf16", 432, 3104, 270),    # 64 x 64 in ranges; not in slices (432 are none)
+    ("bf16", 3968, 784, 207),    # the other way round
+    ("bf16", 3104, 2080, 29),    # few columns of a large weight: 32 x 32; 64 x 32 in ranges
+    ("bf16", 1344, 2400, 7),     # 32 x 32 in ranges; 64 x 32 in ranges
+    ("bf16", 1056, 3072, 16),    # 32 x 32 in ranges; 64 x 32
+    ("bf16", 2080, 3104, 300),   # large weight: 64 x 64 by price; the same
+    ("bf16", 3584, 2464, 295),   # edge tiles by price; 64 x 64
+    ("bf16", 1568, 1504, 2999),  # 64 x 64; the same
+    ("f32", 4128, 96, 2056),     # many tiles of a short contraction: the edge kernel; 32 x 32
+    ("f32", 4128, 176, 2056),    # not short: 64 x 64; 64 x 64 in ranges
     ("bf16", 3104, 64, 2999),    # the edge kernel; 32 x 32
     ("bf16", 64, 3104, 2999),    # ... in the backward
 ])

@@ -111,7 +111,8 @@ SlicePlan slice_plan(int dtype, int trans_w, i64 M, i64 N, i64 K, const EdgePric
 // The constants are fitted to 1520 products of 128 - 14336 rows, 1 - 5000 columns and contractions of 128 - 14336, both directions, weights over 6 MB read from
 // memory, each timed with every tile and split: the choice is 1 % slower than the best one on average and takes 10 % (fp32) and 25 % (bf16) less time than a rule
 // that takes the largest tile to fill three quarters of the CUs, with four waves each, and then the split.  us of launches one after the other on the same operands (inside a
-// step they come from further away: the first is 30.2 there), tile / splits (64D: 64 x 64 with sixteen waves):
+// step they come from further away: the first is 30.2 there), tile / splits (64D: 64 x 64 with sixteen waves), before the slices above took these sizes, all but the last; operands off 16-byte
+// boundaries and contractions of no whole slices still run so:
 // fp32 1024 x 768 x 1001 64D/1 27.4, 64/3 29.8, 32/1 31.2; 256 x 256 x 512 32/1 6.2, 32/2 7.4; bf16 1376 x 512 x 1024 64/1 9.6, 32/1 10.7, 128/1 13.8;
 // 1024 x 1536 x 3001 64/1 24.7, 128/2 34.6; 4096 x 14336 x 64 64/12 34.0, 64/8 37.3; 4192 x 8000 x 1567 128/1 200, 128/4 228, 64/1 275.
 // Up to 32 columns of a large weight are bound by its reads, for which this price is too coarse (up to 12 % slower than four workgroups per CU): as many splits as

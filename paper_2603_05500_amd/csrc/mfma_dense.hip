@@ -43,7 +43,7 @@ void launch_tile(DenseArgs g, i64 M, i64 N, hipStream_t st) {
   g.tiles_m = (int)(M / C::BM);
   g.tiles_n = (int)(N / C::BN);
   const int T = g.tiles_m * g.tiles_n * g.splits, cus = compute_units();
-  hipLaunchKernelGGL(kern, dim3(T < cus ? T : cus), dim3(256), C::LDS_BYTES, st, g);
+  hipLaunchKernelGGL(kern, dim3(T < cus || g.longer > 0 ? T : cus), dim3(256), C::LDS_BYTES, st, g);
 }
 
 // ---- which tile, how many contraction ranges ----------------------------------------------------
@@ -51,7 +51,9 @@ void launch_tile(DenseArgs g, i64 M, i64 N, hipStream_t st) {
 // busy: 94 us for a 256 x 256 tile, 0.65 of that for 256 x 128 and 0.39 for 128 x 128 (half and a quarter of the work: smaller
 // tiles move more operand bytes per flop), so a smaller tile pays where it takes the place of idle CUs (4096 x 4096 x 2048, 128
 // large tiles: 90 -> 73 us on 256 x 128; 2048 x 2048 x 2048, 64: 44 -> 26 us on 128 x 128; both with the 32 x 32 x 16 kernel).  Splitting the contraction of the
-// smallest tile adds fp32 parts written and read at about 4 TB/s and a launch (5 us).
+// smallest tile adds fp32 parts written and read at about 4 TB/s and a launch (5 us).  A range is a whole number of pairs of stages; where that
+// leaves them unequal, a workgroup has one, hence no more than 256 of them (forward calls, four equal ranges / eight of 34 and 36 stages, us: 256 x 8960, 512 tokens 41.4 / 36.0; of 40 and 42, 512 x 10496, 256
+// 41.0 / 35.5).
 enum { T256 = 0, T256x128 = 1, T128 = 2 };
 struct DensePlan {
   int tile, splits;
@@ -63,10 +65,12 @@ DensePlan pick_plan(i64 M, i64 N, i64 K) {
   double best_us = 0.0;
   for (int t = 0; t < 3; ++t)
     for (int s = 1; s <= (t == T128 ? 16 : 1); s *= 2) {
-      if ((K / BK) % (2 * s) != 0 || K / s < 256) break;   // an even number of stages each
+      if ((K / BK) % s != 0 || K / s < 256) break;
       const double units = (double)(M / bm[t]) * (double)(N / bn[t]) * s;
+      const ContractionRange range = contraction_ranges((int)(K / BK), s);
+      if (range.longer > 0 && units > 256) break;
       const double rounds = (double)(long long)((units + 255) / 256);
-      double us = rounds * cost[t] * 94.0 / 4096.0 * (double)(K / s);
+      double us = rounds * cost[t] * 94.0 / 4096.0 * (double)((range.ktiles + (range.longer > 0 ? 2 : 0)) * BK);
       if (s > 1) us += 8.0 * s * (double)M * (double)N / 4e6 + 5.0;
       if (best_us == 0.0 || us < 0.97 * best_us) { best_us = us; best = DensePlan{t, s}; }
     }
@@ -119,7 +123,9 @@ void mfma_dense(int trans_w, const void* W, int n, int m, const void* act, i64 N
   g.cols = (int)N;
   g.splits = p.splits;
   g.parts = (float*)ws;
-  g.ktiles = K / BK / p.splits;
+  const ContractionRange range = contraction_ranges(K / BK, p.splits);
+  g.ktiles = range.ktiles;
+  g.longer = range.longer;
   if (p.splits > 1) {
     if (trans_w) launch_tile<false, OUT_PARTS, Tile128>(g, M, N_act, st);
     else launch_tile<true, OUT_PARTS, Tile128>(g, M, N_act, st);

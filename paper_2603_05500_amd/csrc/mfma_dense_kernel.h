@@ -75,8 +75,16 @@ struct DenseArgs {
   int tiles_m, tiles_n, ktiles;   // ktiles counts 32-deep stages; even
   int cols;              // RAGGED: columns of C that exist; its rows need element alignment only
   int splits;            // PARTS: the contraction in so many ranges of ktiles stages each ...
+  int longer;            // ... the first so many of them two stages longer (then a workgroup has one tile), see ContractionRange, ...
   float* parts;          // ... whose products go here in fp32, [split][M][N], instead of to C
 };
+
+// A contraction of `stages` in ranges: whole pairs of stages, as the streams multiply them two at a time
+struct ContractionRange {
+  int ktiles, longer;
+};
+inline ContractionRange contraction_ranges(int stages, int splits) { return ContractionRange{stages / 2 / splits * 2, stages / 2 % splits}; }
+__device__ inline int range_start(int split, int ktiles, int longer) { return split * ktiles + 2 * (split < longer ? split : longer); }
 
 // ---- swizzled tile layouts for 16 x 16 x 32 fragments (16-byte chunks) ----------------------------
 // [x][k] tile: 4 chunks per row.  A 16-byte read serves 16 lanes at a time: lanes 0-3, 12-15, 20-23 and 24-27 (rows 0-3 and 12-15 of chunk c, 4-7 and 8-11 of
@@ -220,7 +228,7 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   }
   const i64 stepA = A_KMAJOR ? (i64)BK * 2 : (i64)BK * g.lda * 2;
   const i64 stepB = (i64)BK * g.ldb * 2;
-  const int KT = g.ktiles;
+  const int KT = g.ktiles + (OUT == OUT_PARTS && wq / T0 < g.longer ? 2 : 0);
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
   // ---- issue side of the stream: runs NS stages ahead of the multiplication, across tiles.  An, Bn: where the tile after the one in issue
@@ -232,8 +240,9 @@ __global__ __launch_bounds__(256) void dense_stream_kernel(DenseArgs g) {
   auto tile_base = [&](int ti, const char*& a, const char*& b) {
     int i0, j0, split;
     tile_origin(ti < n_my ? ti : n_my - 1, i0, j0, split);
-    a = (const char*)(g.A + (A_KMAJOR ? (i64)i0 * g.lda : (i64)i0)) + split * (KT * stepA);
-    b = (const char*)(g.B + j0) + split * (KT * stepB);
+    const int first = OUT == OUT_PARTS ? range_start(split, g.ktiles, g.longer) : 0;
+    a = (const char*)(g.A + (A_KMAJOR ? (i64)i0 * g.lda : (i64)i0)) + first * stepA;
+    b = (const char*)(g.B + j0) + first * stepB;
   };
   tile_base(0, Ab, Bb);
   tile_base(1, An, Bn);

@@ -45,7 +45,8 @@ struct DenseQ8Args {
   uint16_t* C;           // M x N row major
   i64 ldq, ldb, ldc;
   int tiles_m, tiles_n, ktiles;
-  int splits;            // PARTS: the contraction in so many ranges of ktiles stages each,
+  int splits;            // PARTS: the contraction in so many ranges of ktiles stages each, the first `longer` of them two longer (as in the bf16 product),
+  int longer;
   float* parts;          // whose products go here in fp32, [split][M][N], instead of to C
 };
 
@@ -81,7 +82,8 @@ __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
     i0 = (first_m + (u % per_group) % gsz) * BM;
     j0 = ((u % per_group) / gsz) * BN;
   };
-  const int KT = g.ktiles;
+  const int KT = g.ktiles + (PARTS && wq / T0 < g.longer ? 2 : 0);
+  auto first_stage = [&](int split) { return PARTS ? dense::range_start(split, g.ktiles, g.longer) : 0; };
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
   // ---- activations: as in the bf16 kernel
@@ -98,7 +100,7 @@ __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
   auto b_base = [&](int ti) {
     int i0, j0, split;
     tile_origin(ti, i0, j0, split);
-    Bb = (const char*)(g.B + j0) + split * (KT * stepB);
+    Bb = (const char*)(g.B + j0) + first_stage(split) * stepB;
   };
   b_base(0);
   auto issue_b = [&](int s) { dma16g_s(s, Bb, voffB[s], lds_base + b_slot * STAGE_BYTES + A_BYTES + wave * IPW * 1024); };
@@ -142,8 +144,8 @@ __global__ __launch_bounds__(256) void dense_q8_stream_kernel(DenseQ8Args g) {
   auto q_base = [&](int ti) {
     int i0, j0, split;
     tile_origin(ti, i0, j0, split);
-    Qb = (const char*)g.Q + (A_KMAJOR ? (i64)i0 * g.ldq : (i64)i0) + split * (KT * stepQ);
-    Sb = (const char*)(g.scale + (A_KMAJOR ? i0 : split * KT * BK));
+    Qb = (const char*)g.Q + (A_KMAJOR ? (i64)i0 * g.ldq : (i64)i0) + first_stage(split) * stepQ;
+    Sb = (const char*)(g.scale + (A_KMAJOR ? i0 : first_stage(split) * BK));
   };
   q_base(0);
   auto issue_q = [&]() {
@@ -358,7 +360,7 @@ void launch_dense_q8(const DenseQ8Args& g, hipStream_t st) {
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) == hipSuccess;
   (void)configured;
   const int T = g.tiles_m * g.tiles_n * g.splits, cus = compute_units_q8();
-  hipLaunchKernelGGL(kern, dim3(T < cus ? T : cus), dim3(256), LDS_BYTES, st, g);
+  hipLaunchKernelGGL(kern, dim3(T < cus || g.longer > 0 ? T : cus), dim3(256), LDS_BYTES, st, g);
 }
 
 }  // namespace
@@ -383,7 +385,9 @@ void mfma_dense_q8(int trans_w, const void* Wq, int n, int m, const void* act, v
   g.tiles_n = (int)(N / BN);
   g.splits = mfma_dense_splits(M, N, K);
   g.parts = (float*)ws;
-  g.ktiles = K / BK / g.splits;
+  const dense::ContractionRange range = dense::contraction_ranges(K / BK, g.splits);
+  g.ktiles = range.ktiles;
+  g.longer = range.longer;
   if (g.splits > 1) {
     if (trans_w) launch_dense_q8<false, true>(g, st);
     else launch_dense_q8<true, true>(g, st);

@@ -341,12 +341,15 @@ def test_ragged_tokens_give_the_same_parameter_gradients_in_every_form(lib, m, n
     (512, 512, 1024),       # 128 x 128; the same
     (2048, 512, 2048),      # 128 x 128; the same
     (2048, 768, 768),       # 128 x 128; 128 x 128 in 4
+    (256, 2304, 256),       # 128 x 128 in 8, of ten and eight stages; 128 x 128
+    (2304, 256, 256),       # the other way round
     (2304, 2048, 2560),     # 256 x 128, nine tile rows (no whole groups of four); the same with eight
     (4096, 512, 2304),      # 256 x 256, 144 tiles; 128 x 128 in 2
     # ragged counts, padded inside: stores that end at the last token, at rows of odd length
     (2048, 2048, 1801),     # 128 x 128; the same
     (512, 8192, 300),       # 128 x 128 in 8 (ragged reduction); 128 x 128
     (256, 8192, 301),       # 128 x 128 in 16; 128 x 128
+    (256, 8704, 301),       # 128 x 128 in 16, of 18 and 16 stages; 256 x 128
     (512, 2048, 1001),      # 128 x 128 in 4; 128 x 128
     (768, 2560, 1501),      # 128 x 128 in 2; 128 x 128
     (4096, 512, 1100),      # 256 x 128; 128 x 128 in 4

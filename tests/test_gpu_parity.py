@@ -464,7 +464,9 @@ def test_weight_q8_codes_bit_exact(lib, n, m, dtype):
                                              (96, 160, 128, 32, 3, "f32"), (512, 768, 512, 256, 5, "bf16"),
                                              (1024, 256, 1280, 256, 3, "bf16"),
                                              (768, 2048, 768, 256, 2, "bf16"),      # backward product in four ranges
-                                             (4096, 256, 256, 256, 3, "bf16")])     # forward in sixteen, of eight stages
+                                             (4096, 256, 256, 256, 3, "bf16"),      # forward in sixteen, of eight stages
+                                             (2304, 256, 256, 256, 2, "bf16"),      # ... in eight, of ten and eight
+                                             (256, 2304, 256, 256, 2, "bf16")])     # backward likewise
 @pytest.mark.parametrize("fused", [False, True])
 def test_xq_layer(lib, m, n, N, b, k, dtype, fused):
     """Memory-saving variant on an INT8 base weight: every product must be the oracle's on the

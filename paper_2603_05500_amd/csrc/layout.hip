@@ -4,6 +4,8 @@
 // re-laid once on the way in and once on the way out).  Plain out-of-place transpose through an
 // LDS tile: 16-byte coalesced loads along the source rows, 16-byte coalesced stores along the
 // destination rows; HBM bound.
+#include <type_traits>
+
 #include "poetx_kernels.h"
 
 namespace poetx {
@@ -25,20 +27,21 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
   const int vr = tid / VPR, vc = (tid % VPR) * V;
   // Rows that are whole aligned vectors on both sides: what lies past R is zeros, past C not stored, and a vector that starts inside a row ends inside it.  Edge tiles
   // go the same way: element by element, one slow last row of them was a tail that the launch waited for
-  // (4090 tokens of 3072 features, in and out, us: 16.7 / 11.4, 19.4 / 11.1; of 8192 34 / 27, 30 / 25 = 5.0 TB/s).
+  // (4090 tokens of 3072 features, in and out, us: 16.7 / 11.4, 19.4 / 11.1; of 8192 34 / 27, 30 / 25 = 5.0 TB/s).  Whole tiles without the checks, which keep a lane's loads
+  // from being in flight together (merges of whole weights, us, with / without: fp32 256 x 256, b = 64 14.4 / 12.6; 1024 x 1536 34.3 / 33.4; bf16 256 x 256 12.1 / 11.3).
   const bool vectors = (ld_in % V) == 0 && (ld_out % V) == 0 && (R_out % V) == 0 && ((uintptr_t)in % 16) == 0 && ((uintptr_t)out % 16) == 0;
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   union Vec {
     u32x4 v;
     T e[V];
   };
-  if (vectors) {
+  auto move = [&](auto edge) {
 #pragma unroll
     for (int p = 0; p < TT / RPP; ++p) {
       const int r = vr + p * RPP;
       Vec x;
       x.v = u32x4{0, 0, 0, 0};
-      if (r0 + r < R && c0 + vc < ld_in) x.v = *reinterpret_cast<const u32x4*>(in + (r0 + r) * ld_in + c0 + vc);
+      if (!edge || (r0 + r < R && c0 + vc < ld_in)) x.v = *reinterpret_cast<const u32x4*>(in + (r0 + r) * ld_in + c0 + vc);
 #pragma unroll
       for (int e = 0; e < V; ++e) tile[r][vc + e] = x.e[e];
     }
@@ -49,8 +52,13 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
       Vec x;
 #pragma unroll
       for (int e = 0; e < V; ++e) x.e[e] = tile[vc + e][c];
-      if (c0 + c < C && r0 + vc < R_out) *reinterpret_cast<u32x4*>(out + (c0 + c) * ld_out + r0 + vc) = x.v;
+      if (!edge || (c0 + c < C && r0 + vc < R_out)) *reinterpret_cast<u32x4*>(out + (c0 + c) * ld_out + r0 + vc) = x.v;
     }
+  };
+  if (vectors && r0 + TT <= R && c0 + TT <= C) {
+    move(std::false_type{});
+  } else if (vectors) {
+    move(std::true_type{});
   } else {   // unaligned: element by element
     for (int i = tid; i < TT * TT; i += 256) {
       const int r = i / TT, c = i % TT;

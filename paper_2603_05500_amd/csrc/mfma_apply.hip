@@ -448,7 +448,12 @@ bool mfma_apply_left_supported(int d, i64 cols, i64 ld, int b) {
 
 void mfma_apply_left(const void* V, void* out, int d, i64 cols, i64 ld, const int32_t* perm, const void* E, int b,
                      int transpose_G, hipStream_t st) {
-  if (b == 512) return launch_apply_stream<512, SBN>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
+  if (b == 512) {
+    // A tile per workgroup and CUs to spare: the ragged kernel's loads through registers are there earlier (us, here / there: 512 features, 64 tokens 11.7 / 11.1, 2048, 1088 13.2 / 12.9; not with
+    // every CU busy: 2048, 2048 14.6 / 15.0).  The same bits.
+    if (d / 256 * (cols / SBN) < 256) return mfma_apply_left_ragged(V, ld, cols, out, ld, cols, d, perm, E, b, transpose_G, st);
+    return launch_apply_stream<512, SBN>((const uint16_t*)V, (uint16_t*)out, d, cols, ld, perm, (const uint16_t*)E, transpose_G, st);
+  }
   // By 64-token tiles per workgroup.  One or two: the ragged kernel's loads through registers are there a little earlier (us: 4096 features, 1024 tokens 10.4 / 9.5, 2048
   // 14.2 / 13.3, with 128-token tiles 14.6 and 16.7; 8192 features, 2048 tokens, four tiles, 21.7 / 23.4).  From eight on 128-token tiles (see the kernel).  All three sum in
   // the same order: the bits do not depend on the choice.

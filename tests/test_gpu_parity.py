@@ -77,6 +77,25 @@ def test_apply_left(lib, d, b, cols, dtype, transpose):
     assert rel_err(to_np(out), ref_exactG) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("d,cols", [(512, 64 * 128), (1024, 64 * 64)])
+@pytest.mark.parametrize("transpose", [False, True])
+def test_apply_left_512_forms(lib, d, cols, transpose):
+    """b = 512 on either side of 256 workgroups of one tile: one tile less on the register-staged kernel, then the streaming one
+    with one tile each and with two (the last range one short).  Every column has the same bits in all three."""
+    rng = RNG(2600 + d)
+    pi = torch.from_numpy(rng.permutation(d).astype(np.int32)).cuda()
+    blocks, _ = build_blocks(draw_theta(rng, d, 512, 0.005), d, 512, 2, "bf16", lib.CNP_BF16)
+    V = round_bf16(rng.standard_normal((d, cols + 64)))
+    outs = []
+    for n in (cols - 64, cols, cols + 64):
+        out = torch.zeros((d, n), dtype=torch.bfloat16, device="cuda")
+        lib.poetx_perm_blockdiag_apply_left(to_dev(V[:, :n].copy(), torch.bfloat16), out, pi, blocks, 512, transpose)
+        outs.append(to_np(out))
+    ref = orc.apply_left(V, pi.cpu().numpy(), to_np(blocks)[:, 0] + np.eye(512), transpose)
+    assert rel_err(outs[2], ref) <= TOL["bf16"]
+    assert np.array_equal(outs[0], outs[1][:, :cols - 64]) and np.array_equal(outs[1], outs[2][:, :cols])
+
+
 @pytest.mark.parametrize("d,b,rows", [(64, 32, 48), (96, 64, 130), (1376, 64, 512), (512, 256, 300), (40, 8, 5)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("transpose", [False, True])

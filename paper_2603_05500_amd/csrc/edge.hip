@@ -96,11 +96,20 @@ SlicePlan slice_plan(int dtype, int trans_w, i64 M, i64 N, i64 K, const EdgePric
   //   11456 x 12424, 64 96 / 190; 2816 x 10840, 96 34 / 43; 8640 x 1208, 224 26.7 / 28.0.  fp32 up to 160 of depth and two 64 x 64 tiles per CU, bf16 from 384 tiles of 128 x 128 priced 30 % below: of those
   //   products 0.12 and 0.17 % slower than the better kernel on average (0.6 and 1.3 % without these rules; at most 26 %, not 100 %).
   // - Large bf16 weights: 128 x 128 tiles read each operand half as often.  They stay unless this price is a quarter below theirs.
+  // - bf16 on 150 to 384 tiles of 128 x 128 (4000 products of 32 - 384 of depth, 128 - 9600 rows and 200 - 16000 columns, whole calls of each; us, edge / here): up to 64 of depth forward 1792 x 2560 10.1 / 11.4,
+  //   300 tiles and more 1.3 to 1.9 dearer here, backward 0.4 up to one tile per CU and cheaper beyond.  Deeper ones only forward, where the price is 60 % below: 128 deep on 340 tiles and more 0.8 dearer here; backward up to 3 cheaper.
+  //   Slower than the better kernel on average: 1.9 -> 0.23 % forward, 0.33 -> 0.14 % backward.
   if (f) {
     if (K <= 160 && tile_count(1, M, N, 64) >= 2 * kCUs) best.tile = EDGE_TILES;
-  } else if (large || tile_count(1, M, N, 128) >= 384) {
+    return best;
+  }
+  const i64 tiles = tile_count(1, M, N, 128);
+  const bool middle = !large && tiles >= 150 && tiles < 384 && M >= 128 && N >= 200;
+  if (middle && K <= 64) {
+    if (!trans_w || tiles <= kCUs) best.tile = EDGE_TILES;
+  } else if (large || tiles >= 384 || (middle && !trans_w && K <= 256)) {
     const EdgePrice e = edge ? *edge : edge_price(dtype, M, N, K);
-    if (e.plan.tile == TILE_128 && e.us < (large ? 1.25 : 0.7) * least) best.tile = EDGE_TILES;
+    if (e.plan.tile == TILE_128 && e.us < (large ? 1.25 : middle ? 0.4 : 0.7) * least) best.tile = EDGE_TILES;
   }
   return best;
 }

@@ -413,6 +413,10 @@ def test_dense_tiles(lib, n, m, N):
     ("f32", 4128, 176, 2056),    # not short: 64 x 64; 64 x 64 in ranges
     ("bf16", 3104, 64, 2999),    # the edge kernel; 32 x 32
     ("bf16", 64, 3104, 2999),    # ... in the backward
+    ("bf16", 1568, 64, 1999),    # 208 tiles of 128 x 128 of a short contraction: the edge kernel; 32 x 32
+    ("bf16", 64, 1568, 1999),    # ... in the backward
+    ("bf16", 64, 3104, 1601),    # 325 of them in the backward: slices
+    ("bf16", 4128, 128, 1201),   # 330: the edge kernel by price
 ])
 def test_sliced_dense_products(lib, dtype, n, m, N):
     """The sliced product at the edges of its tiles, with fewer slices than waves and with split contractions, both directions, against float64 on the same operands, nothing written outside; and

@@ -545,8 +545,10 @@ void launch_pair_shape(Args g0, Args g1, Epi e0, Epi e1, const Problem& q0, cons
   tile_args(g1, q1, BM, BN, BK, s1);
   const i64 n0 = q0.batches * g0.tiles_m * g0.tiles_n, n1 = q1.batches * g1.tiles_m * g1.tiles_n;
   const bool whole0 = whole_tiles<BM, BN, BK, A_K, B_K>(g0), whole1 = whole_tiles<BM, BN, BK, A_K, B_K>(g1);
-  // Only one of them whole and the chip full of either: each on its own kernel (gradients of 8192 and 3072 features, 4090 tokens, the latter's padded: 74 us together, 46 + 20 so)
-  if (whole0 != whole1 && n0 * s0 + n1 * s1 > 2 * kCUs) {
+  // Only one of them whole and the chip full of either, on the largest tile: each on its own kernel (gradients of 8192 and 3072 features, 4090 tokens, the latter's padded: 74 us together, 46 + 20 so).
+  // Not otherwise, the second launch costs more: halves of the backward, together / apart, 144 and 3136 features, b = 32, 1792 tokens 11.5 / 15.3 us; over 300 of them on smaller tiles 4 % more apart, on the
+  // largest with a side of 128 to 256 workgroups 1.3 % more, with more on both sides 1 % less (14 % at best).
+  if (BM == 128 && whole0 != whole1 && n0 * s0 > kCUs && n1 * s1 > kCUs) {
     launch_shape<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K>(g0, e0, q0.batches, q0.M, q0.N, q0.K, s0, st);
     launch_shape<T, BM, BN, BK, WGM, WGN, WAVES, A_K, B_K>(g1, e1, q1.batches, q1.M, q1.N, q1.K, s1, st);
     return;

@@ -38,6 +38,7 @@ pytestmark = pytest.mark.gpu
     (256, 384, 512, 128, 2),    # every tile and stage whole, and all but the last: the block gradients of 520 tokens
     (256, 384, 520, 128, 2),
     # other tiles and splits that the rule gives
+    (1032, 1024, 8704, 128, 1), # block gradients on 128 x 128 that fill the chip, of which one side's tiles are whole: each side on its own kernel
     (200, 776, 1001, 40, 1),    # fp32 forward: 64 x 64 with sixteen waves ...
     (1000, 632, 200, 40, 1),    # ... in 6 ranges
     (992, 632, 200, 40, 1),     # a contraction of 16 more takes slices
